@@ -167,7 +167,7 @@ void nm_tables_destroy(nm_tables* t);
  * other shape is computed by a slower loader with identical results.
  * Debug switches (environment, read once per process; results never change, only the kernel that
  * computes them): NM_GEMM_GENERIC=1 sends every shape to the generic kernel; NM_GEMM_CFG=
- * big|wide|split|small|mid3|mid2|oldbig forces a tile configuration where its requirements hold;
+ * big|wide|split|small|mid3|mid2|oldbig|direct0..3 forces a tile configuration where its requirements hold;
  * NM_ATTN_UNFUSED=1 keeps nm_encoder_layer's attention on the three separate kernels.
  * --------------------------------------------------------------------------------------------- */
 typedef struct {

@@ -9,10 +9,11 @@
 // eight wavefronts owns a BM x BN tile of the output, the k-loop streams 64- or 128-byte slices of
 // both operands through a ring of LDS stages, and each wavefront issues 32x32x32 int8 MFMAs on its
 // WM x WN sub-tile with int32 accumulators that never leave registers until the epilogue.
-// Two kernels: gemm_stream_kernel (aligned operands, K a multiple of 64: operands go global -> LDS
+// Here: gemm_stream_kernel (aligned operands, K a multiple of 64: operands go global -> LDS
 // directly; also gathers the rows of a convolution's patch matrix on the fly) in several tile
-// configurations chosen by launch_gemm, and gemm_pwl_kernel (any shape and alignment, W as [N,K]
-// or [K,N], operands through registers).
+// configurations, and gemm_pwl_kernel (any shape and alignment, W as [N,K] or [K,N], operands through
+// registers); large plain products take the tile kernel (nm_gemm_tile.h), small outputs and unaligned
+// operands the small-tile kernel (nm_gemm_direct.hip).  launch_gemm chooses.
 //
 // Operand roles: the MFMA's first operand supplies the rows of its 32x32 result and the second
 // the columns.  W rows (output columns n) go first and A rows (output rows m) second, so a lane
@@ -31,18 +32,14 @@
 
 namespace nm {
 
-// A line of zeros in device memory: the source of operand bytes that fall into a convolution's
-// padding (the direct global -> LDS loads cannot substitute a value, only an address).
-__device__ __attribute__((aligned(256))) int8_t g_zero_line[256];
-
 // Debug switch: NM_GEMM_GENERIC=1 in the environment sends every shape to the generic kernel.
 static bool force_generic()
 {
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig forces that
-// tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
+// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-3> forces
+// that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
 // 256x192 configuration, which the tile kernel has replaced).
 static int forced_cfg()
 {
@@ -50,6 +47,7 @@ static int forced_cfg()
         const char* e = getenv("NM_GEMM_CFG");
         if (!e) return -1;
         static const char* const names[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
+        if (!strncmp(e, "direct", 6)) return 10 + atoi(e + 6);
         for (int i = 0; i < 7; ++i)
             if (!strcmp(e, names[i])) return i;
         return -1;
@@ -79,124 +77,6 @@ __device__ __forceinline__ v4i load_chunk(const int8_t* __restrict__ X, long ld,
         }
     }
     return v;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Epilogue shared by both kernels.  A lane holds, for one output row m, four consecutive columns
-// nb .. nb+3 (one group of four accumulator registers).
-// ---------------------------------------------------------------------------------------------
-// Epilogue specialisations: the generic one reads every option at run time; the others fix the
-// set of outputs and options the encoder layer uses, which removes dead code from the unrolled
-// epilogue (it is instantiated once per accumulator group).
-struct Epi4 {
-    float y[4];
-    int q[4];
-    int s[4];
-};
-
-// Per-column parameters of four consecutive columns, loaded once and reused for every row.
-struct Col4 {
-    float scale[4], bias[4], inv[4];
-};
-
-__device__ __forceinline__ void load4(const float* __restrict__ v, int nb, int N, bool vec, float (&out)[4])
-{
-    if (vec && nb + 3 < N) {
-        const v4f t = *reinterpret_cast<const v4f*>(v + nb);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = t[e];
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (nb + e < N) out[e] = v[nb + e];
-    }
-}
-
-template <int kEpi>
-__device__ __forceinline__ void load_cols(const GemmParams& p, int nb, Col4& c)
-{
-    const float alpha = p.alpha, ois = p.out_inv_scale;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { c.scale[e] = alpha; c.bias[e] = 0.0f; c.inv[e] = ois; }
-    if (kEpi == EPI_ACC) return;
-    if (p.bias) load4(p.bias, nb, p.N, p.vec_cols, c.bias);
-    if (p.alpha_vec) load4(p.alpha_vec, nb, p.N, p.vec_cols, c.scale);
-    if (kEpi == EPI_F32_RESID) return;
-    if (kEpi == EPI_GENERIC && p.out_inv_scale_vec) {
-        load4(p.out_inv_scale_vec, nb, p.N, p.vec_cols, c.inv);
-    } else if (p.split_cols > 0) {
-        const float i0 = p.inv3[0], i1 = p.inv3[1], i2 = p.inv3[2];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c.inv[e] = nb + e >= 2 * p.split_cols ? i2 : (nb + e >= p.split_cols ? i1 : i0);
-    }
-}
-
-// Residual codes of four consecutive columns of one row.
-__device__ __forceinline__ void load_resid4(const GemmParams& p, long rowoff, int nb, bool vec, int (&r4)[4])
-{
-    if (vec) {
-        const unsigned w = *reinterpret_cast<const unsigned*>(p.resid + rowoff + nb);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r4[e] = (int)(int8_t)(w >> (8 * e));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r4[e] = nb + e < p.N ? (int)p.resid[rowoff + nb + e] : 0;
-    }
-}
-
-// The arithmetic of the epilogue for four columns of one row (no global memory access).
-// kTwoSeg: the table has two segments and is evaluated with a compare (specialised table epilogues)
-template <int kEpi, bool kTwoSeg = false>
-__device__ __forceinline__ void epi_math(const GemmParams& p, const float2* s_kb, const int (&a4)[4],
-                                         const Col4& c, const int (&r4)[4], Epi4& o)
-{
-    const bool use_resid = kEpi == EPI_GENERIC ? p.resid != nullptr : (kEpi == EPI_F32_RESID || kEpi == EPI_Q_TABLE_RESID);
-    const bool use_table = kEpi == EPI_GENERIC ? p.has_table != 0 : (kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID);
-    const bool need_q = kEpi == EPI_GENERIC ? p.out_q != nullptr : (kEpi == EPI_Q || kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { o.y[e] = 0.0f; o.q[e] = 0; o.s[e] = 0; }
-    if (kEpi == EPI_ACC) return;
-    const float rs = p.resid_scale;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float v = __builtin_fmaf((float)a4[e], c.scale[e], c.bias[e]);
-        if (use_resid) v = __builtin_fmaf((float)r4[e], rs, v);
-        if (use_table) {
-            if (kTwoSeg) v = pwl_eval_two_segments(v, p.table);
-            else if (kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID) v = pwl_eval_noclamp(v, p.table, s_kb, o.s[e]);
-            else if (p.table.cellmap) v = pwl_eval_two_level(v, p.table, s_kb, o.s[e]);  // merged table, two steps
-            else v = pwl_eval(v, p.table, s_kb, o.s[e]);
-        }
-        o.y[e] = v;
-        if (need_q) o.q[e] = requant(v, c.inv[e]);
-    }
-}
-
-template <int kEpi>
-__device__ __forceinline__ void epi_store(const GemmParams& p, long rowoff, int nb,
-                                          const int (&a4)[4], const Epi4& o, bool vec, bool skip_q)
-{
-    const bool st_q = (kEpi == EPI_GENERIC ? p.out_q != nullptr : (kEpi == EPI_Q || kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID)) && !skip_q;
-    const bool st_f = kEpi == EPI_GENERIC ? p.out_f32 != nullptr : kEpi == EPI_F32_RESID;
-    const bool st_a = kEpi == EPI_GENERIC ? p.out_acc != nullptr : kEpi == EPI_ACC;
-    const bool st_s = kEpi == EPI_GENERIC && p.dbg_seg && p.has_table;
-    if (vec) {
-        if (st_q) *reinterpret_cast<unsigned*>(p.out_q + rowoff + nb) = pack4(o.q[0], o.q[1], o.q[2], o.q[3]);
-        if (st_f) *reinterpret_cast<v4f*>(p.out_f32 + rowoff + nb) = v4f{o.y[0], o.y[1], o.y[2], o.y[3]};
-        if (st_a) *reinterpret_cast<v4i*>(p.out_acc + rowoff + nb) = v4i{a4[0], a4[1], a4[2], a4[3]};
-        if (st_s)
-            *reinterpret_cast<uint2*>(p.dbg_seg + rowoff + nb) =
-                make_uint2((unsigned)o.s[0] | ((unsigned)o.s[1] << 16), (unsigned)o.s[2] | ((unsigned)o.s[3] << 16));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (nb + e < p.N) {
-                if (st_q) p.out_q[rowoff + nb + e] = (int8_t)o.q[e];
-                if (st_f) p.out_f32[rowoff + nb + e] = o.y[e];
-                if (st_a) p.out_acc[rowoff + nb + e] = a4[e];
-                if (st_s) p.dbg_seg[rowoff + nb + e] = (uint16_t)o.s[e];
-            }
-    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -910,22 +790,12 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         else if (f == 4) cfg = CFG_MID3;
         else if (f == 5) cfg = CFG_MID2;
     }
-    if (g.conv) {
-        // gathered A operand: streaming kernel only (the caller has checked Cin % 64 == 0, 16-byte
-        // aligned image and weights); one problem, no batching
-        if (!w_al || !aligned(g.A, 16) || g.cCin % 64 != 0 || g.K % (g.cCin * g.cKw) != 0)
-            return fail(NM_ERR_UNSUPPORTED, "conv gemm: operands not aligned for the gathered loader");
-        if (cfg == CFG_NARROW) rc = launch_stream_conv<256, 64, 4, 1, 1, 64, 2>(p, epi, table_bytes, stream);
-        else if (cfg == CFG_WIDE) rc = launch_stream_conv<256, 128, 2, 2, 1, 64, 2>(p, epi, table_bytes, stream);
-        else if (cfg == CFG_MID2) rc = launch_stream_conv<128, 128, 2, 2, 1, 64, 2>(p, epi, table_bytes, stream);
-        else if (cfg == CFG_SPLIT) rc = launch_stream_conv<128, 128, 2, 2, 2, 128, 3>(p, epi, table_bytes, stream);
-        else if (cfg == CFG_SMALL) rc = launch_stream_conv<64, 128, 1, 2, 2, 128, 3>(p, epi, table_bytes, stream);
-        else rc = launch_stream_conv<128, 128, 2, 2, 1, 64, 3>(p, epi, table_bytes, stream);
-        if (rc) return rc;
-        return check_hip(hipGetLastError(), "conv gemm launch");
-    }
-    const bool stream_ok = al && !g.w_is_kn && g.K % 64 == 0 && !force_generic();
-    // the tile kernel: plain matrix products with the encoder layer's epilogues
+    // a gathered A operand is read 16 bytes at a time by every kernel that takes one (the caller has
+    // checked Cin % 64 == 0, 16-byte aligned image and weights)
+    if (g.conv && (!w_al || !aligned(g.A, 16) || g.cCin % 64 != 0 || g.K % (g.cCin * g.cKw) != 0))
+        return fail(NM_ERR_UNSUPPORTED, "conv gemm: operands not aligned for the gathered loader");
+    const bool stream_ok = al && !g.conv && !g.w_is_kn && g.K % 64 == 0 && !force_generic();
+    // The tile kernel: plain matrix products with the encoder layer's epilogues;
     // int8 output through a merged table kept in two levels: the tile kernel has an epilogue for it
     // (elsewhere the generic one looks it up)
     const bool two_level_q = g.has_table && g.table.cellmap && !g.table.clamp_input && g.out_q && !g.out_f32 &&
@@ -936,6 +806,35 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const bool tile_ok = stream_ok && tile_epi && batches == 1 && g.K % 128 == 0 && g.K / 128 >= 3 && !g.alpha_vec &&
                          g.N % 16 == 0 && g.split_cols % 4 == 0 && (int64_t)g.M * g.lda < (1LL << 32) &&
                          (int64_t)g.N * g.ldw < (1LL << 32) && table_bytes <= 40 * 1024;
+    // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
+    // chosen when the output is too small for the larger tiles to occupy the chip: the tile kernel needs
+    // 96 tiles of 128x128 (and is not at its best with three k-slices), the streaming kernel's tiles
+    // about a million outputs, more when the contraction is short and a large tile is mostly prologue and
+    // epilogue; and for operands the other loaders do not read 16 bytes at a time (4096x1000x1000:
+    // 27 us against the generic kernel's 106).
+    const int64_t a_extent = g.conv ? (int64_t)(g.M / (g.cHo * g.cWo)) * g.cH * g.cW * g.cCin : (int64_t)(g.M - 1) * g.lda + g.K;
+    const bool direct_ok = !force_generic() && !g.w_is_kn && a_extent < (1LL << 31) && (int64_t)(g.N - 1) * g.ldw + g.K < (1LL << 31);
+    const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
+                               g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
+    const int64_t outputs = (int64_t)g.M * g.N * batches;
+    const int64_t direct_below = tile_ok ? (g.K <= 384 ? 2450000 : 128 * 128 * 96) : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
+    const bool direct = direct_ok && (forced_cfg() >= 10 || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
+    if (direct) {
+        rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced_cfg() - 10 >= 0 ? forced_cfg() - 10 : -1, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "gemm launch");
+    }
+    if (g.conv) {
+        // gathered A operand: one problem, no batching
+        if (cfg == CFG_NARROW) rc = launch_stream_conv<256, 64, 4, 1, 1, 64, 2>(p, epi, table_bytes, stream);
+        else if (cfg == CFG_WIDE) rc = launch_stream_conv<256, 128, 2, 2, 1, 64, 2>(p, epi, table_bytes, stream);
+        else if (cfg == CFG_MID2) rc = launch_stream_conv<128, 128, 2, 2, 1, 64, 2>(p, epi, table_bytes, stream);
+        else if (cfg == CFG_SPLIT) rc = launch_stream_conv<128, 128, 2, 2, 2, 128, 3>(p, epi, table_bytes, stream);
+        else if (cfg == CFG_SMALL) rc = launch_stream_conv<64, 128, 1, 2, 2, 128, 3>(p, epi, table_bytes, stream);
+        else rc = launch_stream_conv<128, 128, 2, 2, 1, 64, 3>(p, epi, table_bytes, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "conv gemm launch");
+    }
     // Which tile: the one whose workgroups fill whole rounds of the 256 CUs best, weighted by how much
     // operand traffic per matrix instruction the tile shape costs (weights from timings of the
     // encoder shapes: 256x192 1.0, 256x128 0.92, 128x192 0.85, 128x128 0.75) and by the share of the

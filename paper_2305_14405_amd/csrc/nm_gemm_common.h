@@ -11,6 +11,10 @@ namespace nm {
 constexpr int kGemmThreads = 256;
 constexpr int kBK = 64;  // bytes of k per pipeline stage
 
+// A line of zeros in device memory: the source of operand bytes that fall into a convolution's
+// padding (the direct global -> LDS loads cannot substitute a value, only an address).  One per translation unit.
+static __device__ __attribute__((aligned(256))) int8_t g_zero_line[256];
+
 struct GemmParams {
     int M, N, K;
     const int8_t* A; long lda;
@@ -50,7 +54,12 @@ struct GemmParams {
     // convolution in matrix form (streaming kernel with kConv): row m of A is the output position
     // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
+    int batched;  // small-tile kernel: more than one problem (grid.y)
 };
+
+// The small-tile kernel (nm_gemm_direct.hip).  align: alignment of operand rows and chunks in bytes (16, 4 or
+// 1); forced: tile configuration 0 .. 3, or -1 for the rule.
+int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s);
 
 // XOR swizzle of the 16-byte chunk index inside a 64-byte LDS row: rows that fall into the same
 // bank window get different chunk positions, for both a 128-byte and a 256-byte wide LDS port.
@@ -77,6 +86,124 @@ template <int BK>
 __device__ __forceinline__ int lds_off_bk(int row, int chunk)
 {
     return row * BK + ((chunk ^ swz_bk<BK>(row)) << 4);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Epilogue shared by the kernels of any option.  A lane holds, for one output row m, four consecutive columns
+// nb .. nb+3 (one group of four accumulator registers).
+// ---------------------------------------------------------------------------------------------
+// Epilogue specialisations: the generic one reads every option at run time; the others fix the
+// set of outputs and options the encoder layer uses, which removes dead code from the unrolled
+// epilogue (it is instantiated once per accumulator group).
+struct Epi4 {
+    float y[4];
+    int q[4];
+    int s[4];
+};
+
+// Per-column parameters of four consecutive columns, loaded once and reused for every row.
+struct Col4 {
+    float scale[4], bias[4], inv[4];
+};
+
+__device__ __forceinline__ void load4(const float* __restrict__ v, int nb, int N, bool vec, float (&out)[4])
+{
+    if (vec && nb + 3 < N) {
+        const v4f t = *reinterpret_cast<const v4f*>(v + nb);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = t[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (nb + e < N) out[e] = v[nb + e];
+    }
+}
+
+template <int kEpi>
+__device__ __forceinline__ void load_cols(const GemmParams& p, int nb, Col4& c)
+{
+    const float alpha = p.alpha, ois = p.out_inv_scale;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { c.scale[e] = alpha; c.bias[e] = 0.0f; c.inv[e] = ois; }
+    if (kEpi == EPI_ACC) return;
+    if (p.bias) load4(p.bias, nb, p.N, p.vec_cols, c.bias);
+    if (p.alpha_vec) load4(p.alpha_vec, nb, p.N, p.vec_cols, c.scale);
+    if (kEpi == EPI_F32_RESID) return;
+    if (kEpi == EPI_GENERIC && p.out_inv_scale_vec) {
+        load4(p.out_inv_scale_vec, nb, p.N, p.vec_cols, c.inv);
+    } else if (p.split_cols > 0) {
+        const float i0 = p.inv3[0], i1 = p.inv3[1], i2 = p.inv3[2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c.inv[e] = nb + e >= 2 * p.split_cols ? i2 : (nb + e >= p.split_cols ? i1 : i0);
+    }
+}
+
+// Residual codes of four consecutive columns of one row.
+__device__ __forceinline__ void load_resid4(const GemmParams& p, long rowoff, int nb, bool vec, int (&r4)[4])
+{
+    if (vec) {
+        const unsigned w = *reinterpret_cast<const unsigned*>(p.resid + rowoff + nb);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r4[e] = (int)(int8_t)(w >> (8 * e));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r4[e] = nb + e < p.N ? (int)p.resid[rowoff + nb + e] : 0;
+    }
+}
+
+// The arithmetic of the epilogue for four columns of one row (no global memory access).
+// kTwoSeg: the table has two segments and is evaluated with a compare (specialised table epilogues)
+template <int kEpi, bool kTwoSeg = false>
+__device__ __forceinline__ void epi_math(const GemmParams& p, const float2* s_kb, const int (&a4)[4],
+                                         const Col4& c, const int (&r4)[4], Epi4& o)
+{
+    const bool use_resid = kEpi == EPI_GENERIC ? p.resid != nullptr : (kEpi == EPI_F32_RESID || kEpi == EPI_Q_TABLE_RESID);
+    const bool use_table = kEpi == EPI_GENERIC ? p.has_table != 0 : (kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID);
+    const bool need_q = kEpi == EPI_GENERIC ? p.out_q != nullptr : (kEpi == EPI_Q || kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { o.y[e] = 0.0f; o.q[e] = 0; o.s[e] = 0; }
+    if (kEpi == EPI_ACC) return;
+    const float rs = p.resid_scale;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float v = __builtin_fmaf((float)a4[e], c.scale[e], c.bias[e]);
+        if (use_resid) v = __builtin_fmaf((float)r4[e], rs, v);
+        if (use_table) {
+            if (kTwoSeg) v = pwl_eval_two_segments(v, p.table);
+            else if (kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID) v = pwl_eval_noclamp(v, p.table, s_kb, o.s[e]);
+            else if (p.table.cellmap) v = pwl_eval_two_level(v, p.table, s_kb, o.s[e]);  // merged table, two steps
+            else v = pwl_eval(v, p.table, s_kb, o.s[e]);
+        }
+        o.y[e] = v;
+        if (need_q) o.q[e] = requant(v, c.inv[e]);
+    }
+}
+
+template <int kEpi>
+__device__ __forceinline__ void epi_store(const GemmParams& p, long rowoff, int nb,
+                                          const int (&a4)[4], const Epi4& o, bool vec, bool skip_q)
+{
+    const bool st_q = (kEpi == EPI_GENERIC ? p.out_q != nullptr : (kEpi == EPI_Q || kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID)) && !skip_q;
+    const bool st_f = kEpi == EPI_GENERIC ? p.out_f32 != nullptr : kEpi == EPI_F32_RESID;
+    const bool st_a = kEpi == EPI_GENERIC ? p.out_acc != nullptr : kEpi == EPI_ACC;
+    const bool st_s = kEpi == EPI_GENERIC && p.dbg_seg && p.has_table;
+    if (vec) {
+        if (st_q) *reinterpret_cast<unsigned*>(p.out_q + rowoff + nb) = pack4(o.q[0], o.q[1], o.q[2], o.q[3]);
+        if (st_f) *reinterpret_cast<v4f*>(p.out_f32 + rowoff + nb) = v4f{o.y[0], o.y[1], o.y[2], o.y[3]};
+        if (st_a) *reinterpret_cast<v4i*>(p.out_acc + rowoff + nb) = v4i{a4[0], a4[1], a4[2], a4[3]};
+        if (st_s)
+            *reinterpret_cast<uint2*>(p.dbg_seg + rowoff + nb) =
+                make_uint2((unsigned)o.s[0] | ((unsigned)o.s[1] << 16), (unsigned)o.s[2] | ((unsigned)o.s[3] << 16));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (nb + e < p.N) {
+                if (st_q) p.out_q[rowoff + nb + e] = (int8_t)o.q[e];
+                if (st_f) p.out_f32[rowoff + nb + e] = o.y[e];
+                if (st_a) p.out_acc[rowoff + nb + e] = a4[e];
+                if (st_s) p.dbg_seg[rowoff + nb + e] = (uint16_t)o.s[e];
+            }
+    }
 }
 
 }  // namespace nm

@@ -1,0 +1,430 @@
+// The small-tile int8 GEMM kernel: matrix products whose output has too few large tiles to occupy
+// the chip, and operands of any alignment (paper Section 3.1: fully connected layers and convolutions
+// as matrix products; the epilogue is that of every other GEMM kernel here).
+//
+// What bounds such a product is latency, not a rate: with the LDS-ring kernels 128 x 768 x 3072 is 12
+// workgroups that each wait 24 times for a k-slice, and their prologue and epilogue are as long as
+// the loop.  Here a workgroup owns a small tile (16 x 32 .. 32 x 64 outputs) and its four or eight
+// wavefronts divide K between them.  Each streams its own slices (128 bytes of every A and W row of the
+// tile) through an LDS ring of its own, so the loop has no workgroup barrier and most of what a CU needs is
+// in flight at once: rows of 128 bytes keep the loads at the full 64 bytes per clock and CU (loading
+// fragments straight into registers, 16 rows of 64 bytes per instruction, reached 8).  The wavefronts'
+// int32 partial tiles meet in LDS (exact in any order) and every thread finishes groups of four
+// neighbouring outputs; the epilogue's vectors, residual and table are requested before the slices and
+// not waited for until then, and all kernel arguments are fetched in one step (together 0.4 .. 1.5 us of
+// a launch).  Measured, us before -> after, weights from HBM: 128x768x3072 13.9 -> 5.3, 128x3072x768 8.6 ->
+// 5.0, 64x128x128 6.4 -> 2.9 (an empty launch is 1.6), 847x768x3072 15.0 -> 10.9, 3x3 convolution of
+// 512 channels at 7x7 28.9 -> 6.7, 4096x1000x1000 (rows aligned to 8 bytes) 106 -> 27.
+//
+// Operands that are not 16-byte aligned come through registers and buffer descriptors: words past the end
+// of the buffer read as zero, bytes past K are cleared.
+#include "nm_gemm_common.h"
+
+namespace nm {
+
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr unsigned kOutOfRange = 0xc0000000u;  // past the end of every buffer (their extents are below 2^31)
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
+}
+
+__device__ __forceinline__ v4i buf16(rsrc_t r, unsigned off)
+{
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+    return v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+}
+__device__ __forceinline__ unsigned buf4(rsrc_t r, unsigned off)
+{
+    return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+}
+
+// kAl: bytes every row start and every 16-byte chunk is aligned to (4: whole words, 1: any; the latter reads
+// the words around the chunk and shifts).
+template <int kAl>
+__device__ __forceinline__ v4i load_unit(rsrc_t r, unsigned off)
+{
+    if (kAl == 4) return buf16(r, off);
+    const unsigned base = off & ~3u, sh = off & 3u;
+    const v4i w = buf16(r, base);
+    const unsigned w4 = buf4(r, base + 16);
+    v4i o;
+    o[0] = (int)__builtin_amdgcn_alignbyte((unsigned)w[1], (unsigned)w[0], sh);
+    o[1] = (int)__builtin_amdgcn_alignbyte((unsigned)w[2], (unsigned)w[1], sh);
+    o[2] = (int)__builtin_amdgcn_alignbyte((unsigned)w[3], (unsigned)w[2], sh);
+    o[3] = (int)__builtin_amdgcn_alignbyte(w4, (unsigned)w[3], sh);
+    return o;
+}
+// The same for the last, partly filled k-step: word by word (each is inside the buffer or reads as
+// zero), bytes at and past `left` (the number of valid ones, possibly <= 0) cleared.
+template <int kAl>
+__device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
+{
+    const unsigned base = off & ~3u, sh = kAl == 4 ? 0u : off & 3u;
+    unsigned w[5];
+#pragma unroll
+    for (int t = 0; t < 5; ++t) w[t] = buf4(r, left > 0 ? base + 4 * t : kOutOfRange);
+    v4i o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const unsigned v = kAl == 4 ? w[t] : __builtin_amdgcn_alignbyte(w[t + 1], w[t], sh);
+        const int nb = left - 4 * t;  // valid bytes of this word
+        o[t] = nb >= 4 ? (int)v : nb <= 0 ? 0 : (int)(v & ((1u << (8 * nb)) - 1u));
+    }
+    return o;
+}
+
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32_a1 __attribute__((aligned(1)));
+
+// KW wavefronts divide K in slices of 128 bytes; a wavefront has up to D slices in flight.
+// kAl: 16: operands go global -> LDS directly; 4, 1: alignment of the rows in bytes, through registers.
+template <int BM, int BN, int KW, int D, int kAl, bool kConv>
+__global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
+{
+    constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
+    constexpr int NA = BM / 8, NI = (BM + BN) / 8;   // 1 KB pieces (8 rows) of a slice; the first NA are A rows
+    constexpr int SLICE = (BM + BN) * 128;
+    constexpr int G4 = BN / 4, NGRP = BM * G4;       // groups of four outputs
+    constexpr int GPT = (NGRP + NT - 1) / NT;        // ... per thread
+    static_assert(NT % G4 == 0, "a thread's groups share their columns");
+    static_assert(NGRP % NT == 0 || NGRP < NT, "groups split evenly");
+    static_assert(BM * BN * 4 <= SLICE, "a wavefront's partial tile fits one slice");
+    // 16-byte column slot of a partial tile's row, spread over the banks
+    constexpr auto pslot = [](int row, int slot) { return slot ^ (BN == 64 ? row & 15 : BN == 32 ? (row >> 1) & 7 : (row >> 2) & 3); };
+    static_assert(!kConv || kAl == 16, "gathered operand: aligned");
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];   // [wavefronts with slices][slots][BM + BN rows of 128 bytes]
+
+    // One wait for the kernel arguments the whole kernel uses (left alone, the compiler fetches them in
+    // half a dozen dependent steps, each a memory round trip).
+    asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.bias), "s"(p.alpha_vec), "s"(p.resid), "s"(p.table.kb), "s"(p.M), "s"(p.N), "s"(p.K),
+                 "s"(p.lda), "s"(p.ldw), "s"(p.ldo), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.has_table), "s"(p.vec_out),
+                 "s"(p.batched), "s"(p.table.nseg), "s"(p.table.cellmap), "s"(p.alpha), "s"(p.out_q), "s"(p.out_f32));
+
+    // only as many rings and slots as this K needs (short contractions: several workgroups per CU)
+    const int nk = (p.K + 127) >> 7;
+    const int rings = min(KW, nk), slots = min(D, (nk + KW - 1) / KW);
+    const int ring_bytes = slots * SLICE;
+    float2* s_kb = reinterpret_cast<float2*>(smem + rings * ring_bytes);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 15, fq = lane >> 4;
+
+    // Workgroup i runs on XCD i % 8: an XCD gets a contiguous eighth of the tiles, rows of tiles
+    // innermost, so that a panel of W is fetched into one L2.
+    const int ntiles = p.tiles_m * p.tiles_n, share = (ntiles + 7) >> 3;
+    const int id = (blockIdx.x % 8) * share + blockIdx.x / 8;
+    if (id >= ntiles) return;
+    const int m0 = (id % p.tiles_m) * BM, n0 = (id / p.tiles_m) * BN;
+    const int8_t* A = p.A;
+    const int8_t* W = p.W;
+    long obase = 0;
+    if (p.batched) {
+        const int outer = blockIdx.y / p.inner_count, inner = blockIdx.y % p.inner_count;
+        A += outer * p.a_outer + inner * p.a_inner;
+        W += outer * p.w_outer + inner * p.w_inner;
+        obase = outer * p.o_outer + inner * p.o_inner;
+    }
+
+    // What the epilogue needs is requested first and parked in registers, straight-line, so that
+    // nothing here waits: the waits for the operand slices below count younger loads only.
+    const int c4 = tid % G4, row0 = tid / G4;
+    const int nb = n0 + 4 * c4;
+    const bool n4 = (p.N & 3) == 0;      // a group of four columns is all in or all out
+    v4f bias_r = {0.0f, 0.0f, 0.0f, 0.0f}, scale_r = {p.alpha, p.alpha, p.alpha, p.alpha};
+    unsigned res_r[GPT];
+    if (n4) {
+        const int ncl = min(nb, p.N - 4);
+        if (p.bias) bias_r = *reinterpret_cast<const v4f_a4*>(p.bias + ncl);
+        if (p.alpha_vec) scale_r = *reinterpret_cast<const v4f_a4*>(p.alpha_vec + ncl);
+        if (p.resid) {
+#pragma unroll
+            for (int t = 0; t < GPT; ++t)
+                res_r[t] = *reinterpret_cast<const u32_a1*>(p.resid + obase + (long)min(m0 + row0 + t * (NT / G4), p.M - 1) * p.ldo + ncl);
+        }
+    }
+    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry per thread; a larger table is staged late
+    const bool plain_table = p.has_table && !p.table.cellmap;
+    if (plain_table) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+
+    // source of the lane's 16 bytes in every piece: row l / 8 of the piece, chunk l % 8 (swizzled);
+    // rows past the edge are clamped to the last one (they only feed outputs that are never stored)
+    const int lrow = lane >> 3;
+    const int chunk0 = (lane & 7) ^ (lane >> 4);     // pieces 0, 2, ..; the others: chunk ^ 4
+    unsigned voff[NI];
+    int ch[kConv ? NA : 1], cw[kConv ? NA : 1];
+    const unsigned sha = kAl == 1 ? (unsigned)((uintptr_t)A & 3) : 0u, shw = kAl == 1 ? (unsigned)((uintptr_t)W & 3) : 0u;
+    const unsigned lda = (unsigned)p.lda, ldw = (unsigned)p.ldw;
+    const unsigned a_row0 = (unsigned)(m0 + lrow) * lda, a_last = (unsigned)(p.M - 1) * lda;
+    const unsigned w_row0 = (unsigned)(n0 + lrow) * ldw, w_last = (unsigned)(p.N - 1) * ldw;
+#pragma unroll
+    for (int b = 0; b < NI; ++b) {
+        const unsigned co = 16u * (unsigned)(chunk0 ^ ((b & 1) << 2));
+        if (b < NA) {
+            if (kConv) {
+                const int m = min(m0 + 8 * b + lrow, p.M - 1);
+                const int wo = m % p.cWo, t = m / p.cWo, ho = t % p.cHo, bi = t / p.cHo;
+                ch[b] = ho * p.cStride - p.cPad;
+                cw[b] = wo * p.cStride - p.cPad;
+                voff[b] = (unsigned)(bi * p.cH * p.cW * p.cCin) + (co & 63u);
+            } else {
+                voff[b] = min(a_row0 + 8u * b * lda, a_last) + co + sha;
+            }
+        } else {
+            voff[b] = min(w_row0 + 8u * (b - NA) * ldw, w_last) + co + shw;
+        }
+    }
+    const unsigned ring = (unsigned)(uintptr_t)smem + wave * ring_bytes;
+    int8_t* const ring_p = smem + wave * ring_bytes;
+
+    // this wavefront's slices
+    const int per = nk / KW, rem = nk % KW;
+    const int s0 = wave * per + min(wave, rem), cnt = per + (wave < rem ? 1 : 0);
+    const bool ragged = (p.K & 127) != 0;            // the last slice is partly filled
+    const int8_t* zero_src = g_zero_line + 16 * (lane & 7);
+
+    // ---- aligned operands: slice t of this wavefront goes straight to its ring slot ----
+    int ti = 0, tj = 0, tc = 0;   // kConv: tap and channel of the next half slice to load
+    if (kConv) {
+        const int tap = (s0 * 128) / p.cCin;
+        tc = s0 * 128 - tap * p.cCin;
+        ti = tap / p.cKw;
+        tj = tap - ti * p.cKw;
+    }
+    auto issue = [&](int t, int slot) {
+        const int k0 = 128 * (s0 + t);
+        const unsigned dst = ring + slot * SLICE;
+        const bool part = ragged && k0 + 128 > p.K;  // wave-uniform
+        if (kConv) {
+            int h2[2], w2[2], c2[2];
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                h2[hf] = ti; w2[hf] = tj; c2[hf] = tc;
+                tc += 64;
+                if (tc == p.cCin) { tc = 0; if (++tj == p.cKw) { tj = 0; ++ti; } }
+            }
+            // past the last tap the row is outside every image
+            if (part) h2[1] = 1 << 28;
+#pragma unroll
+            for (int b = 0; b < NA; ++b) {
+                const bool up = ((chunk0 ^ ((b & 1) << 2)) & 4) != 0;
+                const int hi = ch[b] + (up ? h2[1] : h2[0]), wi = cw[b] + (up ? w2[1] : w2[0]);
+                const bool in = (unsigned)hi < (unsigned)p.cH && (unsigned)wi < (unsigned)p.cW;
+                const unsigned off = voff[b] + (unsigned)((hi * p.cW + wi) * p.cCin + (up ? c2[1] : c2[0]));
+                dma16(in ? A + off : zero_src, dst + 1024 * b);
+            }
+        }
+        if (part) {
+#pragma unroll
+            for (int b = kConv ? NA : 0; b < NI; ++b)
+                dma16(k0 + 16 * (chunk0 ^ ((b & 1) << 2)) < p.K ? (b < NA ? A : W) + k0 + voff[b] : zero_src, dst + 1024 * b);
+        } else {
+#pragma unroll
+            for (int b = kConv ? NA : 0; b < NI; ++b) dma16s((b < NA ? A : W) + k0, voff[b], dst + 1024 * b);
+        }
+    };
+
+    v4i acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+    // fragment addresses: row fr of a 16-row block, chunk 4 * ks + fq
+    const int fsw = (fr >> 1) & 7;
+    auto compute = [&](const int8_t* st) {
+        v4i fa[2][TM], fw[2][TN];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int fo = fr * 128 + (((4 * ks + fq) ^ fsw) << 4);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fw[ks][j] = *reinterpret_cast<const v4i*>(st + BM * 128 + 2048 * j + fo);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[ks][i] = *reinterpret_cast<const v4i*>(st + 2048 * i + fo);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    };
+
+    if (kAl == 16) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < cnt) issue(d, d);
+        int slot = 0;
+        for (int t = 0; t < cnt; ++t) {
+            const int young = min(D - 1, cnt - 1 - t);   // younger slices in flight (wave-uniform)
+            if (D >= 4 && young >= 3) wait_vmcnt<3 * NI>();
+            else if (D >= 3 && young == 2) wait_vmcnt<2 * NI>();
+            else if (D >= 2 && young == 1) wait_vmcnt<NI>();
+            else wait_vmcnt<0>();
+            compute(ring_p + slot * SLICE);
+            if (t + D < cnt) {
+                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");   // the slot's fragments have been read
+                issue(t + D, slot);
+            }
+            slot = slot + 1 == slots ? 0 : slot + 1;
+        }
+    } else {
+        // ---- any alignment: through registers, the next slice requested before this one is used ----
+        const rsrc_t ra = make_rsrc(A - sha, (a_last + (unsigned)p.K + sha + 3) & ~3u);
+        const rsrc_t rw = make_rsrc(W - shw, (w_last + (unsigned)p.K + shw + 3) & ~3u);
+        v4i reg[NI];
+        auto fetch = [&](int t) {
+            const unsigned k0 = 128u * (unsigned)(s0 + t);
+            if (ragged && (int)k0 + 128 > p.K) {
+#pragma unroll
+                for (int b = 0; b < NI; ++b)
+                    reg[b] = load_tail<kAl>(b < NA ? ra : rw, voff[b] + k0, p.K - (int)k0 - 16 * (chunk0 ^ ((b & 1) << 2)));
+            } else {
+#pragma unroll
+                for (int b = 0; b < NI; ++b) reg[b] = load_unit<kAl>(b < NA ? ra : rw, voff[b] + k0);
+            }
+        };
+        if (cnt > 0) fetch(0);
+        for (int t = 0; t < cnt; ++t) {
+#pragma unroll
+            for (int b = 0; b < NI; ++b) *reinterpret_cast<v4i*>(ring_p + 1024 * b + 16 * lane) = reg[b];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (t + 1 < cnt) fetch(t + 1);
+            compute(ring_p);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+
+    // Partial tiles meet in LDS, each in its wavefront's own ring (whose fragments have all been read).
+    // Lane (fr, fq) holds row 16i + fr, columns 16j + 4fq .. +3.
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    if (cnt > 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                *reinterpret_cast<v4i*>(ring_p + (16 * i + fr) * (BN * 4) + 16 * pslot(16 * i + fr, 4 * j + fq)) = acc[i][j];
+    }
+    if (plain_table) {
+        if (tid < p.table.nseg) s_kb[tid] = kb_reg;
+        for (int e = tid + NT; e < p.table.nseg; e += NT) s_kb[e] = p.table.kb[e];
+    } else if (p.has_table) {
+        stage_table_two_level(s_kb, p.table);
+    }
+    __syncthreads();
+    if (NGRP < NT && row0 >= BM) return;
+    if (nb >= p.N) return;
+    auto partial_sum = [&](int row, int (&a4)[4]) {
+        const int8_t* at = smem + row * (BN * 4) + 16 * pslot(row, c4);
+        v4i s = *reinterpret_cast<const v4i*>(at);
+#pragma unroll
+        for (int w = 1; w < KW; ++w)
+            if (w < rings) s += *reinterpret_cast<const v4i*>(at + w * ring_bytes);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a4[e] = s[e];
+    };
+    Col4 c;
+    if (n4 && p.vec_out) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            c.bias[e] = bias_r[e];
+            c.scale[e] = scale_r[e];
+            c.inv[e] = p.out_inv_scale;
+        }
+        if (p.out_inv_scale_vec) {
+            const v4f iv = *reinterpret_cast<const v4f_a4*>(p.out_inv_scale_vec + nb);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c.inv[e] = iv[e];
+        } else if (p.split_cols > 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c.inv[e] = nb + e >= 2 * p.split_cols ? p.inv3[2] : nb + e >= p.split_cols ? p.inv3[1] : p.inv3[0];
+        }
+#pragma unroll
+        for (int t = 0; t < GPT; ++t) {
+            const int row = row0 + t * (NT / G4), m = m0 + row;
+            if (m >= p.M) break;
+            int a4[4], r4[4] = {0, 0, 0, 0};
+            partial_sum(row, a4);
+            if (p.resid) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r4[e] = (int)(int8_t)(res_r[t] >> (8 * e));
+            }
+            Epi4 o;
+            epi_math<EPI_GENERIC>(p, s_kb, a4, c, r4, o);
+            epi_store<EPI_GENERIC>(p, obase + (long)m * p.ldo, nb, a4, o, true, false);
+        }
+    } else {
+        load_cols<EPI_GENERIC>(p, nb, c);
+#pragma unroll 1
+        for (int t = 0; t < GPT; ++t) {
+            const int row = row0 + t * (NT / G4), m = m0 + row;
+            if (m >= p.M) break;
+            int a4[4], r4[4] = {0, 0, 0, 0};
+            partial_sum(row, a4);
+            if (p.resid) load_resid4(p, obase + (long)m * p.ldo, nb, false, r4);
+            Epi4 o;
+            epi_math<EPI_GENERIC>(p, s_kb, a4, c, r4, o);
+            epi_store<EPI_GENERIC>(p, obase + (long)m * p.ldo, nb, a4, o, false, false);
+        }
+    }
+}
+
+template <int BM, int BN, int KW, int D, int kAl, bool kConv>
+static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, hipStream_t s)
+{
+    auto kern = gemm_direct_kernel<BM, BN, KW, D, kAl, kConv>;
+    const int nk = (p.K + 127) / 128, need = (nk + KW - 1) / KW;
+    const size_t shmem = (size_t)(nk < KW ? nk : KW) * (need < D ? need : D) * (BM + BN) * 128 + table_bytes;
+    static std::once_flag once;  // one attribute call per instantiation
+    static int32_t once_rc = NM_OK;
+    std::call_once(once, [&] {
+        once_rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+                            "hipFuncSetAttribute(gemm_direct_kernel)");
+    });
+    if (once_rc) return once_rc;
+    p.tiles_m = (p.M + BM - 1) / BM;
+    p.tiles_n = (p.N + BN - 1) / BN;
+    p.batched = batches > 1;
+    const int grid = (p.tiles_m * p.tiles_n + 7) / 8 * 8;   // the kernel's eighths are (tiles + 7) / 8 each
+    hipLaunchKernelGGL(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, p);
+    return NM_OK;
+}
+
+template <int BM, int BN, int KW, int D>
+static int32_t launch_direct_c(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, hipStream_t s)
+{
+    if (conv) return launch_direct_t<BM, BN, KW, D, 16, true>(p, batches, table_bytes, s);
+    if (align >= 16) return launch_direct_t<BM, BN, KW, D, 16, false>(p, batches, table_bytes, s);
+    if (align >= 4) return launch_direct_t<BM, BN, KW, D, 4, false>(p, batches, table_bytes, s);
+    return launch_direct_t<BM, BN, KW, D, 1, false>(p, batches, table_bytes, s);
+}
+
+// Which tile: the smallest one whose workgroups still fit the chip about once; beyond that the one that
+// reads its operands least often, the sooner the longer the contraction.  (Timings of every
+// configuration over 125 products of the encoder at widths 256 .. 1024 and 64 .. 3200 rows, and 51
+// convolutions; us for 16x32 / 32x32 with eight wavefronts / 32x32 with four / 32x64: 128x768x3072
+// 5.3 / 5.9 / 5.5 / 9.0, 392x512x4608 11.5 / 7.6 / 8.8 / 12.9, 600x768x768 6.8 / 5.3 / 5.0 / 5.9, 1200x768x3072
+// 28.6 / 19.9 / 15.0 / 12.3, 1600x1536x384 17.0 / 12.6 / 9.0 / 10.0.)
+int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s)
+{
+    const long t32 = (long)((p.M + 31) / 32) * ((p.N + 31) / 32) * batches;
+    const long wide_from = p.K >= 576 ? 640 : p.K >= 512 ? 1100 : 1L << 40;
+    int cfg = t32 <= 128 ? 0 : t32 <= 256 && p.K >= 2048 ? 1 : t32 <= wide_from ? 2 : 3;
+    if (forced >= 0) cfg = forced;
+    if (cfg == 0 && table_bytes > 16 * 1024) cfg = 1;   // 144 KB of slices: LDS holds a table of 2048 segments beside them
+    switch (cfg) {
+    case 0: return launch_direct_c<16, 32, 8, 3>(p, align, conv, batches, table_bytes, s);
+    case 1: return launch_direct_c<32, 32, 8, 2>(p, align, conv, batches, table_bytes, s);
+    case 2: return launch_direct_c<32, 32, 4, 2>(p, align, conv, batches, table_bytes, s);
+    default: return launch_direct_c<32, 64, 4, 1>(p, align, conv, batches, table_bytes, s);
+    }
+}
+
+}  // namespace nm

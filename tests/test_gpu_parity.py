@@ -617,6 +617,41 @@ def test_gemm_tile_kernel_configurations(oracle, M, N, K, what):
     assert_f32_close(host(of), r2["y"], f"fp32 + residual: {what}")
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 4, 16), (17, 33, 144), (16, 32, 3072), (31, 30, 1001), (128, 96, 130), (64, 1000, 2048), (224, 640, 2112),
+    (225, 643, 2055), (500, 900, 320), (511, 902, 333), (1120, 960, 192), (1099, 990, 200), (1097, 991, 129), (5, 7, 65536)])
+def test_gemm_small_tile_kernel(oracle, M, N, K):
+    """The small-tile kernel in each of its tile configurations, with operands aligned to 16, 4 and 1
+    bytes, edges of tiles and of k-slices: every output with every option of the epilogue."""
+    ot, dt = both_tables(oracle, [("gelu", -8.0, 8.0, 128)])
+    d = W.gemm_inputs(M, N, K, seed=M + 3 * N + K, full_range=False)
+    alpha = float(np.float32(6.0 / (20 * 20 * np.sqrt(K))))
+    av = (d["alpha_vec"] * alpha).astype(np.float32)
+    r = oracle.gemm_pwl(d["A"], d["W"], bias=d["bias"], alpha_vec=av, resid=d["resid"], resid_scale=0.01, table=ot[0],
+                        out_inv_scale=25.0)
+    oq = torch.empty((M, N), dtype=torch.int8, device=DEV)
+    of = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    acc = torch.empty((M, N), dtype=torch.int32, device=DEV)
+    seg = torch.empty((M, N), dtype=torch.int16, device=DEV)
+    dA, dW, db = dev(d["A"]), dev(d["W"]), dev(d["bias"])
+    nm.nm_gemm_pwl(dA, dW, bias=db, alpha_vec=dev(av), resid=dev(d["resid"]), resid_scale=0.01, tables=dt, table_idx=0,
+                   out_inv_scale=25.0, out_q=oq, out_f32=of, out_acc=acc, dbg_seg=seg)
+    assert_exact(host(acc), r["acc"], "acc")
+    assert_exact(host(seg).view(np.uint16), r["seg"], "segments")
+    assert_exact(host(oq), r["q"], "int8")
+    assert_f32_close(host(of), r["y"], "fp32")
+    r1 = oracle.gemm_pwl(d["A"], d["W"], bias=d["bias"], alpha=alpha, out_inv_scale=40.0)
+    nm.nm_gemm_pwl(dA, dW, bias=db, alpha=alpha, out_inv_scale=40.0, out_q=oq)
+    assert_exact(host(oq), r1["q"], "int8 only")
+    # operands that start one byte off a word
+    if M * K < 1 << 22:
+        buf = torch.empty(M * K + 1, dtype=torch.int8, device=DEV)
+        off = buf[1:].view(M, K)
+        off.copy_(dA)
+        nm.nm_gemm_pwl(off, dW, out_acc=acc)
+        assert_exact(host(acc), r["acc"], "acc, A misaligned")
+
+
 def test_gemm_extreme_operands(oracle):
     """All-(-127) x all-(+127) at the largest K of the workloads: |acc| = K * 127^2 > 2^24."""
     M, N, K = 40, 72, 3072
