@@ -167,16 +167,34 @@ def _ptr(t):
     """Device (or host) address of a torch tensor / numpy array / None."""
     if t is None:
         return None
-    if hasattr(t, "data_ptr"):
-        assert t.is_contiguous(), "tensors passed to the C ABI must be contiguous"
-        return t.data_ptr()
-    return t.ctypes.data
+    try:
+        address = t.data_ptr()
+    except AttributeError:
+        return t.ctypes.data
+    assert t.is_contiguous(), "tensors passed to the C ABI must be contiguous"
+    return address
+
+
+_raw_stream = _device = None
+
+
+def _current_stream():
+    """Handle of torch's current stream, by the direct getter where this torch has it: 0.2 us instead of
+    the 2.9 us of building a Stream object, which is a third of a small call."""
+    global _raw_stream, _device
+    if _raw_stream is not None:
+        return _raw_stream(_device())
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream   # also initialises the runtime
+    get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if get is not None and dev is not None:
+        _raw_stream, _device = get, dev
+    return handle
 
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return getattr(stream, "cuda_stream", stream)
 
 
@@ -389,10 +407,7 @@ def nm_encoder_layer_noalloc(desc: LayerDesc, x, y_q, y_f32, stream=None):
 
 
 def _desc_array(descs):
-    arr = (LayerDesc * len(descs))()
-    for i, d in enumerate(descs):
-        C.memmove(C.byref(arr, i * C.sizeof(LayerDesc)), C.byref(d), C.sizeof(LayerDesc))
-    return arr
+    return (LayerDesc * len(descs))(*descs)
 
 
 def nm_encoder_stack_workspace(descs) -> int:
