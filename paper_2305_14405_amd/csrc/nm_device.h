@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "nm_internal.h"
 
 namespace nm {
@@ -23,6 +25,10 @@ __device__ __forceinline__ int seg_index(float x, float lo, float inv_w, int nse
     u = __builtin_amdgcn_fmed3f(u, 0.0f, (float)(nseg - 1));
     return (int)u;
 }
+
+// float -> unsigned, truncating and saturating (negative and NaN -> 0): what v_cvt_u32_f32, the instruction
+// behind the conversion of a value the compiler knows nothing about, does (checked for every float).
+__device__ __forceinline__ unsigned cvt_u32_sat(float x) { return (unsigned)x; }
 
 // y = k[s]*x + b[s] (one fma).  kb may point to LDS or to global memory.
 __device__ __forceinline__ float pwl_eval(float x, const DevTable& t, const float2* kb, int& seg)

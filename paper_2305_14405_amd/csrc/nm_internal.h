@@ -27,6 +27,17 @@ struct DevTable {
     // whose segment index is 1, so that a kernel may pick the line with one compare (two_seg != 0)
     int two_seg;
     float k0, b0, k1, b1, tau;
+    // inv_w is a power of two: (x - lo) * inv_w == fma(x, inv_w, u0) bit for bit, u0 = -lo * inv_w exactly
+    // (scaling by a power of two commutes with rounding)
+    int pow2;
+    float u0;
+};
+
+// Bounds of a table's value (host): over its range, and the lines of its two edge segments, which
+// continue outside it.
+struct TableBounds {
+    double vmin, vmax;              // of fma(k, x, b) over [lo, hi], widened past rounding
+    double k_first, b_first, k_last, b_last;
 };
 
 struct HostTable {
@@ -40,6 +51,11 @@ struct HostTable {
     std::vector<uint8_t> cellmap;
     size_t cblob_offset = 0;  // float2 units
     size_t map_offset = 0;    // float2 units (the map's bytes start there)
+    // derived once (derive_table)
+    float tau = 0.0f;         // two segments: the smallest value of segment 1
+    int pow2 = 0;
+    float u0 = 0.0f;
+    TableBounds bounds{};
 };
 
 int32_t launch_layernorm2(const float* in, const float* gamma, const float* beta, float eps,
@@ -65,6 +81,9 @@ int32_t check_hip(hipError_t e, const char* what);
 // two_level: also hand out the two-level form of a table built with NM_TABLE_COMPACT (only kernels
 // that look tables up in two steps ask for it; everything else works on the expanded form).
 int32_t get_dev_table(const nm_tables* t, int32_t idx, DevTable* dt, const char* what, bool two_level = false);
+
+// Bounds of the values table idx (validated by get_dev_table before) takes for x in [xmin, xmax].
+void table_value_bounds(const nm_tables* t, int32_t idx, double xmin, double xmax, double* vmin, double* vmax);
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
@@ -111,6 +130,20 @@ struct GemmArgs {
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // True when launch_gemm would fold the LayerNorm described by g.ln_* into the GEMM kernel.
 bool gemm_folds_layernorm(const GemmArgs& g);
+
+// The three attention steps as one kernel, for every shape fused_attention_covers accepts.
+struct AttnArgs {
+    const int8_t* qkv;
+    int B, S, H, heads;
+    float alpha_scores, inv_s_p, alpha_ctx, inv_s_ctx;
+    const nm_tables* tables;
+    int exp_idx, recip_idx;
+    int8_t* ctx;
+    int32_t* scores_out;
+    int8_t* p_out;
+};
+bool fused_attention_covers(int S, int H, int heads);
+int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t stream);
 
 int32_t launch_softmax(const void* in, int32_t in_dtype, float alpha, int64_t rows, int32_t cols,
                        const DevTable& t_exp, const DevTable& t_recip, float out_inv_scale,

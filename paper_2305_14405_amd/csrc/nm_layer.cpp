@@ -25,7 +25,7 @@ struct LayerPlan {
 
 static bool fused_attention_shape(const nm_layer_desc* d)
 {
-    return d->H / d->heads == 64 && d->S <= 512 && d->H % 16 == 0 && !unfused_attention();
+    return fused_attention_covers(d->S, d->H, d->heads) && !unfused_attention();
 }
 
 static LayerPlan plan_layer(const nm_layer_desc* d)
@@ -174,15 +174,16 @@ int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, f
     // kernel then still runs if they are aligned enough, else the three-kernel path needs the
     // caller's score / probability taps as storage (the workspace has none for a fused shape)
     bool fused = fused_attention_shape(d);
-    if (fused && !(aligned(qkv, 16) && aligned(ctx, 4) && (!(taps && taps->scores) || aligned(taps->scores, 16)))) {
+    if (fused && !(aligned(qkv, 16) && aligned(ctx, 4) && (!(taps && taps->scores) || aligned(taps->scores, 16)) &&
+                   (!(taps && taps->p) || aligned(taps->p, 4)))) {
         if (!(taps && taps->scores && taps->p))
             return fail(NM_ERR_UNSUPPORTED, "nm_encoder_layer: qkv / ctx / scores taps must be 16-byte aligned");
         fused = false;
     }
     if (fused) {
-        if ((rc = nm_attention_pwl(qkv, B, S, H, nh, d->alpha_scores, d->tables, d->exp_idx, d->recip_idx,
-                                   d->inv_s_p, d->alpha_ctx, d->inv_s_ctx, ctx, taps ? taps->scores : nullptr,
-                                   taps ? taps->p : nullptr, stream)))
+        if ((rc = launch_attention({qkv, B, S, H, nh, d->alpha_scores, d->inv_s_p, d->alpha_ctx, d->inv_s_ctx, d->tables,
+                                    d->exp_idx, d->recip_idx, ctx, taps ? taps->scores : nullptr, taps ? taps->p : nullptr},
+                                   "nm_encoder_layer(attention)", stream)))
             return rc;
     } else {
         if ((rc = nm_attn_scores(qkv, B, S, H, nh, scores, stream))) return rc;

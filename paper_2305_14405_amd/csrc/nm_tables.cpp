@@ -74,6 +74,44 @@ static float two_segment_threshold(float lo, float inv_w)
     return to_float(b);
 }
 
+// What kernels and launchers use of a finished table besides its lines.
+static void derive_table(HostTable& h)
+{
+    const nm_table_desc& d = h.desc;
+    if (d.nseg == 2) h.tau = two_segment_threshold(d.lo, h.inv_w);
+    int e;
+    const float u0 = -d.lo * h.inv_w;
+    h.pow2 = std::frexp(h.inv_w, &e) == 0.5f && std::isnormal(h.inv_w) && std::isfinite(u0) && (u0 == 0.0f || std::isnormal(u0));
+    h.u0 = h.pow2 ? u0 : 0.0f;
+    // a segment's line is monotone, so its extremes are at the segment's ends; the float index may put
+    // values a few roundings outside the nominal segment into it
+    const double w = ((double)d.hi - (double)d.lo) / d.nseg;
+    const double slack = 1e-5 * (std::fabs((double)d.lo) + std::fabs((double)d.hi) + w);
+    double vmin = std::numeric_limits<double>::infinity(), vmax = -vmin;
+    for (int s = 0; s < d.nseg; ++s)
+        for (int end = 0; end < 2; ++end) {
+            const double x = d.lo + (s + end) * w + (end ? slack : -slack);
+            const double v = (double)h.k[s] * x + (double)h.b[s];
+            if (!(v >= vmin)) vmin = v;   // a NaN sticks and fails every later comparison
+            if (!(v <= vmax)) vmax = v;
+        }
+    h.bounds = {vmin, vmax, h.k.front(), h.b.front(), h.k.back(), h.b.back()};
+}
+
+void table_value_bounds(const nm_tables* t, int32_t idx, double xmin, double xmax, double* vmin, double* vmax)
+{
+    const HostTable& h = t->tables[idx];
+    double lo = h.bounds.vmin, hi = h.bounds.vmax;
+    if (!(h.desc.flags & NM_TABLE_CLAMP_INPUT)) {
+        auto take = [&](double v) { if (!(v >= lo)) lo = v; if (!(v <= hi)) hi = v; };
+        if (xmin < h.desc.lo) take(h.bounds.k_first * xmin + h.bounds.b_first);
+        if (xmax > h.desc.hi) take(h.bounds.k_last * xmax + h.bounds.b_last);
+    }
+    // past the rounding of the fp32 evaluation
+    *vmin = lo - 1e-5 * std::fabs(lo) - 1e-30;
+    *vmax = hi + 1e-5 * std::fabs(hi) + 1e-30;
+}
+
 int32_t get_dev_table(const nm_tables* t, int32_t idx, DevTable* dt, const char* what, bool two_level)
 {
     if (!t) return fail(NM_ERR_INVALID_ARG, "%s: tables is NULL", what);
@@ -92,8 +130,10 @@ int32_t get_dev_table(const nm_tables* t, int32_t idx, DevTable* dt, const char*
     if (h.desc.nseg == 2 && !dt->clamp_input) {
         dt->two_seg = 1;
         dt->k0 = h.k[0]; dt->b0 = h.b[0]; dt->k1 = h.k[1]; dt->b1 = h.b[1];
-        dt->tau = two_segment_threshold(h.desc.lo, h.inv_w);
+        dt->tau = h.tau;
     }
+    dt->pow2 = h.pow2;
+    dt->u0 = h.u0;
     if (two_level && !h.cellmap.empty()) {
         dt->ckb = t->d_blob + h.cblob_offset;
         dt->cellmap = reinterpret_cast<const uint8_t*>(t->d_blob + h.map_offset);
@@ -341,6 +381,7 @@ static int32_t make_tables(const nm_table_desc* descs, int32_t n, const float* c
             int32_t rc = make_compact(h);
             if (rc) { delete t; return rc; }
         }
+        derive_table(h);
     }
     int32_t rc = upload(t, (hipStream_t)stream);
     if (rc) {

@@ -849,6 +849,53 @@ def test_fused_attention_clamp_flag_exp_table(oracle, S):
     assert_exact(host(ctx), want_ctx, "fused context, clamped exp input")
 
 
+@pytest.mark.parametrize("S,nseg,inv_p,alpha_s", [(257, 128, 127.0, 1.2e-3), (320, 100, 127.0, 1.2e-3), (500, 64, 900.0, 1.2e-3),
+                                                 (512, 100, 30000.0, 2e-4), (200, 37, 127.0, 3e-3), (128, 64, 900.0, 1.2e-3),
+                                                 (449, 64, 127.0, -1.2e-3), (90, 64, 127.0, 0.0)])
+def test_fused_attention_table_and_requantisation_forms(oracle, S, nseg, inv_p, alpha_s):
+    """Context without the optional outputs: exp tables whose segment width is and is not a power of two,
+    codes that saturate, scales of either sign, and sequences split over two wavefronts."""
+    heads, H = 2, 128
+    ot, dt = both_tables(oracle, [("exp", -16.0, 0.0, nseg), ("recip", 1.0, float(max(64, S)), 128)])
+    g = np.random.default_rng(S + nseg)
+    qkv = np.clip(np.rint(22 * g.standard_normal((S, 3 * H))), -127, 127).astype(np.int8)
+    q, k, v = (qkv[:, i * H:(i + 1) * H].reshape(S, heads, 64).astype(np.int64) for i in range(3))
+    scores = np.einsum("ihc,jhc->hij", q, k)
+    alpha_s = float(np.float32(alpha_s))
+    P = oracle.softmax_pwl(scores.reshape(-1, S).astype(np.int32), alpha_s, ot[0], ot[1], inv_p)["q"].reshape(heads, S, S)
+    assert inv_p < 500 or (P == 127).any()
+    cacc = np.einsum("hij,jhc->ihc", P.astype(np.int64), v).reshape(S, H)
+    alpha_c, inv_c = float(np.float32(2.0e-3)), float(np.float32(1.7))
+    cv = (cacc.astype(np.float32) * np.float32(alpha_c)).astype(np.float32)
+    want = np.clip(np.rint((cv * np.float32(inv_c)).astype(np.float32)), -127, 127).astype(np.int8)
+    ctx = torch.empty((S, H), dtype=torch.int8, device=DEV)
+    nm.nm_attention_pwl(dev(qkv), 1, S, H, heads, alpha_s, dt, 0, 1, inv_p, alpha_c, inv_c, ctx)
+    assert_exact(host(ctx), want, "context")
+
+
+@pytest.mark.parametrize("B,S,H,heads", [(1, 513, 64, 1), (1, 1030, 96, 2), (2, 70, 32, 2), (1, 256, 96, 3)])
+def test_encoder_layer_attention_of_long_sequences_and_small_heads(oracle, B, S, H, heads):
+    """Shapes of the attention kernel that computes its scores three times: more than 512 keys, head
+    sizes 64, 48, 16 and 32; with and without the intermediate tensors."""
+    cfg = dict(B=B, S=S, H=H, heads=heads, F=2 * H, nseg=64)
+    p = W.with_scales(W.layer_tensors(cfg, 5), W.stored_scales("long_seq", 0))
+    ot, dt = both_tables(oracle, [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")])
+    want = oracle.encoder_layer(p, dict(zip(("gelu", "exp", "recip", "rsqrt"), ot)), p["x"])
+    devw = {n: dev(p[n]) for n in nm.LAYER_PTRS}
+    desc = nm.make_layer_desc(p, devw, dt)
+    ws = torch.empty(nm.nm_encoder_layer_workspace(desc), dtype=torch.uint8, device=DEV)
+    taps = dict(scores=torch.empty((B, heads, S, S), dtype=torch.int32, device=DEV), p=torch.empty((B, heads, S, S), dtype=torch.int8, device=DEV),
+                ctx=torch.empty((B * S, H), dtype=torch.int8, device=DEV))
+    yq = torch.empty((B * S, H), dtype=torch.int8, device=DEV)
+    nm.nm_encoder_layer(desc, dev(p["x"]), yq, None, ws, taps=taps)
+    for k in ("scores", "p", "ctx"):
+        assert_exact(host(taps[k]), want[k], k)
+    assert_exact(host(yq), want["y_q"], "y_q")
+    yq.zero_()
+    nm.nm_encoder_layer(desc, dev(p["x"]), yq, None, ws)
+    assert_exact(host(yq), want["y_q"], "y_q without taps")
+
+
 def test_fused_attention_unsupported_shapes():
     dt = nm.nm_build_tables([("exp", -16.0, 0.0, 64), ("recip", 1.0, 64.0, 64)])
     x = torch.zeros((8 * 96 * 3,), dtype=torch.int8, device=DEV)
