@@ -128,6 +128,10 @@ __device__ __forceinline__ float pwl_eval_two_level(float x, const DevTable& t, 
     return __builtin_fmaf(e.x, x, e.y);
 }
 
+// A line of zeros in device memory: the source of operand bytes that fall into a convolution's
+// padding (the direct global -> LDS loads cannot substitute a value, only an address).  One per translation unit.
+static __device__ __attribute__((aligned(256))) int8_t g_zero_line[256];
+
 // Direct global -> LDS load: every lane supplies its own global address of 16 bytes; the wavefront's
 // 1 KB lands contiguously at lds_addr (wave-uniform), lane i at lds_addr + 16*i.  Asynchronous:
 // completion is tracked by the vector-memory counter (wait_vmcnt), not by the LDS counter.
@@ -149,6 +153,61 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// One butterfly step: op(v, value of lane ^ MASK), without going through LDS.  Masks 1 and 2 are
+// quad permutes, 4 and 8 compositions of the row mirrors (lane ^ 7 ^ 3, lane ^ 15 ^ 7), 16 and 32
+// the gfx950 row / half swaps: swapping a register with a copy of itself leaves {even rows twice}
+// in one and {odd rows twice} in the other (halves likewise), and op is commutative, so
+// op(first, second) is op(v, partner) in every lane.
+template <int MASK, typename Op>
+__device__ __forceinline__ int butterfly_step(int v, Op op)
+{
+    if (MASK == 1) return op(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));
+    if (MASK == 2) return op(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));
+    if (MASK == 4) {
+        const int t = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);   // lane ^ 7
+        return op(v, __builtin_amdgcn_update_dpp(0, t, 0x1B, 0xf, 0xf, false));     // ... ^ 3
+    }
+    if (MASK == 8) {
+        const int t = __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);   // lane ^ 15
+        return op(v, __builtin_amdgcn_update_dpp(0, t, 0x141, 0xf, 0xf, false));    // ... ^ 7
+    }
+    if (MASK == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+        return op((int)r[0], (int)r[1]);
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return op((int)r[0], (int)r[1]);
+}
+
+struct AddF32 {
+    __device__ __forceinline__ int operator()(int a, int b) const { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }
+};
+struct MaxF32 {
+    __device__ __forceinline__ int operator()(int a, int b) const { return __float_as_int(__builtin_fmaxf(__int_as_float(a), __int_as_float(b))); }
+};
+struct MaxI32 {
+    __device__ __forceinline__ int operator()(int a, int b) const { return max(a, b); }
+};
+
+// Butterfly over the G lanes that own a row, partner masks G/2 ... 1 in that order.
+template <int G, typename Op>
+__device__ __forceinline__ int group_reduce(int v, Op op)
+{
+    if (G > 32) v = butterfly_step<32>(v, op);
+    if (G > 16) v = butterfly_step<16>(v, op);
+    if (G > 8) v = butterfly_step<8>(v, op);
+    if (G > 4) v = butterfly_step<4>(v, op);
+    if (G > 2) v = butterfly_step<2>(v, op);
+    if (G > 1) v = butterfly_step<1>(v, op);
+    return v;
+}
+
+template <int G>
+__device__ __forceinline__ float group_sum(float v)
+{
+    return __int_as_float(group_reduce<G>(__float_as_int(v), AddF32{}));
 }
 
 }  // namespace nm

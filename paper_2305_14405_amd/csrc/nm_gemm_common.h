@@ -11,10 +11,6 @@ namespace nm {
 constexpr int kGemmThreads = 256;
 constexpr int kBK = 64;  // bytes of k per pipeline stage
 
-// A line of zeros in device memory: the source of operand bytes that fall into a convolution's
-// padding (the direct global -> LDS loads cannot substitute a value, only an address).  One per translation unit.
-static __device__ __attribute__((aligned(256))) int8_t g_zero_line[256];
-
 struct GemmParams {
     int M, N, K;
     const int8_t* A; long lda;

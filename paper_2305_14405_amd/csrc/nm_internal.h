@@ -145,6 +145,11 @@ struct AttnArgs {
 bool fused_attention_covers(int S, int H, int heads);
 int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t stream);
 
+// Steps 5 to 9 of a layer (and step 1 of the next) as one kernel over blocks of rows; *done = false where it
+// does not take the layer.
+int32_t launch_encoder_block(const nm_layer_desc* d, const nm_layer_desc* next, const int8_t* ctx, const int8_t* x, int8_t* y_q,
+                             float* y_f32, int8_t* qkv, hipStream_t stream, bool* done);
+
 int32_t launch_softmax(const void* in, int32_t in_dtype, float alpha, int64_t rows, int32_t cols,
                        const DevTable& t_exp, const DevTable& t_recip, float out_inv_scale,
                        int8_t* out_q, float* out_f32, uint16_t* seg_exp, uint16_t* seg_recip,

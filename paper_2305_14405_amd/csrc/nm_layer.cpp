@@ -28,6 +28,14 @@ static bool fused_attention_shape(const nm_layer_desc* d)
     return fused_attention_covers(d->S, d->H, d->heads) && !unfused_attention();
 }
 
+// Whether the workspace holds score and probability tensors: for the shapes nm_attention_pwl documents it
+// does not; for the others it does, so that taps too little aligned for the fused kernel (and
+// NM_ATTN_UNFUSED) have the three-kernel path to fall back to.
+static bool plan_holds_scores(const nm_layer_desc* d)
+{
+    return d->H / d->heads != 64 || d->S > 512 || d->H % 16 != 0 || unfused_attention();
+}
+
 static LayerPlan plan_layer(const nm_layer_desc* d)
 {
     const size_t M = (size_t)d->B * d->S, H = d->H, F = d->F;
@@ -36,12 +44,9 @@ static LayerPlan plan_layer(const nm_layer_desc* d)
     size_t o = 0;
     auto take = [&o](size_t bytes) { size_t at = o; o = round_up(o + bytes, 256); return at; };
     p.off_qkv = take(M * 3 * H);
-    // the score and probability tensors exist only on the three-kernel attention path (the fused
-    // kernel keeps them in registers; every workspace tensor is 256-byte aligned, so whether it
-    // runs depends on the shape alone)
-    const bool fused = fused_attention_shape(d);
-    p.off_scores = take(fused ? 0 : SS * sizeof(int32_t));
-    p.off_p = take(fused ? 0 : SS);
+    const bool scores = plan_holds_scores(d);
+    p.off_scores = take(scores ? SS * sizeof(int32_t) : 0);
+    p.off_p = take(scores ? SS : 0);
     p.off_ctx = take(M * H);
     p.off_attn = take(M * H * sizeof(float));
     p.off_ln1 = take(M * H);
@@ -107,24 +112,14 @@ static int32_t static_scratch(void** out)
     return NM_OK;
 }
 
-}  // namespace nm
-
-using namespace nm;
-
-extern "C" {
-
-int32_t nm_encoder_layer_workspace(const nm_layer_desc* desc, size_t* bytes)
+// One layer.  next: the layer behind it in a stack (NULL: none), whose QKV projection may then be made by
+// this layer's last kernel: *qkv_ready says on entry whether the previous layer has done so for this one
+// (the projection is the first tensor of the workspace), on return whether this one has for the next.
+static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool* qkv_ready, const int8_t* x, int8_t* y_q,
+                         float* y_f32, void* ws, size_t ws_bytes, const nm_layer_taps* taps, void* stream_)
 {
-    int32_t rc = validate_layer(desc, "nm_encoder_layer_workspace");
-    if (rc) return rc;
-    if (!bytes) return fail(NM_ERR_INVALID_ARG, "nm_encoder_layer_workspace: bytes is NULL");
-    *bytes = plan_layer(desc).total;
-    return NM_OK;
-}
-
-int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, float* y_f32,
-                         void* ws, size_t ws_bytes, const nm_layer_taps* taps, void* stream_)
-{
+    const bool have_qkv = *qkv_ready;
+    *qkv_ready = false;
     int32_t rc = validate_layer(d, "nm_encoder_layer", true);
     if (rc) return rc;
     if (!x) return fail(NM_ERR_INVALID_ARG, "nm_encoder_layer: x is NULL");
@@ -159,7 +154,7 @@ int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, f
     float* ffn2 = (float*)pick(taps ? taps->ffn2 : nullptr, plan.off_ffn2);
 
     // 1: QKV projection, three output scales by column third
-    {
+    if (!have_qkv) {
         GemmArgs g;
         g.M = M; g.N = 3 * H; g.K = H;
         g.A = x; g.lda = H; g.W = d->Wqkv; g.ldw = H;
@@ -176,7 +171,7 @@ int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, f
     bool fused = fused_attention_shape(d);
     if (fused && !(aligned(qkv, 16) && aligned(ctx, 4) && (!(taps && taps->scores) || aligned(taps->scores, 16)) &&
                    (!(taps && taps->p) || aligned(taps->p, 4)))) {
-        if (!(taps && taps->scores && taps->p))
+        if (!plan_holds_scores(d) && !(taps && taps->scores && taps->p))
             return fail(NM_ERR_UNSUPPORTED, "nm_encoder_layer: qkv / ctx / scores taps must be 16-byte aligned");
         fused = false;
     }
@@ -191,6 +186,17 @@ int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, f
                                  d->inv_s_p, pm, nullptr, nullptr, nullptr, stream)))
             return rc;
         if ((rc = nm_attn_context(pm, qkv, B, S, H, nh, d->alpha_ctx, d->inv_s_ctx, ctx, stream))) return rc;
+    }
+    // 5-9 as one kernel over blocks of rows, for narrow layers (no intermediate tensor then exists in memory)
+    const bool block_taps = taps && (taps->attn || taps->ln1 || taps->ffn1 || taps->ffn2);
+    if (!block_taps && !(d->flags & NM_LAYER_FOLD_LAYERNORM)) {
+        const nm_layer_desc* follow = next && next->Wqkv && validate_layer(next, "nm_encoder_stack", true) == NM_OK ? next : nullptr;
+        bool done = false;
+        if ((rc = launch_encoder_block(d, follow, ctx, x, y_q, y_f32, follow ? qkv : nullptr, stream, &done))) return rc;
+        if (done) {
+            *qkv_ready = follow != nullptr;
+            return NM_OK;
+        }
     }
     // 5: output projection + bias + residual(x) -> fp32;  6: LayerNorm-PWL -> int8.  One kernel when
     // the caller asks for it and the shape allows (the fp32 tensor then never reaches memory, so not
@@ -244,6 +250,28 @@ int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, f
     }
     return launch_layernorm(ffn2, d->gamma2, d->beta2, d->eps2, M, H, t_rsqrt, d->inv_s_out, y_q, y_f32,
                             nullptr, stream);
+}
+
+}  // namespace nm
+
+using namespace nm;
+
+extern "C" {
+
+int32_t nm_encoder_layer_workspace(const nm_layer_desc* desc, size_t* bytes)
+{
+    int32_t rc = validate_layer(desc, "nm_encoder_layer_workspace");
+    if (rc) return rc;
+    if (!bytes) return fail(NM_ERR_INVALID_ARG, "nm_encoder_layer_workspace: bytes is NULL");
+    *bytes = plan_layer(desc).total;
+    return NM_OK;
+}
+
+int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, float* y_f32,
+                         void* ws, size_t ws_bytes, const nm_layer_taps* taps, void* stream)
+{
+    bool qkv_ready = false;
+    return run_layer(d, nullptr, &qkv_ready, x, y_q, y_f32, ws, ws_bytes, taps, stream);
 }
 
 int32_t nm_encoder_layer_noalloc(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, float* y_f32, void* stream)
@@ -308,10 +336,12 @@ int32_t nm_encoder_stack(const nm_layer_desc* descs, int32_t n_layers, const int
     int8_t* act_buf[2] = {reinterpret_cast<int8_t*>(w), reinterpret_cast<int8_t*>(w + act)};
     void* lws = w + 2 * act;
     const int8_t* in = x;
+    bool qkv_ready = false;
     for (int32_t l = 0; l < n_layers; ++l) {
         const bool last = l == n_layers - 1;
         int8_t* out = last ? y_q : act_buf[l & 1];
-        if ((rc = nm_encoder_layer(&descs[l], in, out, last ? y_f32 : nullptr, lws, ws_bytes - 2 * act, nullptr, stream)))
+        if ((rc = run_layer(&descs[l], last ? nullptr : &descs[l + 1], &qkv_ready, in, out, last ? y_f32 : nullptr, lws,
+                            ws_bytes - 2 * act, nullptr, stream)))
             return rc;
         in = out;
     }

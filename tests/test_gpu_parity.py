@@ -995,6 +995,42 @@ def test_encoder_stack(oracle, name, n_layers):
     assert ei.value.status == nm.NM_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("B,S,H,heads,F,n_layers,biases", [
+    (1, 1, 16, 1, 16, 2, True), (3, 5, 48, 3, 80, 3, False), (1, 17, 64, 1, 272, 1, True), (2, 16, 160, 10, 144, 2, True),
+    (1, 33, 256, 4, 1024, 2, True), (1024, 1, 320, 5, 1280, 1, True), (31, 33, 448, 7, 1792, 2, True),
+    (1025, 4, 48, 3, 80, 2, True), (151, 32, 192, 3, 768, 1, False), (8200, 2, 32, 2, 32, 2, True), (129, 32, 320, 5, 1280, 2, True)])
+def test_encoder_block_kernel_edges(oracle, B, S, H, heads, F, n_layers, biases):
+    """The kernel that runs everything behind attention for a block of rows: row remainders of 16 and
+    32 per workgroup, widths that are no multiple of 128, more and fewer tiles than wavefronts, the ring
+    depths, the last layer with both outputs and with one, missing biases."""
+    cfg = dict(B=B, S=S, H=H, heads=heads, F=F, nseg=64)
+    ps = [W.with_scales(W.layer_tensors(cfg, 11 + i), W.stored_scales("tiny", 0)) for i in range(n_layers)]
+    names = ("gelu", "exp", "recip", "rsqrt")
+    ot, dt = both_tables(oracle, [W.table_ranges(cfg)[n] for n in names])
+    keep, descs = [], []
+    for p in ps:
+        if not biases:
+            for b in ("bqkv", "bo", "b1", "b2"):
+                p[b] = np.zeros_like(p[b])
+        devw = {n: dev(p[n]) if biases or n not in ("bqkv", "bo", "b1", "b2") else None for n in nm.LAYER_PTRS}
+        keep.append(devw)
+        descs.append(nm.make_layer_desc(p, devw, dt))
+    want = oracle.encoder_stack(ps, dict(zip(names, ot)), ps[0]["x"])
+    x = dev(ps[0]["x"])
+    ws = torch.empty(nm.nm_encoder_stack_workspace(descs), dtype=torch.uint8, device=DEV)
+    yq = torch.empty((B * S, H), dtype=torch.int8, device=DEV)
+    yf = torch.empty((B * S, H), dtype=torch.float32, device=DEV)
+    nm.nm_encoder_stack(descs, x, yq, yf, ws)
+    assert_exact(host(yq), want["y_q"], "y_q")
+    assert_f32_close(host(yf), want["y_f32"], "y_f32")
+    yq.zero_()
+    nm.nm_encoder_stack(descs, x, yq, None, ws)
+    assert_exact(host(yq), want["y_q"], "y_q alone")
+    yf.zero_()
+    nm.nm_encoder_stack(descs, x, None, yf, ws)
+    assert_f32_close(host(yf), want["y_f32"], "y_f32 alone")
+
+
 @pytest.mark.parametrize("name,n_layers,batch", [("bert_base_s512", 12, None), ("bert_large_s512", 24, 8)])
 def test_encoder_stack_full_depth(oracle, name, n_layers, batch):
     """The 12-layer and the 24-layer workloads at their full depth, every layer with weights and
