@@ -690,6 +690,37 @@ bool gemm_folds_layernorm(const GemmArgs& g)
     return al && (int64_t)g.M * g.lda < (1LL << 32) && (int64_t)g.N * g.ldw < (1LL << 32);
 }
 
+// Which tile of the tile kernel: the one whose predicted time is smallest.  A configuration takes
+//   start + rounds * (slice * K / 128 + epilogue)   us,
+// rounds being its tiles over the 256 CUs (or, where two workgroups share a CU, over 512 places; up to
+// 256 tiles behind the full rounds then have a CU each and cost 0.6 of a round).  The constants are a
+// least-squares fit to 72 measured shapes: M from 2048 to 16384, the four products of a layer of width 512, 768
+// and 1024.  Over those, the chosen tile is 1 % slower than the best of the seven (11 % at worst); full rounds
+// weighted by one number per tile, over four of them, were 7 % (54 %) slower.  Examples, us, 256x256 | 256x192 |
+// 256x128 | 128x192 with three and with two stages | 128x128 likewise:
+//   16384 x 1024 x 4096, fp32:   64 | 87 | 72 | 84 | 79 | 89 | 77
+//   12000 x 3072 x 768, table:   52 | 51 | 58 | 59 | 43 | 58 | 47
+//    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21
+static int choose_tile(int M, int N, int K, bool f32, bool table)
+{
+    static const struct { int bm, bn, stages, places; double start, slice, f32, q, table; } kTiles[] = {
+        {256, 256, 2, 256, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, -1.71, 0.93, 10.51, 7.24, 8.83},
+        {256, 128, 3, 256, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0.08, 0.54, 7.35, 4.55, 5.87},
+        {128, 192, 2, 512, 0.90, 1.06, 9.82, 5.74, 6.95},    {128, 128, 3, 256, 0.20, 0.46, 6.15, 2.55, 3.70},
+        {128, 128, 2, 512, 0.94, 0.87, 8.14, 2.91, 4.51}};
+    int best = -1;
+    double best_us = 0.0;
+    for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+        const auto& t = kTiles[c];
+        if (K / 128 < t.stages + 1) continue;
+        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
+        const double rounds = (double)(tiles / t.places) + (rest == 0 ? 0.0 : t.places == 512 && rest <= 256 ? 0.6 : 1.0);
+        const double us = t.start + rounds * (t.slice * (K / 128) + (f32 ? t.f32 : table ? t.table : t.q));
+        if (best < 0 || us < best_us) best_us = us, best = c;
+    }
+    return best;
+}
+
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M == 0) return NM_OK;
@@ -835,37 +866,27 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         if (rc) return rc;
         return check_hip(hipGetLastError(), "conv gemm launch");
     }
-    // Which tile: the one whose workgroups fill whole rounds of the 256 CUs best, weighted by how much
-    // operand traffic per matrix instruction the tile shape costs (weights from timings of the
-    // encoder shapes: 256x192 1.0, 256x128 0.92, 128x192 0.85, 128x128 0.75) and by the share of the
-    // tiles' area that lies inside the output.
     int tile_cfg = -1;
-    if (tile_ok && !old_big && forced_cfg() < 0) {
-        static const struct { int bm, bn, stages; double quality; } kTiles[4] = {
-            {256, 192, 2, 1.0}, {256, 128, 3, 0.92}, {128, 192, 3, 0.85}, {128, 128, 3, 0.75}};
-        double best = 0.0;
-        for (int c = 0; c < 4; ++c) {
-            if (g.K / 128 < kTiles[c].stages + 1) continue;
-            const long tm = (g.M + kTiles[c].bm - 1) / kTiles[c].bm, tn = (g.N + kTiles[c].bn - 1) / kTiles[c].bn;
-            const long tiles = tm * tn, slots = (tiles + 255) / 256 * 256;
-            const double inside = (double)g.M * g.N / ((double)tiles * kTiles[c].bm * kTiles[c].bn);
-            const double score = (double)tiles / (double)slots * inside * kTiles[c].quality;
-            if (score > best) { best = score; tile_cfg = c; }
-        }
+    if (tile_ok && !old_big) {
         // small problems stay with the streaming kernel's small tiles
-        if ((long)g.M * g.N < 128L * 128 * 96) tile_cfg = -1;
-    } else if (tile_ok && !old_big && forced_cfg() == 0 && g.K / 128 >= 3) {
-        tile_cfg = 0;
+        if (forced_cfg() < 0) tile_cfg = (long)g.M * g.N < 128L * 128 * 96 ? -1 : choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
+        else if (forced_cfg() == 0) tile_cfg = 1;
     }
     if (tile_cfg >= 0 && two_level_q) epi = EPI_Q_TABLE2;
     if (tile_cfg == 0) {
-        rc = launch_tile<256, 192, 4, 2, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 256, 2, 4, 2>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 1) {
-        rc = launch_tile<256, 128, 4, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 192, 4, 2, 2>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 2) {
-        rc = launch_tile<128, 192, 2, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 128, 4, 2, 3>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 3) {
+        rc = launch_tile<128, 192, 2, 2, 3>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 4) {
+        rc = launch_tile<128, 192, 2, 2, 2>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 5) {
         rc = launch_tile<128, 128, 2, 2, 3>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 6) {
+        rc = launch_tile<128, 128, 2, 2, 2>(p, epi, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

@@ -24,12 +24,28 @@ namespace nm {
 //    after the k-loop (nothing in front of the first operand slice waits for them);
 //  * the epilogue works on groups of four columns; the table look-up of a group is issued three
 //    groups before its result is used, and int8 rows leave through an LDS patch as 16-byte stores.
-// Eight wavefronts as 4 x 2 (64 x 96 each) keep two wavefronts on every SIMD: the fp32 epilogue
-// issues almost twice as fast that way as with four wavefronts of 128 x 96 (measured: a single
-// wavefront cannot issue dependent-free vector instructions back to back at the SIMD's full rate).
+// Two wavefronts on every SIMD: the fp32 epilogue issues almost twice as fast that way as with one (measured:
+// a single wavefront cannot issue dependent-free vector instructions back to back at the SIMD's full
+// rate).  The large tiles do it with eight wavefronts, the small ones with four and, in a ring of two
+// stages, two workgroups per CU: one's prologue and epilogue then run under the other's matrix work
+// (16384 x 4096 x 1024 with table, 128x192 tiles: 122 us with one workgroup and three stages, 89 with two).
+//
+// What bounds it.  256x256 tiles at 16384 x 1024 x 4096: 64 us, of which 10 are the 64 MB of fp32 results and about
+// 5 launch and prologue; the k-loop runs at the rate the card's power allows (all operands zero: 54 us
+// with the same instructions; operand rows that all lie in L2: no change).  256x128 tiles there: 72 us, because
+// a slice then needs 47 bytes per matrix clock and CU through the direct loads, which deliver about 40 (256x256: 32).
+// With short K the epilogue is the larger part: 12 vector instructions per element with the table, 6 without.
 // ---------------------------------------------------------------------------------------------
+// LDS that the epilogue lays over the ring: the wavefronts' int8 row patches, or the residual tile and the
+// wavefronts' fp32 row patches, then the bias and the table.
+constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
+{
+    return epi == EPI_F32_RESID_LN ? bm * (bn + 16) + (bm * 64 + 2 * bm) * 4
+         : epi == EPI_F32_RESID ? bm * (bn + 16) + nw * 32 * (wn + 4) * 4 : nw * wm * (wn + 16);
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void gemm_tile_kernel(GemmParams p)
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(GemmParams p)
 {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -61,7 +77,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void gemm_tile_kernel(Ge
     constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN;
 
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    float* s_bias = reinterpret_cast<float*>(smem + STAGES * STAGE_BYTES);
+    float* s_bias = reinterpret_cast<float*>(smem + tile_front_bytes(BM, BN, NW, WM, WN, kEpi));
     float2* s_kb = reinterpret_cast<float2*>(s_bias + BN);
 
     const int tid = threadIdx.x;
@@ -359,20 +375,42 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void gemm_tile_kernel(Ge
             if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = rows[t];
         }
     } else if constexpr (kEpi == EPI_F32_RESID) {
+        // Rows leave through an LDS patch of 32 rows per wavefront, 16 or 24 lanes per row.  Stored straight
+        // from the accumulators (32 bytes of each of 32 rows per instruction) the 64 MB of a 16384 x 1024
+        // result took 15 us behind the matrix work (kernel with K = 1024: 36 us); whole lines take 10 (30).
+        constexpr int PW = WN + 4, LPR = WN / 4, NST = 32 * LPR / 64;
+        static_assert(32 * LPR % 64 == 0, "pieces split evenly");
+        float* patch = reinterpret_cast<float*>(smem + BM * RW) + wave * 32 * PW;
         const float rs = p.resid_scale;
 #pragma unroll
-        for (int G = 0; G < NG; ++G) {
-            const int i = G % TM, jg = G / TM, j = jg / 4, g = jg % 4;
-            const int row = wave_m + 32 * i + frag_row, cl = wave_n + 32 * j + 8 * g + 4 * frag_half;
-            const unsigned rw = *reinterpret_cast<const unsigned*>(s_res + row * RW + cl);
-            v4f y;
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = __builtin_fmaf((float)acc[i][j][4 * g + e], alpha, bi[j][g][e]);
-                y[e] = __builtin_fmaf((float)(int)(int8_t)(rw >> (8 * e)), rs, v);
+            for (int jg = 0; jg < 4 * TN; ++jg) {
+                const int j = jg / 4, g = jg % 4;
+                const int cl = 32 * j + 8 * g + 4 * frag_half;
+                const unsigned rw = *reinterpret_cast<const unsigned*>(s_res + (wave_m + 32 * i + frag_row) * RW + wave_n + cl);
+                v4f y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = __builtin_fmaf((float)acc[i][j][4 * g + e], alpha, bi[j][g][e]);
+                    y[e] = __builtin_fmaf((float)(int)(int8_t)(rw >> (8 * e)), rs, v);
+                }
+                *reinterpret_cast<v4f*>(patch + frag_row * PW + cl) = y;
             }
-            const int m = m0 + row, n = n0 + cl;
-            if (full || (m < p.M && n < p.N)) *reinterpret_cast<v4f*>(p.out_f32 + (long)m * p.ldo + n) = y;
+            // the wavefront reads back the rows it wrote, and writes the next ones after that
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int t = 0; t < NST; ++t) {
+                const int c = lane + 64 * t, row = c / LPR, cc = c % LPR;
+                const v4f y = *reinterpret_cast<const v4f*>(patch + row * PW + 4 * cc);
+                const int m = m0 + wave_m + 32 * i + row, n = n0 + wave_n + 4 * cc;
+                if (full || (m < p.M && n < p.N)) *reinterpret_cast<v4f*>(p.out_f32 + (long)m * p.ldo + n) = y;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
     } else {
         // ---- fp32 result + residual, then LayerNorm-PWL over the row (the tile covers whole rows:
@@ -510,7 +548,10 @@ static int32_t launch_tile_epi(GemmParams& p, size_t table_bytes, hipStream_t s)
 {
     auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK>;
     constexpr int NW = WAVES_M * WAVES_N, NBLK = (BM + BN) * BK / 1024;
-    const size_t shmem = (size_t)STAGES * ((NBLK + NW - 1) / NW * NW) * 1024 + BN * sizeof(float) + table_bytes;
+    constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
+    constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M, BN / WAVES_N, kEpi);
+    static_assert(kFront % 16 == 0 && kFront + BN * 4 <= 160 * 1024 && kRing <= 160 * 1024, "LDS");
+    const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {

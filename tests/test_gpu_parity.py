@@ -617,6 +617,16 @@ def test_gemm_tile_kernel_configurations(oracle, M, N, K, what):
     assert_f32_close(host(of), r2["y"], f"fp32 + residual: {what}")
 
 
+@pytest.mark.parametrize("M,N,K,what", [
+    (6449, 1744, 384, "256x256; 128x192 with two workgroups per CU where there is a table"), (5911, 1296, 384, "256x192"),
+    (6567, 784, 512, "256x128"), (6001, 752, 1536, "128x192 with three stages (fp32)"), (6529, 528, 384, "128x192 with two workgroups per CU"),
+    (1363, 1168, 640, "128x128 with three stages"), (2457, 656, 384, "128x128 with two workgroups per CU")])
+def test_gemm_tile_kernel_ragged_edges_of_every_tile(oracle, M, N, K, what):
+    """One shape per configuration of the large-tile kernel whose last row and column tiles are partly
+    outside, down to the fewest k-slices that configuration takes."""
+    test_gemm_tile_kernel_configurations(oracle, M, N, K, what)
+
+
 @pytest.mark.parametrize("M,N,K", [
     (1, 4, 16), (17, 33, 144), (16, 32, 3072), (31, 30, 1001), (128, 96, 130), (64, 1000, 2048), (224, 640, 2112),
     (225, 643, 2055), (500, 900, 320), (511, 902, 333), (1120, 960, 192), (1099, 990, 200), (1097, 991, 129), (5, 7, 65536)])
