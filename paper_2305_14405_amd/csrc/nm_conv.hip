@@ -190,7 +190,7 @@ struct StemParams {
     const int8_t* x; const int8_t* w;   // w: the packed filter [64][kh][32] (stem_pack_filter_kernel)
     const float* bias; const float* alpha_vec;
     float alpha, out_inv_scale;
-    int has_table;
+    int has_table, relu;
     DevTable table;
     int B, H, W, Cin, Cout, kh, kw, stride, pad, Ho, Wo;
     int prow, pcol, pitch;   // staged image patch: rows, pixels per row, bytes per row
@@ -289,9 +289,10 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
 
     // epilogue: lane (m, half) holds, per group g of four registers, channels 32j + 8g + 4half .. +3
     int8_t* patch = sO + wave * (64 * 80);
-    // (twice: a table of two segments, ReLU, is evaluated with a compare instead of index and gather)
-    auto finish = [&](auto two_c) {
-        constexpr bool kTwoSeg = decltype(two_c)::value;
+    // (three times: a table of two segments is evaluated with a compare instead of index and gather, and a ReLU
+    // by clamping the code)
+    auto finish = [&](auto form_c) {
+        constexpr bool kTwoSeg = decltype(form_c)::value == 1, kRelu = decltype(form_c)::value == 2;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -301,6 +302,15 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
                     const int n = 32 * j + 8 * g + 4 * half;
                     const v4f sc = *reinterpret_cast<const v4f*>(s_cols + n);
                     const v4f bi = *reinterpret_cast<const v4f*>(s_cols + 64 + n);
+                    unsigned* out = reinterpret_cast<unsigned*>(patch + (32 * t + fr) * 80 + n);
+                    if (kRelu) {
+                        unsigned w = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            w = relu_requant(__builtin_fmaf((float)acc[t][j][4 * g + e], sc[e], bi[e]), p.out_inv_scale, e, w);
+                        *out = w;
+                        continue;
+                    }
                     int q[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -309,11 +319,12 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
                         else if (p.has_table) { int sg; v = pwl_eval(v, p.table, s_kb, sg); }
                         q[e] = requant(v, p.out_inv_scale);
                     }
-                    *reinterpret_cast<unsigned*>(patch + (32 * t + fr) * 80 + n) = pack4(q[0], q[1], q[2], q[3]);
+                    *out = pack4(q[0], q[1], q[2], q[3]);
                 }
     };
-    if (p.has_table && p.table.two_seg) finish(std::true_type{});
-    else finish(std::false_type{});
+    if (p.relu && __all(relu_finite(s_cols[lane], s_cols[64 + lane]))) finish(std::integral_constant<int, 2>{});
+    else if (p.has_table && p.table.two_seg) finish(std::integral_constant<int, 1>{});
+    else finish(std::integral_constant<int, 0>{});
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -433,6 +444,7 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
         StemParams sp{};
         sp.x = d->x; sp.w = static_cast<const int8_t*>(ws); sp.bias = d->bias; sp.alpha_vec = d->alpha_vec; sp.alpha = d->alpha;
         sp.out_inv_scale = d->out_inv_scale; sp.has_table = g.has_table; sp.table = g.table;
+        sp.relu = g.has_table && relu_codes(g.table, d->out_inv_scale, 0.0f);
         sp.B = d->B; sp.H = d->H; sp.W = d->W; sp.Cin = d->Cin; sp.Cout = d->Cout; sp.kh = d->kh; sp.kw = d->kw;
         sp.stride = d->stride; sp.pad = d->pad; sp.Ho = pl.Ho; sp.Wo = pl.Wo;
         sp.prow = 15 * d->stride + d->kh;

@@ -90,6 +90,19 @@ __device__ __forceinline__ int requant(float v, float inv_scale)
     return __float_as_int(r + 12582912.0f);
 }
 
+// ReLU and int8 code in one (relu_codes holds, v finite): the code of v is that of clamp(v * inv_scale, 0, 127),
+// rounded, saturated and put into byte e of w by one conversion (to nearest even, as requant rounds).
+__device__ __forceinline__ unsigned relu_requant(float v, float inv_scale, int e, unsigned w)
+{
+    return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(v * inv_scale, 0.0f, 127.0f), e, w);
+}
+// Whether fma(accumulator, scale, bias) + residual stays finite whatever the accumulator (the residual's scale
+// is checked by relu_codes); false for a NaN.
+__device__ __forceinline__ bool relu_finite(float scale, float bias)
+{
+    return __builtin_fabsf(scale) <= 1e25f && __builtin_fabsf(bias) <= 1e30f;
+}
+
 // Packs the low bytes of four words into one (a in byte 0).
 __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d)
 {

@@ -544,9 +544,13 @@ void gemm_stream_kernel(GemmParams p)
     // The body exists twice: for a tile that lies wholly inside the output (and vector-aligned
     // outputs) every bounds test is a compile-time constant, which leaves straight-line code whose
     // table look-ups the scheduler can batch; edge tiles take the guarded copy.
-    auto finish_rows = [&](auto full_c, auto two_c) {
+    // Full tiles through a table of two segments compare instead of gathering; where that table is a ReLU
+    // (and the columns' scales and biases cannot make a sum infinite), clamping the code at 0 is all of it:
+    // 4.75 vector instructions per element less of the 19 the residual epilogue issued (ResNet-50, 64 images:
+    // the 1x1 convolutions with shortcut 35 -> 30, 23 -> 21 and 17 -> 15 us, all of it 1.127 -> 1.051 ms).
+    auto finish_rows = [&](auto full_c, auto form_c) {
         constexpr bool kFullTile = decltype(full_c)::value;
-        constexpr bool kTwoSeg = decltype(two_c)::value;   // two-segment table: compare instead of gather
+        constexpr bool kTwoSeg = decltype(form_c)::value == FORM_TWO_SEGMENTS, kRelu = decltype(form_c)::value == FORM_RELU;
 #pragma unroll
         for (int i = 0; i < TMF; ++i) {
             const int prow = 32 * (row_blk0 + i) + frag_row;  // row inside the sub-tile
@@ -564,7 +568,8 @@ void gemm_stream_kernel(GemmParams p)
                     {
                         const v4f sc = *reinterpret_cast<const v4f*>(s_cols + cl);
                         const v4f bi = *reinterpret_cast<const v4f*>(s_cols + BN + cl);
-                        const v4f iv = *reinterpret_cast<const v4f*>(s_cols + 2 * BN + cl);
+                        v4f iv = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                        if (!kRelu) iv = *reinterpret_cast<const v4f*>(s_cols + 2 * BN + cl);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { c.scale[e] = sc[e]; c.bias[e] = bi[e]; c.inv[e] = iv[e]; }
                     }
@@ -581,6 +586,17 @@ void gemm_stream_kernel(GemmParams p)
                         }
                     } else if (kEpi == EPI_GENERIC && p.resid) {
                         load_resid4(p, rowoff, nb, vec, r4);
+                    }
+                    if (kRelu) {
+                        unsigned w = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float v = __builtin_fmaf((float)a4[e], c.scale[e], c.bias[e]);
+                            if (kEpi == EPI_Q_TABLE_RESID) v = __builtin_fmaf((float)r4[e], p.resid_scale, v);
+                            w = relu_requant(v, p.out_inv_scale, e, w);
+                        }
+                        *reinterpret_cast<unsigned*>(patch + prow * SW + 32 * j + 8 * g + 4 * frag_half) = w;
+                        continue;
                     }
                     Epi4 o;
                     epi_math<kEpi, kTwoSeg>(p, s_kb, a4, c, r4, o);
@@ -613,12 +629,22 @@ void gemm_stream_kernel(GemmParams p)
             }
         }
     };
-    constexpr bool kTableEpi = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID;
+    using Any = std::integral_constant<int, FORM_ANY>;
     if (m0 + BM <= p.M && n0 + BN <= p.N && p.vec_out) {
-        if (kTableEpi && p.table.two_seg) finish_rows(std::true_type{}, std::integral_constant<bool, kTableEpi>{});
-        else finish_rows(std::true_type{}, std::false_type{});
+        if constexpr (kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID) {
+            bool relu = p.relu && patch_q;
+            if (relu) {
+                for (int c = lane; c < WN; c += 64) relu = relu && relu_finite(s_cols[wave_n + c], s_cols[BN + wave_n + c]);
+                relu = __all(relu);
+            }
+            if (relu) finish_rows(std::true_type{}, std::integral_constant<int, FORM_RELU>{});
+            else if (p.table.two_seg) finish_rows(std::true_type{}, std::integral_constant<int, FORM_TWO_SEGMENTS>{});
+            else finish_rows(std::true_type{}, Any{});
+        } else {
+            finish_rows(std::true_type{}, Any{});
+        }
     } else {
-        finish_rows(std::false_type{}, std::false_type{});
+        finish_rows(std::false_type{}, Any{});
     }
 }
 
@@ -747,6 +773,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     p.has_table = g.has_table; p.table = g.table;
     p.out_inv_scale = g.out_inv_scale; p.out_inv_scale_vec = g.out_inv_scale_vec;
     p.split_cols = g.split_cols;
+    p.relu = g.has_table && g.split_cols == 0 && !g.out_inv_scale_vec && relu_codes(g.table, g.out_inv_scale, g.resid ? g.resid_scale : 0.0f);
     for (int i = 0; i < 3; ++i) p.inv3[i] = g.inv3[i];
     p.ldo = g.ldo;
     p.cH = g.cH; p.cW = g.cW; p.cCin = g.cCin; p.cKw = g.cKw; p.cStride = g.cStride; p.cPad = g.cPad;

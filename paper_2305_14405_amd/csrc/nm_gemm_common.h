@@ -50,6 +50,7 @@ struct GemmParams {
     // convolution in matrix form (streaming kernel with kConv): row m of A is the output position
     // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
+    int relu;     // relu_codes holds for the table and the one output scale
     int batched;  // small-tile kernel: more than one problem (grid.y)
 };
 
@@ -146,6 +147,9 @@ __device__ __forceinline__ void load_resid4(const GemmParams& p, long rowoff, in
         for (int e = 0; e < 4; ++e) r4[e] = nb + e < p.N ? (int)p.resid[rowoff + nb + e] : 0;
     }
 }
+
+// How the streaming kernel's epilogue evaluates its table.
+enum { FORM_ANY = 0, FORM_TWO_SEGMENTS = 1, FORM_RELU = 2 };
 
 // The arithmetic of the epilogue for four columns of one row (no global memory access).
 // kTwoSeg: the table has two segments and is evaluated with a compare (specialised table epilogues)

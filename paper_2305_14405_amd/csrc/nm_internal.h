@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -32,6 +33,14 @@ struct DevTable {
     int pow2;
     float u0;
 };
+
+// Whether the int8 code of the table's value is that of max(x, 0) for every finite x: the two lines are 0 and x,
+// and between 0 and the threshold (where the float index puts it) either line's value rounds to code 0.
+inline bool relu_codes(const DevTable& t, float out_inv_scale, float resid_scale)
+{
+    return t.two_seg && t.k0 == 0.0f && t.b0 == 0.0f && t.k1 == 1.0f && t.b1 == 0.0f && out_inv_scale > 0.0f && out_inv_scale <= 3e38f &&
+           std::fabs(t.tau) * out_inv_scale < 0.49f && std::fabs(resid_scale) <= 1e30f;
+}
 
 // Bounds of a table's value (host): over its range, and the lines of its two edge segments, which
 // continue outside it.

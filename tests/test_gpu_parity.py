@@ -770,6 +770,34 @@ def test_two_segment_table_is_decided_by_one_compare_exactly(oracle, lo, hi):
     assert any(v < float(mid) and s == 1 for v, s in seg_of.items() if v == v)
 
 
+@pytest.mark.parametrize("lo,hi,inv", [(-8.0, 8.0, 3.0), (-8.0, 8.0, 1e9), (-1.0, 3.0, 3.0), (-8.0, 8.0, -3.0), (-256.0, 256.0, 9000.0)])
+@pytest.mark.parametrize("resid", [False, True])
+def test_relu_clamps_its_codes_exactly(oracle, lo, hi, inv, resid):
+    """Two-segment tables in the streaming kernel, where a ReLU is clamped with its code and everything else
+    compares: blocks of columns with finite biases around the break point and around code ties, others with
+    infinities and NaN among them, output scales for which the threshold's own code is and is not zero."""
+    ot, dt = both_tables(oracle, [("relu", lo, hi, 2)])
+    M, N, K = 700, 4096, 64
+    d = W.gemm_inputs(M, N, K, seed=int(hi), full_range=False)
+    g = np.random.default_rng(5)
+    bias = (g.standard_normal(N) * 8).astype(np.float32)
+    bias[0:512] = np.float32(0.5 / abs(inv)) * np.arange(-256, 256, dtype=np.float32)     # ties of the rounding
+    bias[512:1024] = np.float32((lo + hi) / 2) + np.float32((hi - lo) * 2.0 ** -25) * np.arange(-256, 256, dtype=np.float32)
+    bias[1024:1030] = [np.inf, -np.inf, np.nan, 3e38, -3e38, 1e31]
+    bias[2000] = np.nan
+    alpha = np.full(N, 1e-2, np.float32)
+    alpha[:1024] = 0.0                                                                    # the bias alone
+    alpha[3000] = np.float32(1e26)
+    alpha[3500:3504] = [np.inf, -np.inf, np.nan, -1.0]
+    rs = 1e-8 if resid else 0.0
+    r = oracle.gemm_pwl(d["A"], d["W"], bias=bias, alpha_vec=alpha, resid=d["resid"] if resid else None, resid_scale=rs, table=ot[0],
+                        out_inv_scale=inv)
+    oq = torch.empty((M, N), dtype=torch.int8, device=DEV)
+    nm.nm_gemm_pwl(dev(d["A"]), dev(d["W"]), bias=dev(bias), alpha_vec=dev(alpha), resid=dev(d["resid"]) if resid else None, resid_scale=rs,
+                   tables=dt, table_idx=0, out_inv_scale=inv, out_q=oq)
+    assert_exact(host(oq), r["q"], f"[{lo}, {hi}], scale {inv}")
+
+
 # ---- attention products -----------------------------------------------------------------------
 
 @pytest.mark.parametrize("B,S,H,heads", [(1, 64, 128, 2), (3, 40, 96, 3), (2, 128, 768, 12), (1, 200, 64, 1),
