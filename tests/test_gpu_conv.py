@@ -48,6 +48,30 @@ CASES = [  # B, H, W, Cin, Cout, kh, kw, stride, pad   (route)
 ]
 
 
+@pytest.mark.parametrize("B,H,W,Cin,Cout,kh,kw,stride,pad", [
+    (1, 1, 1, 3, 16, 3, 3, 1, 1), (1, 1, 2, 2, 16, 3, 3, 1, 1), (2, 33, 35, 3, 64, 7, 7, 2, 3), (1, 17, 16, 4, 48, 3, 8, 1, 0),
+    (3, 50, 61, 1, 16, 4, 5, 4, 2), (1, 40, 19, 2, 32, 9, 2, 3, 5), (2, 5, 5, 3, 64, 1, 3, 2, 0)])
+@pytest.mark.parametrize("table", ["relu", None])
+def test_conv2d_few_channels_int8_output(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad, table):
+    """The kernel for at most four input channels: the word that holds the tensor's last pixel, images smaller
+    than a word, padding on every side, each channel count, tile edges in both directions."""
+    g = np.random.default_rng(B * 7 + H + Cin + kh)
+    x, w = rand_i8(g, (B, H, W, Cin)), rand_i8(g, (Cout, kh, kw, Cin), 60)
+    Ho, Wo = oracle.conv_out_hw(H, W, kh, kw, stride, pad)
+    K = kh * kw * Cin
+    alpha_vec = ((3.0 / (35 * 70 * np.sqrt(K))) * (1 + g.random(Cout))).astype(np.float32)
+    bias = (0.3 * g.standard_normal(Cout)).astype(np.float32)
+    ot, dt = relu_tables(oracle)
+    want = oracle.conv2d_pwl(x, w, stride, pad, bias=bias, alpha_vec=alpha_vec, table=ot if table else None, out_inv_scale=20.0)
+    dx, dw, db, da = dev(x), dev(w), dev(bias), dev(alpha_vec)
+    oq = torch.full((B, Ho, Wo, Cout), 77, dtype=torch.int8, device=DEV)
+    d = nm.make_conv_desc(dx, dw, stride, pad, bias=db, alpha_vec=da, tables=dt if table else None, table_idx=0 if table else -1,
+                          out_inv_scale=20.0, out_q=oq)
+    ws = torch.empty(max(nm.nm_conv2d_workspace(d), 256), dtype=torch.uint8, device=DEV)
+    nm.nm_conv2d_pwl(d, ws)
+    assert np.array_equal(host(oq), want["q"])
+
+
 @pytest.mark.parametrize("B,H,W,Cin,Cout,kh,kw,stride,pad", CASES)
 def test_conv2d_all_outputs(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad):
     g = np.random.default_rng(B * 7 + H + Cin + kh)
