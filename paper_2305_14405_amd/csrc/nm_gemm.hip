@@ -717,31 +717,39 @@ bool gemm_folds_layernorm(const GemmArgs& g)
 }
 
 // Which tile of the tile kernel: the one whose predicted time is smallest.  A configuration takes
-//   start + rounds * (slice * K / 128 + epilogue)   us,
-// rounds being its tiles over the 256 CUs (or, where two workgroups share a CU, over 512 places; up to
-// 256 tiles behind the full rounds then have a CU each and cost 0.6 of a round).  The constants are a
-// least-squares fit to 72 measured shapes: M from 2048 to 16384, the four products of a layer of width 512, 768
-// and 1024.  Over those, the chosen tile is 1 % slower than the best of the seven (11 % at worst); full rounds
-// weighted by one number per tile, over four of them, were 7 % (54 %) slower.  Examples, us, 256x256 | 256x192 |
-// 256x128 | 128x192 with three and with two stages | 128x128 likewise:
+//   start + rounds * slice * K / 128 + rounds' * epilogue   us,
+// rounds being its tiles over its places on the 256 CUs (up to three workgroups share one).  Up to 256 tiles behind the
+// full rounds have a CU each and are charged the fraction `alone` of a round (`alone_epi` of an epilogue),
+// up to 512 where three share a CU `paired`.  A ring of two stages only pays where workgroups do share (from
+// `least` tiles on; it is also the one for K = 384): alone on a CU it waits for its operands, 23 instead of 17 us at
+// 4096 x 768 x 3072 with 128x128.  The constants are least-squares fits to 180 measured shapes: M from 64 to
+// 16384, the four products of a layer of width 512, 768 and 1024.  Over those the chosen tile is 1.2 % slower than
+// the best of the nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
+// were 7 % (54 %) slower from M = 2048 on.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
+// 128x128 likewise | 64x128 likewise:
 //   16384 x 1024 x 4096, fp32:   64 | 87 | 72 | 84 | 79 | 89 | 77
-//   12000 x 3072 x 768, table:   52 | 51 | 58 | 59 | 43 | 58 | 47
-//    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21
+//   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
+//    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21 | 18 | 19
+//    2048 x  768 x 3072, fp32:   33 | 26 | 20 | 17 | 17 | 15 | 15 | 10 | 11
 static int choose_tile(int M, int N, int K, bool f32, bool table)
 {
-    static const struct { int bm, bn, stages, places; double start, slice, f32, q, table; } kTiles[] = {
-        {256, 256, 2, 256, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, -1.71, 0.93, 10.51, 7.24, 8.83},
-        {256, 128, 3, 256, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0.08, 0.54, 7.35, 4.55, 5.87},
-        {128, 192, 2, 512, 0.90, 1.06, 9.82, 5.74, 6.95},    {128, 128, 3, 256, 0.20, 0.46, 6.15, 2.55, 3.70},
-        {128, 128, 2, 512, 0.94, 0.87, 8.14, 2.91, 4.51}};
+    static const struct { int bm, bn, stages, places, least; double alone, paired, alone_epi, start, slice, f32, q, table; } kTiles[] = {
+        {256, 256, 2, 256, 0, 1, 1, 1, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, 0, 1, 1, 1, -2.43, 0.89, 10.88, 7.70, 9.41},
+        {256, 128, 3, 256, 0, 1, 1, 1, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0, 1, 1, 1, 0.08, 0.54, 7.35, 4.55, 5.87},
+        {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 5.92, 2.75, 3.90},
+        {128, 128, 2, 512, 257, 0.65, 1, 0.65, 0.48, 0.87, 8.91, 2.98, 4.47}, {64, 128, 3, 512, 0, 0.45, 1, 0.8, 1.19, 0.52, 3.52, 2.23, 3.00},
+        {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}};
     int best = -1;
     double best_us = 0.0;
     for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
         const auto& t = kTiles[c];
-        if (K / 128 < t.stages + 1) continue;
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
-        const double rounds = (double)(tiles / t.places) + (rest == 0 ? 0.0 : t.places == 512 && rest <= 256 ? 0.6 : 1.0);
-        const double us = t.start + rounds * (t.slice * (K / 128) + (f32 ? t.f32 : table ? t.table : t.q));
+        if (K / 128 < t.stages + 1 || (tiles < t.least && K / 128 > 3)) continue;
+        const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
+        const double full = (double)(tiles / t.places);
+        const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);
+        const double epilogues = full + (rest == 0 ? 0.0 : alone ? t.alone_epi : paired ? t.paired : 1.0);
+        const double us = t.start + rounds * t.slice * (K / 128) + epilogues * (f32 ? t.f32 : table ? t.table : t.q);
         if (best < 0 || us < best_us) best_us = us, best = c;
     }
     return best;
@@ -866,7 +874,9 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                          (int64_t)g.N * g.ldw < (1LL << 32) && table_bytes <= 40 * 1024;
     // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
     // chosen when the output is too small for the larger tiles to occupy the chip: the tile kernel needs
-    // 96 tiles of 128x128 (and is not at its best with three k-slices), the streaming kernel's tiles
+    // about 110 tiles of 64x128 (us with operands in L2, this one and the best tile: 512 x 2304 x 768 6.7, 4.6; 1500 x 768 x 3072
+    // 15, 9.2; 512 x 768 x 3072 7.0, 8.7; at 847 x 768 the tiles are ahead by a tenth there, but in a stack, where
+    // the weights come from memory, 84 workgroups keep too few loads in flight: 12 layers 575 us against 561) and more with three k-slices, the streaming kernel's tiles
     // about a million outputs, more when the contraction is short and a large tile is mostly prologue and
     // epilogue; and for operands the other loaders do not read 16 bytes at a time (4096x1000x1000:
     // 27 us against the generic kernel's 106).
@@ -875,7 +885,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
-    const int64_t direct_below = tile_ok ? (g.K <= 384 ? 2450000 : 128 * 128 * 96) : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
+    const int64_t direct_below = tile_ok ? (g.K <= 384 ? 2450000 : 900000) : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
     const bool direct = direct_ok && (forced_cfg() >= 10 || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
     if (direct) {
         rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced_cfg() - 10 >= 0 ? forced_cfg() - 10 : -1, stream);
@@ -895,8 +905,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     }
     int tile_cfg = -1;
     if (tile_ok && !old_big) {
-        // small problems stay with the streaming kernel's small tiles
-        if (forced_cfg() < 0) tile_cfg = (long)g.M * g.N < 128L * 128 * 96 ? -1 : choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
+        if (forced_cfg() < 0) tile_cfg = choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
         else if (forced_cfg() == 0) tile_cfg = 1;
     }
     if (tile_cfg >= 0 && two_level_q) epi = EPI_Q_TABLE2;
@@ -914,6 +923,10 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         rc = launch_tile<128, 128, 2, 2, 3>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 6) {
         rc = launch_tile<128, 128, 2, 2, 2>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 7) {
+        rc = launch_tile<64, 128, 2, 2, 3>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 8) {
+        rc = launch_tile<64, 128, 2, 2, 2>(p, epi, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(Ge
     constexpr int RPS2 = (NR + NMF - 1) / NMF;          // ... and in the other k-steps
     constexpr int DPS = (LB + POST + NMF - 1) / (POST + NMF);  // refill loads per slot (those slots and the next k-step's)
     static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole blocks");
-    static_assert(TM >= 2 && TN >= 2 && KS % 2 == 0, "wavefront tile");
+    static_assert(TN >= 2 && KS % 2 == 0, "wavefront tile");
     constexpr bool kTable = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE2;
     static_assert(kEpi == EPI_Q || kTable || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
                   "epilogues of the tile kernel");

@@ -618,9 +618,10 @@ def test_gemm_tile_kernel_configurations(oracle, M, N, K, what):
 
 
 @pytest.mark.parametrize("M,N,K,what", [
-    (6449, 1744, 384, "256x256; 128x192 with two workgroups per CU where there is a table"), (5911, 1296, 384, "256x192"),
-    (6567, 784, 512, "256x128"), (6001, 752, 1536, "128x192 with three stages (fp32)"), (6529, 528, 384, "128x192 with two workgroups per CU"),
-    (1363, 1168, 640, "128x128 with three stages"), (2457, 656, 384, "128x128 with two workgroups per CU")])
+    (6449, 1744, 384, "256x256; 128x192 with two stages where there is a table"), (5911, 1296, 384, "256x192"),
+    (6985, 784, 512, "256x128; 128x128 with two stages where there is a table"), (6001, 752, 1536, "128x192 with three stages"),
+    (6149, 912, 384, "128x192 with two stages, 128x128 for int8 without table"), (4111, 400, 512, "128x128 with three stages (int8)"),
+    (1005, 912, 512, "64x128 with three stages"), (6539, 528, 384, "64x128 with two stages")])
 def test_gemm_tile_kernel_ragged_edges_of_every_tile(oracle, M, N, K, what):
     """One shape per configuration of the large-tile kernel whose last row and column tiles are partly
     outside, down to the fewest k-slices that configuration takes."""
