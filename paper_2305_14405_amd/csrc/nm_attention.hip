@@ -489,7 +489,6 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
     const VFragments vfrag(lane);
     int mi = INT_MIN;
     float part[16], fm = 0.0f, r = 0.0f;
-    bool small = false;
     v4i a2[4];
 #pragma unroll
     for (int q = 0; q < 16; ++q) part[q] = 0.0f;
@@ -584,7 +583,14 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
         for (int q = 0; q < mask; ++q) part[q] = part[q] + part[q + mask];
     int segr;
     r = pwl_eval(row_add(part[0]), p.t_recip, s_kb_recip, segr);
-    small = attn_small(r, p);
+    // The two forms of the last pass are two copies of its barriers, so the choice is the workgroup's: a wavefront
+    // whose rows would allow the packing conversion takes the clamping form beside one whose rows do not.  (The
+    // patches are not in use yet, and the last pass begins with a barrier.)
+    int* s_small = reinterpret_cast<int*>(sO);
+    const bool wave_small = attn_small(r, p);
+    if (lane == 0) s_small[wave] = wave_small;
+    __syncthreads();
+    const bool small = __all(s_small[lane & (kLongThreads / 64 - 1)]);
     if (small) run_pass(std::integral_constant<int, 2>{}, std::true_type{});
     else run_pass(std::integral_constant<int, 2>{}, std::false_type{});
     attn_store_ctx(p, a2, sO + wave * kCtxPatch, lane, (long)b * S, q0, head, nch);

@@ -935,6 +935,55 @@ def test_encoder_layer_attention_of_long_sequences_and_small_heads(oracle, B, S,
     assert_exact(host(yq), want["y_q"], "y_q without taps")
 
 
+def sharp_layer(B, S, H, heads, inv_s_p):
+    """A layer whose attention weights spread over the int8 codes (score scale sixteen times the stored one)."""
+    cfg = dict(B=B, S=S, H=H, heads=heads, F=2 * H, nseg=64)
+    p = W.with_scales(W.layer_tensors(cfg, 5), W.stored_scales("long_seq", 0))
+    p["alpha_scores"] = float(np.float32(16 * p["alpha_scores"]))
+    p["alpha_ctx"] = float(np.float32(p["alpha_ctx"] * p["inv_s_p"] / inv_s_p))
+    p["inv_s_p"] = float(np.float32(inv_s_p))
+    return cfg, p
+
+
+def check_layer_attention(oracle, p, ot, dt, with_taps):
+    """Context and output of nm_encoder_layer (and scores and probabilities, with_taps) against the oracle."""
+    B, S, H, heads = (p[k] for k in ("B", "S", "H", "heads"))
+    want = oracle.encoder_layer(p, dict(zip(("gelu", "exp", "recip", "rsqrt"), ot)), p["x"])
+    devw = {n: dev(p[n]) for n in nm.LAYER_PTRS}
+    desc = nm.make_layer_desc(p, devw, dt)
+    ws = torch.empty(nm.nm_encoder_layer_workspace(desc), dtype=torch.uint8, device=DEV)
+    taps = dict(ctx=torch.empty((B * S, H), dtype=torch.int8, device=DEV))
+    if with_taps:
+        taps["scores"] = torch.empty((B, heads, S, S), dtype=torch.int32, device=DEV)
+        taps["p"] = torch.empty((B, heads, S, S), dtype=torch.int8, device=DEV)
+    yq = torch.empty((B * S, H), dtype=torch.int8, device=DEV)
+    nm.nm_encoder_layer(desc, dev(p["x"]), yq, None, ws, taps=taps)
+    for k in taps:
+        assert_exact(host(taps[k]), want[k], k)
+    assert_exact(host(yq), want["y_q"], "y_q")
+    return want
+
+
+@pytest.mark.parametrize("B,S,H,heads,inv_p", [(1, 513, 64, 1, None), (1, 700, 96, 2, None), (2, 200, 32, 2, None),
+                                               (1, 1024, 64, 1, 30000.0), (1, 529, 128, 2, 30000.0)])
+def test_encoder_layer_long_attention_saturating_codes(oracle, B, S, H, heads, inv_p):
+    """The attention kernel that computes its scores three times, where codes saturate: in every wavefront, or
+    (inv_p None) in some wavefronts of a workgroup of 64 queries and not in others."""
+    cfg, p = sharp_layer(B, S, H, heads, inv_p or 127.0)
+    specs = [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")]
+    ot, dt = both_tables(oracle, specs)
+    if inv_p is None:
+        sc = oracle.encoder_layer(p, dict(zip(("gelu", "exp", "recip", "rsqrt"), ot)), p["x"])["scores"].astype(np.float64)
+        r = 1.0 / np.exp((sc - sc.max(-1, keepdims=True)) * p["alpha_scores"]).sum(-1)   # a row's largest probability
+        waves = r[:, :, :S // 64 * 64].reshape(B, heads, -1, 4, 16).max(-1)
+        t = np.median(waves)
+        assert ((waves.min(-1) < 0.95 * t) & (waves.max(-1) > 1.05 * t)).any()   # the table's error is below 1 %
+        cfg, p = sharp_layer(B, S, H, heads, 127.0 / t)
+    for with_taps in (False, True):
+        want = check_layer_attention(oracle, p, ot, dt, with_taps)
+    assert (want["p"] == 127).any() and (want["p"] < 127).any()
+
+
 def test_fused_attention_unsupported_shapes():
     dt = nm.nm_build_tables([("exp", -16.0, 0.0, 64), ("recip", 1.0, 64.0, 64)])
     x = torch.zeros((8 * 96 * 3,), dtype=torch.int8, device=DEV)
