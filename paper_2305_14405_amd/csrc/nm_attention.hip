@@ -124,6 +124,11 @@ __device__ __forceinline__ unsigned attn_pack(const float (&x)[4], float r, floa
     }
     return pack4(requant(x[0] * r, inv), requant(x[1] * r, inv), requant(x[2] * r, inv), requant(x[3] * r, inv));
 }
+// The first n (any integer) of a word's four bytes; zeros behind them.
+__device__ __forceinline__ unsigned attn_keep(unsigned w, int n)
+{
+    return n >= 4 ? w : n <= 0 ? 0u : w & ((1u << (8 * n)) - 1u);
+}
 // Whether every row of the wavefront is of that kind: r >= 0 and the bounds of e times r times inv are.
 __device__ __forceinline__ bool attn_small(float r, const AttnParams& p)
 {
@@ -398,6 +403,13 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
                 const float x[4] = {__int_as_float(at[0]), __int_as_float(at[1]), __int_as_float(at[2]), __int_as_float(at[3])};
                 pf[q] = (int)attn_pack(x, r, p.inv_s_p, kSmall);
             }
+            // A masked key's code is 0 whatever r and inv_s_p are (0 times an infinity is a NaN, of code -127); what
+            // the V image holds for these keys then does not count.  In the other form r and inv_s_p are finite.
+            if (!kSmall && ragged && gg == ngroups - 1) {
+                const int left = keys_left(g);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) pf[q] = (int)attn_keep((unsigned)pf[q], left - 16 * q);
+            }
             if (kMode == EXP_ANY && p.p_out && (kFull || m < S)) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -543,6 +555,8 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
                             for (int e = 0; e < 4; ++e) part[4 * g + q] = part[4 * g + q] + x[e];
                         } else {
                             pf[q] = (int)attn_pack(x, r, p.inv_s_p, kSmall);
+                            // (0 also where r or inv_s_p is not finite: see attention_pwl_kernel)
+                            if (kMask && !kSmall) pf[q] = (int)attn_keep((unsigned)pf[q], S - k0 - 16 * q - 4 * hq);
                         }
                     }
                     if (kPass != 2) return;

@@ -984,6 +984,75 @@ def test_encoder_layer_long_attention_saturating_codes(oracle, B, S, H, heads, i
     assert (want["p"] == 127).any() and (want["p"] < 127).any()
 
 
+def spoil(table, kind, at=0):
+    """A table's lines from segment `at` on made non-finite."""
+    if kind == "nan":
+        table.b[at:] = np.nan
+    elif kind == "inf":
+        table.k[at:], table.b[at:] = 0.0, np.inf
+    elif kind == "overflow":
+        table.k[at:], table.b[at:] = -3e38, 0.0
+
+
+def arrays_tables(specs, ot):
+    """Device tables holding exactly the oracle tables' lines."""
+    return nm.nm_tables_from_arrays([(*s, t.flags) for s, t in zip(specs, ot)], [t.k for t in ot], [t.b for t in ot])
+
+
+@pytest.mark.parametrize("kind", ["nan", "inf", "overflow", "some_rows", "inv_inf", "inv_nan", "alpha"])
+@pytest.mark.parametrize("S", [7, 33, 48, 100, 129, 200, 300, 449, 496])
+def test_fused_attention_masked_keys_where_numbers_are_not_finite(oracle, S, kind):
+    """Keys beyond S have code 0, also where the reciprocal, the output scale or the row sum is not finite
+    (0 times an infinity is a NaN, whose code is -127)."""
+    heads, H = 2, 128
+    specs = [("exp", -16.0, 0.0, 64), ("recip", 1.0, float(max(64, S)), 128)]
+    ot = [oracle.build_table(OID[f], lo, hi, n) for (f, lo, hi, n) in specs]
+    g = np.random.default_rng(S)
+    qkv = np.clip(np.rint(22 * g.standard_normal((S, 3 * H))), -127, 127).astype(np.int8)
+    q, k, v = (qkv[:, i * H:(i + 1) * H].reshape(S, heads, 64).astype(np.int64) for i in range(3))
+    scores = np.einsum("ihc,jhc->hij", q, k).reshape(-1, S).astype(np.int32)
+    alpha_s = float(np.float32(2e38 if kind == "alpha" else 1.2e-3))
+    inv_p = {"inv_inf": np.inf, "inv_nan": np.nan}.get(kind, 127.0)
+    if kind == "some_rows":
+        seg = oracle.softmax_pwl(scores, alpha_s, ot[0], ot[1], inv_p)["seg_recip"]
+        spoil(ot[1], "inf", int(np.median(seg)) + (1 if np.median(seg) < seg.max() else 0))
+    else:
+        spoil(ot[1], kind)
+    with np.errstate(invalid="ignore", over="ignore"):
+        P = oracle.softmax_pwl(scores, alpha_s, ot[0], ot[1], inv_p)["q"].reshape(heads, S, S)
+    assert (P == -127).any() or (P == 127).any()
+    cacc = np.einsum("hij,jhc->ihc", P.astype(np.int64), v).reshape(S, H)
+    assert np.abs(cacc).max() < 2 ** 24
+    alpha_c, inv_c = float(np.float32(2.0e-3)), float(np.float32(0.4))
+    cv = (cacc.astype(np.float32) * np.float32(alpha_c)).astype(np.float32)
+    want = np.clip(np.rint((cv * np.float32(inv_c)).astype(np.float32)), -127, 127).astype(np.int8)
+    dt = arrays_tables(specs, ot)
+    ctx = torch.empty((S, H), dtype=torch.int8, device=DEV)
+    nm.nm_attention_pwl(dev(qkv), 1, S, H, heads, alpha_s, dt, 0, 1, inv_p, alpha_c, inv_c, ctx)
+    assert_exact(host(ctx), want, "context")
+    pp = torch.empty((1, heads, S, S), dtype=torch.int8, device=DEV)
+    nm.nm_attention_pwl(dev(qkv), 1, S, H, heads, alpha_s, dt, 0, 1, inv_p, alpha_c, inv_c, ctx, None, pp)
+    assert_exact(host(ctx), want, "context, probabilities written")
+    assert_exact(host(pp)[0], P, "probabilities")
+
+
+@pytest.mark.parametrize("kind", ["nan", "inf", "some_rows"])
+@pytest.mark.parametrize("B,S,H,heads", [(1, 513, 64, 1), (1, 700, 96, 2), (2, 70, 32, 2), (1, 40, 96, 3)])
+def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(oracle, B, S, H, heads, kind):
+    """The same in the kernel that computes its scores three times."""
+    cfg, p = sharp_layer(B, S, H, heads, 10000.0)
+    specs = [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")]
+    ot = [oracle.build_table(OID[f], lo, hi, n) for (f, lo, hi, n) in specs]
+    at = 0
+    if kind == "some_rows":
+        sc = oracle.encoder_layer(p, dict(zip(("gelu", "exp", "recip", "rsqrt"), ot)), p["x"])["scores"].reshape(-1, S)
+        seg = oracle.softmax_pwl(np.ascontiguousarray(sc), p["alpha_scores"], ot[1], ot[2], p["inv_s_p"])["seg_recip"]
+        at = int(seg.max())
+    spoil(ot[2], "inf" if kind == "some_rows" else kind, at)
+    for with_taps in (False, True):
+        check_layer_attention(oracle, p, ot, arrays_tables(specs, ot), with_taps)
+
+
 def test_fused_attention_unsupported_shapes():
     dt = nm.nm_build_tables([("exp", -16.0, 0.0, 64), ("recip", 1.0, 64.0, 64)])
     x = torch.zeros((8 * 96 * 3,), dtype=torch.int8, device=DEV)
