@@ -74,6 +74,14 @@ static float two_segment_threshold(float lo, float inv_w)
     return to_float(b);
 }
 
+// A NaN has no bounds: both become infinite and stay so.
+static void widen_bounds(double v, double* vmin, double* vmax)
+{
+    const double inf = std::numeric_limits<double>::infinity();
+    *vmin = std::isnan(v) ? -inf : std::fmin(*vmin, v);
+    *vmax = std::isnan(v) ? inf : std::fmax(*vmax, v);
+}
+
 // What kernels and launchers use of a finished table besides its lines.
 static void derive_table(HostTable& h)
 {
@@ -91,9 +99,7 @@ static void derive_table(HostTable& h)
     for (int s = 0; s < d.nseg; ++s)
         for (int end = 0; end < 2; ++end) {
             const double x = d.lo + (s + end) * w + (end ? slack : -slack);
-            const double v = (double)h.k[s] * x + (double)h.b[s];
-            if (!(v >= vmin)) vmin = v;   // a NaN sticks and fails every later comparison
-            if (!(v <= vmax)) vmax = v;
+            widen_bounds((double)h.k[s] * x + (double)h.b[s], &vmin, &vmax);
         }
     h.bounds = {vmin, vmax, h.k.front(), h.b.front(), h.k.back(), h.b.back()};
 }
@@ -103,9 +109,8 @@ void table_value_bounds(const nm_tables* t, int32_t idx, double xmin, double xma
     const HostTable& h = t->tables[idx];
     double lo = h.bounds.vmin, hi = h.bounds.vmax;
     if (!(h.desc.flags & NM_TABLE_CLAMP_INPUT)) {
-        auto take = [&](double v) { if (!(v >= lo)) lo = v; if (!(v <= hi)) hi = v; };
-        if (xmin < h.desc.lo) take(h.bounds.k_first * xmin + h.bounds.b_first);
-        if (xmax > h.desc.hi) take(h.bounds.k_last * xmax + h.bounds.b_last);
+        if (xmin < h.desc.lo) widen_bounds(h.bounds.k_first * xmin + h.bounds.b_first, &lo, &hi);
+        if (xmax > h.desc.hi) widen_bounds(h.bounds.k_last * xmax + h.bounds.b_last, &lo, &hi);
     }
     // past the rounding of the fp32 evaluation
     *vmin = lo - 1e-5 * std::fabs(lo) - 1e-30;

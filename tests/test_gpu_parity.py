@@ -1053,6 +1053,36 @@ def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(o
         check_layer_attention(oracle, p, ot, arrays_tables(specs, ot), with_taps)
 
 
+@pytest.mark.parametrize("S,nseg", [(64, 64), (128, 100), (200, 64), (449, 100)])
+@pytest.mark.parametrize("negative", [False, True])
+def test_fused_attention_exp_table_with_a_nan(oracle, S, nseg, negative):
+    """An exp table with a NaN in one segment, and a reciprocal table whose input clamp turns the row's NaN sum into a
+    number: the NaN's code is -127, and negative values in front of the NaN keep their negative codes."""
+    heads, H = 2, 128
+    specs = [("exp", -16.0, 0.0, nseg), ("recip", 1.0, float(max(64, S)), 128)]
+    ot = [oracle.build_table(OID[f], lo, hi, n, flags=fl) for (f, lo, hi, n), fl in zip(specs, (0, 1))]
+    at = nseg - nseg // 8
+    ot[0].b[at] = np.nan
+    if negative:
+        ot[0].k[at - 4:at], ot[0].b[at - 4:at] = 0.0, -0.75
+    g = np.random.default_rng(S + nseg)
+    qkv = np.clip(np.rint(22 * g.standard_normal((S, 3 * H))), -127, 127).astype(np.int8)
+    q, k, v = (qkv[:, i * H:(i + 1) * H].reshape(S, heads, 64).astype(np.int64) for i in range(3))
+    scores = np.einsum("ihc,jhc->hij", q, k).reshape(-1, S).astype(np.int32)
+    alpha_s, inv_p = float(np.float32(2e-4)), 100.0
+    sm = oracle.softmax_pwl(scores, alpha_s, ot[0], ot[1], inv_p)
+    P = sm["q"].reshape(heads, S, S)
+    assert (P == -127).any() and (P > 0).any() and ((P < 0) & (P > -127)).any() == negative
+    cacc = np.einsum("hij,jhc->ihc", P.astype(np.int64), v).reshape(S, H)
+    assert np.abs(cacc).max() < 2 ** 24
+    alpha_c, inv_c = float(np.float32(2.0e-3)), float(np.float32(0.4))
+    cv = (cacc.astype(np.float32) * np.float32(alpha_c)).astype(np.float32)
+    want = np.clip(np.rint((cv * np.float32(inv_c)).astype(np.float32)), -127, 127).astype(np.int8)
+    ctx = torch.empty((S, H), dtype=torch.int8, device=DEV)
+    nm.nm_attention_pwl(dev(qkv), 1, S, H, heads, alpha_s, arrays_tables(specs, ot), 0, 1, inv_p, alpha_c, inv_c, ctx)
+    assert_exact(host(ctx), want, "context")
+
+
 def test_fused_attention_unsupported_shapes():
     dt = nm.nm_build_tables([("exp", -16.0, 0.0, 64), ("recip", 1.0, 64.0, 64)])
     x = torch.zeros((8 * 96 * 3,), dtype=torch.int8, device=DEV)
