@@ -127,7 +127,7 @@ __device__ __forceinline__ unsigned attn_pack(const float (&x)[4], float r, floa
 // The first n (any integer) of a word's four bytes; zeros behind them.
 __device__ __forceinline__ unsigned attn_keep(unsigned w, int n)
 {
-    return n >= 4 ? w : n <= 0 ? 0u : w & ((1u << (8 * n)) - 1u);
+    return w & (unsigned)(0xffffffffull >> (8 * (4 - min(max(n, 0), 4))));
 }
 // Whether every row of the wavefront is of that kind: r >= 0 and the bounds of e times r times inv are.
 __device__ __forceinline__ bool attn_small(float r, const AttnParams& p)
