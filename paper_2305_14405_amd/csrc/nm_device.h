@@ -26,9 +26,14 @@ __device__ __forceinline__ int seg_index(float x, float lo, float inv_w, int nse
     return (int)u;
 }
 
-// float -> unsigned, truncating and saturating (negative and NaN -> 0): what v_cvt_u32_f32, the instruction
-// behind the conversion of a value the compiler knows nothing about, does (checked for every float).
-__device__ __forceinline__ unsigned cvt_u32_sat(float x) { return (unsigned)x; }
+// float -> unsigned, truncating and saturating (negative and NaN -> 0).  The language leaves the conversion of a
+// negative float undefined, so the instruction that does this is named.
+__device__ __forceinline__ unsigned cvt_u32_sat(float x)
+{
+    unsigned u;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(u) : "v"(x));
+    return u;
+}
 
 // y = k[s]*x + b[s] (one fma).  kb may point to LDS or to global memory.
 __device__ __forceinline__ float pwl_eval(float x, const DevTable& t, const float2* kb, int& seg)
