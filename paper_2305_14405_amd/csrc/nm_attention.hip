@@ -76,29 +76,11 @@ constexpr size_t attn_lds_bytes(int nkb) { return 2 * (size_t)nkb * 64 * 64 + (s
 
 typedef int v2i_t __attribute__((ext_vector_type(2)));
 
-// op(v, value of lane ^ MASK) for MASK 32 or 16 with the half / row swap instructions: swapping a
-// register with a copy of itself leaves {lower halves (even rows) twice} in one and {upper halves
-// (odd rows) twice} in the other; op is commutative, so op(first, second) is what every lane needs.
-template <int MASK, typename Op>
-__device__ __forceinline__ int swap_reduce(int v, Op op)
-{
-    if (MASK == 32) {
-        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-        return op((int)r[0], (int)r[1]);
-    }
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-    return op((int)r[0], (int)r[1]);
-}
-__device__ __forceinline__ int row_max(int v)
-{
-    const auto op = [](int a, int b) { return max(a, b); };
-    return swap_reduce<16>(swap_reduce<32>(v, op), op);
-}
-__device__ __forceinline__ float row_add(float v)
-{
-    const auto op = [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); };
-    return __int_as_float(swap_reduce<16>(swap_reduce<32>(__float_as_int(v), op), op));
-}
+// Over the four lanes (m, 0..3) of a query: lane ^ 32, then lane ^ 16.
+template <typename Op>
+__device__ __forceinline__ int query_reduce(int v, Op op) { return butterfly_step<16>(butterfly_step<32>(v, op), op); }
+__device__ __forceinline__ int row_max(int v) { return query_reduce(v, MaxI32{}); }
+__device__ __forceinline__ float row_add(float v) { return __int_as_float(query_reduce(__float_as_int(v), AddF32{})); }
 
 // PWL exp of one score; acc and row maximum as biased accumulators.
 template <int kMode>

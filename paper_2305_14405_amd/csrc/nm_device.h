@@ -125,8 +125,7 @@ __device__ __forceinline__ void stage_table(float2* dst, const DevTable& t)
 
 // Two-level form of a merged table (paper Algorithm 2: neighbouring primary segments with nearly
 // equal slope share one line): nkb {k, b} pairs, then one byte per primary cell naming its merged
-// segment.  LDS bytes: 8 * nkb + nseg (instead of 8 * nseg).
-__device__ __forceinline__ size_t two_level_bytes(const DevTable& t) { return 8 * (size_t)t.nkb + (((size_t)t.nseg + 7) & ~(size_t)7); }
+// segment.  LDS bytes: two_level_bytes (instead of 8 * nseg).
 __device__ __forceinline__ void stage_table_two_level(float2* dst, const DevTable& t)
 {
     for (int i = threadIdx.x; i < t.nkb; i += blockDim.x) dst[i] = t.ckb[i];

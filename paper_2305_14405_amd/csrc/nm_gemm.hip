@@ -804,7 +804,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // LDS bytes of the table: {k, b} per segment, or for the two-level form of a merged table one
     // {k, b} per merged segment plus a byte per primary cell
     const size_t table_bytes = !g.has_table ? 0
-                             : g.table.cellmap ? 8 * (size_t)g.table.nkb + (((size_t)g.table.nseg + 7) & ~(size_t)7)
+                             : g.table.cellmap ? two_level_bytes(g.table)
                                                : sizeof(float2) * (size_t)g.table.nseg;
     const int batches = g.outer_count * g.inner_count;
     if (batches > 65535) return fail(NM_ERR_UNSUPPORTED, "gemm: more than 65535 batched problems");

@@ -34,6 +34,9 @@ struct DevTable {
     float u0;
 };
 
+// Bytes of the two-level form: {k, b} per merged segment, a byte per primary cell (padded to eight).
+inline size_t two_level_bytes(const DevTable& t) { return 8 * (size_t)t.nkb + (((size_t)t.nseg + 7) & ~(size_t)7); }
+
 // Whether the int8 code of the table's value is that of max(x, 0) for every finite x: the two lines are 0 and x,
 // and between 0 and the threshold (where the float index puts it) either line's value rounds to code 0.
 inline bool relu_codes(const DevTable& t, float out_inv_scale, float resid_scale)

@@ -551,7 +551,7 @@ int32_t nm_pwl_apply(const void* in, int32_t in_dtype, float alpha, int64_t n,
     const bool vec = aligned(in, 16) && (!out_f32 || aligned(out_f32, 16)) &&
                      (!out_q || aligned(out_q, 4)) && (!dbg_seg || aligned(dbg_seg, 8));
     const bool two = t.cellmap != nullptr;  // two-level form: merged segments + one byte per cell
-    const size_t shmem = two ? 8 * (size_t)t.nkb + (((size_t)t.nseg + 7) & ~(size_t)7) : sizeof(float2) * (size_t)t.nseg;
+    const size_t shmem = two ? two_level_bytes(t) : sizeof(float2) * (size_t)t.nseg;
     // vector path: one 32 KB span per block up to 2^20 blocks (one span per block measured 3 % faster
     // at 2^26 elements than 4096 blocks looping over two spans each)
     const int blocks = vec ? blocks_for((n + 3) / 4, kRowThreads * kApplyGroupsPerTrip, 1L << 20)
