@@ -1218,6 +1218,33 @@ def test_encoder_block_kernel_edges(oracle, B, S, H, heads, F, n_layers, biases)
     assert_f32_close(host(yf), want["y_f32"], "y_f32 alone")
 
 
+@pytest.mark.parametrize("flags", [nm.NM_TABLE_CLAMP_INPUT, nm.NM_TABLE_MERGE, nm.NM_TABLE_MERGE | nm.NM_TABLE_COMPACT,
+                                   nm.NM_TABLE_MERGE | nm.NM_TABLE_COMPACT | nm.NM_TABLE_CLAMP_INPUT])
+@pytest.mark.parametrize("B,S,H,heads,F", [(3, 5, 48, 3, 80), (1, 33, 256, 4, 1024), (129, 32, 320, 5, 1280)])
+def test_encoder_block_kernel_table_forms(oracle, B, S, H, heads, F, flags):
+    """The same kernel on tables whose inputs are clamped and on merged ones, in both their forms, with ranges that the
+    inputs leave on both sides."""
+    cfg = dict(B=B, S=S, H=H, heads=heads, F=F, nseg=64)
+    ps = [W.with_scales(W.layer_tensors(cfg, 17 + i), W.stored_scales("tiny", 0)) for i in range(2)]
+    names = ("gelu", "exp", "recip", "rsqrt")
+    specs = [("gelu", -0.4, 0.4, 16), ("exp", -1.0, 0.0, 32), ("recip", 1.0, float(max(64, S)), 64), ("rsqrt", 0.7, 1.1, 64)]
+    clamp = oracle.FLAG_CLAMP_INPUT if flags & nm.NM_TABLE_CLAMP_INPUT else 0
+    ot = [oracle.build_table_merged(OID[f], lo, hi, n, 0.05, flags=clamp)[0] if flags & nm.NM_TABLE_MERGE else
+          oracle.build_table(OID[f], lo, hi, n, flags=clamp) for (f, lo, hi, n) in specs]
+    dt = nm.nm_tables_from_arrays([(*s, flags) for s in specs], [t.k for t in ot], [t.b for t in ot])
+    plain = [oracle.build_table(OID[f], lo, hi, n) for (f, lo, hi, n) in specs]
+    want = oracle.encoder_stack(ps, dict(zip(names, ot)), ps[0]["x"])
+    assert (want["y_q"] != oracle.encoder_stack(ps, dict(zip(names, plain)), ps[0]["x"])["y_q"]).any()
+    devws = [{n: dev(p[n]) for n in nm.LAYER_PTRS} for p in ps]
+    descs = [nm.make_layer_desc(p, devw, dt) for p, devw in zip(ps, devws)]
+    ws = torch.empty(nm.nm_encoder_stack_workspace(descs), dtype=torch.uint8, device=DEV)
+    yq = torch.empty((B * S, H), dtype=torch.int8, device=DEV)
+    yf = torch.empty((B * S, H), dtype=torch.float32, device=DEV)
+    nm.nm_encoder_stack(descs, dev(ps[0]["x"]), yq, yf, ws)
+    assert_exact(host(yq), want["y_q"], "y_q")
+    assert_f32_close(host(yf), want["y_f32"], "y_f32")
+
+
 @pytest.mark.parametrize("name,n_layers,batch", [("bert_base_s512", 12, None), ("bert_large_s512", 24, 8)])
 def test_encoder_stack_full_depth(oracle, name, n_layers, batch):
     """The 12-layer and the 24-layer workloads at their full depth, every layer with weights and
