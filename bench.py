@@ -27,12 +27,13 @@ PEAK_INT8_TOPS = 5000.0   # MI355X dense int8 MFMA, published: 5.0 POP/s
 PEAK_HBM_GBS = 8000.0     # MI355X HBM3E, published: 8 TB/s
 # Plain vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-operations/s (one
 # operation per lane per clock; the published 157.3 TFLOP/s counts packed two-wide FMAs, which this
-# build does not emit).  The fused attention kernel is bound by it: per score the method's
-# definition needs 18 scalar operations (row max 1; subtract, convert, scale 3; segment index:
-# subtract, multiply, two-sided clamp, floor 5; k*t+b 1; row-sum add 1; e*r 1; requantisation:
-# multiply, round, two-sided clamp, convert 5; the look-up itself not counted).
+# build does not emit).  The fused attention kernel is bound by it: per score its loops execute 10.5
+# vector instructions (row max 0.5; subtract, scale 2; segment index: fma, convert, address 3; k*t+b 1;
+# row-sum add 1; e*r 1; requantisation: multiply, convert-and-pack 2; the look-up itself not counted).
+# The fraction is that of these: what a wavefront issues once for all its scores comes on top (16.0 in
+# all at 512 keys, by counter).
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-ATTN_OPS_PER_SCORE = 18.0
+ATTN_OPS_PER_SCORE = 10.5
 
 # HBM-side traffic per launch comes from two rocprofv3 --pmc runs of this script (FETCH_SIZE, then
 # WRITE_SIZE; KiB per dispatch), each scaled by what the same counter reads for a plain 64 MiB device
@@ -326,7 +327,7 @@ def bench_encoder(args):
     roofline = dict(bound=dom["bound"], achieved=dom["achieved"], peak=dom["peak"], unit=dom["unit"],
                     frac=dom["frac"], traffic=dom["traffic"], kernel=dom["kernel"],
                     note="int8 MFMA rate (2 operations per multiply-accumulate)" if dom["bound"] == "mfma"
-                    else "plain vector ALU, 18 scalar operations per attention score")
+                    else "plain vector ALU, 10.5 vector instructions per attention score")
     gemm_ops = sum(2.0 * M * n * k for n, k in ((3 * H, H), (H, H), (F, H), (H, F)))
     gemm_ms = sum(k["ms"] for k in kernels if k["bound"] == "mfma" and k["in_layer"])
     row_bytes = float(B * nh * S * S * 5 + 2 * M * H * 5)
