@@ -22,8 +22,12 @@
 // of the eight rows addressed by lanes j / 8, j / 8 + 2, ...), with the row addresses chosen so
 // that the keys arrive in the order the probabilities have in the lanes.
 //
-// What bounds it: vector instructions per score (matrix work is a tenth).  They are kept to ten and
-// a half plus the table's LDS read (18 before), each step with the same value as the normative one:
+// What bounds it: vector instructions (matrix work is a tenth).  By counter 16.0 per score at 32 x 512 tokens and
+// 16 heads, issued in 91 % of the cycles, and 18.5 at 32 x 128 and 12 heads (18.9 in 67 %, and 24.5, before the
+// steps below).  Ten and a half of them, and the table's LDS read, are the loops over the scores (18 before); the
+// rest is paid once per 16 queries and up to 256 keys: addresses of the loads and of the transposing reads,
+// accumulator start values, table staging, the exchange between wavefronts, the context's codes.  The loops' steps
+// have the same values as the normative ones:
 //  * the score accumulators start at the bits of the float 1.5 * 2^23, so an accumulator read as a float
 //    is 1.5 * 2^23 + score exactly (|score| <= 2^20) and the difference of two is the exact difference
 //    of the scores: no conversion; and their integer order is the order of the scores;
@@ -210,10 +214,12 @@ __device__ __forceinline__ int attn_block_id(int total)
 // share 16 queries (kSplit): half h takes the 64-key groups 2h, 2h + 1, 4 + 2h, 5 + 2h, i.e. the
 // accumulators 32h .. 32h + 31 of the row sum with all their elements; the halves exchange their row
 // maxima, their accumulators at the butterfly's first step (mask 32) and their partial contexts
-// (exact integers) through the K image, which is free by then.  With all 512 keys in one wavefront (128
-// score registers, two wavefronts per SIMD) the vector units were busy 44 % of the time; now 89 %.
-// us per launch before -> after: 32 x 512 tokens, 16 heads 120 -> 69; 16 x 512, 12 heads 42 -> 30; 8 x 300, 12
-// heads 38 -> 8.6; 32 x 128, 12 heads 7.8 -> 6.7; 11 x 77, 12 heads 6.3 -> 4.9.
+// (exact integers) through the K image, which is free by then.  (With all 512 keys in one wavefront it had 128
+// score registers, and two wavefronts a SIMD.)
+// us per launch, one behind the other, against the kernel before these steps: 32 x 512 tokens, 16 heads 98 -> 63;
+// with 12 heads 16 x 512 39 -> 25, 16 x 384 59 -> 20, 8 x 300 37 -> 8.1, 16 x 256 10 -> 8.1, 32 x 128 6.7 -> 5.6, 11 x 77 5.9 ->
+// 4.4, 32 x 64 3.9 -> 3.6.  In the 24- and 12-layer stacks, beside operands that come from further away, the first two take
+// 73 and 30.
 template <int NKB, bool kFull, int kMode>
 __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_per_eu(4))) void attention_pwl_kernel(AttnParams p)
 {
@@ -429,11 +435,11 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
 
 // Sequences whose scores do not fit a wavefront's registers (more than 512 keys) and head sizes 16, 32 and
 // 48: the scores are computed three times, for the row maximum, for the sum and for the probabilities
-// (matrix work is cheap: 17.5 vector instructions per score instead of 10.5, and no score or
+// (matrix work is cheap: 22.3 vector instructions per score by counter at 4 x 640 tokens, and no score or
 // probability goes to memory).  K, and V in the last pass, come through LDS in chunks of 256 keys, the
 // next chunk loading while one is used.  A workgroup is four wavefronts of 16 queries.
-// Four sequences of 640 tokens, 12 heads of 64: scores, softmax and context as three kernels took 21 + 20
-// + 15 us.
+// Four sequences of 640 tokens, 12 heads of 64: 22 us; scores, softmax and context as three kernels took 21 + 20
+// + 15.
 constexpr int kLongThreads = 256, kLongKeys = 256;
 constexpr size_t kLongLds = 4 * (size_t)kLongKeys * 64 + (kLongThreads / 64) * (size_t)kCtxPatch;
 
