@@ -725,7 +725,9 @@ bool gemm_folds_layernorm(const GemmArgs& g)
 // 4096 x 768 x 3072 with 128x128.  The constants are least-squares fits to 180 measured shapes: M from 64 to
 // 16384, the four products of a layer of width 512, 768 and 1024.  Over those the chosen tile is 1.2 % slower than
 // the best of the nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
-// were 7 % (54 %) slower from M = 2048 on.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
+// were 7 % (54 %) slower from M = 2048 on.  On 106 shapes outside the fit (widths 384, 640, 896, 1152, 1280 and 1536, FFNs
+// of 4 H and 2 H + 128, M drawn up to 16384) it is 1.6 % slower than the best, at a tenth of them 6 % or more, at the
+// two worst 38 % (1683 x 4608 x 1536) and 11 %.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
 // 128x128 likewise | 64x128 likewise:
 //   16384 x 1024 x 4096, fp32:   64 | 87 | 72 | 84 | 79 | 89 | 77
 //   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
@@ -873,13 +875,22 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                          g.N % 16 == 0 && g.split_cols % 4 == 0 && (int64_t)g.M * g.lda < (1LL << 32) &&
                          (int64_t)g.N * g.ldw < (1LL << 32) && table_bytes <= 40 * 1024;
     // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
-    // chosen when the output is too small for the larger tiles to occupy the chip: the tile kernel needs
-    // about 110 tiles of 64x128 (us with operands in L2, this one and the best tile: 512 x 2304 x 768 6.7, 4.6; 1500 x 768 x 3072
-    // 15, 9.2; 512 x 768 x 3072 7.0, 8.7; at 847 x 768 the tiles are ahead by a tenth there, but in a stack, where
-    // the weights come from memory, 84 workgroups keep too few loads in flight: 12 layers 575 us against 561) and more with three k-slices, the streaming kernel's tiles
+    // chosen when the output is too small for the larger tiles to occupy the chip, and for operands the other
+    // loaders do not read 16 bytes at a time (4096x1000x1000: 27 us against the generic kernel's 106).
+    // Against the tile kernel with more than three k-slices the line is 0.9 million outputs, between two: tiles over
+    // this kernel, products of layers of width 512 to 1024, geometric means (best to worst), with the weights of launch
+    // after launch in the caches and from memory:
+    //   million outputs   0.35   0.5    0.65              0.8               0.95              1.15   1.4
+    //   in the caches     1.18   1.04   0.89 (.77..1.08)  0.89 (.80..1.04)  0.87 (.79..0.98)  0.73   0.72
+    //   from memory       1.27   1.17   1.00 (.85..1.30)  0.98 (.84..1.28)  0.97 (.87..1.23)  0.81   0.80
+    // The losses are fp32 outputs of a long contraction, where few workgroups keep few loads in flight (847 x 768 x 3072
+    // from memory 10.9 us, tiles 13.5; 635 x 1024 x 4096 12.5, 16.2).  Stacks of 12 layers whose fp32 products have 0.65
+    // to 0.79 million outputs, widths 512, 768 and 1024: this kernel ahead by 2 to 8 % at all seven with the weights from
+    // memory (11 x 77 tokens, width 768: 551 us, tiles 573), between 4 % behind and 1 % ahead with the same weights again.
+    // With three k-slices (K = 384) the line, 2.45 million, was drawn when the tiles had three stages; with two they lost at 0.65
+    // million (6 %) and win from 1.15 on (10 %; 26 % at 1.4).  The streaming kernel's tiles need
     // about a million outputs, more when the contraction is short and a large tile is mostly prologue and
-    // epilogue; and for operands the other loaders do not read 16 bytes at a time (4096x1000x1000:
-    // 27 us against the generic kernel's 106).
+    // epilogue.
     const int64_t a_extent = g.conv ? (int64_t)(g.M / (g.cHo * g.cWo)) * g.cH * g.cW * g.cCin : (int64_t)(g.M - 1) * g.lda + g.K;
     const bool direct_ok = !force_generic() && !g.w_is_kn && a_extent < (1LL << 31) && (int64_t)(g.N - 1) * g.ldw + g.K < (1LL << 31);
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
