@@ -1083,6 +1083,15 @@ def test_fused_attention_exp_table_with_a_nan(oracle, S, nseg, negative):
     assert_exact(host(ctx), want, "context")
 
 
+@pytest.mark.parametrize("B,S,H,heads", [(2, 33, 40, 5), (1, 70, 256, 2), (1, 520, 160, 2)])
+def test_encoder_layer_separate_attention_steps(oracle, B, S, H, heads):
+    """Head sizes that no fused attention kernel takes (8, 128, 80): scores, softmax and context as three kernels."""
+    cfg, p = sharp_layer(B, S, H, heads, 2000.0)
+    ot, dt = both_tables(oracle, [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")])
+    for with_taps in (False, True):
+        check_layer_attention(oracle, p, ot, dt, with_taps)
+
+
 def test_fused_attention_unsupported_shapes():
     dt = nm.nm_build_tables([("exp", -16.0, 0.0, 64), ("recip", 1.0, 64.0, 64)])
     x = torch.zeros((8 * 96 * 3,), dtype=torch.int8, device=DEV)
