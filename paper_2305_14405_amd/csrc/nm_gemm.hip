@@ -12,8 +12,9 @@
 // Here: gemm_stream_kernel (aligned operands, K a multiple of 64: operands go global -> LDS
 // directly; also gathers the rows of a convolution's patch matrix on the fly) in several tile
 // configurations, and gemm_pwl_kernel (any shape and alignment, W as [N,K] or [K,N], operands through
-// registers); large plain products take the tile kernel (nm_gemm_tile.h), small outputs and unaligned
-// operands the small-tile kernel (nm_gemm_direct.hip).  launch_gemm chooses.
+// registers); large plain products take the tile kernel (nm_gemm_tile.h), small outputs the small-tile
+// kernel (nm_gemm_direct.hip), and unaligned operands that one or the register-staged tile kernel
+// (nm_gemm_unaligned.hip).  launch_gemm chooses.
 //
 // Operand roles: the MFMA's first operand supplies the rows of its 32x32 result and the second
 // the columns.  W rows (output columns n) go first and A rows (output rows m) second, so a lane
@@ -38,7 +39,7 @@ static bool force_generic()
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-3> forces
+// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-3>|unaligned<0-3> forces
 // that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
 // 256x192 configuration, which the tile kernel has replaced).
 static int forced_cfg()
@@ -48,6 +49,7 @@ static int forced_cfg()
         if (!e) return -1;
         static const char* const names[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
         if (!strncmp(e, "direct", 6)) return 10 + atoi(e + 6);
+        if (!strncmp(e, "unaligned", 9)) return 20 + atoi(e + 9);
         for (int i = 0; i < 7; ++i)
             if (!strcmp(e, names[i])) return i;
         return -1;
@@ -875,8 +877,8 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                          g.N % 16 == 0 && g.split_cols % 4 == 0 && (int64_t)g.M * g.lda < (1LL << 32) &&
                          (int64_t)g.N * g.ldw < (1LL << 32) && table_bytes <= 40 * 1024;
     // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
-    // chosen when the output is too small for the larger tiles to occupy the chip, and for operands the other
-    // loaders do not read 16 bytes at a time (4096x1000x1000: 27 us against the generic kernel's 106).
+    // chosen when the output is too small for the larger tiles to occupy the chip, and for unaligned operands
+    // that the register-staged tiles do not take.
     // Against the tile kernel with more than three k-slices the line is 0.9 million outputs, between two: tiles over
     // this kernel, products of layers of width 512 to 1024, geometric means (best to worst), with the weights of launch
     // after launch in the caches and from memory:
@@ -897,7 +899,17 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
     const int64_t direct_below = tile_ok ? (g.K <= 384 ? 2450000 : 900000) : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
-    const bool direct = direct_ok && (forced_cfg() >= 10 || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
+    const bool direct = direct_ok && ((forced_cfg() >= 10 && forced_cfg() < 20) || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
+    // Register-staged tiles, for operands that cannot go to LDS directly in whole slices: from 0.8 million outputs on.  Below
+    // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do
+    // (8000 x 100 x 777 11.4, 8.5; 1220 x 751 x 40 7.2, 6.5; 1000 x 999 x 999 11.2, 9.9).
+    const bool unaligned = direct_ok && !g.conv && batches == 1 && g.N >= 4 &&
+                           (forced_cfg() >= 20 || (forced_cfg() < 0 && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000));
+    if (unaligned) {
+        rc = launch_unaligned(p, direct_align, table_bytes, forced_cfg() - 20 >= 0 ? forced_cfg() - 20 : -1, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "gemm launch");
+    }
     if (direct) {
         rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced_cfg() - 10 >= 0 ? forced_cfg() - 10 : -1, stream);
         if (rc) return rc;

@@ -58,12 +58,93 @@ struct GemmParams {
 // 1); forced: tile configuration 0 .. 3, or -1 for the rule.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s);
 
+// The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).
+int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s);
+
+// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernel hands XCD x the
+// x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
+// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the
+// r (a divisor of the eighth, with whole columns: tiles_n % c == 0) that makes this sum smallest.
+static inline int xcd_group_rows(int tiles_m, int tiles_n, int BM, int BN)
+{
+    const int ntiles = tiles_m * tiles_n;
+    if (ntiles % 8 != 0) return 8;
+    const int share = ntiles / 8;
+    int best = 8;
+    long best_cost = -1;
+    for (int r = 1; r <= tiles_m && r <= share; ++r) {
+        if (share % r != 0 || tiles_m % r != 0) continue;
+        const int c = share / r;
+        if (c > tiles_n || tiles_n % c != 0) continue;
+        const long cost = (long)r * BM + (long)c * BN;
+        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = r;
+    }
+    return best;
+}
+
 // XOR swizzle of the 16-byte chunk index inside a 64-byte LDS row: rows that fall into the same
 // bank window get different chunk positions, for both a 128-byte and a 256-byte wide LDS port.
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 3) ^ ((row >> 2) & 3); }
 
 __device__ __forceinline__ int lds_off(int row, int chunk) { return row * kBK + ((chunk ^ swz(row)) << 4); }
 
+
+// ---- operands of any alignment, through registers ------------------------------------------------
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr unsigned kOutOfRange = 0xc0000000u;  // past the end of every buffer (their extents are below 2^31)
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
+}
+
+__device__ __forceinline__ v4i buf16(rsrc_t r, unsigned off)
+{
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+    return v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+}
+__device__ __forceinline__ unsigned buf4(rsrc_t r, unsigned off)
+{
+    return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+}
+
+// kAl: bytes every row start and every 16-byte chunk is aligned to (4: whole words, 1: any; the latter reads
+// the words around the chunk and shifts).
+template <int kAl>
+__device__ __forceinline__ v4i load_unit(rsrc_t r, unsigned off)
+{
+    if (kAl == 4) return buf16(r, off);
+    const unsigned base = off & ~3u, sh = off & 3u;
+    const v4i w = buf16(r, base);
+    const unsigned w4 = buf4(r, base + 16);
+    v4i o;
+    o[0] = (int)__builtin_amdgcn_alignbyte((unsigned)w[1], (unsigned)w[0], sh);
+    o[1] = (int)__builtin_amdgcn_alignbyte((unsigned)w[2], (unsigned)w[1], sh);
+    o[2] = (int)__builtin_amdgcn_alignbyte((unsigned)w[3], (unsigned)w[2], sh);
+    o[3] = (int)__builtin_amdgcn_alignbyte(w4, (unsigned)w[3], sh);
+    return o;
+}
+// The same for the last, partly filled k-step: word by word (each is inside the buffer or reads as
+// zero), bytes at and past `left` (the number of valid ones, possibly <= 0) cleared.
+template <int kAl>
+__device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
+{
+    const unsigned base = off & ~3u, sh = kAl == 4 ? 0u : off & 3u;
+    unsigned w[5];
+#pragma unroll
+    for (int t = 0; t < 5; ++t) w[t] = buf4(r, left > 0 ? base + 4 * t : kOutOfRange);
+    v4i o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const unsigned v = kAl == 4 ? w[t] : __builtin_amdgcn_alignbyte(w[t + 1], w[t], sh);
+        const int nb = left - 4 * t;  // valid bytes of this word
+        o[t] = nb >= 4 ? (int)v : nb <= 0 ? 0 : (int)(v & ((1u << (8 * nb)) - 1u));
+    }
+    return o;
+}
+
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32_a1 __attribute__((aligned(1)));
 
 enum { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_TABLE2 = 7 };
 // EPI_Q_TABLE2: EPI_Q_TABLE for a merged table in its two-level form (one byte per primary cell naming the
@@ -86,6 +167,7 @@ __device__ __forceinline__ int lds_off_bk(int row, int chunk)
 }
 
 // ---------------------------------------------------------------------------------------------
+
 // Epilogue shared by the kernels of any option.  A lane holds, for one output row m, four consecutive columns
 // nb .. nb+3 (one group of four accumulator registers).
 // ---------------------------------------------------------------------------------------------

@@ -14,69 +14,13 @@
 // not waited for until then, and all kernel arguments are fetched in one step (together 0.4 .. 1.5 us of
 // a launch).  Measured, us before -> after, weights from HBM: 128x768x3072 13.9 -> 5.3, 128x3072x768 8.6 ->
 // 5.0, 64x128x128 6.4 -> 2.9 (an empty launch is 1.6), 847x768x3072 15.0 -> 10.9, 3x3 convolution of
-// 512 channels at 7x7 28.9 -> 6.7, 4096x1000x1000 (rows aligned to 8 bytes) 106 -> 27.
+// 512 channels at 7x7 28.9 -> 6.7.
 //
 // Operands that are not 16-byte aligned come through registers and buffer descriptors: words past the end
 // of the buffer read as zero, bytes past K are cleared.
 #include "nm_gemm_common.h"
 
 namespace nm {
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr unsigned kOutOfRange = 0xc0000000u;  // past the end of every buffer (their extents are below 2^31)
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
-}
-
-__device__ __forceinline__ v4i buf16(rsrc_t r, unsigned off)
-{
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
-    return v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
-}
-__device__ __forceinline__ unsigned buf4(rsrc_t r, unsigned off)
-{
-    return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
-}
-
-// kAl: bytes every row start and every 16-byte chunk is aligned to (4: whole words, 1: any; the latter reads
-// the words around the chunk and shifts).
-template <int kAl>
-__device__ __forceinline__ v4i load_unit(rsrc_t r, unsigned off)
-{
-    if (kAl == 4) return buf16(r, off);
-    const unsigned base = off & ~3u, sh = off & 3u;
-    const v4i w = buf16(r, base);
-    const unsigned w4 = buf4(r, base + 16);
-    v4i o;
-    o[0] = (int)__builtin_amdgcn_alignbyte((unsigned)w[1], (unsigned)w[0], sh);
-    o[1] = (int)__builtin_amdgcn_alignbyte((unsigned)w[2], (unsigned)w[1], sh);
-    o[2] = (int)__builtin_amdgcn_alignbyte((unsigned)w[3], (unsigned)w[2], sh);
-    o[3] = (int)__builtin_amdgcn_alignbyte(w4, (unsigned)w[3], sh);
-    return o;
-}
-// The same for the last, partly filled k-step: word by word (each is inside the buffer or reads as
-// zero), bytes at and past `left` (the number of valid ones, possibly <= 0) cleared.
-template <int kAl>
-__device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
-{
-    const unsigned base = off & ~3u, sh = kAl == 4 ? 0u : off & 3u;
-    unsigned w[5];
-#pragma unroll
-    for (int t = 0; t < 5; ++t) w[t] = buf4(r, left > 0 ? base + 4 * t : kOutOfRange);
-    v4i o;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const unsigned v = kAl == 4 ? w[t] : __builtin_amdgcn_alignbyte(w[t + 1], w[t], sh);
-        const int nb = left - 4 * t;  // valid bytes of this word
-        o[t] = nb >= 4 ? (int)v : nb <= 0 ? 0 : (int)(v & ((1u << (8 * nb)) - 1u));
-    }
-    return o;
-}
-
-typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef unsigned u32_a1 __attribute__((aligned(1)));
 
 // KW wavefronts divide K in slices of 128 bytes; a wavefront has up to D slices in flight.
 // kAl: 16: operands go global -> LDS directly; 4, 1: alignment of the rows in bytes, through registers.

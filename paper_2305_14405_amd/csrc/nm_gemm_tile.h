@@ -522,27 +522,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(Ge
     }
 }
 
-// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernel hands XCD x the
-// x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
-// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the
-// r (a divisor of the eighth, with whole columns: tiles_n % c == 0) that makes this sum smallest.
-static inline int xcd_group_rows(int tiles_m, int tiles_n, int BM, int BN)
-{
-    const int ntiles = tiles_m * tiles_n;
-    if (ntiles % 8 != 0) return 8;
-    const int share = ntiles / 8;
-    int best = 8;
-    long best_cost = -1;
-    for (int r = 1; r <= tiles_m && r <= share; ++r) {
-        if (share % r != 0 || tiles_m % r != 0) continue;
-        const int c = share / r;
-        if (c > tiles_n || tiles_n % c != 0) continue;
-        const long cost = (long)r * BM + (long)c * BN;
-        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = r;
-    }
-    return best;
-}
-
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128>
 static int32_t launch_tile_epi(GemmParams& p, size_t table_bytes, hipStream_t s)
 {

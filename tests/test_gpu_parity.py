@@ -663,6 +663,20 @@ def test_gemm_small_tile_kernel(oracle, M, N, K):
         assert_exact(host(acc), r["acc"], "acc, A misaligned")
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1201, 701, 37), (4100, 200, 36), (1025, 801, 256),             # 64x64 tiles
+    (5523, 266, 17), (2049, 515, 1000), (3001, 402, 129),           # 128x64
+    (3055, 792, 27), (4096, 1001, 260), (803, 4016, 80),            # 128x128
+    (10308, 726, 34), (6401, 1283, 391)])                           # 256x128
+def test_gemm_register_staged_tiles(oracle, M, N, K):
+    """The register-staged tile kernel in each of its tile configurations: operands aligned to 16, 4 and 1 bytes, rows of
+    every alignment of the results, K below, at and beyond a k-slice with and without a remainder, partly filled row
+    and column tiles; every output and option, a table with the input clamp and one in two levels."""
+    test_gemm_small_tile_kernel(oracle, M, N, K)
+    test_two_level_table_gemm_epilogue(oracle, M, N, K)
+    test_gemm_int8_only_table_out_of_range(oracle, M, N, K, 1)
+
+
 def test_gemm_extreme_operands(oracle):
     """All-(-127) x all-(+127) at the largest K of the workloads: |acc| = K * 127^2 > 2^24."""
     M, N, K = 40, 72, 3072
