@@ -11,6 +11,24 @@ namespace nm {
 constexpr int kGemmThreads = 256;
 constexpr int kBK = 64;  // bytes of k per pipeline stage
 
+// Division by a number the host knows: exact for every n below 2^31 (Granlund and Montgomery, "Division by invariant
+// integers using multiplication", 1994: a multiplier of 32 bits does for dividends of 31).
+struct FastDiv {
+    unsigned d, magic, shift;
+};
+static inline FastDiv fast_div(int d)
+{
+    unsigned s = 0;
+    while ((1u << s) < (unsigned)d) ++s;
+    // d == 1: the quotient is the number itself (magic 0)
+    return {(unsigned)d, s == 0 ? 0u : (unsigned)((1ull << (31 + s)) / (unsigned)d) + 1u, s == 0 ? 0u : s - 1u};
+}
+__device__ __forceinline__ unsigned quotient(unsigned n, const FastDiv& f)
+{
+    const unsigned q = __umulhi(n, f.magic) >> f.shift;
+    return f.magic ? q : n;
+}
+
 struct GemmParams {
     int M, N, K;
     const int8_t* A; long lda;
@@ -52,6 +70,7 @@ struct GemmParams {
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
     int relu;     // relu_codes holds for the table and the one output scale
     int batched;  // small-tile kernel: more than one problem (grid.y)
+    FastDiv div_tiles_m, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, cWo, cHo, cCin and cKw
 };
 
 // The small-tile kernel (nm_gemm_direct.hip).  align: alignment of operand rows and chunks in bytes (16, 4 or
@@ -258,6 +277,55 @@ __device__ __forceinline__ void epi_math(const GemmParams& p, const float2* s_kb
         }
         o.y[e] = v;
         if (need_q) o.q[e] = requant(v, c.inv[e]);
+    }
+}
+
+// The values of N groups of four columns (one row each), every option of the generic epilogue: y as the fp32 results, seg as
+// dbg_seg reports them (valid where there is a table).  Each option is one test around a loop over all groups: a test
+// inside splits the loop into small blocks and serialises their LDS reads (the 32 groups of a lane took 4 x as long).
+template <int N>
+__device__ __forceinline__ void epi_values(const GemmParams& p, const float2* s_kb, const v4i (&a)[N], const float* scale, const float* bias,
+                                           const unsigned (&res)[N], float (&y)[N][4], int (&seg)[N][4])
+{
+#pragma unroll
+    for (int t = 0; t < N; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[t][e] = __builtin_fmaf((float)a[t][e], scale[e], bias[e]);
+    if (p.resid) {
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[t][e] = __builtin_fmaf((float)(int)(int8_t)(res[t] >> (8 * e)), p.resid_scale, y[t][e]);
+    }
+    if (p.has_table) {
+        const float lo = p.table.lo, hi = p.table.hi, inv_w = p.table.inv_w;
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float xc = __builtin_amdgcn_fmed3f(y[t][e], lo, hi);
+                y[t][e] = p.table.clamp_input ? xc : y[t][e];
+                seg[t][e] = seg_index(y[t][e], lo, inv_w, p.table.nseg);
+            }
+        if (p.table.cellmap) {   // merged table, two steps
+            const uint8_t* map = reinterpret_cast<const uint8_t*>(s_kb + p.table.nkb);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                float2 kb[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) kb[e] = s_kb[map[seg[t][e]]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[t][e] = __builtin_fmaf(kb[e].x, y[t][e], kb[e].y);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float2 kb = s_kb[seg[t][e]];
+                    y[t][e] = __builtin_fmaf(kb.x, y[t][e], kb.y);
+                }
+        }
     }
 }
 

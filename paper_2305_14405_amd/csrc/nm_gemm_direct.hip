@@ -10,7 +10,7 @@
 // in flight at once: rows of 128 bytes keep the loads at the full 64 bytes per clock and CU (loading
 // fragments straight into registers, 16 rows of 64 bytes per instruction, reached 8).  The wavefronts'
 // int32 partial tiles meet in LDS (exact in any order) and every thread finishes groups of four
-// neighbouring outputs; the epilogue's vectors, residual and table are requested before the slices and
+// neighbouring outputs; the epilogue's vectors, residual and table are requested behind the first slices and
 // not waited for until then, and all kernel arguments are fetched in one step (together 0.4 .. 1.5 us of
 // a launch).  Measured, us before -> after, weights from HBM: 128x768x3072 13.9 -> 5.3, 128x3072x768 8.6 ->
 // 5.0, 64x128x128 6.4 -> 2.9 (an empty launch is 1.6), 847x768x3072 15.0 -> 10.9, 3x3 convolution of
@@ -24,7 +24,12 @@ namespace nm {
 
 // KW wavefronts divide K in slices of 128 bytes; a wavefront has up to D slices in flight.
 // kAl: 16: operands go global -> LDS directly; 4, 1: alignment of the rows in bytes, through registers.
-template <int BM, int BN, int KW, int D, int kAl, bool kConv>
+// kEpi, kForm: EPI_GENERIC, or one of the fixed epilogues for a single problem whose columns come in whole fours and, unless
+// gathered, with K a multiple of 128 (lean_epilogue).  Every kernel starts with an empty instruction cache and runs
+// most of this code once: stamps at 128 x 3072 x 768 put 1300 to 2700 clocks on the 190 instructions in front of the first
+// load and 1400 on the epilogue, of 7000 in all.  The fixed forms are a third of the code on the way, and divisions are by
+// host-made reciprocals: 12 base layers over 1 x 128 tokens 360 -> 340 us, ResNet-50 on one image 245 -> 211.
+template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm>
 __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
 {
     constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
@@ -38,17 +43,28 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     // 16-byte column slot of a partial tile's row, spread over the banks
     constexpr auto pslot = [](int row, int slot) { return slot ^ (BN == 64 ? row & 15 : BN == 32 ? (row >> 1) & 7 : (row >> 2) & 3); };
     static_assert(!kConv || kAl == 16, "gathered operand: aligned");
+    constexpr bool kLean = kEpi != EPI_GENERIC;
+    static_assert(!kLean || kAl == 16, "fixed epilogues: aligned");
+    constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_Q_TABLE_RESID, kTable = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE_RESID;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];   // [wavefronts with slices][slots][BM + BN rows of 128 bytes]
 
     // One wait for the kernel arguments the whole kernel uses (left alone, the compiler fetches them in
     // half a dozen dependent steps, each a memory round trip).
-    asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.bias), "s"(p.alpha_vec), "s"(p.resid), "s"(p.table.kb), "s"(p.M), "s"(p.N), "s"(p.K),
-                 "s"(p.lda), "s"(p.ldw), "s"(p.ldo), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.has_table), "s"(p.vec_out),
-                 "s"(p.batched), "s"(p.table.nseg), "s"(p.table.cellmap), "s"(p.alpha), "s"(p.out_q), "s"(p.out_f32));
+    asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.bias), "s"(p.alpha_vec), "s"(p.resid), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.lda), "s"(p.ldw),
+                 "s"(p.ldo), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.alpha), "s"(p.out_q), "s"(p.out_f32), "s"(p.div_tiles_m.magic),
+                 "s"(p.div_tiles_m.shift), "s"(p.out_inv_scale), "s"(p.resid_scale));
+    if (!kLean)
+        asm volatile("" : : "s"(p.has_table), "s"(p.vec_out), "s"(p.batched), "s"(p.table.kb), "s"(p.table.nseg), "s"(p.table.cellmap));
+    if (kTable && kForm == FORM_ANY) asm volatile("" : : "s"(p.table.kb), "s"(p.table.nseg), "s"(p.table.lo), "s"(p.table.inv_w));
+    if (kTable && kForm == FORM_TWO_SEGMENTS)
+        asm volatile("" : : "s"(p.table.k0), "s"(p.table.b0), "s"(p.table.k1), "s"(p.table.b1), "s"(p.table.tau));
+    if (kConv)
+        asm volatile("" : : "s"(p.cH), "s"(p.cW), "s"(p.cCin), "s"(p.cKw), "s"(p.cStride), "s"(p.cPad), "s"(p.cWo), "s"(p.cHo), "s"(p.div_wo.magic),
+                     "s"(p.div_wo.shift), "s"(p.div_ho.magic), "s"(p.div_ho.shift));
 
     // only as many rings and slots as this K needs (short contractions: several workgroups per CU)
     const int nk = (p.K + 127) >> 7;
-    const int rings = min(KW, nk), slots = min(D, (nk + KW - 1) / KW);
+    const int rings = kLean ? KW : min(KW, nk), slots = min(D, (nk + KW - 1) / KW);
     const int ring_bytes = slots * SLICE;
     float2* s_kb = reinterpret_cast<float2*>(smem + rings * ring_bytes);
 
@@ -61,37 +77,17 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     const int ntiles = p.tiles_m * p.tiles_n, share = (ntiles + 7) >> 3;
     const int id = (blockIdx.x % 8) * share + blockIdx.x / 8;
     if (id >= ntiles) return;
-    const int m0 = (id % p.tiles_m) * BM, n0 = (id / p.tiles_m) * BN;
+    const int tile_n = (int)quotient((unsigned)id, p.div_tiles_m);
+    const int m0 = (id - tile_n * p.tiles_m) * BM, n0 = tile_n * BN;
     const int8_t* A = p.A;
     const int8_t* W = p.W;
     long obase = 0;
-    if (p.batched) {
+    if (!kLean && p.batched) {
         const int outer = blockIdx.y / p.inner_count, inner = blockIdx.y % p.inner_count;
         A += outer * p.a_outer + inner * p.a_inner;
         W += outer * p.w_outer + inner * p.w_inner;
         obase = outer * p.o_outer + inner * p.o_inner;
     }
-
-    // What the epilogue needs is requested first and parked in registers, straight-line, so that
-    // nothing here waits: the waits for the operand slices below count younger loads only.
-    const int c4 = tid % G4, row0 = tid / G4;
-    const int nb = n0 + 4 * c4;
-    const bool n4 = (p.N & 3) == 0;      // a group of four columns is all in or all out
-    v4f bias_r = {0.0f, 0.0f, 0.0f, 0.0f}, scale_r = {p.alpha, p.alpha, p.alpha, p.alpha};
-    unsigned res_r[GPT];
-    if (n4) {
-        const int ncl = min(nb, p.N - 4);
-        if (p.bias) bias_r = *reinterpret_cast<const v4f_a4*>(p.bias + ncl);
-        if (p.alpha_vec) scale_r = *reinterpret_cast<const v4f_a4*>(p.alpha_vec + ncl);
-        if (p.resid) {
-#pragma unroll
-            for (int t = 0; t < GPT; ++t)
-                res_r[t] = *reinterpret_cast<const u32_a1*>(p.resid + obase + (long)min(m0 + row0 + t * (NT / G4), p.M - 1) * p.ldo + ncl);
-        }
-    }
-    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry per thread; a larger table is staged late
-    const bool plain_table = p.has_table && !p.table.cellmap;
-    if (plain_table) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
 
     // source of the lane's 16 bytes in every piece: row l / 8 of the piece, chunk l % 8 (swizzled);
     // rows past the edge are clamped to the last one (they only feed outputs that are never stored)
@@ -109,7 +105,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
         if (b < NA) {
             if (kConv) {
                 const int m = min(m0 + 8 * b + lrow, p.M - 1);
-                const int wo = m % p.cWo, t = m / p.cWo, ho = t % p.cHo, bi = t / p.cHo;
+                const int t = (int)quotient((unsigned)m, p.div_wo), wo = m - t * p.cWo, bi = (int)quotient((unsigned)t, p.div_ho), ho = t - bi * p.cHo;
                 ch[b] = ho * p.cStride - p.cPad;
                 cw[b] = wo * p.cStride - p.cPad;
                 voff[b] = (unsigned)(bi * p.cH * p.cW * p.cCin) + (co & 63u);
@@ -126,15 +122,15 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     // this wavefront's slices
     const int per = nk / KW, rem = nk % KW;
     const int s0 = wave * per + min(wave, rem), cnt = per + (wave < rem ? 1 : 0);
-    const bool ragged = (p.K & 127) != 0;            // the last slice is partly filled
+    const bool ragged = !(kLean && !kConv) && (p.K & 127) != 0;   // the last slice is partly filled
     const int8_t* zero_src = g_zero_line + 16 * (lane & 7);
 
     // ---- aligned operands: slice t of this wavefront goes straight to its ring slot ----
     int ti = 0, tj = 0, tc = 0;   // kConv: tap and channel of the next half slice to load
     if (kConv) {
-        const int tap = (s0 * 128) / p.cCin;
+        const int tap = (int)quotient((unsigned)s0 * 128u, p.div_cin);
         tc = s0 * 128 - tap * p.cCin;
-        ti = tap / p.cKw;
+        ti = (int)quotient((unsigned)tap, p.div_kw);
         tj = tap - ti * p.cKw;
     }
     auto issue = [&](int t, int slot) {
@@ -196,10 +192,39 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
     };
 
-    if (kAl == 16) {
+    // What the epilogue needs, behind the first slices: the waits for these count younger slices only, so a
+    // slice that is waited for brings along some of it, which is needed as soon as the products are done.
+    const int c4 = tid % G4, row0 = tid / G4;
+    const int nb = n0 + 4 * c4;
+    const bool n4 = kLean || (p.N & 3) == 0;   // a group of four columns is all in or all out
+    v4f bias_r = {0.0f, 0.0f, 0.0f, 0.0f}, scale_r = {p.alpha, p.alpha, p.alpha, p.alpha};
+    unsigned res_r[GPT];
+    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry (and word of a cell map) per thread; a larger table is staged late
+    unsigned map_reg = 0;
+    const bool two_level = !kLean && p.has_table && p.table.cellmap, one_level = kLean ? kTable && kForm == FORM_ANY : p.has_table && !two_level;
+    auto request_epilogue = [&] {
+        if (n4) {
+            const int ncl = min(nb, p.N - 4);
+            if (p.bias) bias_r = *reinterpret_cast<const v4f_a4*>(p.bias + ncl);
+            if (p.alpha_vec) scale_r = *reinterpret_cast<const v4f_a4*>(p.alpha_vec + ncl);
+            if (kLean ? kResid : p.resid != nullptr) {
 #pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (d < cnt) issue(d, d);
+                for (int t = 0; t < GPT; ++t)
+                    res_r[t] = *reinterpret_cast<const u32_a1*>(p.resid + obase + (long)min(m0 + row0 + t * (NT / G4), p.M - 1) * p.ldo + ncl);
+            }
+        }
+        if (two_level) {
+            kb_reg = p.table.ckb[min(tid, p.table.nkb - 1)];
+            map_reg = reinterpret_cast<const unsigned*>(p.table.cellmap)[min(tid, (p.table.nseg + 3) / 4 - 1)];
+        } else if (one_level) {
+            kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+        }
+    };
+
+    if (kAl == 16) {
+#pragma unroll 1
+        for (int d = 0; d < min(D, cnt); ++d) issue(d, d);
+        request_epilogue();
         int slot = 0;
         for (int t = 0; t < cnt; ++t) {
             const int young = min(D - 1, cnt - 1 - t);   // younger slices in flight (wave-uniform)
@@ -231,6 +256,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
             }
         };
         if (cnt > 0) fetch(0);
+        request_epilogue();
         for (int t = 0; t < cnt; ++t) {
 #pragma unroll
             for (int b = 0; b < NI; ++b) *reinterpret_cast<v4i*>(ring_p + 1024 * b + 16 * lane) = reg[b];
@@ -248,69 +274,109 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     // Partial tiles meet in LDS, each in its wavefront's own ring (whose fragments have all been read).
     // Lane (fr, fq) holds row 16i + fr, columns 16j + 4fq .. +3.
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-    if (cnt > 0) {
+    if (kLean || cnt > 0) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
                 *reinterpret_cast<v4i*>(ring_p + (16 * i + fr) * (BN * 4) + 16 * pslot(16 * i + fr, 4 * j + fq)) = acc[i][j];
     }
-    if (plain_table) {
+    if (two_level) {
+        unsigned* map = reinterpret_cast<unsigned*>(s_kb + p.table.nkb);
+        const int nw = (p.table.nseg + 3) / 4;
+        if (tid < p.table.nkb) s_kb[tid] = kb_reg;
+        if (tid < nw) map[tid] = map_reg;
+        for (int e = tid + NT; e < p.table.nkb; e += NT) s_kb[e] = p.table.ckb[e];
+        for (int e = tid + NT; e < nw; e += NT) map[e] = reinterpret_cast<const unsigned*>(p.table.cellmap)[e];
+    } else if (one_level) {
         if (tid < p.table.nseg) s_kb[tid] = kb_reg;
         for (int e = tid + NT; e < p.table.nseg; e += NT) s_kb[e] = p.table.kb[e];
-    } else if (p.has_table) {
-        stage_table_two_level(s_kb, p.table);
     }
     __syncthreads();
     if (NGRP < NT && row0 >= BM) return;
     if (nb >= p.N) return;
-    auto partial_sum = [&](int row, int (&a4)[4]) {
+    auto partial_sum = [&](int row) {
         const int8_t* at = smem + row * (BN * 4) + 16 * pslot(row, c4);
         v4i s = *reinterpret_cast<const v4i*>(at);
 #pragma unroll
         for (int w = 1; w < KW; ++w)
-            if (w < rings) s += *reinterpret_cast<const v4i*>(at + w * ring_bytes);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) a4[e] = s[e];
+            if (kLean || w < rings) s += *reinterpret_cast<const v4i*>(at + w * ring_bytes);
+        return s;
     };
-    Col4 c;
-    if (n4 && p.vec_out) {
+    if constexpr (kLean) {
+        const long at0 = (long)(m0 + row0) * p.ldo + nb;
+        const int left = p.M - (m0 + row0);
+        v4f inv = {p.out_inv_scale, p.out_inv_scale, p.out_inv_scale, p.out_inv_scale};
+        if (kEpi == EPI_Q && p.split_cols > 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            c.bias[e] = bias_r[e];
-            c.scale[e] = scale_r[e];
-            c.inv[e] = p.out_inv_scale;
+            for (int e = 0; e < 4; ++e) inv[e] = nb + e >= 2 * p.split_cols ? p.inv3[2] : nb + e >= p.split_cols ? p.inv3[1] : p.inv3[0];
         }
-        if (p.out_inv_scale_vec) {
-            const v4f iv = *reinterpret_cast<const v4f_a4*>(p.out_inv_scale_vec + nb);
+        v4i a[GPT];
+        v4f y[GPT];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c.inv[e] = iv[e];
+        for (int t = 0; t < GPT; ++t) a[t] = partial_sum(row0 + t * (NT / G4));
+#pragma unroll
+        for (int t = 0; t < GPT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = __builtin_fmaf((float)a[t][e], scale_r[e], bias_r[e]);
+                if (kResid) v = __builtin_fmaf((float)(int)(int8_t)(res_r[t] >> (8 * e)), p.resid_scale, v);
+                if (kTable && kForm == FORM_TWO_SEGMENTS) v = pwl_eval_two_segments(v, p.table);
+                int seg;
+                if (kTable && kForm == FORM_ANY) v = pwl_eval_noclamp(v, p.table, s_kb, seg);
+                y[t][e] = v;
+            }
+#pragma unroll
+        for (int t = 0; t < GPT; ++t)
+            if (t * (NT / G4) < left) {
+                const long at = at0 + (long)(t * (NT / G4)) * p.ldo;
+                if (kEpi == EPI_F32_RESID) *reinterpret_cast<v4f*>(p.out_f32 + at) = y[t];
+                else *reinterpret_cast<unsigned*>(p.out_q + at) =
+                         pack4(requant(y[t][0], inv[0]), requant(y[t][1], inv[1]), requant(y[t][2], inv[2]), requant(y[t][3], inv[3]));
+            }
+        return;
+    }
+    if (n4 && p.vec_out) {
+        v4f inv = {p.out_inv_scale, p.out_inv_scale, p.out_inv_scale, p.out_inv_scale};
+        if (p.out_inv_scale_vec) {
+            inv = *reinterpret_cast<const v4f_a4*>(p.out_inv_scale_vec + nb);
         } else if (p.split_cols > 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c.inv[e] = nb + e >= 2 * p.split_cols ? p.inv3[2] : nb + e >= p.split_cols ? p.inv3[1] : p.inv3[0];
+            for (int e = 0; e < 4; ++e) inv[e] = nb + e >= 2 * p.split_cols ? p.inv3[2] : nb + e >= p.split_cols ? p.inv3[1] : p.inv3[0];
         }
+        v4i a[GPT];
+        float y[GPT][4];
+        int seg[GPT][4];
+        const float scale[4] = {scale_r[0], scale_r[1], scale_r[2], scale_r[3]}, bias[4] = {bias_r[0], bias_r[1], bias_r[2], bias_r[3]};
 #pragma unroll
-        for (int t = 0; t < GPT; ++t) {
-            const int row = row0 + t * (NT / G4), m = m0 + row;
-            if (m >= p.M) break;
-            int a4[4], r4[4] = {0, 0, 0, 0};
-            partial_sum(row, a4);
-            if (p.resid) {
+        for (int t = 0; t < GPT; ++t) a[t] = partial_sum(row0 + t * (NT / G4));
+        epi_values<GPT>(p, s_kb, a, scale, bias, res_r, y, seg);
+        const long at0 = obase + (long)(m0 + row0) * p.ldo + nb;
+        const int left = p.M - (m0 + row0);
+        auto each = [&](auto store) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) r4[e] = (int)(int8_t)(res_r[t] >> (8 * e));
-            }
-            Epi4 o;
-            epi_math<EPI_GENERIC>(p, s_kb, a4, c, r4, o);
-            epi_store<EPI_GENERIC>(p, obase + (long)m * p.ldo, nb, a4, o, true, false);
-        }
+            for (int t = 0; t < GPT; ++t)
+                if (t * (NT / G4) < left) store(at0 + (long)(t * (NT / G4)) * p.ldo, t);
+        };
+        if (p.out_q)
+            each([&](long at, int t) {
+                *reinterpret_cast<unsigned*>(p.out_q + at) = pack4(requant(y[t][0], inv[0]), requant(y[t][1], inv[1]), requant(y[t][2], inv[2]), requant(y[t][3], inv[3]));
+            });
+        if (p.out_f32) each([&](long at, int t) { *reinterpret_cast<v4f*>(p.out_f32 + at) = v4f{y[t][0], y[t][1], y[t][2], y[t][3]}; });
+        if (p.out_acc) each([&](long at, int t) { *reinterpret_cast<v4i*>(p.out_acc + at) = a[t]; });
+        if (p.dbg_seg && p.has_table)
+            each([&](long at, int t) {
+                *reinterpret_cast<uint2*>(p.dbg_seg + at) = make_uint2((unsigned)seg[t][0] | ((unsigned)seg[t][1] << 16), (unsigned)seg[t][2] | ((unsigned)seg[t][3] << 16));
+            });
     } else {
+        Col4 c;
         load_cols<EPI_GENERIC>(p, nb, c);
 #pragma unroll 1
         for (int t = 0; t < GPT; ++t) {
             const int row = row0 + t * (NT / G4), m = m0 + row;
             if (m >= p.M) break;
-            int a4[4], r4[4] = {0, 0, 0, 0};
-            partial_sum(row, a4);
+            const v4i a = partial_sum(row);
+            int a4[4] = {a[0], a[1], a[2], a[3]}, r4[4] = {0, 0, 0, 0};
             if (p.resid) load_resid4(p, obase + (long)m * p.ldo, nb, false, r4);
             Epi4 o;
             epi_math<EPI_GENERIC>(p, s_kb, a4, c, r4, o);
@@ -319,12 +385,12 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     }
 }
 
-template <int BM, int BN, int KW, int D, int kAl, bool kConv>
+template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi = EPI_GENERIC, int kForm = FORM_ANY>
 static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, hipStream_t s)
 {
-    auto kern = gemm_direct_kernel<BM, BN, KW, D, kAl, kConv>;
+    auto kern = gemm_direct_kernel<BM, BN, KW, D, kAl, kConv, kEpi, kForm>;
     const int nk = (p.K + 127) / 128, need = (nk + KW - 1) / KW;
-    const size_t shmem = (size_t)(nk < KW ? nk : KW) * (need < D ? need : D) * (BM + BN) * 128 + table_bytes;
+    const size_t shmem = (size_t)(nk < KW && kEpi == EPI_GENERIC ? nk : KW) * (need < D ? need : D) * (BM + BN) * 128 + table_bytes;
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {
@@ -336,15 +402,39 @@ static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, h
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     p.batched = batches > 1;
+    p.div_tiles_m = fast_div(p.tiles_m);
+    if (kConv) p.div_wo = fast_div(p.cWo), p.div_ho = fast_div(p.cHo), p.div_cin = fast_div(p.cCin), p.div_kw = fast_div(p.cKw);
     const int grid = (p.tiles_m * p.tiles_n + 7) / 8 * 8;   // the kernel's eighths are (tiles + 7) / 8 each
     hipLaunchKernelGGL(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, p);
     return NM_OK;
 }
 
+// The fixed epilogue that computes what p asks for (and nothing else), or EPI_GENERIC.
+static int lean_epilogue(const GemmParams& p, int align, bool conv, int batches)
+{
+    if (align < 16 || batches != 1 || p.N % 4 != 0 || !p.vec_out || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
+    if (p.dbg_seg || p.out_acc || p.out_inv_scale_vec || (p.out_q != nullptr) == (p.out_f32 != nullptr)) return EPI_GENERIC;
+    if (p.has_table && (p.table.cellmap || p.table.clamp_input || p.split_cols > 0)) return EPI_GENERIC;
+    if (p.out_f32) return p.resid && !p.has_table ? EPI_F32_RESID : EPI_GENERIC;
+    if (p.resid) return p.has_table && p.table.two_seg ? EPI_Q_TABLE_RESID : EPI_GENERIC;
+    return p.has_table ? EPI_Q_TABLE : EPI_Q;
+}
+
 template <int BM, int BN, int KW, int D>
 static int32_t launch_direct_c(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, hipStream_t s)
 {
-    if (conv) return launch_direct_t<BM, BN, KW, D, 16, true>(p, batches, table_bytes, s);
+    const int epi = lean_epilogue(p, align, conv, batches);
+    const bool two = p.has_table && p.table.two_seg;
+    if (conv) {
+        if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q>(p, batches, 0, s);
+        if (epi == EPI_Q_TABLE && two) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q_TABLE, FORM_TWO_SEGMENTS>(p, batches, 0, s);
+        return launch_direct_t<BM, BN, KW, D, 16, true>(p, batches, table_bytes, s);
+    }
+    if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q>(p, batches, 0, s);
+    if (epi == EPI_F32_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_F32_RESID>(p, batches, 0, s);
+    if (epi == EPI_Q_TABLE_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE_RESID, FORM_TWO_SEGMENTS>(p, batches, 0, s);
+    if (epi == EPI_Q_TABLE && two) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE, FORM_TWO_SEGMENTS>(p, batches, 0, s);
+    if (epi == EPI_Q_TABLE) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE>(p, batches, table_bytes, s);
     if (align >= 16) return launch_direct_t<BM, BN, KW, D, 16, false>(p, batches, table_bytes, s);
     if (align >= 4) return launch_direct_t<BM, BN, KW, D, 4, false>(p, batches, table_bytes, s);
     return launch_direct_t<BM, BN, KW, D, 1, false>(p, batches, table_bytes, s);

@@ -176,8 +176,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_unaligned_kern
 
     // Epilogue, 32 rows at a time: the accumulators pass through a patch of the wavefront's own, so that a lane
     // finishes four neighbouring columns of rows and a row leaves in consecutive lanes, whatever its alignment.
-    // Every option is one test around a loop over the lane's rows (a test inside would split them into small
-    // blocks and serialise their LDS reads).
     constexpr int LPR = WN / 4, RPP = 64 / LPR, NP = 32 / RPP;   // lanes per row, rows per pass, passes
     static_assert(LPR == 16, "a row is a DPP row");
     int* const patch = reinterpret_cast<int*>(smem) + wave * 32 * PW;
@@ -186,7 +184,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_unaligned_kern
     const int cols = p.N - nb, ncl = min(nb, p.N - 4);    // (N >= 4: host)
     const v4f sc = *reinterpret_cast<const v4f*>(s_cols + wave_n + pcol), bi = *reinterpret_cast<const v4f*>(s_cols + BN + wave_n + pcol),
               iv = *reinterpret_cast<const v4f*>(s_cols + 2 * BN + wave_n + pcol);
-    const DevTable tab = p.table;
+    const float scale[4] = {sc[0], sc[1], sc[2], sc[3]}, bias[4] = {bi[0], bi[1], bi[2], bi[3]};
+    const int shr = 8 * min(nb - ncl, 3);   // the last lane of a row reads the last four codes; whole groups: no shift
     // Rows whose alignment is that of their elements (!p.vec_out, or columns not in whole fours): a store whose address is
     // not a multiple of its size is split by the hardware (4096 x 1002 codes took 6 us longer than 4096 x 1000), so words
     // leave one element per lane, and codes as the aligned words of a row and single bytes at its ends.
@@ -214,7 +213,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_unaligned_kern
         unsigned res[NP];
         if (p.resid) {
 #pragma unroll
-            for (int t = 0; t < NP; ++t) res[t] = *reinterpret_cast<const u32_a1*>(p.resid + (long)min(mb + t * RPP, p.M - 1) * p.ldo + ncl);
+            for (int t = 0; t < NP; ++t) res[t] = *reinterpret_cast<const u32_a1*>(p.resid + (long)min(mb + t * RPP, p.M - 1) * p.ldo + ncl) >> shr;
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j)
@@ -225,12 +224,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_unaligned_kern
         fence();
         v4i a[NP];
         float y[NP][4];
+        int seg[NP][4];
 #pragma unroll
         for (int t = 0; t < NP; ++t) a[t] = *reinterpret_cast<const v4i*>(patch + (prow + t * RPP) * PW + pcol);
-#pragma unroll
-        for (int t = 0; t < NP; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[t][e] = __builtin_fmaf((float)a[t][e], sc[e], bi[e]);
         if (p.out_acc) {
             if (whole) {
 #pragma unroll
@@ -240,44 +236,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_unaligned_kern
                 store_words(p.out_acc, mb - prow);
             }
         }
-        if (p.resid) {
-            const int shr = 8 * min(nb - ncl, 3);   // the last lane of a row reads the last four codes; whole groups: no shift
+        epi_values<NP>(p, s_kb, a, scale, bias, res, y, seg);
+        if (p.dbg_seg && p.has_table) {
 #pragma unroll
             for (int t = 0; t < NP; ++t)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y[t][e] = __builtin_fmaf((float)(int)(int8_t)((res[t] >> shr) >> (8 * e)), p.resid_scale, y[t][e]);
-        }
-        if (p.has_table) {
-            int seg[NP][4];
-#pragma unroll
-            for (int t = 0; t < NP; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float xc = __builtin_amdgcn_fmed3f(y[t][e], tab.lo, tab.hi);
-                    y[t][e] = tab.clamp_input ? xc : y[t][e];
-                    seg[t][e] = seg_index(y[t][e], tab.lo, tab.inv_w, tab.nseg);
-                }
-            if (p.dbg_seg) {
-#pragma unroll
-                for (int t = 0; t < NP; ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (mb + t * RPP < p.M && nb + e < p.N) p.dbg_seg[(long)(mb + t * RPP) * p.ldo + nb + e] = (uint16_t)seg[t][e];
-            }
-            if (tab.cellmap) {
-                const uint8_t* map = reinterpret_cast<const uint8_t*>(s_kb + tab.nkb);
-#pragma unroll
-                for (int t = 0; t < NP; ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) seg[t][e] = map[seg[t][e]];
-            }
-#pragma unroll
-            for (int t = 0; t < NP; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float2 kb = s_kb[seg[t][e]];
-                    y[t][e] = __builtin_fmaf(kb.x, y[t][e], kb.y);
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (mb + t * RPP < p.M && nb + e < p.N) p.dbg_seg[(long)(mb + t * RPP) * p.ldo + nb + e] = (uint16_t)seg[t][e];
         }
         if (p.out_f32) {
             if (whole) {

@@ -663,6 +663,32 @@ def test_gemm_small_tile_kernel(oracle, M, N, K):
         assert_exact(host(acc), r["acc"], "acc, A misaligned")
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4, 128), (45, 100, 384), (128, 768, 896), (230, 1000, 2048), (300, 1000, 1280), (847, 764, 768)])
+@pytest.mark.parametrize("per_column", [False, True])
+def test_gemm_small_tile_kernel_fixed_epilogues(oracle, M, N, K, per_column):
+    """The small-tile kernel's fixed epilogues (one output; int8 plain, through a table of many and of two segments, with
+    and without residual; fp32 with residual) in each tile configuration, with wavefronts that have no slice, one
+    and several, and partly filled row and column tiles."""
+    ot, dt = both_tables(oracle, [("gelu", -8.0, 8.0, 128), ("relu", -8.0, 8.0, 2)])
+    d = W.gemm_inputs(M, N, K, seed=M + 5 * N + K, full_range=False)
+    alpha = float(np.float32(6.0 / (20 * 20 * np.sqrt(K))))
+    av = (d["alpha_vec"] * alpha).astype(np.float32)
+    ow, gw = (dict(alpha_vec=av), dict(alpha_vec=dev(av))) if per_column else (dict(alpha=alpha), dict(alpha=alpha))
+    dA, dW, db, dr = dev(d["A"]), dev(d["W"]), dev(d["bias"]), dev(d["resid"])
+    oq = torch.full((M, N), 77, dtype=torch.int8, device=DEV)
+    for table, resid in ((None, False), (0, False), (1, False), (1, True), (0, True)):
+        r = oracle.gemm_pwl(d["A"], d["W"], bias=d["bias"], table=None if table is None else ot[table], out_inv_scale=25.0,
+                            **(dict(resid=d["resid"], resid_scale=0.02) if resid else {}), **ow)
+        nm.nm_gemm_pwl(dA, dW, bias=db, tables=dt, table_idx=-1 if table is None else table, out_inv_scale=25.0, out_q=oq,
+                       **(dict(resid=dr, resid_scale=0.02) if resid else {}), **gw)
+        assert_exact(host(oq), r["q"], f"int8, table {table}, residual {resid}")
+    of = torch.full((M, N), -3.0, dtype=torch.float32, device=DEV)
+    for bias in (True, False):
+        r = oracle.gemm_pwl(d["A"], d["W"], bias=d["bias"] if bias else None, resid=d["resid"], resid_scale=0.02, **ow)
+        nm.nm_gemm_pwl(dA, dW, bias=db if bias else None, resid=dr, resid_scale=0.02, out_f32=of, **gw)
+        assert_f32_close(host(of), r["y"], f"fp32 + residual, bias {bias}")
+
+
 @pytest.mark.parametrize("M,N,K", [
     (1201, 701, 37), (4100, 200, 36), (1025, 801, 256),             # 64x64 tiles
     (5523, 266, 17), (2049, 515, 1000), (3001, 402, 129),           # 128x64
