@@ -459,6 +459,30 @@ def test_layernorm_pwl(oracle, rows, cols):
     assert_f32_close(host(of), r["y"], f"layernorm fp32 {rows}x{cols}")
 
 
+@pytest.mark.parametrize("nseg", [1, 37, 64, 65, 200, 256, 257])
+@pytest.mark.parametrize("cols", [256, 512, 768, 1024])
+def test_layernorm_one_row_per_wavefront(oracle, cols, nseg):
+    """Whole rows of 256 to 1024 elements without segment output (tables up to 256 segments stay in registers, larger ones
+    in LDS), rows that leave the last workgroup partly filled, variances over the table's whole range and outside
+    it on both sides, with and without the input clamp, each output alone and both."""
+    for flags, rows in ((0, 67), (nm.NM_TABLE_CLAMP_INPUT, 4)):
+        ot, dt = both_tables(oracle, [("rsqrt", 1e-2, 16.0, nseg)], flags=flags)
+        g = np.random.default_rng(cols + nseg)
+        x = W.float_rows(rows, cols, seed=nseg + cols) * np.exp(g.uniform(-4, 2.5, (rows, 1))).astype(np.float32)
+        gamma = (1 + 0.1 * g.standard_normal(cols)).astype(np.float32)
+        beta = (0.1 * g.standard_normal(cols)).astype(np.float32)
+        r = oracle.layernorm_pwl(x, gamma, beta, 1e-5, ot[0], 31.0)
+        assert nseg < 64 or rows < 67 or len(np.unique(r["seg"])) > 10
+        for want_q, want_f in ((True, False), (False, True), (True, True)):
+            oq = torch.full((rows, cols), 77, dtype=torch.int8, device=DEV) if want_q else None
+            of = torch.full((rows, cols), 7.0, dtype=torch.float32, device=DEV) if want_f else None
+            nm.nm_layernorm_pwl(dev(x), dev(gamma), dev(beta), 1e-5, dt, 0, 31.0, out_q=oq, out_f32=of)
+            if want_q:
+                assert_exact(host(oq), r["q"], f"layernorm int8 {cols}, {nseg} segments")
+            if want_f:
+                assert_f32_close(host(of), r["y"], f"layernorm fp32 {cols}, {nseg} segments")
+
+
 @pytest.mark.parametrize("rows,cols", [(37, 96), (101, 128), (64, 768), (9, 1000), (5, 4096)])
 def test_layernorm_pwl2_sqrt_then_reciprocal(oracle, rows, cols):
     """The two-table LayerNorm (square root, then reciprocal): segments of both tables, fp32 and
