@@ -46,6 +46,12 @@
 
 namespace nm {
 
+struct AttnTable {   // what the kernels use of a DevTable, under its names
+    const float2* kb;
+    float lo, hi, inv_w, u0;
+    int nseg, clamp_input;
+};
+
 struct AttnParams {
     const int8_t* qkv;
     int8_t* ctx;
@@ -54,7 +60,8 @@ struct AttnParams {
     float alpha_scores, inv_s_p, alpha_ctx, inv_s_ctx;
     float e_lo, e_hi;                  // bounds of the exp table's value over every reachable input
     int ctx_vec16;                     // ctx is 16-byte aligned: context rows leave as 16-byte stores
-    DevTable t_exp, t_recip;
+    FastDiv div_qblocks, div_heads;
+    AttnTable t_exp, t_recip;
     int32_t* scores_out;               // optional [B, heads, S, S]
     int8_t* p_out;                     // optional [B, heads, S, S]
 };
@@ -236,15 +243,19 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
     float2* s_kb = reinterpret_cast<float2*>(smem + attn_lds_bytes(NKB));
     // the kernel arguments everything in front of the loads needs, in one step
     asm volatile("" : : "s"(p.qkv), "s"(p.S), "s"(p.H), "s"(p.heads), "s"(p.qblocks), "s"(p.total), "s"(p.t_exp.kb), "s"(p.t_recip.kb),
-                 "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.scores_out), "s"(p.p_out));
+                 "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.div_qblocks.magic), "s"(p.div_qblocks.shift), "s"(p.div_heads.magic),
+                 "s"(p.div_heads.shift), "s"(p.alpha_scores), "s"(p.inv_s_p), "s"(p.alpha_ctx), "s"(p.inv_s_ctx), "s"(p.t_exp.lo),
+                 "s"(p.t_exp.inv_w), "s"(p.t_exp.u0), "s"(p.t_recip.lo), "s"(p.t_recip.hi), "s"(p.t_recip.inv_w),
+                 "s"(p.t_recip.clamp_input), "s"(p.e_lo), "s"(p.e_hi), "s"(p.ctx), "s"(p.ctx_vec16));
+    if (kMode == EXP_ANY) asm volatile("" : : "s"(p.scores_out), "s"(p.p_out), "s"(p.t_exp.hi), "s"(p.t_exp.clamp_input));
     float2* s_kb_recip = s_kb + p.t_exp.nseg + 1;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, hq = lane >> 4;
     const int id = attn_block_id(p.total);
     if (id >= p.total) return;
-    const int bx = id % p.qblocks, by = id / p.qblocks;
-    const int b = by / p.heads, head = by % p.heads;
+    const int by = (int)quotient((unsigned)id, p.div_qblocks), bx = id - by * p.qblocks;
+    const int b = (int)quotient((unsigned)by, p.div_heads), head = by - b * p.heads;
     const int S = kFull ? SK : p.S, H = p.H;
     const int ld = 3 * H;
     const int8_t* base = p.qkv + (long)b * S * ld + head * kHeadDim;
@@ -450,14 +461,15 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
     int8_t* sO = smem + 4 * kLongKeys * 64;
     float2* s_kb = reinterpret_cast<float2*>(smem + kLongLds);
     asm volatile("" : : "s"(p.qkv), "s"(p.S), "s"(p.H), "s"(p.heads), "s"(p.qblocks), "s"(p.total), "s"(p.t_exp.kb), "s"(p.t_recip.kb),
-                 "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.nch), "s"(p.scores_out), "s"(p.p_out));
+                 "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.nch), "s"(p.scores_out), "s"(p.p_out), "s"(p.div_qblocks.magic),
+                 "s"(p.div_qblocks.shift), "s"(p.div_heads.magic), "s"(p.div_heads.shift));
     float2* s_kb_recip = s_kb + p.t_exp.nseg + 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, hq = lane >> 4;
     const int id = attn_block_id(p.total);
     if (id >= p.total) return;
-    const int bx = id % p.qblocks, by = id / p.qblocks;
-    const int b = by / p.heads, head = by % p.heads;
+    const int by = (int)quotient((unsigned)id, p.div_qblocks), bx = id - by * p.qblocks;
+    const int b = (int)quotient((unsigned)by, p.div_heads), head = by - b * p.heads;
     const int S = p.S, H = p.H, ld = 3 * H, nch = p.nch;
     const int8_t* base = p.qkv + (long)b * S * ld + head * (16 * nch);
 
@@ -599,7 +611,7 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
 }
 
 template <typename Kern>
-static int32_t launch_attn_kernel(Kern kern, std::once_flag& once, int32_t& once_rc, const AttnParams& p, int threads, size_t shmem, hipStream_t st)
+static int32_t launch_attn_kernel(Kern kern, std::once_flag& once, int32_t& once_rc, AttnParams& p, int threads, size_t shmem, hipStream_t st)
 {
     std::call_once(once, [&] {   // one attribute call per instantiation
         once_rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -607,6 +619,8 @@ static int32_t launch_attn_kernel(Kern kern, std::once_flag& once, int32_t& once
                             "hipFuncSetAttribute(attention kernel)");
     });
     if (once_rc) return once_rc;
+    p.div_qblocks = fast_div(p.qblocks);
+    p.div_heads = fast_div(p.heads);
     hipLaunchKernelGGL(kern, dim3((p.total + 7) / 8 * 8), dim3(threads), shmem, st, p);
     return NM_OK;
 }
@@ -663,9 +677,13 @@ bool fused_attention_covers(int S, int H, int heads)
 int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
 {
     AttnParams p{};
-    int32_t rc = get_dev_table(a.tables, a.exp_idx, &p.t_exp, what);
+    DevTable t_exp, t_recip;
+    int32_t rc = get_dev_table(a.tables, a.exp_idx, &t_exp, what);
     if (rc) return rc;
-    if ((rc = get_dev_table(a.tables, a.recip_idx, &p.t_recip, what))) return rc;
+    if ((rc = get_dev_table(a.tables, a.recip_idx, &t_recip, what))) return rc;
+    auto pick = [](const DevTable& t) { return AttnTable{t.kb, t.lo, t.hi, t.inv_w, t.u0, t.nseg, t.clamp_input}; };
+    p.t_exp = pick(t_exp);
+    p.t_recip = pick(t_recip);
     p.qkv = a.qkv; p.S = a.S; p.H = a.H; p.heads = a.heads;
     p.nch = a.H / a.heads / 16;
     p.alpha_scores = a.alpha_scores; p.inv_s_p = a.inv_s_p; p.alpha_ctx = a.alpha_ctx; p.inv_s_ctx = a.inv_s_ctx;
@@ -681,7 +699,7 @@ int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
     const bool padded = a.alpha_scores >= 0.0f && !p.t_exp.clamp_input && u_at_0 < (float)(p.t_exp.nseg + 1);
     const int pairs = a.B * a.heads;
     if (!padded || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
-    else if (p.t_exp.pow2) rc = launch_mode<EXP_PADDED_POW2>(p, pairs, st);
+    else if (t_exp.pow2) rc = launch_mode<EXP_PADDED_POW2>(p, pairs, st);
     else rc = launch_mode<EXP_PADDED>(p, pairs, st);
     if (rc) return rc;
     return check_hip(hipGetLastError(), "attention launch");

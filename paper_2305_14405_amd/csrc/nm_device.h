@@ -36,7 +36,8 @@ __device__ __forceinline__ unsigned cvt_u32_sat(float x)
 }
 
 // y = k[s]*x + b[s] (one fma).  kb may point to LDS or to global memory.
-__device__ __forceinline__ float pwl_eval(float x, const DevTable& t, const float2* kb, int& seg)
+template <typename Table>
+__device__ __forceinline__ float pwl_eval(float x, const Table& t, const float2* kb, int& seg)
 {
     // one median-of-three plus a select (a branch here would split the caller's unrolled loops
     // into small blocks and serialise their LDS gathers); NaN: med3 returns the smallest non-NaN
@@ -51,7 +52,8 @@ __device__ __forceinline__ float pwl_eval(float x, const DevTable& t, const floa
 // The same for a value that cannot be NaN (an int32 accumulator times finite multipliers): the
 // clamp flag is folded into the bounds (clo, chi = lo, hi with the flag, -inf, +inf without), so no
 // select is needed; identical results for every non-NaN x.
-__device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi, const DevTable& t,
+template <typename Table>
+__device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi, const Table& t,
                                                   const float2* kb, int& seg)
 {
     x = __builtin_amdgcn_fmed3f(x, clo, chi);
@@ -59,7 +61,8 @@ __device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi,
     const float2 e = kb[seg];
     return __builtin_fmaf(e.x, x, e.y);
 }
-__device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi, const DevTable& t,
+template <typename Table>
+__device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi, const Table& t,
                                                   const float2* kb)
 {
     int seg;
@@ -67,7 +70,8 @@ __device__ __forceinline__ float pwl_eval_bounded(float x, float clo, float chi,
 }
 
 // Without the clamp flag.
-__device__ __forceinline__ float pwl_eval_noclamp(float x, const DevTable& t, const float2* kb, int& seg)
+template <typename Table>
+__device__ __forceinline__ float pwl_eval_noclamp(float x, const Table& t, const float2* kb, int& seg)
 {
     seg = seg_index(x, t.lo, t.inv_w, t.nseg);
     const float2 e = kb[seg];
@@ -77,7 +81,8 @@ __device__ __forceinline__ float pwl_eval_noclamp(float x, const DevTable& t, co
 // A table of two segments (no clamp flag): both lines, and a compare against the smallest value of
 // segment 1 (found on the host with the index arithmetic itself) instead of index, gather and one
 // line.  The same value as pwl_eval_noclamp for every x, NaN and infinities included.
-__device__ __forceinline__ float pwl_eval_two_segments(float x, const DevTable& t)
+template <typename Table>
+__device__ __forceinline__ float pwl_eval_two_segments(float x, const Table& t)
 {
     const float y0 = __builtin_fmaf(t.k0, x, t.b0), y1 = __builtin_fmaf(t.k1, x, t.b1);
     return x >= t.tau ? y1 : y0;
@@ -114,6 +119,12 @@ __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d)
     const unsigned lo = __builtin_amdgcn_perm((unsigned)b, (unsigned)a, 0x0c0c0400u);  // a0 b0 0 0
     const unsigned hi = __builtin_amdgcn_perm((unsigned)d, (unsigned)c, 0x04000c0cu);  // 0 0 c0 d0
     return lo | hi;
+}
+
+__device__ __forceinline__ unsigned quotient(unsigned n, const FastDiv& f)
+{
+    const unsigned q = __umulhi(n, f.magic) >> f.shift;
+    return f.magic ? q : n;
 }
 
 // Copy a table's {k, b} pairs into LDS (all threads of the block take part; the caller

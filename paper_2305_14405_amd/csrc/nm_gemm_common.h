@@ -11,24 +11,6 @@ namespace nm {
 constexpr int kGemmThreads = 256;
 constexpr int kBK = 64;  // bytes of k per pipeline stage
 
-// Division by a number the host knows: exact for every n below 2^31 (Granlund and Montgomery, "Division by invariant
-// integers using multiplication", 1994: a multiplier of 32 bits does for dividends of 31).
-struct FastDiv {
-    unsigned d, magic, shift;
-};
-static inline FastDiv fast_div(int d)
-{
-    unsigned s = 0;
-    while ((1u << s) < (unsigned)d) ++s;
-    // d == 1: the quotient is the number itself (magic 0)
-    return {(unsigned)d, s == 0 ? 0u : (unsigned)((1ull << (31 + s)) / (unsigned)d) + 1u, s == 0 ? 0u : s - 1u};
-}
-__device__ __forceinline__ unsigned quotient(unsigned n, const FastDiv& f)
-{
-    const unsigned q = __umulhi(n, f.magic) >> f.shift;
-    return f.magic ? q : n;
-}
-
 struct GemmParams {
     int M, N, K;
     const int8_t* A; long lda;
@@ -165,7 +147,7 @@ __device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
-enum { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_TABLE2 = 7 };
+enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_TABLE2 = 7 };
 // EPI_Q_TABLE2: EPI_Q_TABLE for a merged table in its two-level form (one byte per primary cell naming the
 // merged segment, one {k, b} per merged segment; tile kernel only).
 // EPI_F32_RESID_LN: EPI_F32_RESID followed by LayerNorm-PWL over the row, inside the kernel: the tile
@@ -250,7 +232,7 @@ __device__ __forceinline__ void load_resid4(const GemmParams& p, long rowoff, in
 }
 
 // How the streaming kernel's epilogue evaluates its table.
-enum { FORM_ANY = 0, FORM_TWO_SEGMENTS = 1, FORM_RELU = 2 };
+enum TableForm { FORM_ANY = 0, FORM_TWO_SEGMENTS = 1, FORM_RELU = 2 };
 
 // The arithmetic of the epilogue for four columns of one row (no global memory access).
 // kTwoSeg: the table has two segments and is evaluated with a compare (specialised table epilogues)

@@ -22,6 +22,54 @@
 
 namespace nm {
 
+// Arguments of the fixed epilogues: what they use, under the names GemmParams has for it.  (The host pays 0.9 us more for a
+// launch with the 560 bytes of GemmParams than for one with 160.)
+struct DirectTable {
+    const float2* kb;
+    float lo, inv_w;
+    int nseg;
+    float k0, b0, k1, b1, tau;
+};
+struct DirectParams {
+    const int8_t* A;
+    const int8_t* W;
+    const float* bias;
+    const float* alpha_vec;
+    const int8_t* resid;
+    int8_t* out_q;
+    float* out_f32;
+    int M, N, K, lda, ldw, ldo, tiles_m, tiles_n;
+    FastDiv div_tiles_m;
+    float alpha, resid_scale, out_inv_scale;
+    int split_cols;
+    float inv3[3];
+    DirectTable table;
+};
+struct DirectConvParams : DirectParams {
+    int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
+    FastDiv div_wo, div_ho, div_cin, div_kw;
+};
+template <bool kConv, int kEpi>
+using DirectArgs = std::conditional_t<kEpi == EPI_GENERIC, GemmParams, std::conditional_t<kConv, DirectConvParams, DirectParams>>;
+
+static void direct_args(GemmParams& q, const GemmParams& p) { q = p; }
+static void direct_args(DirectParams& q, const GemmParams& p)
+{
+    q.A = p.A; q.W = p.W; q.bias = p.bias; q.alpha_vec = p.alpha_vec; q.resid = p.resid; q.out_q = p.out_q; q.out_f32 = p.out_f32;
+    q.M = p.M; q.N = p.N; q.K = p.K; q.lda = (int)p.lda; q.ldw = (int)p.ldw; q.ldo = (int)p.ldo; q.tiles_m = p.tiles_m; q.tiles_n = p.tiles_n;
+    q.div_tiles_m = p.div_tiles_m; q.alpha = p.alpha; q.resid_scale = p.resid_scale; q.out_inv_scale = p.out_inv_scale;
+    q.split_cols = p.split_cols;
+    for (int i = 0; i < 3; ++i) q.inv3[i] = p.inv3[i];
+    const DevTable& t = p.table;
+    q.table = {t.kb, t.lo, t.inv_w, t.nseg, t.k0, t.b0, t.k1, t.b1, t.tau};
+}
+static void direct_args(DirectConvParams& q, const GemmParams& p)
+{
+    direct_args(static_cast<DirectParams&>(q), p);
+    q.cH = p.cH; q.cW = p.cW; q.cCin = p.cCin; q.cKw = p.cKw; q.cStride = p.cStride; q.cPad = p.cPad; q.cHo = p.cHo; q.cWo = p.cWo;
+    q.div_wo = p.div_wo; q.div_ho = p.div_ho; q.div_cin = p.div_cin; q.div_kw = p.div_kw;
+}
+
 // KW wavefronts divide K in slices of 128 bytes; a wavefront has up to D slices in flight.
 // kAl: 16: operands go global -> LDS directly; 4, 1: alignment of the rows in bytes, through registers.
 // kEpi, kForm: EPI_GENERIC, or one of the fixed epilogues for a single problem whose columns come in whole fours and, unless
@@ -30,7 +78,7 @@ namespace nm {
 // load and 1400 on the epilogue, of 7000 in all.  The fixed forms are a third of the code on the way, and divisions are by
 // host-made reciprocals: 12 base layers over 1 x 128 tokens 360 -> 340 us, ResNet-50 on one image 245 -> 211.
 template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm>
-__global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
+__global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, kEpi> p)
 {
     constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
     constexpr int NA = BM / 8, NI = (BM + BN) / 8;   // 1 KB pieces (8 rows) of a slice; the first NA are A rows
@@ -53,12 +101,12 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.bias), "s"(p.alpha_vec), "s"(p.resid), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.lda), "s"(p.ldw),
                  "s"(p.ldo), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.alpha), "s"(p.out_q), "s"(p.out_f32), "s"(p.div_tiles_m.magic),
                  "s"(p.div_tiles_m.shift), "s"(p.out_inv_scale), "s"(p.resid_scale));
-    if (!kLean)
+    if constexpr (!kLean)
         asm volatile("" : : "s"(p.has_table), "s"(p.vec_out), "s"(p.batched), "s"(p.table.kb), "s"(p.table.nseg), "s"(p.table.cellmap));
     if (kTable && kForm == FORM_ANY) asm volatile("" : : "s"(p.table.kb), "s"(p.table.nseg), "s"(p.table.lo), "s"(p.table.inv_w));
     if (kTable && kForm == FORM_TWO_SEGMENTS)
         asm volatile("" : : "s"(p.table.k0), "s"(p.table.b0), "s"(p.table.k1), "s"(p.table.b1), "s"(p.table.tau));
-    if (kConv)
+    if constexpr (kConv)
         asm volatile("" : : "s"(p.cH), "s"(p.cW), "s"(p.cCin), "s"(p.cKw), "s"(p.cStride), "s"(p.cPad), "s"(p.cWo), "s"(p.cHo), "s"(p.div_wo.magic),
                      "s"(p.div_wo.shift), "s"(p.div_ho.magic), "s"(p.div_ho.shift));
 
@@ -82,11 +130,13 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     const int8_t* A = p.A;
     const int8_t* W = p.W;
     long obase = 0;
-    if (!kLean && p.batched) {
-        const int outer = blockIdx.y / p.inner_count, inner = blockIdx.y % p.inner_count;
-        A += outer * p.a_outer + inner * p.a_inner;
-        W += outer * p.w_outer + inner * p.w_inner;
-        obase = outer * p.o_outer + inner * p.o_inner;
+    if constexpr (!kLean) {
+        if (p.batched) {
+            const int outer = blockIdx.y / p.inner_count, inner = blockIdx.y % p.inner_count;
+            A += outer * p.a_outer + inner * p.a_inner;
+            W += outer * p.w_outer + inner * p.w_inner;
+            obase = outer * p.o_outer + inner * p.o_inner;
+        }
     }
 
     // source of the lane's 16 bytes in every piece: row l / 8 of the piece, chunk l % 8 (swizzled);
@@ -103,7 +153,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     for (int b = 0; b < NI; ++b) {
         const unsigned co = 16u * (unsigned)(chunk0 ^ ((b & 1) << 2));
         if (b < NA) {
-            if (kConv) {
+            if constexpr (kConv) {
                 const int m = min(m0 + 8 * b + lrow, p.M - 1);
                 const int t = (int)quotient((unsigned)m, p.div_wo), wo = m - t * p.cWo, bi = (int)quotient((unsigned)t, p.div_ho), ho = t - bi * p.cHo;
                 ch[b] = ho * p.cStride - p.cPad;
@@ -127,7 +177,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
 
     // ---- aligned operands: slice t of this wavefront goes straight to its ring slot ----
     int ti = 0, tj = 0, tc = 0;   // kConv: tap and channel of the next half slice to load
-    if (kConv) {
+    if constexpr (kConv) {
         const int tap = (int)quotient((unsigned)s0 * 128u, p.div_cin);
         tc = s0 * 128 - tap * p.cCin;
         ti = (int)quotient((unsigned)tap, p.div_kw);
@@ -137,7 +187,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
         const int k0 = 128 * (s0 + t);
         const unsigned dst = ring + slot * SLICE;
         const bool part = ragged && k0 + 128 > p.K;  // wave-uniform
-        if (kConv) {
+        if constexpr (kConv) {
             int h2[2], w2[2], c2[2];
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
@@ -201,7 +251,11 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
     unsigned res_r[GPT];
     float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry (and word of a cell map) per thread; a larger table is staged late
     unsigned map_reg = 0;
-    const bool two_level = !kLean && p.has_table && p.table.cellmap, one_level = kLean ? kTable && kForm == FORM_ANY : p.has_table && !two_level;
+    bool two_level = false, one_level = kTable && kForm == FORM_ANY;
+    if constexpr (!kLean) {
+        two_level = p.has_table && p.table.cellmap;
+        one_level = p.has_table && !two_level;
+    }
     auto request_epilogue = [&] {
         if (n4) {
             const int ncl = min(nb, p.N - 4);
@@ -213,11 +267,12 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
                     res_r[t] = *reinterpret_cast<const u32_a1*>(p.resid + obase + (long)min(m0 + row0 + t * (NT / G4), p.M - 1) * p.ldo + ncl);
             }
         }
-        if (two_level) {
-            kb_reg = p.table.ckb[min(tid, p.table.nkb - 1)];
-            map_reg = reinterpret_cast<const unsigned*>(p.table.cellmap)[min(tid, (p.table.nseg + 3) / 4 - 1)];
-        } else if (one_level) {
-            kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+        if (one_level) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+        if constexpr (!kLean) {
+            if (two_level) {
+                kb_reg = p.table.ckb[min(tid, p.table.nkb - 1)];
+                map_reg = reinterpret_cast<const unsigned*>(p.table.cellmap)[min(tid, (p.table.nseg + 3) / 4 - 1)];
+            }
         }
     };
 
@@ -281,16 +336,19 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
             for (int j = 0; j < TN; ++j)
                 *reinterpret_cast<v4i*>(ring_p + (16 * i + fr) * (BN * 4) + 16 * pslot(16 * i + fr, 4 * j + fq)) = acc[i][j];
     }
-    if (two_level) {
-        unsigned* map = reinterpret_cast<unsigned*>(s_kb + p.table.nkb);
-        const int nw = (p.table.nseg + 3) / 4;
-        if (tid < p.table.nkb) s_kb[tid] = kb_reg;
-        if (tid < nw) map[tid] = map_reg;
-        for (int e = tid + NT; e < p.table.nkb; e += NT) s_kb[e] = p.table.ckb[e];
-        for (int e = tid + NT; e < nw; e += NT) map[e] = reinterpret_cast<const unsigned*>(p.table.cellmap)[e];
-    } else if (one_level) {
+    if (one_level) {
         if (tid < p.table.nseg) s_kb[tid] = kb_reg;
         for (int e = tid + NT; e < p.table.nseg; e += NT) s_kb[e] = p.table.kb[e];
+    }
+    if constexpr (!kLean) {
+        if (two_level) {
+            unsigned* map = reinterpret_cast<unsigned*>(s_kb + p.table.nkb);
+            const int nw = (p.table.nseg + 3) / 4;
+            if (tid < p.table.nkb) s_kb[tid] = kb_reg;
+            if (tid < nw) map[tid] = map_reg;
+            for (int e = tid + NT; e < p.table.nkb; e += NT) s_kb[e] = p.table.ckb[e];
+            for (int e = tid + NT; e < nw; e += NT) map[e] = reinterpret_cast<const unsigned*>(p.table.cellmap)[e];
+        }
     }
     __syncthreads();
     if (NGRP < NT && row0 >= BM) return;
@@ -304,7 +362,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
         return s;
     };
     if constexpr (kLean) {
-        const long at0 = (long)(m0 + row0) * p.ldo + nb;
+        const long at0 = (long)(m0 + row0) * (long)p.ldo + nb;
         const int left = p.M - (m0 + row0);
         v4f inv = {p.out_inv_scale, p.out_inv_scale, p.out_inv_scale, p.out_inv_scale};
         if (kEpi == EPI_Q && p.split_cols > 0) {
@@ -334,9 +392,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(GemmParams p)
                 else *reinterpret_cast<unsigned*>(p.out_q + at) =
                          pack4(requant(y[t][0], inv[0]), requant(y[t][1], inv[1]), requant(y[t][2], inv[2]), requant(y[t][3], inv[3]));
             }
-        return;
-    }
-    if (n4 && p.vec_out) {
+    } else if (n4 && p.vec_out) {
         v4f inv = {p.out_inv_scale, p.out_inv_scale, p.out_inv_scale, p.out_inv_scale};
         if (p.out_inv_scale_vec) {
             inv = *reinterpret_cast<const v4f_a4*>(p.out_inv_scale_vec + nb);
@@ -405,14 +461,16 @@ static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, h
     p.div_tiles_m = fast_div(p.tiles_m);
     if (kConv) p.div_wo = fast_div(p.cWo), p.div_ho = fast_div(p.cHo), p.div_cin = fast_div(p.cCin), p.div_kw = fast_div(p.cKw);
     const int grid = (p.tiles_m * p.tiles_n + 7) / 8 * 8;   // the kernel's eighths are (tiles + 7) / 8 each
-    hipLaunchKernelGGL(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, p);
+    DirectArgs<kConv, kEpi> args;
+    direct_args(args, p);
+    hipLaunchKernelGGL(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, args);
     return NM_OK;
 }
 
 // The fixed epilogue that computes what p asks for (and nothing else), or EPI_GENERIC.
 static int lean_epilogue(const GemmParams& p, int align, bool conv, int batches)
 {
-    if (align < 16 || batches != 1 || p.N % 4 != 0 || !p.vec_out || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
+    if (align < 16 || batches != 1 || p.N % 4 != 0 || !p.vec_out || p.ldo >= (1LL << 31) || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
     if (p.dbg_seg || p.out_acc || p.out_inv_scale_vec || (p.out_q != nullptr) == (p.out_f32 != nullptr)) return EPI_GENERIC;
     if (p.has_table && (p.table.cellmap || p.table.clamp_input || p.split_cols > 0)) return EPI_GENERIC;
     if (p.out_f32) return p.resid && !p.has_table ? EPI_F32_RESID : EPI_GENERIC;

@@ -34,6 +34,19 @@ struct DevTable {
     float u0;
 };
 
+// Division by a number the host knows: exact for every n below 2^31 (Granlund and Montgomery, "Division by invariant
+// integers using multiplication", 1994: a multiplier of 32 bits does for dividends of 31).
+struct FastDiv {
+    unsigned d, magic, shift;
+};
+static inline FastDiv fast_div(int d)
+{
+    unsigned s = 0;
+    while ((1u << s) < (unsigned)d) ++s;
+    // d == 1: the quotient is the number itself (magic 0)
+    return {(unsigned)d, s == 0 ? 0u : (unsigned)((1ull << (31 + s)) / (unsigned)d) + 1u, s == 0 ? 0u : s - 1u};
+}
+
 // Bytes of the two-level form: {k, b} per merged segment, a byte per primary cell (padded to eight).
 inline size_t two_level_bytes(const DevTable& t) { return 8 * (size_t)t.nkb + (((size_t)t.nseg + 7) & ~(size_t)7); }
 
