@@ -297,42 +297,35 @@ void gemm_stream_kernel(GemmParams p)
     const int wave_m = (wave_t / WAVES_N) * WM;
     const int wave_n = (wave_t % WAVES_N) * WN;
 
+    // every argument of the prologue in one step (left alone, the compiler fetches them in eight dependent ones)
+    asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.bias), "s"(p.alpha_vec), "s"(p.resid), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.lda), "s"(p.ldw),
+                 "s"(p.ldo), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.alpha), "s"(p.out_inv_scale), "s"(p.has_table), "s"(p.batched),
+                 "s"(p.r16), "s"(p.split_cols), "s"(p.table.kb), "s"(p.table.nseg), "s"(p.table.cellmap), "s"(p.div_group.magic),
+                 "s"(p.div_group.shift));
+    if (kConv)
+        asm volatile("" : : "s"(p.cH), "s"(p.cW), "s"(p.cCin), "s"(p.cKw), "s"(p.cStride), "s"(p.cPad), "s"(p.cWo), "s"(p.cHo), "s"(p.div_wo.magic),
+                     "s"(p.div_wo.shift), "s"(p.div_ho.magic), "s"(p.div_ho.shift));
     // XCD-aware tile order: ids that share (id mod 8) are renumbered to be consecutive, then
     // consecutive ids fill groups of 8 tile rows column by column
     int id = blockIdx.x;
     const int ntiles = p.tiles_m * p.tiles_n;
     if (ntiles % 8 == 0) id = (id % 8) * (ntiles / 8) + id / 8;
     constexpr int GM = 8;
-    const int group = id / (GM * p.tiles_n);
+    const int group = (int)quotient((unsigned)id, p.div_group);   // by GM * tiles_n
     const int first_m = group * GM;
     const int gm = min(GM, p.tiles_m - first_m);
     const int in_group = id - group * GM * p.tiles_n;
-    const int tile_m = first_m + in_group % gm;
-    const int tile_n = in_group / gm;
+    const int tile_n = gm == GM ? in_group / GM : in_group / gm;
+    const int tile_m = first_m + in_group - tile_n * gm;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int outer = blockIdx.y / p.inner_count;
-    const int inner = blockIdx.y % p.inner_count;
-    const int8_t* __restrict__ A = p.A + outer * p.a_outer + inner * p.a_inner;
-    const int8_t* __restrict__ W = p.W + outer * p.w_outer + inner * p.w_inner;
-    const long obase = outer * p.o_outer + inner * p.o_inner;
-
-    if (p.has_table) { if (p.table.cellmap) stage_table_two_level(s_kb, p.table); else stage_table(s_kb, p.table); }
-    // per-column epilogue parameters of this tile go to LDS now (their latency hides behind the
-    // main loop) so that the epilogue itself issues no global loads for them
-    if (kEpi != EPI_ACC) {
-        for (int t = tid; t < BN; t += 64 * NW) {
-            const int n = n0 + t;
-            float sc = p.alpha, bi = 0.0f, iv = p.out_inv_scale;
-            if (n < p.N) {
-                if (p.bias) bi = p.bias[n];
-                if (p.alpha_vec) sc = p.alpha_vec[n];
-                if (kEpi == EPI_GENERIC && p.out_inv_scale_vec) iv = p.out_inv_scale_vec[n];
-                else if (p.split_cols > 0) iv = n >= 2 * p.split_cols ? p.inv3[2] : (n >= p.split_cols ? p.inv3[1] : p.inv3[0]);
-            }
-            s_cols[t] = sc;
-            s_cols[BN + t] = bi;
-            s_cols[2 * BN + t] = iv;
-        }
+    const int8_t* __restrict__ A = p.A;
+    const int8_t* __restrict__ W = p.W;
+    long obase = 0;
+    if (p.batched) {
+        const int outer = blockIdx.y / p.inner_count, inner = blockIdx.y % p.inner_count;
+        A += outer * p.a_outer + inner * p.a_inner;
+        W += outer * p.w_outer + inner * p.w_inner;
+        obase = outer * p.o_outer + inner * p.o_inner;
     }
 
     // per-lane source pointers of this wavefront's blocks (k = 0)
@@ -349,8 +342,8 @@ void gemm_stream_kernel(GemmParams p)
         if (r < BM) {
             const int m = min(m0 + r, p.M - 1);
             if (kConv) {
-                const int wo = m % p.cWo, t = m / p.cWo;
-                const int ho = t % p.cHo, bi = t / p.cHo;
+                const int t = (int)quotient((unsigned)m, p.div_wo), wo = m - t * p.cWo;
+                const int bi = (int)quotient((unsigned)t, p.div_ho), ho = t - bi * p.cHo;
                 conv_h[b] = ho * p.cStride - p.cPad;
                 conv_w[b] = wo * p.cStride - p.cPad;
                 src[b] = A + (long)bi * p.cH * p.cW * p.cCin + 16 * chunk;  // image base + chunk
@@ -393,6 +386,53 @@ void gemm_stream_kernel(GemmParams p)
         }
     };
 
+    const int nk = p.K / BK;
+#pragma unroll
+    for (int st = 0; st < kStages - 1; ++st)
+        if (st < nk) issue(st, st, 0, 1);
+
+    // Behind the first slices, what only the epilogue reads; it stays in registers until the products are done.  (In
+    // front of them, each waited for on its way to LDS, the table and the columns' vectors kept the first slice from
+    // being requested for two memory round trips.)
+    // The specialised residual epilogues read the int8 residual rows this wavefront will finish with 16-byte
+    // row loads; after the main loop they pass through the (then free) LDS patch to the lanes that need them.
+    // Every lane makes every load (rows and columns past the edge: the last ones), so that their number is known
+    // to the waits of the main loop.
+    constexpr bool kResid8 = kEpi == EPI_F32_RESID || kEpi == EPI_Q_TABLE_RESID;
+    constexpr int RCPR = WN / 16;                 // 16-byte chunks per residual row of the sub-tile
+    constexpr int RCH = 32 * TMF * RCPR;          // chunks of the rows this wavefront finishes
+    constexpr int RL = RCH / 64;
+    static_assert(RCH % 64 == 0, "chunks split evenly");
+    v4i rpre[RL];
+    const bool resid_rows = kResid8 && p.r16;     // uniform
+    if (resid_rows) {
+#pragma unroll
+        for (int t = 0; t < RL; ++t) {
+            const int c = lane + 64 * t;
+            const int mr = min(m0 + wave_m + 32 * (kg * TMF) + c / RCPR, p.M - 1), n = min(n0 + wave_n + 16 * (c % RCPR), p.N - 16);
+            rpre[t] = *reinterpret_cast<const v4i*>(p.resid + obase + (long)mr * p.ldo + n);
+        }
+    }
+    static_assert(BN <= 64 * NW, "a column per thread");
+    float col_scale = p.alpha, col_bias = 0.0f, col_inv = p.out_inv_scale;
+    if (kEpi != EPI_ACC) {
+        const int n = min(n0 + min(tid, BN - 1), p.N - 1);
+        if (p.bias) col_bias = p.bias[n];
+        if (p.alpha_vec) col_scale = p.alpha_vec[n];
+        if (kEpi == EPI_GENERIC && p.out_inv_scale_vec) col_inv = p.out_inv_scale_vec[n];
+        else if (p.split_cols > 0) col_inv = n >= 2 * p.split_cols ? p.inv3[2] : (n >= p.split_cols ? p.inv3[1] : p.inv3[0]);
+    }
+    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry (and word of a cell map) per thread; a larger table is staged late
+    unsigned map_reg = 0;
+    if (p.has_table) {
+        if (p.table.cellmap) {
+            kb_reg = p.table.ckb[min(tid, p.table.nkb - 1)];
+            map_reg = reinterpret_cast<const unsigned*>(p.table.cellmap)[min(tid, (p.table.nseg + 3) / 4 - 1)];
+        } else {
+            kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+        }
+    }
+
     v16i acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -400,33 +440,6 @@ void gemm_stream_kernel(GemmParams p)
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-
-    // The specialised residual epilogues read the int8 residual rows this wavefront will finish
-    // with 16-byte row loads, issued now so that they travel during the main loop; after it they
-    // pass through the (then free) LDS patch to the lanes that need them.
-    constexpr bool kResid8 = kEpi == EPI_F32_RESID || kEpi == EPI_Q_TABLE_RESID;
-    constexpr int RCPR = WN / 16;                 // 16-byte chunks per residual row of the sub-tile
-    constexpr int RCH = 32 * TMF * RCPR;          // chunks of the rows this wavefront finishes
-    constexpr int RL = (RCH + 63) / 64;
-    v4i rpre[RL];
-    const bool resid_rows = kResid8 && p.r16;     // uniform
-    if (resid_rows) {
-#pragma unroll
-        for (int t = 0; t < RL; ++t) {
-            const int c = lane + 64 * t;
-            rpre[t] = v4i{0, 0, 0, 0};
-            if (c < RCH) {
-                const int mr = m0 + wave_m + 32 * (kg * TMF) + c / RCPR, n = n0 + wave_n + 16 * (c % RCPR);
-                if (mr < p.M && n + 15 < p.N)
-                    rpre[t] = *reinterpret_cast<const v4i*>(p.resid + obase + (long)mr * p.ldo + n);
-            }
-        }
-    }
-
-    const int nk = p.K / BK;
-#pragma unroll
-    for (int st = 0; st < kStages - 1; ++st)
-        if (st < nk) issue(st, st, 0, 1);
 
     const int frag_row = lane & 31, frag_half = lane >> 5;
     // LDS offsets of this lane's fragments inside a stage, per k-step this wavefront owns
@@ -444,7 +457,11 @@ void gemm_stream_kernel(GemmParams p)
         // The loads of stage kt are older than those of the stages issued after it: wait until only
         // the younger ones are in flight.  `young` = number of younger stages already issued.
         const int young = min(kStages - 2, nk - 1 - kt);
-        if (young <= 0) wait_vmcnt<0>();
+        if (kResid8 && resid_rows && kt < kStages - 1) {   // the residual's loads are younger still
+            if (young <= 0) wait_vmcnt<RL>();
+            else if (young == 1) { if (has_last) wait_vmcnt<LB + RL>(); else wait_vmcnt<LB - 1 + RL>(); }
+            else { if (has_last) wait_vmcnt<2 * LB + RL>(); else wait_vmcnt<2 * (LB - 1) + RL>(); }
+        } else if (young <= 0) wait_vmcnt<0>();
         else if (young == 1) { if (has_last) wait_vmcnt<LB>(); else wait_vmcnt<LB - 1>(); }
         else { if (has_last) wait_vmcnt<2 * LB>(); else wait_vmcnt<2 * (LB - 1)>(); }
         __syncthreads();  // stage kt has landed for every wavefront; stage kt - 1 is free again
@@ -467,6 +484,25 @@ void gemm_stream_kernel(GemmParams p)
             if (more) issue(kt + kStages - 1, nxt, kk, KSW);  // in the shadow of the MFMAs just issued
         }
         stage = stage + 1 == kStages ? 0 : stage + 1;
+    }
+
+    if (kEpi != EPI_ACC && tid < BN) {
+        s_cols[tid] = col_scale;
+        s_cols[BN + tid] = col_bias;
+        s_cols[2 * BN + tid] = col_inv;
+    }
+    if (p.has_table) {
+        if (p.table.cellmap) {
+            unsigned* map = reinterpret_cast<unsigned*>(s_kb + p.table.nkb);
+            const int nw = (p.table.nseg + 3) / 4;
+            if (tid < p.table.nkb) s_kb[tid] = kb_reg;
+            if (tid < nw) map[tid] = map_reg;
+            for (int e = tid + 64 * NW; e < p.table.nkb; e += 64 * NW) s_kb[e] = p.table.ckb[e];
+            for (int e = tid + 64 * NW; e < nw; e += 64 * NW) map[e] = reinterpret_cast<const unsigned*>(p.table.cellmap)[e];
+        } else {
+            if (tid < p.table.nseg) s_kb[tid] = kb_reg;
+            for (int e = tid + 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
+        }
     }
 
     // ---- combine the two k-halves (KSPLIT == 2): swap accumulator halves through LDS ----------
@@ -674,6 +710,9 @@ static int32_t launch_stream_epi(GemmParams& p, int batches, size_t table_bytes,
     if (once_rc) return once_rc;
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
+    p.batched = batches > 1;
+    p.div_group = fast_div(8 * p.tiles_n);
+    if (kConv) p.div_wo = fast_div(p.cWo), p.div_ho = fast_div(p.cHo);
     hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, batches), dim3(64 * WAVES_M * WAVES_N * KSPLIT), shmem, s, p);
     return NM_OK;
 }

@@ -51,8 +51,8 @@ struct GemmParams {
     // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
     int relu;     // relu_codes holds for the table and the one output scale
-    int batched;  // small-tile kernel: more than one problem (grid.y)
-    FastDiv div_tiles_m, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, cWo, cHo, cCin and cKw
+    int batched;  // more than one problem (grid.y)
+    FastDiv div_tiles_m, div_group, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, 8 * tiles_n, cWo, cHo, cCin and cKw
 };
 
 // The small-tile kernel (nm_gemm_direct.hip).  align: alignment of operand rows and chunks in bytes (16, 4 or
