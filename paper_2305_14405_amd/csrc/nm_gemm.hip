@@ -39,7 +39,7 @@ static bool force_generic()
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-3>|unaligned<0-3> forces
+// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3> forces
 // that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
 // 256x192 configuration, which the tile kernel has replaced).
 static int forced_cfg()
@@ -918,26 +918,20 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
     // chosen when the output is too small for the larger tiles to occupy the chip, and for unaligned operands
     // that the register-staged tiles do not take.
-    // Against the tile kernel with more than three k-slices the line is 0.9 million outputs, between two: tiles over
-    // this kernel, products of layers of width 512 to 1024, geometric means (best to worst), with the weights of launch
-    // after launch in the caches and from memory:
-    //   million outputs   0.35   0.5    0.65              0.8               0.95              1.15   1.4
-    //   in the caches     1.18   1.04   0.89 (.77..1.08)  0.89 (.80..1.04)  0.87 (.79..0.98)  0.73   0.72
-    //   from memory       1.27   1.17   1.00 (.85..1.30)  0.98 (.84..1.28)  0.97 (.87..1.23)  0.81   0.80
-    // The losses are fp32 outputs of a long contraction, where few workgroups keep few loads in flight (847 x 768 x 3072
-    // from memory 10.9 us, tiles 13.5; 635 x 1024 x 4096 12.5, 16.2).  Stacks of 12 layers whose fp32 products have 0.65
-    // to 0.79 million outputs, widths 512, 768 and 1024: this kernel ahead by 2 to 8 % at all seven with the weights from
-    // memory (11 x 77 tokens, width 768: 551 us, tiles 573), between 4 % behind and 1 % ahead with the same weights again.
-    // With three k-slices (K = 384) the line, 2.45 million, was drawn when the tiles had three stages; with two they lost at 0.65
-    // million (6 %) and win from 1.15 on (10 %; 26 % at 1.4).  The streaming kernel's tiles need
-    // about a million outputs, more when the contraction is short and a large tile is mostly prologue and
-    // epilogue.
+    // Against the tile kernel the line is 1.05 million outputs, 256 tiles of 64x64: up to there one round of its tiles holds
+    // the output, beyond it a second one begins.  Tiles over this kernel, us, products of layers of width 384 to 1024:
+    //    512 x 2048 x  512  4.64 | 4.17     1200 x 768 x 3072  11.1 | 10.2    1024 x 1024 x 4096  13.0 | 10.8
+    //    700 x 1536 x  512  3.98 | 4.40     1400 x 768 x 3072  11.2 | 14.8    1200 x 1024 x 4096  13.7 | 16.5
+    //   1024 x 1152 x  384  3.77 | 4.25     2500 x 384 x  384  4.69 | 4.47    3300 x  384 x  384  4.90 | 5.19
+    // The largest losses on this side are 300 x 3072 x 1024 (4.9 | 5.3) and 1500 x 640 x 640 (5.1 | 5.2).  The streaming
+    // kernel's tiles need about a million outputs, more when the contraction is short and a large tile is mostly
+    // prologue and epilogue.
     const int64_t a_extent = g.conv ? (int64_t)(g.M / (g.cHo * g.cWo)) * g.cH * g.cW * g.cCin : (int64_t)(g.M - 1) * g.lda + g.K;
     const bool direct_ok = !force_generic() && !g.w_is_kn && a_extent < (1LL << 31) && (int64_t)(g.N - 1) * g.ldw + g.K < (1LL << 31);
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
-    const int64_t direct_below = tile_ok ? (g.K <= 384 ? 2450000 : 900000) : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
+    const int64_t direct_below = tile_ok ? 1050000 : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
     const bool direct = direct_ok && ((forced_cfg() >= 10 && forced_cfg() < 20) || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
     // Register-staged tiles, for operands that cannot go to LDS directly in whole slices: from 0.8 million outputs on.  Below
     // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do

@@ -468,9 +468,9 @@ static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, h
 }
 
 // The fixed epilogue that computes what p asks for (and nothing else), or EPI_GENERIC.
-static int lean_epilogue(const GemmParams& p, int align, bool conv, int batches)
+static int lean_epilogue(const GemmParams& p, bool conv, int batches)
 {
-    if (align < 16 || batches != 1 || p.N % 4 != 0 || !p.vec_out || p.ldo >= (1LL << 31) || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
+    if (batches != 1 || p.N % 4 != 0 || !p.vec_out || p.ldo >= (1LL << 31) || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
     if (p.dbg_seg || p.out_acc || p.out_inv_scale_vec || (p.out_q != nullptr) == (p.out_f32 != nullptr)) return EPI_GENERIC;
     if (p.has_table && (p.table.cellmap || p.table.clamp_input || p.split_cols > 0)) return EPI_GENERIC;
     if (p.out_f32) return p.resid && !p.has_table ? EPI_F32_RESID : EPI_GENERIC;
@@ -479,9 +479,9 @@ static int lean_epilogue(const GemmParams& p, int align, bool conv, int batches)
 }
 
 template <int BM, int BN, int KW, int D>
-static int32_t launch_direct_c(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, hipStream_t s)
+static int32_t launch_direct_aligned(GemmParams& p, bool conv, int batches, size_t table_bytes, hipStream_t s)
 {
-    const int epi = lean_epilogue(p, align, conv, batches);
+    const int epi = lean_epilogue(p, conv, batches);
     const bool two = p.has_table && p.table.two_seg;
     if (conv) {
         if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q>(p, batches, 0, s);
@@ -493,29 +493,67 @@ static int32_t launch_direct_c(GemmParams& p, int align, bool conv, int batches,
     if (epi == EPI_Q_TABLE_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE_RESID, FORM_TWO_SEGMENTS>(p, batches, 0, s);
     if (epi == EPI_Q_TABLE && two) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE, FORM_TWO_SEGMENTS>(p, batches, 0, s);
     if (epi == EPI_Q_TABLE) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE>(p, batches, table_bytes, s);
-    if (align >= 16) return launch_direct_t<BM, BN, KW, D, 16, false>(p, batches, table_bytes, s);
-    if (align >= 4) return launch_direct_t<BM, BN, KW, D, 4, false>(p, batches, table_bytes, s);
-    return launch_direct_t<BM, BN, KW, D, 1, false>(p, batches, table_bytes, s);
+    return launch_direct_t<BM, BN, KW, D, 16, false>(p, batches, table_bytes, s);
 }
 
-// Which tile: the smallest one whose workgroups still fit the chip about once; beyond that the one that
-// reads its operands least often, the sooner the longer the contraction.  (Timings of every
-// configuration over 125 products of the encoder at widths 256 .. 1024 and 64 .. 3200 rows, and 51
-// convolutions; us for 16x32 / 32x32 with eight wavefronts / 32x32 with four / 32x64: 128x768x3072
-// 5.3 / 5.9 / 5.5 / 9.0, 392x512x4608 11.5 / 7.6 / 8.8 / 12.9, 600x768x768 6.8 / 5.3 / 5.0 / 5.9, 1200x768x3072
-// 28.6 / 19.9 / 15.0 / 12.3, 1600x1536x384 17.0 / 12.6 / 9.0 / 10.0.)
+template <int BM, int BN, int KW>
+static int32_t launch_direct_unaligned(GemmParams& p, int align, int batches, size_t table_bytes, hipStream_t s)
+{
+    if (align >= 4) return launch_direct_t<BM, BN, KW, 1, 4, false>(p, batches, table_bytes, s);
+    return launch_direct_t<BM, BN, KW, 1, 1, false>(p, batches, table_bytes, s);
+}
+
+// Which tile, aligned operands: the one whose predicted time is smallest,
+//   start + L * (tile + slice * slices) + R * (round + chain * c) + wave * c   us,
+// c being the slices of a wavefront, L the workgroups of the CU that has most and R the rounds it takes for them (as many
+// workgroups share a CU as LDS and its 32 wavefronts allow).  The constants are least-squares fits to 285 measured
+// products (16 to 1500 rows, the four products of layers of width 384 to 1024, convolutions of a residual CNN as products;
+// rms 5 to 9 %).  Over those the chosen tile is 0.8 % slower than the best of nine (11 % at worst), the rule by the
+// number of tiles before it 3.0 %.  us, 16x32 | 32x32 | 32x64 with four wavefronts, with eight | 48x64 | 64x64:
+//   128 x 768 x 3072   3.9 | 3.9 | 5.9 | 5.2 | 5.8 | 6.9      847 x  768 x 3072  11.4 | 10.1 | 10.5 | 12.0 | 8.4 | 9.2
+//   512 x 1024 x 4096   10 | 8.9 | 9.8 | 7.7 | 8.4 | 9.4     1024 x 1024 x 1024   6.6 |  6.5 |  6.0 |  7.2 | 7.9 | 5.9
+static int choose_direct(const GemmParams& p, int batches, size_t table_bytes)
+{
+    static const struct { int bm, bn, kw, depth; double start, tile, round, slice, chain, wave; } kTiles[] = {
+        {16, 32, 8, 3, 1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {32, 32, 4, 2, 1.92, 0.08, 0.45, 0.102, 0.14, -0.25},
+        {32, 64, 4, 1, 1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {32, 64, 8, 1, 1.92, 0.43, 0.43, 0.125, 0.69, -0.74},
+        {48, 64, 4, 2, 1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {64, 64, 4, 2, 1.38, 0.63, 1.45, 0.132, 0.41, -0.20}};
+    int best = 2;
+    double best_us = 0.0;
+    bool any = false;
+    const int nk = (p.K + 127) / 128;
+    for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+        const auto& t = kTiles[c];
+        const int chain = (nk + t.kw - 1) / t.kw;
+        const size_t lds = (size_t)t.kw * (chain < t.depth ? chain : t.depth) * (t.bm + t.bn) * 128 + table_bytes;
+        if (lds > 160 * 1024) continue;
+        const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * batches, L = (tiles + 255) / 256;
+        const long fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap, R = (L + share - 1) / share;
+        const double us = t.start + L * (t.tile + t.slice * nk) + R * (t.round + t.chain * chain) + t.wave * chain;
+        if (!any || us < best_us) best_us = us, best = c, any = true;
+    }
+    return best;
+}
+
+// forced: tile 0 .. 5, or -1 for the rule.  Operands aligned to 4 or 1 bytes pass through registers, a slice at a time: the
+// smallest tile whose workgroups still fit the chip about once, beyond that the one that reads its operands least often.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s)
 {
-    const long t32 = (long)((p.M + 31) / 32) * ((p.N + 31) / 32) * batches;
-    const long wide_from = p.K >= 576 ? 640 : p.K >= 512 ? 1100 : 1L << 40;
-    int cfg = t32 <= 128 ? 0 : t32 <= 256 && p.K >= 2048 ? 1 : t32 <= wide_from ? 2 : 3;
-    if (forced >= 0) cfg = forced;
-    if (cfg == 0 && table_bytes > 16 * 1024) cfg = 1;   // 144 KB of slices: LDS holds a table of 2048 segments beside them
-    switch (cfg) {
-    case 0: return launch_direct_c<16, 32, 8, 3>(p, align, conv, batches, table_bytes, s);
-    case 1: return launch_direct_c<32, 32, 8, 2>(p, align, conv, batches, table_bytes, s);
-    case 2: return launch_direct_c<32, 32, 4, 2>(p, align, conv, batches, table_bytes, s);
-    default: return launch_direct_c<32, 64, 4, 1>(p, align, conv, batches, table_bytes, s);
+    if (align < 16) {
+        const long t32 = (long)((p.M + 31) / 32) * ((p.N + 31) / 32) * batches;
+        const long wide_from = p.K >= 576 ? 640 : p.K >= 512 ? 1100 : 1L << 40;
+        if (t32 <= 128) return launch_direct_unaligned<16, 32, 8>(p, align, batches, table_bytes, s);
+        if (t32 <= 256 && p.K >= 2048) return launch_direct_unaligned<32, 32, 8>(p, align, batches, table_bytes, s);
+        if (t32 <= wide_from) return launch_direct_unaligned<32, 32, 4>(p, align, batches, table_bytes, s);
+        return launch_direct_unaligned<32, 64, 4>(p, align, batches, table_bytes, s);
+    }
+    switch (forced >= 0 ? forced : choose_direct(p, batches, table_bytes)) {
+    case 0: return launch_direct_aligned<16, 32, 8, 3>(p, conv, batches, table_bytes, s);
+    case 1: return launch_direct_aligned<32, 32, 4, 2>(p, conv, batches, table_bytes, s);
+    case 2: return launch_direct_aligned<32, 64, 4, 1>(p, conv, batches, table_bytes, s);
+    case 3: return launch_direct_aligned<32, 64, 8, 1>(p, conv, batches, table_bytes, s);
+    case 4: return launch_direct_aligned<48, 64, 4, 2>(p, conv, batches, table_bytes, s);
+    default: return launch_direct_aligned<64, 64, 4, 2>(p, conv, batches, table_bytes, s);
     }
 }
 
