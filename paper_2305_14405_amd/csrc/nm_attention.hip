@@ -621,7 +621,7 @@ static int32_t launch_attn_kernel(Kern kern, std::once_flag& once, int32_t& once
     if (once_rc) return once_rc;
     p.div_qblocks = fast_div(p.qblocks);
     p.div_heads = fast_div(p.heads);
-    hipLaunchKernelGGL(kern, dim3((p.total + 7) / 8 * 8), dim3(threads), shmem, st, p);
+    queue_kernel(kern, dim3((p.total + 7) / 8 * 8), dim3(threads), shmem, st, p);
     return NM_OK;
 }
 

@@ -385,7 +385,7 @@ static int32_t launch_block_t(const BlockParams& p, size_t shmem, hipStream_t s)
                             "hipFuncSetAttribute(encoder_block_kernel)");
     });
     if (once_rc) return once_rc;
-    hipLaunchKernelGGL(kern, dim3((p.M + 16 * RT - 1) / (16 * RT)), dim3(kBlockThreads), shmem, s, p);
+    queue_kernel(kern, dim3((p.M + 16 * RT - 1) / (16 * RT)), dim3(kBlockThreads), shmem, s, p);
     return check_hip(hipGetLastError(), "encoder_block launch");
 }
 template <int RT>

@@ -459,7 +459,7 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
         if (!aligned(ws, 256)) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace not 256-byte aligned");
         if (ws_bytes < pl.ws_bytes)
             return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace %zu bytes < %zu needed", ws_bytes, pl.ws_bytes);
-        hipLaunchKernelGGL(stem_pack_filter_kernel, dim3((64 * d->kh * 8 + 255) / 256), dim3(256), 0, stream, d->w,
+        queue_kernel(stem_pack_filter_kernel, dim3((64 * d->kh * 8 + 255) / 256), dim3(256), 0, stream, d->w,
                            d->Cout, d->kh, d->kw, d->Cin, static_cast<int8_t*>(ws));
         StemParams sp{};
         sp.x = d->x; sp.w = static_cast<const int8_t*>(ws); sp.bias = d->bias; sp.alpha_vec = d->alpha_vec; sp.alpha = d->alpha;
@@ -480,7 +480,7 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
         sp.front = (int)(operands > rows ? operands : rows);
         const size_t shmem = sp.front + behind;
         const dim3 grid(((pl.Ho + 15) / 16) * ((pl.Wo + 15) / 16), d->B);
-        hipLaunchKernelGGL(stem_conv_kernel, grid, dim3(256), shmem, stream, sp);
+        queue_kernel(stem_conv_kernel, grid, dim3(256), shmem, stream, sp);
         return check_hip(hipGetLastError(), "nm_conv2d_pwl direct launch");
     }
     if (pl.route == 0) {
@@ -497,10 +497,10 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
             return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace %zu bytes < %zu needed", ws_bytes, pl.ws_bytes);
         int8_t* patches = static_cast<int8_t*>(ws);
         int8_t* wpad = patches + (size_t)pl.M * pl.K16;
-        hipLaunchKernelGGL(im2col_kernel, dim3(grid_for(pl.M * (pl.K16 / 16))), dim3(kConvThreads), 0, stream,
+        queue_kernel(im2col_kernel, dim3(grid_for(pl.M * (pl.K16 / 16))), dim3(kConvThreads), 0, stream,
                            d->x, d->H, d->W, d->Cin, d->kw, d->stride, d->pad, pl.Ho, pl.Wo, pl.K, pl.K16, pl.M,
                            patches);
-        hipLaunchKernelGGL(pad_rows_kernel, dim3(grid_for((long)d->Cout * pl.K16)), dim3(kConvThreads), 0, stream,
+        queue_kernel(pad_rows_kernel, dim3(grid_for((long)d->Cout * pl.K16)), dim3(kConvThreads), 0, stream,
                            d->w, d->Cout, pl.K, pl.K16, wpad);
         if ((rc = check_hip(hipGetLastError(), "nm_conv2d_pwl patch matrix launch"))) return rc;
         g.A = patches; g.lda = pl.K16;
@@ -525,14 +525,14 @@ int32_t nm_maxpool_i8(const int8_t* x, int32_t B, int32_t H, int32_t W, int32_t 
     const bool vec = C % 4 == 0 && aligned(x, 4) && aligned(y, 4);
     if (C % 16 == 0 && aligned(x, 16) && aligned(y, 16)) {
         const long total16 = rows * (C / 16);
-        hipLaunchKernelGGL(maxpool16_kernel, dim3(grid_for(total16)), dim3(kConvThreads), 0, (hipStream_t)stream,
+        queue_kernel(maxpool16_kernel, dim3(grid_for(total16)), dim3(kConvThreads), 0, (hipStream_t)stream,
                            x, H, W, C, k, stride, pad, Ho, Wo, total16, y);
         return check_hip(hipGetLastError(), "nm_maxpool_i8 launch");
     }
     const long total = rows * (vec ? C / 4 : C);
-    if (vec) hipLaunchKernelGGL(maxpool_kernel<true>, dim3(grid_for(total)), dim3(kConvThreads), 0, (hipStream_t)stream,
+    if (vec) queue_kernel(maxpool_kernel<true>, dim3(grid_for(total)), dim3(kConvThreads), 0, (hipStream_t)stream,
                                 x, H, W, C, k, stride, pad, Ho, Wo, total, y);
-    else hipLaunchKernelGGL(maxpool_kernel<false>, dim3(grid_for(total)), dim3(kConvThreads), 0, (hipStream_t)stream,
+    else queue_kernel(maxpool_kernel<false>, dim3(grid_for(total)), dim3(kConvThreads), 0, (hipStream_t)stream,
                             x, H, W, C, k, stride, pad, Ho, Wo, total, y);
     return check_hip(hipGetLastError(), "nm_maxpool_i8 launch");
 }
@@ -547,10 +547,10 @@ int32_t nm_avgpool_i8(const int8_t* x, int32_t B, int32_t HW, int32_t C, float a
     if (!x) return fail(NM_ERR_INVALID_ARG, "nm_avgpool_i8: x is NULL");
     const bool vec = C % 4 == 0 && aligned(x, 4) && (!out_q || aligned(out_q, 4)) && (!out_f32 || aligned(out_f32, 16));
     if (vec)
-        hipLaunchKernelGGL(avgpool_kernel<true>, dim3(grid_for((long)B * (C / 4))), dim3(kConvThreads), 0,
+        queue_kernel(avgpool_kernel<true>, dim3(grid_for((long)B * (C / 4))), dim3(kConvThreads), 0,
                            (hipStream_t)stream, x, B, HW, C, alpha, out_inv_scale, out_q, out_f32);
     else
-        hipLaunchKernelGGL(avgpool_kernel<false>, dim3(grid_for((long)B * C)), dim3(kConvThreads), 0,
+        queue_kernel(avgpool_kernel<false>, dim3(grid_for((long)B * C)), dim3(kConvThreads), 0,
                            (hipStream_t)stream, x, B, HW, C, alpha, out_inv_scale, out_q, out_f32);
     return check_hip(hipGetLastError(), "nm_avgpool_i8 launch");
 }

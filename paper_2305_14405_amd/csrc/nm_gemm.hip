@@ -689,10 +689,10 @@ void gemm_stream_kernel(GemmParams p)
 template <int BM, int BN, int WM, int WN>
 static void launch_cfg(const GemmParams& p, bool al, bool wkn, dim3 grid, size_t shmem, hipStream_t s)
 {
-    if (al && !wkn) hipLaunchKernelGGL((gemm_pwl_kernel<BM, BN, WM, WN, true, false>), grid, dim3(kGemmThreads), shmem, s, p);
-    else if (!al && !wkn) hipLaunchKernelGGL((gemm_pwl_kernel<BM, BN, WM, WN, false, false>), grid, dim3(kGemmThreads), shmem, s, p);
-    else if (al && wkn) hipLaunchKernelGGL((gemm_pwl_kernel<BM, BN, WM, WN, true, true>), grid, dim3(kGemmThreads), shmem, s, p);
-    else hipLaunchKernelGGL((gemm_pwl_kernel<BM, BN, WM, WN, false, true>), grid, dim3(kGemmThreads), shmem, s, p);
+    if (al && !wkn) queue_kernel(gemm_pwl_kernel<BM, BN, WM, WN, true, false>, grid, dim3(kGemmThreads), shmem, s, p);
+    else if (!al && !wkn) queue_kernel(gemm_pwl_kernel<BM, BN, WM, WN, false, false>, grid, dim3(kGemmThreads), shmem, s, p);
+    else if (al && wkn) queue_kernel(gemm_pwl_kernel<BM, BN, WM, WN, true, true>, grid, dim3(kGemmThreads), shmem, s, p);
+    else queue_kernel(gemm_pwl_kernel<BM, BN, WM, WN, false, true>, grid, dim3(kGemmThreads), shmem, s, p);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int KSPLIT, int BK, int kStages, int kEpi, bool kConv = false>
@@ -713,7 +713,7 @@ static int32_t launch_stream_epi(GemmParams& p, int batches, size_t table_bytes,
     p.batched = batches > 1;
     p.div_group = fast_div(8 * p.tiles_n);
     if (kConv) p.div_wo = fast_div(p.cWo), p.div_ho = fast_div(p.cHo);
-    hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, batches), dim3(64 * WAVES_M * WAVES_N * KSPLIT), shmem, s, p);
+    queue_kernel(kern, dim3(p.tiles_m * p.tiles_n, batches), dim3(64 * WAVES_M * WAVES_N * KSPLIT), shmem, s, p);
     return NM_OK;
 }
 
@@ -803,7 +803,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     if (g.M == 0) return NM_OK;
     if (g.ln) {
         if (!gemm_folds_layernorm(g)) return fail(NM_ERR_UNSUPPORTED, "gemm: this shape does not fold the LayerNorm");
-        GemmParams q{};
+        GemmLnParams q{};
         q.M = g.M; q.N = g.N; q.K = g.K; q.A = g.A; q.lda = g.lda; q.W = g.W; q.ldw = g.ldw; q.inner_count = 1;
         q.bias = g.bias; q.alpha = g.alpha; q.resid = g.resid; q.resid_scale = g.resid_scale; q.ldo = g.ldo;
         q.ln_gamma = g.ln_gamma; q.ln_beta = g.ln_beta; q.ln_eps = g.ln_eps; q.ln_inv_scale = g.ln_inv_scale;
@@ -830,8 +830,6 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     p.cH = g.cH; p.cW = g.cW; p.cCin = g.cCin; p.cKw = g.cKw; p.cStride = g.cStride; p.cPad = g.cPad;
     p.cHo = g.cHo; p.cWo = g.cWo;
     p.out_q = g.out_q; p.out_f32 = g.out_f32; p.out_acc = g.out_acc; p.dbg_seg = g.dbg_seg;
-    p.ln_gamma = g.ln_gamma; p.ln_beta = g.ln_beta; p.ln_eps = g.ln_eps; p.ln_inv_scale = g.ln_inv_scale;
-    p.ln_table = g.ln_table; p.ln_out_q = g.ln_out_q; p.ln_out_f32 = g.ln_out_f32;
 
     // 16-byte loads need every row start and every batch offset on a 16-byte boundary
     const bool a_al = aligned(g.A, 16) && g.lda % 16 == 0 && g.a_outer % 16 == 0 && g.a_inner % 16 == 0;

@@ -39,6 +39,15 @@ struct GemmParams {
     uint16_t* dbg_seg;
     int tiles_m, tiles_n;
     int group_m;  // tile kernel: tile rows per group of the XCD-aware tile order
+    // convolution in matrix form (streaming kernel with kConv): row m of A is the output position
+    // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
+    int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
+    int relu;     // relu_codes holds for the table and the one output scale
+    int batched;  // more than one problem (grid.y)
+    FastDiv div_tiles_m, div_group, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, 8 * tiles_n, cWo, cHo, cCin and cKw
+};
+
+struct GemmLnParams : GemmParams {
     // LayerNorm-PWL folded into the epilogue (EPI_F32_RESID_LN): y = fma(d * r, gamma, beta) with
     // r = PWL_rsqrt(var + eps); outputs its int8 code and / or fp32 value, row stride N
     const float* ln_gamma;
@@ -47,12 +56,6 @@ struct GemmParams {
     DevTable ln_table;
     int8_t* ln_out_q;
     float* ln_out_f32;
-    // convolution in matrix form (streaming kernel with kConv): row m of A is the output position
-    // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
-    int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
-    int relu;     // relu_codes holds for the table and the one output scale
-    int batched;  // more than one problem (grid.y)
-    FastDiv div_tiles_m, div_group, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, 8 * tiles_n, cWo, cHo, cCin and cKw
 };
 
 // The small-tile kernel (nm_gemm_direct.hip).  align: alignment of operand rows and chunks in bytes (16, 4 or

@@ -463,7 +463,7 @@ static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, h
     const int grid = (p.tiles_m * p.tiles_n + 7) / 8 * 8;   // the kernel's eighths are (tiles + 7) / 8 each
     DirectArgs<kConv, kEpi> args;
     direct_args(args, p);
-    hipLaunchKernelGGL(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, args);
+    queue_kernel(kern, dim3(grid, batches), dim3(64 * KW), shmem, s, args);
     return NM_OK;
 }
 

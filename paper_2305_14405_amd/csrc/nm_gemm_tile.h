@@ -45,7 +45,7 @@ constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(GemmParams p)
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, GemmParams> p)
 {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -522,8 +522,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(Ge
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128>
-static int32_t launch_tile_epi(GemmParams& p, size_t table_bytes, hipStream_t s)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, typename Params>
+static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 {
     auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK>;
     constexpr int NW = WAVES_M * WAVES_N, NBLK = (BM + BN) * BK / 1024;
@@ -542,7 +542,7 @@ static int32_t launch_tile_epi(GemmParams& p, size_t table_bytes, hipStream_t s)
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     p.group_m = xcd_group_rows(p.tiles_m, p.tiles_n, BM, BN);
-    hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(64 * WAVES_M * WAVES_N), shmem, s, p);
+    queue_kernel(kern, dim3(p.tiles_m * p.tiles_n), dim3(64 * WAVES_M * WAVES_N), shmem, s, p);
     return NM_OK;
 }
 

@@ -311,7 +311,7 @@ static int32_t launch_unaligned_t(GemmParams& p, size_t table_bytes, hipStream_t
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     p.group_m = xcd_group_rows(p.tiles_m, p.tiles_n, BM, BN);
-    hipLaunchKernelGGL(kern, dim3((p.tiles_m * p.tiles_n + 7) / 8 * 8), dim3(64 * WAVES_M * WAVES_N), shmem, s, p);
+    queue_kernel(kern, dim3((p.tiles_m * p.tiles_n + 7) / 8 * 8), dim3(64 * WAVES_M * WAVES_N), shmem, s, p);
     return NM_OK;
 }
 

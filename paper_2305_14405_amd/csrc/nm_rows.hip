@@ -529,15 +529,15 @@ static bool launch_softmax_t(RowShape rs, dim3 grid_hint, size_t shmem, hipStrea
         constexpr int rpb = (64 / GG) * (kRowThreads / 64);                                         \
         constexpr int ku = kVec ? rows_per_trip(CC) : 1;                                            \
         if (kVec && cols == 4 * GG * CC && streams)                                                 \
-            hipLaunchKernelGGL((softmax_pwl_kernel<GG, CC, kI32, kVec, kVec, ku, kVec>),            \
+            queue_kernel(softmax_pwl_kernel<GG, CC, kI32, kVec, kVec, ku, kVec>,            \
                                dim3(blocks_for(rows, rpb * ku)), dim3(kRowThreads), shmem, stream,  \
                                in, alpha, rows, cols, te, tr, ois, oq, of, se, sr);                 \
         else if (kVec && cols == 4 * GG * CC)                                                       \
-            hipLaunchKernelGGL((softmax_pwl_kernel<GG, CC, kI32, kVec, kVec>),                      \
+            queue_kernel(softmax_pwl_kernel<GG, CC, kI32, kVec, kVec>,                      \
                                dim3(blocks_for(rows, rpb)), dim3(kRowThreads), shmem, stream, in,   \
                                alpha, rows, cols, te, tr, ois, oq, of, se, sr);                     \
         else                                                                                        \
-            hipLaunchKernelGGL((softmax_pwl_kernel<GG, CC, kI32, kVec, false>),                     \
+            queue_kernel(softmax_pwl_kernel<GG, CC, kI32, kVec, false>,                     \
                                dim3(blocks_for(rows, rpb)), dim3(kRowThreads), shmem, stream, in,   \
                                alpha, rows, cols, te, tr, ois, oq, of, se, sr);                     \
         return true;                                                                                \
@@ -581,11 +581,11 @@ static bool launch_layernorm_t(RowShape rs, hipStream_t stream, const float* in,
     if (rs.G == GG && rs.C == CC) {                                                                 \
         constexpr int rpb = (64 / GG) * (kRowThreads / 64);                                         \
         if (kVec && cols == 4 * GG * CC)                                                            \
-            hipLaunchKernelGGL((layernorm_pwl_kernel<GG, CC, kVec, kVec>), dim3(blocks_for(rows, rpb)), \
+            queue_kernel(layernorm_pwl_kernel<GG, CC, kVec, kVec>, dim3(blocks_for(rows, rpb)), \
                                dim3(kRowThreads), shmem, stream, in, gamma,                         \
                                beta, eps, inv_L, rows, cols, t, t2, two, ois, oq, of, seg, seg2);   \
         else                                                                                        \
-            hipLaunchKernelGGL((layernorm_pwl_kernel<GG, CC, kVec, false>), dim3(blocks_for(rows, rpb)), \
+            queue_kernel(layernorm_pwl_kernel<GG, CC, kVec, false>, dim3(blocks_for(rows, rpb)), \
                                dim3(kRowThreads), shmem, stream, in, gamma,                         \
                                beta, eps, inv_L, rows, cols, t, t2, two, ois, oq, of, seg, seg2);   \
         return true;                                                                                \
@@ -620,7 +620,7 @@ int32_t launch_layernorm2(const float* in, const float* gamma, const float* beta
         constexpr int rpb = kRowThreads / 64;
         const dim3 grid((unsigned)((rows + rpb - 1) / rpb));
         auto launch = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, dim3(kRowThreads), 0, stream, in, gamma, beta, t.kb, out_q, out_f32, (int)rows, t.nseg, t.lo, t.hi,
+            queue_kernel(kern, grid, dim3(kRowThreads), 0, stream, in, gamma, beta, t.kb, out_q, out_f32, (int)rows, t.nseg, t.lo, t.hi,
                                t.inv_w, t.clamp_input, eps, inv_L, out_inv_scale);
         };
         if (cols == 256) launch(layernorm_row_kernel<1>);
@@ -663,7 +663,7 @@ int32_t nm_pwl_apply(const void* in, int32_t in_dtype, float alpha, int64_t n,
     const int blocks = vec ? blocks_for((n + 3) / 4, kRowThreads * kApplyGroupsPerTrip, 1L << 20)
                            : blocks_for(n, kRowThreads);
     auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kRowThreads), shmem, (hipStream_t)stream, in,
+        queue_kernel(kern, dim3(blocks), dim3(kRowThreads), shmem, (hipStream_t)stream, in,
                            in_dtype == NM_DT_I32, alpha, (long)n, t, out_inv_scale, out_q, out_f32, dbg_seg,
                            (int)streaming_input((long)n * 4));
     };
