@@ -50,6 +50,7 @@ static int forced_cfg()
         static const char* const names[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
         if (!strncmp(e, "direct", 6)) return 10 + atoi(e + 6);
         if (!strncmp(e, "unaligned", 9)) return 20 + atoi(e + 9);
+        if (!strncmp(e, "relu", 4)) return 30 + atoi(e + 4);
         for (int i = 0; i < 7; ++i)
             if (!strcmp(e, names[i])) return i;
         return -1;
@@ -774,7 +775,8 @@ bool gemm_folds_layernorm(const GemmArgs& g)
 //   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
 //    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21 | 18 | 19
 //    2048 x  768 x 3072, fp32:   33 | 26 | 20 | 17 | 17 | 15 | 15 | 10 | 11
-static int choose_tile(int M, int N, int K, bool f32, bool table)
+// allowed: a bit per configuration.
+static int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allowed = ~0u)
 {
     static const struct { int bm, bn, stages, places, least; double alone, paired, alone_epi, start, slice, f32, q, table; } kTiles[] = {
         {256, 256, 2, 256, 0, 1, 1, 1, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, 0, 1, 1, 1, -2.43, 0.89, 10.88, 7.70, 9.41},
@@ -787,7 +789,7 @@ static int choose_tile(int M, int N, int K, bool f32, bool table)
     for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
         const auto& t = kTiles[c];
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
-        if (K / 128 < t.stages + 1 || (tiles < t.least && K / 128 > 3)) continue;
+        if (!(allowed >> c & 1) || K / 128 < t.stages + 1 || (tiles < t.least && K / 128 > 3)) continue;
         const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
         const double full = (double)(tiles / t.places);
         const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);
@@ -935,7 +937,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do
     // (8000 x 100 x 777 11.4, 8.5; 1220 x 751 x 40 7.2, 6.5; 1000 x 999 x 999 11.2, 9.9).
     const bool unaligned = direct_ok && !g.conv && batches == 1 && g.N >= 4 &&
-                           (forced_cfg() >= 20 || (forced_cfg() < 0 && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000));
+                           ((forced_cfg() >= 20 && forced_cfg() < 30) || (forced_cfg() < 0 && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000));
     if (unaligned) {
         rc = launch_unaligned(p, direct_align, table_bytes, forced_cfg() - 20 >= 0 ? forced_cfg() - 20 : -1, stream);
         if (rc) return rc;
@@ -943,6 +945,25 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     }
     if (direct) {
         rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced_cfg() - 10 >= 0 ? forced_cfg() - 10 : -1, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "gemm launch");
+    }
+    // The tile kernel's convolution epilogues
+    const bool relu_epi = (epi == EPI_Q_TABLE || epi == EPI_Q_TABLE_RESID) && g.table.two_seg && p.q16 && g.N % 16 == 0 && batches == 1 &&
+                          g.split_cols == 0 && (!g.resid || p.r16) && w_al && (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
+    const bool relu_tile = relu_epi && g.K % 128 == 0 && g.K / 128 >= 3 &&
+                           (g.conv ? !g.resid && g.cCin % 128 == 0 && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
+                                   : al && (int64_t)g.M * g.lda < (1LL << 32));
+    if (relu_tile && (forced_cfg() < 0 || forced_cfg() >= 30)) {
+        p.taps_w = g.cKw;
+        if (g.conv) p.div_wo = fast_div(g.cWo), p.div_ho = fast_div(g.cHo);
+        switch (forced_cfg() >= 30 ? forced_cfg() - 30 : choose_tile(g.M, g.N, g.K, false, false, 0x1e4)) {
+        case 2: rc = launch_tile_relu<256, 128, 4, 2, 3>(p, g.conv != 0, stream); break;
+        case 5: rc = launch_tile_relu<128, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
+        case 6: rc = launch_tile_relu<128, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
+        case 7: rc = launch_tile_relu<64, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
+        default: rc = launch_tile_relu<64, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
+        }
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
     }

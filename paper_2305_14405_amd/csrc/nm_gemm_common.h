@@ -44,6 +44,7 @@ struct GemmParams {
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
     int relu;     // relu_codes holds for the table and the one output scale
     int batched;  // more than one problem (grid.y)
+    int taps_w;            // tile kernel, kConv: filter columns (taps are numbered row by row, at most 32)
     FastDiv div_tiles_m, div_group, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, 8 * tiles_n, cWo, cHo, cCin and cKw
 };
 
@@ -150,11 +151,13 @@ __device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
-enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_TABLE2 = 7 };
+enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_TABLE2 = 7, EPI_Q_RELU = 8, EPI_Q_RELU_RESID = 9 };
 // EPI_Q_TABLE2: EPI_Q_TABLE for a merged table in its two-level form (one byte per primary cell naming the
 // merged segment, one {k, b} per merged segment; tile kernel only).
 // EPI_F32_RESID_LN: EPI_F32_RESID followed by LayerNorm-PWL over the row, inside the kernel: the tile
 // covers whole rows (tile kernel only).
+// EPI_Q_RELU, EPI_Q_RELU_RESID: per-column scales, a table of two segments, without and with an int8 residual (tile
+// kernel only: convolutions).
 // EPI_Q_TABLE_RESID: int8 residual, table (no input clamp), int8 output: the last convolution of a
 // residual block (sum with the shortcut, ReLU).
 

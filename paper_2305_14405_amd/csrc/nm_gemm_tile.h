@@ -40,11 +40,12 @@ namespace nm {
 // wavefronts' fp32 row patches, then the bias and the table.
 constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
 {
-    return epi == EPI_F32_RESID_LN ? bm * (bn + 16) + (bm * 64 + 2 * bm) * 4
+    return epi == EPI_Q_RELU_RESID ? bm * (bn + 16)
+         : epi == EPI_F32_RESID_LN ? bm * (bn + 16) + (bm * 64 + 2 * bm) * 4
          : epi == EPI_F32_RESID ? bm * (bn + 16) + nw * 32 * (wn + 4) * 4 : nw * wm * (wn + 16);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, GemmParams> p)
 {
     constexpr int NW = WAVES_M * WAVES_N;
@@ -71,14 +72,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole blocks");
     static_assert(TN >= 2 && KS % 2 == 0, "wavefront tile");
     constexpr bool kTable = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE2;
-    static_assert(kEpi == EPI_Q || kTable || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
+    constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
+    static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
                   "epilogues of the tile kernel");
+    static_assert(!kConv || (kEven && BK == 128), "gathered rows: a wavefront's A blocks are the same for every slice");
     static_assert(kEpi != EPI_F32_RESID_LN || WAVES_M == 1, "row statistics: a wavefront holds all rows of its columns");
-    constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN;
+    constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN || kEpi == EPI_Q_RELU_RESID;
 
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     float* s_bias = reinterpret_cast<float*>(smem + tile_front_bytes(BM, BN, NW, WM, WN, kEpi));
     float2* s_kb = reinterpret_cast<float2*>(s_bias + BN);
+    float* s_scale = s_bias + BN;   // kRelu (which has no table in LDS)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -101,21 +105,59 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
 
     // per-lane byte offsets of this wavefront's blocks (rows past the edge are clamped: they only
     // feed accumulators that are never stored); M * K and N * K fit 32 bits (host)
+    // kConv: row r of A is an output position; ctap[b] has a bit for every filter tap whose input position lies inside the
+    // image, voff[b] is the (possibly negative) offset of the tap (0, 0).
     unsigned voff[LB];
+    unsigned ctap[kConv ? LBA : 1];
+    if constexpr (kConv)
+        asm volatile("" : : "s"(p.cH), "s"(p.cW), "s"(p.cCin), "s"(p.taps_w), "s"(p.cStride), "s"(p.cPad), "s"(p.cWo), "s"(p.cHo),
+                     "s"(p.div_wo.magic), "s"(p.div_wo.shift), "s"(p.div_ho.magic), "s"(p.div_ho.shift));
 #pragma unroll
     for (int b = 0; b < LB; ++b) {
         const int blk = wave + b * NW;
         const int r = blk * RPI + lane / CPR;
         const int chunk = (lane % CPR) ^ swz_bk<BK>(r);
         const bool is_a = kEven ? b < LBA : blk < ABLK;  // wave-uniform
-        if (is_a) voff[b] = (unsigned)min(m0 + r, p.M - 1) * (unsigned)p.lda + 16u * chunk;
+        if (kConv && b < LBA) {
+            if constexpr (kConv) {
+                const int m = min(m0 + r, p.M - 1), q = (int)quotient((unsigned)m, p.div_wo), bi = (int)quotient((unsigned)q, p.div_ho);
+                const int h0 = (q - bi * p.cHo) * p.cStride - p.cPad, w0 = (m - q * p.cWo) * p.cStride - p.cPad;
+                voff[b] = (unsigned)(((bi * p.cH + h0) * p.cW + w0) * p.cCin + 16 * chunk);
+                // taps of a row that lie inside, then the rows
+                unsigned cols = 0;
+                for (int j = 0; j < p.taps_w; ++j) cols |= (unsigned)(w0 + j) < (unsigned)p.cW ? 1u << j : 0u;
+                const int rows = p.K / (p.cCin * p.taps_w);
+                unsigned in = 0;
+                for (int i = 0; i < rows; ++i) in |= (unsigned)(h0 + i) < (unsigned)p.cH ? cols << (i * p.taps_w) : 0u;
+                ctap[b] = in;
+            }
+        } else if (is_a) voff[b] = (unsigned)min(m0 + r, p.M - 1) * (unsigned)p.lda + 16u * chunk;
         else voff[b] = (unsigned)min(n0 + r - BM, p.N - 1) * (unsigned)p.ldw + 16u * chunk;
     }
     const unsigned lds_base = (unsigned)(uintptr_t)smem;
     const int8_t* __restrict__ gA = p.A;
     const int8_t* __restrict__ gW = p.W;
+    // kConv: tap and offset of the slice whose A blocks are requested next (slices are requested in order)
+    unsigned tap_bit = 1;
+    int tap_off = 0, tap_col = 0, tap_c = 0;
+    const int8_t* const zero_src = g_zero_line + 16 * (lane % CPR);
     auto issue1 = [&](int kt, int slot, int b) {
         const unsigned dst = lds_base + slot * STAGE_BYTES + (wave + b * NW) * 1024;
+        if constexpr (kConv) {
+            if (b < LBA) {
+                dma16((ctap[b] & tap_bit) ? gA + (int)(voff[b] + (unsigned)tap_off) : zero_src, dst);
+                if (b == LBA - 1) {
+                    tap_off += BK;
+                    tap_c += BK;
+                    if (tap_c == p.cCin) {   // the next tap's offset is that of this one's end, but for the image's row
+                        tap_c = 0;
+                        tap_bit <<= 1;
+                        if (++tap_col == p.taps_w) { tap_col = 0; tap_off += (p.cW - p.taps_w) * p.cCin; }
+                    }
+                }
+                return;
+            }
+        }
         const bool is_a = kEven ? b < LBA : wave + b * NW < ABLK;
         dma16s((is_a ? gA : gW) + (long)kt * BK, voff[b], dst);
     };
@@ -127,11 +169,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
 
     // epilogue parameters: fetched now, parked in registers until the k-loop is over
     constexpr int BPT = (BN + 64 * NW - 1) / (64 * NW);
-    float bias_reg[BPT];
+    float bias_reg[BPT], scale_reg[kRelu ? BPT : 1];
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
         const int c = tid + t * 64 * NW;
         bias_reg[t] = (p.bias && c < BN && n0 + c < p.N) ? p.bias[n0 + c] : 0.0f;
+        if (kRelu) scale_reg[t] = (p.alpha_vec && c < BN && n0 + c < p.N) ? p.alpha_vec[n0 + c] : p.alpha;
     }
     constexpr int KPT = 4;  // table entries per thread held in registers (more are staged late)
     float2 kb_reg[KPT];
@@ -263,6 +306,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     for (int t = 0; t < BPT; ++t) {
         const int c = tid + t * 64 * NW;
         if (c < BN) s_bias[c] = bias_reg[t];
+        if (kRelu && c < BN) s_scale[c] = scale_reg[t];
     }
     if (kEpi == EPI_Q_TABLE) {
 #pragma unroll
@@ -373,6 +417,61 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
             const int c = lane + 64 * t, row = c / PCPR, cc = c % PCPR;
             const int mr = m0 + wave_m + row, n = n0 + wave_n + 16 * cc;
             if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = rows[t];
+        }
+    } else if constexpr (kRelu) {
+        // Codes go to an image of the tile's rows (over the residual's, word by word, where there is one) and leave as
+        // 16-byte stores.  Where the table is a ReLU and the columns' numbers cannot make a sum infinite, clamping the
+        // code at 0 is all of it; any other table of two segments is a compare.
+        constexpr int SW = kResid ? RW : WN + 16;
+        int8_t* patch = kResid ? s_res + wave_m * RW + wave_n : smem + wave * (WM * SW);
+        const float rs = p.resid_scale, inv = p.out_inv_scale;
+        bool relu = p.relu;
+        if (relu) {
+            for (int c = lane; c < WN; c += 64) relu = relu && relu_finite(s_scale[wave_n + c], s_bias[wave_n + c]);
+            relu = __all(relu);
+        }
+        auto finish = [&](auto clamp_c) {
+            constexpr bool kClamp = decltype(clamp_c)::value;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int cl = 32 * j + 8 * g + 4 * frag_half;
+                    const v4f sc = *reinterpret_cast<const v4f*>(s_scale + wave_n + cl);
+                    unsigned rw[TM];
+                    if (kResid) {
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) rw[i] = *reinterpret_cast<const unsigned*>(patch + (32 * i + frag_row) * SW + cl);
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        unsigned w = 0;
+                        int q[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float v = __builtin_fmaf((float)acc[i][j][4 * g + e], sc[e], bi[j][g][e]);
+                            if (kResid) v = __builtin_fmaf((float)(int)(int8_t)(rw[i] >> (8 * e)), rs, v);
+                            if (kClamp) w = relu_requant(v, inv, e, w);
+                            else q[e] = requant(pwl_eval_two_segments(v, p.table), inv);
+                        }
+                        if (!kClamp) w = pack4(q[0], q[1], q[2], q[3]);
+                        *reinterpret_cast<unsigned*>(patch + (32 * i + frag_row) * SW + cl) = w;
+                    }
+                }
+        };
+        if (relu) finish(std::true_type{}); else finish(std::false_type{});
+        // the wavefront reads back the rows it wrote
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        constexpr int PCPR = WN / 16, NCH = WM * PCPR / 64;
+        static_assert(WM * PCPR % 64 == 0, "chunks split evenly");
+#pragma unroll
+        for (int t = 0; t < NCH; ++t) {
+            const int c = lane + 64 * t, row = c / PCPR, cc = c % PCPR;
+            const v4i o = *reinterpret_cast<const v4i*>(patch + row * SW + 16 * cc);
+            const int mr = m0 + wave_m + row, n = n0 + wave_n + 16 * cc;
+            if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = o;
         }
     } else if constexpr (kEpi == EPI_F32_RESID) {
         // Rows leave through an LDS patch of 32 rows per wavefront, 16 or 24 lanes per row.  Stored straight
@@ -522,10 +621,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, typename Params>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, typename Params>
 static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 {
-    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK>;
+    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK, kConv>;
     constexpr int NW = WAVES_M * WAVES_N, NBLK = (BM + BN) * BK / 1024;
     constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
     constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M, BN / WAVES_N, kEpi);
@@ -555,6 +654,16 @@ static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream
     case EPI_Q_TABLE2: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2>(p, table_bytes, s);
     default: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID>(p, table_bytes, s);
     }
+}
+
+// Convolutions: the 1x1 ones with K a multiple of 128 as products, the others with gathered rows (Cin a multiple of 128).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
+static int32_t launch_tile_relu(GemmParams& p, bool conv, hipStream_t s)
+{
+    constexpr size_t cols = BN * sizeof(float);   // the scales, where other epilogues have their table
+    if (conv) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, 128, true>(p, cols, s);
+    if (p.resid) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU_RESID>(p, cols, s);
+    return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU>(p, cols, s);
 }
 
 }  // namespace nm
