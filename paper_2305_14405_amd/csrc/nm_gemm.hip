@@ -39,7 +39,7 @@ static bool force_generic()
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3> forces
+// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3>|relu<2,5-10> forces
 // that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
 // 256x192 configuration, which the tile kernel has replaced).
 static int forced_cfg()
@@ -948,21 +948,33 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
     }
-    // The tile kernel's convolution epilogues
-    const bool relu_epi = (epi == EPI_Q_TABLE || epi == EPI_Q_TABLE_RESID) && g.table.two_seg && p.q16 && g.N % 16 == 0 && batches == 1 &&
-                          g.split_cols == 0 && (!g.resid || p.r16) && w_al && (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
-    const bool relu_tile = relu_epi && g.K % 128 == 0 && g.K / 128 >= 3 &&
-                           (g.conv ? !g.resid && g.cCin % 128 == 0 && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
+    // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
+    // residual; the rows gathered or not).  128-byte slices and the cost model's tile where K (a gathered row's Cin) is a
+    // multiple of 128 and long enough for a ring; 64-byte ones of 128x128 tiles, three in flight, otherwise; of 128x64 for at
+    // most 64 columns.  us, streaming kernel -> these: 200704 x 64 x 576 (3x3) 21.7 -> 17.0, 200704 x 64 x 256 17.9 ->
+    // 13.3, 50176 x 512 x 128 with residual 18.4 -> 15.4, 12544 x 1024 x 256 with residual 12.8 -> 11.8, 200704 x 256 x 64
+    // 22.6 -> 19.6, with residual 26.3 -> 25.6; with 128-byte slices in launch_tile_relu.
+    const bool relu_epi = (epi == EPI_Q ? g.conv || g.alpha_vec : (epi == EPI_Q_TABLE || epi == EPI_Q_TABLE_RESID) && g.table.two_seg) &&
+                          p.q16 && g.N % 16 == 0 && batches == 1 && g.split_cols == 0 && (!g.resid || p.r16) && w_al &&
+                          (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
+    const int kunit = g.conv ? g.cCin : g.K;
+    const bool relu_tile = relu_epi && kunit % 64 == 0 && (forced_cfg() < 0 || forced_cfg() >= 30) &&
+                           (g.conv ? !g.resid && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
                                    : al && (int64_t)g.M * g.lda < (1LL << 32));
-    if (relu_tile && (forced_cfg() < 0 || forced_cfg() >= 30)) {
+    if (relu_tile) {
         p.taps_w = g.cKw;
         if (g.conv) p.div_wo = fast_div(g.cWo), p.div_ho = fast_div(g.cHo);
-        switch (forced_cfg() >= 30 ? forced_cfg() - 30 : choose_tile(g.M, g.N, g.K, false, false, 0x1e4)) {
+        int c = forced_cfg() >= 30 ? forced_cfg() - 30 : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
+                                                       : choose_tile(g.M, g.N, g.K, false, false, 0x1e4);
+        if (c <= 8 && kunit % 128 != 0) c = 9;
+        switch (c) {
         case 2: rc = launch_tile_relu<256, 128, 4, 2, 3>(p, g.conv != 0, stream); break;
         case 5: rc = launch_tile_relu<128, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
         case 6: rc = launch_tile_relu<128, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
         case 7: rc = launch_tile_relu<64, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
-        default: rc = launch_tile_relu<64, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
+        case 8: rc = launch_tile_relu<64, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
+        case 9: rc = launch_tile_relu<128, 128, 2, 2, 3, 64>(p, g.conv != 0, stream); break;
+        default: rc = launch_tile_relu<128, 64, 4, 1, 3, 64>(p, g.conv != 0, stream); break;
         }
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
     static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
                   "epilogues of the tile kernel");
-    static_assert(!kConv || (kEven && BK == 128), "gathered rows: a wavefront's A blocks are the same for every slice");
+    static_assert(!kConv || kEven, "gathered rows: a wavefront's A blocks are the same for every slice");
     static_assert(kEpi != EPI_F32_RESID_LN || WAVES_M == 1, "row statistics: a wavefront holds all rows of its columns");
     constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN || kEpi == EPI_Q_RELU_RESID;
 
@@ -161,11 +161,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         const bool is_a = kEven ? b < LBA : wave + b * NW < ABLK;
         dma16s((is_a ? gA : gW) + (long)kt * BK, voff[b], dst);
     };
-    const int nk = p.K / BK;  // >= STAGES + 1 (host)
+    const int nk = p.K / BK;  // >= STAGES + 1 (host; any with kShort)
+    constexpr bool kShort = kRelu;
 #pragma unroll
-    for (int st = 0; st < STAGES; ++st)
+    for (int st = 0; st < STAGES; ++st) {
+        if (kShort && st >= nk) break;
 #pragma unroll
         for (int b = 0; b < LB; ++b) issue1(st, st, b);
+    }
 
     // epilogue parameters: fetched now, parked in registers until the k-loop is over
     constexpr int BPT = (BN + 64 * NW - 1) / (64 * NW);
@@ -234,7 +237,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     };
 
     // k-slice 0 has landed (the younger slices of the prologue stay in flight)
-    wait_vmcnt<(STAGES - 1) * LB>();
+    if (kShort && nk == 1) wait_vmcnt<0>();
+    else if (kShort && STAGES > 2 && nk == 2) wait_vmcnt<LB>();
+    else wait_vmcnt<(STAGES - 1) * LB>();
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < NR; ++t) ldfrag1(0, 0, 0, t);
@@ -291,15 +296,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     };
     using T_ = std::true_type;
     using F_ = std::false_type;
-    slice(T_{}, F_{}, std::integral_constant<int, STAGES - 2>{}, 0);
-    for (int kt = 1; kt < nk - STAGES; ++kt) slice(T_{}, T_{}, std::integral_constant<int, STAGES - 2>{}, kt);
-    slice(F_{}, T_{}, std::integral_constant<int, STAGES - 2>{}, nk - STAGES);
     auto tail = [&](auto self, auto r_c) -> void {
         constexpr int R = decltype(r_c)::value;  // slices after this one
         slice(F_{}, F_{}, std::integral_constant<int, R - 1>{}, nk - 1 - R);
         if constexpr (R > 0) self(self, std::integral_constant<int, R - 1>{});
     };
-    tail(tail, std::integral_constant<int, STAGES - 2>{});
+    if (kShort && nk == 1) {
+        tail(tail, std::integral_constant<int, 0>{});
+    } else if (kShort && nk == 2) {
+        tail(tail, std::integral_constant<int, 1>{});
+    } else if (kShort && STAGES > 2 && nk == 3) {
+        tail(tail, std::integral_constant<int, (STAGES > 2 ? 2 : 1)>{});
+    } else {
+        slice(T_{}, F_{}, std::integral_constant<int, STAGES - 2>{}, 0);
+        for (int kt = 1; kt < nk - STAGES; ++kt) slice(T_{}, T_{}, std::integral_constant<int, STAGES - 2>{}, kt);
+        slice(F_{}, T_{}, std::integral_constant<int, STAGES - 2>{}, nk - STAGES);
+        tail(tail, std::integral_constant<int, STAGES - 2>{});
+    }
     __syncthreads();  // every wavefront is done with the ring
 
 #pragma unroll
@@ -425,13 +438,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         constexpr int SW = kResid ? RW : WN + 16;
         int8_t* patch = kResid ? s_res + wave_m * RW + wave_n : smem + wave * (WM * SW);
         const float rs = p.resid_scale, inv = p.out_inv_scale;
+        const bool plain = !p.has_table;
         bool relu = p.relu;
         if (relu) {
             for (int c = lane; c < WN; c += 64) relu = relu && relu_finite(s_scale[wave_n + c], s_bias[wave_n + c]);
             relu = __all(relu);
         }
-        auto finish = [&](auto clamp_c) {
-            constexpr bool kClamp = decltype(clamp_c)::value;
+        auto finish = [&](auto clamp_c, auto table_c) {
+            constexpr bool kClamp = decltype(clamp_c)::value, kLines = decltype(table_c)::value;
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -452,14 +466,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
                             float v = __builtin_fmaf((float)acc[i][j][4 * g + e], sc[e], bi[j][g][e]);
                             if (kResid) v = __builtin_fmaf((float)(int)(int8_t)(rw[i] >> (8 * e)), rs, v);
                             if (kClamp) w = relu_requant(v, inv, e, w);
-                            else q[e] = requant(pwl_eval_two_segments(v, p.table), inv);
+                            else q[e] = requant(kLines ? pwl_eval_two_segments(v, p.table) : v, inv);
                         }
                         if (!kClamp) w = pack4(q[0], q[1], q[2], q[3]);
                         *reinterpret_cast<unsigned*>(patch + (32 * i + frag_row) * SW + cl) = w;
                     }
                 }
         };
-        if (relu) finish(std::true_type{}); else finish(std::false_type{});
+        if (relu) finish(std::true_type{}, std::false_type{});
+        else if (plain) finish(std::false_type{}, std::false_type{});
+        else finish(std::false_type{}, std::true_type{});
         // the wavefront reads back the rows it wrote
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -656,14 +672,16 @@ static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream
     }
 }
 
-// Convolutions: the 1x1 ones with K a multiple of 128 as products, the others with gathered rows (Cin a multiple of 128).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
+// Convolutions, as products or with gathered rows.  us, streaming kernel -> this one with 128-byte slices: 12544 x 256 x 2304
+// (3x3) 16.4 -> 12.0, 3136 x 512 x 4608 (3x3) 22.3 -> 14.2, 50176 x 128 x 1152 (3x3) 15.8 -> 11.9, 3136 x 2048 x 512 with
+// residual 14.1 -> 8.4, 12544 x 256 x 1024 9.3 -> 6.9, 3136 x 2048 x 1024 (stride 2) 15.9 -> 11.1.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK = 128>
 static int32_t launch_tile_relu(GemmParams& p, bool conv, hipStream_t s)
 {
     constexpr size_t cols = BN * sizeof(float);   // the scales, where other epilogues have their table
-    if (conv) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, 128, true>(p, cols, s);
-    if (p.resid) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU_RESID>(p, cols, s);
-    return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU>(p, cols, s);
+    if (conv) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK, true>(p, cols, s);
+    if (p.resid) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU_RESID, BK>(p, cols, s);
+    return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK>(p, cols, s);
 }
 
 }  // namespace nm

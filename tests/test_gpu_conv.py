@@ -110,6 +110,45 @@ def test_conv2d_all_outputs(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad):
         assert np.array_equal(host(oq2), r2["q"]), f"int8-only, table={table is not None}"
 
 
+@pytest.mark.parametrize("B,H,W,Cin,Cout,k,stride,pad", [
+    (27, 40, 40, 64, 48, 3, 1, 1), (13, 31, 29, 192, 96, 3, 1, 1), (7, 39, 35, 128, 112, 3, 1, 1), (1, 90, 93, 128, 128, 3, 1, 2),
+    (3, 61, 63, 256, 400, 1, 2, 0), (2, 35, 37, 512, 432, 1, 1, 0), (1, 60, 61, 1024, 304, 1, 1, 0), (2, 40, 41, 128, 528, 1, 1, 0),
+    (5, 43, 41, 64, 208, 1, 1, 0), (3, 50, 51, 192, 240, 1, 1, 0), (31, 30, 30, 64, 64, 1, 1, 0), (9, 45, 41, 128, 112, 2, 1, 0)])
+def test_conv2d_large_tile_kernel(oracle, B, H, W, Cin, Cout, k, stride, pad):
+    """Convolutions whose outputs are large enough for the tile kernel: gathered rows (64- and 128-byte slices, several taps
+    per slice count, strides, padding wider than needed) and plain ones of one, two, three and more slices; partly filled
+    row and column tiles; a ReLU, a table of two other lines, none, and a residual.  The results sit between guards."""
+    g = np.random.default_rng(B + H + Cin + Cout)
+    x, w = rand_i8(g, (B, H, W, Cin), 60), rand_i8(g, (Cout, k, k, Cin), 60)
+    Ho, Wo = oracle.conv_out_hw(H, W, k, k, stride, pad)
+    assert B * Ho * Wo * Cout >= 1000000
+    alpha_vec = ((3.0 / (35 * 35 * np.sqrt(k * k * Cin))) * (1 + g.random(Cout))).astype(np.float32)
+    bias = (0.3 * g.standard_normal(Cout)).astype(np.float32)
+    ot, dt = relu_tables(oracle)
+    ot2 = oracle.build_table(oracle.F_GELU, -1.0, 3.0, 2)
+    dt2 = nm.nm_tables_from_arrays([("gelu", -1.0, 3.0, 2, 0)], [ot2.k], [ot2.b])
+    dx, dw, db, dav = dev(x), dev(w), dev(bias), dev(alpha_vec)
+    n = B * Ho * Wo * Cout
+    resid = rand_i8(g, (B, Ho, Wo, Cout)) if k == 1 and stride == 1 else None
+    dres = dev(resid)
+    for tab, dtab, res in ((ot, dt, False), (ot2, dt2, False), (None, None, False), (ot, dt, True)):
+        if res and resid is None:
+            continue
+        rk = dict(resid=resid, resid_scale=0.01) if res else {}
+        want = oracle.conv2d_pwl(x, w, stride=stride, pad=pad, bias=bias, alpha_vec=alpha_vec, table=tab, out_inv_scale=30.0,
+                                 want_acc=False, **rk)["q"]
+        buf = torch.full((n + 256,), 77, dtype=torch.int8, device=DEV)
+        oq = buf[128:128 + n].view(B, Ho, Wo, Cout)
+        dk = dict(resid=dres, resid_scale=0.01) if res else {}
+        d = nm.make_conv_desc(dx, dw, stride=stride, pad=pad, bias=db, alpha_vec=dav, tables=dtab, table_idx=-1 if tab is None else 0,
+                              out_inv_scale=30.0, out_q=oq, **dk)
+        ws = torch.empty(max(256, nm.nm_conv2d_workspace(d)), dtype=torch.uint8, device=DEV)
+        nm.nm_conv2d_pwl(d, ws)
+        assert np.array_equal(host(oq), want), (tab is not None, res)
+        edge = host(buf)
+        assert np.all(edge[:128] == 77) and np.all(edge[128 + n:] == 77)
+
+
 @pytest.mark.parametrize("B,H,W,Cc,k,stride,pad", [(2, 112, 112, 64, 3, 2, 1), (3, 9, 10, 5, 3, 2, 1), (1, 8, 8, 12, 2, 2, 0)])
 def test_maxpool(oracle, B, H, W, Cc, k, stride, pad):
     x = rand_i8(np.random.default_rng(H), (B, H, W, Cc))
