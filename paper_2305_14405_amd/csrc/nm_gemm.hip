@@ -39,7 +39,7 @@ static bool force_generic()
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3>|relu<2,5-10> forces
+// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3>|relu<2,5-11>|tile<0-9> forces
 // that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
 // 256x192 configuration, which the tile kernel has replaced).
 static int forced_cfg()
@@ -51,6 +51,7 @@ static int forced_cfg()
         if (!strncmp(e, "direct", 6)) return 10 + atoi(e + 6);
         if (!strncmp(e, "unaligned", 9)) return 20 + atoi(e + 9);
         if (!strncmp(e, "relu", 4)) return 30 + atoi(e + 4);
+        if (!strncmp(e, "tile", 4)) return 50 + atoi(e + 4);
         for (int i = 0; i < 7; ++i)
             if (!strcmp(e, names[i])) return i;
         return -1;
@@ -764,9 +765,12 @@ bool gemm_folds_layernorm(const GemmArgs& g)
 // full rounds have a CU each and are charged the fraction `alone` of a round (`alone_epi` of an epilogue),
 // up to 512 where three share a CU `paired`.  A ring of two stages only pays where workgroups do share (from
 // `least` tiles on; it is also the one for K = 384): alone on a CU it waits for its operands, 23 instead of 17 us at
-// 4096 x 768 x 3072 with 128x128.  The constants are least-squares fits to 180 measured shapes: M from 64 to
+// 4096 x 768 x 3072 with 128x128.  The last entry is 128x128 with two wavefronts to a sub-tile, each taking half of a slice's
+// k-steps: two on every SIMD where one workgroup has a CU, for the fp32 epilogue (4096 x 768 x 3072 18.4 -> 16.4 us, 2560 x
+// 1024 x 4096 20.9 -> 18.3, 4096 x 768 x 768 10.6 -> 9.4); the shorter int8 ones do not repay the exchange (1500 x 2304 x 768
+// 6.6, 7.0).  The constants are least-squares fits to 180 measured shapes: M from 64 to
 // 16384, the four products of a layer of width 512, 768 and 1024.  Over those the chosen tile is 1.2 % slower than
-// the best of the nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
+// the best of the first nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
 // were 7 % (54 %) slower from M = 2048 on.  On 106 shapes outside the fit (widths 384, 640, 896, 1152, 1280 and 1536, FFNs
 // of 4 H and 2 H + 128, M drawn up to 16384) it is 1.6 % slower than the best, at a tenth of them 6 % or more, at the
 // two worst 38 % (1683 x 4608 x 1536) and 11 %.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
@@ -783,12 +787,13 @@ static int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allow
         {256, 128, 3, 256, 0, 1, 1, 1, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0, 1, 1, 1, 0.08, 0.54, 7.35, 4.55, 5.87},
         {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 5.92, 2.75, 3.90},
         {128, 128, 2, 512, 257, 0.65, 1, 0.65, 0.48, 0.87, 8.91, 2.98, 4.47}, {64, 128, 3, 512, 0, 0.45, 1, 0.8, 1.19, 0.52, 3.52, 2.23, 3.00},
-        {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}};
+        {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.385, 6.7, 0, 0}};
     int best = -1;
     double best_us = 0.0;
     for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
         const auto& t = kTiles[c];
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
+        if (c == 5 ? f32 : c == 9 && !f32) continue;
         if (!(allowed >> c & 1) || K / 128 < t.stages + 1 || (tiles < t.least && K / 128 > 3)) continue;
         const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
         const double full = (double)(tiles / t.places);
@@ -958,21 +963,23 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                           p.q16 && g.N % 16 == 0 && batches == 1 && g.split_cols == 0 && (!g.resid || p.r16) && w_al &&
                           (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
     const int kunit = g.conv ? g.cCin : g.K;
-    const bool relu_tile = relu_epi && kunit % 64 == 0 && (forced_cfg() < 0 || forced_cfg() >= 30) &&
+    const bool relu_tile = relu_epi && kunit % 64 == 0 && (forced_cfg() < 0 || (forced_cfg() >= 30 && forced_cfg() < 50)) &&
                            (g.conv ? !g.resid && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
                                    : al && (int64_t)g.M * g.lda < (1LL << 32));
     if (relu_tile) {
         p.taps_w = g.cKw;
         if (g.conv) p.div_wo = fast_div(g.cWo), p.div_ho = fast_div(g.cHo);
-        int c = forced_cfg() >= 30 ? forced_cfg() - 30 : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
+        int c = forced_cfg() >= 30 && forced_cfg() < 50 ? forced_cfg() - 30 : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
                                                        : choose_tile(g.M, g.N, g.K, false, false, 0x1e4);
         if (c <= 8 && kunit % 128 != 0) c = 9;
+        if (c == 5 && g.K >= 1536) c = 11;   // 12544 x 256 x 2304 (3x3) 12.8 -> 12.0; 12544 x 256 x 1024 7.0 with 5, 7.6
         switch (c) {
         case 2: rc = launch_tile_relu<256, 128, 4, 2, 3>(p, g.conv != 0, stream); break;
         case 5: rc = launch_tile_relu<128, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
         case 6: rc = launch_tile_relu<128, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
         case 7: rc = launch_tile_relu<64, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
         case 8: rc = launch_tile_relu<64, 128, 2, 2, 2>(p, g.conv != 0, stream); break;
+        case 11: rc = launch_tile_relu<128, 128, 2, 2, 3, 128, 2>(p, g.conv != 0, stream); break;
         case 9: rc = launch_tile_relu<128, 128, 2, 2, 3, 64>(p, g.conv != 0, stream); break;
         default: rc = launch_tile_relu<128, 64, 4, 1, 3, 64>(p, g.conv != 0, stream); break;
         }
@@ -994,6 +1001,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     if (tile_ok && !old_big) {
         if (forced_cfg() < 0) tile_cfg = choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
         else if (forced_cfg() == 0) tile_cfg = 1;
+        else if (forced_cfg() >= 50) tile_cfg = forced_cfg() - 50;
     }
     if (tile_cfg >= 0 && two_level_q) epi = EPI_Q_TABLE2;
     if (tile_cfg == 0) {
@@ -1014,6 +1022,8 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         rc = launch_tile<64, 128, 2, 2, 3>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 8) {
         rc = launch_tile<64, 128, 2, 2, 2>(p, epi, table_bytes, stream);
+    } else if (tile_cfg == 9) {
+        rc = launch_tile<128, 128, 2, 2, 3, 2>(p, epi, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

@@ -45,12 +45,14 @@ constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
          : epi == EPI_F32_RESID ? bm * (bn + 16) + nw * 32 * (wn + 4) * 4 : nw * wm * (wn + 16);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, GemmParams> p)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_kernel(std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, GemmParams> p)
 {
-    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int NWT = WAVES_M * WAVES_N;   // wavefront tiles
+    constexpr int NW = NWT * KSPLIT;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int EM = WM / KSPLIT, ETM = TM / KSPLIT;   // rows, 32-row blocks a wavefront finishes
     constexpr int ROWS = BM + BN;
     constexpr int CPR = BK / 16;
     constexpr int RPI = 64 / CPR;
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     constexpr bool kEven = NBLK % NW == 0 && ABLK % NW == 0;
     constexpr int LBA = ABLK / NW;           // A blocks per wavefront (even split)
     constexpr int STAGE_BYTES = LB * NW * 1024;
-    constexpr int KS = BK / 32;
+    constexpr int KS = BK / 32 / KSPLIT;     // k-steps of a slice that are the wavefront's
     constexpr int NR = TM + TN;              // fragments per k-step
     constexpr int NMF = TM * TN;             // matrix instructions per k-step
     constexpr int HALF = NMF - NR >= 1 ? NMF - NR : 1;  // ... of the last k-step in front of the slice barrier
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     constexpr int RPS2 = (NR + NMF - 1) / NMF;          // ... and in the other k-steps
     constexpr int DPS = (LB + POST + NMF - 1) / (POST + NMF);  // refill loads per slot (those slots and the next k-step's)
     static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole blocks");
-    static_assert(TN >= 2 && KS % 2 == 0, "wavefront tile");
+    static_assert(TN >= 2 && KS % 2 == 0 && TM % KSPLIT == 0, "wavefront tile");
     constexpr bool kTable = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE2;
     constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
     static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
@@ -80,15 +82,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     constexpr bool kResid = kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN || kEpi == EPI_Q_RELU_RESID;
 
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    float* s_bias = reinterpret_cast<float*>(smem + tile_front_bytes(BM, BN, NW, WM, WN, kEpi));
+    float* s_bias = reinterpret_cast<float*>(smem + tile_front_bytes(BM, BN, NW, EM, WN, kEpi));
     float2* s_kb = reinterpret_cast<float2*>(s_bias + BN);
     float* s_scale = s_bias + BN;   // kRelu (which has no table in LDS)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_m = (wave / WAVES_N) * WM;
-    const int wave_n = (wave % WAVES_N) * WN;
+    const int kg = KSPLIT == 1 ? 0 : wave / NWT, wave_t = KSPLIT == 1 ? wave : wave % NWT;   // half of the k-steps, sub-tile
+    const int wave_m = (wave_t / WAVES_N) * WM;
+    const int wave_n = (wave_t % WAVES_N) * WN;
 
     // XCD-aware tile order, as in the streaming kernel
     int id = blockIdx.x;
@@ -223,8 +226,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const int ra = wave_m + frag_row, rw = wave_n + frag_row;
-        offA[ks] = lds_off_bk<BK>(ra, 2 * ks + frag_half);
-        offW[ks] = BM * BK + lds_off_bk<BK>(rw, 2 * ks + frag_half);
+        offA[ks] = lds_off_bk<BK>(ra, 2 * (kg * KS + ks) + frag_half);
+        offW[ks] = BM * BK + lds_off_bk<BK>(rw, 2 * (kg * KS + ks) + frag_half);
     }
     v4i fa[2][TM], fw[2][TN];
     // fragment t of a k-step, in the order the matrix instructions of that k-step need them
@@ -315,6 +318,43 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     }
     __syncthreads();  // every wavefront is done with the ring
 
+    // KSPLIT == 2: the two wavefronts of a sub-tile swap halves of their sums through LDS (exact in any order) and each
+    // finishes half of its rows
+    v16i half_sum[KSPLIT == 2 ? ETM : 1][TN];
+    if constexpr (KSPLIT == 2) {
+        static_assert(NW * ETM * TN * 4096 <= STAGES * STAGE_BYTES, "exchange fits the ring");
+        v4i* const mine = reinterpret_cast<v4i*>(smem) + (wave_t * 2 + kg) * (ETM * TN * 256) + lane;
+        const v4i* const other = reinterpret_cast<const v4i*>(smem) + (wave_t * 2 + 1 - kg) * (ETM * TN * 256) + lane;
+#pragma unroll
+        for (int i = 0; i < ETM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {   // give away the row blocks the partner finishes
+                    v4i o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = kg == 0 ? acc[ETM + i][j][4 * v + e] : acc[i][j][4 * v + e];
+                    mine[((i * TN + j) * 4 + v) * 64] = o;
+                }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ETM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const v4i o = other[((i * TN + j) * 4 + v) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) half_sum[i][j][4 * v + e] = (kg == 0 ? acc[i][j][4 * v + e] : acc[ETM + i][j][4 * v + e]) + o[e];
+                }
+        __syncthreads();
+    }
+    auto sum = [&](int i, int j) -> v16i& {
+        if constexpr (KSPLIT == 2) return half_sum[i][j];
+        else return acc[i][j];
+    };
+    const int erow = wave_m + kg * EM;   // first row of the tile that this wavefront finishes
+
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
         const int c = tid + t * 64 * NW;
@@ -353,11 +393,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) bi[j][g] = *reinterpret_cast<const v4f*>(s_bias + wave_n + 32 * j + 8 * g + 4 * frag_half);
-    constexpr int NG = TM * TN * 4;  // groups of four columns per lane
+    constexpr int NG = ETM * TN * 4;  // groups of four columns per lane
     if constexpr (kTable || kEpi == EPI_Q) {
         constexpr int SW = WN + 16;
-        static_assert(NW * WM * SW <= STAGES * STAGE_BYTES, "patch fits the ring");
-        int8_t* patch = smem + wave * (WM * SW);
+        static_assert(NW * EM * SW <= STAGES * STAGE_BYTES, "patch fits the ring");
+        int8_t* patch = smem + wave * (EM * SW);
         // inverse output scale of a group (the QKV projection has one per column third)
         float inv_g[TN][4];
 #pragma unroll
@@ -374,11 +414,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         const float tlo = p.table.lo, tiw = p.table.inv_w, tmax = (float)(p.table.nseg - 1);
         // group index -> (i, j, g), i innermost: consecutive groups use different accumulators
         auto stage_a = [&](int G) {
-            const int i = G % TM, jg = G / TM, j = jg / 4, g = jg % 4;
+            const int i = G % ETM, jg = G / ETM, j = jg / 4, g = jg % 4;
             unsigned cellv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float v = __builtin_fmaf((float)acc[i][j][4 * g + e], alpha, bi[j][g][e]);
+                const float v = __builtin_fmaf((float)sum(i, j)[4 * g + e], alpha, bi[j][g][e]);
                 x[G % (DEPTH + 1)][e] = v;
                 if (kTable) {  // segment of v (subtract, multiply, clamp in float, floor)
                     float u = v - tlo;
@@ -394,7 +434,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
             }
         };
         auto stage_b = [&](int G) {
-            const int i = G % TM, jg = G / TM, j = jg / 4, g = jg % 4;
+            const int i = G % ETM, jg = G / ETM, j = jg / 4, g = jg % 4;
             int q[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -417,8 +457,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         constexpr int PCPR = WN / 16;
-        constexpr int NCH = WM * PCPR / 64;  // 16-byte chunks per lane
-        static_assert(WM * PCPR % 64 == 0, "chunks split evenly");
+        constexpr int NCH = EM * PCPR / 64;  // 16-byte chunks per lane
+        static_assert(EM * PCPR % 64 == 0, "chunks split evenly");
         v4i rows[NCH];
 #pragma unroll
         for (int t = 0; t < NCH; ++t) {
@@ -428,7 +468,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
 #pragma unroll
         for (int t = 0; t < NCH; ++t) {
             const int c = lane + 64 * t, row = c / PCPR, cc = c % PCPR;
-            const int mr = m0 + wave_m + row, n = n0 + wave_n + 16 * cc;
+            const int mr = m0 + erow + row, n = n0 + wave_n + 16 * cc;
             if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = rows[t];
         }
     } else if constexpr (kRelu) {
@@ -436,7 +476,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         // 16-byte stores.  Where the table is a ReLU and the columns' numbers cannot make a sum infinite, clamping the
         // code at 0 is all of it; any other table of two segments is a compare.
         constexpr int SW = kResid ? RW : WN + 16;
-        int8_t* patch = kResid ? s_res + wave_m * RW + wave_n : smem + wave * (WM * SW);
+        int8_t* patch = kResid ? s_res + erow * RW + wave_n : smem + wave * (EM * SW);
         const float rs = p.resid_scale, inv = p.out_inv_scale;
         const bool plain = !p.has_table;
         bool relu = p.relu;
@@ -452,18 +492,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
                 for (int g = 0; g < 4; ++g) {
                     const int cl = 32 * j + 8 * g + 4 * frag_half;
                     const v4f sc = *reinterpret_cast<const v4f*>(s_scale + wave_n + cl);
-                    unsigned rw[TM];
+                    unsigned rw[ETM];
                     if (kResid) {
 #pragma unroll
-                        for (int i = 0; i < TM; ++i) rw[i] = *reinterpret_cast<const unsigned*>(patch + (32 * i + frag_row) * SW + cl);
+                        for (int i = 0; i < ETM; ++i) rw[i] = *reinterpret_cast<const unsigned*>(patch + (32 * i + frag_row) * SW + cl);
                     }
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
+                    for (int i = 0; i < ETM; ++i) {
                         unsigned w = 0;
                         int q[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            float v = __builtin_fmaf((float)acc[i][j][4 * g + e], sc[e], bi[j][g][e]);
+                            float v = __builtin_fmaf((float)sum(i, j)[4 * g + e], sc[e], bi[j][g][e]);
                             if (kResid) v = __builtin_fmaf((float)(int)(int8_t)(rw[i] >> (8 * e)), rs, v);
                             if (kClamp) w = relu_requant(v, inv, e, w);
                             else q[e] = requant(kLines ? pwl_eval_two_segments(v, p.table) : v, inv);
@@ -480,13 +520,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        constexpr int PCPR = WN / 16, NCH = WM * PCPR / 64;
-        static_assert(WM * PCPR % 64 == 0, "chunks split evenly");
+        constexpr int PCPR = WN / 16, NCH = EM * PCPR / 64;
+        static_assert(EM * PCPR % 64 == 0, "chunks split evenly");
 #pragma unroll
         for (int t = 0; t < NCH; ++t) {
             const int c = lane + 64 * t, row = c / PCPR, cc = c % PCPR;
             const v4i o = *reinterpret_cast<const v4i*>(patch + row * SW + 16 * cc);
-            const int mr = m0 + wave_m + row, n = n0 + wave_n + 16 * cc;
+            const int mr = m0 + erow + row, n = n0 + wave_n + 16 * cc;
             if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = o;
         }
     } else if constexpr (kEpi == EPI_F32_RESID) {
@@ -498,16 +538,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
         float* patch = reinterpret_cast<float*>(smem + BM * RW) + wave * 32 * PW;
         const float rs = p.resid_scale;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int i = 0; i < ETM; ++i) {
 #pragma unroll
             for (int jg = 0; jg < 4 * TN; ++jg) {
                 const int j = jg / 4, g = jg % 4;
                 const int cl = 32 * j + 8 * g + 4 * frag_half;
-                const unsigned rw = *reinterpret_cast<const unsigned*>(s_res + (wave_m + 32 * i + frag_row) * RW + wave_n + cl);
+                const unsigned rw = *reinterpret_cast<const unsigned*>(s_res + (erow + 32 * i + frag_row) * RW + wave_n + cl);
                 v4f y;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float v = __builtin_fmaf((float)acc[i][j][4 * g + e], alpha, bi[j][g][e]);
+                    const float v = __builtin_fmaf((float)sum(i, j)[4 * g + e], alpha, bi[j][g][e]);
                     y[e] = __builtin_fmaf((float)(int)(int8_t)(rw >> (8 * e)), rs, v);
                 }
                 *reinterpret_cast<v4f*>(patch + frag_row * PW + cl) = y;
@@ -520,7 +560,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
             for (int t = 0; t < NST; ++t) {
                 const int c = lane + 64 * t, row = c / LPR, cc = c % LPR;
                 const v4f y = *reinterpret_cast<const v4f*>(patch + row * PW + 4 * cc);
-                const int m = m0 + wave_m + 32 * i + row, n = n0 + wave_n + 4 * cc;
+                const int m = m0 + erow + 32 * i + row, n = n0 + wave_n + 4 * cc;
                 if (full || (m < p.M && n < p.N)) *reinterpret_cast<v4f*>(p.out_f32 + (long)m * p.ldo + n) = y;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -637,13 +677,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_tile_kernel(st
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, typename Params>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1, typename Params>
 static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 {
-    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK, kConv>;
-    constexpr int NW = WAVES_M * WAVES_N, NBLK = (BM + BN) * BK / 1024;
+    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK, kConv, KSPLIT>;
+    constexpr int NW = WAVES_M * WAVES_N * KSPLIT, NBLK = (BM + BN) * BK / 1024;
     constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
-    constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M, BN / WAVES_N, kEpi);
+    constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M / KSPLIT, BN / WAVES_N, kEpi);
     static_assert(kFront % 16 == 0 && kFront + BN * 4 <= 160 * 1024 && kRing <= 160 * 1024, "LDS");
     const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;
     static std::once_flag once;  // one attribute call per instantiation
@@ -657,31 +697,31 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     p.group_m = xcd_group_rows(p.tiles_m, p.tiles_n, BM, BN);
-    queue_kernel(kern, dim3(p.tiles_m * p.tiles_n), dim3(64 * WAVES_M * WAVES_N), shmem, s, p);
+    queue_kernel(kern, dim3(p.tiles_m * p.tiles_n), dim3(64 * NW), shmem, s, p);
     return NM_OK;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KSPLIT = 1>
 static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
 {
     switch (epi) {
-    case EPI_Q: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q>(p, table_bytes, s);
-    case EPI_Q_TABLE: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE>(p, table_bytes, s);
-    case EPI_Q_TABLE2: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2>(p, table_bytes, s);
-    default: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID>(p, table_bytes, s);
+    case EPI_Q: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT>(p, table_bytes, s);
+    case EPI_Q_TABLE: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT>(p, table_bytes, s);
+    case EPI_Q_TABLE2: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2, 128, false, KSPLIT>(p, table_bytes, s);
+    default: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT>(p, table_bytes, s);
     }
 }
 
 // Convolutions, as products or with gathered rows.  us, streaming kernel -> this one with 128-byte slices: 12544 x 256 x 2304
 // (3x3) 16.4 -> 12.0, 3136 x 512 x 4608 (3x3) 22.3 -> 14.2, 50176 x 128 x 1152 (3x3) 15.8 -> 11.9, 3136 x 2048 x 512 with
 // residual 14.1 -> 8.4, 12544 x 256 x 1024 9.3 -> 6.9, 3136 x 2048 x 1024 (stride 2) 15.9 -> 11.1.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK = 128>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK = 128, int KSPLIT = 1>
 static int32_t launch_tile_relu(GemmParams& p, bool conv, hipStream_t s)
 {
     constexpr size_t cols = BN * sizeof(float);   // the scales, where other epilogues have their table
-    if (conv) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK, true>(p, cols, s);
-    if (p.resid) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU_RESID, BK>(p, cols, s);
-    return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK>(p, cols, s);
+    if (conv) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK, true, KSPLIT>(p, cols, s);
+    if (p.resid) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU_RESID, BK, false, KSPLIT>(p, cols, s);
+    return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_RELU, BK, false, KSPLIT>(p, cols, s);
 }
 
 }  // namespace nm

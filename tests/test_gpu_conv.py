@@ -113,7 +113,8 @@ def test_conv2d_all_outputs(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad):
 @pytest.mark.parametrize("B,H,W,Cin,Cout,k,stride,pad", [
     (27, 40, 40, 64, 48, 3, 1, 1), (13, 31, 29, 192, 96, 3, 1, 1), (7, 39, 35, 128, 112, 3, 1, 1), (1, 90, 93, 128, 128, 3, 1, 2),
     (3, 61, 63, 256, 400, 1, 2, 0), (2, 35, 37, 512, 432, 1, 1, 0), (1, 60, 61, 1024, 304, 1, 1, 0), (2, 40, 41, 128, 528, 1, 1, 0),
-    (5, 43, 41, 64, 208, 1, 1, 0), (3, 50, 51, 192, 240, 1, 1, 0), (31, 30, 30, 64, 64, 1, 1, 0), (9, 45, 41, 128, 112, 2, 1, 0)])
+    (5, 43, 41, 64, 208, 1, 1, 0), (3, 50, 51, 192, 240, 1, 1, 0), (31, 30, 30, 64, 64, 1, 1, 0), (9, 45, 41, 128, 112, 2, 1, 0),
+    (1, 111, 113, 256, 240, 3, 1, 1)])
 def test_conv2d_large_tile_kernel(oracle, B, H, W, Cin, Cout, k, stride, pad):
     """Convolutions whose outputs are large enough for the tile kernel: gathered rows (64- and 128-byte slices, several taps
     per slice count, strides, padding wider than needed) and plain ones of one, two, three and more slices; partly filled

@@ -616,7 +616,8 @@ def test_gemm_every_streaming_tile_configuration(oracle, M, N, K, what):
 @pytest.mark.parametrize("M,N,K,what", [
     (3900, 2992, 384, "256x192 tiles, two stages, ragged edges"), (8192, 1024, 512, "256x128 tiles"),
     (8192, 768, 512, "128x192 tiles"), (4096, 768, 512, "128x128 tiles"),
-    (4000, 720, 640, "128x128 tiles, ragged edges"), (4096, 3072, 768, "256x192 tiles, one per CU")])
+    (4000, 720, 640, "128x128 tiles, ragged edges"), (4096, 3072, 768, "256x192 tiles, one per CU"),
+    (3301, 752, 2048, "128x128 with two wavefronts to a sub-tile (fp32), ragged edges"), (3968, 1024, 512, "the same, few slices")])
 def test_gemm_tile_kernel_configurations(oracle, M, N, K, what):
     """Shapes that reach each configuration of the large-tile kernel (aligned operands, K a multiple
     of 128, scalar alpha): int8 output with and without the table, fp32 output with the residual."""
