@@ -13,6 +13,9 @@ constexpr int kBK = 64;  // bytes of k per pipeline stage
 
 struct GemmParams {
     int M, N, K;
+    int tiles_m, tiles_n;
+    int group_m;  // tile rows per group of the XCD-aware tile order
+    FastDiv div_group, div_gm;   // by group_m * tiles_n (streaming kernel: 8 * tiles_n) and group_m
     const int8_t* A; long lda;
     const int8_t* W; long ldw;
     int inner_count;
@@ -37,15 +40,13 @@ struct GemmParams {
     float* out_f32;
     int32_t* out_acc;
     uint16_t* dbg_seg;
-    int tiles_m, tiles_n;
-    int group_m;  // tile kernel: tile rows per group of the XCD-aware tile order
     // convolution in matrix form (streaming kernel with kConv): row m of A is the output position
     // (b, ho, wo), column k the (tap, channel) pair; A points to the NHWC image tensor
     int cH, cW, cCin, cKw, cStride, cPad, cHo, cWo;
     int relu;     // relu_codes holds for the table and the one output scale
     int batched;  // more than one problem (grid.y)
     int taps_w;            // tile kernel, kConv: filter columns (taps are numbered row by row, at most 32)
-    FastDiv div_tiles_m, div_group, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, 8 * tiles_n, cWo, cHo, cCin and cKw
+    FastDiv div_tiles_m, div_wo, div_ho, div_cin, div_kw;   // by tiles_m, cWo, cHo, cCin and cKw
 };
 
 struct GemmLnParams : GemmParams {
@@ -66,22 +67,30 @@ int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t t
 // The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).
 int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s);
 
-// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernel hands XCD x the
+// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
-// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the
-// r (a divisor of the eighth, with whole columns: tiles_n % c == 0) that makes this sum smallest.
+// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this
+// sum smallest, counting the rows and columns that an eighth straddles where r x c tiles are not exactly one.  (Operand
+// stream of 128x128 tiles of 4096 x 768 x 3072 alone: 20.5 TB/s with 4 x 6 tiles to an XCD, 11.5 with 24 x 1.)
 static inline int xcd_group_rows(int tiles_m, int tiles_n, int BM, int BN)
 {
-    const int ntiles = tiles_m * tiles_n;
-    if (ntiles % 8 != 0) return 8;
-    const int share = ntiles / 8;
-    int best = 8;
+    const int ntiles = tiles_m * tiles_n, share = (ntiles + 7) / 8;
+    int best = 1;
     long best_cost = -1;
     for (int r = 1; r <= tiles_m && r <= share; ++r) {
-        if (share % r != 0 || tiles_m % r != 0) continue;
-        const int c = share / r;
-        if (c > tiles_n || tiles_n % c != 0) continue;
-        const long cost = (long)r * BM + (long)c * BN;
+        long rows, cols;
+        if (share >= r * tiles_n) {   // whole groups
+            const int groups = (share + r * tiles_n - 1) / (r * tiles_n);
+            rows = (long)r * (share % (r * tiles_n) == 0 ? groups : groups + 1);
+            cols = tiles_n;
+        } else {
+            const bool exact = ntiles % 8 == 0 && share % r == 0 && tiles_n % (share / r) == 0 && tiles_m % r == 0;
+            rows = exact ? r : r + r / 2;
+            cols = exact ? share / r : share / r + 1;
+        }
+        if (rows > tiles_m) rows = tiles_m;
+        if (cols > tiles_n) cols = tiles_n;
+        const long cost = rows * BM + cols * BN;
         if (best_cost < 0 || cost < best_cost) best_cost = cost, best = r;
     }
     return best;

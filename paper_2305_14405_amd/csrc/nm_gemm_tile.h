@@ -93,17 +93,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     const int wave_m = (wave_t / WAVES_N) * WM;
     const int wave_n = (wave_t % WAVES_N) * WN;
 
-    // XCD-aware tile order, as in the streaming kernel
-    int id = blockIdx.x;
-    const int ntiles = p.tiles_m * p.tiles_n;
-    if (ntiles % 8 == 0) id = (id % 8) * (ntiles / 8) + id / 8;
-    const int GM = p.group_m;
-    const int group = id / (GM * p.tiles_n);
-    const int first_m = group * GM;
-    const int gm = min(GM, p.tiles_m - first_m);
-    const int in_group = id - group * GM * p.tiles_n;
-    const int tile_m = first_m + in_group % gm;
-    const int tile_n = in_group / gm;
+    // the arguments of everything in front of the first loads, in one step
+    asm volatile("" : : "s"(p.A), "s"(p.W), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.lda), "s"(p.ldw), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.group_m),
+                 "s"(p.div_group.magic), "s"(p.div_group.shift), "s"(p.div_gm.magic), "s"(p.div_gm.shift), "s"(p.bias));
+    // Workgroup i runs on XCD i % 8: an XCD gets a contiguous eighth of the tile sequence, which walks groups of
+    // group_m tile rows column by column (xcd_group_rows).
+    const int ntiles = p.tiles_m * p.tiles_n, share = (ntiles + 7) >> 3;
+    const int id = (blockIdx.x & 7) * share + (blockIdx.x >> 3);
+    if (id >= ntiles) return;
+    const int GM = p.group_m, group = (int)quotient((unsigned)id, p.div_group);   // by GM * tiles_n
+    const int first_m = group * GM, gm = min(GM, p.tiles_m - first_m);
+    const int in_group = id - first_m * p.tiles_n;
+    const int tile_n = gm == GM ? (int)quotient((unsigned)in_group, p.div_gm) : in_group / gm;
+    const int tile_m = first_m + in_group - tile_n * gm;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     // per-lane byte offsets of this wavefront's blocks (rows past the edge are clamped: they only
@@ -697,7 +699,9 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     p.group_m = xcd_group_rows(p.tiles_m, p.tiles_n, BM, BN);
-    queue_kernel(kern, dim3(p.tiles_m * p.tiles_n), dim3(64 * NW), shmem, s, p);
+    p.div_group = fast_div(p.group_m * p.tiles_n);
+    p.div_gm = fast_div(p.group_m);
+    queue_kernel(kern, dim3((p.tiles_m * p.tiles_n + 7) / 8 * 8), dim3(64 * NW), shmem, s, p);
     return NM_OK;
 }
 
