@@ -300,11 +300,13 @@ __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
     // before -> after, one behind the other, 128 x 768 2.8 -> 2.6, 4096 x 768 5.2 -> 4.7, 16384 x 1024 16.4 -> 13.8; in a
     // stack of 12 layers over one sequence of 128 tokens, where the vectors come from memory, 24 of them 20 us less.
     extern __shared__ float2 s_kb[];
-    asm volatile("" : : "s"(in), "s"(gamma), "s"(beta), "s"(t.kb), "s"(t.nseg), "s"(rows), "s"(cols), "s"(out_q), "s"(out_f32), "s"(eps),
-                 "s"(inv_L), "s"(two_tables), "s"(out_inv_scale), "s"(seg), "s"(seg2), "s"(t.lo), "s"(t.hi), "s"(t.inv_w),
-                 "s"(t.clamp_input), "s"(gridDim.x));
     bool staged = false;
-    constexpr bool kHold = kVec && C <= 4;   // the vectors stay in registers
+    // (beyond 1024 elements a row the registers for that cost more wavefronts than the wait: 4000 x 3000 21 us, 28 so)
+    constexpr bool kAhead = C <= 4, kHold = kVec && kAhead;   // the vectors stay in registers
+    if (kAhead)
+        asm volatile("" : : "s"(in), "s"(gamma), "s"(beta), "s"(t.kb), "s"(t.nseg), "s"(rows), "s"(cols), "s"(out_q), "s"(out_f32), "s"(eps),
+                     "s"(inv_L), "s"(two_tables), "s"(out_inv_scale), "s"(seg), "s"(seg2), "s"(t.lo), "s"(t.hi), "s"(t.inv_w),
+                     "s"(t.clamp_input), "s"(gridDim.x));
     v4f ga[kHold ? C : 1], be[kHold ? C : 1];
     float2 entry = make_float2(0.0f, 0.0f);
 
@@ -335,8 +337,13 @@ __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
                 for (int q = 0; q < 4; ++q)
                     if (ok[c][q]) x[c][q] = in[base + j0 + q];
             }
+            if (!kAhead) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (ok[c][q]) part = part + x[c][q];
+            }
         }
-        if (!staged) {
+        if (kAhead && !staged) {
             entry = t.kb[min((int)threadIdx.x, t.nseg - 1)];
             if (kHold) {
 #pragma unroll
@@ -348,14 +355,16 @@ __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (kAhead) {
 #pragma unroll
-        for (int c = 0; c < C; ++c)
+            for (int c = 0; c < C; ++c)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (ok[c][q]) part = part + x[c][q];
+                for (int q = 0; q < 4; ++q)
+                    if (ok[c][q]) part = part + x[c][q];
+        }
         if (!staged) {
-            if ((int)threadIdx.x < t.nseg) s_kb[threadIdx.x] = entry;
-            for (int i = threadIdx.x + kRowThreads; i < t.nseg; i += kRowThreads) s_kb[i] = t.kb[i];
+            if (kAhead && (int)threadIdx.x < t.nseg) s_kb[threadIdx.x] = entry;
+            for (int i = threadIdx.x + (kAhead ? kRowThreads : 0); i < t.nseg; i += kRowThreads) s_kb[i] = t.kb[i];
             if (two_tables) stage_table(s_kb + t.nseg, t2);
             __syncthreads();
             staged = true;
