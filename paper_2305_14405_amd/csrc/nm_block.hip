@@ -403,15 +403,17 @@ static int32_t launch_block(const BlockParams& p, size_t shmem, hipStream_t s)
 // 0: keep the separate kernels.  One workgroup runs on a CU, so up to 4096 rows 16 per workgroup are one round
 // of the chip and cost what 64 rows cost; beyond, 32 rows halve the rounds.  The cost of a round grows with
 // the weights (65 bytes per ns), that of the separate kernels with the rows.  Measured crossings (layer of a
-// stack, square heads, F = 4 H): up to 0.8 MB (H = 256) this kernel is faster at any number of rows, up to
-// 1.25 MB (H = 320) from 1024 rows, with 32 rows up to the 24576 that were measured; up to 2.5 MB (H = 448)
-// from 1024 rows to 4096 (beyond, 384: two rounds of 16 rows 61 us, separate 53; 512 at 4096 rows: 51, 50.5).
+// stack, heads of 64, F = 4 H; this kernel, separate kernels, us a layer): up to 0.6 MB (H = 192) this kernel is faster at
+// any number of rows (64 rows 17.8, 19.2; 4096 22, 41; 16384 51, 65); up to 1.25 MB from 850 rows, with 32 rows up to the
+// 24576 that were measured (H = 256: 512 rows 20.7, 19.8, 896 21.3, 22.0; 320: 768 30.3, 26.4, 896 30.3, 32.8, 16384 81,
+// 93); up to 2.5 MB from 1536 rows to 4096 (H = 384: 896 33, 29, 2048 34, 36; 448: 1536 45.4, 45.2, 3072 47, 54; beyond 4096,
+// 384: two rounds of 16 rows 61 us, separate 53; 512 at 4096 rows: 51, 46).
 static int block_rows(BlockParams& p, size_t* shmem)
 {
     if (p.H % 16 || p.F % 16 || p.M > 24576) return 0;
     const long weights = (long)p.H * (p.H + 2L * p.F + 3 * p.H);
     const int bm = p.M <= 4096 ? 16 : 32;
-    if (weights > (bm == 16 ? 2500000 : 1250000) || (weights > 800000 && p.M < 1024)) return 0;
+    if (weights > (bm == 16 ? 2500000 : 1250000) || (weights > 600000 && p.M < 850) || (weights > 1250000 && p.M < 1536)) return 0;
     if (p.H > 16 * kBlockWaves * kBlockHold) return 0;   // the tiles that a wavefront holds in registers
     return block_layout(p, bm, shmem) ? bm : 0;
 }
