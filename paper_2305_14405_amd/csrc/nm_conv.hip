@@ -194,7 +194,6 @@ struct StemParams {
     DevTable table;
     int B, H, W, Cin, Cout, kh, kw, stride, pad, Ho, Wo;
     int prow, pitch;         // staged image patch: rows, bytes per row
-    unsigned npx_magic;      // ceil(2^32 / pixels per row): exact division of a pixel's number (host)
     int front;               // LDS in front of the column vectors: patch and filter, or the output rows over them
     int8_t* out_q;
 };
@@ -215,12 +214,20 @@ __global__ __launch_bounds__(256) void stem_pack_filter_kernel(const int8_t* __r
     }
 }
 
-__global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+constexpr int kStemRow = 72;   // bytes of an output position's row in LDS
+__device__ __forceinline__ v4i stem_chunk(const int8_t* row)   // 16 bytes of such a row, eight-byte aligned
+{
+    const v2u lo = *reinterpret_cast<const v2u*>(row), hi = *reinterpret_cast<const v2u*>(row + 8);
+    return v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+}
+
+__global__ __launch_bounds__(256, 4) void stem_conv_kernel(StemParams p)
 {
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     int8_t* sX = smem;                                   // [prow][pitch]
     int8_t* sW = smem + p.prow * p.pitch;                // [64][kh][32]
-    int8_t* sO = smem;                                   // [4 wavefronts][64 positions][80], over both once they have been read
+    int8_t* sO = smem;                                   // [4 wavefronts][64 positions][kStemRow], over both once they have been read
     float* s_cols = reinterpret_cast<float*>(smem + p.front);   // scale | bias, 64 each
     float2* s_kb = reinterpret_cast<float2*>(s_cols + 128);
 
@@ -230,45 +237,57 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
     const long b = blockIdx.y;
     const int hi0 = ho0 * p.stride - p.pad, wi0 = wo0 * p.stride - p.pad;
 
-    if (p.has_table) stage_table(s_kb, p.table);
-    if (tid < 64) {
-        s_cols[tid] = tid < p.Cout ? (p.alpha_vec ? p.alpha_vec[tid] : p.alpha) : 0.0f;
-        s_cols[64 + tid] = (tid < p.Cout && p.bias) ? p.bias[tid] : 0.0f;
-    }
     // filter, already packed as [n][i][8 pixels of 4 bytes]: direct loads
     for (int i = wave; i < 2 * p.kh; i += 4) dma16(p.w + 1024 * i + 16 * lane, (unsigned)(uintptr_t)sW + 1024 * i);
+    // scale (first wavefront) and bias (second): requested here, written behind the patch
+    const float* const cols = wave == 0 ? p.alpha_vec : p.bias;
+    float col_value = wave == 0 ? p.alpha : 0.0f;
+    if (wave < 2 && lane < p.Cout && cols) col_value = cols[lane];
     // Image patch: one dword per pixel, read as one unaligned word and shifted where that word would pass the
     // end of the tensor.  (Pixels behind the patch's last column fill the rows up to their pitch: the last
-    // positions' 32-byte windows reach them, with zero filter bytes.)  Six words per thread travel together:
-    // with a byte load per channel, waited for pixel by pixel, the kernel took 57 us on 64 images of 224 x 224 and 12
-    // on one; now 36 and 7.3 (the output rows over the operands let four workgroups share a CU instead of three).
+    // positions' 32-byte windows reach them, with zero filter bytes.)  A wavefront takes whole rows, a lane one column:
+    // the row's address and whether it is inside are scalar work, a pixel few vector instructions.  On 64 images of
+    // 224 x 224 and on one, us: pixels numbered through, one accumulator set in the other half of the register file
+    // (three workgroups to a CU) 34.6 and 7.5; this with four workgroups 35.0 and 7.4 (820 vector instructions a
+    // wavefront instead of 985); with the column vectors requested in front instead of waited for 31.8 and 6.7.  Vector
+    // instructions issue in 64 % of the cycles; ten rows at a time instead of five need 187 registers and take 45.8.
     {
-        constexpr int U = 6;
-        const int npx = p.pitch >> 2, total = p.prow * npx;
+        constexpr int U = 5;
+        const int npx = p.pitch >> 2, row0 = __builtin_amdgcn_readfirstlane(wave);
         const long row_bytes = (long)p.W * p.Cin;
         const int8_t* const img = p.x + b * p.H * row_bytes;
         const int8_t* const last = p.x + (long)p.B * p.H * row_bytes - 4;
-        const unsigned mask = 0xffffffffu >> (32 - 8 * p.Cin);
-        for (int i0 = 0; i0 < total; i0 += 256 * U) {
-            unsigned px[U];
-            int shift[U];
+        for (int c0 = 0; c0 < npx; c0 += 64) {
+            const int c = c0 + lane, wi = wi0 + c;
+            const bool col = (unsigned)wi < (unsigned)p.W;
+            const int from_col = min(max(wi0 + c0, 0), p.W - 1);   // lanes count from here
+            const unsigned off = col ? (unsigned)(wi - from_col) * (unsigned)p.Cin : 0u;
+            const unsigned mask = col ? 0xffffffffu >> (32 - 8 * p.Cin) : 0u;
+            for (int r0 = row0; r0 < p.prow; r0 += 4 * U) {
+                unsigned px[U], shift[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int idx = i0 + 256 * u + tid, r = (int)__umulhi((unsigned)idx, p.npx_magic), c = idx - r * npx;
-                const int hi = hi0 + r, wi = wi0 + c;
-                const bool inside = (unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W;
-                const int8_t* const a = inside ? img + hi * row_bytes + wi * p.Cin : img;
-                const int8_t* const from = a < last ? a : last;
-                __builtin_memcpy(&px[u], from, 4);
-                shift[u] = inside ? 8 * (int)(a - from) : -1;
-            }
+                for (int u = 0; u < U; ++u) {
+                    const int hi = hi0 + r0 + 4 * u;
+                    const int8_t* const a = img + ((unsigned)hi < (unsigned)p.H ? hi : 0) * row_bytes + (long)from_col * p.Cin;
+                    const long left = last - a;   // bytes to the last whole word; -3 at least
+                    const int high = (int)(left >> 32);
+                    const unsigned limit = high < 0 ? 0u : high > 0 ? 0x7fffffffu : (unsigned)left;
+                    const unsigned at = off + (high < 0 ? (unsigned)-(int)left : 0u), from = min(at, limit);
+                    __builtin_memcpy(&px[u], (high < 0 ? last : a) + from, 4);
+                    shift[u] = 8 * (at - from);
+                }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int idx = i0 + 256 * u + tid;
-                if (idx < total) *reinterpret_cast<unsigned*>(sX + 4 * idx) = shift[u] < 0 ? 0u : (px[u] >> shift[u]) & mask;
+                for (int u = 0; u < U; ++u) {
+                    const int r = r0 + 4 * u;
+                    if (r >= p.prow) break;
+                    const unsigned m = (unsigned)(hi0 + r) < (unsigned)p.H ? mask : 0u;
+                    if (c < npx) *reinterpret_cast<unsigned*>(sX + r * p.pitch + 4 * c) = (px[u] >> shift[u]) & m;
+                }
             }
         }
     }
+    if (wave < 2) s_cols[tid] = lane < p.Cout ? col_value : 0.0f;
+    if (p.has_table && !p.table.two_seg) stage_table(s_kb, p.table);
     wait_vmcnt<0>();
     __syncthreads();
 
@@ -306,40 +325,44 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
     }
 
     __syncthreads();   // the output rows lie over the operands
-    // epilogue: lane (m, half) holds, per group g of four registers, channels 32j + 8g + 4half .. +3
-    int8_t* patch = sO + wave * (64 * 80);
+    // epilogue: lane (m, half) holds, per group g of four registers, channels 32j + 8g + 4half .. +3; the halves of two
+    // groups change lanes, so that a lane writes eight consecutive channels.  Rows of 72 bytes: 32 lanes' eight bytes
+    // fall on all 64 banks once.
+    int8_t* patch = sO + wave * (64 * kStemRow);
     // (three times: a table of two segments is evaluated with a compare instead of index and gather, and a ReLU
     // by clamping the code)
     auto finish = [&](auto form_c) {
         constexpr bool kTwoSeg = decltype(form_c)::value == 1, kRelu = decltype(form_c)::value == 2;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int h = 0; h < 2; ++h) {
+                v4f sc[2], bi[2];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int n = 32 * j + 8 * g + 4 * half;
-                    const v4f sc = *reinterpret_cast<const v4f*>(s_cols + n);
-                    const v4f bi = *reinterpret_cast<const v4f*>(s_cols + 64 + n);
-                    unsigned* out = reinterpret_cast<unsigned*>(patch + (32 * t + fr) * 80 + n);
-                    if (kRelu) {
-                        unsigned w = 0;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            w = relu_requant(__builtin_fmaf((float)acc[t][j][4 * g + e], sc[e], bi[e]), p.out_inv_scale, e, w);
-                        *out = w;
-                        continue;
-                    }
-                    int q[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float v = __builtin_fmaf((float)acc[t][j][4 * g + e], sc[e], bi[e]);
-                        if (kTwoSeg) v = pwl_eval_two_segments(v, p.table);
-                        else if (p.has_table) { int sg; v = pwl_eval(v, p.table, s_kb, sg); }
-                        q[e] = requant(v, p.out_inv_scale);
-                    }
-                    *out = pack4(q[0], q[1], q[2], q[3]);
+                for (int g = 0; g < 2; ++g) {
+                    sc[g] = *reinterpret_cast<const v4f*>(s_cols + 32 * j + 16 * h + 8 * g + 4 * half);
+                    bi[g] = *reinterpret_cast<const v4f*>(s_cols + 64 + 32 * j + 16 * h + 8 * g + 4 * half);
                 }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    unsigned w[2] = {0, 0};
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        int q[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float v = __builtin_fmaf((float)acc[t][j][8 * h + 4 * g + e], sc[g][e], bi[g][e]);
+                            if (kRelu) { w[g] = relu_requant(v, p.out_inv_scale, e, w[g]); continue; }
+                            if (kTwoSeg) v = pwl_eval_two_segments(v, p.table);
+                            else if (p.has_table) { int sg; v = pwl_eval(v, p.table, s_kb, sg); }
+                            q[e] = requant(v, p.out_inv_scale);
+                        }
+                        if (!kRelu) w[g] = pack4(q[0], q[1], q[2], q[3]);
+                    }
+                    const auto x = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);
+                    *reinterpret_cast<v2u*>(patch + (32 * t + fr) * kStemRow + 32 * j + 16 * h + 8 * half) = v2u{x[0], x[1]};
+                }
+            }
     };
     if (p.relu && __all(relu_finite(s_cols[lane], s_cols[64 + lane]))) finish(std::integral_constant<int, 2>{});
     else if (p.has_table && p.table.two_seg) finish(std::integral_constant<int, 1>{});
@@ -354,7 +377,7 @@ __global__ __launch_bounds__(256) void stem_conv_kernel(StemParams p)
         const int ho = ho0 + wave * 4 + (pos >> 4), wo = wo0 + (pos & 15);
         if (ho < p.Ho && wo < p.Wo)
             *reinterpret_cast<v4i*>(p.out_q + ((b * p.Ho + ho) * p.Wo + wo) * p.Cout + 16 * cc) =
-                *reinterpret_cast<const v4i*>(patch + pos * 80 + 16 * cc);
+                stem_chunk(patch + pos * kStemRow + 16 * cc);
     }
 }
 
@@ -470,10 +493,8 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
         sp.prow = 15 * d->stride + d->kh;
         // a position's window is 32 bytes from its first pixel: the last position's reaches 8 pixels
         sp.pitch = ((15 * d->stride + 8) * 4 + 15) / 16 * 16;
-        // pixel numbers stay below 2^13 (at most 64 rows of at most 68 pixels) plus a workgroup's surplus
-        sp.npx_magic = (unsigned)(((1ULL << 32) + sp.pitch / 4 - 1) / (sp.pitch / 4));
         sp.out_q = d->out_q;
-        const size_t operands = (size_t)sp.prow * sp.pitch + 64 * (size_t)d->kh * 32, rows = 4 * 64 * 80;
+        const size_t operands = (size_t)sp.prow * sp.pitch + 64 * (size_t)d->kh * 32, rows = 4 * 64 * kStemRow;
         const size_t behind = 128 * sizeof(float) + (g.has_table ? sizeof(float2) * (size_t)g.table.nseg : 0);
         if (operands + rows + behind > 64 * 1024)
             return fail(NM_ERR_UNSUPPORTED, "nm_conv2d_pwl: direct route needs %zu bytes of LDS", operands + rows + behind);
