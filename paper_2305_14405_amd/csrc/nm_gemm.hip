@@ -26,8 +26,8 @@
 // k of one row.  The same k of A and W always meet in the same (lane group, byte) slot, and int32
 // addition is exact, so results do not depend on tiling, on the k order or on any split of K.
 #include <cstdlib>
-#include <cstring>
 
+#include "nm_gemm_choice.h"
 #include "nm_gemm_common.h"
 #include "nm_gemm_tile.h"
 
@@ -39,23 +39,10 @@ static bool force_generic()
     static const bool v = [] { const char* e = getenv("NM_GEMM_GENERIC"); return e && e[0] == '1'; }();
     return v;
 }
-// Debug switch, read once per process: NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3>|relu<2,5-11>|tile<0-9> forces
-// that tile configuration wherever its requirements hold (tuning aid; "oldbig" is the streaming kernel's
-// 256x192 configuration, which the tile kernel has replaced).
-static int forced_cfg()
+// Debug switch NM_GEMM_CFG (tuning aid), read once per process.
+static ForcedCfg forced_cfg()
 {
-    static const int v = [] {
-        const char* e = getenv("NM_GEMM_CFG");
-        if (!e) return -1;
-        static const char* const names[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
-        if (!strncmp(e, "direct", 6)) return 10 + atoi(e + 6);
-        if (!strncmp(e, "unaligned", 9)) return 20 + atoi(e + 9);
-        if (!strncmp(e, "relu", 4)) return 30 + atoi(e + 4);
-        if (!strncmp(e, "tile", 4)) return 50 + atoi(e + 4);
-        for (int i = 0; i < 7; ++i)
-            if (!strcmp(e, names[i])) return i;
-        return -1;
-    }();
+    static const ForcedCfg v = parse_forced_cfg(getenv("NM_GEMM_CFG"));
     return v;
 }
 
@@ -759,52 +746,6 @@ bool gemm_folds_layernorm(const GemmArgs& g)
     return al && (int64_t)g.M * g.lda < (1LL << 32) && (int64_t)g.N * g.ldw < (1LL << 32);
 }
 
-// Which tile of the tile kernel: the one whose predicted time is smallest.  A configuration takes
-//   start + rounds * slice * K / 128 + rounds' * epilogue   us,
-// rounds being its tiles over its places on the 256 CUs (up to three workgroups share one).  Up to 256 tiles behind the
-// full rounds have a CU each and are charged the fraction `alone` of a round (`alone_epi` of an epilogue),
-// up to 512 where three share a CU `paired`.  A ring of two stages only pays where workgroups do share (from
-// `least` tiles on; it is also the one for K = 384): alone on a CU it waits for its operands, 23 instead of 17 us at
-// 4096 x 768 x 3072 with 128x128.  The last entry is 128x128 with two wavefronts to a sub-tile, each taking half of a slice's
-// k-steps: two on every SIMD where one workgroup has a CU, for the fp32 epilogue (4096 x 768 x 3072 18.4 -> 16.4 us, 2560 x
-// 1024 x 4096 20.9 -> 18.3, 4096 x 768 x 768 10.6 -> 9.4); the shorter int8 ones do not repay the exchange (1500 x 2304 x 768
-// 6.6, 7.0).  The constants are least-squares fits to 180 measured shapes: M from 64 to
-// 16384, the four products of a layer of width 512, 768 and 1024.  Over those the chosen tile is 1.2 % slower than
-// the best of the first nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
-// were 7 % (54 %) slower from M = 2048 on.  On 106 shapes outside the fit (widths 384, 640, 896, 1152, 1280 and 1536, FFNs
-// of 4 H and 2 H + 128, M drawn up to 16384) it is 1.6 % slower than the best, at a tenth of them 6 % or more, at the
-// two worst 38 % (1683 x 4608 x 1536) and 11 %.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
-// 128x128 likewise | 64x128 likewise:
-//   16384 x 1024 x 4096, fp32:   64 | 87 | 72 | 84 | 79 | 89 | 77
-//   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
-//    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21 | 18 | 19
-//    2048 x  768 x 3072, fp32:   33 | 26 | 20 | 17 | 17 | 15 | 15 | 10 | 11
-// allowed: a bit per configuration.
-static int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allowed = ~0u)
-{
-    static const struct { int bm, bn, stages, places, least; double alone, paired, alone_epi, start, slice, f32, q, table; } kTiles[] = {
-        {256, 256, 2, 256, 0, 1, 1, 1, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, 0, 1, 1, 1, -2.43, 0.89, 10.88, 7.70, 9.41},
-        {256, 128, 3, 256, 0, 1, 1, 1, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0, 1, 1, 1, 0.08, 0.54, 7.35, 4.55, 5.87},
-        {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 5.92, 2.75, 3.90},
-        {128, 128, 2, 512, 257, 0.65, 1, 0.65, 0.48, 0.87, 8.91, 2.98, 4.47}, {64, 128, 3, 512, 0, 0.45, 1, 0.8, 1.19, 0.52, 3.52, 2.23, 3.00},
-        {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.385, 6.7, 0, 0}};
-    int best = -1;
-    double best_us = 0.0;
-    for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
-        const auto& t = kTiles[c];
-        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
-        if (c == 5 ? f32 : c == 9 && !f32) continue;
-        if (!(allowed >> c & 1) || K / 128 < t.stages + 1 || (tiles < t.least && K / 128 > 3)) continue;
-        const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
-        const double full = (double)(tiles / t.places);
-        const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);
-        const double epilogues = full + (rest == 0 ? 0.0 : alone ? t.alone_epi : paired ? t.paired : 1.0);
-        const double us = t.start + rounds * t.slice * (K / 128) + epilogues * (f32 ? t.f32 : table ? t.table : t.q);
-        if (best < 0 || us < best_us) best_us = us, best = c;
-    }
-    return best;
-}
-
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M == 0) return NM_OK;
@@ -893,17 +834,6 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     else if (mid_tiles >= 320) cfg = (split_ok && g.K >= 2048) ? CFG_SMALL : CFG_MID3;
     else if (split_ok) cfg = (mid_tiles < 160 && g.M > 64) ? CFG_SMALL : CFG_SPLIT;
     else cfg = CFG_MID3;
-    bool old_big = false;
-    if (g.N > 64) {
-        const int f = forced_cfg();
-        if (f == 6 && !g.conv && k128) { cfg = CFG_BIG; old_big = true; }
-        if (f == 0 && !g.conv && k128) cfg = CFG_BIG;
-        else if (f == 1) cfg = CFG_WIDE;
-        else if (f == 2 && split_ok) cfg = CFG_SPLIT;
-        else if (f == 3 && split_ok) cfg = CFG_SMALL;
-        else if (f == 4) cfg = CFG_MID3;
-        else if (f == 5) cfg = CFG_MID2;
-    }
     // a gathered A operand is read 16 bytes at a time by every kernel that takes one (the caller has
     // checked Cin % 64 == 0, 16-byte aligned image and weights)
     if (g.conv && (!w_al || !aligned(g.A, 16) || g.cCin % 64 != 0 || g.K % (g.cCin * g.cKw) != 0))
@@ -937,22 +867,10 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
     const int64_t direct_below = tile_ok ? 1050000 : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
-    const bool direct = direct_ok && ((forced_cfg() >= 10 && forced_cfg() < 20) || (forced_cfg() < 0 && (direct_align < 16 || outputs < direct_below)));
     // Register-staged tiles, for operands that cannot go to LDS directly in whole slices: from 0.8 million outputs on.  Below
     // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do
     // (8000 x 100 x 777 11.4, 8.5; 1220 x 751 x 40 7.2, 6.5; 1000 x 999 x 999 11.2, 9.9).
-    const bool unaligned = direct_ok && !g.conv && batches == 1 && g.N >= 4 &&
-                           ((forced_cfg() >= 20 && forced_cfg() < 30) || (forced_cfg() < 0 && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000));
-    if (unaligned) {
-        rc = launch_unaligned(p, direct_align, table_bytes, forced_cfg() - 20 >= 0 ? forced_cfg() - 20 : -1, stream);
-        if (rc) return rc;
-        return check_hip(hipGetLastError(), "gemm launch");
-    }
-    if (direct) {
-        rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced_cfg() - 10 >= 0 ? forced_cfg() - 10 : -1, stream);
-        if (rc) return rc;
-        return check_hip(hipGetLastError(), "gemm launch");
-    }
+    const bool unaligned_ok = direct_ok && !g.conv && batches == 1 && g.N >= 4;
     // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
     // residual; the rows gathered or not).  128-byte slices and the cost model's tile where K (a gathered row's Cin) is a
     // multiple of 128 and long enough for a ring; 64-byte ones of 128x128 tiles, three in flight, otherwise; of 128x64 for at
@@ -963,16 +881,34 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                           p.q16 && g.N % 16 == 0 && batches == 1 && g.split_cols == 0 && (!g.resid || p.r16) && w_al &&
                           (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
     const int kunit = g.conv ? g.cCin : g.K;
-    const bool relu_tile = relu_epi && kunit % 64 == 0 && (forced_cfg() < 0 || (forced_cfg() >= 30 && forced_cfg() < 50)) &&
-                           (g.conv ? !g.resid && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
-                                   : al && (int64_t)g.M * g.lda < (1LL << 32));
-    if (relu_tile) {
+    const bool relu_ok = relu_epi && kunit % 64 == 0 &&
+                         (g.conv ? !g.resid && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
+                                 : al && (int64_t)g.M * g.lda < (1LL << 32));
+    // the debug switch's configuration, if this product meets its requirements
+    ForcedCfg forced = forced_cfg();
+    const bool holds = forced.kind == FORCED_STREAM ? g.N > 64 && (g.conv || stream_ok) && stream_takes(forced.number, g.conv != 0, k128, split_ok)
+                     : forced.kind == FORCED_DIRECT ? direct_ok && direct_takes(forced.number, g.K, table_bytes)
+                     : forced.kind == FORCED_UNALIGNED ? unaligned_ok
+                     : forced.kind == FORCED_RELU ? relu_ok && relu_takes(forced.number, kunit)
+                     : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K) : false;
+    if (!holds) forced = ForcedCfg();
+    const bool free_choice = forced.kind == FORCED_NONE;
+    if (forced.kind == FORCED_UNALIGNED || (free_choice && unaligned_ok && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000)) {
+        rc = launch_unaligned(p, direct_align, table_bytes, forced.number, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "gemm launch");
+    }
+    if (forced.kind == FORCED_DIRECT || (free_choice && direct_ok && (direct_align < 16 || outputs < direct_below))) {
+        rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced.number, stream);
+        if (rc) return rc;
+        return check_hip(hipGetLastError(), "gemm launch");
+    }
+    if (forced.kind == FORCED_RELU || (free_choice && relu_ok)) {
         p.taps_w = g.cKw;
         if (g.conv) p.div_wo = fast_div(g.cWo), p.div_ho = fast_div(g.cHo);
-        int c = forced_cfg() >= 30 && forced_cfg() < 50 ? forced_cfg() - 30 : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
+        int c = !free_choice ? forced.number : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
                                                        : choose_tile(g.M, g.N, g.K, false, false, 0x1e4);
-        if (c <= 8 && kunit % 128 != 0) c = 9;
-        if (c == 5 && g.K >= 1536) c = 11;   // 12544 x 256 x 2304 (3x3) 12.8 -> 12.0; 12544 x 256 x 1024 7.0 with 5, 7.6
+        if (free_choice && c == 5 && g.K >= 1536) c = 11;   // 12544 x 256 x 2304 (3x3) 12.8 -> 12.0; 12544 x 256 x 1024 7.0 with 5, 7.6
         switch (c) {
         case 2: rc = launch_tile_relu<256, 128, 4, 2, 3>(p, g.conv != 0, stream); break;
         case 5: rc = launch_tile_relu<128, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
@@ -986,6 +922,10 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
     }
+    if (forced.kind == FORCED_STREAM) {
+        static constexpr decltype(cfg) kStream[] = {CFG_BIG, CFG_WIDE, CFG_SPLIT, CFG_SMALL, CFG_MID3, CFG_MID2, CFG_BIG};
+        cfg = kStream[forced.number];
+    }
     if (g.conv) {
         // gathered A operand: one problem, no batching
         if (cfg == CFG_NARROW) rc = launch_stream_conv<256, 64, 4, 1, 1, 64, 2>(p, epi, table_bytes, stream);
@@ -998,10 +938,10 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         return check_hip(hipGetLastError(), "conv gemm launch");
     }
     int tile_cfg = -1;
-    if (tile_ok && !old_big) {
-        if (forced_cfg() < 0) tile_cfg = choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
-        else if (forced_cfg() == 0) tile_cfg = 1;
-        else if (forced_cfg() >= 50) tile_cfg = forced_cfg() - 50;
+    if (tile_ok) {
+        if (free_choice) tile_cfg = choose_tile(g.M, g.N, g.K, epi == EPI_F32_RESID, g.has_table != 0);
+        else if (forced.kind == FORCED_TILE) tile_cfg = forced.number;
+        else if (forced.number == STREAM_BIG) tile_cfg = 1;
     }
     if (tile_cfg >= 0 && two_level_q) epi = EPI_Q_TABLE2;
     if (tile_cfg == 0) {

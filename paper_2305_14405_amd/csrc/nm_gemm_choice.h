@@ -1,0 +1,160 @@
+// Choices that the GEMM launchers make on the host, in plain C++ (no HIP header: the CPU tests compile this file alone).
+#pragma once
+
+#include <cstddef>
+#include <cstdlib>
+#include <cstring>
+
+namespace nm {
+
+// Debug switch NM_GEMM_CFG (tuning aid): the kernel, and the configuration of it, that a product takes wherever it meets that
+// configuration's requirements; anywhere else, and where the value is not one of these, the rules decide.
+//   big|wide|split|small|mid3|mid2|oldbig   streaming kernel (big: the tile kernel's 256x192 where that one takes the product,
+//                                           which has replaced the streaming kernel's, oldbig)
+//   direct<0-5>  unaligned<0-3>  tile<0-9>  small-tile, register-staged and tile kernel
+//   relu<2,5-11>                            tile kernel with the epilogues of convolutions
+enum ForcedKind { FORCED_NONE, FORCED_STREAM, FORCED_DIRECT, FORCED_UNALIGNED, FORCED_RELU, FORCED_TILE };
+enum { STREAM_BIG, STREAM_WIDE, STREAM_SPLIT, STREAM_SMALL, STREAM_MID3, STREAM_MID2, STREAM_OLDBIG };
+struct ForcedCfg {
+    ForcedKind kind = FORCED_NONE;
+    int number = -1;
+};
+
+inline ForcedCfg parse_forced_cfg(const char* e)
+{
+    static const char* const stream[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
+    static const struct { const char* name; ForcedKind kind; unsigned numbers; } numbered[] = {
+        {"direct", FORCED_DIRECT, 0x3f}, {"unaligned", FORCED_UNALIGNED, 0xf}, {"tile", FORCED_TILE, 0x3ff}, {"relu", FORCED_RELU, 0xfe4}};
+    ForcedCfg f;
+    if (!e) return f;
+    for (int i = 0; i < 7; ++i)
+        if (!std::strcmp(e, stream[i])) f.kind = FORCED_STREAM, f.number = i;
+    for (const auto& n : numbered) {
+        const size_t len = std::strlen(n.name);
+        if (std::strncmp(e, n.name, len)) continue;
+        const char* const digits = e + len;   // one or two, nothing in front of or behind them
+        const size_t count = std::strspn(digits, "0123456789");
+        if (count < 1 || count > 2 || digits[count]) continue;
+        const int number = std::atoi(digits);
+        if (number < 32 && (n.numbers >> number & 1)) f.kind = n.kind, f.number = number;
+    }
+    return f;
+}
+
+// Requirements of a configuration beyond those of its kernel.  k128: K (of a gathered row: Cin) is a multiple of 128; split_ok:
+// and the table leaves room for a ring of three such slices; kunit: K or Cin, a multiple of 64 (9 and 10 have slices of 64 bytes).
+constexpr bool stream_takes(int c, bool conv, bool k128, bool split_ok)
+{
+    return c == STREAM_BIG || c == STREAM_OLDBIG ? !conv && k128 : c == STREAM_SPLIT || c == STREAM_SMALL ? split_ok : true;
+}
+constexpr bool relu_takes(int c, int kunit) { return c == 9 || c == 10 || kunit % 128 == 0; }
+
+// Which tile of the tile kernel: the one whose predicted time is smallest.  A configuration takes
+//   start + rounds * slice * K / 128 + rounds' * epilogue   us,
+// rounds being its tiles over its places on the 256 CUs (up to three workgroups share one).  Up to 256 tiles behind the
+// full rounds have a CU each and are charged the fraction `alone` of a round (`alone_epi` of an epilogue),
+// up to 512 where three share a CU `paired`.  A ring of two stages only pays where workgroups do share (from
+// `least` tiles on; it is also the one for K = 384): alone on a CU it waits for its operands, 23 instead of 17 us at
+// 4096 x 768 x 3072 with 128x128.  The last entry is 128x128 with two wavefronts to a sub-tile, each taking half of a slice's
+// k-steps: two on every SIMD where one workgroup has a CU, for the fp32 epilogue (4096 x 768 x 3072 18.4 -> 16.4 us, 2560 x
+// 1024 x 4096 20.9 -> 18.3, 4096 x 768 x 768 10.6 -> 9.4); the shorter int8 ones do not repay the exchange (1500 x 2304 x 768
+// 6.6, 7.0).  The constants are least-squares fits to 180 measured shapes: M from 64 to
+// 16384, the four products of a layer of width 512, 768 and 1024.  Over those the chosen tile is 1.2 % slower than
+// the best of the first nine (12 % at worst); full rounds weighted by one number per tile, over four of them,
+// were 7 % (54 %) slower from M = 2048 on.  On 106 shapes outside the fit (widths 384, 640, 896, 1152, 1280 and 1536, FFNs
+// of 4 H and 2 H + 128, M drawn up to 16384) it is 1.6 % slower than the best, at a tenth of them 6 % or more, at the
+// two worst 38 % (1683 x 4608 x 1536) and 11 %.  Examples, us, 256x256 | 256x192 | 256x128 | 128x192 with three and two stages |
+// 128x128 likewise | 64x128 likewise:
+//   16384 x 1024 x 4096, fp32:   64 | 87 | 72 | 84 | 79 | 89 | 77
+//   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
+//    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21 | 18 | 19
+//    2048 x  768 x 3072, fp32:   33 | 26 | 20 | 17 | 17 | 15 | 15 | 10 | 11
+// allowed: a bit per configuration.
+struct TileConfig {
+    int bm, bn, stages, places, least;
+    double alone, paired, alone_epi, start, slice, f32, q, table;
+};
+constexpr TileConfig kTileConfigs[] = {
+    {256, 256, 2, 256, 0, 1, 1, 1, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, 0, 1, 1, 1, -2.43, 0.89, 10.88, 7.70, 9.41},
+    {256, 128, 3, 256, 0, 1, 1, 1, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0, 1, 1, 1, 0.08, 0.54, 7.35, 4.55, 5.87},
+    {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 5.92, 2.75, 3.90},
+    {128, 128, 2, 512, 257, 0.65, 1, 0.65, 0.48, 0.87, 8.91, 2.98, 4.47}, {64, 128, 3, 512, 0, 0.45, 1, 0.8, 1.19, 0.52, 3.52, 2.23, 3.00},
+    {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.385, 6.7, 0, 0}};
+
+// Whether the tile kernel's configuration c takes a contraction of K bytes: its k-loop is a first slice, the steady state
+// and the last slices, so it needs one slice more than its ring has stages.
+constexpr bool tile_takes(int c, int K)
+{
+    return c >= 0 && c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])) && K / 128 >= kTileConfigs[c].stages + 1;
+}
+
+inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allowed = ~0u)
+{
+    int best = -1;
+    double best_us = 0.0;
+    for (int c = 0; c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])); ++c) {
+        const auto& t = kTileConfigs[c];
+        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
+        if (c == 5 ? f32 : c == 9 && !f32) continue;
+        if (!(allowed >> c & 1) || !tile_takes(c, K) || (tiles < t.least && K / 128 > 3)) continue;
+        const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
+        const double full = (double)(tiles / t.places);
+        const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);
+        const double epilogues = full + (rest == 0 ? 0.0 : alone ? t.alone_epi : paired ? t.paired : 1.0);
+        const double us = t.start + rounds * t.slice * (K / 128) + epilogues * (f32 ? t.f32 : table ? t.table : t.q);
+        if (best < 0 || us < best_us) best_us = us, best = c;
+    }
+    return best;
+}
+
+// Which tile, aligned operands: the one whose predicted time is smallest,
+//   start + L * (tile + slice * slices) + R * (round + chain * c) + wave * c   us,
+// c being the slices of a wavefront, L the workgroups of the CU that has most and R the rounds it takes for them (as many
+// workgroups share a CU as LDS and its 32 wavefronts allow).  The constants are least-squares fits to 285 measured
+// products (16 to 1500 rows, the four products of layers of width 384 to 1024, convolutions of a residual CNN as products;
+// rms 5 to 9 %).  Over those the chosen tile is 0.8 % slower than the best of nine (11 % at worst), the rule by the
+// number of tiles before it 3.0 %.  us, 16x32 | 32x32 | 32x64 with four wavefronts, with eight | 48x64 | 64x64:
+//   128 x 768 x 3072   3.9 | 3.9 | 5.9 | 5.2 | 5.8 | 6.9      847 x  768 x 3072  11.4 | 10.1 | 10.5 | 12.0 | 8.4 | 9.2
+//   512 x 1024 x 4096   10 | 8.9 | 9.8 | 7.7 | 8.4 | 9.4     1024 x 1024 x 1024   6.6 |  6.5 |  6.0 |  7.2 | 7.9 | 5.9
+struct DirectTile {
+    int bm, bn, kw, depth;
+    double start, tile, round, slice, chain, wave;
+};
+constexpr DirectTile kDirectTiles[] = {
+    {16, 32, 8, 3, 1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {32, 32, 4, 2, 1.92, 0.08, 0.45, 0.102, 0.14, -0.25},
+    {32, 64, 4, 1, 1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {32, 64, 8, 1, 1.92, 0.43, 0.43, 0.125, 0.69, -0.74},
+    {48, 64, 4, 2, 1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {64, 64, 4, 2, 1.38, 0.63, 1.45, 0.132, 0.41, -0.20}};
+
+// LDS of configuration c at most: the wavefronts' rings, and the table.
+inline size_t direct_lds(int c, int K, size_t table_bytes)
+{
+    const DirectTile& t = kDirectTiles[c];
+    const int chain = ((K + 127) / 128 + t.kw - 1) / t.kw;
+    return (size_t)t.kw * (chain < t.depth ? chain : t.depth) * (t.bm + t.bn) * 128 + table_bytes;
+}
+// Whether configuration c exists and its rings and the table fit LDS (16x32 tiles and a table of 4096 segments do not).
+inline bool direct_takes(int c, int K, size_t table_bytes)
+{
+    return c >= 0 && c < (int)(sizeof(kDirectTiles) / sizeof(kDirectTiles[0])) && direct_lds(c, K, table_bytes) <= 160 * 1024;
+}
+
+inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes)
+{
+    int best = 2;
+    double best_us = 0.0;
+    bool any = false;
+    const int nk = (K + 127) / 128;
+    for (int c = 0; c < (int)(sizeof(kDirectTiles) / sizeof(kDirectTiles[0])); ++c) {
+        const auto& t = kDirectTiles[c];
+        const int chain = (nk + t.kw - 1) / t.kw;
+        const size_t lds = direct_lds(c, K, table_bytes);
+        if (!direct_takes(c, K, table_bytes)) continue;
+        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batches, L = (tiles + 255) / 256;
+        const long fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap, R = (L + share - 1) / share;
+        const double us = t.start + L * (t.tile + t.slice * nk) + R * (t.round + t.chain * chain) + t.wave * chain;
+        if (!any || us < best_us) best_us = us, best = c, any = true;
+    }
+    return best;
+}
+
+}  // namespace nm

@@ -18,6 +18,7 @@
 //
 // Operands that are not 16-byte aligned come through registers and buffer descriptors: words past the end
 // of the buffer read as zero, bytes past K are cleared.
+#include "nm_gemm_choice.h"
 #include "nm_gemm_common.h"
 
 namespace nm {
@@ -503,39 +504,7 @@ static int32_t launch_direct_unaligned(GemmParams& p, int align, int batches, si
     return launch_direct_t<BM, BN, KW, 1, 1, false>(p, batches, table_bytes, s);
 }
 
-// Which tile, aligned operands: the one whose predicted time is smallest,
-//   start + L * (tile + slice * slices) + R * (round + chain * c) + wave * c   us,
-// c being the slices of a wavefront, L the workgroups of the CU that has most and R the rounds it takes for them (as many
-// workgroups share a CU as LDS and its 32 wavefronts allow).  The constants are least-squares fits to 285 measured
-// products (16 to 1500 rows, the four products of layers of width 384 to 1024, convolutions of a residual CNN as products;
-// rms 5 to 9 %).  Over those the chosen tile is 0.8 % slower than the best of nine (11 % at worst), the rule by the
-// number of tiles before it 3.0 %.  us, 16x32 | 32x32 | 32x64 with four wavefronts, with eight | 48x64 | 64x64:
-//   128 x 768 x 3072   3.9 | 3.9 | 5.9 | 5.2 | 5.8 | 6.9      847 x  768 x 3072  11.4 | 10.1 | 10.5 | 12.0 | 8.4 | 9.2
-//   512 x 1024 x 4096   10 | 8.9 | 9.8 | 7.7 | 8.4 | 9.4     1024 x 1024 x 1024   6.6 |  6.5 |  6.0 |  7.2 | 7.9 | 5.9
-static int choose_direct(const GemmParams& p, int batches, size_t table_bytes)
-{
-    static const struct { int bm, bn, kw, depth; double start, tile, round, slice, chain, wave; } kTiles[] = {
-        {16, 32, 8, 3, 1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {32, 32, 4, 2, 1.92, 0.08, 0.45, 0.102, 0.14, -0.25},
-        {32, 64, 4, 1, 1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {32, 64, 8, 1, 1.92, 0.43, 0.43, 0.125, 0.69, -0.74},
-        {48, 64, 4, 2, 1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {64, 64, 4, 2, 1.38, 0.63, 1.45, 0.132, 0.41, -0.20}};
-    int best = 2;
-    double best_us = 0.0;
-    bool any = false;
-    const int nk = (p.K + 127) / 128;
-    for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
-        const auto& t = kTiles[c];
-        const int chain = (nk + t.kw - 1) / t.kw;
-        const size_t lds = (size_t)t.kw * (chain < t.depth ? chain : t.depth) * (t.bm + t.bn) * 128 + table_bytes;
-        if (lds > 160 * 1024) continue;
-        const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * batches, L = (tiles + 255) / 256;
-        const long fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap, R = (L + share - 1) / share;
-        const double us = t.start + L * (t.tile + t.slice * nk) + R * (t.round + t.chain * chain) + t.wave * chain;
-        if (!any || us < best_us) best_us = us, best = c, any = true;
-    }
-    return best;
-}
-
-// forced: tile 0 .. 5, or -1 for the rule.  Operands aligned to 4 or 1 bytes pass through registers, a slice at a time: the
+// forced: a configuration that direct_takes, or -1 for the rule.  Operands aligned to 4 or 1 bytes pass through registers, a slice at a time: the
 // smallest tile whose workgroups still fit the chip about once, beyond that the one that reads its operands least often.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s)
 {
@@ -547,7 +516,7 @@ int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t t
         if (t32 <= wide_from) return launch_direct_unaligned<32, 32, 4>(p, align, batches, table_bytes, s);
         return launch_direct_unaligned<32, 64, 4>(p, align, batches, table_bytes, s);
     }
-    switch (forced >= 0 ? forced : choose_direct(p, batches, table_bytes)) {
+    switch (forced >= 0 ? forced : choose_direct(p.M, p.N, p.K, batches, table_bytes)) {
     case 0: return launch_direct_aligned<16, 32, 8, 3>(p, conv, batches, table_bytes, s);
     case 1: return launch_direct_aligned<32, 32, 4, 2>(p, conv, batches, table_bytes, s);
     case 2: return launch_direct_aligned<32, 64, 4, 1>(p, conv, batches, table_bytes, s);

@@ -1,0 +1,81 @@
+// The host-side choices of the GEMM launchers (csrc/nm_gemm_choice.h), compiled alone by tests/test_gemm_choice.py
+// with -fsanitize=address,undefined.
+#include <cstdio>
+#include <cstring>
+#include <initializer_list>
+
+#include "nm_gemm_choice.h"
+
+using namespace nm;
+
+#define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); return 1; } } while (0)
+
+static bool is(const char* value, ForcedKind kind, int number)
+{
+    const ForcedCfg f = parse_forced_cfg(value);
+    return f.kind == kind && f.number == number;
+}
+
+static int forced_values()
+{
+    static const char* const stream[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
+    for (int i = 0; i < 7; ++i) EXPECT(is(stream[i], FORCED_STREAM, i));
+    char name[32];
+    for (int i = 0; i < 100; ++i) {
+        struct { const char* name; ForcedKind kind; bool known; } kinds[] = {
+            {"direct", FORCED_DIRECT, i <= 5}, {"unaligned", FORCED_UNALIGNED, i <= 3}, {"tile", FORCED_TILE, i <= 9},
+            {"relu", FORCED_RELU, i == 2 || (i >= 5 && i <= 11)}};
+        for (const auto& k : kinds) {
+            std::snprintf(name, sizeof(name), "%s%d", k.name, i);
+            EXPECT(k.known ? is(name, k.kind, i) : is(name, FORCED_NONE, -1));
+        }
+    }
+    EXPECT(is(nullptr, FORCED_NONE, -1));
+    for (const char* v : {"", "tile", "tile-1", "tile+1", "tile 1", "tile1x", "tile001", "tile99999999999", "bigger", "mid", "direct", "relu2 ", "Tile1"})
+        EXPECT(is(v, FORCED_NONE, -1));
+    return 0;
+}
+
+// What the kernels assume of a configuration, with the ring depths and slice widths of their instantiations.
+static int requirements()
+{
+    static const int stages[10] = {2, 2, 3, 3, 2, 3, 2, 3, 2, 3};
+    EXPECT(sizeof(kTileConfigs) / sizeof(kTileConfigs[0]) == 10);
+    for (int c = 0; c < 10; ++c) {
+        EXPECT(kTileConfigs[c].stages == stages[c]);
+        for (int slices = 1; slices <= 8; ++slices) EXPECT(tile_takes(c, 128 * slices) == (slices >= stages[c] + 1));
+    }
+    EXPECT(!tile_takes(-1, 4096) && !tile_takes(10, 4096) && !tile_takes(49, 4096));
+    for (int K = 384; K <= 8192; K += 128)
+        for (int M : {1, 77, 847, 1005, 1205, 4096, 16384})
+            for (int N : {16, 400, 768, 1744, 4096})
+                for (int f32 = 0; f32 < 2; ++f32)
+                    for (unsigned allowed : {~0u, 0x1e4u}) {
+                        const int c = choose_tile(M, N, K, f32 != 0, false, allowed);
+                        EXPECT(c >= 0 && (allowed >> c & 1) && tile_takes(c, K));
+                    }
+    for (int c = 0; c < 12; ++c) {   // a contraction of 64 (2 n + 1) bytes has no whole slices of 128
+        EXPECT(relu_takes(c, 128) && relu_takes(c, 1024));
+        EXPECT(relu_takes(c, 64) == (c == 9 || c == 10) && relu_takes(c, 192) == (c == 9 || c == 10));
+    }
+    for (int c = 0; c < 7; ++c) {
+        const bool big = c == STREAM_BIG || c == STREAM_OLDBIG, split = c == STREAM_SPLIT || c == STREAM_SMALL;
+        EXPECT(stream_takes(c, false, true, true) && stream_takes(c, true, true, true) == !big);
+        EXPECT(stream_takes(c, false, false, false) == (!big && !split) && stream_takes(c, false, true, false) == !split);
+    }
+    for (int K : {16, 128, 200, 1024, 3072, 65536})
+        for (size_t table : {size_t(0), size_t(16), size_t(16384), size_t(16392), size_t(32768)}) {
+            for (int c = 0; c < 6; ++c) EXPECT(direct_takes(c, K, table) == (direct_lds(c, K, table) <= 160 * 1024));
+            EXPECT(direct_takes(0, K, table) == (K < 3072 || table <= 16384));   // 24 slices in rings of three
+            for (int M : {1, 100, 1500}) EXPECT(direct_takes(choose_direct(M, 512, K, 1, table), K, table));
+        }
+    EXPECT(!direct_takes(-1, 128, 0) && !direct_takes(6, 128, 0));
+    return 0;
+}
+
+int main()
+{
+    if (forced_values() || requirements()) return 1;
+    std::printf("SANITIZE_OK\n");
+    return 0;
+}

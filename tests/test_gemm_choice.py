@@ -1,0 +1,55 @@
+"""The choices that the GEMM launchers make on the host (csrc/nm_gemm_choice.h): the values of the debug switch
+NM_GEMM_CFG and what each configuration requires of a product, in a C++ driver of its own (CPU); and products under a
+forced configuration whose requirements they do not meet, against the oracle (GPU)."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from test_sanitizers import SAN, _run
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_gemm_choices_on_the_host(tmp_path):
+    exe = str(tmp_path / "choice_driver")
+    _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
+
+
+# A program of its own: the switch is read once per process.
+PRODUCT = """
+import sys, numpy as np, torch
+from oracle import oracle as O
+from paper_2305_14405_amd import binding as nm
+M, N, K, nseg, per_column = (int(v) for v in sys.argv[1:])
+g = np.random.default_rng(M + N + K)
+A, W = (g.integers(-127, 128, s, dtype=np.int64).astype(np.int8) for s in ((M, K), (N, K)))
+bias = g.standard_normal(N).astype(np.float32)
+alpha = np.full(N, 3.0 / (70 * 70 * np.sqrt(K)), np.float32) * (1 + g.random(N)).astype(np.float32) if per_column else None
+scale = float(np.float32(3.0 / (70 * 70 * np.sqrt(K))))
+dev = lambda a: None if a is None else torch.from_numpy(a).to("cuda:0")
+ot = O.build_table(O.F_GELU, -8.0, 8.0, nseg) if nseg else None
+dt = nm.nm_tables_from_arrays([("gelu", -8.0, 8.0, nseg, 0)], [ot.k], [ot.b]) if nseg else None
+q = torch.full((M, N), 77, dtype=torch.int8, device="cuda:0")
+args = [dev(A), dev(W), dev(bias), dev(alpha)]
+nm.nm_gemm_pwl(args[0], args[1], bias=args[2], alpha=scale, alpha_vec=args[3], tables=dt, table_idx=0 if nseg else -1, out_inv_scale=30.0, out_q=q)
+torch.cuda.synchronize()
+want = O.gemm_pwl(A, W, bias=bias, alpha=scale, alpha_vec=alpha, table=ot, out_inv_scale=30.0)
+assert np.array_equal(q.cpu().numpy(), want["q"])
+print("PRODUCT_OK")
+"""
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,M,N,K,nseg,per_column", [
+    ("tile3", 1500, 768, 384, 0, 0),      # three slices, a ring of three stages: one slice too few
+    ("relu11", 1200, 912, 192, 0, 1),     # slices of 128 bytes, one and a half of them
+    ("direct0", 64, 128, 3072, 4096, 0),  # rings and table together beyond LDS
+    ("tile3", 1500, 768, 512, 64, 0)])    # one that the configuration does take
+def test_forced_configuration_keeps_results(cfg, M, N, K, nseg, per_column):
+    run = subprocess.run([sys.executable, "-c", PRODUCT, *map(str, (M, N, K, nseg, per_column))], capture_output=True, text=True, cwd=ROOT,
+                         env=dict(os.environ, NM_GEMM_CFG=cfg, PYTHONPATH=ROOT), timeout=100)
+    assert run.returncode == 0 and "PRODUCT_OK" in run.stdout, (run.stdout[-1000:], run.stderr[-3000:])
