@@ -27,7 +27,6 @@
 // addition is exact, so results do not depend on tiling, on the k order or on any split of K.
 #include <cstdlib>
 
-#include "nm_gemm_choice.h"
 #include "nm_gemm_common.h"
 #include "nm_gemm_tile.h"
 

@@ -157,4 +157,36 @@ inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes)
     return best;
 }
 
+// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
+// x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
+// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this
+// sum smallest, counting the rows and columns that an eighth straddles where r x c tiles are not exactly one.  (Operand
+// stream of 128x128 tiles of 4096 x 768 x 3072 alone: 20.5 TB/s with 4 x 6 tiles to an XCD, 11.5 with 24 x 1.)
+// It is host work of every launch: of the r whose groups an eighth holds whole, r = 1 reads fewest rows, and r beyond the
+// best sum's rows cannot be better.  Every r up to an eighth of the tiles took 1.7 us at 1568 x 2 tiles and 25 at 12544 x 4;
+// these few take less than 0.02 (a launch takes 3.1).
+inline int xcd_group_rows(int tiles_m, int tiles_n, int BM, int BN)
+{
+    const int ntiles = tiles_m * tiles_n, share = (ntiles + 7) / 8, whole = share / tiles_n;
+    int best = 1;
+    long best_cost = -1;
+    for (int r = 1; r <= tiles_m && r <= share; r = r == 1 && whole > 1 ? whole + 1 : r + 1) {
+        if (best_cost >= 0 && (long)r * BM + BN >= best_cost) break;
+        long rows, cols;
+        if (r <= whole) {   // whole groups (r = 1)
+            rows = share % tiles_n == 0 ? whole : whole + 2;
+            cols = tiles_n;
+        } else {
+            const bool exact = ntiles % 8 == 0 && share % r == 0 && tiles_n % (share / r) == 0 && tiles_m % r == 0;
+            rows = exact ? r : r + r / 2;
+            cols = exact ? share / r : share / r + 1;
+        }
+        if (rows > tiles_m) rows = tiles_m;
+        if (cols > tiles_n) cols = tiles_n;
+        const long cost = rows * BM + cols * BN;
+        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = r;
+    }
+    return best;
+}
+
 }  // namespace nm

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "nm_device.h"
+#include "nm_gemm_choice.h"
 
 namespace nm {
 
@@ -66,35 +67,6 @@ int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t t
 
 // The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).
 int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s);
-
-// Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
-// x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
-// eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this
-// sum smallest, counting the rows and columns that an eighth straddles where r x c tiles are not exactly one.  (Operand
-// stream of 128x128 tiles of 4096 x 768 x 3072 alone: 20.5 TB/s with 4 x 6 tiles to an XCD, 11.5 with 24 x 1.)
-static inline int xcd_group_rows(int tiles_m, int tiles_n, int BM, int BN)
-{
-    const int ntiles = tiles_m * tiles_n, share = (ntiles + 7) / 8;
-    int best = 1;
-    long best_cost = -1;
-    for (int r = 1; r <= tiles_m && r <= share; ++r) {
-        long rows, cols;
-        if (share >= r * tiles_n) {   // whole groups
-            const int groups = (share + r * tiles_n - 1) / (r * tiles_n);
-            rows = (long)r * (share % (r * tiles_n) == 0 ? groups : groups + 1);
-            cols = tiles_n;
-        } else {
-            const bool exact = ntiles % 8 == 0 && share % r == 0 && tiles_n % (share / r) == 0 && tiles_m % r == 0;
-            rows = exact ? r : r + r / 2;
-            cols = exact ? share / r : share / r + 1;
-        }
-        if (rows > tiles_m) rows = tiles_m;
-        if (cols > tiles_n) cols = tiles_n;
-        const long cost = rows * BM + cols * BN;
-        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = r;
-    }
-    return best;
-}
 
 // XOR swizzle of the 16-byte chunk index inside a 64-byte LDS row: rows that fall into the same
 // bank window get different chunk positions, for both a 128-byte and a 256-byte wide LDS port.

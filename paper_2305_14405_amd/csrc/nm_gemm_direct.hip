@@ -18,7 +18,6 @@
 //
 // Operands that are not 16-byte aligned come through registers and buffer descriptors: words past the end
 // of the buffer read as zero, bytes past K are cleared.
-#include "nm_gemm_choice.h"
 #include "nm_gemm_common.h"
 
 namespace nm {
