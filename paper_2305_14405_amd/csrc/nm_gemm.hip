@@ -889,7 +889,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                      : forced.kind == FORCED_DIRECT ? direct_ok && direct_takes(forced.number, g.K, table_bytes)
                      : forced.kind == FORCED_UNALIGNED ? unaligned_ok
                      : forced.kind == FORCED_RELU ? relu_ok && relu_takes(forced.number, kunit)
-                     : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K) : false;
+                     : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K, epi == EPI_F32_RESID) : false;
     if (!holds) forced = ForcedCfg();
     const bool free_choice = forced.kind == FORCED_NONE;
     if (forced.kind == FORCED_UNALIGNED || (free_choice && unaligned_ok && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000)) {
@@ -954,7 +954,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     } else if (tile_cfg == 4) {
         rc = launch_tile<128, 192, 2, 2, 2>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 5) {
-        rc = launch_tile<128, 128, 2, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 128, 2, 2, 3, OUT_INT8>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 6) {
         rc = launch_tile<128, 128, 2, 2, 2>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 7) {
@@ -962,7 +962,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     } else if (tile_cfg == 8) {
         rc = launch_tile<64, 128, 2, 2, 2>(p, epi, table_bytes, stream);
     } else if (tile_cfg == 9) {
-        rc = launch_tile<128, 128, 2, 2, 3, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

@@ -69,7 +69,8 @@ constexpr bool relu_takes(int c, int kunit) { return c == 9 || c == 10 || kunit 
 //   12000 x 3072 x  768, table:  52 | 51 | 58 | 59 | 43 | 58 | 47
 //    4096 x  768 x 3072, fp32:   34 | 29 | 21 | 19 | 23 | 17 | 21 | 18 | 19
 //    2048 x  768 x 3072, fp32:   33 | 26 | 20 | 17 | 17 | 15 | 15 | 10 | 11
-// allowed: a bit per configuration.
+// An epilogue's constant of 0 says that the configuration is not built for it: fp32 results take 128x128 with three stages in the
+// last entry's form alone, int8 ones in the first.  allowed: a bit per configuration.
 struct TileConfig {
     int bm, bn, stages, places, least;
     double alone, paired, alone_epi, start, slice, f32, q, table;
@@ -77,15 +78,16 @@ struct TileConfig {
 constexpr TileConfig kTileConfigs[] = {
     {256, 256, 2, 256, 0, 1, 1, 1, -1.88, 1.15, 11.73, 7.67, 11.42}, {256, 192, 2, 256, 0, 1, 1, 1, -2.43, 0.89, 10.88, 7.70, 9.41},
     {256, 128, 3, 256, 0, 1, 1, 1, -0.71, 0.68, 8.25, 4.37, 6.47},   {128, 192, 3, 256, 0, 1, 1, 1, 0.08, 0.54, 7.35, 4.55, 5.87},
-    {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 5.92, 2.75, 3.90},
+    {128, 192, 2, 512, 257, 0.65, 1, 0.65, 0.94, 1.10, 9.88, 5.25, 6.32}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.44, 0, 2.75, 3.90},
     {128, 128, 2, 512, 257, 0.65, 1, 0.65, 0.48, 0.87, 8.91, 2.98, 4.47}, {64, 128, 3, 512, 0, 0.45, 1, 0.8, 1.19, 0.52, 3.52, 2.23, 3.00},
     {64, 128, 2, 768, 513, 0.5, 0.7, 0.5, 1.27, 0.80, 5.53, 2.23, 3.44}, {128, 128, 3, 256, 0, 1, 1, 1, 0.21, 0.385, 6.7, 0, 0}};
 
-// Whether the tile kernel's configuration c takes a contraction of K bytes: its k-loop is a first slice, the steady state
-// and the last slices, so it needs one slice more than its ring has stages.
-constexpr bool tile_takes(int c, int K)
+// Whether the tile kernel's configuration c is built for such results (fp32 or int8) and takes a contraction of K bytes: its
+// k-loop is a first slice, the steady state and the last slices, so it needs one slice more than its ring has stages.
+constexpr bool tile_takes(int c, int K, bool f32)
 {
-    return c >= 0 && c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])) && K / 128 >= kTileConfigs[c].stages + 1;
+    return c >= 0 && c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])) && K / 128 >= kTileConfigs[c].stages + 1 &&
+           (f32 ? kTileConfigs[c].f32 : kTileConfigs[c].q) != 0;
 }
 
 inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allowed = ~0u)
@@ -95,8 +97,7 @@ inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allow
     for (int c = 0; c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])); ++c) {
         const auto& t = kTileConfigs[c];
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
-        if (c == 5 ? f32 : c == 9 && !f32) continue;
-        if (!(allowed >> c & 1) || !tile_takes(c, K) || (tiles < t.least && K / 128 > 3)) continue;
+        if (!(allowed >> c & 1) || !tile_takes(c, K, f32) || (tiles < t.least && K / 128 > 3)) continue;
         const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
         const double full = (double)(tiles / t.places);
         const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);

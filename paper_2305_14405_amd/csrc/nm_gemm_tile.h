@@ -711,15 +711,20 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
     return NM_OK;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KSPLIT = 1>
+// The epilogues a configuration is built for (kTileConfigs).
+enum TileOutputs { OUT_ANY, OUT_INT8, OUT_F32 };
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, TileOutputs kOut = OUT_ANY, int KSPLIT = 1>
 static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
 {
-    switch (epi) {
-    case EPI_Q: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT>(p, table_bytes, s);
-    case EPI_Q_TABLE: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT>(p, table_bytes, s);
-    case EPI_Q_TABLE2: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2, 128, false, KSPLIT>(p, table_bytes, s);
-    default: return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT>(p, table_bytes, s);
+    if constexpr (kOut != OUT_F32) {
+        if (epi == EPI_Q) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT>(p, table_bytes, s);
+        if (epi == EPI_Q_TABLE) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT>(p, table_bytes, s);
+        if (epi == EPI_Q_TABLE2) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2, 128, false, KSPLIT>(p, table_bytes, s);
     }
+    if constexpr (kOut != OUT_INT8) {
+        if (epi == EPI_F32_RESID) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT>(p, table_bytes, s);
+    }
+    return fail(NM_ERR_UNSUPPORTED, "gemm: tile configuration not built for this epilogue");
 }
 
 // Convolutions, as products or with gathered rows.  us, streaming kernel -> this one with 128-byte slices: 12544 x 256 x 2304

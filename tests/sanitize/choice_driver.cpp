@@ -44,16 +44,19 @@ static int requirements()
     EXPECT(sizeof(kTileConfigs) / sizeof(kTileConfigs[0]) == 10);
     for (int c = 0; c < 10; ++c) {
         EXPECT(kTileConfigs[c].stages == stages[c]);
-        for (int slices = 1; slices <= 8; ++slices) EXPECT(tile_takes(c, 128 * slices) == (slices >= stages[c] + 1));
+        for (int slices = 1; slices <= 8; ++slices) {   // 5: int8 alone, 9: fp32 alone
+            EXPECT(tile_takes(c, 128 * slices, false) == (slices >= stages[c] + 1 && c != 9));
+            EXPECT(tile_takes(c, 128 * slices, true) == (slices >= stages[c] + 1 && c != 5));
+        }
     }
-    EXPECT(!tile_takes(-1, 4096) && !tile_takes(10, 4096) && !tile_takes(49, 4096));
+    for (int f32 = 0; f32 < 2; ++f32) EXPECT(!tile_takes(-1, 4096, f32) && !tile_takes(10, 4096, f32) && !tile_takes(49, 4096, f32));
     for (int K = 384; K <= 8192; K += 128)
         for (int M : {1, 77, 847, 1005, 1205, 4096, 16384})
             for (int N : {16, 400, 768, 1744, 4096})
                 for (int f32 = 0; f32 < 2; ++f32)
                     for (unsigned allowed : {~0u, 0x1e4u}) {
                         const int c = choose_tile(M, N, K, f32 != 0, false, allowed);
-                        EXPECT(c >= 0 && (allowed >> c & 1) && tile_takes(c, K));
+                        EXPECT(c >= 0 && (allowed >> c & 1) && tile_takes(c, K, f32 != 0));
                     }
     for (int c = 0; c < 12; ++c) {   // a contraction of 64 (2 n + 1) bytes has no whole slices of 128
         EXPECT(relu_takes(c, 128) && relu_takes(c, 1024));
