@@ -13,10 +13,10 @@
 // only has G non-zero accumulators; adding the +0 of an empty accumulator changes nothing, so a
 // butterfly over the G lanes that own the row gives the same bits.
 #include "nm_device.h"
+#include "nm_rows_choice.h"
 
 namespace nm {
 
-constexpr int kRowThreads = 256;
 constexpr int kApplyGroupsPerTrip = 8;  // pwl_apply: 16-byte groups a lane loads per trip
 
 // ------------------------------------------------------------------------------------------
@@ -625,9 +625,8 @@ int32_t launch_layernorm2(const float* in, const float* gamma, const float* beta
     const float inv_L = (float)(1.0 / (double)cols);
     const bool vec = cols % 4 == 0 && aligned(in, 16) && aligned(gamma, 16) && aligned(beta, 16) &&
                      (!out_f32 || aligned(out_f32, 16)) && (!out_q || aligned(out_q, 4));
-    if (vec && !two && !seg && !seg2 && cols % 256 == 0 && cols <= 1024 && t.nseg <= 256 && rows < (1LL << 31) - 4) {
-        constexpr int rpb = kRowThreads / 64;
-        const dim3 grid((unsigned)((rows + rpb - 1) / rpb));
+    if (vec && !two && !seg && !seg2 && layernorm_row_takes(rows, cols, t.nseg)) {
+        const dim3 grid((unsigned)layernorm_row_blocks(rows));
         auto launch = [&](auto kern) {
             queue_kernel(kern, grid, dim3(kRowThreads), 0, stream, in, gamma, beta, t.kb, out_q, out_f32, (int)rows, t.nseg, t.lo, t.hi,
                                t.inv_w, t.clamp_input, eps, inv_L, out_inv_scale);

@@ -1,11 +1,12 @@
-// The host-side choices of the GEMM launchers (csrc/nm_gemm_choice.h), compiled alone by tests/test_gemm_choice.py
-// with -fsanitize=address,undefined.
+// The host-side choices of the launchers (csrc/nm_gemm_choice.h, csrc/nm_rows_choice.h), compiled alone by
+// tests/test_gemm_choice.py with -fsanitize=address,undefined.
 #include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <initializer_list>
 
 #include "nm_gemm_choice.h"
+#include "nm_rows_choice.h"
 
 using namespace nm;
 
@@ -119,9 +120,22 @@ static int group_rows()
     return 0;
 }
 
+// A launch has less than 2^32 work-items, and four rows take 256.
+static int layernorm_rows()
+{
+    const long edge = (1L << 26) - 4;   // the last number of rows whose launch is one
+    for (long rows : {1L, 3L, 4L, 5L, 67L, 98304L, edge - 1, edge}) EXPECT(layernorm_row_takes(rows, 256, 128));
+    for (long rows : {edge + 1, edge + 4, 1L << 27, (1L << 31) - 5, 1L << 32, 1L << 40}) EXPECT(!layernorm_row_takes(rows, 256, 128));
+    for (long rows = 1; rows < 1L << 40; rows = rows * 5 / 4 + 1)
+        if (layernorm_row_takes(rows, 1024, 256)) EXPECT(layernorm_row_blocks(rows) * 256 < 1L << 32 && layernorm_row_blocks(rows) * 4 >= rows);
+    for (int cols : {1, 128, 255, 300, 1280, 4096}) EXPECT(!layernorm_row_takes(4, cols, 128));
+    EXPECT(!layernorm_row_takes(4, 256, 257) && !layernorm_row_takes(0, 256, 128));
+    return 0;
+}
+
 int main()
 {
-    if (forced_values() || requirements() || group_rows()) return 1;
+    if (forced_values() || requirements() || group_rows() || layernorm_rows()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;
 }

@@ -1,6 +1,7 @@
-"""The choices that the GEMM launchers make on the host (csrc/nm_gemm_choice.h): the values of the debug switch
-NM_GEMM_CFG and what each configuration requires of a product, in a C++ driver of its own (CPU); and products under a
-forced configuration whose requirements they do not meet, against the oracle (GPU)."""
+"""The choices that the launchers make on the host (csrc/nm_gemm_choice.h, csrc/nm_rows_choice.h): the values of the debug
+switch NM_GEMM_CFG and what each configuration requires of a product, and the rows that one launch of the LayerNorm kernel
+can hold, in a C++ driver of its own (CPU); and products under a forced configuration whose requirements they do not meet,
+against the oracle (GPU)."""
 import os
 import shutil
 import subprocess
@@ -14,7 +15,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
-def test_gemm_choices_on_the_host(tmp_path):
+def test_choices_on_the_host(tmp_path):
     exe = str(tmp_path / "choice_driver")
     _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
 
