@@ -50,7 +50,8 @@ CASES = [  # B, H, W, Cin, Cout, kh, kw, stride, pad   (route)
 
 @pytest.mark.parametrize("B,H,W,Cin,Cout,kh,kw,stride,pad", [
     (1, 1, 1, 3, 16, 3, 3, 1, 1), (1, 1, 2, 2, 16, 3, 3, 1, 1), (2, 33, 35, 3, 64, 7, 7, 2, 3), (1, 17, 16, 4, 48, 3, 8, 1, 0),
-    (3, 50, 61, 1, 16, 4, 5, 4, 2), (1, 40, 19, 2, 32, 9, 2, 3, 5), (2, 5, 5, 3, 64, 1, 3, 2, 0)])
+    (3, 50, 61, 1, 16, 4, 5, 4, 2), (1, 40, 19, 2, 32, 9, 2, 3, 5), (2, 5, 5, 3, 64, 1, 3, 2, 0),
+    (2, 70, 150, 3, 64, 4, 8, 4, 2), (3, 19, 68, 4, 16, 2, 8, 4, 0), (1, 68, 65, 1, 32, 4, 6, 4, 1)])   # stride 4: patches of 68 columns
 @pytest.mark.parametrize("table", ["relu", None])
 def test_conv2d_few_channels_int8_output(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad, table):
     """The kernel for at most four input channels: the word that holds the tensor's last pixel, images smaller
