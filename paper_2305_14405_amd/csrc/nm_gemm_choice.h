@@ -141,6 +141,10 @@ inline bool direct_takes(int c, int K, size_t table_bytes)
 
 inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes)
 {
+    // Many products of a short contraction (attention scores; the fit has none): 32x32 tiles, 16x32 where those are few.  us, 16x32 |
+    // 32x32 | 32x64 with four wavefronts: 270 of 58 x 58 x 64 10.0 | 8.5 | 13.1, 384 of 40 x 40 x 64 11.0 | 8.6 | 12.0, 2 of
+    // 16 x 16 x 16 2.8 | 2.9 | 3.3; from 640 on the fit holds again (270 of 58 x 58 x 640 14.0 | 17.2 | 22.7).
+    if (batches > 1 && K <= 512) return (long)((M + 31) / 32) * ((N + 31) / 32) * batches <= 128 ? 0 : 1;
     int best = 2;
     double best_us = 0.0;
     bool any = false;

@@ -75,6 +75,10 @@ static int requirements()
             for (int M : {1, 100, 1500}) EXPECT(direct_takes(choose_direct(M, 512, K, 1, table), K, table));
         }
     EXPECT(!direct_takes(-1, 128, 0) && !direct_takes(6, 128, 0));
+    for (int K : {16, 64, 80, 256, 512}) {   // attention scores: many small products
+        EXPECT(choose_direct(58, 58, K, 270, 0) == 1 && choose_direct(40, 40, K, 384, 0) == 1 && choose_direct(10, 10, K, 168, 0) == 1);
+        EXPECT(choose_direct(16, 16, K, 8, 0) == 0 && choose_direct(500, 500, K, 4, 0) == 1);
+    }
     return 0;
 }
 
