@@ -167,7 +167,7 @@ void nm_tables_destroy(nm_tables* t);
  * other shape is computed by a slower loader with identical results.
  * Debug switches (environment, read once per process; results never change, only the kernel that
  * computes them): NM_GEMM_GENERIC=1 sends every product whose operand is not gathered from an image to the
- * generic kernel; NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-5>|unaligned<0-3>|relu<2,5-11>|
+ * generic kernel; NM_GEMM_CFG=big|wide|split|small|mid3|mid2|oldbig|direct<0-6>|unaligned<0-3>|relu<2,5-11>|
  * tile<0-9> forces a kernel and its tile configuration where that one's requirements hold (anywhere else, and
  * where the value is not one of these, the rules choose as without it); NM_ATTN_UNFUSED=1 keeps
  * nm_encoder_layer's attention on the three separate kernels.

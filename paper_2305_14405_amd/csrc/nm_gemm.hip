@@ -886,7 +886,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // the debug switch's configuration, if this product meets its requirements
     ForcedCfg forced = forced_cfg();
     const bool holds = forced.kind == FORCED_STREAM ? g.N > 64 && (g.conv || stream_ok) && stream_takes(forced.number, g.conv != 0, k128, split_ok)
-                     : forced.kind == FORCED_DIRECT ? direct_ok && direct_takes(forced.number, g.K, table_bytes)
+                     : forced.kind == FORCED_DIRECT ? direct_ok && direct_takes(forced.number, g.K, table_bytes, g.conv != 0)
                      : forced.kind == FORCED_UNALIGNED ? unaligned_ok
                      : forced.kind == FORCED_RELU ? relu_ok && relu_takes(forced.number, kunit)
                      : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K, epi == EPI_F32_RESID) : false;

@@ -11,7 +11,7 @@ namespace nm {
 // configuration's requirements; anywhere else, and where the value is not one of these, the rules decide.
 //   big|wide|split|small|mid3|mid2|oldbig   streaming kernel (big: the tile kernel's 256x192 where that one takes the product,
 //                                           which has replaced the streaming kernel's, oldbig)
-//   direct<0-5>  unaligned<0-3>  tile<0-9>  small-tile, register-staged and tile kernel
+//   direct<0-6>  unaligned<0-3>  tile<0-9>  small-tile, register-staged and tile kernel
 //   relu<2,5-11>                            tile kernel with the epilogues of convolutions
 enum ForcedKind { FORCED_NONE, FORCED_STREAM, FORCED_DIRECT, FORCED_UNALIGNED, FORCED_RELU, FORCED_TILE };
 enum { STREAM_BIG, STREAM_WIDE, STREAM_SPLIT, STREAM_SMALL, STREAM_MID3, STREAM_MID2, STREAM_OLDBIG };
@@ -24,7 +24,7 @@ inline ForcedCfg parse_forced_cfg(const char* e)
 {
     static const char* const stream[] = {"big", "wide", "split", "small", "mid3", "mid2", "oldbig"};
     static const struct { const char* name; ForcedKind kind; unsigned numbers; } numbered[] = {
-        {"direct", FORCED_DIRECT, 0x3f}, {"unaligned", FORCED_UNALIGNED, 0xf}, {"tile", FORCED_TILE, 0x3ff}, {"relu", FORCED_RELU, 0xfe4}};
+        {"direct", FORCED_DIRECT, 0x7f}, {"unaligned", FORCED_UNALIGNED, 0xf}, {"tile", FORCED_TILE, 0x3ff}, {"relu", FORCED_RELU, 0xfe4}};
     ForcedCfg f;
     if (!e) return f;
     for (int i = 0; i < 7; ++i)
@@ -117,14 +117,27 @@ inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allow
 // number of tiles before it 3.0 %.  us, 16x32 | 32x32 | 32x64 with four wavefronts, with eight | 48x64 | 64x64:
 //   128 x 768 x 3072   3.9 | 3.9 | 5.9 | 5.2 | 5.8 | 6.9      847 x  768 x 3072  11.4 | 10.1 | 10.5 | 12.0 | 8.4 | 9.2
 //   512 x 1024 x 4096   10 | 8.9 | 9.8 | 7.7 | 8.4 | 9.4     1024 x 1024 x 1024   6.6 |  6.5 |  6.0 |  7.2 | 7.9 | 5.9
-struct DirectTile {
-    int bm, bn, kw, depth;
+// Rows gathered from an image cost other things (addresses and tap masks in every slice), and with those constants long filters
+// took 1.1 to 1.6 times as long as the rule by the number of tiles: they have their own, fitted to 710 convolutions (filters of 1 to
+// 7, 64 to 1024 channels, 49 to 9408 positions, each epilogue; rms 7 to 11 %), and 32x32 tiles with eight wavefronts.  Chosen over
+// best of seven 0.6 % (16 % at worst).  us, by the other constants -> by these: 1575 x 128 x 25088 (7x7) 26.8 -> 17.0, 972 x 200 x
+// 12800 (5x5) 15.5 -> 10.8, 972 x 200 x 9216 (3x3) 11.9 -> 9.3, 3136 x 256 x 25600 (5x5) 47.0 -> 43.9.
+struct DirectCost {
     double start, tile, round, slice, chain, wave;
 };
+struct DirectTile {
+    int bm, bn, kw, depth;
+    DirectCost plain, gathered;   // a start of 0: not built
+};
 constexpr DirectTile kDirectTiles[] = {
-    {16, 32, 8, 3, 1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {32, 32, 4, 2, 1.92, 0.08, 0.45, 0.102, 0.14, -0.25},
-    {32, 64, 4, 1, 1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {32, 64, 8, 1, 1.92, 0.43, 0.43, 0.125, 0.69, -0.74},
-    {48, 64, 4, 2, 1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {64, 64, 4, 2, 1.38, 0.63, 1.45, 0.132, 0.41, -0.20}};
+    {16, 32, 8, 3, {1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {1.481, 0, 1.594, 0.039, 0.134, -0.002}},
+    {32, 32, 4, 2, {1.92, 0.08, 0.45, 0.102, 0.14, -0.25}, {1.271, 0.288, 1.332, 0.029, 0.265, 0.098}},
+    {32, 64, 4, 1, {1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {1.427, 0.43, 1.427, 0.041, 0.266, 0.266}},
+    {32, 64, 8, 1, {1.92, 0.43, 0.43, 0.125, 0.69, -0.74}, {2.368, 0.597, 0.597, 0.112, 0.055, -0.17}},
+    {48, 64, 4, 2, {1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {1.172, 0.117, 2.693, 0.086, 0.302, 0.033}},
+    {64, 64, 4, 2, {1.38, 0.63, 1.45, 0.132, 0.41, -0.20}, {1.485, 1.485, 1.485, 0.098, 0.231, 0.231}},
+    {32, 32, 8, 2, {0, 0, 0, 0, 0, 0}, {1.268, 0.055, 1.953, 0.064, 0.045, 0.011}}};
+constexpr int kDirectTileCount = sizeof(kDirectTiles) / sizeof(kDirectTiles[0]);
 
 // LDS of configuration c at most: the wavefronts' rings, and the table.
 inline size_t direct_lds(int c, int K, size_t table_bytes)
@@ -133,13 +146,14 @@ inline size_t direct_lds(int c, int K, size_t table_bytes)
     const int chain = ((K + 127) / 128 + t.kw - 1) / t.kw;
     return (size_t)t.kw * (chain < t.depth ? chain : t.depth) * (t.bm + t.bn) * 128 + table_bytes;
 }
-// Whether configuration c exists and its rings and the table fit LDS (16x32 tiles and a table of 4096 segments do not).
-inline bool direct_takes(int c, int K, size_t table_bytes)
+constexpr const DirectCost& direct_cost(int c, bool gathered) { return gathered ? kDirectTiles[c].gathered : kDirectTiles[c].plain; }
+// Whether configuration c exists for such rows and its rings and the table fit LDS (16x32 tiles and a table of 4096 segments do not).
+inline bool direct_takes(int c, int K, size_t table_bytes, bool gathered)
 {
-    return c >= 0 && c < (int)(sizeof(kDirectTiles) / sizeof(kDirectTiles[0])) && direct_lds(c, K, table_bytes) <= 160 * 1024;
+    return c >= 0 && c < kDirectTileCount && direct_cost(c, gathered).start > 0 && direct_lds(c, K, table_bytes) <= 160 * 1024;
 }
 
-inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes)
+inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes, bool gathered)
 {
     // Many products of a short contraction (attention scores; the fit has none): 32x32 tiles, 16x32 where those are few.  us, 16x32 |
     // 32x32 | 32x64 with four wavefronts: 270 of 58 x 58 x 64 10.0 | 8.5 | 13.1, 384 of 40 x 40 x 64 11.0 | 8.6 | 12.0, 2 of
@@ -149,14 +163,15 @@ inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes)
     double best_us = 0.0;
     bool any = false;
     const int nk = (K + 127) / 128;
-    for (int c = 0; c < (int)(sizeof(kDirectTiles) / sizeof(kDirectTiles[0])); ++c) {
-        const auto& t = kDirectTiles[c];
+    for (int c = 0; c < kDirectTileCount; ++c) {
+        if (!direct_takes(c, K, table_bytes, gathered)) continue;
+        const DirectTile& t = kDirectTiles[c];
+        const DirectCost& u = direct_cost(c, gathered);
         const int chain = (nk + t.kw - 1) / t.kw;
         const size_t lds = direct_lds(c, K, table_bytes);
-        if (!direct_takes(c, K, table_bytes)) continue;
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batches, L = (tiles + 255) / 256;
         const long fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap, R = (L + share - 1) / share;
-        const double us = t.start + L * (t.tile + t.slice * nk) + R * (t.round + t.chain * chain) + t.wave * chain;
+        const double us = u.start + L * (u.tile + u.slice * nk) + R * (u.round + u.chain * chain) + u.wave * chain;
         if (!any || us < best_us) best_us = us, best = c, any = true;
     }
     return best;

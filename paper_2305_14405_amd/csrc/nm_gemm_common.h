@@ -62,7 +62,7 @@ struct GemmLnParams : GemmParams {
 };
 
 // The small-tile kernel (nm_gemm_direct.hip).  align: alignment of operand rows and chunks in bytes (16, 4 or
-// 1); forced: tile configuration 0 .. 5, or -1 for the rule.
+// 1); forced: tile configuration 0 .. 6, or -1 for the rule.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s);
 
 // The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).

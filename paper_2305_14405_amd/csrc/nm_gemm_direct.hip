@@ -479,15 +479,20 @@ static int lean_epilogue(const GemmParams& p, bool conv, int batches)
 }
 
 template <int BM, int BN, int KW, int D>
+static int32_t launch_direct_conv(GemmParams& p, int batches, size_t table_bytes, hipStream_t s)
+{
+    const int epi = lean_epilogue(p, true, batches);
+    if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q>(p, batches, 0, s);
+    if (epi == EPI_Q_TABLE && p.table.two_seg) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q_TABLE, FORM_TWO_SEGMENTS>(p, batches, 0, s);
+    return launch_direct_t<BM, BN, KW, D, 16, true>(p, batches, table_bytes, s);
+}
+
+template <int BM, int BN, int KW, int D>
 static int32_t launch_direct_aligned(GemmParams& p, bool conv, int batches, size_t table_bytes, hipStream_t s)
 {
-    const int epi = lean_epilogue(p, conv, batches);
+    if (conv) return launch_direct_conv<BM, BN, KW, D>(p, batches, table_bytes, s);
+    const int epi = lean_epilogue(p, false, batches);
     const bool two = p.has_table && p.table.two_seg;
-    if (conv) {
-        if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q>(p, batches, 0, s);
-        if (epi == EPI_Q_TABLE && two) return launch_direct_t<BM, BN, KW, D, 16, true, EPI_Q_TABLE, FORM_TWO_SEGMENTS>(p, batches, 0, s);
-        return launch_direct_t<BM, BN, KW, D, 16, true>(p, batches, table_bytes, s);
-    }
     if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q>(p, batches, 0, s);
     if (epi == EPI_F32_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_F32_RESID>(p, batches, 0, s);
     if (epi == EPI_Q_TABLE_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE_RESID, FORM_TWO_SEGMENTS>(p, batches, 0, s);
@@ -515,12 +520,13 @@ int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t t
         if (t32 <= wide_from) return launch_direct_unaligned<32, 32, 4>(p, align, batches, table_bytes, s);
         return launch_direct_unaligned<32, 64, 4>(p, align, batches, table_bytes, s);
     }
-    switch (forced >= 0 ? forced : choose_direct(p.M, p.N, p.K, batches, table_bytes)) {
+    switch (forced >= 0 ? forced : choose_direct(p.M, p.N, p.K, batches, table_bytes, conv)) {
     case 0: return launch_direct_aligned<16, 32, 8, 3>(p, conv, batches, table_bytes, s);
     case 1: return launch_direct_aligned<32, 32, 4, 2>(p, conv, batches, table_bytes, s);
     case 2: return launch_direct_aligned<32, 64, 4, 1>(p, conv, batches, table_bytes, s);
     case 3: return launch_direct_aligned<32, 64, 8, 1>(p, conv, batches, table_bytes, s);
     case 4: return launch_direct_aligned<48, 64, 4, 2>(p, conv, batches, table_bytes, s);
+    case 6: return launch_direct_conv<32, 32, 8, 2>(p, batches, table_bytes, s);
     default: return launch_direct_aligned<64, 64, 4, 2>(p, conv, batches, table_bytes, s);
     }
 }

@@ -25,7 +25,7 @@ static int forced_values()
     char name[32];
     for (int i = 0; i < 100; ++i) {
         struct { const char* name; ForcedKind kind; bool known; } kinds[] = {
-            {"direct", FORCED_DIRECT, i <= 5}, {"unaligned", FORCED_UNALIGNED, i <= 3}, {"tile", FORCED_TILE, i <= 9},
+            {"direct", FORCED_DIRECT, i <= 6}, {"unaligned", FORCED_UNALIGNED, i <= 3}, {"tile", FORCED_TILE, i <= 9},
             {"relu", FORCED_RELU, i == 2 || (i >= 5 && i <= 11)}};
         for (const auto& k : kinds) {
             std::snprintf(name, sizeof(name), "%s%d", k.name, i);
@@ -70,14 +70,20 @@ static int requirements()
     }
     for (int K : {16, 128, 200, 1024, 3072, 65536})
         for (size_t table : {size_t(0), size_t(16), size_t(16384), size_t(16392), size_t(32768)}) {
-            for (int c = 0; c < 6; ++c) EXPECT(direct_takes(c, K, table) == (direct_lds(c, K, table) <= 160 * 1024));
-            EXPECT(direct_takes(0, K, table) == (K < 3072 || table <= 16384));   // 24 slices in rings of three
-            for (int M : {1, 100, 1500}) EXPECT(direct_takes(choose_direct(M, 512, K, 1, table), K, table));
+            for (int gathered = 0; gathered < 2; ++gathered) {
+                for (int c = 0; c < 6; ++c) EXPECT(direct_takes(c, K, table, gathered) == (direct_lds(c, K, table) <= 160 * 1024));
+                EXPECT(direct_takes(0, K, table, gathered) == (K < 3072 || table <= 16384));   // 24 slices in rings of three
+                EXPECT(direct_takes(6, K, table, gathered) == (gathered && (K <= 1024 || table <= 32768)));
+                for (int M : {1, 100, 1500}) EXPECT(direct_takes(choose_direct(M, 512, K, 1, table, gathered), K, table, gathered));
+            }
         }
-    EXPECT(!direct_takes(-1, 128, 0) && !direct_takes(6, 128, 0));
+    EXPECT(!direct_takes(-1, 128, 0, true) && !direct_takes(7, 128, 0, true));
+    for (int cin : {256, 512, 1024})   // long filters over few positions: eight wavefronts to a 32x32 tile
+        for (int k : {5, 7}) EXPECT(choose_direct(1575, 128, k * k * cin, 1, 0, true) == 6 && choose_direct(972, 200, k * k * cin, 1, 0, true) == 6);
+    EXPECT(choose_direct(899, 136, 4800, 1, 0, true) == 6 && choose_direct(840, 136, 3136, 1, 0, true) == 6);   // tests/test_gpu_conv.py
     for (int K : {16, 64, 80, 256, 512}) {   // attention scores: many small products
-        EXPECT(choose_direct(58, 58, K, 270, 0) == 1 && choose_direct(40, 40, K, 384, 0) == 1 && choose_direct(10, 10, K, 168, 0) == 1);
-        EXPECT(choose_direct(16, 16, K, 8, 0) == 0 && choose_direct(500, 500, K, 4, 0) == 1);
+        EXPECT(choose_direct(58, 58, K, 270, 0, false) == 1 && choose_direct(40, 40, K, 384, 0, false) == 1 && choose_direct(10, 10, K, 168, 0, false) == 1);
+        EXPECT(choose_direct(16, 16, K, 8, 0, false) == 0 && choose_direct(500, 500, K, 4, 0, false) == 1);
     }
     return 0;
 }

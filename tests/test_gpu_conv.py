@@ -45,6 +45,8 @@ CASES = [  # B, H, W, Cin, Cout, kh, kw, stride, pad   (route)
     (2, 11, 11, 64, 48, 3, 3, 1, 1),      # gathered operand, fewer than 64 output channels
     (2, 10, 10, 128, 100, 3, 3, 1, 1),    # output channels not a multiple of 16 (no 16-byte row stores)
     (1, 30, 30, 64, 72, 1, 1, 3, 0),      # stride 3
+    (1, 29, 31, 192, 136, 5, 5, 1, 2),    # long filters over few positions: small tiles of eight wavefronts
+    (1, 28, 30, 64, 136, 7, 7, 1, 3),     # the same, fewer slices
 ]
 
 
