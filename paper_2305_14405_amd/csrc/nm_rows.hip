@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kRowThreads) void softmax_pwl_kernel(
 // ------------------------------------------------------------------------------------------
 // LayerNorm-PWL.  Same ownership as softmax.
 // ------------------------------------------------------------------------------------------
-template <int G, int C, bool kVec, bool kFull>
+template <int G, int C, bool kVec, bool kFull, bool kAhead>
 __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
     const float* __restrict__ in, const float* __restrict__ gamma, const float* __restrict__ beta,
     float eps, float inv_L, long rows, int cols, DevTable t, DevTable t2, int two_tables,
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
     const int lane = threadIdx.x & 63;
     const int g = lane % G;
     const int sub = (threadIdx.x >> 6) * kRowsPerWave + lane / G;
-    // Everything the kernel reads is requested in one go, the first row first, then the rsqrt table and the
+    // kAhead: everything the kernel reads is requested in one go, the first row first, then the rsqrt table and the
     // vectors: nothing but the row is waited for before its mean is known.  (The table goes to LDS inside the first trip;
     // every thread of a block makes the same number of trips, so the barrier there is reached by all.)  With the table
     // requested behind the row's arrival and the vectors behind the look-up, a row took two memory round trips more: us,
@@ -301,8 +301,10 @@ __global__ __launch_bounds__(kRowThreads) void layernorm_pwl_kernel(
     // stack of 12 layers over one sequence of 128 tokens, where the vectors come from memory, 24 of them 20 us less.
     extern __shared__ float2 s_kb[];
     bool staged = false;
-    // (beyond 1024 elements a row the registers for that cost more wavefronts than the wait: 4000 x 3000 21 us, 28 so)
-    constexpr bool kAhead = C <= 4, kHold = kVec && kAhead;   // the vectors stay in registers
+    // (Beyond 1024 elements a row the registers for that cost more wavefronts than the wait: 4000 x 3000 21 us, 28 so; without
+    // 16-byte loads it gains nothing at few rows and loses at many: 435774 x 77 115 us, 126 so.  layernorm_form has the rest.)
+    static_assert(kVec || !kAhead, "vectors by four");
+    constexpr bool kHold = kAhead;   // the vectors stay in registers
     if (kAhead)
         asm volatile("" : : "s"(in), "s"(gamma), "s"(beta), "s"(t.kb), "s"(t.nseg), "s"(rows), "s"(cols), "s"(out_q), "s"(out_f32), "s"(eps),
                      "s"(inv_L), "s"(two_tables), "s"(out_inv_scale), "s"(seg), "s"(seg2), "s"(t.lo), "s"(t.hi), "s"(t.inv_w),
@@ -583,20 +585,22 @@ template <bool kVec>
 static bool launch_layernorm_t(RowShape rs, hipStream_t stream, const float* in, const float* gamma,
                                const float* beta, float eps, float inv_L, long rows, int cols,
                                const DevTable& t, const DevTable& t2, int two, float ois, int8_t* oq, float* of,
-                               uint16_t* seg, uint16_t* seg2)
+                               uint16_t* seg, uint16_t* seg2, bool late)
 {
     const size_t shmem = sizeof(float2) * ((size_t)t.nseg + (two ? (size_t)t2.nseg : 0));
 #define NM_LN_CASE(GG, CC)                                                                          \
     if (rs.G == GG && rs.C == CC) {                                                                 \
         constexpr int rpb = (64 / GG) * (kRowThreads / 64);                                         \
-        if (kVec && cols == 4 * GG * CC)                                                            \
-            queue_kernel(layernorm_pwl_kernel<GG, CC, kVec, kVec>, dim3(blocks_for(rows, rpb)), \
-                               dim3(kRowThreads), shmem, stream, in, gamma,                         \
-                               beta, eps, inv_L, rows, cols, t, t2, two, ois, oq, of, seg, seg2);   \
-        else                                                                                        \
-            queue_kernel(layernorm_pwl_kernel<GG, CC, kVec, false>, dim3(blocks_for(rows, rpb)), \
-                               dim3(kRowThreads), shmem, stream, in, gamma,                         \
-                               beta, eps, inv_L, rows, cols, t, t2, two, ois, oq, of, seg, seg2);   \
+        auto launch = [&](auto kern) {                                                              \
+            queue_kernel(kern, dim3(blocks_for(rows, rpb)), dim3(kRowThreads), shmem, stream, in, gamma, beta, eps, inv_L, rows, cols, \
+                         t, t2, two, ois, oq, of, seg, seg2);                                       \
+        };                                                                                          \
+        constexpr bool kAhead = kVec && CC <= 4, kLate = kAhead && CC >= 2;                         \
+        const bool full = kVec && cols == 4 * GG * CC;                                              \
+        if (kLate && late && full) launch(layernorm_pwl_kernel<GG, CC, kVec, kVec, kAhead && !kLate>);   \
+        else if (kLate && late) launch(layernorm_pwl_kernel<GG, CC, kVec, false, kAhead && !kLate>);     \
+        else if (full) launch(layernorm_pwl_kernel<GG, CC, kVec, kVec, kAhead>);                    \
+        else launch(layernorm_pwl_kernel<GG, CC, kVec, false, kAhead>);                             \
         return true;                                                                                \
     }
     NM_LN_CASE(1, 1) NM_LN_CASE(2, 1) NM_LN_CASE(4, 1) NM_LN_CASE(8, 1) NM_LN_CASE(16, 1)
@@ -625,7 +629,8 @@ int32_t launch_layernorm2(const float* in, const float* gamma, const float* beta
     const float inv_L = (float)(1.0 / (double)cols);
     const bool vec = cols % 4 == 0 && aligned(in, 16) && aligned(gamma, 16) && aligned(beta, 16) &&
                      (!out_f32 || aligned(out_f32, 16)) && (!out_q || aligned(out_q, 4));
-    if (vec && !two && !seg && !seg2 && layernorm_row_takes(rows, cols, t.nseg)) {
+    const LayerNormForm form = layernorm_form(rows, cols, t.nseg, !two && !seg && !seg2, out_f32 != nullptr);
+    if (vec && form == LN_ROW) {
         const dim3 grid((unsigned)layernorm_row_blocks(rows));
         auto launch = [&](auto kern) {
             queue_kernel(kern, grid, dim3(kRowThreads), 0, stream, in, gamma, beta, t.kb, out_q, out_f32, (int)rows, t.nseg, t.lo, t.hi,
@@ -637,8 +642,8 @@ int32_t launch_layernorm2(const float* in, const float* gamma, const float* beta
         else launch(layernorm_row_kernel<4>);
         return check_hip(hipGetLastError(), "layernorm launch");
     }
-    bool ok = vec ? launch_layernorm_t<true>(rs, stream, in, gamma, beta, eps, inv_L, rows, cols, t, t2, two, out_inv_scale, out_q, out_f32, seg, seg2)
-                  : launch_layernorm_t<false>(rs, stream, in, gamma, beta, eps, inv_L, rows, cols, t, t2, two, out_inv_scale, out_q, out_f32, seg, seg2);
+    bool ok = vec ? launch_layernorm_t<true>(rs, stream, in, gamma, beta, eps, inv_L, rows, cols, t, t2, two, out_inv_scale, out_q, out_f32, seg, seg2, form == LN_LATE)
+                  : launch_layernorm_t<false>(rs, stream, in, gamma, beta, eps, inv_L, rows, cols, t, t2, two, out_inv_scale, out_q, out_f32, seg, seg2, false);
     if (!ok) return fail(NM_ERR_UNSUPPORTED, "layernorm: no kernel for cols %d", cols);
     return check_hip(hipGetLastError(), "layernorm launch");
 }

@@ -15,4 +15,30 @@ constexpr bool layernorm_row_takes(int64_t rows, int cols, int nseg)
     return rows >= 1 && cols % 256 == 0 && cols <= 1024 && nseg <= 256 && layernorm_row_blocks(rows) < (1LL << 32) / kRowThreads;
 }
 
+// Rows of 16-byte loads: the row kernel, or layernorm_pwl_kernel with the vectors requested with the first row (held in registers:
+// a third to three quarters more of them) or behind the look-up.  plain: one table, no segment output.  us, row kernel | with
+// the row | behind the look-up, int8 results, int8 and fp32:
+//   4096 x 256   2.82 | 2.90 | 2.85    3.35 | 3.41 | 3.38      8195 x 256    3.76 | 3.58 | 3.59    4.92 | 4.71 | 4.77
+// 131075 x 256   30.9 | 25.3 | 28.2    62.4 | 48.1 | 52.2      8195 x 512    4.79 | 4.64 | 4.47    7.09 | 7.14 | 7.53
+//  16384 x 512   8.33 | 8.37 | 9.19    12.5 | 12.6 | 14.2      8195 x 768    5.93 | 6.33 | 6.09    9.52 | 9.97 | 10.3
+//   1027 x 384          2.85 | 2.85           2.97 | 3.02      8195 x 384           5.15 | 4.86           6.99 | 6.64
+//  24000 x 384          10.0 | 10.9           13.8 | 14.7      6000 x 640           5.45 | 4.86           7.63 | 7.07
+//  14000 x 640          10.3 | 11.1           14.0 | 15.9      5000 x 896           6.34 | 5.41           8.99 | 7.95
+//  10000 x 896          10.6 | 10.2           14.7 | 15.1     10000 x 1000         10.9 | 11.1           15.6 | 16.2
+//  12000 x 896          12.1 | 12.8           16.6 | 17.4      8195 x 1000          9.19 | 9.54           12.9 | 13.8
+// A wavefront of the row kernel reads table and vectors for one row, which of 256 columns are more than the row.  Requested
+// with the row the vectors arrive earlier, and rows beyond the 4096 workgroups find them there; in between fewer wavefronts
+// fit a CU: from about one row for each of them to the second round of the others.
+enum LayerNormForm { LN_ROW, LN_AHEAD, LN_LATE };
+constexpr LayerNormForm layernorm_form(int64_t rows, int cols, int nseg, bool plain, bool f32)
+{
+    if (plain && layernorm_row_takes(rows, cols, nseg)) {
+        if (cols == 256) return rows <= 5000 ? LN_ROW : LN_AHEAD;
+        return cols == 512 && !f32 && rows > 5000 && rows <= 14000 ? LN_LATE : LN_ROW;
+    }
+    if (cols <= 256 || cols > 1024) return LN_AHEAD;
+    const int64_t most = cols > 768 ? (f32 || cols > 896 ? 8192 : 11000) : cols > 512 ? (f32 ? 8192 : 12500) : f32 ? 12000 : 16384;
+    return rows >= (f32 ? 4096 : 1250) && rows <= most ? LN_LATE : LN_AHEAD;
+}
+
 }  // namespace nm

@@ -140,6 +140,20 @@ static int layernorm_rows()
         if (layernorm_row_takes(rows, 1024, 256)) EXPECT(layernorm_row_blocks(rows) * 256 < 1L << 32 && layernorm_row_blocks(rows) * 4 >= rows);
     for (int cols : {1, 128, 255, 300, 1280, 4096}) EXPECT(!layernorm_row_takes(4, cols, 128));
     EXPECT(!layernorm_row_takes(4, 256, 257) && !layernorm_row_takes(0, 256, 128));
+    // which form, on both sides of every line
+    for (bool f32 : {false, true}) {
+        EXPECT(layernorm_form(5000, 256, 64, true, f32) == LN_ROW && layernorm_form(5001, 256, 64, true, f32) == LN_AHEAD);
+        EXPECT(layernorm_form(edge, 768, 64, true, f32) == LN_ROW && layernorm_form(edge + 1, 768, 64, true, f32) == LN_AHEAD);
+        EXPECT(layernorm_form(5000, 512, 64, true, f32) == LN_ROW && layernorm_form(14001, 512, 64, true, f32) == LN_ROW);
+        EXPECT(layernorm_form(5001, 512, 64, true, f32) == (f32 ? LN_ROW : LN_LATE) && layernorm_form(14000, 512, 64, true, f32) == (f32 ? LN_ROW : LN_LATE));
+        const struct { int cols; long most; } lines[] = {{320, f32 ? 12000 : 16384}, {512, f32 ? 12000 : 16384}, {640, f32 ? 8192 : 12500}, {896, f32 ? 8192 : 11000}, {900, 8192}, {1024, 8192}};
+        for (const auto& l : lines) {
+            const long least = f32 ? 4096 : 1250;
+            EXPECT(layernorm_form(least - 1, l.cols, 300, true, f32) == LN_AHEAD && layernorm_form(least, l.cols, 300, true, f32) == LN_LATE);
+            EXPECT(layernorm_form(l.most, l.cols, 64, false, f32) == LN_LATE && layernorm_form(l.most + 1, l.cols, 64, false, f32) == LN_AHEAD);
+        }
+        for (int cols : {4, 64, 256, 1028, 4096}) EXPECT(layernorm_form(6000, cols, 300, true, f32) == LN_AHEAD);
+    }
     return 0;
 }
 

@@ -483,6 +483,30 @@ def test_layernorm_one_row_per_wavefront(oracle, cols, nseg):
                 assert_f32_close(host(of), r["y"], f"layernorm fp32 {cols}, {nseg} segments")
 
 
+@pytest.mark.parametrize("rows,cols", [(1251, 320), (1250, 768), (4099, 448), (4097, 640), (1303, 892), (4100, 1000), (5003, 256), (5001, 512), (1250, 1024)])
+def test_layernorm_vectors_behind_the_look_up(oracle, rows, cols):
+    """Sizes at which the general kernel, or its form that requests the vectors late, takes over from the others; each
+    output alone and both, one table and two."""
+    ot, dt = both_tables(oracle, [("rsqrt", 1e-2, 16.0, 100), ("sqrt", 1e-2, 16.0, 100), ("recip", 0.1, 4.0, 100)])
+    g = np.random.default_rng(rows + cols)
+    x = W.float_rows(rows, cols, seed=cols)
+    gamma = (1 + 0.1 * g.standard_normal(cols)).astype(np.float32)
+    beta = (0.1 * g.standard_normal(cols)).astype(np.float32)
+    r = oracle.layernorm_pwl(x, gamma, beta, 1e-5, ot[0], 31.0)
+    r2 = oracle.layernorm_pwl2(x, gamma, beta, 1e-5, ot[1], ot[2], 31.0)
+    dx, dg, db = dev(x), dev(gamma), dev(beta)
+    for want_q, want_f in ((True, False), (False, True), (True, True)):
+        oq = torch.full((rows, cols), 77, dtype=torch.int8, device=DEV) if want_q else None
+        of = torch.full((rows, cols), 7.0, dtype=torch.float32, device=DEV) if want_f else None
+        for want, call in ((r, lambda: nm.nm_layernorm_pwl(dx, dg, db, 1e-5, dt, 0, 31.0, out_q=oq, out_f32=of)),
+                           (r2, lambda: nm.nm_layernorm_pwl2(dx, dg, db, 1e-5, dt, 1, 2, 31.0, out_q=oq, out_f32=of))):
+            call()
+            if want_q:
+                assert_exact(host(oq), want["q"], f"layernorm int8 {rows}x{cols}")
+            if want_f:
+                assert_f32_close(host(of), want["y"], f"layernorm fp32 {rows}x{cols}")
+
+
 @pytest.mark.parametrize("rows,cols", [(37, 96), (101, 128), (64, 768), (9, 1000), (5, 4096)])
 def test_layernorm_pwl2_sqrt_then_reciprocal(oracle, rows, cols):
     """The two-table LayerNorm (square root, then reciprocal): segments of both tables, fp32 and
