@@ -877,12 +877,10 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // 13.3, 50176 x 512 x 128 with residual 18.4 -> 15.4, 12544 x 1024 x 256 with residual 12.8 -> 11.8, 200704 x 256 x 64
     // 22.6 -> 19.6, with residual 26.3 -> 25.6; with 128-byte slices in launch_tile_relu.
     const bool relu_epi = (epi == EPI_Q ? g.conv || g.alpha_vec : (epi == EPI_Q_TABLE || epi == EPI_Q_TABLE_RESID) && g.table.two_seg) &&
-                          p.q16 && g.N % 16 == 0 && batches == 1 && g.split_cols == 0 && (!g.resid || p.r16) && w_al &&
-                          (int64_t)g.N * g.ldw < (1LL << 32) && !force_generic();
+                          p.q16 && g.N % 16 == 0 && batches == 1 && g.split_cols == 0 && (!g.resid || p.r16) && !force_generic();
     const int kunit = g.conv ? g.cCin : g.K;
-    const bool relu_ok = relu_epi && kunit % 64 == 0 &&
-                         (g.conv ? !g.resid && g.K / g.cCin <= 32 && a_extent < (1LL << 31) - (1 << 24)
-                                 : al && (int64_t)g.M * g.lda < (1LL << 32));
+    const bool relu_ok = relu_epi && relu_operands({g.conv != 0, g.w_is_kn != 0, w_al, al, g.resid != nullptr, kunit, g.conv ? g.K / g.cCin : 0,
+                                                    g.conv ? a_extent : (int64_t)g.M * g.lda, (int64_t)g.N * g.ldw});
     // the debug switch's configuration, if this product meets its requirements
     ForcedCfg forced = forced_cfg();
     const bool holds = forced.kind == FORCED_STREAM ? g.N > 64 && (g.conv || stream_ok) && stream_takes(forced.number, g.conv != 0, k128, split_ok)

@@ -49,6 +49,20 @@ constexpr bool stream_takes(int c, bool conv, bool k128, bool split_ok)
 }
 constexpr bool relu_takes(int c, int kunit) { return c == 9 || c == 10 || kunit % 128 == 0; }
 
+// Operands of the tile kernel's epilogues for convolutions: rows of W with K bytes each (not [K,N]), 32-bit offsets from both
+// bases; gathered rows whose taps are bits of a word and whose offsets stay positive with the padding's, plain ones aligned to 16
+// bytes.  kunit: K, or Cin of gathered rows; a_bytes: of the image or of M rows.
+struct ReluOperands {
+    bool gathered, w_is_kn, w_aligned, both_aligned, resid;
+    int kunit, taps;
+    long long a_bytes, w_bytes;
+};
+constexpr bool relu_operands(const ReluOperands& o)
+{
+    return !o.w_is_kn && o.w_aligned && o.w_bytes < (1LL << 32) && o.kunit % 64 == 0 &&
+           (o.gathered ? !o.resid && o.taps <= 32 && o.a_bytes < (1LL << 31) - (1 << 24) : o.both_aligned && o.a_bytes < (1LL << 32));
+}
+
 // Which tile of the tile kernel: the one whose predicted time is smallest.  A configuration takes
 //   start + rounds * slice * K / 128 + rounds' * epilogue   us,
 // rounds being its tiles over its places on the 256 CUs (up to three workgroups share one).  Up to 256 tiles behind the

@@ -63,6 +63,17 @@ static int requirements()
         EXPECT(relu_takes(c, 128) && relu_takes(c, 1024));
         EXPECT(relu_takes(c, 64) == (c == 9 || c == 10) && relu_takes(c, 192) == (c == 9 || c == 10));
     }
+    const ReluOperands plain = {false, false, true, true, false, 512, 0, 1 << 20, 1 << 20}, conv = {true, false, true, true, false, 128, 9, 1 << 20, 1 << 20};
+    for (ReluOperands o : {plain, conv}) {
+        EXPECT(relu_operands(o));
+        auto without = [&o](auto change) { ReluOperands q = o; change(q); return relu_operands(q); };
+        EXPECT(!without([](ReluOperands& q) { q.w_is_kn = true; }));   // V in nm_attn_context: rows of W are not contiguous in k
+        EXPECT(!without([](ReluOperands& q) { q.w_aligned = q.both_aligned = false; }));
+        EXPECT(!without([](ReluOperands& q) { q.kunit = 96; }) && without([](ReluOperands& q) { q.kunit = 192; }));
+        EXPECT(!without([](ReluOperands& q) { q.w_bytes = 1LL << 32; }) && !without([](ReluOperands& q) { q.a_bytes = 1LL << 32; }));
+        EXPECT(without([](ReluOperands& q) { q.resid = true; }) == !o.gathered && without([](ReluOperands& q) { q.both_aligned = false; }) == o.gathered);
+        EXPECT(without([](ReluOperands& q) { q.taps = 33; }) == !o.gathered && without([](ReluOperands& q) { q.a_bytes = (1LL << 31) - (1 << 24); }) == !o.gathered);
+    }
     for (int c = 0; c < 7; ++c) {
         const bool big = c == STREAM_BIG || c == STREAM_OLDBIG, split = c == STREAM_SPLIT || c == STREAM_SMALL;
         EXPECT(stream_takes(c, false, true, true) && stream_takes(c, true, true, true) == !big);
