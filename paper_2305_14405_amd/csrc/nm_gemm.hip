@@ -865,15 +865,12 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
-    const int64_t direct_below = tile_ok ? 1050000 : (g.K <= 256 || g.N <= 64 ? 1700000 : 1000000);
     // Register-staged tiles, for operands that cannot go to LDS directly in whole slices: from 0.8 million outputs on.  Below
     // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do
     // (8000 x 100 x 777 11.4, 8.5; 1220 x 751 x 40 7.2, 6.5; 1000 x 999 x 999 11.2, 9.9).
     const bool unaligned_ok = direct_ok && !g.conv && batches == 1 && g.N >= 4;
     // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
-    // residual; the rows gathered or not).  128-byte slices and the cost model's tile where K (a gathered row's Cin) is a
-    // multiple of 128 and long enough for a ring; 64-byte ones of 128x128 tiles, three in flight, otherwise; of 128x64 for at
-    // most 64 columns.  us, streaming kernel -> these: 200704 x 64 x 576 (3x3) 21.7 -> 17.0, 200704 x 64 x 256 17.9 ->
+    // residual; the rows gathered or not).  us, streaming kernel -> these: 200704 x 64 x 576 (3x3) 21.7 -> 17.0, 200704 x 64 x 256 17.9 ->
     // 13.3, 50176 x 512 x 128 with residual 18.4 -> 15.4, 12544 x 1024 x 256 with residual 12.8 -> 11.8, 200704 x 256 x 64
     // 22.6 -> 19.6, with residual 26.3 -> 25.6; with 128-byte slices in launch_tile_relu.
     const bool relu_epi = (epi == EPI_Q ? g.conv || g.alpha_vec : (epi == EPI_Q_TABLE || epi == EPI_Q_TABLE_RESID) && g.table.two_seg) &&
@@ -895,7 +892,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
     }
-    if (forced.kind == FORCED_DIRECT || (free_choice && direct_ok && (direct_align < 16 || outputs < direct_below))) {
+    if (forced.kind == FORCED_DIRECT || (free_choice && direct_ok && (direct_align < 16 || outputs < direct_below(tile_ok, g.N, g.K)))) {
         rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced.number, stream);
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
@@ -903,10 +900,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     if (forced.kind == FORCED_RELU || (free_choice && relu_ok)) {
         p.taps_w = g.cKw;
         if (g.conv) p.div_wo = fast_div(g.cWo), p.div_ho = fast_div(g.cHo);
-        int c = !free_choice ? forced.number : g.N <= 64 ? 10 : kunit % 128 != 0 || g.K < 384 ? 9
-                                                       : choose_tile(g.M, g.N, g.K, false, false, 0x1e4);
-        if (free_choice && c == 5 && g.K >= 1536) c = 11;   // 12544 x 256 x 2304 (3x3) 12.8 -> 12.0; 12544 x 256 x 1024 7.0 with 5, 7.6
-        switch (c) {
+        switch (free_choice ? choose_relu(g.M, g.N, g.K, kunit) : forced.number) {
         case 2: rc = launch_tile_relu<256, 128, 4, 2, 3>(p, g.conv != 0, stream); break;
         case 5: rc = launch_tile_relu<128, 128, 2, 2, 3>(p, g.conv != 0, stream); break;
         case 6: rc = launch_tile_relu<128, 128, 2, 2, 2>(p, g.conv != 0, stream); break;

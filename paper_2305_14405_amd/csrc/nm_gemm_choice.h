@@ -122,6 +122,21 @@ inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allow
     return best;
 }
 
+// Which of the tile kernel's configurations with the epilogues for convolutions: 128-byte slices and the cost model's tile where K (a
+// gathered row's Cin, kunit) is a multiple of 128 and long enough for a ring; 64-byte ones of 128x128 tiles (9), three in flight,
+// otherwise; of 128x64 (10) for at most 64 columns; 11 is 5 with two wavefronts to a sub-tile.
+inline int choose_relu(int M, int N, int K, int kunit)
+{
+    if (N <= 64) return 10;
+    if (kunit % 128 != 0 || K < 384) return 9;
+    const int c = choose_tile(M, N, K, false, false, 0x1e4);
+    return c == 5 && K >= 1536 ? 11 : c;   // 12544 x 256 x 2304 (3x3) 12.8 -> 12.0; 12544 x 256 x 1024 7.0 with 5, 7.6
+}
+
+// Outputs from which the larger tiles take an aligned product and the small-tile kernel no longer does.  tile_ok: those of the tile
+// kernel with the epilogues of an encoder layer.
+constexpr long long direct_below(bool tile_ok, int N, int K) { return tile_ok ? 1050000 : K <= 256 || N <= 64 ? 1700000 : 1000000; }
+
 // Which tile, aligned operands: the one whose predicted time is smallest,
 //   start + L * (tile + slice * slices) + R * (round + chain * c) + wave * c   us,
 // c being the slices of a wavefront, L the workgroups of the CU that has most and R the rounds it takes for them (as many

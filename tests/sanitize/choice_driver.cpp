@@ -2,6 +2,7 @@
 // tests/test_gemm_choice.py with -fsanitize=address,undefined.
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <initializer_list>
 
@@ -168,8 +169,21 @@ static int layernorm_rows()
     return 0;
 }
 
-int main()
+// choice_driver M N K kunit ...: for each product with the epilogues for convolutions the tile kernel's configuration, or -1 for the
+// small-tile kernel.
+static int configurations(int n, char** v)
 {
+    for (int i = 0; i + 3 < n; i += 4) {
+        const int M = std::atoi(v[i]), N = std::atoi(v[i + 1]), K = std::atoi(v[i + 2]);
+        std::printf("%d\n", (long long)M * N < direct_below(false, N, K) ? -1 : choose_relu(M, N, K, std::atoi(v[i + 3])));
+    }
+    std::printf("SANITIZE_OK\n");
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    if (argc > 1) return configurations(argc - 1, argv + 1);
     if (forced_values() || requirements() || group_rows() || layernorm_rows()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;

@@ -9,6 +9,7 @@ import sys
 
 import pytest
 
+from test_gpu_conv import LARGE_TILE_CASES
 from test_sanitizers import SAN, _run
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -18,6 +19,23 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def test_choices_on_the_host(tmp_path):
     exe = str(tmp_path / "choice_driver")
     _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_large_convolutions_reach_every_configuration(tmp_path):
+    """The cases that compare the tile kernel's epilogues for convolutions with the oracle do take that kernel, and between them
+    each of its configurations, with rows gathered from the image and with plain ones."""
+    exe = str(tmp_path / "choice_driver")
+    products, wanted = [], []
+    for B, H, W, Cin, Cout, k, stride, pad, tile in LARGE_TILE_CASES:
+        Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+        products += [B * Ho * Wo, Cout, k * k * Cin, Cin]
+        wanted.append(tile)
+    _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
+    out = subprocess.run([exe, *map(str, products)], capture_output=True, text=True, timeout=60)
+    assert [int(v) for v in out.stdout.split()[:-1]] == wanted, out.stdout + out.stderr
+    reached = {(c[8], c[5] > 1 or c[6] > 1) for c in LARGE_TILE_CASES}
+    assert reached == {(tile, gathered) for tile in (2, 5, 6, 7, 8, 9, 10, 11) for gathered in (False, True)}
 
 
 # A program of its own: the switch is read once per process.

@@ -113,19 +113,26 @@ def test_conv2d_all_outputs(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad):
         assert np.array_equal(host(oq2), r2["q"]), f"int8-only, table={table is not None}"
 
 
-@pytest.mark.parametrize("B,H,W,Cin,Cout,k,stride,pad", [
-    (27, 40, 40, 64, 48, 3, 1, 1), (13, 31, 29, 192, 96, 3, 1, 1), (7, 39, 35, 128, 112, 3, 1, 1), (1, 90, 93, 128, 128, 3, 1, 2),
-    (3, 61, 63, 256, 400, 1, 2, 0), (2, 35, 37, 512, 432, 1, 1, 0), (1, 60, 61, 1024, 304, 1, 1, 0), (2, 40, 41, 128, 528, 1, 1, 0),
-    (5, 43, 41, 64, 208, 1, 1, 0), (3, 50, 51, 192, 240, 1, 1, 0), (31, 30, 30, 64, 64, 1, 1, 0), (9, 45, 41, 128, 112, 2, 1, 0),
-    (1, 111, 113, 256, 240, 3, 1, 1)])
-def test_conv2d_large_tile_kernel(oracle, B, H, W, Cin, Cout, k, stride, pad):
+# B, H, W, Cin, Cout, k, stride, pad, and the tile kernel's configuration (choose_relu in csrc/nm_gemm_choice.h; that each case
+# takes it is shown in test_gemm_choice.py): each of them with rows gathered and with plain ones
+LARGE_TILE_CASES = [
+    (27, 40, 40, 64, 48, 3, 1, 1, 10), (13, 31, 29, 192, 96, 3, 1, 1, 9), (7, 39, 35, 128, 112, 3, 1, 1, 7), (1, 90, 93, 128, 128, 3, 1, 2, 7),
+    (3, 61, 63, 384, 400, 1, 2, 0, 8), (2, 35, 37, 512, 432, 1, 1, 0, 7), (1, 60, 61, 1024, 304, 1, 1, 0, 7), (2, 40, 41, 128, 528, 1, 1, 0, 9),
+    (5, 43, 41, 64, 208, 1, 1, 0, 9), (3, 50, 51, 192, 240, 1, 1, 0, 9), (31, 30, 30, 64, 64, 1, 1, 0, 10), (9, 45, 41, 128, 112, 2, 1, 0, 7),
+    (1, 111, 113, 256, 240, 3, 1, 1, 11), (9, 45, 42, 512, 144, 1, 1, 0, 2), (9, 37, 35, 128, 272, 2, 1, 0, 2), (3, 59, 57, 512, 144, 1, 1, 0, 5),
+    (11, 45, 43, 512, 272, 1, 2, 0, 5), (5, 56, 59, 384, 80, 1, 1, 0, 6), (9, 41, 44, 384, 400, 1, 2, 0, 6), (1, 46, 44, 384, 496, 1, 1, 0, 8),
+    (3, 61, 63, 1664, 144, 1, 1, 0, 11), (5, 77, 75, 256, 304, 3, 2, 1, 11), (5, 65, 63, 192, 240, 3, 2, 1, 9)]
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout,k,stride,pad,tile", LARGE_TILE_CASES)
+def test_conv2d_large_tile_kernel(oracle, B, H, W, Cin, Cout, k, stride, pad, tile):
     """Convolutions whose outputs are large enough for the tile kernel: gathered rows (64- and 128-byte slices, several taps
     per slice count, strides, padding wider than needed) and plain ones of one, two, three and more slices; partly filled
     row and column tiles; a ReLU, a table of two other lines, none, and a residual.  The results sit between guards."""
     g = np.random.default_rng(B + H + Cin + Cout)
     x, w = rand_i8(g, (B, H, W, Cin), 60), rand_i8(g, (Cout, k, k, Cin), 60)
     Ho, Wo = oracle.conv_out_hw(H, W, k, k, stride, pad)
-    assert B * Ho * Wo * Cout >= 1000000
+    assert B * Ho * Wo * Cout >= (1700000 if k * k * Cin <= 256 or Cout <= 64 else 1000000)   # below: the small-tile kernel
     alpha_vec = ((3.0 / (35 * 35 * np.sqrt(k * k * Cin))) * (1 + g.random(Cout))).astype(np.float32)
     bias = (0.3 * g.standard_normal(Cout)).astype(np.float32)
     ot, dt = relu_tables(oracle)
