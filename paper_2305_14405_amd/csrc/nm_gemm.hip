@@ -865,10 +865,9 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
-    // Register-staged tiles, for operands that cannot go to LDS directly in whole slices: from 0.8 million outputs on.  Below
-    // that the small tiles win (700 x 700 x 1001 6.5 us, tiles 8.2; 2323 x 89 x 430 4.7, 6.6), above it these do
-    // (8000 x 100 x 777 11.4, 8.5; 1220 x 751 x 40 7.2, 6.5; 1000 x 999 x 999 11.2, 9.9).
+    // Register-staged tiles, for operands that cannot go to LDS directly in whole slices (staged_from)
     const bool unaligned_ok = direct_ok && !g.conv && batches == 1 && g.N >= 4;
+    const bool staged = unaligned_ok && (direct_align < 16 || g.K % 64 != 0);
     // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
     // residual; the rows gathered or not).  us, streaming kernel -> these: 200704 x 64 x 576 (3x3) 21.7 -> 17.0, 200704 x 64 x 256 17.9 ->
     // 13.3, 50176 x 512 x 128 with residual 18.4 -> 15.4, 12544 x 1024 x 256 with residual 12.8 -> 11.8, 200704 x 256 x 64
@@ -887,12 +886,12 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                      : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K, epi == EPI_F32_RESID) : false;
     if (!holds) forced = ForcedCfg();
     const bool free_choice = forced.kind == FORCED_NONE;
-    if (forced.kind == FORCED_UNALIGNED || (free_choice && unaligned_ok && (direct_align < 16 || g.K % 64 != 0) && outputs >= 800000)) {
+    if (forced.kind == FORCED_UNALIGNED || (free_choice && staged && outputs >= staged_from(direct_align, g.K))) {
         rc = launch_unaligned(p, direct_align, table_bytes, forced.number, stream);
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");
     }
-    if (forced.kind == FORCED_DIRECT || (free_choice && direct_ok && (direct_align < 16 || outputs < direct_below(tile_ok, g.N, g.K)))) {
+    if (forced.kind == FORCED_DIRECT || (free_choice && direct_ok && (staged || direct_align < 16 || outputs < direct_below(tile_ok, g.N, g.K)))) {
         rc = launch_direct(p, direct_align, g.conv != 0, batches, table_bytes, forced.number, stream);
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");

@@ -206,6 +206,20 @@ inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes, b
     return best;
 }
 
+// Outputs from which the register-staged tiles take a product whose operands cannot go to LDS directly in whole slices (align: of
+// their rows and chunks, 1, 4 or 16 bytes; at 16, K is no multiple of 64); the small-tile kernel has those below.  It reads 16-byte
+// aligned operands without the others' shifts and holds longer there, longest where a slice or two are all the contraction.
+// Over 499 products aligned to 16 and 197 others, of 0.2 to 4.5 million outputs, the kernel chosen is 1.0 and 0.1 % slower than the
+// faster one, 29 and 14 % at worst (one line at 0.8 million: 6.1 and 0.7 %, 72 and 14 %).  us, small tiles | register-staged:
+//   16 bytes:  1016 x 896 x 144 4.3 | 5.9    784 x 1312 x 480 5.6 | 7.3   3064 x 722 x 624 14.4 | 9.9   1054 x 1488 x 2800 18.3 | 14.6
+//   less:      700 x 700 x 1001 6.5 | 8.2    413 x 2496 x 60 4.4 | 4.9    1000 x 999 x 999 11.2 | 9.9   8000 x 100 x 777 11.4 | 8.5
+inline double staged_from(int align, int K)
+{
+    if (align < 16) return K < 256 ? 1050000 : 800000;
+    const double line = 2400000 / (1 + K / 900.0);
+    return line > 900000 ? line : 900000;
+}
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

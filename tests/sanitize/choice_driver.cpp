@@ -100,6 +100,18 @@ static int requirements()
     return 0;
 }
 
+// Products on both sides of the line between the small-tile and the register-staged kernel, each with the faster one.
+static int staged_line()
+{
+    const struct { int M, N, K, align; bool staged; } products[] = {
+        {1016, 896, 144, 16, false}, {667, 2112, 272, 16, false}, {784, 1312, 480, 16, false}, {198, 4192, 992, 16, false}, {565, 1440, 480, 16, false},
+        {149, 5680, 16, 16, false}, {23492, 105, 16, 16, true}, {3064, 722, 624, 16, true}, {1054, 1488, 2800, 16, true}, {2048, 768, 1008, 16, true}, {783, 676, 416, 16, false},
+        {413, 2496, 60, 4, false}, {122, 8192, 11, 1, false}, {1220, 900, 40, 4, true}, {700, 700, 1001, 1, false}, {8000, 100, 777, 1, true},
+        {1000, 999, 999, 1, true}, {4096, 1001, 1000, 4, true}};
+    for (const auto& p : products) EXPECT(((double)p.M * p.N >= staged_from(p.align, p.K)) == p.staged);
+    return 0;
+}
+
 // Every r in turn.
 static int group_rows_searched(int tiles_m, int tiles_n, int BM, int BN)
 {
@@ -184,7 +196,7 @@ static int configurations(int n, char** v)
 int main(int argc, char** argv)
 {
     if (argc > 1) return configurations(argc - 1, argv + 1);
-    if (forced_values() || requirements() || group_rows() || layernorm_rows()) return 1;
+    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;
 }

@@ -680,7 +680,8 @@ def test_gemm_tile_kernel_ragged_edges_of_every_tile(oracle, M, N, K, what):
 
 @pytest.mark.parametrize("M,N,K", [
     (1, 4, 16), (17, 33, 144), (16, 32, 3072), (31, 30, 1001), (128, 96, 130), (64, 1000, 2048), (224, 640, 2112),
-    (225, 643, 2055), (500, 900, 320), (511, 902, 333), (1120, 960, 192), (1099, 990, 200), (1097, 991, 129), (5, 7, 65536)])
+    (225, 643, 2055), (500, 900, 320), (511, 902, 333), (1120, 960, 192), (1099, 990, 200), (1097, 991, 129), (5, 7, 65536),
+    (1016, 896, 144), (1490, 1511, 16), (784, 1312, 480)])
 def test_gemm_small_tile_kernel(oracle, M, N, K):
     """The small-tile kernel in each of its tile configurations, with operands aligned to 16, 4 and 1
     bytes, edges of tiles and of k-slices: every output with every option of the epilogue."""
