@@ -220,6 +220,29 @@ inline double staged_from(int align, int K)
     return line > 900000 ? line : 900000;
 }
 
+// Which tile of the register-staged kernel: the one whose predicted time is smallest,  start + L * (slice * slices + epilogue) +
+// latency * slices  us, L being the workgroups of the CU that has most.  The constants are least-squares fits to 40 to 76 measured
+// shapes each (M and N from 10 to 16384, K from 16 to 4096, rms 10 to 15 %); over the 55 of them with 0.8 million outputs and more
+// the tile chosen is 1.6 % slower than the best (23 % at worst).  The smallest tiles where a CU would get more than two of them
+// are left out: there the fit flatters them (1951 x 2393 x 35 15.4 us, 128x64 12.5).
+inline int choose_unaligned(int M, int N, int K, bool q, bool f32, bool table, bool resid)
+{
+    static constexpr struct { int bm, bn; double start, slice, latency, q, f32, table, resid; } kTiles[] = {
+        {256, 128, 1.0, 1.70, -0.62, 5.8, 6.1, 1.9, 2.8}, {128, 128, 2.4, 0.91, -0.18, 3.2, 3.0, 0.9, 0.2},
+        {128, 64, 2.8, 0.44, 0.19, 1.3, 1.8, 0.5, 0.3},   {64, 64, 3.7, 0.26, 0.21, 0.55, 1.0, 0.3, 0.4}};
+    int cfg = 0;
+    double best = 0.0;
+    for (int c = 0; c < 4; ++c) {
+        const auto& t = kTiles[c];
+        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (c == 3 && tiles > 512) continue;
+        const double L = (double)((tiles + 255) / 256), nk = (K + 127) / 128;
+        const double us = t.start + t.latency * nk + L * (t.slice * nk + (q ? t.q : 0.0) + (f32 ? t.f32 : 0.0) + (table ? t.table : 0.0) + (resid ? t.resid : 0.0));
+        if (c == 0 || us < best) best = us, cfg = c;
+    }
+    return cfg;
+}
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

@@ -322,28 +322,9 @@ static int32_t launch_unaligned_a(GemmParams& p, int align, size_t table_bytes, 
                       : launch_unaligned_t<BM, BN, WAVES_M, WAVES_N, D, 1>(p, table_bytes, s);
 }
 
-// Which tile: the one whose predicted time is smallest,  start + L * (slice * slices + epilogue) + latency * slices  us, L
-// being the workgroups of the CU that has most.  The constants are least-squares fits to 40 to 76 measured shapes each (M
-// and N from 10 to 16384, K from 16 to 4096, rms 10 to 15 %); over the 55 of them with 0.8 million outputs and more the tile
-// chosen is 1.6 % slower than the best (23 % at worst).  The smallest tiles where a CU would get more than two of them
-// are left out: there the fit flatters them (1951 x 2393 x 35 15.4 us, 128x64 12.5).
 int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s)
 {
-    static const struct { int bm, bn; double start, slice, latency, q, f32, table, resid; } kTiles[] = {
-        {256, 128, 1.0, 1.70, -0.62, 5.8, 6.1, 1.9, 2.8}, {128, 128, 2.4, 0.91, -0.18, 3.2, 3.0, 0.9, 0.2},
-        {128, 64, 2.8, 0.44, 0.19, 1.3, 1.8, 0.5, 0.3},   {64, 64, 3.7, 0.26, 0.21, 0.55, 1.0, 0.3, 0.4}};
-    int cfg = 0;
-    double best = 0.0;
-    for (int c = 0; c < 4; ++c) {
-        const auto& t = kTiles[c];
-        const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
-        if (c == 3 && tiles > 512) continue;
-        const double L = (double)((tiles + 255) / 256), nk = (p.K + 127) / 128;
-        const double us = t.start + t.latency * nk + L * (t.slice * nk + (p.out_q ? t.q : 0.0) + (p.out_f32 || p.out_acc ? t.f32 : 0.0) +
-                                                          (p.has_table ? t.table : 0.0) + (p.resid ? t.resid : 0.0));
-        if (c == 0 || us < best) best = us, cfg = c;
-    }
-    if (forced >= 0) cfg = forced;
+    const int cfg = forced >= 0 ? forced : choose_unaligned(p.M, p.N, p.K, p.out_q != nullptr, p.out_f32 || p.out_acc, p.has_table != 0, p.resid != nullptr);
     switch (cfg) {
     case 0: return launch_unaligned_a<256, 128, 4, 2, 2>(p, align, table_bytes, s);
     case 1: return launch_unaligned_a<128, 128, 4, 2, 2>(p, align, table_bytes, s);

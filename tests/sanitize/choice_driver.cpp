@@ -181,13 +181,17 @@ static int layernorm_rows()
     return 0;
 }
 
-// choice_driver M N K kunit ...: for each product with the epilogues for convolutions the tile kernel's configuration, or -1 for the
-// small-tile kernel.
-static int configurations(int n, char** v)
+// choice_driver relu M N K kunit ...: for each product with the epilogues for convolutions the tile kernel's configuration, or -1 for
+// the small-tile kernel.  staged M N K align ...: the register-staged kernel's, with every output, table and residual, or -1.
+static int configurations(bool staged, int n, char** v)
 {
     for (int i = 0; i + 3 < n; i += 4) {
         const int M = std::atoi(v[i]), N = std::atoi(v[i + 1]), K = std::atoi(v[i + 2]);
-        std::printf("%d\n", (long long)M * N < direct_below(false, N, K) ? -1 : choose_relu(M, N, K, std::atoi(v[i + 3])));
+        if (staged) {
+            const int align = std::atoi(v[i + 3]);
+            const bool takes = (align < 16 || K % 64 != 0) && (double)M * N >= staged_from(align, K);
+            std::printf("%d\n", takes ? choose_unaligned(M, N, K, true, true, true, true) : -1);
+        } else std::printf("%d\n", (long long)M * N < direct_below(false, N, K) ? -1 : choose_relu(M, N, K, std::atoi(v[i + 3])));
     }
     std::printf("SANITIZE_OK\n");
     return 0;
@@ -195,7 +199,7 @@ static int configurations(int n, char** v)
 
 int main(int argc, char** argv)
 {
-    if (argc > 1) return configurations(argc - 1, argv + 1);
+    if (argc > 2) return configurations(!std::strcmp(argv[1], "staged"), argc - 2, argv + 2);
     if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;

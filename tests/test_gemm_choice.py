@@ -10,6 +10,7 @@ import sys
 import pytest
 
 from test_gpu_conv import LARGE_TILE_CASES
+from test_gpu_parity import STAGED_CASES
 from test_sanitizers import SAN, _run
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -21,21 +22,34 @@ def test_choices_on_the_host(tmp_path):
     _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
 
 
+def _configurations(tmp_path, kind, products):
+    exe = str(tmp_path / "choice_driver")
+    _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
+    out = subprocess.run([exe, kind, *(str(v) for p in products for v in p)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.endswith("SANITIZE_OK\n"), out.stdout + out.stderr
+    return [int(v) for v in out.stdout.split()[:-1]]
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
 def test_large_convolutions_reach_every_configuration(tmp_path):
     """The cases that compare the tile kernel's epilogues for convolutions with the oracle do take that kernel, and between them
     each of its configurations, with rows gathered from the image and with plain ones."""
-    exe = str(tmp_path / "choice_driver")
-    products, wanted = [], []
+    products = []
     for B, H, W, Cin, Cout, k, stride, pad, tile in LARGE_TILE_CASES:
         Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
-        products += [B * Ho * Wo, Cout, k * k * Cin, Cin]
-        wanted.append(tile)
-    _run(["g++", "-std=c++17", *SAN, "-Wall", "-Werror", "-I", "paper_2305_14405_amd/csrc", "tests/sanitize/choice_driver.cpp", "-o", exe], exe)
-    out = subprocess.run([exe, *map(str, products)], capture_output=True, text=True, timeout=60)
-    assert [int(v) for v in out.stdout.split()[:-1]] == wanted, out.stdout + out.stderr
+        products.append((B * Ho * Wo, Cout, k * k * Cin, Cin))
+    assert _configurations(tmp_path, "relu", products) == [c[8] for c in LARGE_TILE_CASES]
     reached = {(c[8], c[5] > 1 or c[6] > 1) for c in LARGE_TILE_CASES}
     assert reached == {(tile, gathered) for tile in (2, 5, 6, 7, 8, 9, 10, 11) for gathered in (False, True)}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_staged_products_reach_every_configuration(tmp_path):
+    """Likewise the register-staged kernel's cases: each configuration with operands aligned to 16, 4 and 1 bytes."""
+    products = [(M, N, K, 16 if K % 16 == 0 else 4 if K % 4 == 0 else 1) for M, N, K, tile in STAGED_CASES]
+    assert _configurations(tmp_path, "staged", products) == [c[3] for c in STAGED_CASES]
+    reached = {(c[3], p[3]) for c, p in zip(STAGED_CASES, products) if c[3] >= 0}
+    assert reached == {(tile, align) for tile in range(4) for align in (16, 4, 1)}
 
 
 # A program of its own: the switch is read once per process.

@@ -741,13 +741,19 @@ def test_gemm_small_tile_kernel_fixed_epilogues(oracle, M, N, K, per_column):
         assert_f32_close(host(of), r["y"], f"fp32 + residual, bias {bias}")
 
 
-@pytest.mark.parametrize("M,N,K", [
-    (1201, 701, 37), (4100, 200, 36), (1025, 801, 256),             # 64x64 tiles
-    (5523, 266, 17), (2049, 515, 1000), (3001, 402, 129),           # 128x64
-    (3055, 792, 27), (4096, 1001, 260), (803, 4016, 80),            # 128x128
-    (10308, 726, 34), (6401, 1283, 391)])                           # 256x128
-def test_gemm_register_staged_tiles(oracle, M, N, K):
-    """The register-staged tile kernel in each of its tile configurations: operands aligned to 16, 4 and 1 bytes, rows of
+# M, N, K and the register-staged kernel's configuration for every output and option (choose_unaligned in csrc/nm_gemm_choice.h), -1:
+# on the small-tile kernel's side of the line; test_gemm_choice.py shows that each case takes the one beside it
+STAGED_CASES = [
+    (1201, 701, 37, -1), (4100, 200, 36, -1), (1025, 801, 256, -1),
+    (793, 1044, 267, 3), (984, 823, 284, 3), (1164, 1636, 352, 3),                              # 64x64
+    (5523, 266, 17, 2), (2049, 515, 1000, 2), (3001, 402, 129, 2), (6401, 1283, 391, 2), (4258, 947, 16, 2),   # 128x64
+    (3055, 792, 27, 1), (4096, 1001, 260, 1), (803, 4016, 80, 1), (10308, 726, 34, 1),          # 128x128
+    (5210, 1218, 131, 0), (2828, 2150, 132, 0), (6813, 901, 144, 0)]                            # 256x128
+
+
+@pytest.mark.parametrize("M,N,K,tile", STAGED_CASES)
+def test_gemm_register_staged_tiles(oracle, M, N, K, tile):
+    """The register-staged tile kernel in each of its tile configurations, each with operands aligned to 16, 4 and 1 bytes; rows of
     every alignment of the results, K below, at and beyond a k-slice with and without a remainder, partly filled row
     and column tiles; every output and option, a table with the input clamp and one in two levels."""
     test_gemm_small_tile_kernel(oracle, M, N, K)
