@@ -4,7 +4,7 @@
 //
 // What bounds such a product is latency, not a rate: with the LDS-ring kernels 128 x 768 x 3072 is 12
 // workgroups that each wait 24 times for a k-slice, and their prologue and epilogue are as long as
-// the loop.  Here a workgroup owns a small tile (16 x 32 .. 32 x 64 outputs) and its four or eight
+// the loop.  Here a workgroup owns a small tile (16 x 32 .. 64 x 64 outputs) and its four or eight
 // wavefronts divide K between them.  Each streams its own slices (128 bytes of every A and W row of the
 // tile) through an LDS ring of its own, so the loop has no workgroup barrier and most of what a CU needs is
 // in flight at once: rows of 128 bytes keep the loads at the full 64 bytes per clock and CU (loading

@@ -1,6 +1,6 @@
 // The register-staged tile int8 GEMM kernel: matrix products whose operand rows are not 16-byte aligned (a
 // contraction of 1000 or 1001 bytes), or aligned ones of a K that is no multiple of 64, whose output is large enough for
-// tiles (paper Section 3.1; the epilogue is that of every other GEMM kernel here).
+// tiles (staged_from; paper Section 3.1; the epilogue is that of every other GEMM kernel here).
 //
 // Such rows cannot go global -> LDS directly.  They pass through registers: buffer loads of 16 bytes (words past the end of the
 // buffer read as zero), shifted to the row's own start when they are written to LDS, two slices of 128 bytes in LDS and
@@ -10,7 +10,7 @@
 // The epilogue was the larger half before its options became loops of their own and its stores aligned: 4096 x 1000 x
 // 128 through a table 13.2 -> 6.6 us, 4096 x 1001 x 128 20.9 -> 7.3, with fp32 results 15.0 -> 7.7.
 // Against the small-tile kernel, which took these shapes (gemm_direct_kernel, tiles of at most 32x64), us: 4096x1001x1000
-// through a table 28.6 -> 13.6, 2766x491x1334 19.4 -> 15.1, 10932x1375x163 58 -> 23, 13810x1350x2686 251 -> 111,
+// through a table 29.1 -> 12.6, 2766x491x1334 19.4 -> 15.1, 10932x1375x163 58 -> 23, 13810x1350x2686 251 -> 111,
 // 16384x4000x4095 1135 -> 440; 2048x768x1008 (aligned) 18.9 -> 8.9.
 #include "nm_gemm_common.h"
 

@@ -670,7 +670,7 @@ def test_gemm_tile_kernel_configurations(oracle, M, N, K, what):
     (6449, 1744, 384, "256x256; 128x192 with two stages where there is a table"), (5911, 1296, 384, "256x192"),
     (6985, 784, 512, "256x128; 128x128 with two stages where there is a table"), (6001, 752, 1536, "128x192 with three stages"),
     (6149, 912, 384, "128x192 with two stages, 128x128 for int8 without table"), (4111, 400, 512, "128x128 with three stages (int8)"),
-    (1005, 912, 512, "64x128 with three stages"), (6539, 528, 384, "64x128 with two stages"),
+    (1005, 912, 512, "below the tile kernel's line: small tiles"), (6539, 528, 384, "64x128 with two stages"),
     (1205, 912, 512, "64x128 with three stages, beyond the small tiles' line")])
 def test_gemm_tile_kernel_ragged_edges_of_every_tile(oracle, M, N, K, what):
     """One shape per configuration of the large-tile kernel whose last row and column tiles are partly
