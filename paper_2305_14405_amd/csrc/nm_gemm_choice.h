@@ -147,10 +147,12 @@ constexpr long long direct_below(bool tile_ok, int N, int K) { return tile_ok ? 
 //   128 x 768 x 3072   3.9 | 3.9 | 5.9 | 5.2 | 5.8 | 6.9      847 x  768 x 3072  11.4 | 10.1 | 10.5 | 12.0 | 8.4 | 9.2
 //   512 x 1024 x 4096   10 | 8.9 | 9.8 | 7.7 | 8.4 | 9.4     1024 x 1024 x 1024   6.6 |  6.5 |  6.0 |  7.2 | 7.9 | 5.9
 // Rows gathered from an image cost other things (addresses and tap masks in every slice), and with those constants long filters
-// took 1.1 to 1.6 times as long as the rule by the number of tiles: they have their own, fitted to 710 convolutions (filters of 1 to
-// 7, 64 to 1024 channels, 49 to 9408 positions, each epilogue; rms 7 to 11 %), and 32x32 tiles with eight wavefronts.  Chosen over
-// best of seven 0.6 % (16 % at worst).  us, by the other constants -> by these: 1575 x 128 x 25088 (7x7) 26.8 -> 17.0, 972 x 200 x
-// 12800 (5x5) 15.5 -> 10.8, 972 x 200 x 9216 (3x3) 11.9 -> 9.3, 3136 x 256 x 25600 (5x5) 47.0 -> 43.9.
+// took 1.1 to 1.6 times as long as the rule by the number of tiles: they have their own, and 32x32 tiles with eight wavefronts.
+// Fitted to 1120 convolutions (filters of 1 to 7, 64 to 1024 channels, 16 to 14000 positions, 510 of them a residual CNN's at images
+// of 32 to 224; rms 6 to 7 %) by what the choice costs: over 500 others the chosen tile is 0.03 % slower than the best of seven (3 % at
+// worst; a least-squares fit of the times alone 0.8 and 16 %).  us, by the other constants -> by these: 1575 x 128 x 25088
+// (7x7) 26.8 -> 17.0, 972 x 200 x 12800 (5x5) 15.5 -> 10.8, 972 x 200 x 9216 (3x3) 11.9 -> 9.3; by the fit of the times -> by these:
+// 3136 x 64 x 576 (3x3) 3.7 -> 3.4, 6075 x 64 x 576 4.3 -> 4.0, 576 x 512 x 256 (1x1, stride 2) 3.7 -> 3.3, 144 x 2048 x 1024 4.6 -> 4.0.
 struct DirectCost {
     double start, tile, round, slice, chain, wave;
 };
@@ -159,13 +161,13 @@ struct DirectTile {
     DirectCost plain, gathered;   // a start of 0: not built
 };
 constexpr DirectTile kDirectTiles[] = {
-    {16, 32, 8, 3, {1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {1.481, 0, 1.594, 0.039, 0.134, -0.002}},
-    {32, 32, 4, 2, {1.92, 0.08, 0.45, 0.102, 0.14, -0.25}, {1.271, 0.288, 1.332, 0.029, 0.265, 0.098}},
-    {32, 64, 4, 1, {1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {1.427, 0.43, 1.427, 0.041, 0.266, 0.266}},
-    {32, 64, 8, 1, {1.92, 0.43, 0.43, 0.125, 0.69, -0.74}, {2.368, 0.597, 0.597, 0.112, 0.055, -0.17}},
-    {48, 64, 4, 2, {1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {1.172, 0.117, 2.693, 0.086, 0.302, 0.033}},
-    {64, 64, 4, 2, {1.38, 0.63, 1.45, 0.132, 0.41, -0.20}, {1.485, 1.485, 1.485, 0.098, 0.231, 0.231}},
-    {32, 32, 8, 2, {0, 0, 0, 0, 0, 0}, {1.268, 0.055, 1.953, 0.064, 0.045, 0.011}}};
+    {16, 32, 8, 3, {1.92, 0.14, 0.33, 0.055, 0.36, -0.37}, {1.603, 0.494, 0.399, 0.044, 0.211, -0.072}},
+    {32, 32, 4, 2, {1.92, 0.08, 0.45, 0.102, 0.14, -0.25}, {0.909, 0.152, 1.452, 0.044, 0.243, 0.11}},
+    {32, 64, 4, 1, {1.38, 0.30, 0.93, 0.134, -0.16, 0.29}, {1.141, 0.121, 1.799, 0.091, 0.246, 0.119}},
+    {32, 64, 8, 1, {1.92, 0.43, 0.43, 0.125, 0.69, -0.74}, {1.244, 0.89, 0.89, 0.07, 0.528, -0.286}},
+    {48, 64, 4, 2, {1.67, 0.43, 0.97, 0.116, 0.44, -0.31}, {0.8, 0.6, 2.057, 0.116, 0.034, 0.241}},
+    {64, 64, 4, 2, {1.38, 0.63, 1.45, 0.132, 0.41, -0.20}, {2.079, 0.057, 2.323, 0, 0.909, -0.077}},
+    {32, 32, 8, 2, {0, 0, 0, 0, 0, 0}, {1.379, 0.575, 0.843, 0.05, 0.334, -0.13}}};
 constexpr int kDirectTileCount = sizeof(kDirectTiles) / sizeof(kDirectTiles[0]);
 
 // LDS of configuration c at most: the wavefronts' rings, and the table.

@@ -92,7 +92,14 @@ static int requirements()
     EXPECT(!direct_takes(-1, 128, 0, true) && !direct_takes(7, 128, 0, true));
     for (int cin : {256, 512, 1024})   // long filters over few positions: eight wavefronts to a 32x32 tile
         for (int k : {5, 7}) EXPECT(choose_direct(1575, 128, k * k * cin, 1, 0, true) == 6 && choose_direct(972, 200, k * k * cin, 1, 0, true) == 6);
-    EXPECT(choose_direct(899, 136, 4800, 1, 0, true) == 6 && choose_direct(840, 136, 3136, 1, 0, true) == 6);   // tests/test_gpu_conv.py
+    // short filters of a residual CNN, each with the fastest tile (us 3.3, 4.0, 4.0 and 3.4; with those of a fit of the times alone 3.7, 4.6, 4.3 and 3.7)
+    EXPECT(choose_direct(576, 512, 256, 1, 0, true) == 1 && choose_direct(144, 2048, 1024, 1, 0, true) == 3);
+    EXPECT(choose_direct(6075, 64, 576, 1, 0, true) == 3 && choose_direct(3136, 64, 576, 1, 0, true) == 6);
+    const int gathered[][4] = {{392, 64, 576, 0}, {840, 208, 256, 1}, {2520, 400, 256, 2}, {4048, 72, 576, 3}, {3599, 136, 576, 4},   // tests/test_gpu_conv.py
+                               {3870, 400, 256, 5}, {899, 136, 4800, 6}, {840, 136, 3136, 6}};
+    for (const auto& g : gathered)   // without a table and with a ReLU's two segments
+        for (size_t table : {size_t(0), size_t(16)})
+            EXPECT(g[0] * g[1] < direct_below(false, g[1], g[2]) && choose_direct(g[0], g[1], g[2], 1, table, true) == g[3]);
     for (int K : {16, 64, 80, 256, 512}) {   // attention scores: many small products
         EXPECT(choose_direct(58, 58, K, 270, 0, false) == 1 && choose_direct(40, 40, K, 384, 0, false) == 1 && choose_direct(10, 10, K, 168, 0, false) == 1);
         EXPECT(choose_direct(16, 16, K, 8, 0, false) == 0 && choose_direct(500, 500, K, 4, 0, false) == 1);

@@ -47,6 +47,11 @@ CASES = [  # B, H, W, Cin, Cout, kh, kw, stride, pad   (route)
     (1, 30, 30, 64, 72, 1, 1, 3, 0),      # stride 3
     (1, 29, 31, 192, 136, 5, 5, 1, 2),    # long filters over few positions: small tiles of eight wavefronts
     (1, 28, 30, 64, 136, 7, 7, 1, 3),     # the same, fewer slices
+    (1, 29, 31, 64, 208, 2, 2, 1, 0),     # the other small tiles beyond 16x32: 32x32,
+    (3, 29, 31, 64, 400, 2, 2, 1, 0),     # 32x64 with four wavefronts,
+    (2, 44, 46, 64, 72, 3, 3, 1, 1),      # with eight,
+    (1, 59, 61, 64, 136, 3, 3, 1, 1),     # 48x64
+    (2, 44, 46, 64, 400, 2, 2, 1, 0),     # and 64x64
 ]
 
 
