@@ -865,7 +865,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;
     const int64_t outputs = (int64_t)g.M * g.N * batches;
-    // Register-staged tiles, for operands that cannot go to LDS directly in whole slices (staged_from)
+    // Register-staged tiles, for operands that cannot go to LDS directly in whole slices (staged_faster)
     const bool unaligned_ok = direct_ok && !g.conv && batches == 1 && g.N >= 4;
     const bool staged = unaligned_ok && (direct_align < 16 || g.K % 64 != 0);
     // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
@@ -886,7 +886,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
                      : forced.kind == FORCED_TILE ? tile_ok && tile_takes(forced.number, g.K, epi == EPI_F32_RESID) : false;
     if (!holds) forced = ForcedCfg();
     const bool free_choice = forced.kind == FORCED_NONE;
-    if (forced.kind == FORCED_UNALIGNED || (free_choice && staged && outputs >= staged_from(direct_align, g.K))) {
+    if (forced.kind == FORCED_UNALIGNED || (free_choice && staged && staged_faster(direct_align, g.M, g.N, g.K, g.out_q != nullptr, g.out_f32 || g.out_acc, g.has_table != 0, g.resid != nullptr))) {
         rc = launch_unaligned(p, direct_align, table_bytes, forced.number, stream);
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm launch");

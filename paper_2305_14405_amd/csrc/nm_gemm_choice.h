@@ -1,6 +1,7 @@
 // Choices that the GEMM launchers make on the host, in plain C++ (no HIP header: the CPU tests compile this file alone).
 #pragma once
 
+#include <cmath>
 #include <cstddef>
 #include <cstdlib>
 #include <cstring>
@@ -208,18 +209,29 @@ inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes, b
     return best;
 }
 
-// Outputs from which the register-staged tiles take a product whose operands cannot go to LDS directly in whole slices (align: of
-// their rows and chunks, 1, 4 or 16 bytes; at 16, K is no multiple of 64); the small-tile kernel has those below.  It reads 16-byte
-// aligned operands without the others' shifts and holds longer there, longest where a slice or two are all the contraction.
-// Over 499 products aligned to 16 and 197 others, of 0.2 to 4.5 million outputs, the kernel chosen is 1.0 and 0.1 % slower than the
-// faster one, 29 and 14 % at worst (one line at 0.8 million: 6.1 and 0.7 %, 72 and 14 %).  us, small tiles | register-staged:
+// Whether the register-staged tiles take a product whose operands cannot go to LDS directly in whole slices (align: of their rows and
+// chunks, 1, 4 or 16 bytes; at 16, K is no multiple of 64) or the small-tile kernel does: the sign of a fit to the logarithm of their
+// times' ratio.  The small tiles hold longer where operands are aligned to 16 bytes (the others cost them shifts), where a slice or
+// two are all the contraction (nothing repays the larger tiles' prologue) and with fp32 results or several; shorter where result
+// rows are not, since the register-staged kernel aligns its stores, and where few columns leave tiles half empty.  Fitted
+// to 1229 products aligned to 16 and 771 others of 0.4 to 4.5 million outputs and K up to 4096 (with nothing below or beyond: the
+// fit is not asked there), results and options drawn; over 725 and 475 others the kernel chosen is 0.7 and 0.5 % slower than the
+// faster one, 38 and 22 % at worst (a line by alignment and K alone: 1.6 and 1.2 %, 41 and 51 %; at 0.8 million outputs: 4.7 and
+// 1.1 %, 67 and 28 %).  us, small tiles | register-staged, int8 results:
 //   16 bytes:  1016 x 896 x 144 4.3 | 5.9    784 x 1312 x 480 5.6 | 7.3   3064 x 722 x 624 14.4 | 9.9   1054 x 1488 x 2800 18.3 | 14.6
-//   less:      700 x 700 x 1001 6.5 | 8.2    413 x 2496 x 60 4.4 | 4.9    1000 x 999 x 999 11.2 | 9.9   8000 x 100 x 777 11.4 | 8.5
-inline double staged_from(int align, int K)
+//   less:      700 x 700 x 1001 6.5 | 8.2   1000 x 999 x 999 11.2 | 9.9   8000 x 100 x 777 11.4 | 8.5
+//   fp32 too:  11704 x 199 x 16 12.1 | 8.8   4420 x 438 x 80 10.8 | 8.1   (less) 8195 x 107 x 51 9.6 | 6.9
+inline bool staged_faster(int align, int M, int N, int K, bool q, bool f32, bool table, bool resid)
 {
-    if (align < 16) return K < 256 ? 1050000 : 800000;
-    const double line = 2400000 / (1 + K / 900.0);
-    return line > 900000 ? line : 900000;
+    static constexpr struct { double one, outputs, k, f32, q, ragged, ragged_f32, ragged_q, table, resid, narrow; } kLog[2] = {
+        {-0.17, 0.40, 0.20, -0.08, -0.08, 0.11, 0.03, 0.07, -0.08, -0.05, 0.09}, {0.04, 0.46, 0.07, -0.06, -0.06, 0.04, 0.09, -0.01, 0, 0, 0.09}};
+    const auto& t = kLog[align < 16];
+    const double outputs = (double)M * N * 1e-6;
+    if (outputs < 0.4) return false;
+    const bool ragged = N % 16 != 0;
+    return t.one + t.outputs * std::log(outputs < 4.5 ? outputs : 4.5) + t.k * std::log(1 + (K < 4096 ? K : 4096) / 900.0) + (f32 ? t.f32 : 0) + (q ? t.q : 0) +
+               (ragged ? t.ragged + (f32 ? t.ragged_f32 : 0) + (q ? t.ragged_q : 0) : 0) + (table ? t.table : 0) + (resid ? t.resid : 0) +
+               t.narrow * (N > 64 ? 64.0 / N : 1) > 0;
 }
 
 // Which tile of the register-staged kernel: the one whose predicted time is smallest,  start + L * (slice * slices + epilogue) +

@@ -1,6 +1,6 @@
 // The register-staged tile int8 GEMM kernel: matrix products whose operand rows are not 16-byte aligned (a
 // contraction of 1000 or 1001 bytes), or aligned ones of a K that is no multiple of 64, whose output is large enough for
-// tiles (staged_from; paper Section 3.1; the epilogue is that of every other GEMM kernel here).
+// tiles (staged_faster; paper Section 3.1; the epilogue is that of every other GEMM kernel here).
 //
 // Such rows cannot go global -> LDS directly.  They pass through registers: buffer loads of 16 bytes (words past the end of the
 // buffer read as zero), shifted to the row's own start when they are written to LDS, two slices of 128 bytes in LDS and

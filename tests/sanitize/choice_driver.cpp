@@ -113,9 +113,17 @@ static int staged_line()
     const struct { int M, N, K, align; bool staged; } products[] = {
         {1016, 896, 144, 16, false}, {667, 2112, 272, 16, false}, {784, 1312, 480, 16, false}, {198, 4192, 992, 16, false}, {565, 1440, 480, 16, false},
         {149, 5680, 16, 16, false}, {23492, 105, 16, 16, true}, {3064, 722, 624, 16, true}, {1054, 1488, 2800, 16, true}, {2048, 768, 1008, 16, true}, {783, 676, 416, 16, false},
-        {413, 2496, 60, 4, false}, {122, 8192, 11, 1, false}, {1220, 900, 40, 4, true}, {700, 700, 1001, 1, false}, {8000, 100, 777, 1, true},
+        {122, 8192, 11, 1, false}, {1220, 900, 40, 4, true}, {700, 700, 1001, 1, false}, {8000, 100, 777, 1, true},
         {1000, 999, 999, 1, true}, {4096, 1001, 1000, 4, true}};
-    for (const auto& p : products) EXPECT(((double)p.M * p.N >= staged_from(p.align, p.K)) == p.staged);
+    for (const auto& p : products) EXPECT(staged_faster(p.align, p.M, p.N, p.K, true, false, false, false) == p.staged);
+    // which results, and whether their rows are aligned, count too
+    EXPECT(staged_faster(16, 8020, 202, 16, true, true, false, false) && staged_faster(16, 5322, 191, 1040, true, false, false, false));
+    EXPECT(staged_faster(1, 8195, 107, 51, true, true, false, false) && !staged_faster(16, 737, 3168, 80, true, true, false, true));
+    for (int align : {1, 4, 16})
+        for (int options = 0; options < 4; ++options) {   // beyond what was measured
+            EXPECT(!staged_faster(align, 630, 630, 65536, true, false, options & 1, options & 2));
+            EXPECT(staged_faster(align, 16384, 16384, 65536, true, true, options & 1, options & 2));
+        }
     return 0;
 }
 
@@ -196,7 +204,7 @@ static int configurations(bool staged, int n, char** v)
         const int M = std::atoi(v[i]), N = std::atoi(v[i + 1]), K = std::atoi(v[i + 2]);
         if (staged) {
             const int align = std::atoi(v[i + 3]);
-            const bool takes = (align < 16 || K % 64 != 0) && (double)M * N >= staged_from(align, K);
+            const bool takes = (align < 16 || K % 64 != 0) && staged_faster(align, M, N, K, true, true, true, true);
             std::printf("%d\n", takes ? choose_unaligned(M, N, K, true, true, true, true) : -1);
         } else std::printf("%d\n", (long long)M * N < direct_below(false, N, K) ? -1 : choose_relu(M, N, K, std::atoi(v[i + 3])));
     }

@@ -745,7 +745,8 @@ def test_gemm_small_tile_kernel_fixed_epilogues(oracle, M, N, K, per_column):
 # on the small-tile kernel's side of the line; test_gemm_choice.py shows that each case takes the one beside it
 STAGED_CASES = [
     (1201, 701, 37, -1), (4100, 200, 36, -1), (1025, 801, 256, -1),
-    (793, 1044, 267, 3), (984, 823, 284, 3), (1164, 1636, 352, 3),                              # 64x64
+    (793, 1044, 267, -1), (984, 823, 284, -1),
+    (851, 1103, 267, 3), (1164, 823, 284, 3), (1164, 1636, 352, 3),                              # 64x64
     (5523, 266, 17, 2), (2049, 515, 1000, 2), (3001, 402, 129, 2), (6401, 1283, 391, 2), (4258, 947, 16, 2),   # 128x64
     (3055, 792, 27, 1), (4096, 1001, 260, 1), (803, 4016, 80, 1), (10308, 726, 34, 1),          # 128x128
     (5210, 1218, 131, 0), (2828, 2150, 132, 0), (6813, 901, 144, 0)]                            # 256x128
