@@ -26,6 +26,9 @@ constexpr bool layernorm_row_takes(int64_t rows, int cols, int nseg)
 //  14000 x 640          10.3 | 11.1           14.0 | 15.9      5000 x 896           6.34 | 5.41           8.99 | 7.95
 //  10000 x 896          10.6 | 10.2           14.7 | 15.1     10000 x 1000         10.9 | 11.1           15.6 | 16.2
 //  12000 x 896          12.1 | 12.8           16.6 | 17.4      8195 x 1000          9.19 | 9.54           12.9 | 13.8
+// and on both sides of the lines, the first two pairs with fp32 results:
+//   5993 x 832  9.51 | 8.82     9616 x 432  7.96 | 7.69     6258 x  960  7.67 | 7.32
+//   6685 x 896  11.0 | 11.7    10039 x 476  8.48 | 8.78     7460 x 1000  8.93 | 9.33    12358 x 724  10.3 | 11.0
 // A wavefront of the row kernel reads table and vectors for one row, which of 256 columns are more than the row.  Requested
 // with the row the vectors arrive earlier, and rows beyond the 4096 workgroups find them there; in between fewer wavefronts
 // fit a CU: from about one row for each of them to the second round of the others.
@@ -37,7 +40,7 @@ constexpr LayerNormForm layernorm_form(int64_t rows, int cols, int nseg, bool pl
         return cols == 512 && !f32 && rows > 5000 && rows <= 14000 ? LN_LATE : LN_ROW;
     }
     if (cols <= 256 || cols > 1024) return LN_AHEAD;
-    const int64_t most = cols > 768 ? (f32 || cols > 896 ? 8192 : 11000) : cols > 512 ? (f32 ? 8192 : 12500) : f32 ? 12000 : 16384;
+    const int64_t most = f32 ? (cols > 512 ? 6144 : cols > 384 ? 9728 : 12000) : cols > 896 ? 6656 : cols > 768 ? 11000 : cols > 512 ? 12288 : 16384;
     return rows >= (f32 ? 4096 : 1250) && rows <= most ? LN_LATE : LN_AHEAD;
 }
 

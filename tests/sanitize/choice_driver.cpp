@@ -185,7 +185,7 @@ static int layernorm_rows()
         EXPECT(layernorm_form(edge, 768, 64, true, f32) == LN_ROW && layernorm_form(edge + 1, 768, 64, true, f32) == LN_AHEAD);
         EXPECT(layernorm_form(5000, 512, 64, true, f32) == LN_ROW && layernorm_form(14001, 512, 64, true, f32) == LN_ROW);
         EXPECT(layernorm_form(5001, 512, 64, true, f32) == (f32 ? LN_ROW : LN_LATE) && layernorm_form(14000, 512, 64, true, f32) == (f32 ? LN_ROW : LN_LATE));
-        const struct { int cols; long most; } lines[] = {{320, f32 ? 12000 : 16384}, {512, f32 ? 12000 : 16384}, {640, f32 ? 8192 : 12500}, {896, f32 ? 8192 : 11000}, {900, 8192}, {1024, 8192}};
+        const struct { int cols; long most; } lines[] = {{320, f32 ? 12000 : 16384}, {384, f32 ? 12000 : 16384}, {388, f32 ? 9728 : 16384}, {512, f32 ? 9728 : 16384}, {640, f32 ? 6144 : 12288}, {896, f32 ? 6144 : 11000}, {900, f32 ? 6144 : 6656}, {1024, f32 ? 6144 : 6656}};
         for (const auto& l : lines) {
             const long least = f32 ? 4096 : 1250;
             EXPECT(layernorm_form(least - 1, l.cols, 300, true, f32) == LN_AHEAD && layernorm_form(least, l.cols, 300, true, f32) == LN_LATE);
