@@ -22,18 +22,17 @@
 // of the eight rows addressed by lanes j / 8, j / 8 + 2, ...), with the row addresses chosen so
 // that the keys arrive in the order the probabilities have in the lanes.
 //
-// What bounds it: vector instructions (matrix work is a tenth).  By counter 16.0 per score at 32 x 512 tokens and
-// 16 heads, issued in 91 % of the cycles, and 18.5 at 32 x 128 and 12 heads (18.9 in 67 %, and 24.5, before the
-// steps below).  Ten and a half of them, and the table's LDS read, are the loops over the scores (18 before); the
-// rest is paid once per 16 queries and up to 256 keys: addresses of the loads and of the transposing reads,
-// accumulator start values, table staging, the exchange between wavefronts, the context's codes.  The loops' steps
+// What bounds it: vector instructions (by counter 14.3 per score at 32 x 512 tokens and 16 heads, 10.5 of them in the loops over
+// the scores), the matrix instructions, which the SIMD issues in their stead (16 clocks each, an eighth of the time), and
+// what is not hidden of loads and look-ups: without K's and V's loads the kernel takes 91 % of its time, without the
+// look-ups 91 %, without V's reads 92 %.  The instructions beyond the loops' are paid once per 16 queries and up to 256
+// keys: addresses, table staging, the exchange between wavefronts, the context's codes.  The loops' steps
 // have the same values as the normative ones:
 //  * the score accumulators start at the bits of the float 1.5 * 2^23, so an accumulator read as a float
 //    is 1.5 * 2^23 + score exactly (|score| <= 2^20) and the difference of two is the exact difference
 //    of the scores: no conversion; and their integer order is the order of the scores;
-//  * t = difference * alpha <= 0, so the segment index needs no upper clamp when the table is
-//    extended by a copy of its last entry (the index of t = 0 is at most nseg), and the hardware's
-//    unsigned conversion saturates below at 0;
+//  * the table lies in slots (nm_device.h) and everything uniform in vector registers, so that all steps but the maximum and the
+//    final conversion are of the kind that issues at twice the rate;
 //  * where inv_w is a power of two, (t - lo) * inv_w is one fma: scaling by it commutes with rounding;
 //  * a row whose codes provably lie in [0, 127] (bounds of the exp table over every reachable t, times
 //    the row's reciprocal: rounding is monotone) is requantised by v_cvt_pk_u8_f32, which rounds to
@@ -59,6 +58,7 @@ struct AttnParams {
     int nch;                           // 16-byte chunks of a head's row (head size / 16)
     float alpha_scores, inv_s_p, alpha_ctx, inv_s_ctx;
     float e_lo, e_hi;                  // bounds of the exp table's value over every reachable input
+    int off_tile;                      // bytes of LDS in front of the images: the tables
     int ctx_vec16;                     // ctx is 16-byte aligned: context rows leave as 16-byte stores
     FastDiv div_qblocks, div_heads;
     AttnTable t_exp, t_recip;
@@ -67,23 +67,28 @@ struct AttnParams {
 };
 
 // How the exp table's segment is found: any table and scale (this form also writes the optional
-// outputs); a table whose index at t = 0 is at most nseg, with alpha >= 0 and no input clamp; the same
-// with inv_w a power of two.
-enum { EXP_ANY = 0, EXP_PADDED = 1, EXP_PADDED_POW2 = 2 };
+// outputs); a table of at most 256 segments without input clamp, in slots; the same with inv_w a power of two.
+enum { EXP_ANY = 0, EXP_SLOTS = 1, EXP_SLOTS_POW2 = 2 };
+constexpr size_t attn_exp_bytes(int mode, int nseg) { return mode == EXP_ANY ? sizeof(float2) * (size_t)nseg : kSlotBytes; }
 
-// Wavefronts per workgroup of 64 queries: one per 16 queries, two beyond 256 keys.
-constexpr int attn_waves(int nkb) { return nkb >= 8 ? 8 : 4; }
+// Wavefronts that share 16 queries (at most 256 keys each).
+constexpr int attn_parts(int S) { return S <= 256 ? 1 : S <= 512 ? 2 : 4; }
 constexpr int kHeadDim = 64;
 constexpr int kScoreBias = 0x4B400000;   // bits of 1.5 * 2^23: the accumulators' start value
 
 // K image: 64-byte rows, the four 16-byte chunks of a row rotated by (row / 4) % 4 so that the 16
 // lanes of an operand read (16 consecutive rows, one chunk) cover all banks.
 __device__ __forceinline__ int attn_koff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
-// V image: the same, with the rotation also depending on (row / 16) % 4, because one transposing
-// read touches rows 16 apart.
+// V image: the same, with the rotation also depending on (row / (16 kParts)) % 4, because one transposing
+// read touches rows that far apart.
 
 constexpr int kCtxPatch = 16 * 80;   // per wavefront: 16 context rows of 64 bytes, 80 apart
-constexpr size_t attn_lds_bytes(int nkb) { return 2 * (size_t)nkb * 64 * 64 + (size_t)attn_waves(nkb) * kCtxPatch; }
+// K and V images of ng groups of 64 keys per part, then the context patches or, where wavefronts share queries, their row maxima
+// (64 bytes each) and sums (256)
+constexpr size_t attn_lds_bytes(int parts, int ng)
+{
+    return 2 * (size_t)(parts * ng) * 64 * 64 + 4 * (size_t)parts * (parts > 1 ? 64 + 256 : kCtxPatch);
+}
 
 typedef int v2i_t __attribute__((ext_vector_type(2)));
 
@@ -93,17 +98,53 @@ __device__ __forceinline__ int query_reduce(int v, Op op) { return butterfly_ste
 __device__ __forceinline__ int row_max(int v) { return query_reduce(v, MaxI32{}); }
 __device__ __forceinline__ float row_add(float v) { return __int_as_float(query_reduce(__float_as_int(v), AddF32{})); }
 
-// PWL exp of one score; acc and row maximum as biased accumulators.
+// What the loops over the scores use, in vector registers (nm_device.h: a scalar operand halves an instruction's rate).
 template <int kMode>
-__device__ __forceinline__ float attn_exp(int acc, float fmax_, const AttnParams& p, float clo, float chi, const float2* s_kb)
+struct AttnConsts {
+    float alpha, inv_p, lo, inv_w, u0, steps;   // position in slots: times inv_w (and plus u0), which are 1/256 of the table's
+    float clo, chi;                             // EXP_ANY: the input clamp, or infinities
+    __device__ __forceinline__ AttnConsts(const AttnParams& p) : alpha(in_vgpr(p.alpha_scores)), inv_p(in_vgpr(p.inv_s_p)), lo(0.0f), u0(0.0f)
+    {
+        if (kMode == EXP_ANY) {
+            clo = p.t_exp.clamp_input ? p.t_exp.lo : -__builtin_inff();
+            chi = p.t_exp.clamp_input ? p.t_exp.hi : __builtin_inff();
+        } else {
+            inv_w = in_vgpr(p.t_exp.inv_w * (1.0f / kSlotSegments));
+            if (kMode == EXP_SLOTS_POW2) u0 = in_vgpr(p.t_exp.u0 * (1.0f / kSlotSegments));
+            else lo = in_vgpr(p.t_exp.lo);
+            steps = in_vgpr(8.0f * kSlotSegments);
+        }
+    }
+};
+
+// PWL exp of one score (acc and row maximum as biased accumulators) in two steps: the score's t in its place and its line
+// requested, then the line's value in its place.  (Left to itself the compiler writes the value over the line's b, and every one
+// keeps the register pair of its table entry: 64 of them spill.)
+struct AttnLine { float k, b; };
+template <int kMode>
+__device__ __forceinline__ AttnLine attn_look_up(int& s, float fmax_, const AttnParams& p, const AttnConsts<kMode>& c, const int8_t* s_exp)
 {
-    const float t = (__int_as_float(acc) - fmax_) * p.alpha_scores;
-    if (kMode == EXP_ANY) return pwl_eval_bounded(t, clo, chi, p.t_exp, s_kb);
-    float u;
-    if (kMode == EXP_PADDED_POW2) u = __builtin_fmaf(t, p.t_exp.inv_w, p.t_exp.u0);
-    else u = (t - p.t_exp.lo) * p.t_exp.inv_w;
-    const float2 e = s_kb[cvt_u32_sat(u)];
-    return __builtin_fmaf(e.x, t, e.y);
+    float t = (__int_as_float(s) - fmax_) * c.alpha;
+    float2 e;
+    if (kMode == EXP_ANY) {
+        t = __builtin_amdgcn_fmed3f(t, c.clo, c.chi);
+        e = reinterpret_cast<const float2*>(s_exp)[seg_index(t, p.t_exp.lo, p.t_exp.inv_w, p.t_exp.nseg)];
+    } else {
+        const float u = kMode == EXP_SLOTS_POW2 ? fma_clamp01(t, c.inv_w, c.u0) : mul_clamp01(t - c.lo, c.inv_w);
+        e = slot_line(slot_offset(u, c.steps));   // (the slots are the first thing in LDS)
+    }
+    s = __float_as_int(t);
+    return {e.x, e.y};
+}
+__device__ __forceinline__ void attn_line(int& s, const AttnLine& e)
+{
+    asm("v_fma_f32 %0, %1, %0, %2" : "+v"(s) : "v"(e.k), "v"(e.b));
+}
+template <int kMode>
+__device__ __forceinline__ float attn_exp(int acc, float fmax_, const AttnParams& p, const AttnConsts<kMode>& c, const int8_t* s_exp)
+{
+    const AttnLine e = attn_look_up<kMode>(acc, fmax_, p, c, s_exp);
+    return __builtin_fmaf(e.k, __int_as_float(acc), e.b);
 }
 
 // Four probabilities as int8 codes; small: all codes of the row are known to lie in [0, 127].
@@ -129,22 +170,27 @@ __device__ __forceinline__ bool attn_small(float r, const AttnParams& p)
     return __all(ok);
 }
 
-// The exp table with its last entry twice, then the reciprocal table, requested into registers
+// The exp table (in slots, but for EXP_ANY) and the reciprocal table, requested into registers
 // (before the operand loads, which are younger) and written to LDS.
+template <int kMode, int kThreads>
 struct AttnTables {
+    static_assert(kThreads >= kSlotSegments, "a slot per thread");
     float2 te, tr;
     __device__ __forceinline__ void request(const AttnParams& p)
     {
         te = p.t_exp.kb[min((int)threadIdx.x, p.t_exp.nseg - 1)];
         tr = p.t_recip.kb[min((int)threadIdx.x, p.t_recip.nseg - 1)];
     }
-    template <int kThreads>
     __device__ __forceinline__ void write(const AttnParams& p, float2* s_exp, float2* s_recip) const
     {
         const int ne = p.t_exp.nseg, nr = p.t_recip.nseg, tid = threadIdx.x;
-        if (tid <= ne) s_exp[tid] = te;
+        if (kMode == EXP_ANY) {
+            if (tid < ne) s_exp[tid] = te;
+            for (int i = tid + kThreads; i < ne; i += kThreads) s_exp[i] = p.t_exp.kb[i];
+        } else {
+            write_slots(s_exp, te, tid);
+        }
         if (tid < nr) s_recip[tid] = tr;
-        for (int i = tid + kThreads; i <= ne; i += kThreads) s_exp[i] = p.t_exp.kb[min(i, ne - 1)];
         for (int i = tid + kThreads; i < nr; i += kThreads) s_recip[i] = p.t_recip.kb[i];
     }
 };
@@ -178,10 +224,11 @@ __device__ __forceinline__ void attn_store_ctx(const AttnParams& p, const v4i (&
     }
 }
 
-// Operand slot s (0..15) of lane group hq must hold key 64*kb + 16*(s/4) + 4*hq + s%4 (where the
-// probabilities sit).  A transposing read delivers eight rows: this lane supplies the address of
+// Operand slot s (0..15) of lane group hq must hold key 4*hq + s%4 of the (s/4)-th of four 16-key blocks, kParts blocks apart
+// (where the probabilities sit).  A transposing read delivers eight rows: this lane supplies the address of
 // row (lane % 16) / 2 of its group, shifted by 8 bytes for odd lanes so that lanes 8..15 of the
 // group receive head columns 8..15.
+template <int kParts>
 struct VFragments {
     int off[2], sw[2];
     __device__ __forceinline__ VFragments(int lane)
@@ -190,7 +237,7 @@ struct VFragments {
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             const int sidx = 8 * hh + (fr >> 1);
-            off[hh] = (16 * (sidx >> 2) + 4 * hq + (sidx & 3)) * 64 + 8 * (fr & 1);
+            off[hh] = (16 * kParts * (sidx >> 2) + 4 * hq + (sidx & 3)) * 64 + 8 * (fr & 1);
             sw[hh] = hq ^ (sidx >> 2);   // chunk position of column block cb: cb ^ sw
         }
     }
@@ -214,41 +261,45 @@ __device__ __forceinline__ int attn_block_id(int total)
     return (int)(blockIdx.x & 7) * ((total + 7) >> 3) + (int)(blockIdx.x >> 3);
 }
 
-// NKB: padded key count / 64, head size 64.  kFull: S == 64 * NKB, so no key or query is masked.
-//
 // A wavefront holds at most 256 keys of its 16 queries (64 score registers), so that four wavefronts fit
-// a SIMD and one workgroup's K / V loads run under another's arithmetic.  Beyond 256 keys two wavefronts
-// share 16 queries (kSplit): half h takes the 64-key groups 2h, 2h + 1, 4 + 2h, 5 + 2h, i.e. the
-// accumulators 32h .. 32h + 31 of the row sum with all their elements; the halves exchange their row
-// maxima, their accumulators at the butterfly's first step (mask 32) and their partial contexts
-// (exact integers) through the K image, which is free by then.  (With all 512 keys in one wavefront it had 128
-// score registers, and two wavefronts a SIMD.)
-// us per launch, one behind the other, against the kernel before these steps: 32 x 512 tokens, 16 heads 98 -> 63;
-// with 12 heads 16 x 512 39 -> 25, 16 x 384 59 -> 20, 8 x 300 37 -> 8.1, 16 x 256 10 -> 8.1, 32 x 128 6.7 -> 5.6, 11 x 77 5.9 ->
-// 4.4, 32 x 64 3.9 -> 3.6.  In the 24- and 12-layer stacks, beside operands that come from further away, the first two take
-// 73 and 30.
-template <int NKB, bool kFull, int kMode>
-__global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_per_eu(4))) void attention_pwl_kernel(AttnParams p)
+// a SIMD and one workgroup's K / V loads run under another's arithmetic.  Beyond 256 keys kParts = 2 or 4 wavefronts
+// share 16 queries: part h takes every kParts-th 16-key block from block h on, i.e. (its bits 2, or 2 and 3, being h) whole
+// accumulators of the row sum with all their elements, and the parts have equally many blocks, but for one, whatever S is.
+// They exchange their row maxima, their sums at the butterfly's steps with masks 8 and 4, and their partial contexts
+// (exact integers, each part finishing its share of the head's columns) through the K image, which is free by then.
+// NG: groups of four such blocks per part.  kFull: S == 64 * kParts * NG and head size 64, so that nothing is masked or clamped.
+// kHead64: head size 64 (else 16, 32 or 48: Q is zero in the chunks beyond the head's, and the column blocks beyond it are left out).
+// us per launch, one behind the other, before -> after the division by blocks, the slots and the look-ups requested ahead, 12 heads
+// of 64: 16 x 512 tokens 28.8 -> 26.6 (16 heads, 32 x 512: 69 -> 64), 16 x 384 20.6 -> 18.4, 8 x 300 8.7 -> 8.9, 16 x 256 8.8 ->
+// 8.5, 32 x 128 6.2 -> 6.0, 11 x 77 4.6 -> 4.3, 4 x 640 20.7 -> 16.9, 8 x 1024 81 -> 54.
+template <int kParts, int NG, bool kFull, int kMode, bool kHead64>
+__global__ __launch_bounds__(256 * kParts) __attribute__((amdgpu_waves_per_eu(4))) void attention_pwl_kernel(AttnParams p)
 {
-    constexpr bool kSplit = NKB > 4;
-    constexpr int kAttnThreads = 64 * attn_waves(NKB);
-    constexpr int kQueries = 64;       // queries per workgroup
-    constexpr int SK = NKB * 64;       // padded key count
-    constexpr int NG = kSplit ? NKB / 2 : NKB;   // 64-key groups of a wavefront
-    constexpr int NACC = kSplit ? 8 : 4 * NG;    // row-sum accumulators of a lane
+    static_assert(!kFull || kHead64, "nothing clamped");
+    constexpr int kWaves = 4 * kParts, kAttnThreads = 64 * kWaves;
+    constexpr int kQueries = 64;              // queries per workgroup
+    constexpr int SK = 64 * kParts * NG;      // padded key count
+    constexpr int NU = 4 * NG;                // 16-key blocks of a part
+    constexpr int kPeriod = 16 / kParts;      // ... of each 256 keys: the row sum's accumulators of a lane
+    constexpr int NACC = NU < kPeriod ? NU : kPeriod;
+    constexpr int kBlock = 1024 * kParts;     // bytes of K and V from one block of a part to the next
+    constexpr int kColumns = 4 / kParts;      // column blocks of the context that a wavefront finishes
+    // With up to 1024 keys one workgroup fills a CU: V is requested behind K and arrives under the scores and the softmax.
+    constexpr bool kLateV = kParts >= 2;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    int8_t* sK = smem;
-    int8_t* sV = smem + SK * 64;
-    int8_t* sO = smem + 2 * SK * 64;   // context patches
-    float2* s_kb = reinterpret_cast<float2*>(smem + attn_lds_bytes(NKB));
+    // tables (the exp table's at 0, so that a slot's offset is its address), then K and V images, context patches
+    int8_t* const s_tile = smem + p.off_tile;
+    int8_t* sK = s_tile;
+    int8_t* sV = s_tile + SK * 64;
+    int8_t* sO = s_tile + 2 * SK * 64;
     // the kernel arguments everything in front of the loads needs, in one step
     asm volatile("" : : "s"(p.qkv), "s"(p.S), "s"(p.H), "s"(p.heads), "s"(p.qblocks), "s"(p.total), "s"(p.t_exp.kb), "s"(p.t_recip.kb),
                  "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.div_qblocks.magic), "s"(p.div_qblocks.shift), "s"(p.div_heads.magic),
                  "s"(p.div_heads.shift), "s"(p.alpha_scores), "s"(p.inv_s_p), "s"(p.alpha_ctx), "s"(p.inv_s_ctx), "s"(p.t_exp.lo),
                  "s"(p.t_exp.inv_w), "s"(p.t_exp.u0), "s"(p.t_recip.lo), "s"(p.t_recip.hi), "s"(p.t_recip.inv_w),
-                 "s"(p.t_recip.clamp_input), "s"(p.e_lo), "s"(p.e_hi), "s"(p.ctx), "s"(p.ctx_vec16));
+                 "s"(p.t_recip.clamp_input), "s"(p.e_lo), "s"(p.e_hi), "s"(p.ctx), "s"(p.ctx_vec16), "s"(p.nch), "s"(p.off_tile));
     if (kMode == EXP_ANY) asm volatile("" : : "s"(p.scores_out), "s"(p.p_out), "s"(p.t_exp.hi), "s"(p.t_exp.clamp_input));
-    float2* s_kb_recip = s_kb + p.t_exp.nseg + 1;
+    float2* s_kb_recip = reinterpret_cast<float2*>(smem + attn_exp_bytes(kMode, p.t_exp.nseg));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, hq = lane >> 4;
@@ -256,136 +307,154 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
     if (id >= p.total) return;
     const int by = (int)quotient((unsigned)id, p.div_qblocks), bx = id - by * p.qblocks;
     const int b = (int)quotient((unsigned)by, p.div_heads), head = by - b * p.heads;
-    const int S = kFull ? SK : p.S, H = p.H;
+    const int S = kFull ? SK : p.S, H = p.H, nch = kHead64 ? 4 : p.nch;
     const int ld = 3 * H;
-    const int8_t* base = p.qkv + (long)b * S * ld + head * kHeadDim;
+    const int8_t* base = p.qkv + (long)b * S * ld + head * (16 * nch);
 
-    AttnTables tabs;
+    AttnTables<kMode, kAttnThreads> tabs;
     tabs.request(p);
     // K and V -> LDS, row-major, by direct global -> LDS loads (16 rows of 64 bytes per wavefront
     // instruction; the chunk rotation is applied to the source address).  Rows past S repeat the last
-    // one: their keys are masked.
-    {
-        const unsigned lds_k = (unsigned)(uintptr_t)sK, lds_v = (unsigned)(uintptr_t)sV;
+    // one: their keys are masked.  Chunks beyond the head's meet zeros of Q and unused columns: any valid address will do.
+    const auto load = [&](int third, const int8_t* image, int rotation) {
+        const unsigned lds = (unsigned)(uintptr_t)image;
+        const int c = (lane & 3) ^ hq ^ rotation, row = lane >> 2;
+        const int at = third * H + 16 * (kHead64 || c < nch ? c : 0), voff = row * ld + at;
         const int nb16 = kFull ? SK / 16 : (S + 15) >> 4;
-        for (int blk16 = wave; blk16 < nb16; blk16 += kAttnThreads / 64) {
-            int r = 16 * blk16 + (lane >> 2);
-            if (!kFull) r = min(r, S - 1);
-            const int at = r * ld + H;
-            dma16s(base, (unsigned)(at + 16 * ((lane & 3) ^ hq)), lds_k + 1024 * blk16);
-            dma16s(base, (unsigned)(at + H + 16 * ((lane & 3) ^ hq ^ (blk16 & 3))), lds_v + 1024 * blk16);
+        for (int blk16 = wave; blk16 < nb16; blk16 += kWaves) {
+            int v = voff;
+            if (!kFull && 16 * blk16 + 16 > S) v = min(row, S - 1 - 16 * blk16) * ld + at;
+            dma16s(base + (long)(16 * blk16 * ld), (unsigned)v, lds + 1024 * blk16);
         }
-    }
+    };
+    const int v_rotation = (wave / kParts) & 3;   // (a wavefront's blocks are kWaves apart)
+    load(1, sK, 0);
+    if (!kLateV) load(2, sV, v_rotation);
     // this lane's query row, straight from global memory into the MFMA operand registers
-    const int half = kSplit ? wave & 1 : 0, qwave = kSplit ? wave >> 1 : wave;
+    const int part_id = wave & (kParts - 1), qwave = wave / kParts;
     const int q0 = bx * kQueries + qwave * 16, m = q0 + fr;
-    const v4i qf = *reinterpret_cast<const v4i*>(base + (long)(kFull ? m : min(m, S - 1)) * ld + 16 * hq);
-    tabs.template write<kAttnThreads>(p, s_kb, s_kb_recip);
+    v4i qf = {0, 0, 0, 0};
+    if (kHead64 || hq < nch) qf = *reinterpret_cast<const v4i*>(base + (long)(kFull ? m : min(m, S - 1)) * ld + 16 * hq);
+    tabs.write(p, reinterpret_cast<float2*>(smem), s_kb_recip);
+    const AttnConsts<kMode> consts(p);
     wait_vmcnt<0>();   // this wavefront's loads have landed (the barrier covers the others')
     __syncthreads();
-    if (!kFull && !kSplit && q0 >= S) return;
+    if (!kFull && kParts == 1 && q0 >= S) return;
+    if (kLateV) {
+        asm volatile("" : : "v"(qf));   // (the compiler's wait for Q, which would count the loads of V)
+        load(2, sV, v_rotation);
+    }
 
-    const int ngroups = kFull ? NKB : (S + 63) >> 6;   // 64-key groups with valid keys; the last may be partial
-    const bool ragged = !kFull && (S & 63) != 0;
-    const auto group_of = [&](int g) { return kSplit ? (g & 1) + 2 * half + 4 * (g >> 1) : g; };   // g-th group of this wavefront
-    const auto keys_left = [&](int g) { return S - 64 * group_of(g) - 4 * hq; };   // key (g, q, e) is valid if 16q + e is below it
+    // Unit u: the part's u-th block, keys 16 (kParts u + part) + 4 hq + e.  Keys from S on lie in the last group's units alone:
+    // all bits set where e + 16 kParts (u - first unit of that group) is below `left`.
+    sK += 1024 * part_id;
+    sV += 1024 * part_id;
+    const int left = S - 16 * kParts * 4 * (NG - 1) - 16 * part_id - 4 * hq;
+    const auto valid = [&](int u, int e) { return (16 * kParts * (u - 4 * (NG - 1)) + e - left) >> 31; };
 
     // ---- scores and row maximum -----------------------------------------------------------------
-    int sc[16 * NG];   // biased scores, then exp values (float bits): key 16q + 4hq + e of group g is sc[16g + 4q + e]
+    // operands of a group one group ahead of its products, the maximum one behind
+    int sc[16 * NG];   // biased scores, then t, then exp values (float bits): e of unit u is sc[4u + e]
     int mi = INT_MIN;
+    v4i kf[2][4];
+    const int8_t* const k_frag = sK + attn_koff(fr, hq);
+    const auto load_k = [&](int g) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) kf[g & 1][q] = *reinterpret_cast<const v4i*>(k_frag + kBlock * (4 * g + q));
+    };
+    const auto group_max = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            int& s = sc[16 * g + i];
+            if (!kFull && g == NG - 1) {
+                const int ok = valid(4 * g + i / 4, i % 4);
+                s = (s & ok) | (INT_MIN & ~ok);
+            }
+            mi = max(mi, s);
+        }
+    };
+    load_k(0);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-        const int gg = group_of(g);
-        if (!kFull && gg >= ngroups) continue;   // (the values of an absent group are never read)
+        if (g + 1 < NG) load_k(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const v4i kf = *reinterpret_cast<const v4i*>(&sK[4096 * gg + attn_koff(16 * q + fr, hq)]);
-            const v4i a = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf, qf, v4i{kScoreBias, kScoreBias, kScoreBias, kScoreBias}, 0, 0, 0);
+            const v4i a = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[g & 1][q], qf, v4i{kScoreBias, kScoreBias, kScoreBias, kScoreBias}, 0, 0, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) sc[16 * g + 4 * q + e] = a[e];
         }
-        if (ragged && gg == ngroups - 1) {
-            const int left = keys_left(g);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sc[16 * g + i] = 16 * (i / 4) + i % 4 < left ? sc[16 * g + i] : INT_MIN;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mi = max(mi, sc[16 * g + i]);
-        // keeps the operand reads of later groups from piling up in registers
-        if (NG >= 4) __builtin_amdgcn_sched_barrier(0);
+        if (g > 0) group_max(g - 1);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    group_max(NG - 1);
     const long row_ss = ((long)by * S + m) * S;  // offset of this query's row in [B,heads,S,S]
     const bool vec4 = (S & 3) == 0;
-    if (kMode == EXP_ANY && p.scores_out && (kFull || m < S)) {
+    const auto key_of = [&](int u) { return 16 * (kParts * u + part_id) + 4 * hq; };
+    if (kMode == EXP_ANY && p.scores_out && m < S) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int key = 64 * group_of(g) + 16 * q + 4 * hq;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (kFull || key + e < S) p.scores_out[row_ss + key + e] = sc[16 * g + 4 * q + e] - kScoreBias;
-            }
+        for (int i = 0; i < 16 * NG; ++i)
+            if (key_of(i / 4) + i % 4 < S) p.scores_out[row_ss + key_of(i / 4) + i % 4] = sc[i] - kScoreBias;
     }
     mi = row_max(mi);
-    int* s_max = reinterpret_cast<int*>(sO);             // (the patches are not in use yet)
-    int8_t* s_xch = sK;                                  // exchange area, once everybody is done with K
-    if (kSplit) {
+    int* const s_max = reinterpret_cast<int*>(sO);
+    float* const s_sum = reinterpret_cast<float*>(sO + 64 * kWaves);
+    if (kParts > 1) {
         if (lane < 16) s_max[16 * wave + lane] = mi;
-        __syncthreads();
-        mi = max(mi, s_max[16 * (wave ^ 1) + fr]);
+        __syncthreads();   // (everybody is done with K, too)
+#pragma unroll
+        for (int o = 1; o < kParts; ++o) mi = max(mi, s_max[16 * (wave ^ o) + fr]);
     }
 
     // ---- softmax-PWL ----------------------------------------------------------------------------
     // Keys 256.. wrap onto the 64 accumulators of keys 0..255 (accumulator = (key / 4) % 64) and continue
-    // their sums.
+    // their sums.  The look-ups of a unit are requested kAhead units before they are used, so that a wavefront has
+    // some in flight all the time (eight at a time and then waited for: 32 x 512 tokens, 16 heads 68 us, 66 so).
     float part[NACC];
     const float fm = __int_as_float(mi);
-    const float clo = p.t_exp.clamp_input ? p.t_exp.lo : -__builtin_inff();
-    const float chi = p.t_exp.clamp_input ? p.t_exp.hi : __builtin_inff();
 #pragma unroll
-    for (int q = 0; q < NACC; ++q) part[q] = 0.0f;
+    for (int j = 0; j < NACC; ++j) part[j] = 0.0f;
+    constexpr int kAhead = 3;
+    AttnLine line[kAhead + 1][4];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (!kFull && group_of(g) >= ngroups) continue;
+    for (int u = 0; u < NU + kAhead; ++u) {
+        if (u < NU) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            sc[16 * g + i] = __float_as_int(attn_exp<kMode>(sc[16 * g + i], fm, p, clo, chi, s_kb));
-            // bounds the number of table look-ups in flight (each holds three registers)
-            if (NG >= 4 && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 4; ++e) line[u % (kAhead + 1)][e] = attn_look_up<kMode>(sc[4 * u + e], fm, p, consts, smem);
         }
-        if (ragged && group_of(g) == ngroups - 1) {
-            const int left = keys_left(g);
+        __builtin_amdgcn_sched_barrier(0);
+        if (u >= kAhead) {
+            const int d = u - kAhead;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sc[16 * g + i] = 16 * (i / 4) + i % 4 < left ? sc[16 * g + i] : 0;
+            for (int e = 0; e < 4; ++e) {
+                int& s = sc[4 * d + e];
+                attn_line(s, line[d % (kAhead + 1)][e]);
+                if (!kFull && d >= 4 * (NG - 1)) s &= valid(d, e);
+                part[d % kPeriod] = part[d % kPeriod] + __int_as_float(s);
+            }
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part[(4 * g + i / 4) % NACC] = part[(4 * g + i / 4) % NACC] + __int_as_float(sc[16 * g + i]);
-        if (NG >= 4) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    // butterfly over the accumulator index 4*blk + hq: masks 32, 16, 8, 4 (blk), then 2, 1 (hq)
-    if (kSplit) {
+    // butterfly over the accumulator index 4 * (kParts j + part) + hq: masks 32 .. of j, then the part's, then 2 and 1 (hq)
+    if (kLateV) wait_vmcnt<0>();   // V has landed (the next barrier covers the others')
 #pragma unroll
-        for (int i = 0; i < NACC; i += 4)
-            *reinterpret_cast<v4f*>(s_xch + wave * 2048 + i * 256 + 16 * lane) = v4f{part[i], part[i + 1], part[i + 2], part[i + 3]};
+    for (int mask = kPeriod / 2; mask >= 1; mask >>= 1)
+#pragma unroll
+        for (int j = 0; j < mask; ++j)
+            if (j + mask < NACC) part[j] = part[j] + part[j + mask];   // (an absent one is +0, and no sum is -0)
+    float sum = part[0];
+    if (kParts > 1) {
+        s_sum[64 * wave + lane] = sum;
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NACC; i += 4) {
-            const v4f o = *reinterpret_cast<const v4f*>(s_xch + (wave ^ 1) * 2048 + i * 256 + 16 * lane);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) part[i + e] = part[i + e] + o[e];
-        }
+        sum = sum + s_sum[64 * (wave ^ (kParts / 2)) + lane];
+        if (kParts == 4) sum = sum + (s_sum[64 * (wave ^ 1) + lane] + s_sum[64 * (wave ^ 3) + lane]);
     }
-#pragma unroll
-    for (int mask = NACC / 2; mask >= 1; mask >>= 1)
-#pragma unroll
-        for (int i = 0; i < mask; ++i) part[i] = part[i] + part[i + mask];
-    const float sum = row_add(part[0]);
+    sum = row_add(sum);
     int segr;
     const float r = pwl_eval(sum, p.t_recip, s_kb_recip, segr);
 
     // ---- probabilities and context --------------------------------------------------------------
-    const VFragments vfrag(lane);
+    const VFragments<kParts> vfrag(lane);
     v4i a2[4];
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) a2[cb] = v4i{0, 0, 0, 0};
@@ -393,27 +462,29 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
         constexpr bool kSmall = decltype(small_c)::value;
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const int gg = group_of(g);
-            if (!kFull && gg >= ngroups) continue;
+            v4i vf[4];
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+                if (kHead64 || cb < nch) vf[cb] = vfrag.read(sV + 4 * kBlock * g, cb);
+            __builtin_amdgcn_sched_barrier(0);
             v4i pf;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int* at = sc + 16 * g + 4 * q;
                 const float x[4] = {__int_as_float(at[0]), __int_as_float(at[1]), __int_as_float(at[2]), __int_as_float(at[3])};
-                pf[q] = (int)attn_pack(x, r, p.inv_s_p, kSmall);
+                pf[q] = (int)attn_pack(x, r, consts.inv_p, kSmall);
             }
             // A masked key's code is 0 whatever r and inv_s_p are (0 times an infinity is a NaN, of code -127); what
             // the V image holds for these keys then does not count.  In the other form r and inv_s_p are finite.
-            if (!kSmall && ragged && gg == ngroups - 1) {
-                const int left = keys_left(g);
+            if (!kFull && !kSmall && g == NG - 1) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) pf[q] = (int)attn_keep((unsigned)pf[q], left - 16 * q);
+                for (int q = 0; q < 4; ++q) pf[q] = (int)attn_keep((unsigned)pf[q], left - 16 * kParts * q);
             }
-            if (kMode == EXP_ANY && p.p_out && (kFull || m < S)) {
+            if (kMode == EXP_ANY && p.p_out && m < S) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int key = 64 * gg + 16 * q + 4 * hq;
-                    if (vec4 && (kFull || key < S)) {
+                    const int key = key_of(4 * g + q);
+                    if (vec4 && key < S) {
                         *reinterpret_cast<unsigned*>(p.p_out + row_ss + key) = (unsigned)pf[q];
                     } else {
 #pragma unroll
@@ -424,46 +495,66 @@ __global__ __launch_bounds__(64 * attn_waves(NKB)) __attribute__((amdgpu_waves_p
             }
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb)
-                a2[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vfrag.read(sV + 4096 * gg, cb), pf, a2[cb], 0, 0, 0);
-            if (NG >= 4) __builtin_amdgcn_sched_barrier(0);
+                if (kHead64 || cb < nch) a2[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[cb], pf, a2[cb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     if (attn_small(r, p)) finish(std::true_type{}); else finish(std::false_type{});
-    if (kSplit) {
-        // half 0 finishes the context; half 1 hands its partial sums over
-        int8_t* x = s_xch + 16384 + qwave * 4096 + 16 * lane;
-        if (half == 1) {
+    if constexpr (kParts == 1) {
+        attn_store_ctx(p, a2, sO + wave * kCtxPatch, lane, (long)b * S, q0, head, nch);
+    } else {
+        // part h finishes column blocks kColumns * h .., the others hand their sums of these over
+        int8_t* const x = s_tile + 16 * lane;
+        const auto slot = [&](int cb, int from) {   // of part from (not the finisher) for column block cb
+            return ((qwave * 4 + cb) * (kParts - 1) + from - (from > cb / kColumns ? 1 : 0)) * 1024;
+        };
+        static_assert(16 * (kParts - 1) * 1024 <= SK * 64, "exchange fits the K image");
 #pragma unroll
-            for (int cb = 0; cb < 4; ++cb) *reinterpret_cast<v4i*>(x + 1024 * cb) = a2[cb];
-        }
+        for (int cb = 0; cb < 4; ++cb)
+            if (cb / kColumns != part_id) *reinterpret_cast<v4i*>(x + slot(cb, part_id)) = a2[cb];
         __syncthreads();
-        if (half == 1) return;
+        v4i mine[kColumns];
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) a2[cb] += *reinterpret_cast<const v4i*>(x + 1024 * cb);
+        for (int c = 0; c < kColumns; ++c) {
+            mine[c] = a2[c];
+#pragma unroll
+            for (int h = 1; h < kParts; ++h)   // (a2 is indexed by constants only: its registers have no addresses)
+                if (part_id == h) mine[c] = a2[kColumns * h + c];
+#pragma unroll
+            for (int o = 0; o < kParts - 1; ++o)
+                mine[c] += *reinterpret_cast<const v4i*>(x + ((qwave * 4 + kColumns * part_id + c) * (kParts - 1) + o) * 1024);
+        }
+        if (!kFull && m >= S) return;
+        int8_t* dst = p.ctx + ((long)b * S + m) * H + head * (16 * nch) + 16 * kColumns * part_id + 4 * hq;
+#pragma unroll
+        for (int c = 0; c < kColumns; ++c) {
+            if (!kHead64 && kColumns * part_id + c >= nch) break;
+            int q[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[e] = requant(__builtin_fmaf((float)mine[c][e], p.alpha_ctx, 0.0f), p.inv_s_ctx);
+            *reinterpret_cast<unsigned*>(dst + 16 * c) = pack4(q[0], q[1], q[2], q[3]);
+        }
     }
-    attn_store_ctx(p, a2, sO + wave * kCtxPatch, lane, (long)b * S, q0, head, 4);
 }
 
-// Sequences whose scores do not fit a wavefront's registers (more than 512 keys) and head sizes 16, 32 and
-// 48: the scores are computed three times, for the row maximum, for the sum and for the probabilities
-// (matrix work is cheap: 22.3 vector instructions per score by counter at 4 x 640 tokens, and no score or
-// probability goes to memory).  K, and V in the last pass, come through LDS in chunks of 256 keys, the
-// next chunk loading while one is used.  A workgroup is four wavefronts of 16 queries.
-// Four sequences of 640 tokens, 12 heads of 64: 22 us; scores, softmax and context as three kernels took 21 + 20
-// + 15.
+// Sequences beyond 1024 keys: the scores are computed three times, for the row maximum, for the sum and for the
+// probabilities (matrix work is cheap, and no score or probability goes to memory).  K, and V in the last pass, come
+// through LDS in chunks of 256 keys, the next chunk loading while one is used.  A workgroup is four wavefronts of 16
+// queries.  Up to 1024 keys the kernel above is the faster one: 4 x 520 tokens, 12 heads of 64, 17.8 us here, 15.1 there; 2 x
+// 1000, 8 heads, 23.6 and 10.8; and heads of 32 at any length: 32 x 128 tokens, 8 heads, 6.5 and 4.9.
 constexpr int kLongThreads = 256, kLongKeys = 256;
 constexpr size_t kLongLds = 4 * (size_t)kLongKeys * 64 + (kLongThreads / 64) * (size_t)kCtxPatch;
 
 template <int kMode>
 __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2))) void attention_long_kernel(AttnParams p)
 {
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];   // K, K, V, V chunks of 16 KB, context patches, tables
-    int8_t* sO = smem + 4 * kLongKeys * 64;
-    float2* s_kb = reinterpret_cast<float2*>(smem + kLongLds);
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];   // tables, K, K, V, V chunks of 16 KB, context patches
+    int8_t* const s_tile = smem + p.off_tile;
+    int8_t* sO = s_tile + 4 * kLongKeys * 64;
     asm volatile("" : : "s"(p.qkv), "s"(p.S), "s"(p.H), "s"(p.heads), "s"(p.qblocks), "s"(p.total), "s"(p.t_exp.kb), "s"(p.t_recip.kb),
                  "s"(p.t_exp.nseg), "s"(p.t_recip.nseg), "s"(p.nch), "s"(p.scores_out), "s"(p.p_out), "s"(p.div_qblocks.magic),
-                 "s"(p.div_qblocks.shift), "s"(p.div_heads.magic), "s"(p.div_heads.shift));
-    float2* s_kb_recip = s_kb + p.t_exp.nseg + 1;
+                 "s"(p.div_qblocks.shift), "s"(p.div_heads.magic), "s"(p.div_heads.shift), "s"(p.off_tile));
+    float2* s_kb_recip = reinterpret_cast<float2*>(smem + attn_exp_bytes(kMode, p.t_exp.nseg));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 15, hq = lane >> 4;
     const int id = attn_block_id(p.total);
@@ -473,10 +564,10 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
     const int S = p.S, H = p.H, ld = 3 * H, nch = p.nch;
     const int8_t* base = p.qkv + (long)b * S * ld + head * (16 * nch);
 
-    AttnTables tabs;
+    AttnTables<kMode, kLongThreads> tabs;
     tabs.request(p);
     const int nchunks = (S + kLongKeys - 1) / kLongKeys, steps = 3 * nchunks;
-    const unsigned lds0 = (unsigned)(uintptr_t)smem;
+    const unsigned lds0 = (unsigned)(uintptr_t)s_tile;
     // chunks of a row beyond the head's are never used (Q is zero there): any valid address will do
     auto chunk_at = [&](int c) { return 16 * (c < nch ? c : 0); };
     auto issue = [&](int pass, int c, int buf) {
@@ -492,13 +583,12 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
     const int q0 = bx * (kLongThreads / 4) + wave * 16, m = q0 + fr;
     v4i qf = {0, 0, 0, 0};
     if (hq < nch) qf = *reinterpret_cast<const v4i*>(base + (long)min(m, S - 1) * ld + 16 * hq);
-    tabs.write<kLongThreads>(p, s_kb, s_kb_recip);
+    tabs.write(p, reinterpret_cast<float2*>(smem), s_kb_recip);
+    const AttnConsts<kMode> consts(p);
 
     const bool ragged = (S & 63) != 0, vec4 = (S & 3) == 0;
     const long row_ss = ((long)by * S + m) * S;
-    const float clo = p.t_exp.clamp_input ? p.t_exp.lo : -__builtin_inff();
-    const float chi = p.t_exp.clamp_input ? p.t_exp.hi : __builtin_inff();
-    const VFragments vfrag(lane);
+    const VFragments<1> vfrag(lane);
     int mi = INT_MIN;
     float part[16], fm = 0.0f, r = 0.0f;
     v4i a2[4];
@@ -518,8 +608,8 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
                 const bool wrap = c + 1 == nchunks;
                 issue(wrap ? kPass + 1 : kPass, wrap ? 0 : c + 1, (step + 1) & 1);
             }
-            const int8_t* sK = smem + (step & 1) * 16384;
-            const int8_t* sV = smem + 32768 + (step & 1) * 16384;
+            const int8_t* sK = s_tile + (step & 1) * 16384;
+            const int8_t* sV = s_tile + 32768 + (step & 1) * 16384;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int k0 = kLongKeys * c + 64 * g;   // first key of the group
@@ -548,7 +638,7 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) x[q][e] = attn_exp<kMode>(acc[q][e], fm, p, clo, chi, s_kb);
+                        for (int e = 0; e < 4; ++e) x[q][e] = attn_exp<kMode>(acc[q][e], fm, p, consts, smem);
                         if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
                     }
 #pragma unroll
@@ -560,7 +650,7 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
                             for (int e = 0; e < 4; ++e) part[4 * g + q] = part[4 * g + q] + x[q][e];
                         } else {
-                            pf[q] = (int)attn_pack(x[q], r, p.inv_s_p, kSmall);
+                            pf[q] = (int)attn_pack(x[q], r, consts.inv_p, kSmall);
                             // (0 also where r or inv_s_p is not finite: see attention_pwl_kernel)
                             if (kMask && !kSmall) pf[q] = (int)attn_keep((unsigned)pf[q], S - k0 - 16 * q - 4 * hq);
                         }
@@ -631,12 +721,13 @@ static int32_t launch_attn_kernel(Kern kern, std::once_flag& once, int32_t& once
     return NM_OK;
 }
 
-template <int NKB, bool kFull, int kMode>
+template <int kParts, int NG, bool kFull, int kMode, bool kHead64>
 static int32_t launch_short(AttnParams& p, size_t tables, hipStream_t st)
 {
     static std::once_flag once;
     static int32_t once_rc = NM_OK;
-    return launch_attn_kernel(attention_pwl_kernel<NKB, kFull, kMode>, once, once_rc, p, 64 * attn_waves(NKB), attn_lds_bytes(NKB) + tables, st);
+    return launch_attn_kernel(attention_pwl_kernel<kParts, NG, kFull, kMode, kHead64>, once, once_rc, p, 256 * kParts,
+                              attn_lds_bytes(kParts, NG) + tables, st);
 }
 template <int kMode>
 static int32_t launch_long(AttnParams& p, size_t tables, hipStream_t st)
@@ -646,32 +737,34 @@ static int32_t launch_long(AttnParams& p, size_t tables, hipStream_t st)
     return launch_attn_kernel(attention_long_kernel<kMode>, once, once_rc, p, kLongThreads, kLongLds + tables, st);
 }
 
-template <int NKB, int kMode>
-static int32_t launch_nkb(AttnParams& p, int pairs, size_t tables, hipStream_t st)
+template <int kParts, int NG, int kMode>
+static int32_t launch_groups(AttnParams& p, size_t tables, hipStream_t st)
 {
-    p.qblocks = (p.S + 63) / 64;
-    p.total = p.qblocks * pairs;
-    // (from 256 keys on the masked form is the better one even where nothing is masked: its branches keep the
-    // compiler from interleaving the groups until registers spill)
-    if constexpr (NKB <= 2) {
-        if (p.S == 64 * NKB) return launch_short<NKB, true, kMode>(p, tables, st);
+    if (p.nch != 4) return launch_short<kParts, NG, false, kMode, false>(p, tables, st);
+    if constexpr (kMode != EXP_ANY) {
+        if (p.S == 64 * kParts * NG) return launch_short<kParts, NG, true, kMode, true>(p, tables, st);
     }
-    return launch_short<NKB, false, kMode>(p, tables, st);
+    return launch_short<kParts, NG, false, kMode, true>(p, tables, st);
 }
 
 template <int kMode>
 static int32_t launch_mode(AttnParams& p, int pairs, hipStream_t st)
 {
-    const size_t tables = sizeof(float2) * ((size_t)p.t_exp.nseg + 1 + (size_t)p.t_recip.nseg);
-    if (p.nch != 4 || p.S > 512) {
-        p.qblocks = (p.S + kLongThreads / 4 - 1) / (kLongThreads / 4);
-        p.total = p.qblocks * pairs;
-        return launch_long<kMode>(p, tables, st);
+    const size_t tables = (attn_exp_bytes(kMode, p.t_exp.nseg) + sizeof(float2) * (size_t)p.t_recip.nseg + 255) & ~(size_t)255;
+    p.off_tile = (int)tables;
+    static_assert(kLongThreads / 4 == 64, "queries per workgroup");
+    p.qblocks = (p.S + 63) / 64;
+    p.total = p.qblocks * pairs;
+    const int parts = attn_parts(p.S), ng = (p.S + 64 * parts - 1) / (64 * parts);
+    if (p.S > 1024 || attn_lds_bytes(parts, ng) + tables > 160 * 1024) return launch_long<kMode>(p, tables, st);
+    if (parts == 1) {
+        if (ng == 1) return launch_groups<1, 1, kMode>(p, tables, st);
+        if (ng == 2) return launch_groups<1, 2, kMode>(p, tables, st);
+        if (ng == 3) return launch_groups<1, 3, kMode>(p, tables, st);
+        return launch_groups<1, 4, kMode>(p, tables, st);
     }
-    if (p.S <= 64) return launch_nkb<1, kMode>(p, pairs, tables, st);
-    if (p.S <= 128) return launch_nkb<2, kMode>(p, pairs, tables, st);
-    if (p.S <= 256) return launch_nkb<4, kMode>(p, pairs, tables, st);
-    return launch_nkb<8, kMode>(p, pairs, tables, st);
+    if (parts == 2) return ng == 3 ? launch_groups<2, 3, kMode>(p, tables, st) : launch_groups<2, 4, kMode>(p, tables, st);
+    return ng == 3 ? launch_groups<4, 3, kMode>(p, tables, st) : launch_groups<4, 4, kMode>(p, tables, st);
 }
 
 bool fused_attention_covers(int S, int H, int heads)
@@ -700,13 +793,11 @@ int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
     double vmin, vmax;
     table_value_bounds(a.tables, a.exp_idx, a.alpha_scores >= 0 ? -reach : 0.0, a.alpha_scores >= 0 ? 0.0 : reach, &vmin, &vmax);
     p.e_lo = (float)vmin; p.e_hi = (float)vmax;
-    // index of t = 0 by the kernel's own arithmetic
-    const float d0 = 0.0f - p.t_exp.lo, u_at_0 = d0 * p.t_exp.inv_w;
-    const bool padded = a.alpha_scores >= 0.0f && !p.t_exp.clamp_input && u_at_0 < (float)(p.t_exp.nseg + 1);
+    const bool slots = a.alpha_scores >= 0.0f && t_exp.slots;
     const int pairs = a.B * a.heads;
-    if (!padded || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
-    else if (t_exp.pow2) rc = launch_mode<EXP_PADDED_POW2>(p, pairs, st);
-    else rc = launch_mode<EXP_PADDED>(p, pairs, st);
+    if (!slots || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
+    else if (t_exp.slots == SLOTS_POW2) rc = launch_mode<EXP_SLOTS_POW2>(p, pairs, st);
+    else rc = launch_mode<EXP_SLOTS>(p, pairs, st);
     if (rc) return rc;
     return check_hip(hipGetLastError(), "attention launch");
 }

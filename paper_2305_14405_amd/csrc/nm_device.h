@@ -88,6 +88,67 @@ __device__ __forceinline__ float pwl_eval_two_segments(float x, const Table& t)
     return x >= t.tau ? y1 : y0;
 }
 
+// ---- instructions at twice the rate -----------------------------------------------------------------
+// With two or more wavefronts on a SIMD, gfx950 issues a vector instruction every 2.2 clocks, but of most kinds only one every
+// 4.2: conversions, minima, maxima and medians, shifts to the left, byte permutes, three-operand integer arithmetic, and
+// anything with a scalar register among its operands.  Free of that are fp32 additions, multiplications and fused
+// multiply-adds (their clamp to [0, 1] and literals included), 32-bit logic, integer additions, shifts to the right and moves.
+// (Measured on 256 CUs, clocks per instruction and SIMD: v_mul_f32, v_fma_f32, v_fmaak_f32, v_add_u32, v_and_b32 2.2 .. 2.5;
+// v_mul_f32 with an SGPR, v_med3_f32, v_cvt_u32_f32, v_lshlrev_b32, v_lshl_add_u32, v_perm_b32, v_cvt_pk_u8_f32 4.2; both kinds in
+// turn 2.2.  A single wavefront issues any of them every 5.)  A loop's time is thus 2.2 clocks an instruction or 4.2 for
+// each of the slower kind, whichever is more.
+//
+// A uniform value in a vector register (opaque, so that no scalar register is put in its place).
+__device__ __forceinline__ float in_vgpr(float x)
+{
+    float v;
+    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(x));
+    return v;
+}
+// clamp(a * b + c, 0, 1) and clamp(a * b, 0, 1), rounded once in front of the clamp; a NaN becomes 0.
+__device__ __forceinline__ float fma_clamp01(float a, float b, float c)
+{
+    float v;
+    asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(v) : "v"(a), "v"(b), "v"(c));
+    return v;
+}
+__device__ __forceinline__ float mul_clamp01(float a, float b)
+{
+    float v;
+    asm("v_mul_f32 %0, %1, %2 clamp" : "=v"(v) : "v"(a), "v"(b));
+    return v;
+}
+
+// A table of at most 256 segments as 512 slots of eight bytes in LDS, found by three of the faster instructions instead of four
+// of the others (multiply with a scalar, clamp, convert, shift): with the position u' = u / 256 clamped to [0, 1] (the scaling is exact),
+// 2048 u' + (2^23 - 0.5), rounded once, has in its low bits the integer nearest to 8 u - 0.5, which lies in
+// [8 s, 8 s + 7] for every u in segment s (a tie at 8 s - 0.5 goes to the even 8 s): bits 3 .. 11 are the slot.  u below 1/16
+// leaves the sum below 2^23, in the binade whose low bits then read all ones: slot 511 is segment 0 again.  Slots from nseg
+// to 256 (u' = 1) hold the last segment.
+constexpr int kTableSlots = 2 * kSlotSegments;
+constexpr size_t kSlotBytes = kTableSlots * sizeof(float2);
+__device__ __forceinline__ unsigned slot_offset(float u, float steps)   // steps: 2048 in a vector register
+{
+    float x;
+    asm("v_fmaak_f32 %0, %1, %2, 0x4affffff" : "=v"(x) : "v"(u), "v"(steps));   // 8388607.5
+    return __float_as_uint(x) & 0xff8u;
+}
+// The line at an offset into LDS as a whole, which the kernel's dynamic array begins (it has no other object there); added to that
+// array's address, which only the linker knows to be 0, the offset would cost an instruction more.
+__device__ __forceinline__ float2 slot_line(unsigned offset)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f e = *reinterpret_cast<const __attribute__((address_space(3))) v2f*>(offset);
+    return make_float2(e[0], e[1]);
+}
+// The table into its slots, by kSlotSegments threads or more: thread i < kSlotSegments has entry min(i, nseg - 1).
+__device__ __forceinline__ void write_slots(float2* s_kb, float2 entry, int i)
+{
+    if (i < kSlotSegments) s_kb[i] = entry;
+    if (i == kSlotSegments - 1) s_kb[kSlotSegments] = entry;
+    if (i == 0) s_kb[kTableSlots - 1] = entry;
+}
+
 // Symmetric int8 code: round-to-nearest-even of v * inv_scale, saturated to [-127, 127].
 // Returns a word whose LOW BYTE is the code (the other bytes are not meaningful): saturate first
 // (the bounds are integers and rounding is monotone, so clamp and round commute), then add

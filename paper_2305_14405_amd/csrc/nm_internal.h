@@ -34,7 +34,12 @@ struct DevTable {
     // (scaling by a power of two commutes with rounding)
     int pow2;
     float u0;
+    int slots;   // TableSlots: whether the kernels may look the table up by slots
 };
+// nm_device.h has the look-up: tables of at most 256 segments without the clamp flag whose scaled numbers are exact; SLOTS_POW2: with
+// the position by one fma.
+enum TableSlots { SLOTS_NONE = 0, SLOTS_ANY = 1, SLOTS_POW2 = 2 };
+constexpr int kSlotSegments = 256;
 
 // Division by a number the host knows: exact for every n below 2^31 (Granlund and Montgomery, "Division by invariant
 // integers using multiplication", 1994: a multiplier of 32 bits does for dividends of 31).
@@ -82,6 +87,7 @@ struct HostTable {
     float tau = 0.0f;         // two segments: the smallest value of segment 1
     int pow2 = 0;
     float u0 = 0.0f;
+    int slots = 0;
     TableBounds bounds{};
 };
 

@@ -91,6 +91,11 @@ static void derive_table(HostTable& h)
     const float u0 = -d.lo * h.inv_w;
     h.pow2 = std::frexp(h.inv_w, &e) == 0.5f && std::isnormal(h.inv_w) && std::isfinite(u0) && (u0 == 0.0f || std::isnormal(u0));
     h.u0 = h.pow2 ? u0 : 0.0f;
+    // 1/kSlotSegments of the numbers has to be exact
+    const auto scales = [](float v) { return std::isnormal(v) && std::fabs(v) >= kSlotSegments * std::numeric_limits<float>::min(); };
+    h.slots = SLOTS_NONE;
+    if (d.nseg <= kSlotSegments && !(d.flags & NM_TABLE_CLAMP_INPUT) && scales(h.inv_w))
+        h.slots = h.pow2 && (u0 == 0.0f || scales(u0)) ? SLOTS_POW2 : SLOTS_ANY;
     // a segment's line is monotone, so its extremes are at the segment's ends; the float index may put
     // values a few roundings outside the nominal segment into it
     const double w = ((double)d.hi - (double)d.lo) / d.nseg;
@@ -139,6 +144,7 @@ int32_t get_dev_table(const nm_tables* t, int32_t idx, DevTable* dt, const char*
     }
     dt->pow2 = h.pow2;
     dt->u0 = h.u0;
+    dt->slots = h.slots;
     if (two_level && !h.cellmap.empty()) {
         dt->ckb = t->d_blob + h.cblob_offset;
         dt->cellmap = reinterpret_cast<const uint8_t*>(t->d_blob + h.map_offset);

@@ -1013,8 +1013,7 @@ def test_fused_attention_table_and_requantisation_forms(oracle, S, nseg, inv_p, 
 
 @pytest.mark.parametrize("B,S,H,heads", [(1, 513, 64, 1), (1, 1030, 96, 2), (2, 70, 32, 2), (1, 256, 96, 3)])
 def test_encoder_layer_attention_of_long_sequences_and_small_heads(oracle, B, S, H, heads):
-    """Shapes of the attention kernel that computes its scores three times: more than 512 keys, head
-    sizes 64, 48, 16 and 32; with and without the intermediate tensors."""
+    """More than 512 keys and head sizes 64, 48, 16 and 32; with and without the intermediate tensors."""
     cfg = dict(B=B, S=S, H=H, heads=heads, F=2 * H, nseg=64)
     p = W.with_scales(W.layer_tensors(cfg, 5), W.stored_scales("long_seq", 0))
     ot, dt = both_tables(oracle, [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")])
@@ -1066,8 +1065,8 @@ def check_layer_attention(oracle, p, ot, dt, with_taps):
 @pytest.mark.parametrize("B,S,H,heads,inv_p", [(1, 513, 64, 1, None), (1, 700, 96, 2, None), (2, 200, 32, 2, None),
                                                (1, 1024, 64, 1, 30000.0), (1, 529, 128, 2, 30000.0)])
 def test_encoder_layer_long_attention_saturating_codes(oracle, B, S, H, heads, inv_p):
-    """The attention kernel that computes its scores three times, where codes saturate: in every wavefront, or
-    (inv_p None) in some wavefronts of a workgroup of 64 queries and not in others."""
+    """Long sequences and small heads where codes saturate: in every wavefront, or (inv_p None) in some wavefronts of a
+    workgroup of 64 queries and not in others."""
     cfg, p = sharp_layer(B, S, H, heads, inv_p or 127.0)
     specs = [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")]
     ot, dt = both_tables(oracle, specs)
@@ -1081,6 +1080,22 @@ def test_encoder_layer_long_attention_saturating_codes(oracle, B, S, H, heads, i
     for with_taps in (False, True):
         want = check_layer_attention(oracle, p, ot, dt, with_taps)
     assert (want["p"] == 127).any() and (want["p"] < 127).any()
+
+
+@pytest.mark.parametrize("S,H,heads,nseg", [(65, 32, 1, 64), (129, 96, 2, 100), (192, 64, 1, 256), (193, 64, 2, 64), (257, 64, 1, 64),
+                                           (272, 32, 1, 16), (273, 64, 1, 100), (384, 64, 1, 64), (385, 64, 1, 256), (400, 96, 2, 64),
+                                           (512, 32, 2, 257), (528, 64, 1, 64), (577, 96, 2, 100), (768, 64, 1, 64), (769, 32, 1, 64),
+                                           (1000, 64, 1, 256), (1023, 16, 1, 64), (1024, 64, 1, 100), (1025, 64, 1, 64), (1100, 32, 1, 100)])
+def test_encoder_layer_attention_divided_over_wavefronts(oracle, S, H, heads, nseg):
+    """Every division of a query's keys over wavefronts (1, 2 or 4 parts of up to four groups of 16-key blocks; the kernel that
+    computes its scores three times beyond 1024), at its first and last length and with blocks that one part has and
+    another has not, head sizes 16 to 64, exp tables in slots (segment widths that are and are not a power of two) and too
+    long for them."""
+    p = sharp_layer(1, S, H, heads, 300.0)[1]
+    specs = [("gelu", -8.0, 8.0, 64), ("exp", -16.0, 0.0, nseg), ("recip", 1.0, float(max(64, S)), 128), ("rsqrt", 1e-3, 64.0, 64)]
+    ot, dt = both_tables(oracle, specs)
+    for with_taps in (False, True):
+        check_layer_attention(oracle, p, ot, dt, with_taps)
 
 
 def spoil(table, kind, at=0):
@@ -1138,7 +1153,7 @@ def test_fused_attention_masked_keys_where_numbers_are_not_finite(oracle, S, kin
 @pytest.mark.parametrize("kind", ["nan", "inf", "some_rows"])
 @pytest.mark.parametrize("B,S,H,heads", [(1, 513, 64, 1), (1, 700, 96, 2), (2, 70, 32, 2), (1, 40, 96, 3)])
 def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(oracle, B, S, H, heads, kind):
-    """The same in the kernel that computes its scores three times."""
+    """The same for long sequences and small heads."""
     cfg, p = sharp_layer(B, S, H, heads, 10000.0)
     specs = [W.table_ranges(cfg)[n] for n in ("gelu", "exp", "recip", "rsqrt")]
     ot = [oracle.build_table(OID[f], lo, hi, n) for (f, lo, hi, n) in specs]
