@@ -760,6 +760,11 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         if (rc) return rc;
         return check_hip(hipGetLastError(), "gemm + LayerNorm launch");
     }
+    // A merged table kept in two levels is looked up in its expanded form where the results are int8 codes alone: one look-up
+    // instead of two, and the fixed epilogues (4096 x 3072 x 768: 16.9 us in two levels in the tile kernel, 15.6 expanded).
+    const bool only_q = g.out_q && !g.out_f32 && !g.out_acc;
+    DevTable table = g.table;
+    if (only_q && !g.resid && !g.out_inv_scale_vec && !g.dbg_seg && !table.clamp_input) table.cellmap = nullptr;
     GemmParams p{};
     p.M = g.M; p.N = g.N; p.K = g.K;
     p.A = g.A; p.lda = g.lda; p.W = g.W; p.ldw = g.ldw;
@@ -768,7 +773,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     p.o_outer = g.o_outer; p.o_inner = g.o_inner;
     p.bias = g.bias; p.alpha_vec = g.alpha_vec; p.alpha = g.alpha;
     p.resid = g.resid; p.resid_scale = g.resid_scale;
-    p.has_table = g.has_table; p.table = g.table;
+    p.has_table = g.has_table; p.table = table;
     p.out_inv_scale = g.out_inv_scale; p.out_inv_scale_vec = g.out_inv_scale_vec;
     p.split_cols = g.split_cols;
     p.relu = g.has_table && g.split_cols == 0 && !g.out_inv_scale_vec && relu_codes(g.table, g.out_inv_scale, g.resid ? g.resid_scale : 0.0f);
@@ -792,16 +797,14 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // LDS bytes of the table: {k, b} per segment, or for the two-level form of a merged table one
     // {k, b} per merged segment plus a byte per primary cell
     const size_t table_bytes = !g.has_table ? 0
-                             : g.table.cellmap ? two_level_bytes(g.table)
-                                               : sizeof(float2) * (size_t)g.table.nseg;
+                             : table.cellmap ? two_level_bytes(table) : sizeof(float2) * (size_t)table.nseg;
     const int batches = g.outer_count * g.inner_count;
     if (batches > 65535) return fail(NM_ERR_UNSUPPORTED, "gemm: more than 65535 batched problems");
     int32_t rc = NM_OK;
     p.vec_cols = (!g.bias || aligned(g.bias, 16)) && (!g.alpha_vec || aligned(g.alpha_vec, 16)) &&
                  (!g.out_inv_scale_vec || aligned(g.out_inv_scale_vec, 16));
     int epi = EPI_GENERIC;
-    if (!g.out_inv_scale_vec && !g.dbg_seg && !(g.has_table && g.table.cellmap)) {
-        const bool only_q = g.out_q && !g.out_f32 && !g.out_acc;
+    if (!g.out_inv_scale_vec && !g.dbg_seg && !(g.has_table && table.cellmap)) {
         // EPI_Q_TABLE is compiled without the input clamp; a table with that flag takes the generic epilogue
         if (only_q && !g.resid) epi = !g.has_table ? EPI_Q : g.table.clamp_input ? EPI_GENERIC : EPI_Q_TABLE;
         else if (g.out_f32 && !g.out_q && !g.out_acc && g.resid && !g.has_table && p.vec_out) epi = EPI_F32_RESID;
@@ -838,13 +841,8 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     if (g.conv && (!w_al || !aligned(g.A, 16) || g.cCin % 64 != 0 || g.K % (g.cCin * g.cKw) != 0))
         return fail(NM_ERR_UNSUPPORTED, "conv gemm: operands not aligned for the gathered loader");
     const bool stream_ok = al && !g.conv && !g.w_is_kn && g.K % 64 == 0 && !force_generic();
-    // The tile kernel: plain matrix products with the encoder layer's epilogues;
-    // int8 output through a merged table kept in two levels: the tile kernel has an epilogue for it
-    // (elsewhere the generic one looks it up)
-    const bool two_level_q = g.has_table && g.table.cellmap && !g.table.clamp_input && g.out_q && !g.out_f32 &&
-                             !g.out_acc && !g.resid && !g.out_inv_scale_vec && !g.dbg_seg && g.table.nkb <= 256 &&
-                             g.table.nseg <= 1024;
-    const bool tile_epi = (epi == EPI_Q || epi == EPI_Q_TABLE || two_level_q) ? p.q16 != 0
+    // The tile kernel: plain matrix products with the encoder layer's epilogues
+    const bool tile_epi = (epi == EPI_Q || epi == EPI_Q_TABLE) ? p.q16 != 0
                         : epi == EPI_F32_RESID ? (p.r16 != 0 && aligned(g.out_f32, 16) && g.ldo % 4 == 0) : false;
     const bool tile_ok = stream_ok && tile_epi && batches == 1 && g.K % 128 == 0 && g.K / 128 >= 3 && !g.alpha_vec &&
                          g.N % 16 == 0 && g.split_cols % 4 == 0 && (int64_t)g.M * g.lda < (1LL << 32) &&
@@ -933,27 +931,27 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         else if (forced.kind == FORCED_TILE) tile_cfg = forced.number;
         else if (forced.number == STREAM_BIG) tile_cfg = 1;
     }
-    if (tile_cfg >= 0 && two_level_q) epi = EPI_Q_TABLE2;
+    const size_t tile_table = table.slots ? 0 : table_bytes;   // (slots are part of the kernel's own LDS)
     if (tile_cfg == 0) {
-        rc = launch_tile<256, 256, 2, 4, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 256, 2, 4, 2>(p, epi, tile_table, stream);
     } else if (tile_cfg == 1) {
-        rc = launch_tile<256, 192, 4, 2, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 192, 4, 2, 2>(p, epi, tile_table, stream);
     } else if (tile_cfg == 2) {
-        rc = launch_tile<256, 128, 4, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<256, 128, 4, 2, 3>(p, epi, tile_table, stream);
     } else if (tile_cfg == 3) {
-        rc = launch_tile<128, 192, 2, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 192, 2, 2, 3>(p, epi, tile_table, stream);
     } else if (tile_cfg == 4) {
-        rc = launch_tile<128, 192, 2, 2, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 192, 2, 2, 2>(p, epi, tile_table, stream);
     } else if (tile_cfg == 5) {
-        rc = launch_tile<128, 128, 2, 2, 3, OUT_INT8>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 128, 2, 2, 3, OUT_INT8>(p, epi, tile_table, stream);
     } else if (tile_cfg == 6) {
-        rc = launch_tile<128, 128, 2, 2, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 128, 2, 2, 2>(p, epi, tile_table, stream);
     } else if (tile_cfg == 7) {
-        rc = launch_tile<64, 128, 2, 2, 3>(p, epi, table_bytes, stream);
+        rc = launch_tile<64, 128, 2, 2, 3>(p, epi, tile_table, stream);
     } else if (tile_cfg == 8) {
-        rc = launch_tile<64, 128, 2, 2, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<64, 128, 2, 2, 2>(p, epi, tile_table, stream);
     } else if (tile_cfg == 9) {
-        rc = launch_tile<128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, table_bytes, stream);
+        rc = launch_tile<128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, tile_table, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

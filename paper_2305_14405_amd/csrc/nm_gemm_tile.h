@@ -34,14 +34,15 @@ namespace nm {
 // 5 launch and prologue; the k-loop runs at the rate the card's power allows (all operands zero: 54 us
 // with the same instructions; operand rows that all lie in L2: no change).  256x128 tiles there: 72 us, because
 // a slice then needs 47 bytes per matrix clock and CU through the direct loads, which deliver about 40 (256x256: 32).
-// With short K the epilogue is the larger part: 12 vector instructions per element with the table (11 where its segments'
-// width is a power of two), 6 without.
+// With short K the epilogue is the larger part: 10 vector instructions per element with the table, 6 without.
 // ---------------------------------------------------------------------------------------------
 // LDS that the epilogue lays over the ring: the wavefronts' int8 row patches, or the residual tile and the
 // wavefronts' fp32 row patches, then the bias and the table.
+// In front of the int8 patches of EPI_Q_TABLE lie the table's slots, so that a slot's offset is its address.
 constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
 {
-    return epi == EPI_Q_RELU_RESID ? bm * (bn + 16)
+    return epi == EPI_Q_TABLE ? (int)kSlotBytes + nw * wm * (wn + 16)
+         : epi == EPI_Q_RELU_RESID ? bm * (bn + 16)
          : epi == EPI_F32_RESID_LN ? bm * (bn + 16) + (bm * 64 + 2 * bm) * 4
          : epi == EPI_F32_RESID ? bm * (bn + 16) + nw * 32 * (wn + 4) * 4 : nw * wm * (wn + 16);
 }
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     constexpr int DPS = (LB + POST + NMF - 1) / (POST + NMF);  // refill loads per slot (those slots and the next k-step's)
     static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole blocks");
     static_assert(TN >= 2 && KS % 2 == 0 && TM % KSPLIT == 0, "wavefront tile");
-    constexpr bool kTable = kEpi == EPI_Q_TABLE || kEpi == EPI_Q_TABLE2;
+    constexpr bool kTable = kEpi == EPI_Q_TABLE;
     constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
     static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
                   "epilogues of the tile kernel");
@@ -185,22 +186,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         bias_reg[t] = (p.bias && c < BN && n0 + c < p.N) ? p.bias[n0 + c] : 0.0f;
         if (kRelu) scale_reg[t] = (p.alpha_vec && c < BN && n0 + c < p.N) ? p.alpha_vec[n0 + c] : p.alpha;
     }
-    constexpr int KPT = 4;  // table entries per thread held in registers (more are staged late)
-    float2 kb_reg[KPT];
-    if (kEpi == EPI_Q_TABLE) {
-#pragma unroll
-        for (int t = 0; t < KPT; ++t) {
-            const int e = tid + t * 64 * NW;
-            kb_reg[t] = e < p.table.nseg ? p.table.kb[e] : make_float2(0.0f, 0.0f);
-        }
-    }
-    // two-level form: at most 256 merged segments and 256 cells (host), i.e. one {k, b} pair and one
-    // word of four cell bytes per thread at most
-    unsigned map_reg = 0;
-    if (kEpi == EPI_Q_TABLE2) {
-        kb_reg[0] = tid < p.table.nkb ? p.table.ckb[tid] : make_float2(0.0f, 0.0f);
-        if (tid < (p.table.nseg + 3) / 4) map_reg = reinterpret_cast<const unsigned*>(p.table.cellmap)[tid];
-    }
+    static_assert(!kTable || 64 * NW >= kSlotSegments, "a slot per thread");
+    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry per thread held in a register (more are staged late)
+    if (kTable) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
 
     // the int8 residual tile (fp32 epilogue) as 16-byte row pieces
     constexpr int CPRW = BN / 16;
@@ -364,18 +352,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         if (c < BN) s_bias[c] = bias_reg[t];
         if (kRelu && c < BN) s_scale[c] = scale_reg[t];
     }
-    if (kEpi == EPI_Q_TABLE) {
-#pragma unroll
-        for (int t = 0; t < KPT; ++t) {
-            const int e = tid + t * 64 * NW;
-            if (e < p.table.nseg) s_kb[e] = kb_reg[t];
+    if (kTable) {
+        if (p.table.slots) write_slots(reinterpret_cast<float2*>(smem), kb_reg, tid);
+        else {
+            if (tid < p.table.nseg) s_kb[tid] = kb_reg;
+            for (int e = tid + 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
         }
-        for (int e = tid + KPT * 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
-    }
-    const uint8_t* s_map = reinterpret_cast<const uint8_t*>(s_kb + p.table.nkb);  // cell -> merged segment
-    if (kEpi == EPI_Q_TABLE2) {
-        if (tid < p.table.nkb) s_kb[tid] = kb_reg[0];
-        if (tid < (p.table.nseg + 3) / 4) reinterpret_cast<unsigned*>(s_kb + p.table.nkb)[tid] = map_reg;
     }
     constexpr int RW = BN + 16;  // row stride of the residual image
     int8_t* s_res = smem;        // in the ring, which is free now
@@ -389,7 +371,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     __syncthreads();
 
     // ---- epilogue -----------------------------------------------------------------------------
-    const float alpha = p.alpha;
+    // uniform factors in vector registers: with a scalar operand an instruction issues at half the rate
+    const float alpha = in_vgpr(p.alpha);
     const bool full = m0 + BM <= p.M && n0 + BN <= p.N;
     v4f bi[TN][4];
 #pragma unroll
@@ -399,9 +382,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     constexpr int NG = ETM * TN * 4;  // groups of four columns per lane
     if constexpr (kTable || kEpi == EPI_Q) {
         constexpr int SW = WN + 16;
-        static_assert(NW * EM * SW <= STAGES * STAGE_BYTES, "patch fits the ring");
-        int8_t* patch = smem + wave * (EM * SW);
+        constexpr int kAt = kTable ? (int)kSlotBytes : 0;
+        static_assert(kAt + NW * EM * SW <= STAGES * STAGE_BYTES, "patch fits the ring");
+        int8_t* patch = smem + kAt + wave * (EM * SW);
         // inverse output scale of a group (the QKV projection has one per column third)
+        const float inv_all = in_vgpr(p.out_inv_scale);
         float inv_g[TN][4];
 #pragma unroll
         for (int j = 0; j < TN; ++j)
@@ -409,34 +394,36 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             for (int g = 0; g < 4; ++g) {
                 const int n = n0 + wave_n + 32 * j + 8 * g + 4 * frag_half;
                 inv_g[j][g] = p.split_cols > 0 ? (n >= 2 * p.split_cols ? p.inv3[2] : n >= p.split_cols ? p.inv3[1] : p.inv3[0])
-                                               : p.out_inv_scale;
+                                               : inv_all;
             }
         constexpr int DEPTH = 3;
         float x[DEPTH + 1][4];
         float2 kb[DEPTH + 1][4];
-        const float tlo = p.table.lo, tiw = p.table.inv_w, tu0 = p.table.u0, tmax = (float)(p.table.nseg - 1);
         // group index -> (i, j, g), i innermost: consecutive groups use different accumulators
-        // pow2: the segment's position by one fma (the same bits: DevTable); 8192 x 3072 x 768 30.2 -> 28.6 us, 4096 x
-        // 3072 x 768 16.3 -> 16.0
-        auto finish = [&](auto pow2_c) {
-        constexpr bool kPow2 = decltype(pow2_c)::value;
+        // form: the table in slots (nm_device.h), with the position by one fma (SLOTS_POW2) or two steps (SLOTS_ANY); SLOTS_NONE: more
+        // than 256 segments.  Of an element's eleven instructions nine issued at half the rate (scalar operands, clamp, conversions,
+        // shift), now two and a half of ten.  us, before -> after: 4096 x 3072 x 768 16.3 -> 16.1, 8192 x 3072 x 768 29.3 -> 28.9,
+        // 16384 x 4096 x 1024 85.8 -> 85.0, with 100 segments 87.4 -> 85.0 (the card's power limits that one); a base stack
+        // over 16 x 512 tokens 0.4 % less, a large one over 32 x 512 1 %.
+        auto finish = [&](auto form_c) {
+        constexpr int kForm = decltype(form_c)::value;
+        constexpr float kPart = kForm == SLOTS_NONE ? 1.0f : 1.0f / kSlotSegments;
+        const float tlo = in_vgpr(p.table.lo), tiw = in_vgpr(p.table.inv_w * kPart), tu0 = in_vgpr(p.table.u0 * kPart);
+        const float steps = in_vgpr(8.0f * kSlotSegments), tmax = (float)(p.table.nseg - 1);
         auto stage_a = [&](int G) {
             const int i = G % ETM, jg = G / ETM, j = jg / 4, g = jg % 4;
-            unsigned cellv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float v = __builtin_fmaf((float)sum(i, j)[4 * g + e], alpha, bi[j][g][e]);
                 x[G % (DEPTH + 1)][e] = v;
-                if (kTable) {  // segment of v (subtract, multiply, clamp in float, floor)
-                    float u = kPow2 ? __builtin_fmaf(v, tiw, tu0) : (v - tlo) * tiw;
-                    u = __builtin_amdgcn_fmed3f(u, 0.0f, tmax);
-                    if (kEpi == EPI_Q_TABLE2) cellv[e] = s_map[(int)u];
-                    else kb[G % (DEPTH + 1)][e] = s_kb[(int)u];
+                if (!kTable) continue;
+                if (kForm == SLOTS_NONE) {  // subtract, multiply, clamp in float, floor
+                    const float u = __builtin_amdgcn_fmed3f((v - tlo) * tiw, 0.0f, tmax);
+                    kb[G % (DEPTH + 1)][e] = s_kb[(int)u];
+                } else {
+                    const float u = kForm == SLOTS_POW2 ? fma_clamp01(v, tiw, tu0) : mul_clamp01(v - tlo, tiw);
+                    kb[G % (DEPTH + 1)][e] = slot_line(slot_offset(u, steps));
                 }
-            }
-            if (kEpi == EPI_Q_TABLE2) {  // second level: the four cell bytes have been requested together
-#pragma unroll
-                for (int e = 0; e < 4; ++e) kb[G % (DEPTH + 1)][e] = s_kb[cellv[e]];
             }
         };
         auto stage_b = [&](int G) {
@@ -459,7 +446,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             __builtin_amdgcn_sched_barrier(0);
         }
         };
-        if (kTable && p.table.pow2) finish(std::true_type{}); else finish(std::false_type{});
+        if (kTable && p.table.slots == SLOTS_POW2) finish(std::integral_constant<int, SLOTS_POW2>{});
+        else if (kTable && p.table.slots == SLOTS_ANY) finish(std::integral_constant<int, SLOTS_ANY>{});
+        else finish(std::integral_constant<int, SLOTS_NONE>{});
         // the wavefront reads back the rows it wrote: order its LDS writes before its reads
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -544,7 +533,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         constexpr int PW = WN + 4, LPR = WN / 4, NST = 32 * LPR / 64;
         static_assert(32 * LPR % 64 == 0, "pieces split evenly");
         float* patch = reinterpret_cast<float*>(smem + BM * RW) + wave * 32 * PW;
-        const float rs = p.resid_scale;
+        const float rs = in_vgpr(p.resid_scale);
 #pragma unroll
         for (int i = 0; i < ETM; ++i) {
 #pragma unroll
@@ -693,7 +682,7 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
     constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
     constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M / KSPLIT, BN / WAVES_N, kEpi);
     static_assert(kFront % 16 == 0 && kFront + BN * 4 <= 160 * 1024 && kRing <= 160 * 1024, "LDS");
-    const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;
+    const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;   // (table_bytes: 0 for a table in slots)
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {
@@ -719,7 +708,6 @@ static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream
     if constexpr (kOut != OUT_F32) {
         if (epi == EPI_Q) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT>(p, table_bytes, s);
         if (epi == EPI_Q_TABLE) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT>(p, table_bytes, s);
-        if (epi == EPI_Q_TABLE2) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE2, 128, false, KSPLIT>(p, table_bytes, s);
     }
     if constexpr (kOut != OUT_INT8) {
         if (epi == EPI_F32_RESID) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT>(p, table_bytes, s);

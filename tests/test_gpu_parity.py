@@ -332,6 +332,23 @@ def test_two_level_table_in_the_tile_kernel_sampled(oracle, M, N, K, nprim, dk):
     assert len(np.unique(s)) > 5
 
 
+@pytest.mark.parametrize("lo,hi,nseg", [(-8.0, 8.0, 1), (-8.0, 8.0, 2), (-8.0, 8.0, 128), (-8.0, 8.0, 256), (-8.0, 8.0, 257), (-6.0, 7.0, 100),
+                                        (-5.0, 8.0, 255), (0.5, 3.0, 37), (-8.0, 8.0, 1024)])
+def test_table_forms_of_the_tile_kernel(oracle, lo, hi, nseg):
+    """Tables in slots (up to 256 segments, their width a power of two or not) and beyond in the tile kernel's epilogue, values
+    in every segment and past both ends, ragged edges."""
+    M, N, K = 1100, 1008, 384
+    ot, dt = both_tables(oracle, [("gelu", lo, hi, nseg)])
+    d = W.gemm_inputs(M, N, K, seed=nseg, full_range=False)
+    alpha = float(np.float32(0.8 * max(abs(lo), hi) / (20 * 20 * np.sqrt(K))))
+    r = oracle.gemm_pwl(d["A"], d["W"], bias=d["bias"], alpha=alpha, table=ot[0], out_inv_scale=25.0)
+    q = torch.full((M + 1, N), 77, dtype=torch.int8, device=DEV)
+    nm.nm_gemm_pwl(dev(d["A"]), dev(d["W"]), bias=dev(d["bias"]), alpha=alpha, tables=dt, table_idx=0, out_inv_scale=25.0, out_q=q, M=M)
+    got = host(q)
+    assert_exact(got[:M], r["q"], f"{nseg} segments on [{lo}, {hi}]")
+    assert np.all(got[M] == 77)
+
+
 def test_two_level_table_limits():
     """More than 256 merged segments do not fit the byte map; the other entry points use a two-level
     table's expanded form (same results)."""
