@@ -257,6 +257,24 @@ inline int choose_unaligned(int M, int N, int K, bool q, bool f32, bool table, b
     return cfg;
 }
 
+// Whether a product makes the LayerNorm in front of it, and with which tile of nm_gemm_ln.hip (16x32, 16x64, 16x128), or -1: as two
+// kernels.  The narrowest tile whose workgroups a single round of the 256 CUs holds: a wider one repeats less of the LayerNorm but
+// leaves CUs idle, and a second round costs more than the launch it saves.  us of GPU time, one kernel less two, 16x32 | 16x64 |
+// 16x128 with the workgroups of each, weights from memory:
+//    64 x 1152 x  384   144 -1.3 |  72 -1.3 |  36 -1.0       128 x 2304 x 768   576      | 288 +1.5 | 144 -0.6
+//    64 x 2560 x  640   320 +1.1 | 160 -1.4 |  80 -1.1       128 x 4096 x 1024 1024      | 512 +2.3 | 256 -0.2
+//   200 x 2560 x  640            | 520 +3.1 | 260 +1.6       256 x 2048 x 512            | 512 +0.4 | 256 -0.4
+//   200 x 3072 x  768                       | 312 +2.4       384 x 1152 x 384                       | 216 -0.9
+// Launches of their own are 3.1 us of host time each as well, which is what narrow layers of few rows wait for: nine layers of
+// width 384 over 64 tokens 25.5 us a layer, 4.8 less by either product.
+inline int ln_gemm_tile(int M, int N)
+{
+    const long rows = (M + 15) / 16;
+    for (int t = 0; t < 3; ++t)
+        if (rows * ((N + (32 << t) - 1) / (32 << t)) <= 256) return t;
+    return -1;
+}
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

@@ -179,6 +179,19 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // True when launch_gemm would fold the LayerNorm described by g.ln_* into the GEMM kernel.
 bool gemm_folds_layernorm(const GemmArgs& g);
 
+// LayerNorm-PWL of M fp32 rows of K columns (the M and K of the product behind it), its int8 codes to out_q if given.
+struct LnRows {
+    const float* x = nullptr;
+    const float* gamma = nullptr;
+    const float* beta = nullptr;
+    float eps = 0.0f, inv_scale = 1.0f;
+    DevTable table{};
+    int8_t* out_q = nullptr;
+};
+// That and a product of the codes as one kernel (g.A is not read); tile: of ln_gemm_tile.
+bool ln_gemm_takes(const LnRows& n, const GemmArgs& g);
+int32_t launch_ln_gemm(const LnRows& n, const GemmArgs& g, int tile, hipStream_t stream);
+
 // The three attention steps as one kernel, for every shape fused_attention_covers accepts.
 struct AttnArgs {
     const int8_t* qkv;

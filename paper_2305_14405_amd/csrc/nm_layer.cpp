@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <mutex>
 
+#include "nm_gemm_choice.h"
 #include "nm_internal.h"
 
 namespace nm {
@@ -112,14 +113,39 @@ static int32_t static_scratch(void** out)
     return NM_OK;
 }
 
-// One layer.  next: the layer behind it in a stack (NULL: none), whose QKV projection may then be made by
-// this layer's last kernel: *qkv_ready says on entry whether the previous layer has done so for this one
-// (the projection is the first tensor of the workspace), on return whether this one has for the next.
-static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool* qkv_ready, const int8_t* x, int8_t* y_q,
+static GemmArgs qkv_args(const nm_layer_desc* d, const int8_t* x, int8_t* qkv)
+{
+    GemmArgs g;
+    g.M = d->B * d->S; g.N = 3 * d->H; g.K = d->H;
+    g.A = x; g.lda = d->H; g.W = d->Wqkv; g.ldw = d->H;
+    g.bias = d->bqkv; g.alpha = d->alpha_qkv;
+    g.split_cols = d->H; g.inv3[0] = d->inv_s_q; g.inv3[1] = d->inv_s_k; g.inv3[2] = d->inv_s_v;
+    g.ldo = 3L * d->H; g.out_q = qkv;
+    return g;
+}
+
+// The tile with which a product also makes the LayerNorm in front of it, or -1: as two kernels.
+static int ln_tile(const LnRows& n, const GemmArgs& g)
+{
+    const int tile = ln_gemm_tile(g.M, g.N);
+    return tile >= 0 && ln_gemm_takes(n, g) ? tile : -1;
+}
+
+// What a layer of a stack has left to the next one or done for it: its last LayerNorm, which the next one's QKV projection then makes
+// (the rows lie in the workspace behind that projection's result), or that projection itself, whose result is the first tensor of the
+// workspace.
+struct LayerCarry {
+    bool qkv_ready = false;
+    int ln_tile = -1;
+    LnRows ln;
+};
+
+// One layer.  next: the layer behind it in a stack (NULL: none).
+static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, LayerCarry* carry, const int8_t* x, int8_t* y_q,
                          float* y_f32, void* ws, size_t ws_bytes, const nm_layer_taps* taps, void* stream_)
 {
-    const bool have_qkv = *qkv_ready;
-    *qkv_ready = false;
+    const LayerCarry have = *carry;
+    *carry = LayerCarry();
     int32_t rc = validate_layer(d, "nm_encoder_layer", true);
     if (rc) return rc;
     if (!x) return fail(NM_ERR_INVALID_ARG, "nm_encoder_layer: x is NULL");
@@ -154,14 +180,9 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool
     float* ffn2 = (float*)pick(taps ? taps->ffn2 : nullptr, plan.off_ffn2);
 
     // 1: QKV projection, three output scales by column third
-    if (!have_qkv) {
-        GemmArgs g;
-        g.M = M; g.N = 3 * H; g.K = H;
-        g.A = x; g.lda = H; g.W = d->Wqkv; g.ldw = H;
-        g.bias = d->bqkv; g.alpha = d->alpha_qkv;
-        g.split_cols = H; g.inv3[0] = d->inv_s_q; g.inv3[1] = d->inv_s_k; g.inv3[2] = d->inv_s_v;
-        g.ldo = 3L * H; g.out_q = qkv;
-        if ((rc = launch_gemm(g, stream))) return rc;
+    if (!have.qkv_ready) {
+        const GemmArgs g = qkv_args(d, x, qkv);
+        if ((rc = have.ln_tile >= 0 ? launch_ln_gemm(have.ln, g, have.ln_tile, stream) : launch_gemm(g, stream))) return rc;
     }
     // 2-4: attention.  One fused kernel when the shape allows it (the scores and probabilities then
     // stay in registers; the taps, if given, still receive them), else three kernels.
@@ -189,18 +210,19 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool
     }
     // 5-9 as one kernel over blocks of rows, for narrow layers (no intermediate tensor then exists in memory)
     const bool block_taps = taps && (taps->attn || taps->ln1 || taps->ffn1 || taps->ffn2);
+    const nm_layer_desc* follow = next && next->Wqkv && validate_layer(next, "nm_encoder_stack", true) == NM_OK ? next : nullptr;
     if (!block_taps && !(d->flags & NM_LAYER_FOLD_LAYERNORM)) {
-        const nm_layer_desc* follow = next && next->Wqkv && validate_layer(next, "nm_encoder_stack", true) == NM_OK ? next : nullptr;
         bool done = false;
         if ((rc = launch_encoder_block(d, follow, ctx, x, y_q, y_f32, follow ? qkv : nullptr, stream, &done))) return rc;
         if (done) {
-            *qkv_ready = follow != nullptr;
+            carry->qkv_ready = follow != nullptr;
             return NM_OK;
         }
     }
     // 5: output projection + bias + residual(x) -> fp32;  6: LayerNorm-PWL -> int8.  One kernel when
     // the caller asks for it and the shape allows (the fp32 tensor then never reaches memory, so not
     // when its tap is wanted), else two.
+    bool ln1_done = false;
     const bool want_fold = (d->flags & NM_LAYER_FOLD_LAYERNORM) && !(d->flags & NM_LAYER_NO_FOLD_LAYERNORM);
     {
         GemmArgs g;
@@ -214,14 +236,12 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool
         if (want_fold && !(taps && taps->attn) && gemm_folds_layernorm(g)) {
             g.ln = 1;
             if ((rc = launch_gemm(g, stream))) return rc;
+            ln1_done = true;
         } else {
             if ((rc = launch_gemm(g, stream))) return rc;
-            if ((rc = launch_layernorm(attn, d->gamma1, d->beta1, d->eps1, M, H, t_rsqrt, d->inv_s_ln1, ln1,
-                                       nullptr, nullptr, stream)))
-                return rc;
         }
     }
-    // 7: FFN1 + bias, GELU-PWL in the epilogue -> int8
+    // 7: FFN1 + bias, GELU-PWL in the epilogue -> int8; for few rows it makes the LayerNorm too
     {
         GemmArgs g;
         g.M = M; g.N = F; g.K = H;
@@ -230,7 +250,16 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool
         g.has_table = 1; g.table = t_gelu;
         g.out_inv_scale = d->inv_s_ffn1;
         g.ldo = F; g.out_q = ffn1;
-        if ((rc = launch_gemm(g, stream))) return rc;
+        g.table.cellmap = nullptr;   // (the expanded form, as launch_gemm takes for int8 results)
+        const LnRows n{attn, d->gamma1, d->beta1, d->eps1, d->inv_s_ln1, t_rsqrt, ln1};
+        const int tile = ln1_done ? -1 : ln_tile(n, g);
+        if (tile >= 0) {
+            if ((rc = launch_ln_gemm(n, g, tile, stream))) return rc;
+        } else {
+            if (!ln1_done && (rc = launch_layernorm(attn, d->gamma1, d->beta1, d->eps1, M, H, t_rsqrt, d->inv_s_ln1, ln1, nullptr, nullptr, stream)))
+                return rc;
+            if ((rc = launch_gemm(g, stream))) return rc;
+        }
     }
     // 8: FFN2 + bias + residual(LN1 output) -> fp32;  9: LayerNorm-PWL -> layer output (one kernel or two, as above)
     {
@@ -247,6 +276,14 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, bool
             return launch_gemm(g, stream);
         }
         if ((rc = launch_gemm(g, stream))) return rc;
+    }
+    if (follow && y_q && !y_f32) {
+        const LnRows n{ffn2, d->gamma2, d->beta2, d->eps2, d->inv_s_out, t_rsqrt, y_q};
+        carry->ln_tile = ln_tile(n, qkv_args(follow, y_q, (int8_t*)(w + plan_layer(follow).off_qkv)));
+        if (carry->ln_tile >= 0) {
+            carry->ln = n;
+            return NM_OK;
+        }
     }
     return launch_layernorm(ffn2, d->gamma2, d->beta2, d->eps2, M, H, t_rsqrt, d->inv_s_out, y_q, y_f32,
                             nullptr, stream);
@@ -270,8 +307,8 @@ int32_t nm_encoder_layer_workspace(const nm_layer_desc* desc, size_t* bytes)
 int32_t nm_encoder_layer(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, float* y_f32,
                          void* ws, size_t ws_bytes, const nm_layer_taps* taps, void* stream)
 {
-    bool qkv_ready = false;
-    return run_layer(d, nullptr, &qkv_ready, x, y_q, y_f32, ws, ws_bytes, taps, stream);
+    LayerCarry carry;
+    return run_layer(d, nullptr, &carry, x, y_q, y_f32, ws, ws_bytes, taps, stream);
 }
 
 int32_t nm_encoder_layer_noalloc(const nm_layer_desc* d, const int8_t* x, int8_t* y_q, float* y_f32, void* stream)
@@ -336,11 +373,11 @@ int32_t nm_encoder_stack(const nm_layer_desc* descs, int32_t n_layers, const int
     int8_t* act_buf[2] = {reinterpret_cast<int8_t*>(w), reinterpret_cast<int8_t*>(w + act)};
     void* lws = w + 2 * act;
     const int8_t* in = x;
-    bool qkv_ready = false;
+    LayerCarry carry;
     for (int32_t l = 0; l < n_layers; ++l) {
         const bool last = l == n_layers - 1;
         int8_t* out = last ? y_q : act_buf[l & 1];
-        if ((rc = run_layer(&descs[l], last ? nullptr : &descs[l + 1], &qkv_ready, in, out, last ? y_f32 : nullptr, lws,
+        if ((rc = run_layer(&descs[l], last ? nullptr : &descs[l + 1], &carry, in, out, last ? y_f32 : nullptr, lws,
                             ws_bytes - 2 * act, nullptr, stream)))
             return rc;
         in = out;

@@ -1184,6 +1184,47 @@ def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(o
         check_layer_attention(oracle, p, ot, arrays_tables(specs, ot), with_taps)
 
 
+@pytest.mark.parametrize("S,H,heads,F,nseg", [(1, 384, 6, 1536, 64), (16, 768, 12, 3072, 128), (17, 512, 8, 520, 256), (63, 640, 10, 2560, 100),
+                                              (77, 896, 14, 900, 65), (128, 768, 12, 3072, 128), (128, 1024, 16, 4096, 1), (129, 768, 12, 3072, 64),
+                                              (250, 384, 6, 1536, 257), (682, 384, 6, 132, 64)])
+def test_layernorm_in_the_product_behind_it(S, H, heads, F, nseg):
+    """Few rows: FFN1 and the next layer's QKV projection make the LayerNorm in front of them (16x32 to 16x128 tiles, rows and columns
+    that do not fill one, widths that are and are not whole pieces of 256, tables of more than 256 segments and rows of more than one
+    round as two kernels).  The same bits as the separate entry points: the layer's stages one by one, and a stack as single layers."""
+    tables = nm.nm_build_tables([("gelu", -8.0, 8.0, nseg), ("exp", -16.0, 0.0, 64), ("recip", 1.0, 1024.0, 64), ("rsqrt", 1e-3, 64.0, nseg)])
+    g = torch.Generator(device=DEV).manual_seed(S + H + F)
+    codes = lambda *s: torch.randint(-100, 101, s, generator=g, device=DEV).to(torch.int8)
+    real = lambda n, m=0.0: torch.randn(n, generator=g, device=DEV) * 0.1 + m
+    act = dict(q=0.1, k=0.1, v=0.1, p=1.0 / 127, ctx=0.05, ln1=5.0 / 127, ffn1=0.1, out=5.0 / 127)
+    p = W.with_scales(dict(B=1, S=S, H=H, heads=heads, F=F, s_x=5.0 / 127, s_wqkv=1e-3, s_wo=1e-3, s_w1=1e-3, s_w2=1e-3, eps1=1e-5, eps2=1e-5), act)
+    descs, keep = [], []
+    for _ in range(3):
+        w = dict(Wqkv=codes(3 * H, H), bqkv=real(3 * H), Wo=codes(H, H), bo=real(H), W1=codes(F, H), b1=real(F), W2=codes(H, F), b2=real(H),
+                 gamma1=real(H, 1.0), beta1=real(H), gamma2=real(H, 1.0), beta2=real(H))
+        keep.append(w)
+        descs.append(nm.make_layer_desc(p, w, tables))
+    x = codes(S, H)
+    i8 = lambda *s: torch.full(s, 77, dtype=torch.int8, device=DEV)
+    ws = torch.empty(nm.nm_encoder_stack_workspace(descs), dtype=torch.uint8, device=DEV)
+    taps = dict(attn=torch.empty((S, H), device=DEV), ln1=i8(S, H), ffn1=i8(S, F))
+    y = x
+    for l in range(3):
+        q = i8(S, H)
+        nm.nm_encoder_layer(descs[l], y, q, None, ws, taps=taps if l == 0 else None)
+        y = q
+        if l == 0:
+            ln1, ffn1 = i8(S, H), i8(S, F)
+            nm.nm_layernorm_pwl(taps["attn"], keep[0]["gamma1"], keep[0]["beta1"], p["eps1"], tables, 3, p["inv_s_ln1"], out_q=ln1)
+            assert_exact(host(taps["ln1"]), host(ln1), "LayerNorm in FFN1")
+            nm.nm_gemm_pwl(ln1, keep[0]["W1"], bias=keep[0]["b1"], alpha=p["alpha_1"], tables=tables, table_idx=0, out_inv_scale=p["inv_s_ffn1"], out_q=ffn1)
+            assert_exact(host(taps["ffn1"]), host(ffn1), "FFN1 behind its LayerNorm")
+            assert len(np.unique(host(ln1))) > 20 and len(np.unique(host(ffn1))) > (2 if nseg == 1 else 10)
+    out, f32 = i8(S + 1, H), torch.empty((S, H), device=DEV)
+    nm.nm_encoder_stack(descs, x, out, f32, ws)
+    assert_exact(host(out)[:S], host(y), "stack")
+    assert np.all(host(out)[S] == 77)
+
+
 @pytest.mark.parametrize("S,nseg", [(64, 64), (128, 100), (200, 64), (449, 100)])
 @pytest.mark.parametrize("negative", [False, True])
 def test_fused_attention_exp_table_with_a_nan(oracle, S, nseg, negative):
