@@ -52,36 +52,55 @@ __global__ __launch_bounds__(kConvThreads) void im2col_kernel(
 }
 
 // Max pooling on int8 codes (exact, order-free); padding never takes part.  One thread per
-// output position and 16 channels (C % 16 == 0, 16-byte loads).
+// output position and 16 channels (C % 16 == 0, 16-byte loads).  A tap outside the image is taken from the nearest position
+// inside, which lies in the same window, so all loads of a window (of a row of it where kK is 0: any size) are requested at once.  Codes are
+// compared as pairs of 16-bit numbers: the word itself, whose odd bytes decide, and the word shifted by a byte for the even
+// ones.  us, 64 images of 112 x 112 x 64, 3x3 with stride 2 (64 MB: 12.6 us at a copy's rate): 13.7, where one tap was waited for at a time and
+// bytes compared singly 16.8; one image 2.2, was 3.9.
+typedef short v2s __attribute__((ext_vector_type(2)));
+template <int kK>
 __global__ __launch_bounds__(kConvThreads) void maxpool16_kernel(
-    const int8_t* __restrict__ x, int H, int W, int C, int k, int stride, int pad, int Ho, int Wo,
-    long total, int8_t* __restrict__ y)
+    const int8_t* __restrict__ x, int H, int W, int C, int k, int stride, int pad, int Ho, int Wo, FastDiv div_c, FastDiv div_wo, FastDiv div_ho,
+    unsigned total, int8_t* __restrict__ y)
 {
-    const int cg = C / 16;
-    for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (long)gridDim.x * blockDim.x) {
-        const int c = (int)(idx % cg);
-        const long m = idx / cg;
-        const int wo = (int)(m % Wo), ho = (int)((m / Wo) % Ho);
-        const long b = m / ((long)Wo * Ho);
-        int best[16];
+    const unsigned idx = blockIdx.x * kConvThreads + threadIdx.x;
+    if (idx >= total) return;
+    const unsigned m = quotient(idx, div_c), t = quotient(m, div_wo), b = quotient(t, div_ho);
+    const int c = (int)(idx - m * (unsigned)(C / 16)), w0 = (int)(m - t * (unsigned)Wo) * stride - pad, h0 = (int)(t - b * (unsigned)Ho) * stride - pad;
+    const int8_t* const img = x + (long)b * H * W * C + 16 * c;
+    v2s odd[4], even[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) best[e] = -128;
-        for (int i = 0; i < k; ++i) {
-            const int hi = ho * stride - pad + i;
-            if ((unsigned)hi >= (unsigned)H) continue;
-            for (int j = 0; j < k; ++j) {
-                const int wi = wo * stride - pad + j;
-                if ((unsigned)wi >= (unsigned)W) continue;
-                const v4i w4 = *reinterpret_cast<const v4i*>(x + ((b * H + hi) * W + wi) * C + 16 * c);
+    for (int q = 0; q < 4; ++q) odd[q] = even[q] = v2s{-32768, -32768};
+    auto take = [&](v4i w) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) best[e] = max(best[e], (int)(int8_t)((unsigned)w4[e >> 2] >> (8 * (e & 3))));
-            }
+        for (int q = 0; q < 4; ++q) {
+            const unsigned u = (unsigned)w[q];   // (of a vector's element itself the cast takes the first)
+            odd[q] = __builtin_elementwise_max(odd[q], __builtin_bit_cast(v2s, u));
+            even[q] = __builtin_elementwise_max(even[q], __builtin_bit_cast(v2s, u << 8));
         }
-        v4i o;
+    };
+    const int pitch = W * C;   // (an image has less than 2^31 bytes: host)
+    auto row = [&](int i) { return img + (unsigned)(min(max(h0 + i, 0), H - 1) * pitch); };
+    auto tap = [&](const int8_t* r, int j) { return *reinterpret_cast<const v4i*>(r + (unsigned)(min(max(w0 + j, 0), W - 1) * C)); };
+    if constexpr (kK > 0) {
+        v4i w[kK * kK];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = (int)pack4(best[4 * q], best[4 * q + 1], best[4 * q + 2], best[4 * q + 3]);
-        *reinterpret_cast<v4i*>(y + m * C + 16 * c) = o;
+        for (int i = 0; i < kK; ++i)
+#pragma unroll
+            for (int j = 0; j < kK; ++j) w[i * kK + j] = tap(row(i), j);
+#pragma unroll
+        for (int e = 0; e < kK * kK; ++e) take(w[e]);
+    } else {
+        for (int i = 0; i < k; ++i) {
+            const int8_t* const r = row(i);
+            for (int j = 0; j < k; ++j) take(tap(r, j));
+        }
     }
+    v4i o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        o[q] = (int)__builtin_amdgcn_perm(__builtin_bit_cast(unsigned, odd[q]), __builtin_bit_cast(unsigned, even[q]), 0x07030501u);
+    *reinterpret_cast<v4i*>(y + 16 * (long)idx) = o;
 }
 
 // The same with four channels (C % 4 == 0) or one channel per thread.
@@ -558,10 +577,10 @@ int32_t nm_maxpool_i8(const int8_t* x, int32_t B, int32_t H, int32_t W, int32_t 
     if (rows == 0) return NM_OK;
     if (!x || !y) return fail(NM_ERR_INVALID_ARG, "nm_maxpool_i8: NULL pointer");
     const bool vec = C % 4 == 0 && aligned(x, 4) && aligned(y, 4);
-    if (C % 16 == 0 && aligned(x, 16) && aligned(y, 16)) {
-        const long total16 = rows * (C / 16);
-        queue_kernel(maxpool16_kernel, dim3(grid_for(total16)), dim3(kConvThreads), 0, (hipStream_t)stream,
-                           x, H, W, C, k, stride, pad, Ho, Wo, total16, y);
+    if (C % 16 == 0 && aligned(x, 16) && aligned(y, 16) && rows * (C / 16) < (1LL << 31) && (int64_t)H * W * C < (1LL << 31)) {
+        const unsigned total16 = (unsigned)(rows * (C / 16));
+        queue_kernel(k == 2 ? maxpool16_kernel<2> : k == 3 ? maxpool16_kernel<3> : maxpool16_kernel<0>, dim3((total16 - 1) / kConvThreads + 1), dim3(kConvThreads), 0,
+                     (hipStream_t)stream, x, H, W, C, k, stride, pad, Ho, Wo, fast_div(C / 16), fast_div(Wo), fast_div(Ho), total16, y);
         return check_hip(hipGetLastError(), "nm_maxpool_i8 launch");
     }
     const long total = rows * (vec ? C / 4 : C);

@@ -165,7 +165,9 @@ def test_conv2d_large_tile_kernel(oracle, B, H, W, Cin, Cout, k, stride, pad, ti
         assert np.all(edge[:128] == 77) and np.all(edge[128 + n:] == 77)
 
 
-@pytest.mark.parametrize("B,H,W,Cc,k,stride,pad", [(2, 112, 112, 64, 3, 2, 1), (3, 9, 10, 5, 3, 2, 1), (1, 8, 8, 12, 2, 2, 0)])
+@pytest.mark.parametrize("B,H,W,Cc,k,stride,pad", [(2, 112, 112, 64, 3, 2, 1), (3, 9, 10, 5, 3, 2, 1), (1, 8, 8, 12, 2, 2, 0),
+                                                     (3, 9, 11, 48, 3, 1, 2), (5, 7, 8, 16, 2, 3, 1), (2, 13, 9, 80, 5, 2, 3), (1, 1, 1, 16, 1, 1, 0),
+                                                     (2, 4, 3, 32, 4, 3, 3)])
 def test_maxpool(oracle, B, H, W, Cc, k, stride, pad):
     x = rand_i8(np.random.default_rng(H), (B, H, W, Cc))
     want = oracle.maxpool_i8(x, k, stride, pad)
