@@ -41,216 +41,9 @@
 #include <cmath>
 #include <mutex>
 
-#include "nm_device.h"
+#include "nm_attention.h"
 
 namespace nm {
-
-struct AttnTable {   // what the kernels use of a DevTable, under its names
-    const float2* kb;
-    float lo, hi, inv_w, u0;
-    int nseg, clamp_input;
-};
-
-struct AttnParams {
-    const int8_t* qkv;
-    int8_t* ctx;
-    int S, H, heads, qblocks, total;   // total: workgroups that have work
-    int nch;                           // 16-byte chunks of a head's row (head size / 16)
-    float alpha_scores, inv_s_p, alpha_ctx, inv_s_ctx;
-    float e_lo, e_hi;                  // bounds of the exp table's value over every reachable input
-    int off_tile;                      // bytes of LDS in front of the images: the tables
-    int ctx_vec16;                     // ctx is 16-byte aligned: context rows leave as 16-byte stores
-    FastDiv div_qblocks, div_heads;
-    AttnTable t_exp, t_recip;
-    int32_t* scores_out;               // optional [B, heads, S, S]
-    int8_t* p_out;                     // optional [B, heads, S, S]
-};
-
-// How the exp table's segment is found: any table and scale (this form also writes the optional
-// outputs); a table of at most 256 segments without input clamp, in slots; the same with inv_w a power of two.
-enum { EXP_ANY = 0, EXP_SLOTS = 1, EXP_SLOTS_POW2 = 2 };
-constexpr size_t attn_exp_bytes(int mode, int nseg) { return mode == EXP_ANY ? sizeof(float2) * (size_t)nseg : kSlotBytes; }
-
-// Wavefronts that share 16 queries (at most 256 keys each).
-constexpr int attn_parts(int S) { return S <= 256 ? 1 : S <= 512 ? 2 : 4; }
-constexpr int kHeadDim = 64;
-constexpr int kScoreBias = 0x4B400000;   // bits of 1.5 * 2^23: the accumulators' start value
-
-// K image: 64-byte rows, the four 16-byte chunks of a row rotated by (row / 4) % 4 so that the 16
-// lanes of an operand read (16 consecutive rows, one chunk) cover all banks.
-__device__ __forceinline__ int attn_koff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
-// V image: the same, with the rotation also depending on (row / (16 kParts)) % 4, because one transposing
-// read touches rows that far apart.
-
-constexpr int kCtxPatch = 16 * 80;   // per wavefront: 16 context rows of 64 bytes, 80 apart
-// K and V images of ng groups of 64 keys per part, then the context patches or, where wavefronts share queries, their row maxima
-// (64 bytes each) and sums (256)
-constexpr size_t attn_lds_bytes(int parts, int ng)
-{
-    return 2 * (size_t)(parts * ng) * 64 * 64 + 4 * (size_t)parts * (parts > 1 ? 64 + 256 : kCtxPatch);
-}
-
-typedef int v2i_t __attribute__((ext_vector_type(2)));
-
-// Over the four lanes (m, 0..3) of a query: lane ^ 32, then lane ^ 16.
-template <typename Op>
-__device__ __forceinline__ int query_reduce(int v, Op op) { return butterfly_step<16>(butterfly_step<32>(v, op), op); }
-__device__ __forceinline__ int row_max(int v) { return query_reduce(v, MaxI32{}); }
-__device__ __forceinline__ float row_add(float v) { return __int_as_float(query_reduce(__float_as_int(v), AddF32{})); }
-
-// What the loops over the scores use, in vector registers (nm_device.h: a scalar operand halves an instruction's rate).
-template <int kMode>
-struct AttnConsts {
-    float alpha, inv_p, lo, inv_w, u0, steps;   // position in slots: times inv_w (and plus u0), which are 1/256 of the table's
-    float clo, chi;                             // EXP_ANY: the input clamp, or infinities
-    __device__ __forceinline__ AttnConsts(const AttnParams& p) : alpha(in_vgpr(p.alpha_scores)), inv_p(in_vgpr(p.inv_s_p)), lo(0.0f), u0(0.0f)
-    {
-        if (kMode == EXP_ANY) {
-            clo = p.t_exp.clamp_input ? p.t_exp.lo : -__builtin_inff();
-            chi = p.t_exp.clamp_input ? p.t_exp.hi : __builtin_inff();
-        } else {
-            inv_w = in_vgpr(p.t_exp.inv_w * (1.0f / kSlotSegments));
-            if (kMode == EXP_SLOTS_POW2) u0 = in_vgpr(p.t_exp.u0 * (1.0f / kSlotSegments));
-            else lo = in_vgpr(p.t_exp.lo);
-            steps = in_vgpr(8.0f * kSlotSegments);
-        }
-    }
-};
-
-// PWL exp of one score (acc and row maximum as biased accumulators) in two steps: the score's t in its place and its line
-// requested, then the line's value in its place.  (Left to itself the compiler writes the value over the line's b, and every one
-// keeps the register pair of its table entry: 64 of them spill.)
-struct AttnLine { float k, b; };
-template <int kMode>
-__device__ __forceinline__ AttnLine attn_look_up(int& s, float fmax_, const AttnParams& p, const AttnConsts<kMode>& c, const int8_t* s_exp)
-{
-    float t = (__int_as_float(s) - fmax_) * c.alpha;
-    float2 e;
-    if (kMode == EXP_ANY) {
-        t = __builtin_amdgcn_fmed3f(t, c.clo, c.chi);
-        e = reinterpret_cast<const float2*>(s_exp)[seg_index(t, p.t_exp.lo, p.t_exp.inv_w, p.t_exp.nseg)];
-    } else {
-        const float u = kMode == EXP_SLOTS_POW2 ? fma_clamp01(t, c.inv_w, c.u0) : mul_clamp01(t - c.lo, c.inv_w);
-        e = slot_line(slot_offset(u, c.steps));   // (the slots are the first thing in LDS)
-    }
-    s = __float_as_int(t);
-    return {e.x, e.y};
-}
-__device__ __forceinline__ void attn_line(int& s, const AttnLine& e)
-{
-    asm("v_fma_f32 %0, %1, %0, %2" : "+v"(s) : "v"(e.k), "v"(e.b));
-}
-template <int kMode>
-__device__ __forceinline__ float attn_exp(int acc, float fmax_, const AttnParams& p, const AttnConsts<kMode>& c, const int8_t* s_exp)
-{
-    const AttnLine e = attn_look_up<kMode>(acc, fmax_, p, c, s_exp);
-    return __builtin_fmaf(e.k, __int_as_float(acc), e.b);
-}
-
-// Four probabilities as int8 codes; small: all codes of the row are known to lie in [0, 127].
-__device__ __forceinline__ unsigned attn_pack(const float (&x)[4], float r, float inv, bool small)
-{
-    if (small) {
-        unsigned w = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w = __builtin_amdgcn_cvt_pk_u8_f32((x[e] * r) * inv, e, w);
-        return w;
-    }
-    return pack4(requant(x[0] * r, inv), requant(x[1] * r, inv), requant(x[2] * r, inv), requant(x[3] * r, inv));
-}
-// The first n (any integer) of a word's four bytes; zeros behind them.
-__device__ __forceinline__ unsigned attn_keep(unsigned w, int n)
-{
-    return w & (unsigned)(0xffffffffull >> (8 * (4 - min(max(n, 0), 4))));
-}
-// Whether every row of the wavefront is of that kind: r >= 0 and the bounds of e times r times inv are.
-__device__ __forceinline__ bool attn_small(float r, const AttnParams& p)
-{
-    const bool ok = r >= 0.0f && p.inv_s_p >= 0.0f && (p.e_hi * r) * p.inv_s_p <= 127.0f && (p.e_lo * r) * p.inv_s_p >= -0.5f;
-    return __all(ok);
-}
-
-// The exp table (in slots, but for EXP_ANY) and the reciprocal table, requested into registers
-// (before the operand loads, which are younger) and written to LDS.
-template <int kMode, int kThreads>
-struct AttnTables {
-    static_assert(kThreads >= kSlotSegments, "a slot per thread");
-    float2 te, tr;
-    __device__ __forceinline__ void request(const AttnParams& p)
-    {
-        te = p.t_exp.kb[min((int)threadIdx.x, p.t_exp.nseg - 1)];
-        tr = p.t_recip.kb[min((int)threadIdx.x, p.t_recip.nseg - 1)];
-    }
-    __device__ __forceinline__ void write(const AttnParams& p, float2* s_exp, float2* s_recip) const
-    {
-        const int ne = p.t_exp.nseg, nr = p.t_recip.nseg, tid = threadIdx.x;
-        if (kMode == EXP_ANY) {
-            if (tid < ne) s_exp[tid] = te;
-            for (int i = tid + kThreads; i < ne; i += kThreads) s_exp[i] = p.t_exp.kb[i];
-        } else {
-            write_slots(s_exp, te, tid);
-        }
-        if (tid < nr) s_recip[tid] = tr;
-        for (int i = tid + kThreads; i < nr; i += kThreads) s_recip[i] = p.t_recip.kb[i];
-    }
-};
-
-// Context accumulators of a wavefront -> int8 rows, through a per-wavefront LDS patch so that every lane
-// stores 16 consecutive bytes.  Lane (m, hq) holds head columns 16*cb + 4*hq + e of query m.
-__device__ __forceinline__ void attn_store_ctx(const AttnParams& p, const v4i (&a2)[4], int8_t* patch, int lane, long row0, int q0,
-                                               int head, int nch)
-{
-    const int fr = lane & 15, hq = lane >> 4;
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-        int q[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) q[e] = requant(__builtin_fmaf((float)a2[cb][e], p.alpha_ctx, 0.0f), p.inv_s_ctx);
-        *reinterpret_cast<unsigned*>(patch + fr * 80 + 16 * cb + 4 * hq) = pack4(q[0], q[1], q[2], q[3]);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int mq = q0 + (lane >> 2), c = lane & 3;
-    if (mq < p.S && c < nch) {
-        const v4i o = *reinterpret_cast<const v4i*>(patch + (lane >> 2) * 80 + 16 * c);
-        int8_t* dst = p.ctx + (row0 + mq) * p.H + head * (16 * nch) + 16 * c;
-        if (p.ctx_vec16) {
-            *reinterpret_cast<v4i*>(dst) = o;
-        } else {
-#pragma unroll
-            for (int w = 0; w < 4; ++w) *reinterpret_cast<int*>(dst + 4 * w) = o[w];
-        }
-    }
-}
-
-// Operand slot s (0..15) of lane group hq must hold key 4*hq + s%4 of the (s/4)-th of four 16-key blocks, kParts blocks apart
-// (where the probabilities sit).  A transposing read delivers eight rows: this lane supplies the address of
-// row (lane % 16) / 2 of its group, shifted by 8 bytes for odd lanes so that lanes 8..15 of the
-// group receive head columns 8..15.
-template <int kParts>
-struct VFragments {
-    int off[2], sw[2];
-    __device__ __forceinline__ VFragments(int lane)
-    {
-        const int fr = lane & 15, hq = lane >> 4;
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int sidx = 8 * hh + (fr >> 1);
-            off[hh] = (16 * kParts * (sidx >> 2) + 4 * hq + (sidx & 3)) * 64 + 8 * (fr & 1);
-            sw[hh] = hq ^ (sidx >> 2);   // chunk position of column block cb: cb ^ sw
-        }
-    }
-    __device__ __forceinline__ v4i read(const int8_t* base, int cb) const
-    {
-        v2i_t part[2];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            part[hh] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
-                (__attribute__((address_space(3))) v2i_t*)(base + off[hh] + 16 * (cb ^ sw[hh])));
-        return v4i{part[0][0], part[0][1], part[1][0], part[1][1]};
-    }
-};
 
 // Workgroups are dealt to the eight XCDs round-robin.  Renumbered so that an XCD receives consecutive
 // (head, query block) pairs: the query blocks of a head share its K and V, and neighbouring heads
@@ -279,11 +72,6 @@ __global__ __launch_bounds__(256 * kParts) __attribute__((amdgpu_waves_per_eu(4)
     constexpr int kWaves = 4 * kParts, kAttnThreads = 64 * kWaves;
     constexpr int kQueries = 64;              // queries per workgroup
     constexpr int SK = 64 * kParts * NG;      // padded key count
-    constexpr int NU = 4 * NG;                // 16-key blocks of a part
-    constexpr int kPeriod = 16 / kParts;      // ... of each 256 keys: the row sum's accumulators of a lane
-    constexpr int NACC = NU < kPeriod ? NU : kPeriod;
-    constexpr int kBlock = 1024 * kParts;     // bytes of K and V from one block of a part to the next
-    constexpr int kColumns = 4 / kParts;      // column blocks of the context that a wavefront finishes
     // With up to 1024 keys one workgroup fills a CU: V is requested behind K and arrives under the scores and the softmax.
     constexpr bool kLateV = kParts >= 2;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -331,8 +119,7 @@ __global__ __launch_bounds__(256 * kParts) __attribute__((amdgpu_waves_per_eu(4)
     load(1, sK, 0);
     if (!kLateV) load(2, sV, v_rotation);
     // this lane's query row, straight from global memory into the MFMA operand registers
-    const int part_id = wave & (kParts - 1), qwave = wave / kParts;
-    const int q0 = bx * kQueries + qwave * 16, m = q0 + fr;
+    const int q0 = bx * kQueries + wave / kParts * 16, m = q0 + fr;
     v4i qf = {0, 0, 0, 0};
     if (kHead64 || hq < nch) qf = *reinterpret_cast<const v4i*>(base + (long)(kFull ? m : min(m, S - 1)) * ld + 16 * hq);
     tabs.write(p, reinterpret_cast<float2*>(smem), s_kb_recip);
@@ -345,196 +132,7 @@ __global__ __launch_bounds__(256 * kParts) __attribute__((amdgpu_waves_per_eu(4)
         load(2, sV, v_rotation);
     }
 
-    // Unit u: the part's u-th block, keys 16 (kParts u + part) + 4 hq + e.  Keys from S on lie in the last group's units alone:
-    // all bits set where e + 16 kParts (u - first unit of that group) is below `left`.
-    sK += 1024 * part_id;
-    sV += 1024 * part_id;
-    const int left = S - 16 * kParts * 4 * (NG - 1) - 16 * part_id - 4 * hq;
-    const auto valid = [&](int u, int e) { return (16 * kParts * (u - 4 * (NG - 1)) + e - left) >> 31; };
-
-    // ---- scores and row maximum -----------------------------------------------------------------
-    // operands of a group one group ahead of its products, the maximum one behind
-    int sc[16 * NG];   // biased scores, then t, then exp values (float bits): e of unit u is sc[4u + e]
-    int mi = INT_MIN;
-    v4i kf[2][4];
-    const int8_t* const k_frag = sK + attn_koff(fr, hq);
-    const auto load_k = [&](int g) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) kf[g & 1][q] = *reinterpret_cast<const v4i*>(k_frag + kBlock * (4 * g + q));
-    };
-    const auto group_max = [&](int g) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            int& s = sc[16 * g + i];
-            if (!kFull && g == NG - 1) {
-                const int ok = valid(4 * g + i / 4, i % 4);
-                s = (s & ok) | (INT_MIN & ~ok);
-            }
-            mi = max(mi, s);
-        }
-    };
-    load_k(0);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) load_k(g + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const v4i a = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[g & 1][q], qf, v4i{kScoreBias, kScoreBias, kScoreBias, kScoreBias}, 0, 0, 0);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sc[16 * g + 4 * q + e] = a[e];
-        }
-        if (g > 0) group_max(g - 1);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    group_max(NG - 1);
-    const long row_ss = ((long)by * S + m) * S;  // offset of this query's row in [B,heads,S,S]
-    const bool vec4 = (S & 3) == 0;
-    const auto key_of = [&](int u) { return 16 * (kParts * u + part_id) + 4 * hq; };
-    if (kMode == EXP_ANY && p.scores_out && m < S) {
-#pragma unroll
-        for (int i = 0; i < 16 * NG; ++i)
-            if (key_of(i / 4) + i % 4 < S) p.scores_out[row_ss + key_of(i / 4) + i % 4] = sc[i] - kScoreBias;
-    }
-    mi = row_max(mi);
-    int* const s_max = reinterpret_cast<int*>(sO);
-    float* const s_sum = reinterpret_cast<float*>(sO + 64 * kWaves);
-    if (kParts > 1) {
-        if (lane < 16) s_max[16 * wave + lane] = mi;
-        __syncthreads();   // (everybody is done with K, too)
-#pragma unroll
-        for (int o = 1; o < kParts; ++o) mi = max(mi, s_max[16 * (wave ^ o) + fr]);
-    }
-
-    // ---- softmax-PWL ----------------------------------------------------------------------------
-    // Keys 256.. wrap onto the 64 accumulators of keys 0..255 (accumulator = (key / 4) % 64) and continue
-    // their sums.  The look-ups of a unit are requested kAhead units before they are used, so that a wavefront has
-    // some in flight all the time (eight at a time and then waited for: 32 x 512 tokens, 16 heads 68 us, 66 so).
-    float part[NACC];
-    const float fm = __int_as_float(mi);
-#pragma unroll
-    for (int j = 0; j < NACC; ++j) part[j] = 0.0f;
-    constexpr int kAhead = 3;
-    AttnLine line[kAhead + 1][4];
-#pragma unroll
-    for (int u = 0; u < NU + kAhead; ++u) {
-        if (u < NU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) line[u % (kAhead + 1)][e] = attn_look_up<kMode>(sc[4 * u + e], fm, p, consts, smem);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (u >= kAhead) {
-            const int d = u - kAhead;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                int& s = sc[4 * d + e];
-                attn_line(s, line[d % (kAhead + 1)][e]);
-                if (!kFull && d >= 4 * (NG - 1)) s &= valid(d, e);
-                part[d % kPeriod] = part[d % kPeriod] + __int_as_float(s);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // butterfly over the accumulator index 4 * (kParts j + part) + hq: masks 32 .. of j, then the part's, then 2 and 1 (hq)
-    if (kLateV) wait_vmcnt<0>();   // V has landed (the next barrier covers the others')
-#pragma unroll
-    for (int mask = kPeriod / 2; mask >= 1; mask >>= 1)
-#pragma unroll
-        for (int j = 0; j < mask; ++j)
-            if (j + mask < NACC) part[j] = part[j] + part[j + mask];   // (an absent one is +0, and no sum is -0)
-    float sum = part[0];
-    if (kParts > 1) {
-        s_sum[64 * wave + lane] = sum;
-        __syncthreads();
-        sum = sum + s_sum[64 * (wave ^ (kParts / 2)) + lane];
-        if (kParts == 4) sum = sum + (s_sum[64 * (wave ^ 1) + lane] + s_sum[64 * (wave ^ 3) + lane]);
-    }
-    sum = row_add(sum);
-    int segr;
-    const float r = pwl_eval(sum, p.t_recip, s_kb_recip, segr);
-
-    // ---- probabilities and context --------------------------------------------------------------
-    const VFragments<kParts> vfrag(lane);
-    v4i a2[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) a2[cb] = v4i{0, 0, 0, 0};
-    auto finish = [&](auto small_c) {
-        constexpr bool kSmall = decltype(small_c)::value;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            v4i vf[4];
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
-                if (kHead64 || cb < nch) vf[cb] = vfrag.read(sV + 4 * kBlock * g, cb);
-            __builtin_amdgcn_sched_barrier(0);
-            v4i pf;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int* at = sc + 16 * g + 4 * q;
-                const float x[4] = {__int_as_float(at[0]), __int_as_float(at[1]), __int_as_float(at[2]), __int_as_float(at[3])};
-                pf[q] = (int)attn_pack(x, r, consts.inv_p, kSmall);
-            }
-            // A masked key's code is 0 whatever r and inv_s_p are (0 times an infinity is a NaN, of code -127); what
-            // the V image holds for these keys then does not count.  In the other form r and inv_s_p are finite.
-            if (!kFull && !kSmall && g == NG - 1) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) pf[q] = (int)attn_keep((unsigned)pf[q], left - 16 * kParts * q);
-            }
-            if (kMode == EXP_ANY && p.p_out && m < S) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int key = key_of(4 * g + q);
-                    if (vec4 && key < S) {
-                        *reinterpret_cast<unsigned*>(p.p_out + row_ss + key) = (unsigned)pf[q];
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (key + e < S) p.p_out[row_ss + key + e] = (int8_t)((unsigned)pf[q] >> (8 * e));
-                    }
-                }
-            }
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
-                if (kHead64 || cb < nch) a2[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[cb], pf, a2[cb], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    if (attn_small(r, p)) finish(std::true_type{}); else finish(std::false_type{});
-    if constexpr (kParts == 1) {
-        attn_store_ctx(p, a2, sO + wave * kCtxPatch, lane, (long)b * S, q0, head, nch);
-    } else {
-        // part h finishes column blocks kColumns * h .., the others hand their sums of these over
-        int8_t* const x = s_tile + 16 * lane;
-        const auto slot = [&](int cb, int from) {   // of part from (not the finisher) for column block cb
-            return ((qwave * 4 + cb) * (kParts - 1) + from - (from > cb / kColumns ? 1 : 0)) * 1024;
-        };
-        static_assert(16 * (kParts - 1) * 1024 <= SK * 64, "exchange fits the K image");
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-            if (cb / kColumns != part_id) *reinterpret_cast<v4i*>(x + slot(cb, part_id)) = a2[cb];
-        __syncthreads();
-        v4i mine[kColumns];
-#pragma unroll
-        for (int c = 0; c < kColumns; ++c) {
-            mine[c] = a2[c];
-#pragma unroll
-            for (int h = 1; h < kParts; ++h)   // (a2 is indexed by constants only: its registers have no addresses)
-                if (part_id == h) mine[c] = a2[kColumns * h + c];
-#pragma unroll
-            for (int o = 0; o < kParts - 1; ++o)
-                mine[c] += *reinterpret_cast<const v4i*>(x + ((qwave * 4 + kColumns * part_id + c) * (kParts - 1) + o) * 1024);
-        }
-        if (!kFull && m >= S) return;
-        int8_t* dst = p.ctx + ((long)b * S + m) * H + head * (16 * nch) + 16 * kColumns * part_id + 4 * hq;
-#pragma unroll
-        for (int c = 0; c < kColumns; ++c) {
-            if (!kHead64 && kColumns * part_id + c >= nch) break;
-            int q[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) q[e] = requant(__builtin_fmaf((float)mine[c][e], p.alpha_ctx, 0.0f), p.inv_s_ctx);
-            *reinterpret_cast<unsigned*>(dst + 16 * c) = pack4(q[0], q[1], q[2], q[3]);
-        }
-    }
+    attn_queries<kParts, NG, kFull, kMode, kHead64>(p, consts, qf, s_tile, sK, sV, sO, smem, s_kb_recip, lane, wave, S, by, b, head, q0);
 }
 
 // Sequences beyond 1024 keys: the scores are computed three times, for the row maximum, for the sum and for the
@@ -773,9 +371,9 @@ bool fused_attention_covers(int S, int H, int heads)
     return d <= kHeadDim && d % 16 == 0 && S <= 4096;
 }
 
-int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
+int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* out, int* slots)
 {
-    AttnParams p{};
+    AttnParams& p = *out;
     DevTable t_exp, t_recip;
     int32_t rc = get_dev_table(a.tables, a.exp_idx, &t_exp, what);
     if (rc) return rc;
@@ -793,10 +391,19 @@ int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
     double vmin, vmax;
     table_value_bounds(a.tables, a.exp_idx, a.alpha_scores >= 0 ? -reach : 0.0, a.alpha_scores >= 0 ? 0.0 : reach, &vmin, &vmax);
     p.e_lo = (float)vmin; p.e_hi = (float)vmax;
-    const bool slots = a.alpha_scores >= 0.0f && t_exp.slots;
+    *slots = a.alpha_scores >= 0.0f ? t_exp.slots : SLOTS_NONE;
+    return NM_OK;
+}
+
+int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
+{
+    AttnParams p{};
+    int slots;
+    int32_t rc = attn_params(a, what, &p, &slots);
+    if (rc) return rc;
     const int pairs = a.B * a.heads;
-    if (!slots || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
-    else if (t_exp.slots == SLOTS_POW2) rc = launch_mode<EXP_SLOTS_POW2>(p, pairs, st);
+    if (slots == SLOTS_NONE || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
+    else if (slots == SLOTS_POW2) rc = launch_mode<EXP_SLOTS_POW2>(p, pairs, st);
     else rc = launch_mode<EXP_SLOTS>(p, pairs, st);
     if (rc) return rc;
     return check_hip(hipGetLastError(), "attention launch");

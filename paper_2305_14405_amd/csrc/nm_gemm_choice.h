@@ -275,6 +275,26 @@ inline int ln_gemm_tile(int M, int N)
     return -1;
 }
 
+// Whether the QKV projection and attention of a layer are one kernel (nm_qkv_attention.hip), by workgroups (128 tokens of whole sequences and a head)
+// and by how much of their rows is tokens.  Up to 256 workgroups, each alone on a CU: eight wavefronts, which the contraction has
+// slices enough for; beyond, four in a ring of two stages, two workgroups to a CU.  Workgroups x share of rows below 90 leave the chip to
+// kernels of smaller tiles, padded rows cost what tokens do.  us a layer, this less the two kernels; width, workgroups, share:
+//   eight:  768  48 1.00 +0.6 |  768 120 0.86 -0.5 |  768 132 0.60 +0.2 |  768 192 1.00 -2.4 | 1024  64 1.00 +0.4 | 1024 176 0.60 -1.5
+//           512  80 1.00 +0.7 |  512 128 1.00 -1.6 |  768 156 0.70 -0.7 |  896  70 0.78 +1.4 | 1024 240 0.25 +2.2 | 1024 128 1.00 -1.0
+//   four:   768 384 1.00 -2.6 |  768 768 0.62 +2.0 |  768 768 0.75 -2.4 |  768 768 0.70 -0.7 | 1024 768 0.60 +3.5 | 1024 2048 1.00 -18
+//           768 264 1.00 -0.2 | 1024 512 0.75 -3.4 |  512 400 0.78 -3.5 |  384 600 0.52 +3.0 |  384 360 0.55 -0.7 |  384  96 1.00 -1.1
+enum { QKV_ATTENTION_NONE, QKV_ATTENTION_FOUR, QKV_ATTENTION_EIGHT };
+inline int qkv_attention_form(int B, int S, int heads, int K)
+{
+    if (S > 128 || K < 384) return QKV_ATTENTION_NONE;
+    const int seqs = S <= 64 ? 2 : 1;
+    const long groups = ((long)B + seqs - 1) / seqs * heads;
+    const double share = seqs * S / 128.0;
+    if (groups > 256) return share >= 0.75 ? QKV_ATTENTION_FOUR : QKV_ATTENTION_NONE;
+    if (share < 0.6 || groups * share < 90) return QKV_ATTENTION_NONE;
+    return K >= 512 ? QKV_ATTENTION_EIGHT : QKV_ATTENTION_FOUR;
+}
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

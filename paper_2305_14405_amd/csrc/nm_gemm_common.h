@@ -132,11 +132,12 @@ __device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
-enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_RELU = 8, EPI_Q_RELU_RESID = 9 };
+enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_RELU = 8, EPI_Q_RELU_RESID = 9, EPI_ATTENTION = 10 };
 // EPI_F32_RESID_LN: EPI_F32_RESID followed by LayerNorm-PWL over the row, inside the kernel: the tile
 // covers whole rows (tile kernel only).
 // EPI_Q_RELU, EPI_Q_RELU_RESID: per-column scales, a table of two segments, without and with an int8 residual (tile
 // kernel only: convolutions).
+// EPI_ATTENTION: the Q, K and V of one head, which go no further than LDS, and attention behind them (tile kernel only).
 // EPI_Q_TABLE_RESID: int8 residual, table (no input clamp), int8 output: the last convolution of a
 // residual block (sum with the shortcut, ReLU).
 

@@ -2,6 +2,7 @@
 // Section 3.2: the nonlinearity behind one is the PWL calculation y = k[s]*x + b[s]).
 #pragma once
 
+#include "nm_attention.h"
 #include "nm_gemm_common.h"
 
 namespace nm {
@@ -41,14 +42,18 @@ namespace nm {
 // In front of the int8 patches of EPI_Q_TABLE lie the table's slots, so that a slot's offset is its address.
 constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
 {
-    return epi == EPI_Q_TABLE ? (int)kSlotBytes + nw * wm * (wn + 16)
+    return epi == EPI_ATTENTION ? (int)kSlotBytes + kQkvRecip * 8 + 3 * bm * 64 + nw * kCtxPatch
+         : epi == EPI_Q_TABLE ? (int)kSlotBytes + nw * wm * (wn + 16)
          : epi == EPI_Q_RELU_RESID ? bm * (bn + 16)
          : epi == EPI_F32_RESID_LN ? bm * (bn + 16) + (bm * 64 + 2 * bm) * 4
          : epi == EPI_F32_RESID ? bm * (bn + 16) + nw * 32 * (wn + 4) * 4 : nw * wm * (wn + 16);
 }
 
+template <int kEpi>
+using TileParams = std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, std::conditional_t<kEpi == EPI_ATTENTION, QkvAttnParams, GemmParams>>;
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_kernel(std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, GemmParams> p)
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_kernel(TileParams<kEpi> p)
 {
     constexpr int NWT = WAVES_M * WAVES_N;   // wavefront tiles
     constexpr int NW = NWT * KSPLIT;
@@ -77,7 +82,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     static_assert(TN >= 2 && KS % 2 == 0 && TM % KSPLIT == 0, "wavefront tile");
     constexpr bool kTable = kEpi == EPI_Q_TABLE;
     constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
-    static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN,
+    static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN || kEpi == EPI_ATTENTION,
                   "epilogues of the tile kernel");
     static_assert(!kConv || kEven, "gathered rows: a wavefront's A blocks are the same for every slice");
     static_assert(kEpi != EPI_F32_RESID_LN || WAVES_M == 1, "row statistics: a wavefront holds all rows of its columns");
@@ -125,7 +130,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         const int r = blk * RPI + lane / CPR;
         const int chunk = (lane % CPR) ^ swz_bk<BK>(r);
         const bool is_a = kEven ? b < LBA : blk < ABLK;  // wave-uniform
-        if (kConv && b < LBA) {
+        if constexpr (kEpi == EPI_ATTENTION) {
+            // row r: token r % keys of the workgroup's sequence r / keys; column c: of Q, K or V (c / 64) of head tile_n
+            static_assert(BM == 128 && BN == 192, "a head's Q, K and V");
+            const int seq = min((tile_m << (7 - p.keys_log2)) + (r >> p.keys_log2), p.B - 1), token = min(r & ((1 << p.keys_log2) - 1), p.at.S - 1);
+            const int c = r - BM;
+            voff[b] = (is_a ? (unsigned)(seq * p.at.S + token) * (unsigned)p.lda : (unsigned)((c >> 6) * p.at.H + tile_n * 64 + (c & 63)) * (unsigned)p.ldw) + 16u * chunk;
+        } else if (kConv && b < LBA) {
             if constexpr (kConv) {
                 const int m = min(m0 + r, p.M - 1), q = (int)quotient((unsigned)m, p.div_wo), bi = (int)quotient((unsigned)q, p.div_ho);
                 const int h0 = (q - bi * p.cHo) * p.cStride - p.cPad, w0 = (m - q * p.cWo) * p.cStride - p.cPad;
@@ -183,12 +194,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
         const int c = tid + t * 64 * NW;
-        bias_reg[t] = (p.bias && c < BN && n0 + c < p.N) ? p.bias[n0 + c] : 0.0f;
+        if constexpr (kEpi == EPI_ATTENTION) bias_reg[t] = (p.bias && c < BN) ? p.bias[(c >> 6) * p.at.H + tile_n * 64 + (c & 63)] : 0.0f;
+        else bias_reg[t] = (p.bias && c < BN && n0 + c < p.N) ? p.bias[n0 + c] : 0.0f;
         if (kRelu) scale_reg[t] = (p.alpha_vec && c < BN && n0 + c < p.N) ? p.alpha_vec[n0 + c] : p.alpha;
     }
     static_assert(!kTable || 64 * NW >= kSlotSegments, "a slot per thread");
     float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry per thread held in a register (more are staged late)
     if (kTable) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+
+    AttnTables<EXP_SLOTS, kEpi == EPI_ATTENTION ? 64 * NW : kSlotSegments> attn_tabs;
+    if constexpr (kEpi == EPI_ATTENTION) attn_tabs.request(p.at);
 
     // the int8 residual tile (fp32 epilogue) as 16-byte row pieces
     constexpr int CPRW = BN / 16;
@@ -359,6 +374,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             for (int e = tid + 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
         }
     }
+    if constexpr (kEpi == EPI_ATTENTION) attn_tabs.write(p.at, reinterpret_cast<float2*>(smem), reinterpret_cast<float2*>(smem + kSlotBytes));
     constexpr int RW = BN + 16;  // row stride of the residual image
     int8_t* s_res = smem;        // in the ring, which is free now
     if (kResid) {
@@ -467,6 +483,53 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             const int c = lane + 64 * t, row = c / PCPR, cc = c % PCPR;
             const int mr = m0 + erow + row, n = n0 + wave_n + 16 * cc;
             if (full || (mr < p.M && n < p.N)) *reinterpret_cast<v4i*>(p.out_q + (long)mr * p.ldo + n) = rows[t];
+        }
+    } else if constexpr (kEpi == EPI_ATTENTION) {
+        // The codes become the images that attention reads (nm_attention.h; Q's is K's), then every wavefront takes 16 queries, or twice.
+        static_assert(TN == 3 && NW * ETM == 8, "wavefront tiles of 64 x 96");
+        int8_t* const images = smem + kSlotBytes + kQkvRecip * 8;
+        const float2* const s_recip = reinterpret_cast<const float2*>(smem + kSlotBytes);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int t = wave_n / 32 + j, third = t >> 1;   // block of 32 columns
+            const float inv = in_vgpr(third == 0 ? p.inv3[0] : third == 1 ? p.inv3[1] : p.inv3[2]);
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int i = 0; i < ETM; ++i) {
+                    int q[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) q[e] = requant(__builtin_fmaf((float)sum(i, j)[4 * g + e], alpha, bi[j][g][e]), inv);
+                    const int row = erow + 32 * i + frag_row, chunk = 2 * (t & 1) + (g >> 1);
+                    const int turn = ((row >> 2) & 3) ^ (third == 2 ? (row >> 4) & 3 : 0);
+                    *reinterpret_cast<unsigned*>(images + third * (BM * 64) + row * 64 + ((chunk ^ turn) << 4) + 8 * (g & 1) + 4 * frag_half) =
+                        pack4(q[0], q[1], q[2], q[3]);
+                }
+        }
+        __syncthreads();
+        auto attend = [&](auto ng_c, auto full_c, auto mode_c) {
+            constexpr int NG = decltype(ng_c)::value, kMode = decltype(mode_c)::value;
+            const AttnConsts<kMode> consts(p.at);
+#pragma unroll 1
+            for (int t = 0; t < 8 / NW; ++t) {
+                const int row0 = 16 * (8 / NW * wave + t), first = row0 & ~(64 * NG - 1), q0 = row0 - first;   // first row of the sequence
+                const int seq = (tile_m << (NG == 1 ? 1 : 0)) + (NG == 1 ? row0 >> 6 : 0);
+                if (seq >= p.B || q0 >= p.at.S) continue;
+                const v4i qf = *reinterpret_cast<const v4i*>(images + attn_koff(row0 + (lane & 15), lane >> 4));
+                attn_queries<1, NG, decltype(full_c)::value, kMode, true>(p.at, consts, qf, nullptr, images + BM * 64 + first * 64, images + 2 * BM * 64 + first * 64,
+                                                                         images + 3 * BM * 64, smem, s_recip, lane, wave, p.at.S, 0, seq, tile_n, q0);
+            }
+        };
+        auto by_mode = [&](auto ng_c, auto full_c) {
+            if (p.pow2) attend(ng_c, full_c, std::integral_constant<int, EXP_SLOTS_POW2>{});
+            else attend(ng_c, full_c, std::integral_constant<int, EXP_SLOTS>{});
+        };
+        if (p.keys_log2 == 6) {
+            if (p.at.S == 64) by_mode(std::integral_constant<int, 1>{}, std::true_type{});
+            else by_mode(std::integral_constant<int, 1>{}, std::false_type{});
+        } else {
+            if (p.at.S == 128) by_mode(std::integral_constant<int, 2>{}, std::true_type{});
+            else by_mode(std::integral_constant<int, 2>{}, std::false_type{});
         }
     } else if constexpr (kRelu) {
         // Codes go to an image of the tile's rows (over the residual's, word by word, where there is one) and leave as

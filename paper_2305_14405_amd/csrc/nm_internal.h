@@ -205,6 +205,10 @@ struct AttnArgs {
 };
 bool fused_attention_covers(int S, int H, int heads);
 int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t stream);
+// That and the QKV projection g in front of it (a.qkv and g.out_q are not touched), where qkv_attention_takes; *done = false where the tables
+// or the size are not for it.
+bool qkv_attention_takes(const AttnArgs& a, const GemmArgs& g);
+int32_t launch_qkv_attention(const AttnArgs& a, const GemmArgs& g, const char* what, hipStream_t stream, bool* done);
 
 // Steps 5 to 9 of a layer (and step 1 of the next) as one kernel over blocks of rows; *done = false where it
 // does not take the layer.

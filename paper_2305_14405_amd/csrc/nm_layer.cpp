@@ -180,9 +180,16 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, Laye
     float* ffn2 = (float*)pick(taps ? taps->ffn2 : nullptr, plan.off_ffn2);
 
     // 1: QKV projection, three output scales by column third
+    const AttnArgs at{qkv, B, S, H, nh, d->alpha_scores, d->inv_s_p, d->alpha_ctx, d->inv_s_ctx, d->tables, d->exp_idx, d->recip_idx, ctx,
+                      taps ? taps->scores : nullptr, taps ? taps->p : nullptr};
+    bool attended = false;
     if (!have.qkv_ready) {
         const GemmArgs g = qkv_args(d, x, qkv);
-        if ((rc = have.ln_tile >= 0 ? launch_ln_gemm(have.ln, g, have.ln_tile, stream) : launch_gemm(g, stream))) return rc;
+        if (have.ln_tile < 0 && !(taps && taps->qkv) && fused_attention_shape(d) && qkv_attention_takes(at, g)) {
+            if ((rc = launch_qkv_attention(at, g, "nm_encoder_layer(qkv, attention)", stream, &attended))) return rc;
+        }
+        if (attended) {
+        } else if ((rc = have.ln_tile >= 0 ? launch_ln_gemm(have.ln, g, have.ln_tile, stream) : launch_gemm(g, stream))) return rc;
     }
     // 2-4: attention.  One fused kernel when the shape allows it (the scores and probabilities then
     // stay in registers; the taps, if given, still receive them), else three kernels.
@@ -190,17 +197,15 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, Laye
     // kernel then still runs if they are aligned enough, else the three-kernel path needs the
     // caller's score / probability taps as storage (the workspace has none for a fused shape)
     bool fused = fused_attention_shape(d);
-    if (fused && !(aligned(qkv, 16) && aligned(ctx, 4) && (!(taps && taps->scores) || aligned(taps->scores, 16)) &&
+    if (fused && !attended && !(aligned(qkv, 16) && aligned(ctx, 4) && (!(taps && taps->scores) || aligned(taps->scores, 16)) &&
                    (!(taps && taps->p) || aligned(taps->p, 4)))) {
         if (!plan_holds_scores(d) && !(taps && taps->scores && taps->p))
             return fail(NM_ERR_UNSUPPORTED, "nm_encoder_layer: qkv / ctx / scores taps must be 16-byte aligned");
         fused = false;
     }
-    if (fused) {
-        if ((rc = launch_attention({qkv, B, S, H, nh, d->alpha_scores, d->inv_s_p, d->alpha_ctx, d->inv_s_ctx, d->tables,
-                                    d->exp_idx, d->recip_idx, ctx, taps ? taps->scores : nullptr, taps ? taps->p : nullptr},
-                                   "nm_encoder_layer(attention)", stream)))
-            return rc;
+    if (attended) {
+    } else if (fused) {
+        if ((rc = launch_attention(at, "nm_encoder_layer(attention)", stream))) return rc;
     } else {
         if ((rc = nm_attn_scores(qkv, B, S, H, nh, scores, stream))) return rc;
         if ((rc = launch_softmax(scores, NM_DT_I32, d->alpha_scores, (int64_t)B * nh * S, S, t_exp, t_recip,

@@ -1184,6 +1184,39 @@ def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(o
         check_layer_attention(oracle, p, ot, arrays_tables(specs, ot), with_taps)
 
 
+@pytest.mark.parametrize("B,S,H,heads,nseg,recip", [(24, 128, 512, 8, 128, 64), (40, 128, 768, 12, 100, 128), (23, 128, 1024, 16, 256, 256),
+                                                    (48, 64, 512, 8, 100, 64), (47, 64, 640, 10, 64, 64), (33, 100, 384, 6, 64, 100),
+                                                    (63, 50, 512, 8, 3, 64), (45, 49, 768, 12, 128, 64), (25, 127, 640, 10, 255, 1), (46, 63, 384, 6, 16, 64),
+                                                    (24, 128, 512, 8, 257, 64), (24, 113, 512, 8, 64, 257)])
+def test_qkv_projection_and_attention_in_one_kernel(B, S, H, heads, nseg, recip):
+    """Up to 128 tokens: the same context, layer and stack as by the separate kernels, which the qkv tap asks for (four and eight wavefronts, one
+    sequence and two to a workgroup, an odd number of sequences, padded rows, exp tables in slots of both kinds; the last two sets of tables
+    take the separate kernels)."""
+    tables = nm.nm_build_tables([("gelu", -8.0, 8.0, 64), ("exp", -16.0, 0.0, nseg), ("recip", 1.0, 128.0, recip), ("rsqrt", 1e-3, 64.0, 64)])
+    g = torch.Generator(device=DEV).manual_seed(B + S + H)
+    codes = lambda *s: torch.randint(-100, 101, s, generator=g, device=DEV).to(torch.int8)
+    real = lambda n, m=0.0: torch.randn(n, generator=g, device=DEV) * 0.1 + m
+    F, M = 512, B * S
+    act = dict(q=0.03, k=0.035, v=0.04, p=1.0 / 127, ctx=0.03, ln1=5.0 / 127, ffn1=0.1, out=5.0 / 127)
+    p = W.with_scales(dict(B=B, S=S, H=H, heads=heads, F=F, s_x=5.0 / 127, s_wqkv=1e-3, s_wo=1e-3, s_w1=1e-3, s_w2=1e-3, eps1=1e-5, eps2=1e-5), act)
+    w = dict(Wqkv=codes(3 * H, H), bqkv=real(3 * H), Wo=codes(H, H), bo=real(H), W1=codes(F, H), b1=real(F), W2=codes(H, F), b2=real(H),
+             gamma1=real(H, 1.0), beta1=real(H), gamma2=real(H, 1.0), beta2=real(H))
+    desc = nm.make_layer_desc(p, w, tables)
+    ws = torch.empty(nm.nm_encoder_stack_workspace([desc, desc]), dtype=torch.uint8, device=DEV)
+    x = codes(M, H)
+    i8 = lambda *s: torch.full(s, 77, dtype=torch.int8, device=DEV)
+    one, apart, y1, y2 = i8(M + 1, H), i8(M, H), i8(M, H), i8(M, H)
+    nm.nm_encoder_layer(desc, x, y1, None, ws, taps=dict(ctx=one))
+    nm.nm_encoder_layer(desc, x, y2, None, ws, taps=dict(ctx=apart, qkv=i8(M, 3 * H)))
+    assert_exact(host(one)[:M], host(apart), "context")
+    assert np.all(host(one)[M] == 77) and len(np.unique(host(apart))) > 30
+    assert_exact(host(y1), host(y2), "layer")
+    stack = i8(M, H)
+    nm.nm_encoder_stack([desc, desc], x, stack, None, ws)
+    nm.nm_encoder_layer(desc, y2, y1, None, ws, taps=dict(qkv=i8(M, 3 * H)))
+    assert_exact(host(stack), host(y1), "stack")
+
+
 @pytest.mark.parametrize("S,H,heads,F,nseg", [(1, 384, 6, 1536, 64), (16, 768, 12, 3072, 128), (17, 512, 8, 520, 256), (63, 640, 10, 2560, 100),
                                               (77, 896, 14, 900, 65), (128, 768, 12, 3072, 128), (128, 1024, 16, 4096, 1), (129, 768, 12, 3072, 64),
                                               (250, 384, 6, 1536, 257), (682, 384, 6, 132, 64)])
