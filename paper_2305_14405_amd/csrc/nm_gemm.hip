@@ -840,11 +840,11 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // checked Cin % 64 == 0, 16-byte aligned image and weights)
     if (g.conv && (!w_al || !aligned(g.A, 16) || g.cCin % 64 != 0 || g.K % (g.cCin * g.cKw) != 0))
         return fail(NM_ERR_UNSUPPORTED, "conv gemm: operands not aligned for the gathered loader");
-    const bool stream_ok = al && !g.conv && !g.w_is_kn && g.K % 64 == 0 && !force_generic();
+    const bool rows_ok = al && !g.conv && !g.w_is_kn && !force_generic(), stream_ok = rows_ok && g.K % 64 == 0;
     // The tile kernel: plain matrix products with the encoder layer's epilogues
     const bool tile_epi = (epi == EPI_Q || epi == EPI_Q_TABLE) ? p.q16 != 0
                         : epi == EPI_F32_RESID ? (p.r16 != 0 && aligned(g.out_f32, 16) && g.ldo % 4 == 0) : false;
-    const bool tile_ok = stream_ok && tile_epi && batches == 1 && g.K % 128 == 0 && g.K / 128 >= 3 && !g.alpha_vec &&
+    const bool tile_ok = rows_ok && tile_epi && batches == 1 && g.K > 256 && !g.alpha_vec &&
                          g.N % 16 == 0 && g.split_cols % 4 == 0 && (int64_t)g.M * g.lda < (1LL << 32) &&
                          (int64_t)g.N * g.ldw < (1LL << 32) && table_bytes <= 40 * 1024;
     // The small-tile kernel takes any shape and alignment whose operands are addressable with 31 bits.  It is
@@ -865,7 +865,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int64_t outputs = (int64_t)g.M * g.N * batches;
     // Register-staged tiles, for operands that cannot go to LDS directly in whole slices (staged_faster)
     const bool unaligned_ok = direct_ok && !g.conv && batches == 1 && g.N >= 4;
-    const bool staged = unaligned_ok && (direct_align < 16 || g.K % 64 != 0);
+    const bool staged = unaligned_ok && !tile_ok && (direct_align < 16 || g.K % 64 != 0);
     // The tile kernel's epilogues for convolutions (int8, per-column scales, no table or one of two segments, an int8
     // residual; the rows gathered or not).  us, streaming kernel -> these: 200704 x 64 x 576 (3x3) 21.7 -> 17.0, 200704 x 64 x 256 17.9 ->
     // 13.3, 50176 x 512 x 128 with residual 18.4 -> 15.4, 12544 x 1024 x 256 with residual 12.8 -> 11.8, 200704 x 256 x 64
@@ -932,26 +932,8 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         else if (forced.number == STREAM_BIG) tile_cfg = 1;
     }
     const size_t tile_table = table.slots ? 0 : table_bytes;   // (slots are part of the kernel's own LDS)
-    if (tile_cfg == 0) {
-        rc = launch_tile<256, 256, 2, 4, 2>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 1) {
-        rc = launch_tile<256, 192, 4, 2, 2>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 2) {
-        rc = launch_tile<256, 128, 4, 2, 3>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 3) {
-        rc = launch_tile<128, 192, 2, 2, 3>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 4) {
-        rc = launch_tile<128, 192, 2, 2, 2>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 5) {
-        rc = launch_tile<128, 128, 2, 2, 3, OUT_INT8>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 6) {
-        rc = launch_tile<128, 128, 2, 2, 2>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 7) {
-        rc = launch_tile<64, 128, 2, 2, 3>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 8) {
-        rc = launch_tile<64, 128, 2, 2, 2>(p, epi, tile_table, stream);
-    } else if (tile_cfg == 9) {
-        rc = launch_tile<128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, tile_table, stream);
+    if (tile_cfg >= 0) {
+        rc = g.K % 128 ? launch_tile_end(tile_cfg, p, epi, tile_table, stream) : launch_tile_config<false>(tile_cfg, p, epi, tile_table, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

@@ -101,23 +101,24 @@ constexpr TileConfig kTileConfigs[] = {
 // k-loop is a first slice, the steady state and the last slices, so it needs one slice more than its ring has stages.
 constexpr bool tile_takes(int c, int K, bool f32)
 {
-    return c >= 0 && c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])) && K / 128 >= kTileConfigs[c].stages + 1 &&
+    return c >= 0 && c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])) && (K + 127) / 128 >= kTileConfigs[c].stages + 1 &&
            (f32 ? kTileConfigs[c].f32 : kTileConfigs[c].q) != 0;
 }
 
 inline int choose_tile(int M, int N, int K, bool f32, bool table, unsigned allowed = ~0u)
 {
     int best = -1;
+    const int nk = (K + 127) / 128;
     double best_us = 0.0;
     for (int c = 0; c < (int)(sizeof(kTileConfigs) / sizeof(kTileConfigs[0])); ++c) {
         const auto& t = kTileConfigs[c];
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rest = tiles % t.places;
-        if (!(allowed >> c & 1) || !tile_takes(c, K, f32) || (tiles < t.least && K / 128 > 3)) continue;
+        if (!(allowed >> c & 1) || !tile_takes(c, K, f32) || (tiles < t.least && nk > 3)) continue;
         const bool alone = rest <= t.places - 256 && rest <= 256, paired = rest <= t.places - 256;
         const double full = (double)(tiles / t.places);
         const double rounds = full + (rest == 0 ? 0.0 : alone ? t.alone : paired ? t.paired : 1.0);
         const double epilogues = full + (rest == 0 ? 0.0 : alone ? t.alone_epi : paired ? t.paired : 1.0);
-        const double us = t.start + rounds * t.slice * (K / 128) + epilogues * (f32 ? t.f32 : table ? t.table : t.q);
+        const double us = t.start + rounds * t.slice * nk + epilogues * (f32 ? t.f32 : table ? t.table : t.q);
         if (best < 0 || us < best_us) best_us = us, best = c;
     }
     return best;
@@ -286,13 +287,13 @@ inline int ln_gemm_tile(int M, int N)
 enum { QKV_ATTENTION_NONE, QKV_ATTENTION_FOUR, QKV_ATTENTION_EIGHT };
 inline int qkv_attention_form(int B, int S, int heads, int K)
 {
-    if (S > 128 || K < 384) return QKV_ATTENTION_NONE;
+    if (S > 128 || K <= 256) return QKV_ATTENTION_NONE;
     const int seqs = S <= 64 ? 2 : 1;
     const long groups = ((long)B + seqs - 1) / seqs * heads;
     const double share = seqs * S / 128.0;
     if (groups > 256) return share >= 0.75 ? QKV_ATTENTION_FOUR : QKV_ATTENTION_NONE;
     if (share < 0.6 || groups * share < 90) return QKV_ATTENTION_NONE;
-    return K >= 512 ? QKV_ATTENTION_EIGHT : QKV_ATTENTION_FOUR;
+    return K > 384 ? QKV_ATTENTION_EIGHT : QKV_ATTENTION_FOUR;
 }
 
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the

@@ -65,6 +65,9 @@ struct GemmLnParams : GemmParams {
 // 1); forced: tile configuration 0 .. 6, or -1 for the rule.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s);
 
+// The tile kernel's configuration cfg for K in whole chunks of 16 bytes but not whole slices (nm_gemm_end.hip).
+int32_t launch_tile_end(int cfg, GemmParams& p, int epi, size_t table_bytes, hipStream_t s);
+
 // The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).
 int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s);
 

@@ -73,11 +73,11 @@ static void direct_args(DirectConvParams& q, const GemmParams& p)
 // KW wavefronts divide K in slices of 128 bytes; a wavefront has up to D slices in flight.
 // kAl: 16: operands go global -> LDS directly; 4, 1: alignment of the rows in bytes, through registers.
 // kEpi, kForm: EPI_GENERIC, or one of the fixed epilogues for a single problem whose columns come in whole fours and, unless
-// gathered, with K a multiple of 128 (lean_epilogue).  Every kernel starts with an empty instruction cache and runs
+// gathered, with K a multiple of 16 (lean_epilogue; kEnd: not of 128, the last slice is partly filled).  Every kernel starts with an empty instruction cache and runs
 // most of this code once: stamps at 128 x 3072 x 768 put 1300 to 2700 clocks on the 190 instructions in front of the first
 // load and 1400 on the epilogue, of 7000 in all.  The fixed forms are a third of the code on the way, and divisions are by
 // host-made reciprocals: 12 base layers over 1 x 128 tokens 360 -> 340 us, ResNet-50 on one image 245 -> 211.
-template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm>
+template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm, bool kEnd>
 __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, kEpi> p)
 {
     constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, 
     // this wavefront's slices
     const int per = nk / KW, rem = nk % KW;
     const int s0 = wave * per + min(wave, rem), cnt = per + (wave < rem ? 1 : 0);
-    const bool ragged = !(kLean && !kConv) && (p.K & 127) != 0;   // the last slice is partly filled
+    const bool ragged = kLean && !kConv ? kEnd : (p.K & 127) != 0;   // the last slice is partly filled
     const int8_t* zero_src = g_zero_line + 16 * (lane & 7);
 
     // ---- aligned operands: slice t of this wavefront goes straight to its ring slot ----
@@ -441,10 +441,10 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, 
     }
 }
 
-template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi = EPI_GENERIC, int kForm = FORM_ANY>
+template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi = EPI_GENERIC, int kForm = FORM_ANY, bool kEnd = false>
 static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, hipStream_t s)
 {
-    auto kern = gemm_direct_kernel<BM, BN, KW, D, kAl, kConv, kEpi, kForm>;
+    auto kern = gemm_direct_kernel<BM, BN, KW, D, kAl, kConv, kEpi, kForm, kEnd>;
     const int nk = (p.K + 127) / 128, need = (nk + KW - 1) / KW;
     const size_t shmem = (size_t)(nk < KW && kEpi == EPI_GENERIC ? nk : KW) * (need < D ? need : D) * (BM + BN) * 128 + table_bytes;
     static std::once_flag once;  // one attribute call per instantiation
@@ -470,7 +470,7 @@ static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, h
 // The fixed epilogue that computes what p asks for (and nothing else), or EPI_GENERIC.
 static int lean_epilogue(const GemmParams& p, bool conv, int batches)
 {
-    if (batches != 1 || p.N % 4 != 0 || !p.vec_out || p.ldo >= (1LL << 31) || (!conv && p.K % 128 != 0)) return EPI_GENERIC;
+    if (batches != 1 || p.N % 4 != 0 || !p.vec_out || p.ldo >= (1LL << 31) || (!conv && p.K % 16 != 0)) return EPI_GENERIC;
     if (p.dbg_seg || p.out_acc || p.out_inv_scale_vec || (p.out_q != nullptr) == (p.out_f32 != nullptr)) return EPI_GENERIC;
     if (p.has_table && (p.table.cellmap || p.table.clamp_input || p.split_cols > 0)) return EPI_GENERIC;
     if (p.out_f32) return p.resid && !p.has_table ? EPI_F32_RESID : EPI_GENERIC;
@@ -493,6 +493,12 @@ static int32_t launch_direct_aligned(GemmParams& p, bool conv, int batches, size
     if (conv) return launch_direct_conv<BM, BN, KW, D>(p, batches, table_bytes, s);
     const int epi = lean_epilogue(p, false, batches);
     const bool two = p.has_table && p.table.two_seg;
+    if (p.K % 128 != 0) {
+        if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q, FORM_ANY, true>(p, batches, 0, s);
+        if (epi == EPI_F32_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_F32_RESID, FORM_ANY, true>(p, batches, 0, s);
+        if (epi == EPI_Q_TABLE) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE, FORM_ANY, true>(p, batches, table_bytes, s);
+        return launch_direct_t<BM, BN, KW, D, 16, false>(p, batches, table_bytes, s);
+    }
     if (epi == EPI_Q) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q>(p, batches, 0, s);
     if (epi == EPI_F32_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_F32_RESID>(p, batches, 0, s);
     if (epi == EPI_Q_TABLE_RESID) return launch_direct_t<BM, BN, KW, D, 16, false, EPI_Q_TABLE_RESID, FORM_TWO_SEGMENTS>(p, batches, 0, s);

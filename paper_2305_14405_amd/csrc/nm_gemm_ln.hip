@@ -66,7 +66,7 @@ __global__ __launch_bounds__(1024) void gemm_ln_kernel(LnGemmParams p)
     if (id >= ntiles) return;
     const int tile_n = (int)quotient((unsigned)id, p.div_tiles_m);
     const int m0 = (id - tile_n * p.tiles_m) * BM, n0 = tile_n * BN;
-    const int K = p.K, nk = K >> 7;
+    const int K = p.K, nk = (K + 127) >> 7;
     int8_t* const s_a = smem + nk * SLICE;
     float2* const s_kb = reinterpret_cast<float2*>(s_a + 2 * kC * BM * 128);
 
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(1024) void gemm_ln_kernel(LnGemmParams p)
         // ---- the rows: accumulator i of the normative sums is lane i ---------------------------------------------------
         v4f x[R][kC], ga[kC], be[kC];
         float2 tab[4];
-        const bool last_live = 256 * (kC - 1) + 4 * lane < K;   // (the last piece of a row may be half of one)
+        const bool last_live = 256 * (kC - 1) + 4 * lane < K;   // (the last piece of a row may be a part of one)
         const int last_col = min(256 * (kC - 1) + 4 * lane, K - 4);
         const auto row_of = [&](int r) { return p.x + (long)min(m0 + wave * R + r, p.M - 1) * K; };   // past the edge: the last one, never stored
 #pragma unroll
@@ -134,6 +134,7 @@ __global__ __launch_bounds__(1024) void gemm_ln_kernel(LnGemmParams p)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) q[i] = requant(__builtin_fmaf(d[c][i] * scale, ga[c][i], be[c][i]), p.ln_inv_scale);
                 w[c] = pack4(q[0], q[1], q[2], q[3]);
+                if (c == kC - 1 && !last_live) w[c] = 0;   // beyond K the A image is zero, whatever the W slice has there
                 *reinterpret_cast<unsigned*>(to + 2 * c * BM * 128) = w[c];
             }
             if (tile_n == 0 && p.ln_out && m0 + row < p.M) {
@@ -155,10 +156,11 @@ __global__ __launch_bounds__(1024) void gemm_ln_kernel(LnGemmParams p)
     if (wave < nk) {
         const int lrow = lane >> 3, chunk0 = (lane & 7) ^ (lane >> 4);   // row and chunk of the lane in even pieces; the others: chunk ^ 4
         const unsigned ring = (unsigned)(uintptr_t)mine;
+        const unsigned left = (unsigned)(K - 128 * wave - 16);   // the row's last chunk from here: chunks beyond are that one again
         const unsigned ldw = (unsigned)p.ldw, w_row0 = (unsigned)(n0 + lrow) * ldw, w_last = (unsigned)(p.N - 1) * ldw;
 #pragma unroll
         for (int b = 0; b < NI; ++b)
-            dma16s(p.W + 128 * wave, min(w_row0 + 8u * b * ldw, w_last) + 16u * (unsigned)(chunk0 ^ ((b & 1) << 2)), ring + 1024 * b);
+            dma16s(p.W + 128 * wave, min(w_row0 + 8u * b * ldw, w_last) + min(16u * (unsigned)(chunk0 ^ ((b & 1) << 2)), left), ring + 1024 * b);
     }
     v4f bias_r = {0.0f, 0.0f, 0.0f, 0.0f};
     if (p.bias) bias_r = *reinterpret_cast<const v4f_a4*>(p.bias + min(nb, p.N - 4));
@@ -242,7 +244,7 @@ template <int BM, int BN, int kC, int kEpi>
 static int32_t launch_ln(LnGemmParams& p, hipStream_t s)
 {
     auto kern = gemm_ln_kernel<BM, BN, kC, kEpi>;
-    const size_t shmem = p.K / 128 * BN * 128 + 2 * kC * BM * 128 + (kEpi == EPI_Q_TABLE ? sizeof(float2) * (size_t)p.nseg : 0);
+    const size_t shmem = (p.K + 127) / 128 * BN * 128 + 2 * kC * BM * 128 + (kEpi == EPI_Q_TABLE ? sizeof(float2) * (size_t)p.nseg : 0);
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {
@@ -267,12 +269,12 @@ static int32_t launch_ln_tile(LnGemmParams& p, bool table, hipStream_t s)
     }
 }
 
-// Whether the kernel takes the LayerNorm n and the product g behind it: whole slices of at most 1024 columns, rows that follow one
+// Whether the kernel takes the LayerNorm n and the product g behind it: whole chunks of at most 1024 columns, rows that follow one
 // another, 16-byte rows of x and W, int8 results in whole groups of four, one table of at most 256 segments for the rows (it lies in
 // registers).
 bool ln_gemm_takes(const LnRows& n, const GemmArgs& g)
 {
-    return g.K % 128 == 0 && g.K >= 256 && g.K <= 1024 && aligned(n.x, 16) && aligned(n.gamma, 16) && aligned(n.beta, 16) && n.table.nseg <= 256 &&
+    return g.K % 16 == 0 && g.K >= 192 && g.K <= 1024 && aligned(n.x, 16) && aligned(n.gamma, 16) && aligned(n.beta, 16) && n.table.nseg <= 256 &&
            (!n.out_q || aligned(n.out_q, 4)) && g.N % 4 == 0 && aligned(g.W, 16) && g.ldw % 16 == 0 && (int64_t)g.N * g.ldw < (1LL << 31) &&
            (!g.bias || aligned(g.bias, 4)) && g.out_q && aligned(g.out_q, 4) && g.ldo % 4 == 0 && g.ldo < (1LL << 31) && !g.out_f32 && !g.out_acc &&
            !g.alpha_vec && !g.resid && !g.out_inv_scale_vec && !g.dbg_seg && !g.conv && !g.w_is_kn && g.outer_count * g.inner_count == 1 &&

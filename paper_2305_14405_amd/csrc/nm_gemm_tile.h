@@ -9,7 +9,7 @@ namespace nm {
 
 // ---------------------------------------------------------------------------------------------
 // Tile kernel: the large-tile path for the plain matrix products of the encoder layer (aligned
-// operands, K a multiple of 128, scalar alpha, int8 output with or without the table, or fp32
+// operands, K a multiple of 16 and more than 256, scalar alpha, int8 output with or without the table, or fp32
 // output with the int8 residual).  Same LDS image and MFMA operand roles as the streaming kernel;
 // what differs is how the instruction stream is laid out:
 //  * the k-loop is software-pipelined by hand and its issue order is pinned with scheduling
@@ -52,7 +52,10 @@ constexpr int tile_front_bytes(int bm, int bn, int nw, int wm, int wn, int epi)
 template <int kEpi>
 using TileParams = std::conditional_t<kEpi == EPI_F32_RESID_LN, GemmLnParams, std::conditional_t<kEpi == EPI_ATTENTION, QkvAttnParams, GemmParams>>;
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1>
+// kEnd: K is a multiple of 16 but not of 128.  The last slice is then the last 128 bytes of K, whose first chunks the slice in front has had
+// already: of A they are cleared in registers (around other matrix instructions for this slice the compiler moves accumulators
+// between register classes and spills, whole slices or not: 256x256 tiles 400 registers).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1, bool kEnd = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_kernel(TileParams<kEpi> p)
 {
     constexpr int NWT = WAVES_M * WAVES_N;   // wavefront tiles
@@ -177,9 +180,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             }
         }
         const bool is_a = kEven ? b < LBA : wave + b * NW < ABLK;
-        dma16s((is_a ? gA : gW) + (long)kt * BK, voff[b], dst);
+        dma16s((is_a ? gA : gW) + (kEnd ? min((long)kt * BK, (long)p.K - BK) : (long)kt * BK), voff[b], dst);
     };
-    const int nk = p.K / BK;  // >= STAGES + 1 (host; any with kShort)
+    const int nk = kEnd ? (p.K + BK - 1) / BK : p.K / BK;  // >= STAGES + 1 (host; any with kShort)
+    const int first_chunk = kEnd ? nk * CPR - p.K / 16 : 0;   // that counts in the last slice
+    static_assert(!kEnd || (!kRelu && !kConv && BK == 128), "whole slices");
     constexpr bool kShort = kRelu;
 #pragma unroll
     for (int st = 0; st < STAGES; ++st) {
@@ -267,6 +272,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
 #pragma unroll
             for (int t = 0; t < NMF; ++t) {
                 const int i = t / TN, j = t % TN;
+                if (kEnd && YOUNG < 0 && t == 0) {
+                    const bool counts = 2 * (kg * KS + ks) + frag_half >= first_chunk;
+#pragma unroll
+                    for (int r = 0; r < TM; ++r)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) fa[cur][r][e] = counts ? fa[cur][r][e] : 0;
+                }
                 if (ks == KS - 1 && t == HALF && YOUNG >= 0) {
                     // every wavefront has read all of slice kt (its last fragments were requested
                     // during the previous k-step); slice kt + 1 has landed for this wavefront
@@ -737,10 +749,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1, typename Params>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int kEpi, int BK = 128, bool kConv = false, int KSPLIT = 1, bool kEnd = false, typename Params>
 static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 {
-    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK, kConv, KSPLIT>;
+    auto kern = gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, kEpi, BK, kConv, KSPLIT, kEnd>;
     constexpr int NW = WAVES_M * WAVES_N * KSPLIT, NBLK = (BM + BN) * BK / 1024;
     constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
     constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M / KSPLIT, BN / WAVES_N, kEpi);
@@ -765,17 +777,34 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 
 // The epilogues a configuration is built for (kTileConfigs).
 enum TileOutputs { OUT_ANY, OUT_INT8, OUT_F32 };
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, TileOutputs kOut = OUT_ANY, int KSPLIT = 1>
+template <bool kEnd, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, TileOutputs kOut = OUT_ANY, int KSPLIT = 1>
 static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
 {
     if constexpr (kOut != OUT_F32) {
-        if (epi == EPI_Q) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT>(p, table_bytes, s);
-        if (epi == EPI_Q_TABLE) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT>(p, table_bytes, s);
+        if (epi == EPI_Q) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
+        if (epi == EPI_Q_TABLE) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
     }
     if constexpr (kOut != OUT_INT8) {
-        if (epi == EPI_F32_RESID) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT>(p, table_bytes, s);
+        if (epi == EPI_F32_RESID) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
     }
     return fail(NM_ERR_UNSUPPORTED, "gemm: tile configuration not built for this epilogue");
+}
+// Configuration cfg of kTileConfigs.
+template <bool kEnd>
+static int32_t launch_tile_config(int cfg, GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
+{
+    switch (cfg) {
+    case 0: return launch_tile<kEnd, 256, 256, 2, 4, 2>(p, epi, table_bytes, s);
+    case 1: return launch_tile<kEnd, 256, 192, 4, 2, 2>(p, epi, table_bytes, s);
+    case 2: return launch_tile<kEnd, 256, 128, 4, 2, 3>(p, epi, table_bytes, s);
+    case 3: return launch_tile<kEnd, 128, 192, 2, 2, 3>(p, epi, table_bytes, s);
+    case 4: return launch_tile<kEnd, 128, 192, 2, 2, 2>(p, epi, table_bytes, s);
+    case 5: return launch_tile<kEnd, 128, 128, 2, 2, 3, OUT_INT8>(p, epi, table_bytes, s);
+    case 6: return launch_tile<kEnd, 128, 128, 2, 2, 2>(p, epi, table_bytes, s);
+    case 7: return launch_tile<kEnd, 64, 128, 2, 2, 3>(p, epi, table_bytes, s);
+    case 8: return launch_tile<kEnd, 64, 128, 2, 2, 2>(p, epi, table_bytes, s);
+    default: return launch_tile<kEnd, 128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, table_bytes, s);
+    }
 }
 
 // Convolutions, as products or with gathered rows.  us, streaming kernel -> this one with 128-byte slices: 12544 x 256 x 2304

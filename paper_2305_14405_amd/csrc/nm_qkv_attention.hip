@@ -14,7 +14,7 @@ namespace nm {
 
 bool qkv_attention_takes(const AttnArgs& a, const GemmArgs& g)
 {
-    return a.S <= 128 && a.H == 64 * a.heads && g.K % 128 == 0 && g.K / 128 >= 3 && aligned(g.A, 16) && aligned(g.W, 16) && (!g.bias || aligned(g.bias, 4)) &&
+    return a.S <= 128 && a.H == 64 * a.heads && g.K % 16 == 0 && aligned(g.A, 16) && aligned(g.W, 16) && (!g.bias || aligned(g.bias, 4)) &&
            aligned(a.ctx, 4) && !a.scores_out && !a.p_out && (int64_t)g.M * g.lda < (1LL << 32) && (int64_t)g.N * g.ldw < (1LL << 32);
 }
 
@@ -33,8 +33,12 @@ int32_t launch_qkv_attention(const AttnArgs& a, const GemmArgs& g, const char* w
     p.A = g.A; p.lda = g.lda; p.W = g.W; p.ldw = g.ldw; p.inner_count = 1;
     p.bias = g.bias; p.alpha = g.alpha;
     for (int i = 0; i < 3; ++i) p.inv3[i] = g.inv3[i];
-    rc = form == QKV_ATTENTION_EIGHT ? launch_tile_epi<128, 192, 2, 2, 3, EPI_ATTENTION, 128, false, 2>(p, 0, stream)
-                                     : launch_tile_epi<128, 192, 2, 2, 2, EPI_ATTENTION>(p, 0, stream);
+    const auto launch = [&](auto end_c) {
+        constexpr bool kEnd = decltype(end_c)::value;
+        return form == QKV_ATTENTION_EIGHT ? launch_tile_epi<128, 192, 2, 2, 3, EPI_ATTENTION, 128, false, 2, kEnd>(p, 0, stream)
+                                           : launch_tile_epi<128, 192, 2, 2, 2, EPI_ATTENTION, 128, false, 1, kEnd>(p, 0, stream);
+    };
+    rc = g.K % 128 ? launch(std::true_type{}) : launch(std::false_type{});
     if (rc) return rc;
     *done = true;
     return check_hip(hipGetLastError(), "QKV + attention launch");

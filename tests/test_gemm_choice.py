@@ -81,7 +81,11 @@ print("PRODUCT_OK")
     ("tile3", 1500, 768, 384, 0, 0),      # three slices, a ring of three stages: one slice too few
     ("relu11", 1200, 912, 192, 0, 1),     # slices of 128 bytes, one and a half of them
     ("direct0", 64, 128, 3072, 4096, 0),  # rings and table together beyond LDS
-    ("tile3", 1500, 768, 512, 64, 0)])    # one that the configuration does take
+    ("tile3", 1500, 768, 512, 64, 0),   # one that the configuration does take
+    # K in whole chunks but not whole slices, every remainder
+    ("tile0", 700, 1024, 272, 128, 0), ("tile1", 700, 1008, 416, 0, 0), ("tile2", 700, 1008, 688, 64, 0), ("tile3", 500, 1008, 576, 0, 0),
+    ("tile4", 500, 1008, 336, 100, 0), ("tile5", 500, 1008, 752, 0, 0), ("tile6", 500, 1008, 480, 64, 0), ("tile7", 300, 1008, 400, 300, 0),
+    ("tile8", 300, 1008, 304, 0, 0), ("direct0", 100, 260, 400, 64, 0), ("direct3", 100, 260, 80, 0, 0), ("direct5", 100, 260, 1104, 64, 0)])
 def test_forced_configuration_keeps_results(cfg, M, N, K, nseg, per_column):
     run = subprocess.run([sys.executable, "-c", PRODUCT, *map(str, (M, N, K, nseg, per_column))], capture_output=True, text=True, cwd=ROOT,
                          env=dict(os.environ, NM_GEMM_CFG=cfg, PYTHONPATH=ROOT), timeout=100)

@@ -349,6 +349,22 @@ def test_table_forms_of_the_tile_kernel(oracle, lo, hi, nseg):
     assert np.all(got[M] == 77)
 
 
+@pytest.mark.parametrize("M,N,K", [(1100, 1008, 272), (1100, 1008, 304), (1100, 1008, 336), (1100, 1008, 464), (2100, 768, 3088), (4096, 704, 704), (4096, 704, 2816 + 32),
+                                   (9000, 832, 832), (16390, 960, 400), (300, 704, 704), (300, 576, 2304 + 48), (40, 448, 448), (3000, 448, 272)])
+def test_fp32_results_of_whole_chunks(oracle, M, N, K):
+    """fp32 results with an int8 residual, K a multiple of 16 but not of 128: the tile kernel's configurations and the small-tile kernel's; sampled
+    rows, both edges of the tiles among them."""
+    d = W.gemm_inputs(M, N, K, seed=M + K, full_range=True)
+    rows = np.unique(np.clip(np.concatenate([[0, 1, 63, 64, 127, 128, 255, 256, M - 2, M - 1], np.random.default_rng(K).integers(0, M, 40)]), 0, M - 1))
+    res = np.random.default_rng(N).integers(-127, 128, (M, N)).astype(np.int8)
+    want = oracle.gemm_pwl(np.ascontiguousarray(d["A"][rows]), d["W"], bias=d["bias"], alpha=2e-4, resid=np.ascontiguousarray(res[rows]), resid_scale=0.03)["y"]
+    out = torch.full((M + 1, N), 77.0, device=DEV)
+    nm.nm_gemm_pwl(dev(d["A"]), dev(d["W"]), bias=dev(d["bias"]), alpha=2e-4, resid=dev(res), resid_scale=0.03, out_f32=out, M=M)
+    got = host(out)
+    assert_f32_close(got[rows], want, "fp32")
+    assert np.all(got[M] == 77.0)
+
+
 def test_two_level_table_limits():
     """More than 256 merged segments do not fit the byte map; the other entry points use a two-level
     table's expanded form (same results)."""
@@ -1187,7 +1203,8 @@ def test_encoder_layer_long_attention_masked_keys_where_numbers_are_not_finite(o
 @pytest.mark.parametrize("B,S,H,heads,nseg,recip", [(24, 128, 512, 8, 128, 64), (40, 128, 768, 12, 100, 128), (23, 128, 1024, 16, 256, 256),
                                                     (48, 64, 512, 8, 100, 64), (47, 64, 640, 10, 64, 64), (33, 100, 384, 6, 64, 100),
                                                     (63, 50, 512, 8, 3, 64), (45, 49, 768, 12, 128, 64), (25, 127, 640, 10, 255, 1), (46, 63, 384, 6, 16, 64),
-                                                    (24, 128, 512, 8, 257, 64), (24, 113, 512, 8, 64, 257)])
+                                                    (24, 128, 704, 11, 128, 64), (60, 100, 320, 5, 100, 64), (60, 57, 576, 9, 64, 64),
+                                                    (30, 128, 832, 13, 64, 64), (24, 128, 512, 8, 257, 64), (24, 113, 512, 8, 64, 257)])
 def test_qkv_projection_and_attention_in_one_kernel(B, S, H, heads, nseg, recip):
     """Up to 128 tokens: the same context, layer and stack as by the separate kernels, which the qkv tap asks for (four and eight wavefronts, one
     sequence and two to a workgroup, an odd number of sequences, padded rows, exp tables in slots of both kinds; the last two sets of tables
@@ -1219,7 +1236,8 @@ def test_qkv_projection_and_attention_in_one_kernel(B, S, H, heads, nseg, recip)
 
 @pytest.mark.parametrize("S,H,heads,F,nseg", [(1, 384, 6, 1536, 64), (16, 768, 12, 3072, 128), (17, 512, 8, 520, 256), (63, 640, 10, 2560, 100),
                                               (77, 896, 14, 900, 65), (128, 768, 12, 3072, 128), (128, 1024, 16, 4096, 1), (129, 768, 12, 3072, 64),
-                                              (250, 384, 6, 1536, 257), (682, 384, 6, 132, 64)])
+                                              (250, 384, 6, 1536, 257), (682, 384, 6, 132, 64), (100, 448, 7, 1792, 64), (33, 704, 11, 512, 128),
+                                              (16, 960, 15, 960, 64), (47, 240, 5, 480, 64), (50, 832, 13, 3328, 100)])
 def test_layernorm_in_the_product_behind_it(S, H, heads, F, nseg):
     """Few rows: FFN1 and the next layer's QKV projection make the LayerNorm in front of them (16x32 to 16x128 tiles, rows and columns
     that do not fill one, widths that are and are not whole pieces of 256, tables of more than 256 segments and rows of more than one
