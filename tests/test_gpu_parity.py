@@ -1417,7 +1417,8 @@ def test_encoder_stack(oracle, name, n_layers):
 @pytest.mark.parametrize("B,S,H,heads,F,n_layers,biases", [
     (1, 1, 16, 1, 16, 2, True), (3, 5, 48, 3, 80, 3, False), (1, 17, 64, 1, 272, 1, True), (2, 16, 160, 10, 144, 2, True),
     (1, 33, 256, 4, 1024, 2, True), (1024, 1, 320, 5, 1280, 1, True), (31, 33, 448, 7, 1792, 2, True),
-    (1025, 4, 48, 3, 80, 2, True), (151, 32, 192, 3, 768, 1, False), (8200, 2, 32, 2, 32, 2, True), (129, 32, 320, 5, 1280, 2, True)])
+    (1025, 4, 48, 3, 80, 2, True), (151, 32, 192, 3, 768, 1, False), (8200, 2, 32, 2, 32, 2, True), (129, 32, 320, 5, 1280, 2, True),
+    (100, 13, 320, 5, 1280, 2, True), (97, 16, 384, 6, 1536, 1, True), (47, 15, 256, 4, 1024, 2, True), (19, 32, 192, 3, 768, 2, True)])
 def test_encoder_block_kernel_edges(oracle, B, S, H, heads, F, n_layers, biases):
     """The kernel that runs everything behind attention for a block of rows: row remainders of 16 and
     32 per workgroup, widths that are no multiple of 128, more and fewer tiles than wavefronts, the ring
