@@ -472,6 +472,60 @@ __global__ __launch_bounds__(kConvThreads) void pad_rows_kernel(const int8_t* __
     }
 }
 
+// The product behind a convolution, without its A operand.
+static int32_t conv_args(const nm_conv_desc* d, const ConvPlan& pl, GemmArgs* out)
+{
+    GemmArgs& g = *out;
+    if (d->table_idx >= 0) {
+        const int32_t rc = get_dev_table(d->tables, d->table_idx, &g.table, "nm_conv2d_pwl");
+        if (rc) return rc;
+        g.has_table = 1;
+    }
+    g.M = (int)pl.M; g.N = d->Cout; g.K = pl.K;
+    g.W = d->w; g.ldw = pl.K;
+    g.bias = d->bias; g.alpha_vec = d->alpha_vec; g.alpha = d->alpha;
+    g.resid = d->resid; g.resid_scale = d->resid_scale;
+    g.out_inv_scale = d->out_inv_scale;
+    g.ldo = d->Cout;
+    g.out_q = d->out_q; g.out_f32 = d->out_f32; g.out_acc = d->dbg_acc;
+    return NM_OK;
+}
+// ... whose rows are gathered from the image.
+static void gather_args(const nm_conv_desc* d, const ConvPlan& pl, GemmArgs* g)
+{
+    g->A = d->x; g->lda = d->Cin;
+    g->conv = 1;
+    g->cH = d->H; g->cW = d->W; g->cCin = d->Cin; g->cKw = d->kw; g->cStride = d->stride; g->cPad = d->pad;
+    g->cHo = pl.Ho; g->cWo = pl.Wo;
+}
+
+// Two steps of a network as one launch where both are small convolutions and neither touches what the other writes.
+static int32_t conv_pair(const nm_conv_desc* a, const nm_conv_desc* b, hipStream_t stream, bool* done)
+{
+    *done = false;
+    const nm_conv_desc* const d[2] = {a, b};
+    GemmArgs g[2];
+    for (int i = 0; i < 2; ++i) {
+        ConvPlan pl;
+        if (!d[i]->out_q || d[i]->out_f32 || d[i]->dbg_acc || d[i]->resid || !d[i]->x || !d[i]->w || d[i]->Cin % 64 != 0) return NM_OK;
+        if (plan_conv(d[i], "nm_conv2d_pwl", &pl) || pl.route > 1 || pl.M == 0 || conv_args(d[i], pl, &g[i])) return NM_OK;   // (the step itself reports it)
+        gather_args(d[i], pl, &g[i]);
+    }
+    const auto apart = [](const void* p, size_t n, const void* q, size_t m) {
+        const uintptr_t u = reinterpret_cast<uintptr_t>(p), v = reinterpret_cast<uintptr_t>(q);
+        return !p || !q || u + n <= v || v + m <= u;
+    };
+    for (int i = 0; i < 2; ++i) {   // what step i writes
+        const nm_conv_desc* const o = d[1 - i];
+        const size_t n = (size_t)g[i].M * g[i].N, cols = (size_t)o->Cout * sizeof(float);
+        if (!apart(g[i].out_q, n, o->x, (size_t)o->B * o->H * o->W * o->Cin) || !apart(g[i].out_q, n, o->w, (size_t)o->Cout * g[1 - i].K) ||
+            !apart(g[i].out_q, n, o->bias, cols) || !apart(g[i].out_q, n, o->alpha_vec, cols) ||
+            !apart(g[i].out_q, n, g[1 - i].out_q, (size_t)g[1 - i].M * g[1 - i].N))
+            return NM_OK;
+    }
+    return launch_conv_pair(g[0], g[1], stream, done);
+}
+
 }  // namespace nm
 
 using namespace nm;
@@ -495,21 +549,10 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
     if (rc) return rc;
     if (!d->out_q && !d->out_f32 && !d->dbg_acc) return fail(NM_ERR_INVALID_ARG, "nm_conv2d_pwl: no output");
     GemmArgs g;
-    if (d->table_idx >= 0) {
-        rc = get_dev_table(d->tables, d->table_idx, &g.table, "nm_conv2d_pwl");
-        if (rc) return rc;
-        g.has_table = 1;
-    }
+    if ((rc = conv_args(d, pl, &g))) return rc;
     if (pl.M == 0) return NM_OK;  // an empty batch may come with NULL pointers
     if (!d->x || !d->w) return fail(NM_ERR_INVALID_ARG, "nm_conv2d_pwl: x or w is NULL");
     hipStream_t stream = (hipStream_t)stream_;
-    g.M = (int)pl.M; g.N = d->Cout; g.K = pl.K;
-    g.W = d->w; g.ldw = pl.K;
-    g.bias = d->bias; g.alpha_vec = d->alpha_vec; g.alpha = d->alpha;
-    g.resid = d->resid; g.resid_scale = d->resid_scale;
-    g.out_inv_scale = d->out_inv_scale;
-    g.ldo = d->Cout;
-    g.out_q = d->out_q; g.out_f32 = d->out_f32; g.out_acc = d->dbg_acc;
     if (pl.route == 3) {
         if (!ws) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace is NULL");
         if (!aligned(ws, 256)) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace not 256-byte aligned");
@@ -540,10 +583,7 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
     if (pl.route == 0) {
         g.A = d->x; g.lda = d->Cin;
     } else if (pl.route == 1) {
-        g.A = d->x; g.lda = d->Cin;
-        g.conv = 1;
-        g.cH = d->H; g.cW = d->W; g.cCin = d->Cin; g.cKw = d->kw; g.cStride = d->stride; g.cPad = d->pad;
-        g.cHo = pl.Ho; g.cWo = pl.Wo;
+        gather_args(d, pl, &g);
     } else {
         if (!ws) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace is NULL");
         if (!aligned(ws, 256)) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace not 256-byte aligned");
@@ -635,7 +675,13 @@ int32_t nm_cnn_run(const nm_cnn_op* ops, int32_t n_ops, void* ws, size_t ws_byte
         const nm_cnn_op& o = ops[i];
         int32_t rc;
         switch (o.kind) {
-        case NM_OP_CONV: rc = nm_conv2d_pwl(&o.conv, ws, ws_bytes, stream); break;
+        case NM_OP_CONV: {
+            bool both = false;
+            if (i + 1 < n_ops && ops[i + 1].kind == NM_OP_CONV && (rc = conv_pair(&o.conv, &ops[i + 1].conv, (hipStream_t)stream, &both))) return rc;
+            if (both) ++i;
+            rc = both ? NM_OK : nm_conv2d_pwl(&o.conv, ws, ws_bytes, stream);
+            break;
+        }
         case NM_OP_MAXPOOL: rc = nm_maxpool_i8(o.x, o.B, o.H, o.W, o.C, o.k, o.stride, o.pad, o.y, stream); break;
         case NM_OP_AVGPOOL: rc = nm_avgpool_i8(o.x, o.B, o.H, o.C, o.alpha, o.out_inv_scale, o.y, o.y_f32, stream); break;
         case NM_OP_GEMM: rc = nm_gemm_pwl(&o.gemm, stream); break;

@@ -745,6 +745,64 @@ bool gemm_folds_layernorm(const GemmArgs& g)
     return al && (int64_t)g.M * g.lda < (1LL << 32) && (int64_t)g.N * g.ldw < (1LL << 32);
 }
 
+// 16-byte loads need every row start and every batch offset on a 16-byte boundary
+static bool rows_aligned(const void* base, long ld, long outer, long inner) { return aligned(base, 16) && ld % 16 == 0 && outer % 16 == 0 && inner % 16 == 0; }
+
+// table: g's, or its expanded form
+static void fill_params(const GemmArgs& g, const DevTable& table, GemmParams& p)
+{
+    p.M = g.M; p.N = g.N; p.K = g.K;
+    p.A = g.A; p.lda = g.lda; p.W = g.W; p.ldw = g.ldw;
+    p.inner_count = g.inner_count;
+    p.a_outer = g.a_outer; p.a_inner = g.a_inner; p.w_outer = g.w_outer; p.w_inner = g.w_inner;
+    p.o_outer = g.o_outer; p.o_inner = g.o_inner;
+    p.bias = g.bias; p.alpha_vec = g.alpha_vec; p.alpha = g.alpha;
+    p.resid = g.resid; p.resid_scale = g.resid_scale;
+    p.has_table = g.has_table; p.table = table;
+    p.out_inv_scale = g.out_inv_scale; p.out_inv_scale_vec = g.out_inv_scale_vec;
+    p.split_cols = g.split_cols;
+    p.relu = g.has_table && g.split_cols == 0 && !g.out_inv_scale_vec && relu_codes(table, g.out_inv_scale, g.resid ? g.resid_scale : 0.0f);
+    for (int i = 0; i < 3; ++i) p.inv3[i] = g.inv3[i];
+    p.ldo = g.ldo;
+    p.cH = g.cH; p.cW = g.cW; p.cCin = g.cCin; p.cKw = g.cKw; p.cStride = g.cStride; p.cPad = g.cPad;
+    p.cHo = g.cHo; p.cWo = g.cWo;
+    p.out_q = g.out_q; p.out_f32 = g.out_f32; p.out_acc = g.out_acc; p.dbg_seg = g.dbg_seg;
+
+    p.vec_out = g.ldo % 4 == 0 && g.o_outer % 4 == 0 && g.o_inner % 4 == 0 &&
+                (!g.out_q || aligned(g.out_q, 4)) && (!g.out_f32 || aligned(g.out_f32, 16)) &&
+                (!g.out_acc || aligned(g.out_acc, 16)) && (!g.dbg_seg || aligned(g.dbg_seg, 8)) &&
+                (!g.resid || aligned(g.resid, 4));
+    p.r16 = g.resid && aligned(g.resid, 16) && g.ldo % 16 == 0 && g.o_outer % 16 == 0 && g.o_inner % 16 == 0 && g.N % 16 == 0;
+    p.q16 = g.out_q && aligned(g.out_q, 16) && g.ldo % 16 == 0 && g.o_outer % 16 == 0 && g.o_inner % 16 == 0;
+    p.vec_cols = (!g.bias || aligned(g.bias, 16)) && (!g.alpha_vec || aligned(g.alpha_vec, 16)) &&
+                 (!g.out_inv_scale_vec || aligned(g.out_inv_scale_vec, 16));
+}
+
+// Bytes of A that a gathered or plain product reads.
+static int64_t operand_extent(const GemmArgs& g)
+{
+    return g.conv ? (int64_t)(g.M / (g.cHo * g.cWo)) * g.cH * g.cW * g.cCin : (int64_t)(g.M - 1) * g.lda + g.K;
+}
+
+int32_t launch_conv_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done)
+{
+    *done = false;
+    const GemmArgs* const g[2] = {&a, &b};
+    GemmParams p[2] = {};
+    for (int i = 0; i < 2; ++i) {
+        const GemmArgs& c = *g[i];
+        fill_params(c, c.table, p[i]);
+        if (force_generic() || forced_cfg().kind != FORCED_NONE || !rows_aligned(c.A, 0, 0, 0) || !rows_aligned(c.W, c.ldw, 0, 0) || c.cCin % 64 != 0 ||
+            c.K % (c.cCin * c.cKw) != 0 || operand_extent(c) >= (1LL << 31) || (int64_t)(c.N - 1) * c.ldw + c.K >= (1LL << 31) ||
+            (int64_t)c.M * c.N >= direct_below(false, c.N, c.K) || !direct_pair_takes(p[i]))
+            return NM_OK;
+    }
+    const int cfg = choose_direct_pair({a.M, b.M}, {a.N, b.N}, {a.K, b.K});
+    if (cfg < 0) return NM_OK;
+    *done = true;
+    return launch_direct_pair(p, cfg, stream);
+}
+
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.M == 0) return NM_OK;
@@ -766,33 +824,9 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     DevTable table = g.table;
     if (only_q && !g.resid && !g.out_inv_scale_vec && !g.dbg_seg && !table.clamp_input) table.cellmap = nullptr;
     GemmParams p{};
-    p.M = g.M; p.N = g.N; p.K = g.K;
-    p.A = g.A; p.lda = g.lda; p.W = g.W; p.ldw = g.ldw;
-    p.inner_count = g.inner_count;
-    p.a_outer = g.a_outer; p.a_inner = g.a_inner; p.w_outer = g.w_outer; p.w_inner = g.w_inner;
-    p.o_outer = g.o_outer; p.o_inner = g.o_inner;
-    p.bias = g.bias; p.alpha_vec = g.alpha_vec; p.alpha = g.alpha;
-    p.resid = g.resid; p.resid_scale = g.resid_scale;
-    p.has_table = g.has_table; p.table = table;
-    p.out_inv_scale = g.out_inv_scale; p.out_inv_scale_vec = g.out_inv_scale_vec;
-    p.split_cols = g.split_cols;
-    p.relu = g.has_table && g.split_cols == 0 && !g.out_inv_scale_vec && relu_codes(g.table, g.out_inv_scale, g.resid ? g.resid_scale : 0.0f);
-    for (int i = 0; i < 3; ++i) p.inv3[i] = g.inv3[i];
-    p.ldo = g.ldo;
-    p.cH = g.cH; p.cW = g.cW; p.cCin = g.cCin; p.cKw = g.cKw; p.cStride = g.cStride; p.cPad = g.cPad;
-    p.cHo = g.cHo; p.cWo = g.cWo;
-    p.out_q = g.out_q; p.out_f32 = g.out_f32; p.out_acc = g.out_acc; p.dbg_seg = g.dbg_seg;
-
-    // 16-byte loads need every row start and every batch offset on a 16-byte boundary
-    const bool a_al = aligned(g.A, 16) && g.lda % 16 == 0 && g.a_outer % 16 == 0 && g.a_inner % 16 == 0;
-    const bool w_al = aligned(g.W, 16) && g.ldw % 16 == 0 && g.w_outer % 16 == 0 && g.w_inner % 16 == 0;
+    fill_params(g, table, p);
+    const bool a_al = rows_aligned(g.A, g.lda, g.a_outer, g.a_inner), w_al = rows_aligned(g.W, g.ldw, g.w_outer, g.w_inner);
     const bool al = a_al && w_al && g.K % 16 == 0 && (!g.w_is_kn || g.N % 16 == 0);
-    p.vec_out = g.ldo % 4 == 0 && g.o_outer % 4 == 0 && g.o_inner % 4 == 0 &&
-                (!g.out_q || aligned(g.out_q, 4)) && (!g.out_f32 || aligned(g.out_f32, 16)) &&
-                (!g.out_acc || aligned(g.out_acc, 16)) && (!g.dbg_seg || aligned(g.dbg_seg, 8)) &&
-                (!g.resid || aligned(g.resid, 4));
-    p.r16 = g.resid && aligned(g.resid, 16) && g.ldo % 16 == 0 && g.o_outer % 16 == 0 && g.o_inner % 16 == 0 && g.N % 16 == 0;
-    p.q16 = g.out_q && aligned(g.out_q, 16) && g.ldo % 16 == 0 && g.o_outer % 16 == 0 && g.o_inner % 16 == 0;
 
     // LDS bytes of the table: {k, b} per segment, or for the two-level form of a merged table one
     // {k, b} per merged segment plus a byte per primary cell
@@ -801,8 +835,6 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     const int batches = g.outer_count * g.inner_count;
     if (batches > 65535) return fail(NM_ERR_UNSUPPORTED, "gemm: more than 65535 batched problems");
     int32_t rc = NM_OK;
-    p.vec_cols = (!g.bias || aligned(g.bias, 16)) && (!g.alpha_vec || aligned(g.alpha_vec, 16)) &&
-                 (!g.out_inv_scale_vec || aligned(g.out_inv_scale_vec, 16));
     int epi = EPI_GENERIC;
     if (!g.out_inv_scale_vec && !g.dbg_seg && !(g.has_table && table.cellmap)) {
         // EPI_Q_TABLE is compiled without the input clamp; a table with that flag takes the generic epilogue
@@ -858,7 +890,7 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
     // The largest losses on this side are 300 x 3072 x 1024 (4.9 | 5.3) and 1500 x 640 x 640 (5.1 | 5.2).  The streaming
     // kernel's tiles need about a million outputs, more when the contraction is short and a large tile is mostly
     // prologue and epilogue.
-    const int64_t a_extent = g.conv ? (int64_t)(g.M / (g.cHo * g.cWo)) * g.cH * g.cW * g.cCin : (int64_t)(g.M - 1) * g.lda + g.K;
+    const int64_t a_extent = operand_extent(g);
     const bool direct_ok = !force_generic() && !g.w_is_kn && a_extent < (1LL << 31) && (int64_t)(g.N - 1) * g.ldw + g.K < (1LL << 31);
     const int direct_align = !(aligned(g.A, 4) && g.lda % 4 == 0 && g.a_outer % 4 == 0 && g.a_inner % 4 == 0 && aligned(g.W, 4) &&
                                g.ldw % 4 == 0 && g.w_outer % 4 == 0 && g.w_inner % 4 == 0) ? 1 : al ? 16 : 4;

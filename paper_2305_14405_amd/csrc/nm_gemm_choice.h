@@ -186,6 +186,19 @@ inline bool direct_takes(int c, int K, size_t table_bytes, bool gathered)
     return c >= 0 && c < kDirectTileCount && direct_cost(c, gathered).start > 0 && direct_lds(c, K, table_bytes) <= 160 * 1024;
 }
 
+inline long direct_tiles(int c, int M, int N) { return (long)((M + kDirectTiles[c].bm - 1) / kDirectTiles[c].bm) * ((N + kDirectTiles[c].bn - 1) / kDirectTiles[c].bn); }
+// slices: of a tile, on average
+inline double direct_us(int c, long tiles, int K, double slices, size_t table_bytes, bool gathered)
+{
+    const DirectTile& t = kDirectTiles[c];
+    const DirectCost& u = direct_cost(c, gathered);
+    const int chain = ((K + 127) / 128 + t.kw - 1) / t.kw;
+    const size_t lds = direct_lds(c, K, table_bytes);
+    const long L = (tiles + 255) / 256, fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap;
+    const long R = (L + share - 1) / share;
+    return u.start + L * (u.tile + u.slice * slices) + R * (u.round + u.chain * chain) + u.wave * chain;
+}
+
 inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes, bool gathered)
 {
     // Many products of a short contraction (attention scores; the fit has none): 32x32 tiles, 16x32 where those are few.  us, 16x32 |
@@ -195,17 +208,30 @@ inline int choose_direct(int M, int N, int K, int batches, size_t table_bytes, b
     int best = 2;
     double best_us = 0.0;
     bool any = false;
-    const int nk = (K + 127) / 128;
     for (int c = 0; c < kDirectTileCount; ++c) {
         if (!direct_takes(c, K, table_bytes, gathered)) continue;
-        const DirectTile& t = kDirectTiles[c];
-        const DirectCost& u = direct_cost(c, gathered);
-        const int chain = (nk + t.kw - 1) / t.kw;
-        const size_t lds = direct_lds(c, K, table_bytes);
-        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batches, L = (tiles + 255) / 256;
-        const long fit = (long)(160 * 1024 / (lds + 1024)), cap = 32 / t.kw, share = fit < 1 ? 1 : fit < cap ? fit : cap, R = (L + share - 1) / share;
-        const double us = u.start + L * (u.tile + u.slice * nk) + R * (u.round + u.chain * chain) + u.wave * chain;
+        const double us = direct_us(c, direct_tiles(c, M, N) * batches, K, (K + 127) / 128, table_bytes, gathered);
         if (!any || us < best_us) best_us = us, best = c, any = true;
+    }
+    return best;
+}
+
+// Two gathered products as one launch: the tile for both, or -1 where two launches are predicted to take less.  The cost is that of all
+// tiles with the longer contraction's chain and the tiles' mean number of slices.
+inline int choose_direct_pair(const int (&M)[2], const int (&N)[2], const int (&K)[2])
+{
+    double apart = 0.0;
+    for (int i = 0; i < 2; ++i) {
+        const int c = choose_direct(M[i], N[i], K[i], 1, 0, true);
+        apart += direct_us(c, direct_tiles(c, M[i], N[i]), K[i], (K[i] + 127) / 128, 0, true);
+    }
+    int best = -1;
+    for (int c = 0; c < kDirectTileCount; ++c) {
+        const int k = K[0] > K[1] ? K[0] : K[1];
+        if (!direct_takes(c, k, 0, true)) continue;
+        const long t0 = direct_tiles(c, M[0], N[0]), t1 = direct_tiles(c, M[1], N[1]);
+        const double us = direct_us(c, t0 + t1, k, (double)(t0 * ((K[0] + 127) / 128) + t1 * ((K[1] + 127) / 128)) / (t0 + t1), 0, true);
+        if (us < apart) apart = us, best = c;
     }
     return best;
 }

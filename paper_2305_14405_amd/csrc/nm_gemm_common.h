@@ -65,6 +65,10 @@ struct GemmLnParams : GemmParams {
 // 1); forced: tile configuration 0 .. 6, or -1 for the rule.
 int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t table_bytes, int forced, hipStream_t s);
 
+// Two convolutions as one launch of that kernel: whether the epilogue of p allows it, and the launch (tile configuration cfg for both).
+bool direct_pair_takes(const GemmParams& p);
+int32_t launch_direct_pair(GemmParams (&p)[2], int cfg, hipStream_t s);
+
 // The tile kernel's configuration cfg for K in whole chunks of 16 bytes but not whole slices (nm_gemm_end.hip).
 int32_t launch_tile_end(int cfg, GemmParams& p, int epi, size_t table_bytes, hipStream_t s);
 

@@ -78,7 +78,7 @@ static void direct_args(DirectConvParams& q, const GemmParams& p)
 // load and 1400 on the epilogue, of 7000 in all.  The fixed forms are a third of the code on the way, and divisions are by
 // host-made reciprocals: 12 base layers over 1 x 128 tokens 360 -> 340 us, ResNet-50 on one image 245 -> 211.
 template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm, bool kEnd>
-__global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, kEpi> p)
+__device__ __forceinline__ void direct_tile(const DirectArgs<kConv, kEpi>& p, const unsigned block)
 {
     constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
     constexpr int NA = BM / 8, NI = (BM + BN) / 8;   // 1 KB pieces (8 rows) of a slice; the first NA are A rows
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, 
     // Workgroup i runs on XCD i % 8: an XCD gets a contiguous eighth of the tiles, rows of tiles
     // innermost, so that a panel of W is fetched into one L2.
     const int ntiles = p.tiles_m * p.tiles_n, share = (ntiles + 7) >> 3;
-    const int id = (blockIdx.x % 8) * share + blockIdx.x / 8;
+    const int id = (int)((block % 8) * share + block / 8);
     if (id >= ntiles) return;
     const int tile_n = (int)quotient((unsigned)id, p.div_tiles_m);
     const int m0 = (id - tile_n * p.tiles_m) * BM, n0 = tile_n * BN;
@@ -441,6 +441,26 @@ __global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, 
     }
 }
 
+template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm, bool kEnd>
+__global__ __launch_bounds__(64 * KW) void gemm_direct_kernel(DirectArgs<kConv, kEpi> p)
+{
+    direct_tile<BM, BN, KW, D, kAl, kConv, kEpi, kForm, kEnd>(p, blockIdx.x);
+}
+
+// Two convolutions that do not depend on one another (the 3x3 one of a residual block and the projection of its shortcut): the workgroups of
+// the second behind the first's.  At small batches either is half a launch.  us, two launches -> one, four such pairs: ResNet-50 on one image of 224 x 224
+// 196 -> 188, a network of one block a stage 79 -> 71, on three images of 160 x 160 83 -> 75.
+struct DirectPair {
+    DirectConvParams p[2];
+    unsigned first;   // workgroups of the first, a multiple of 8
+};
+template <int BM, int BN, int KW, int D>
+__global__ __launch_bounds__(64 * KW) void gemm_direct_pair_kernel(DirectPair q)
+{
+    const bool second = blockIdx.x >= q.first;
+    direct_tile<BM, BN, KW, D, 16, true, EPI_Q_TABLE, FORM_TWO_SEGMENTS, false>(second ? q.p[1] : q.p[0], second ? blockIdx.x - q.first : blockIdx.x);
+}
+
 template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi = EPI_GENERIC, int kForm = FORM_ANY, bool kEnd = false>
 static int32_t launch_direct_t(GemmParams& p, int batches, size_t table_bytes, hipStream_t s)
 {
@@ -534,6 +554,58 @@ int32_t launch_direct(GemmParams& p, int align, bool conv, int batches, size_t t
     case 4: return launch_direct_aligned<48, 64, 4, 2>(p, conv, batches, table_bytes, s);
     case 6: return launch_direct_conv<32, 32, 8, 2>(p, batches, table_bytes, s);
     default: return launch_direct_aligned<64, 64, 4, 2>(p, conv, batches, table_bytes, s);
+    }
+}
+
+template <int BM, int BN, int KW, int D>
+static int32_t launch_pair(GemmParams (&p)[2], hipStream_t s)
+{
+    auto kern = gemm_direct_pair_kernel<BM, BN, KW, D>;
+    static std::once_flag once;  // one attribute call per instantiation
+    static int32_t once_rc = NM_OK;
+    std::call_once(once, [&] {
+        once_rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+                            "hipFuncSetAttribute(gemm_direct_pair_kernel)");
+    });
+    if (once_rc) return once_rc;
+    DirectPair q;
+    size_t shmem = 0;
+    unsigned grid[2];
+    for (int i = 0; i < 2; ++i) {
+        const int need = ((p[i].K + 127) / 128 + KW - 1) / KW;
+        const size_t lds = (size_t)KW * (need < D ? need : D) * (BM + BN) * 128;
+        shmem = shmem > lds ? shmem : lds;
+        p[i].tiles_m = (p[i].M + BM - 1) / BM;
+        p[i].tiles_n = (p[i].N + BN - 1) / BN;
+        p[i].batched = 0;
+        p[i].div_tiles_m = fast_div(p[i].tiles_m);
+        p[i].div_wo = fast_div(p[i].cWo), p[i].div_ho = fast_div(p[i].cHo), p[i].div_cin = fast_div(p[i].cCin), p[i].div_kw = fast_div(p[i].cKw);
+        grid[i] = (unsigned)(p[i].tiles_m * p[i].tiles_n + 7) / 8 * 8;
+        direct_args(q.p[i], p[i]);
+        if (!p[i].has_table) q.p[i].table.k0 = q.p[i].table.k1 = 1.0f, q.p[i].table.b0 = q.p[i].table.b1 = q.p[i].table.tau = 0.0f;   // x itself
+    }
+    q.first = grid[0];
+    queue_kernel(kern, dim3(grid[0] + grid[1]), dim3(64 * KW), shmem, s, q);
+    return check_hip(hipGetLastError(), "gemm pair launch");
+}
+
+bool direct_pair_takes(const GemmParams& p)
+{
+    const int epi = lean_epilogue(p, true, 1);
+    return epi == EPI_Q || (epi == EPI_Q_TABLE && p.table.two_seg);
+}
+
+int32_t launch_direct_pair(GemmParams (&p)[2], int cfg, hipStream_t s)
+{
+    switch (cfg) {
+    case 0: return launch_pair<16, 32, 8, 3>(p, s);
+    case 1: return launch_pair<32, 32, 4, 2>(p, s);
+    case 2: return launch_pair<32, 64, 4, 1>(p, s);
+    case 3: return launch_pair<32, 64, 8, 1>(p, s);
+    case 4: return launch_pair<48, 64, 4, 2>(p, s);
+    case 6: return launch_pair<32, 32, 8, 2>(p, s);
+    default: return launch_pair<64, 64, 4, 2>(p, s);
     }
 }
 

@@ -176,6 +176,8 @@ struct GemmArgs {
 };
 
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream);
+// Two gathered products, neither of which reads or writes what the other writes, as one launch; *done = false where they are not for it.
+int32_t launch_conv_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done);
 // True when launch_gemm would fold the LayerNorm described by g.ln_* into the GEMM kernel.
 bool gemm_folds_layernorm(const GemmArgs& g);
 

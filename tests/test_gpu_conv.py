@@ -336,6 +336,44 @@ def test_cnn_run_matches_oracle_network(oracle):
     assert ei.value.status == nm.NM_ERR_INVALID_ARG
 
 
+# two neighbouring steps: H, Cin, then (Cout, k, stride, ReLU) of each on the same image, and how the second one is tied to the first
+@pytest.mark.parametrize("B,H,Cin,first,second,tie", [
+    (1, 28, 128, (128, 3, 2, True), (512, 1, 2, False), ""),        # a residual block's 3x3 convolution and its projection
+    (1, 14, 64, (64, 3, 1, True), (256, 1, 1, False), ""), (3, 15, 64, (52, 1, 1, False), (36, 5, 1, True), ""),
+    (1, 7, 512, (512, 3, 1, True), (2048, 1, 2, False), ""), (2, 30, 192, (136, 3, 1, False), (68, 2, 1, False), ""),
+    (5, 28, 128, (128, 3, 2, True), (512, 1, 2, False), ""), (1, 9, 64, (64, 3, 1, True), (30, 1, 1, False), ""),
+    (1, 14, 128, (128, 3, 1, True), (64, 3, 1, True), "chain"),     # the second reads the first's result,
+    (1, 14, 128, (128, 3, 1, True), (128, 1, 1, True), "image"),    # writes over its image,
+    (1, 14, 128, (128, 3, 1, True), (128, 1, 1, True), "result")])  # or over its result
+def test_neighbouring_convolutions(oracle, B, H, Cin, first, second, tie):
+    """nm_cnn_run on two convolutions: as one launch where neither touches what the other writes, one after the other where it does."""
+    g = np.random.default_rng(H + Cin)
+    ot, dt = relu_tables(oracle)
+    x = rand_i8(g, (B, H, H, Cin), 60)
+    dx = dev(x)
+    ops, keep, want, ys, src, dsrc = [], [], [], [], x, dx
+    for n, (cout, k, stride, relu) in enumerate((first, second)):
+        w, bias = rand_i8(g, (cout, k, k, Cin), 60), g.standard_normal(cout).astype(np.float32)
+        alpha = (1e-3 * (1 + g.random(cout))).astype(np.float32)
+        r = oracle.conv2d_pwl(src, w, stride, k // 2, bias=bias, alpha_vec=alpha, table=ot if relu else None, out_inv_scale=9.0)
+        want.append(r["q"])
+        y = torch.full(r["q"].shape, 77, dtype=torch.int8, device=DEV)
+        if n == 1 and tie == "image": y = dx
+        if n == 1 and tie == "result": y = ys[0]
+        ys.append(y)
+        d = [dev(w), dev(bias), dev(alpha)]
+        keep += d
+        ops.append(nm.cnn_op_conv(nm.make_conv_desc(dsrc, d[0], stride, k // 2, bias=d[1], alpha_vec=d[2], tables=dt, table_idx=0 if relu else -1,
+                                                    out_inv_scale=9.0, out_q=y)))
+        if tie == "chain": src, dsrc, Cin = r["q"], y, cout
+    if tie == "image":
+        ops = ops[:1] + [nm.cnn_op_conv(nm.make_conv_desc(ys[0], keep[3], 1, 0, bias=keep[4], alpha_vec=keep[5], tables=dt, table_idx=0, out_inv_scale=9.0, out_q=dx))]
+        want[1] = oracle.conv2d_pwl(want[0], host(keep[3]), 1, 0, bias=host(keep[4]), alpha_vec=host(keep[5]), table=ot, out_inv_scale=9.0)["q"]
+    nm.nm_cnn_run(ops, torch.empty(256, dtype=torch.uint8, device=DEV))
+    for n in (0, 1):
+        if not (n == 0 and tie == "result"): assert np.array_equal(host(ys[n]), want[n]), f"step {n}"
+
+
 def test_conv2d_unaligned_operands_take_the_patch_matrix_route(oracle):
     """A 64-channel convolution whose image or filter pointer is not 16-byte aligned cannot use the
     gathered loader: it needs a workspace and still matches the oracle."""
