@@ -524,6 +524,19 @@ static void gather_args(const nm_conv_desc* d, const ConvPlan& pl, GemmArgs* g)
     g->cHo = pl.Ho; g->cWo = pl.Wo;
 }
 
+static bool apart(const void* p, size_t n, const void* q, size_t m)
+{
+    const uintptr_t u = reinterpret_cast<uintptr_t>(p), v = reinterpret_cast<uintptr_t>(q);
+    return !p || !q || u + n <= v || v + m <= u;
+}
+// Whether n bytes at `out` are apart from all that a step reads (g: its product, whose A is d->x) and writes.
+static bool apart_from_step(const void* out, size_t n, const nm_conv_desc* d, const GemmArgs& g)
+{
+    const size_t cols = (size_t)g.N * sizeof(float), outputs = (size_t)g.M * g.N;
+    return apart(out, n, d->x, (size_t)d->B * d->H * d->W * d->Cin) && apart(out, n, d->w, (size_t)g.N * g.K) && apart(out, n, d->bias, cols) &&
+           apart(out, n, d->alpha_vec, cols) && apart(out, n, d->resid, outputs) && apart(out, n, d->out_q, outputs);
+}
+
 // Two steps of a network as one launch where both are small convolutions and neither touches what the other writes.
 static int32_t conv_pair(const nm_conv_desc* a, const nm_conv_desc* b, hipStream_t stream, bool* done)
 {
@@ -536,19 +549,33 @@ static int32_t conv_pair(const nm_conv_desc* a, const nm_conv_desc* b, hipStream
         if (plan_conv(d[i], "nm_conv2d_pwl", &pl) || pl.route > 1 || pl.M == 0 || conv_args(d[i], pl, &g[i])) return NM_OK;   // (the step itself reports it)
         gather_args(d[i], pl, &g[i]);
     }
-    const auto apart = [](const void* p, size_t n, const void* q, size_t m) {
-        const uintptr_t u = reinterpret_cast<uintptr_t>(p), v = reinterpret_cast<uintptr_t>(q);
-        return !p || !q || u + n <= v || v + m <= u;
-    };
-    for (int i = 0; i < 2; ++i) {   // what step i writes
-        const nm_conv_desc* const o = d[1 - i];
-        const size_t n = (size_t)g[i].M * g[i].N, cols = (size_t)o->Cout * sizeof(float);
-        if (!apart(g[i].out_q, n, o->x, (size_t)o->B * o->H * o->W * o->Cin) || !apart(g[i].out_q, n, o->w, (size_t)o->Cout * g[1 - i].K) ||
-            !apart(g[i].out_q, n, o->bias, cols) || !apart(g[i].out_q, n, o->alpha_vec, cols) ||
-            !apart(g[i].out_q, n, g[1 - i].out_q, (size_t)g[1 - i].M * g[1 - i].N))
-            return NM_OK;
-    }
+    for (int i = 0; i < 2; ++i)
+        if (!apart_from_step(g[i].out_q, (size_t)g[i].M * g[i].N, d[1 - i], g[1 - i])) return NM_OK;
     return launch_conv_pair(g[0], g[1], stream, done);
+}
+
+// A 1x1 convolution with a shortcut and the 1x1 one that reads its result as one launch, where nothing else that either reads or writes
+// is what the other writes.
+static int32_t conv_chain(const nm_conv_desc* a, const nm_conv_desc* b, hipStream_t stream, bool* done)
+{
+    *done = false;
+    if (!a->resid || b->resid || !a->out_q || b->x != a->out_q) return NM_OK;
+    const nm_conv_desc* const d[2] = {a, b};
+    GemmArgs g[2];
+    for (int i = 0; i < 2; ++i) {
+        ConvPlan pl;
+        if (!d[i]->out_q || d[i]->out_f32 || d[i]->dbg_acc || !d[i]->x || !d[i]->w) return NM_OK;
+        if (plan_conv(d[i], "nm_conv2d_pwl", &pl) || pl.route != 0 || pl.M == 0 || conv_args(d[i], pl, &g[i])) return NM_OK;   // (the step itself reports it)
+        g[i].A = d[i]->x; g[i].lda = d[i]->Cin;
+    }
+    if (g[0].M != g[1].M || g[0].N != g[1].K) return NM_OK;
+    const size_t n0 = (size_t)g[0].M * g[0].N, n1 = (size_t)g[1].M * g[1].N, cols0 = (size_t)g[0].N * sizeof(float), cols1 = (size_t)g[1].N * sizeof(float);
+    if (!apart_from_step(g[1].out_q, n1, a, g[0]) || !apart(g[0].out_q, n0, a->x, (size_t)g[0].M * g[0].K) || !apart(g[0].out_q, n0, a->w, (size_t)g[0].N * g[0].K) ||
+        !apart(g[0].out_q, n0, a->bias, cols0) || !apart(g[0].out_q, n0, a->alpha_vec, cols0) || !apart(g[0].out_q, n0, a->resid, n0) ||
+        !apart(g[0].out_q, n0, b->w, (size_t)g[1].N * g[1].K) || !apart(g[0].out_q, n0, b->bias, cols1) || !apart(g[0].out_q, n0, b->alpha_vec, cols1) ||
+        !apart(g[1].out_q, n1, b->w, (size_t)g[1].N * g[1].K) || !apart(g[1].out_q, n1, b->bias, cols1) || !apart(g[1].out_q, n1, b->alpha_vec, cols1))
+        return NM_OK;
+    return launch_conv_chain(g[0], g[1], stream, done);
 }
 
 }  // namespace nm
@@ -705,6 +732,7 @@ int32_t nm_cnn_run(const nm_cnn_op* ops, int32_t n_ops, void* ws, size_t ws_byte
         case NM_OP_CONV: {
             bool both = false;
             if (i + 1 < n_ops && ops[i + 1].kind == NM_OP_CONV && (rc = conv_pair(&o.conv, &ops[i + 1].conv, (hipStream_t)stream, &both))) return rc;
+            if (!both && i + 1 < n_ops && ops[i + 1].kind == NM_OP_CONV && (rc = conv_chain(&o.conv, &ops[i + 1].conv, (hipStream_t)stream, &both))) return rc;
             if (both) ++i;
             rc = both ? NM_OK : nm_conv2d_pwl(&o.conv, ws, ws_bytes, stream);
             break;

@@ -45,6 +45,8 @@ static ForcedCfg forced_cfg()
     return v;
 }
 
+bool gemm_switched() { return force_generic() || forced_cfg().kind != FORCED_NONE; }
+
 // 16 bytes of a row-major int8 matrix at (row, k .. k+15); zeros outside [0,nrows) x [0,K).
 template <bool kAligned>
 __device__ __forceinline__ v4i load_chunk(const int8_t* __restrict__ X, long ld, int row, int nrows,
@@ -792,7 +794,7 @@ int32_t launch_conv_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t strea
     for (int i = 0; i < 2; ++i) {
         const GemmArgs& c = *g[i];
         fill_params(c, c.table, p[i]);
-        if (force_generic() || forced_cfg().kind != FORCED_NONE || !rows_aligned(c.A, 0, 0, 0) || !rows_aligned(c.W, c.ldw, 0, 0) || c.cCin % 64 != 0 ||
+        if (gemm_switched() || !rows_aligned(c.A, 0, 0, 0) || !rows_aligned(c.W, c.ldw, 0, 0) || c.cCin % 64 != 0 ||
             c.K % (c.cCin * c.cKw) != 0 || operand_extent(c) >= (1LL << 31) || (int64_t)(c.N - 1) * c.ldw + c.K >= (1LL << 31) ||
             (int64_t)c.M * c.N >= direct_below(false, c.N, c.K) || !direct_pair_takes(p[i]))
             return NM_OK;

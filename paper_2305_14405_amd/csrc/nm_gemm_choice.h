@@ -322,6 +322,38 @@ inline int qkv_attention_form(int B, int S, int heads, int K)
     return K > 384 ? QKV_ATTENTION_EIGHT : QKV_ATTENTION_FOUR;
 }
 
+// Two 1x1 convolutions as one kernel (nm_conv_chain.hip): K to N1 channels with a shortcut, and those to N2, at M positions.
+constexpr int chain_waves(int K) { return K == 64 ? 4 : 8; }   // of a workgroup
+// LDS: both filters, scale and bias of both products' columns, a word per wavefront.
+constexpr size_t conv_chain_lds(int K, int N1, int N2) { return (size_t)N1 * (K + N2) + 8 * (size_t)(N1 + N2) + 32; }
+constexpr bool conv_chain_built(int K, int N1, int N2)
+{
+    return (K == 64 || (K == 128 && N2 == 128)) && (N2 == 64 || N2 == 128) && N1 % 256 == 0 && conv_chain_lds(K, N1, N2) <= 148 * 1024;
+}
+// Workgroups that a CU holds: by LDS, and by registers (12 or 8 wavefronts).
+constexpr int conv_chain_share(int K, int N1, int N2)
+{
+    const int fit = (int)(160 * 1024 / conv_chain_lds(K, N1, N2)), most = K != 64 ? 1 : N2 == 64 ? 3 : 2;
+    return fit < most ? fit : most;
+}
+// Whether the one kernel is predicted to take less than two: a chain of 32 positions through all N1 channels per wavefront, as often as a
+// SIMD (at K = 128, its two wavefronts) has to, and the bytes of the one; a latency and the bytes of the two, which small tiles keep
+// from falling further.  Fitted to 160 measured triples of M from 300 to 262144 (rms 6 % and 9 %); over them the choice is 0.3 % slower than the better
+// one and 7 % at worst.  us, two kernels | one:
+//    64 ->  256 ->  64:  3136 7.7 | 7.8     12544 11.2 |  8.3    36000 11.8 | 12.6   100352 24.0 | 20.7   200704 36.7 | 29.7
+//    64 ->  256 -> 128:  3136 8.1 | 8.6     12544 12.6 |  9.4    36000 13.6 | 14.0   100352 27.6 | 23.8   200704 42.2 | 34.8
+//   128 ->  512 -> 128: 12544 11.6 | 18.9   36000 20.7 | 20.2    50176 25.1 | 21.1    75000 34.8 | 36.4   131072 51.1 | 42.4
+//    64 -> 1024 ->  64: 12544 15.3 | 21.4   32000 26.3 | 23.0    36000 29.7 | 34.0    65536 40.9 | 34.9   200704 135  | 127
+inline bool conv_chain_faster(int M, int K, int N1, int N2)
+{
+    const double m = M * 1e-6, bytes = m * (K + 2.0 * N1 + N2);
+    const long blocks = ((long)M + 31) / 32;
+    const double apart = 6.0 + 0.2 * (bytes + m * N1), least = m * N1 > 1.2 ? 10.0 : 0.0;
+    const double turns = (double)(K == 64 ? (blocks + 1023) / 1024 : (blocks + 2047) / 2048) * N1 / 256;
+    const double one = K != 64 ? 6.55 + 5.34 * turns + 0.097 * bytes : N2 == 64 ? 5.04 + 3.03 * turns + 0.05 * bytes : 5.31 + 3.45 * turns + 0.061 * bytes;
+    return one < (apart > least ? apart : least);
+}
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

@@ -178,6 +178,10 @@ struct GemmArgs {
 int32_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // Two gathered products, neither of which reads or writes what the other writes, as one launch; *done = false where they are not for it.
 int32_t launch_conv_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done);
+// A 1x1 convolution (rows of K, a shortcut) and the one that reads its result (b.A == a.out_q), nothing else of which is what the other
+// touches, as one launch; *done = false where they are not for it.
+int32_t launch_conv_chain(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done);
+bool gemm_switched();   // one of the debug switches says which kernel products take
 // True when launch_gemm would fold the LayerNorm described by g.ln_* into the GEMM kernel.
 bool gemm_folds_layernorm(const GemmArgs& g);
 

@@ -198,11 +198,14 @@ static int layernorm_rows()
 
 // choice_driver relu M N K kunit ...: for each product with the epilogues for convolutions the tile kernel's configuration, or -1 for
 // the small-tile kernel.  staged M N K align ...: the register-staged kernel's, with every output, table and residual, or -1.
-static int configurations(bool staged, int n, char** v)
+static int configurations(const char* kind, int n, char** v)
 {
     for (int i = 0; i + 3 < n; i += 4) {
         const int M = std::atoi(v[i]), N = std::atoi(v[i + 1]), K = std::atoi(v[i + 2]);
-        if (staged) {
+        if (!std::strcmp(kind, "chain")) {   // M, K, N1, N2
+            const int N2 = std::atoi(v[i + 3]);
+            std::printf("%d\n", conv_chain_built(N, K, N2) && conv_chain_faster(M, N, K, N2));
+        } else if (!std::strcmp(kind, "staged")) {
             const int align = std::atoi(v[i + 3]);
             const bool takes = (align < 16 || K % 64 != 0) && staged_faster(align, M, N, K, true, true, true, true);
             std::printf("%d\n", takes ? choose_unaligned(M, N, K, true, true, true, true) : -1);
@@ -214,7 +217,7 @@ static int configurations(bool staged, int n, char** v)
 
 int main(int argc, char** argv)
 {
-    if (argc > 2) return configurations(!std::strcmp(argv[1], "staged"), argc - 2, argv + 2);
+    if (argc > 2) return configurations(argv[1], argc - 2, argv + 2);
     if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;

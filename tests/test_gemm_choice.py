@@ -9,7 +9,7 @@ import sys
 
 import pytest
 
-from test_gpu_conv import LARGE_TILE_CASES
+from test_gpu_conv import CHAIN_CASES, LARGE_TILE_CASES
 from test_gpu_parity import STAGED_CASES
 from test_sanitizers import SAN, _run
 
@@ -50,6 +50,16 @@ def test_staged_products_reach_every_configuration(tmp_path):
     assert _configurations(tmp_path, "staged", products) == [c[3] for c in STAGED_CASES]
     reached = {(c[3], p[3]) for c, p in zip(STAGED_CASES, products) if c[3] >= 0}
     assert reached == {(tile, align) for tile in range(4) for align in (16, 4, 1)}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_chained_convolutions_are_one_kernel(tmp_path):
+    """The cases that compare two chained convolutions with the steps by themselves are one kernel, each of those built among them; few
+    positions, a second turn that is nearly empty and channels that it is not built for are not."""
+    assert _configurations(tmp_path, "chain", CHAIN_CASES) == [1] * len(CHAIN_CASES)
+    assert {(K, N2) for M, K, N1, N2 in CHAIN_CASES} == {(64, 64), (64, 128), (128, 128)}
+    others = [(300, 64, 256, 64), (33000, 64, 256, 64), (70000, 128, 512, 128), (50003, 128, 512, 64), (50003, 64, 320, 64), (50003, 64, 256, 256), (50003, 128, 1024, 128)]
+    assert _configurations(tmp_path, "chain", others) == [0] * len(others)
 
 
 # A program of its own: the switch is read once per process.

@@ -374,6 +374,57 @@ def test_neighbouring_convolutions(oracle, B, H, Cin, first, second, tie):
         if not (n == 0 and tie == "result"): assert np.array_equal(host(ys[n]), want[n]), f"step {n}"
 
 
+# positions (a last block of 32 that is not full, a second turn of the wavefronts) and channels of a widening and a narrowing convolution
+# that are one kernel (tests/test_gemm_choice.py holds them to its rule); forms at the smallest of each kernel
+CHAIN_CASES = [(5037, 64, 256, 64), (5037, 64, 256, 128), (50003, 128, 256, 128), (25089, 64, 512, 64), (100003, 64, 256, 64), (70003, 64, 256, 128),
+               (131041, 128, 512, 128)]
+
+
+@pytest.mark.parametrize("M,K,N1,N2,form", [(*c, "relu") for c in CHAIN_CASES] + [
+    (*c, form) for c in CHAIN_CASES[:3] for form in ("lines", "nonfinite", "scalar")] + [
+    (5037, 64, 256, 64, form) for form in ("over_x", "over_shortcut", "over_result", "over_bias", "apart")])
+def test_chained_convolutions(oracle, M, K, N1, N2, form):
+    """nm_cnn_run on a 1x1 convolution with a shortcut and the 1x1 one behind it gives what the two steps by themselves give, to the
+    bit: any two-segment table, columns that make a sum infinite or NaN, no bias, buffers that one step reads and the other writes."""
+    g = np.random.default_rng(M + K + N1 + N2)
+    if form == "lines": tables = nm.nm_tables_from_arrays([("relu", -8.0, 8.0, 2, 0)], [np.float32([0.125, 1.0])], [np.float32([0.1, -0.3])])
+    else: tables = relu_tables(oracle)[1]
+    x, w1, w2, r = rand_i8(g, (M, 1, 1, K)), rand_i8(g, (N1, 1, 1, K)), rand_i8(g, (N2, 1, 1, N1)), rand_i8(g, (M, 1, 1, N1))
+    bias = [g.standard_normal(n).astype(np.float32) for n in (N1, N2)]
+    alpha = [(a * (1 + g.random(n))).astype(np.float32) for a, n in ((1e-4, N1), (4e-5, N2))]
+    if form == "nonfinite":
+        bias[0][[3, 77]] = np.nan, np.inf
+        alpha[0][200], bias[1][17], alpha[1][60] = 3e38, -np.inf, np.nan
+
+    def run(call):
+        dx, dr, d1, d2 = dev(x), dev(r), dev(w1), dev(w2)
+        db, da = [dev(v) if form != "scalar" else None for v in bias], [dev(v) if form != "scalar" else None for v in alpha]
+        y1, y2 = (torch.full((M, 1, 1, n), 77, dtype=torch.int8, device=DEV) for n in (N1, N2))
+        if form == "over_x": y2 = dx
+        if form == "over_shortcut": y1 = dr
+        if form == "over_result": y2 = y1.view(-1)[M * N2:2 * M * N2].view(M, 1, 1, N2)
+        if form == "over_bias":   # of the second step, in what the first one writes
+            db[1] = y1.view(-1)[-4 * N2:].view(torch.float32)
+        src = y1.clone() if form == "apart" else y1   # the second step reads something else
+        ops = [nm.cnn_op_conv(nm.make_conv_desc(dx, d1, 1, 0, bias=db[0], alpha=2e-4, alpha_vec=da[0], resid=dr, resid_scale=0.01, tables=tables, table_idx=0,
+                                                out_inv_scale=30.0, out_q=y1)),
+               nm.cnn_op_conv(nm.make_conv_desc(src, d2, 1, 0, bias=db[1], alpha=6e-5, alpha_vec=da[1], tables=tables, table_idx=0, out_inv_scale=25.0, out_q=y2))]
+        call(ops)
+        return host(y1), host(y2)
+
+    ws = torch.empty(256, dtype=torch.uint8, device=DEV)
+    got = run(lambda ops: nm.nm_cnn_run(ops, ws))
+    want = run(lambda ops: (nm.nm_cnn_run(ops[:1], ws), nm.nm_cnn_run(ops[1:], ws)))
+    if form != "over_result":   # (rows of the second product read what others of it have written: any order is right)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        assert 0.1 < np.mean(got[0] != 0) and len(np.unique(got[0])) > 20
+    if form == "relu" and M < 10000:
+        ot = oracle.relu_table()
+        q1 = oracle.conv2d_pwl(x, w1, 1, 0, bias=bias[0], alpha_vec=alpha[0], resid=r, resid_scale=0.01, table=ot, out_inv_scale=30.0)["q"]
+        q2 = oracle.conv2d_pwl(q1, w2, 1, 0, bias=bias[1], alpha_vec=alpha[1], table=ot, out_inv_scale=25.0)["q"]
+        assert np.array_equal(got[0], q1) and np.array_equal(got[1], q2)
+
+
 def test_conv2d_unaligned_operands_take_the_patch_matrix_route(oracle):
     """A 64-channel convolution whose image or filter pointer is not 16-byte aligned cannot use the
     gathered loader: it needs a workspace and still matches the oracle."""
