@@ -8,8 +8,8 @@
 // widened 32 channels that a matrix instruction leaves in a lane's accumulators become, after two half swaps, the 16 bytes that the
 // second product's operand wants from that lane (and that are its piece of the output row), so neither LDS nor a barrier lies between
 // them.  LDS holds both filters whole, once per workgroup; the shortcut's next 256 channels are requested while the present ones are
-// worked on.  us, two kernels -> this one: 200704 positions of 64 -> 256 -> 64 channels 38.1 -> 31.0, -> 128 42.7 -> 34.8, 50176 of 128 -> 512
-// -> 128 25.3 -> 21.2; conv_chain_faster has the rest.  64 positions a wavefront, which halves the reads of scales and filters, was
+// worked on.  us, two kernels -> this one: 200704 positions of 64 -> 256 -> 64 channels 38.1 -> 29.6, -> 128 42.7 -> 34.5, 50176 of 128 -> 512
+// -> 128 25.3 -> 20.5; conv_chain_faster has the rest.  64 positions a wavefront, which halves the reads of scales and filters, was
 // slower (33.3), as was the next block's first product queued ahead (128 -> 512 -> 128 22.1) and 16 wavefronts a CU, which spill (36.4).
 #include <mutex>
 
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(64 * chain_waves(32 * KS), TN == 2 ? 3 : 2) void co
     // Lanes past the edge compute row M - 1 again and write its bytes again: in a branch, stores would be unknown to the wait for
     // the ring's loads.
     const auto row_of = [&](int blk) { return (long)min(32 * blk + fr, p.M - 1); };
-    int blk = blockIdx.x * NW + wave;
+    int blk = wave * gridDim.x + blockIdx.x;   // what is left of a last turn is one block to a workgroup
     v4i x[KS], r[RING];
     const auto load_x = [&](int blk) {
 #pragma unroll
@@ -239,7 +239,7 @@ static int32_t launch_chain_as(ChainParams& p, size_t shmem, int groups, hipStre
     });
     if (once_rc) return once_rc;
     p.blocks = (p.M + 31) / 32;
-    const int all = (p.blocks + NW - 1) / NW, grid = all < groups ? all : groups;
+    const int all = (p.blocks + NW - 1) / NW, grid = all < groups ? all : groups;   // (more of them, each with fewer blocks, wait for the filters: 25088 positions 8.2 -> 11.5)
     p.step = grid * NW;
     queue_kernel(kern, dim3(grid), dim3(64 * NW), shmem, s, p);
     return check_hip(hipGetLastError(), "convolution chain launch");
