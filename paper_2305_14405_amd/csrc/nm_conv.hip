@@ -638,6 +638,8 @@ int32_t nm_conv2d_pwl(const nm_conv_desc* d, void* ws, size_t ws_bytes, void* st
         g.A = d->x; g.lda = d->Cin;
     } else if (pl.route == 1) {
         gather_args(d, pl, &g);
+        bool done = false;
+        if ((rc = launch_conv_taps(g, stream, &done)) || done) return rc;
     } else {
         if (!ws) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace is NULL");
         if (!aligned(ws, 256)) return fail(NM_ERR_WORKSPACE, "nm_conv2d_pwl: workspace not 256-byte aligned");

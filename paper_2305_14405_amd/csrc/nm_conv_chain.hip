@@ -31,12 +31,7 @@ struct ChainParams {
     int8_t *y1, *y2;
 };
 
-// 16 bytes a lane between the accumulators' order (word g: columns 8 g + 4 * half) and the operands' (columns 16 * half and on).
-__device__ __forceinline__ v4i halves_to_row(unsigned w0, unsigned w1, unsigned w2, unsigned w3)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false), b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
-    return v4i{(int)a[0], (int)a[1], (int)b[0], (int)b[1]};
-}
+// The other way round from halves_to_row.
 __device__ __forceinline__ v4i row_to_halves(v4i r)
 {
     const auto a = __builtin_amdgcn_permlane32_swap((unsigned)r[0], (unsigned)r[1], false, false);

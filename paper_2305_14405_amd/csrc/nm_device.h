@@ -182,6 +182,13 @@ __device__ __forceinline__ unsigned pack4(int a, int b, int c, int d)
     return lo | hi;
 }
 
+// A row's 32 codes as a 32x32 matrix instruction leaves them (word g of a lane: columns 8 g + 4 * half, half = lane / 32) as the 16 bytes
+// from column 16 * half on: the lane's piece of the row, and of the next product's operand.
+__device__ __forceinline__ v4i halves_to_row(unsigned w0, unsigned w1, unsigned w2, unsigned w3)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false), b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+    return v4i{(int)a[0], (int)a[1], (int)b[0], (int)b[1]};
+}
 __device__ __forceinline__ unsigned quotient(unsigned n, const FastDiv& f)
 {
     const unsigned q = __umulhi(n, f.magic) >> f.shift;

@@ -354,6 +354,12 @@ inline bool conv_chain_faster(int M, int K, int N1, int N2)
     return one < (apart > least ? apart : least);
 }
 
+// 3x3 convolutions of 64 channels (nm_conv_taps.hip), or the small-tile and the tile kernel: up to here the filter, which every workgroup
+// loads whole, costs more than the image read nine times.  us, those | this: 3136 positions 3.7 | 4.4, 6272 4.1 | 4.5, 10000 5.0 | 4.7,
+// 12544 5.2 | 4.8, 25088 8.1 | 5.1, 50176 7.5 | 6.4, 200704 17.2 | 14.0.
+constexpr int kTapsWaves = 8;   // of a workgroup
+constexpr bool conv_taps_faster(int M) { return M >= 8192; }
+
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An
 // eighth of r x c tiles reads r * BM rows of A and c * BN rows of W through that XCD's L2: pick the r that makes this

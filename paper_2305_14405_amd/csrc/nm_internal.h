@@ -181,6 +181,8 @@ int32_t launch_conv_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t strea
 // A 1x1 convolution (rows of K, a shortcut) and the one that reads its result (b.A == a.out_q), nothing else of which is what the other
 // touches, as one launch; *done = false where they are not for it.
 int32_t launch_conv_chain(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done);
+// A 3x3 convolution whose filter fits LDS (g.conv, operands that the gathered loader takes); *done = false where it is not for that kernel.
+int32_t launch_conv_taps(const GemmArgs& g, hipStream_t stream, bool* done);
 bool gemm_switched();   // one of the debug switches says which kernel products take
 // True when launch_gemm would fold the LayerNorm described by g.ln_* into the GEMM kernel.
 bool gemm_folds_layernorm(const GemmArgs& g);

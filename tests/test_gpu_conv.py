@@ -374,6 +374,31 @@ def test_neighbouring_convolutions(oracle, B, H, Cin, first, second, tie):
         if not (n == 0 and tie == "result"): assert np.array_equal(host(ys[n]), want[n]), f"step {n}"
 
 
+@pytest.mark.parametrize("B,H,W,form", [
+    (3, 56, 56, "relu"), (9, 31, 33, "relu"), (1, 1, 8193, "relu"), (1, 8200, 1, "relu"), (4100, 1, 2, "relu"), (911, 3, 3, "relu"), (22, 55, 57, "relu"),
+    (3, 53, 59, "lines"), (3, 53, 59, "nonfinite"), (3, 53, 59, "scalar"), (3, 53, 59, "none")])
+def test_3x3_convolutions_of_64_channels(oracle, B, H, W, form):
+    """Stride 1, a border of 1, from 8192 positions on: images of one row, one column, fewer pixels than a block; a last block that is not
+    full; more than one turn of the wavefronts (22 x 55 x 57); any two-segment table, none, columns whose sums are infinite or NaN."""
+    g = np.random.default_rng(B + H + W)
+    ot, tables = relu_tables(oracle)
+    if form == "lines":
+        k, b = np.float32([0.125, 1.0]), np.float32([0.1, -0.3])
+        tables, ot.k[:], ot.b[:] = nm.nm_tables_from_arrays([("relu", -8.0, 8.0, 2, 0)], [k], [b]), k, b
+    x, w = rand_i8(g, (B, H, W, 64)), rand_i8(g, (64, 3, 3, 64))
+    bias, alpha = g.standard_normal(64).astype(np.float32), (5e-5 * (1 + g.random(64))).astype(np.float32)
+    if form == "nonfinite": bias[[3, 40]], alpha[50] = (np.nan, np.inf), 3e38
+    if form == "scalar": bias = alpha = None
+    table = form != "none"
+    dx, dw, db, da = (dev(v) for v in (x, w, bias, alpha))
+    y = torch.full((B * H * W + 64, 64), 77, dtype=torch.int8, device=DEV)   # 64 rows behind the result stay as they are
+    nm.nm_conv2d_pwl(nm.make_conv_desc(dx, dw, 1, 1, bias=db, alpha=6e-5, alpha_vec=da, tables=tables, table_idx=0 if table else -1, out_inv_scale=30.0,
+                                       out_q=y[:B * H * W].view(B, H, W, 64)), torch.empty(256, dtype=torch.uint8, device=DEV))
+    want = oracle.conv2d_pwl(x, w, 1, 1, bias=bias, alpha=6e-5, alpha_vec=alpha, table=ot if table else None, out_inv_scale=30.0)["q"]
+    got = host(y)
+    assert np.array_equal(got[:B * H * W].reshape(want.shape), want) and (got[B * H * W:] == 77).all()
+
+
 # positions (a last block of 32 that is not full, a second turn of the wavefronts) and channels of a widening and a narrowing convolution
 # that are one kernel (tests/test_gemm_choice.py holds them to its rule); forms at the smallest of each kernel
 CHAIN_CASES = [(5037, 64, 256, 64), (5037, 64, 256, 128), (50003, 128, 256, 128), (25089, 64, 512, 64), (100003, 64, 256, 64), (70003, 64, 256, 128),
