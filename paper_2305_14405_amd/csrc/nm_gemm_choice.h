@@ -284,6 +284,13 @@ inline int choose_unaligned(int M, int N, int K, bool q, bool f32, bool table, b
     return cfg;
 }
 
+// LDS of nm_gemm_ln.hip: a slice of W rows per 128 bytes of K, the A image (whole pieces of 256 columns) and the product's table, for which K beyond
+// 896 and 128 columns leave 2048 segments' room.
+constexpr size_t ln_gemm_lds(int tile, int K, size_t table_bytes)
+{
+    return (size_t)((K + 127) / 128) * (32 << tile) * 128 + (size_t)((K + 255) / 256) * 2 * 16 * 128 + table_bytes;
+}
+
 // Whether a product makes the LayerNorm in front of it, and with which tile of nm_gemm_ln.hip (16x32, 16x64, 16x128), or -1: as two
 // kernels.  The narrowest tile whose workgroups a single round of the 256 CUs holds: a wider one repeats less of the LayerNorm but
 // leaves CUs idle, and a second round costs more than the launch it saves.  us of GPU time, one kernel less two, 16x32 | 16x64 |
@@ -293,12 +300,12 @@ inline int choose_unaligned(int M, int N, int K, bool q, bool f32, bool table, b
 //   200 x 2560 x  640            | 520 +3.1 | 260 +1.6       256 x 2048 x 512            | 512 +0.4 | 256 -0.4
 //   200 x 3072 x  768                       | 312 +2.4       384 x 1152 x 384                       | 216 -0.9
 // Launches of their own are 3.1 us of host time each as well, which is what narrow layers of few rows wait for: nine layers of
-// width 384 over 64 tokens 25.5 us a layer, 4.8 less by either product.
-inline int ln_gemm_tile(int M, int N)
+// width 384 over 64 tokens 25.5 us a layer, 4.8 less by either product.  Where the table does not fit LDS beside the operands: two kernels.
+inline int ln_gemm_tile(int M, int N, int K, size_t table_bytes)
 {
     const long rows = (M + 15) / 16;
     for (int t = 0; t < 3; ++t)
-        if (rows * ((N + (32 << t) - 1) / (32 << t)) <= 256) return t;
+        if (rows * ((N + (32 << t) - 1) / (32 << t)) <= 256) return ln_gemm_lds(t, K, table_bytes) <= 160 * 1024 ? t : -1;
     return -1;
 }
 

@@ -11,6 +11,7 @@
 // too: 12 layers of width 768 over 128 tokens 310 us instead of 287, weights not in the caches; the kernels apart 305.)  Every column
 // tile repeats the work, so the kernel is for products of few rows (ln_gemm_tile, with what it measured); of 32 rows a
 // workgroup took 1 to 2 us more than the separate kernels wherever it was tried.
+#include "nm_gemm_choice.h"
 #include "nm_gemm_common.h"
 
 namespace nm {
@@ -244,7 +245,8 @@ template <int BM, int BN, int kC, int kEpi>
 static int32_t launch_ln(LnGemmParams& p, hipStream_t s)
 {
     auto kern = gemm_ln_kernel<BM, BN, kC, kEpi>;
-    const size_t shmem = (p.K + 127) / 128 * BN * 128 + 2 * kC * BM * 128 + (kEpi == EPI_Q_TABLE ? sizeof(float2) * (size_t)p.nseg : 0);
+    static_assert(BM == 16 && (BN == 32 || BN == 64 || BN == 128), "tiles of ln_gemm_lds");
+    const size_t shmem = ln_gemm_lds(BN / 64, p.K, kEpi == EPI_Q_TABLE ? sizeof(float2) * (size_t)p.nseg : 0);
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {

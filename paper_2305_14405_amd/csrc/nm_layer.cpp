@@ -127,7 +127,7 @@ static GemmArgs qkv_args(const nm_layer_desc* d, const int8_t* x, int8_t* qkv)
 // The tile with which a product also makes the LayerNorm in front of it, or -1: as two kernels.
 static int ln_tile(const LnRows& n, const GemmArgs& g)
 {
-    const int tile = ln_gemm_tile(g.M, g.N);
+    const int tile = ln_gemm_tile(g.M, g.N, g.K, g.has_table ? sizeof(float2) * (size_t)g.table.nseg : 0);
     return tile >= 0 && ln_gemm_takes(n, g) ? tile : -1;
 }
 

@@ -196,6 +196,23 @@ static int layernorm_rows()
     return 0;
 }
 
+// The tile of a product that makes the LayerNorm in front of it, and that its LDS, with the product's table, is what a CU has.
+static int layernorm_products()
+{
+    EXPECT(ln_gemm_tile(16, 4096, 1024, 0) == 0 && ln_gemm_tile(64, 4096, 1024, 0) == 1 && ln_gemm_tile(128, 4096, 1024, 0) == 2 && ln_gemm_tile(129, 4096, 1024, 0) == -1);
+    // a slice has 128 bytes of each of 32, 64 or 128 rows of W; of A two slices of 16 rows for each 256 columns
+    EXPECT(ln_gemm_lds(0, 1024, 8) == 8 * 4096 + 16384 + 8 && ln_gemm_lds(1, 768, 0) == 6 * 8192 + 12288 && ln_gemm_lds(2, 912, 80) == 8 * 16384 + 16384 + 80);
+    EXPECT(ln_gemm_tile(128, 4096, 1024, 8 * 2048) == 2 && ln_gemm_tile(128, 4096, 1024, 8 * 2049) == -1 && ln_gemm_tile(128, 4096, 896, 8 * 4096) == 2);
+    for (int M : {1, 16, 17, 64, 100, 128, 250, 682})
+        for (int N : {128, 520, 1152, 3072, 4096})
+            for (int K = 192; K <= 1024; K += 16)
+                for (int nseg : {0, 1, 256, 257, 2048, 2049, 4096}) {
+                    const int t = ln_gemm_tile(M, N, K, 8 * (size_t)nseg);
+                    EXPECT(t < 0 || (t == ln_gemm_tile(M, N, K, 0) && ln_gemm_lds(t, K, 8 * (size_t)nseg) <= 160 * 1024));
+                }
+    return 0;
+}
+
 // choice_driver relu M N K kunit ...: for each product with the epilogues for convolutions the tile kernel's configuration, or -1 for
 // the small-tile kernel.  staged M N K align ...: the register-staged kernel's, with every output, table and residual, or -1.
 static int configurations(const char* kind, int n, char** v)
@@ -218,7 +235,7 @@ static int configurations(const char* kind, int n, char** v)
 int main(int argc, char** argv)
 {
     if (argc > 2) return configurations(argv[1], argc - 2, argv + 2);
-    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows()) return 1;
+    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows() || layernorm_products()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;
 }

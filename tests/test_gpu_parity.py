@@ -1240,9 +1240,22 @@ def test_qkv_projection_and_attention_in_one_kernel(B, S, H, heads, nseg, recip)
                                               (16, 960, 15, 960, 64), (47, 240, 5, 480, 64), (50, 832, 13, 3328, 100)])
 def test_layernorm_in_the_product_behind_it(S, H, heads, F, nseg):
     """Few rows: FFN1 and the next layer's QKV projection make the LayerNorm in front of them (16x32 to 16x128 tiles, rows and columns
-    that do not fill one, widths that are and are not whole pieces of 256, tables of more than 256 segments and rows of more than one
+    that do not fill one, widths that are and are not whole pieces of 256, rsqrt tables of more than 256 segments and rows of more than one
     round as two kernels).  The same bits as the separate entry points: the layer's stages one by one, and a stack as single layers."""
-    tables = nm.nm_build_tables([("gelu", -8.0, 8.0, nseg), ("exp", -16.0, 0.0, 64), ("recip", 1.0, 1024.0, 64), ("rsqrt", 1e-3, 64.0, nseg)])
+    check_layernorm_products(S, H, heads, F, nseg, nseg)
+
+
+@pytest.mark.parametrize("S,H,heads,F,gelu", [(16, 1024, 16, 4096, 257), (16, 1024, 16, 4096, 4096), (64, 1024, 16, 4096, 1024), (64, 1024, 16, 4096, 4096),
+                                              (100, 640, 10, 2560, 2048), (128, 768, 12, 3072, 4096), (128, 1024, 16, 4096, 257),
+                                              (128, 1024, 16, 4096, 2048), (128, 1024, 16, 4096, 2049), (120, 960, 15, 3840, 4096)])
+def test_layernorm_in_the_product_behind_it_with_a_long_table(S, H, heads, F, gelu):
+    """The same with a GELU table of more than 256 segments beside a short rsqrt table, on each tile width and at the largest
+    contraction; the last two leave no room for the table beside the operands, and are two kernels."""
+    check_layernorm_products(S, H, heads, F, gelu, 64)
+
+
+def check_layernorm_products(S, H, heads, F, gelu, rsqrt):
+    tables = nm.nm_build_tables([("gelu", -8.0, 8.0, gelu), ("exp", -16.0, 0.0, 64), ("recip", 1.0, 1024.0, 64), ("rsqrt", 1e-3, 64.0, rsqrt)])
     g = torch.Generator(device=DEV).manual_seed(S + H + F)
     codes = lambda *s: torch.randint(-100, 101, s, generator=g, device=DEV).to(torch.int8)
     real = lambda n, m=0.0: torch.randn(n, generator=g, device=DEV) * 0.1 + m
@@ -1269,7 +1282,7 @@ def test_layernorm_in_the_product_behind_it(S, H, heads, F, nseg):
             assert_exact(host(taps["ln1"]), host(ln1), "LayerNorm in FFN1")
             nm.nm_gemm_pwl(ln1, keep[0]["W1"], bias=keep[0]["b1"], alpha=p["alpha_1"], tables=tables, table_idx=0, out_inv_scale=p["inv_s_ffn1"], out_q=ffn1)
             assert_exact(host(taps["ffn1"]), host(ffn1), "FFN1 behind its LayerNorm")
-            assert len(np.unique(host(ln1))) > 20 and len(np.unique(host(ffn1))) > (2 if nseg == 1 else 10)
+            assert len(np.unique(host(ln1))) > 20 and len(np.unique(host(ffn1))) > (2 if gelu == 1 else 10)
     out, f32 = i8(S + 1, H), torch.empty((S, H), device=DEV)
     nm.nm_encoder_stack(descs, x, out, f32, ws)
     assert_exact(host(out)[:S], host(y), "stack")
