@@ -37,13 +37,24 @@ struct QkvAttnParams : GemmParams {
 };
 constexpr int kQkvRecip = 256;   // entries of the reciprocal table at most
 
-// Fills p; slots: how the exp table may be looked up (TableSlots).
-int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* p, int* slots);
+// How the exp table may be looked up (all false and SLOTS_NONE: as any table).
+struct AttnExp {
+    int slots;           // TableSlots
+    bool padded, pow2;   // as EXP_PADDED; with the position by one fma
+};
+// Fills p and e.
+int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* p, AttnExp* e);
 
-// How the exp table's segment is found: any table and scale (this form also writes the optional
-// outputs); a table of at most 256 segments without input clamp, in slots; the same with inv_w a power of two.
-enum { EXP_ANY = 0, EXP_SLOTS = 1, EXP_SLOTS_POW2 = 2 };
-constexpr size_t attn_exp_bytes(int mode, int nseg) { return mode == EXP_ANY ? sizeof(float2) * (size_t)nseg : kSlotBytes; }
+// How the exp table's segment is found.  EXP_ANY: any table and scale (this form also writes the optional outputs).  EXP_SLOTS: a table of at
+// most 256 segments without input clamp, in slots, EXP_SLOTS_POW2 with inv_w a power of two.  EXP_PADDED: one that slots do not take (of more
+// segments, most of all), without input clamp and with an index of at most nseg at t = 0, the largest t where alpha_scores >= 0: its last
+// entry twice instead of the clamp; EXP_PADDED_POW2 (sequences beyond 1024 keys alone, where a SIMD's one wavefront pays for every
+// instruction) with inv_w a power of two.  us, any | padded, 257 segments: 32 x 128 tokens, 12 heads 7.3 | 7.1, 16 x 256 10.6 | 10.1, 16 x 512 29.0 |
+// 27.5; layers of 4 heads over 2 x 1200 tokens 49.2 | 46.0, over 1 x 4000 117 | 105 (512 segments 117 | 104).
+enum { EXP_ANY = 0, EXP_SLOTS = 1, EXP_SLOTS_POW2 = 2, EXP_PADDED = 3, EXP_PADDED_POW2 = 4 };
+constexpr bool attn_slots(int mode) { return mode == EXP_SLOTS || mode == EXP_SLOTS_POW2; }
+constexpr bool attn_padded(int mode) { return mode == EXP_PADDED || mode == EXP_PADDED_POW2; }
+constexpr size_t attn_exp_bytes(int mode, int nseg) { return attn_slots(mode) ? kSlotBytes : sizeof(float2) * (size_t)(nseg + (attn_padded(mode) ? 1 : 0)); }
 
 // Wavefronts that share 16 queries (at most 256 keys each).
 constexpr int attn_parts(int S) { return S <= 256 ? 1 : S <= 512 ? 2 : 4; }
@@ -83,8 +94,9 @@ struct AttnConsts {
             clo = p.t_exp.clamp_input ? p.t_exp.lo : -__builtin_inff();
             chi = p.t_exp.clamp_input ? p.t_exp.hi : __builtin_inff();
         } else {
-            inv_w = in_vgpr(p.t_exp.inv_w * (1.0f / kSlotSegments));
-            if (kMode == EXP_SLOTS_POW2) u0 = in_vgpr(p.t_exp.u0 * (1.0f / kSlotSegments));
+            constexpr float kPart = attn_slots(kMode) ? 1.0f / kSlotSegments : 1.0f;
+            inv_w = in_vgpr(p.t_exp.inv_w * kPart);
+            if (kMode == EXP_SLOTS_POW2 || kMode == EXP_PADDED_POW2) u0 = in_vgpr(p.t_exp.u0 * kPart);
             else lo = in_vgpr(p.t_exp.lo);
             steps = in_vgpr(8.0f * kSlotSegments);
         }
@@ -103,6 +115,9 @@ __device__ __forceinline__ AttnLine attn_look_up(int& s, float fmax_, const Attn
     if (kMode == EXP_ANY) {
         t = __builtin_amdgcn_fmed3f(t, c.clo, c.chi);
         e = reinterpret_cast<const float2*>(s_exp)[seg_index(t, p.t_exp.lo, p.t_exp.inv_w, p.t_exp.nseg)];
+    } else if (attn_padded(kMode)) {
+        const float u = kMode == EXP_PADDED_POW2 ? __builtin_fmaf(t, c.inv_w, c.u0) : (t - c.lo) * c.inv_w;
+        e = slot_line(cvt_u32_sat(u) * (unsigned)sizeof(float2));   // (the table is the first thing in LDS)
     } else {
         const float u = kMode == EXP_SLOTS_POW2 ? fma_clamp01(t, c.inv_w, c.u0) : mul_clamp01(t - c.lo, c.inv_w);
         e = slot_line(slot_offset(u, c.steps));   // (the slots are the first thing in LDS)
@@ -144,23 +159,25 @@ __device__ __forceinline__ bool attn_small(float r, const AttnParams& p)
     return __all(ok);
 }
 
-// The exp table (in slots, but for EXP_ANY) and the reciprocal table, requested into registers
+// The exp table (in slots, or its entries) and the reciprocal table, requested into registers
 // (before the operand loads, which are younger) and written to LDS.
 template <int kMode, int kThreads>
 struct AttnTables {
     static_assert(kThreads >= kSlotSegments, "a slot per thread");
-    float2 te, tr;
+    float2 te, tr, last;
     __device__ __forceinline__ void request(const AttnParams& p)
     {
         te = p.t_exp.kb[min((int)threadIdx.x, p.t_exp.nseg - 1)];
         tr = p.t_recip.kb[min((int)threadIdx.x, p.t_recip.nseg - 1)];
+        if (attn_padded(kMode)) last = p.t_exp.kb[p.t_exp.nseg - 1];
     }
     __device__ __forceinline__ void write(const AttnParams& p, float2* s_exp, float2* s_recip) const
     {
         const int ne = p.t_exp.nseg, nr = p.t_recip.nseg, tid = threadIdx.x;
-        if (kMode == EXP_ANY) {
+        if (!attn_slots(kMode)) {
             if (tid < ne) s_exp[tid] = te;
             for (int i = tid + kThreads; i < ne; i += kThreads) s_exp[i] = p.t_exp.kb[i];
+            if (attn_padded(kMode) && tid == 0) s_exp[ne] = last;
         } else {
             write_slots(s_exp, te, tid);
         }
@@ -311,7 +328,9 @@ __device__ __forceinline__ void attn_queries(const AttnParams& p, const AttnCons
     const float fm = __int_as_float(mi);
 #pragma unroll
     for (int j = 0; j < NACC; ++j) part[j] = 0.0f;
-    constexpr int kAhead = 3;
+    // (The forms without slots need more registers for a look-up: with three ahead EXP_ANY spilled 16 at 256 keys, 16 x 256 tokens, 12 heads, with
+    // the input clamp 12.7 us, now 9.8.)
+    constexpr int kAhead = attn_slots(kMode) ? 3 : 1;
     AttnLine line[kAhead + 1][4];
 #pragma unroll
     for (int u = 0; u < NU + kAhead; ++u) {

@@ -235,8 +235,9 @@ __global__ __launch_bounds__(kLongThreads) __attribute__((amdgpu_waves_per_eu(2)
                     float x[4][4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
+                        // (a score of a row that was not loaded may be above the maximum, and its index beyond the padded table)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) x[q][e] = attn_exp<kMode>(acc[q][e], fm, p, consts, smem);
+                        for (int e = 0; e < 4; ++e) x[q][e] = attn_exp<kMode>(attn_padded(kMode) && kMask && !key_ok(q, e) ? INT_MIN : acc[q][e], fm, p, consts, smem);
                         if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
                     }
 #pragma unroll
@@ -328,33 +329,36 @@ static int32_t launch_short(AttnParams& p, size_t tables, hipStream_t st)
                               attn_lds_bytes(kParts, NG) + tables, st);
 }
 template <int kMode>
-static int32_t launch_long(AttnParams& p, size_t tables, hipStream_t st)
+static size_t table_bytes(AttnParams& p)
+{
+    const size_t tables = (attn_exp_bytes(kMode, p.t_exp.nseg) + sizeof(float2) * (size_t)p.t_recip.nseg + 255) & ~(size_t)255;
+    p.off_tile = (int)tables;
+    return tables;
+}
+template <int kMode>
+static int32_t launch_long(AttnParams& p, hipStream_t st)
 {
     static std::once_flag once;
     static int32_t once_rc = NM_OK;
-    return launch_attn_kernel(attention_long_kernel<kMode>, once, once_rc, p, kLongThreads, kLongLds + tables, st);
+    return launch_attn_kernel(attention_long_kernel<kMode>, once, once_rc, p, kLongThreads, kLongLds + table_bytes<kMode>(p), st);
 }
 
 template <int kParts, int NG, int kMode>
 static int32_t launch_groups(AttnParams& p, size_t tables, hipStream_t st)
 {
     if (p.nch != 4) return launch_short<kParts, NG, false, kMode, false>(p, tables, st);
-    if constexpr (kMode != EXP_ANY) {
-        if (p.S == 64 * kParts * NG) return launch_short<kParts, NG, true, kMode, true>(p, tables, st);
-    }
+    // (EXP_ANY too: masked stores of the optional outputs are four times as many; 32 x 128 tokens, 12 heads 20.5 us masked, 12.9, 16 x 256 39.5 and 20.7)
+    if (p.S == 64 * kParts * NG) return launch_short<kParts, NG, true, kMode, true>(p, tables, st);
     return launch_short<kParts, NG, false, kMode, true>(p, tables, st);
 }
 
-template <int kMode>
-static int32_t launch_mode(AttnParams& p, int pairs, hipStream_t st)
+// kLongMode: of the kernel for long sequences.
+template <int kMode, int kLongMode = kMode>
+static int32_t launch_mode(AttnParams& p, hipStream_t st)
 {
-    const size_t tables = (attn_exp_bytes(kMode, p.t_exp.nseg) + sizeof(float2) * (size_t)p.t_recip.nseg + 255) & ~(size_t)255;
-    p.off_tile = (int)tables;
-    static_assert(kLongThreads / 4 == 64, "queries per workgroup");
-    p.qblocks = (p.S + 63) / 64;
-    p.total = p.qblocks * pairs;
+    const size_t tables = table_bytes<kMode>(p);
     const int parts = attn_parts(p.S), ng = (p.S + 64 * parts - 1) / (64 * parts);
-    if (p.S > 1024 || attn_lds_bytes(parts, ng) + tables > 160 * 1024) return launch_long<kMode>(p, tables, st);
+    if (p.S > 1024 || attn_lds_bytes(parts, ng) + tables > 160 * 1024) return launch_long<kLongMode>(p, st);
     if (parts == 1) {
         if (ng == 1) return launch_groups<1, 1, kMode>(p, tables, st);
         if (ng == 2) return launch_groups<1, 2, kMode>(p, tables, st);
@@ -371,7 +375,7 @@ bool fused_attention_covers(int S, int H, int heads)
     return d <= kHeadDim && d % 16 == 0 && S <= 4096;
 }
 
-int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* out, int* slots)
+int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* out, AttnExp* e)
 {
     AttnParams& p = *out;
     DevTable t_exp, t_recip;
@@ -391,20 +395,27 @@ int32_t attn_params(const AttnArgs& a, const char* what, AttnParams* out, int* s
     double vmin, vmax;
     table_value_bounds(a.tables, a.exp_idx, a.alpha_scores >= 0 ? -reach : 0.0, a.alpha_scores >= 0 ? 0.0 : reach, &vmin, &vmax);
     p.e_lo = (float)vmin; p.e_hi = (float)vmax;
-    *slots = a.alpha_scores >= 0.0f ? t_exp.slots : SLOTS_NONE;
+    // index of t = 0 by the kernels' own arithmetic
+    const float from_lo = 0.0f - t_exp.lo, at_0 = from_lo * t_exp.inv_w;
+    e->slots = a.alpha_scores >= 0.0f ? t_exp.slots : SLOTS_NONE;
+    e->padded = a.alpha_scores >= 0.0f && !t_exp.clamp_input && at_0 < (float)(t_exp.nseg + 1);
+    e->pow2 = t_exp.pow2;
     return NM_OK;
 }
 
 int32_t launch_attention(const AttnArgs& a, const char* what, hipStream_t st)
 {
     AttnParams p{};
-    int slots;
-    int32_t rc = attn_params(a, what, &p, &slots);
+    AttnExp e;
+    int32_t rc = attn_params(a, what, &p, &e);
     if (rc) return rc;
-    const int pairs = a.B * a.heads;
-    if (slots == SLOTS_NONE || p.scores_out || p.p_out) rc = launch_mode<EXP_ANY>(p, pairs, st);
-    else if (slots == SLOTS_POW2) rc = launch_mode<EXP_SLOTS_POW2>(p, pairs, st);
-    else rc = launch_mode<EXP_SLOTS>(p, pairs, st);
+    static_assert(kLongThreads / 4 == 64, "queries per workgroup");
+    p.qblocks = (p.S + 63) / 64;
+    p.total = p.qblocks * a.B * a.heads;
+    if (p.scores_out || p.p_out || (e.slots == SLOTS_NONE && !e.padded)) rc = launch_mode<EXP_ANY>(p, st);
+    else if (e.slots == SLOTS_POW2) rc = launch_mode<EXP_SLOTS_POW2>(p, st);
+    else if (e.slots == SLOTS_ANY) rc = launch_mode<EXP_SLOTS>(p, st);
+    else rc = e.pow2 ? launch_mode<EXP_PADDED, EXP_PADDED_POW2>(p, st) : launch_mode<EXP_PADDED>(p, st);
     if (rc) return rc;
     return check_hip(hipGetLastError(), "attention launch");
 }

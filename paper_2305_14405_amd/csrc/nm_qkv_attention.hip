@@ -24,11 +24,11 @@ int32_t launch_qkv_attention(const AttnArgs& a, const GemmArgs& g, const char* w
     const int form = qkv_attention_form(a.B, a.S, a.heads, g.K);
     if (form == QKV_ATTENTION_NONE) return NM_OK;
     QkvAttnParams p{};
-    int slots;
-    int32_t rc = attn_params(a, what, &p.at, &slots);
+    AttnExp e;
+    int32_t rc = attn_params(a, what, &p.at, &e);
     if (rc) return rc;
-    if (slots == SLOTS_NONE || p.at.t_recip.nseg > kQkvRecip) return NM_OK;
-    p.B = a.B; p.keys_log2 = a.S <= 64 ? 6 : 7; p.pow2 = slots == SLOTS_POW2;
+    if (e.slots == SLOTS_NONE || p.at.t_recip.nseg > kQkvRecip) return NM_OK;
+    p.B = a.B; p.keys_log2 = a.S <= 64 ? 6 : 7; p.pow2 = e.slots == SLOTS_POW2;
     p.M = (int)(((int64_t)a.B + (128 >> p.keys_log2) - 1) >> (7 - p.keys_log2)) * 128; p.N = 192 * a.heads; p.K = g.K;
     p.A = g.A; p.lda = g.lda; p.W = g.W; p.ldw = g.ldw; p.inner_count = 1;
     p.bias = g.bias; p.alpha = g.alpha;

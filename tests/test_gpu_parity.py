@@ -1131,6 +1131,22 @@ def test_encoder_layer_attention_divided_over_wavefronts(oracle, S, H, heads, ns
         check_layer_attention(oracle, p, ot, dt, with_taps)
 
 
+@pytest.mark.parametrize("S,H,heads,nseg,hi,flags", [
+    (64, 64, 1, 257, 0.0, 0), (128, 128, 2, 512, 0.0, 0), (192, 64, 1, 1000, 0.0, 0), (256, 64, 1, 300, 0.0, 0), (384, 64, 1, 1024, 0.0, 0), (512, 64, 1, 257, 0.0, 0),
+    (768, 64, 1, 300, 0.0, 0), (1024, 64, 1, 512, 0.0, 0), (1024, 64, 1, 4096, 0.0, 0), (100, 64, 1, 4096, 0.0, 0), (300, 96, 2, 257, 0.0, 0), (1000, 32, 1, 2048, 0.0, 0),
+    (1025, 64, 1, 257, 0.0, 0), (1100, 64, 1, 512, 0.0, 0), (1281, 32, 1, 300, 0.0, 0), (1300, 64, 1, 64, 2.0, 0),
+    (256, 64, 1, 300, 2.0, 0), (200, 64, 1, 300, -1.0, 0), (1100, 64, 1, 300, -1.0, 0),
+    (64, 64, 1, 64, 0.0, 1), (256, 64, 1, 64, 0.0, 1), (512, 64, 1, 300, 0.0, 1), (1024, 64, 1, 64, 0.0, 1), (1100, 64, 1, 64, 0.0, 1)])
+def test_encoder_layer_attention_tables_that_slots_do_not_take(oracle, S, H, heads, nseg, hi, flags):
+    """Exp tables of more than 256 segments (their last entry at t = 0, t = 0 inside the table and so far behind it that the look-up clamps, LDS for
+    both images and not) and with the input clamp, at lengths that fill the kernels' blocks and others; with the scores and probabilities too."""
+    p = sharp_layer(1, S, H, heads, 300.0)[1]
+    specs = [("gelu", -8.0, 8.0, 64), ("exp", -16.0, hi, nseg), ("recip", 1.0, float(max(64, S)), 128), ("rsqrt", 1e-3, 64.0, 64)]
+    ot, dt = both_tables(oracle, specs, flags=flags)
+    for with_taps in (False, True):
+        check_layer_attention(oracle, p, ot, dt, with_taps)
+
+
 def spoil(table, kind, at=0):
     """A table's lines from segment `at` on made non-finite."""
     if kind == "nan":
