@@ -47,7 +47,7 @@ KERNEL_SOURCES = os.path.join(ROOT, "paper_2305_14405_amd", "csrc")
 # the sources the encoder layer's kernels are built from (the convolution path is not among them)
 LAYER_KERNEL_SOURCES = ("nm_device.h", "nm_internal.h", "nm_gemm_common.h", "nm_gemm_choice.h", "nm_gemm_tile.h", "nm_gemm.hip",
                         "nm_gemm_direct.hip", "nm_gemm_unaligned.hip", "nm_rows_choice.h", "nm_rows.hip", "nm_attention.h", "nm_attention.hip",
-                        "nm_block.hip", "nm_gemm_end.hip", "nm_gemm_ln.hip", "nm_qkv_attention.hip", "nm_layer.cpp")
+                        "nm_block.hip", "nm_gemm_end.hip", "nm_gemm_long.hip", "nm_gemm_ln.hip", "nm_qkv_attention.hip", "nm_layer.cpp")
 
 
 def kernel_source_hash():

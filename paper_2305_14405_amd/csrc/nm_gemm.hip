@@ -965,9 +965,11 @@ int32_t launch_gemm(const GemmArgs& g, hipStream_t stream)
         else if (forced.kind == FORCED_TILE) tile_cfg = forced.number;
         else if (forced.number == STREAM_BIG) tile_cfg = 1;
     }
-    const size_t tile_table = table.slots ? 0 : table_bytes;   // (slots are part of the kernel's own LDS)
-    if (tile_cfg >= 0) {
-        rc = g.K % 128 ? launch_tile_end(tile_cfg, p, epi, tile_table, stream) : launch_tile_config<false>(tile_cfg, p, epi, tile_table, stream);
+    if (tile_cfg >= 0 && epi == EPI_Q_TABLE && !table.slots) {
+        rc = launch_tile_long(tile_cfg, p, table_bytes, stream);
+    } else if (tile_cfg >= 0) {
+        // (no bytes for the table: slots are part of the kernel's own LDS)
+        rc = g.K % 128 ? launch_tile_end(tile_cfg, p, epi, 0, stream) : launch_tile_config<false>(tile_cfg, p, epi, 0, stream);
     } else if (stream_ok && cfg == CFG_WIDE) {
         rc = launch_stream<256, 128, 2, 2, 1, 64, 2>(p, epi, batches, table_bytes, stream);
     } else if (stream_ok && cfg == CFG_BIG) {

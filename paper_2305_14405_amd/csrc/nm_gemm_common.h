@@ -72,6 +72,9 @@ int32_t launch_direct_pair(GemmParams (&p)[2], int cfg, hipStream_t s);
 // The tile kernel's configuration cfg for K in whole chunks of 16 bytes but not whole slices (nm_gemm_end.hip).
 int32_t launch_tile_end(int cfg, GemmParams& p, int epi, size_t table_bytes, hipStream_t s);
 
+// The same for any such K and int8 results through a table that slots do not take (nm_gemm_long.hip).
+int32_t launch_tile_long(int cfg, GemmParams& p, size_t table_bytes, hipStream_t s);
+
 // The register-staged tile kernel (nm_gemm_unaligned.hip): one problem, operands of any alignment (align: 4 or 1).
 int32_t launch_unaligned(GemmParams& p, int align, size_t table_bytes, int forced, hipStream_t s);
 
@@ -139,9 +142,10 @@ __device__ __forceinline__ v4i load_tail(rsrc_t r, unsigned off, int left)
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
-enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_RELU = 8, EPI_Q_RELU_RESID = 9, EPI_ATTENTION = 10 };
+enum Epilogue { EPI_GENERIC = 0, EPI_Q = 1, EPI_Q_TABLE = 2, EPI_F32_RESID = 3, EPI_ACC = 4, EPI_Q_TABLE_RESID = 5, EPI_F32_RESID_LN = 6, EPI_Q_LONG = 7, EPI_Q_RELU = 8, EPI_Q_RELU_RESID = 9, EPI_ATTENTION = 10 };
 // EPI_F32_RESID_LN: EPI_F32_RESID followed by LayerNorm-PWL over the row, inside the kernel: the tile
 // covers whole rows (tile kernel only).
+// EPI_Q_LONG: EPI_Q_TABLE with a table that slots do not take (tile kernel only, nm_gemm_long.hip; there EPI_Q_TABLE is one that they do).
 // EPI_Q_RELU, EPI_Q_RELU_RESID: per-column scales, a table of two segments, without and with an int8 residual (tile
 // kernel only: convolutions).
 // EPI_ATTENTION: the Q, K and V of one head, which go no further than LDS, and attention behind them (tile kernel only).

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     constexpr int DPS = (LB + POST + NMF - 1) / (POST + NMF);  // refill loads per slot (those slots and the next k-step's)
     static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole blocks");
     static_assert(TN >= 2 && KS % 2 == 0 && TM % KSPLIT == 0, "wavefront tile");
-    constexpr bool kTable = kEpi == EPI_Q_TABLE;
+    constexpr bool kSlots = kEpi == EPI_Q_TABLE, kTable = kSlots || kEpi == EPI_Q_LONG;
     constexpr bool kRelu = kEpi == EPI_Q_RELU || kEpi == EPI_Q_RELU_RESID;   // per-column scales, two segments
     static_assert(kEpi == EPI_Q || kTable || kRelu || kEpi == EPI_F32_RESID || kEpi == EPI_F32_RESID_LN || kEpi == EPI_ATTENTION,
                   "epilogues of the tile kernel");
@@ -203,9 +203,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         else bias_reg[t] = (p.bias && c < BN && n0 + c < p.N) ? p.bias[n0 + c] : 0.0f;
         if (kRelu) scale_reg[t] = (p.alpha_vec && c < BN && n0 + c < p.N) ? p.alpha_vec[n0 + c] : p.alpha;
     }
-    static_assert(!kTable || 64 * NW >= kSlotSegments, "a slot per thread");
-    float2 kb_reg = make_float2(0.0f, 0.0f);   // one table entry per thread held in a register (more are staged late)
-    if (kTable) kb_reg = p.table.kb[min(tid, p.table.nseg - 1)];
+    static_assert(!kSlots || 64 * NW >= kSlotSegments, "a slot per thread");
+    constexpr int KPT = kSlots ? 1 : 4;   // table entries per thread held in registers (more are staged late)
+    float2 kb_reg[KPT];
+    if (kTable) {
+#pragma unroll
+        for (int t = 0; t < KPT; ++t) kb_reg[t] = p.table.kb[min(tid + t * 64 * NW, p.table.nseg - 1)];
+    }
 
     AttnTables<EXP_SLOTS, kEpi == EPI_ATTENTION ? 64 * NW : kSlotSegments> attn_tabs;
     if constexpr (kEpi == EPI_ATTENTION) attn_tabs.request(p.at);
@@ -379,12 +383,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         if (c < BN) s_bias[c] = bias_reg[t];
         if (kRelu && c < BN) s_scale[c] = scale_reg[t];
     }
-    if (kTable) {
-        if (p.table.slots) write_slots(reinterpret_cast<float2*>(smem), kb_reg, tid);
-        else {
-            if (tid < p.table.nseg) s_kb[tid] = kb_reg;
-            for (int e = tid + 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
-        }
+    if constexpr (kSlots) {
+        write_slots(reinterpret_cast<float2*>(smem), kb_reg[0], tid);
+    } else if constexpr (kTable) {
+#pragma unroll
+        for (int t = 0; t < KPT; ++t)
+            if (tid + t * 64 * NW < p.table.nseg) s_kb[tid + t * 64 * NW] = kb_reg[t];
+        for (int e = tid + KPT * 64 * NW; e < p.table.nseg; e += 64 * NW) s_kb[e] = p.table.kb[e];
     }
     if constexpr (kEpi == EPI_ATTENTION) attn_tabs.write(p.at, reinterpret_cast<float2*>(smem), reinterpret_cast<float2*>(smem + kSlotBytes));
     constexpr int RW = BN + 16;  // row stride of the residual image
@@ -410,7 +415,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
     constexpr int NG = ETM * TN * 4;  // groups of four columns per lane
     if constexpr (kTable || kEpi == EPI_Q) {
         constexpr int SW = WN + 16;
-        constexpr int kAt = kTable ? (int)kSlotBytes : 0;
+        constexpr int kAt = kSlots ? (int)kSlotBytes : 0;
         static_assert(kAt + NW * EM * SW <= STAGES * STAGE_BYTES, "patch fits the ring");
         int8_t* patch = smem + kAt + wave * (EM * SW);
         // inverse output scale of a group (the QKV projection has one per column third)
@@ -428,14 +433,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
         float x[DEPTH + 1][4];
         float2 kb[DEPTH + 1][4];
         // group index -> (i, j, g), i innermost: consecutive groups use different accumulators
-        // form: the table in slots (nm_device.h), with the position by one fma (SLOTS_POW2) or two steps (SLOTS_ANY); SLOTS_NONE: more
-        // than 256 segments.  Of an element's eleven instructions nine issued at half the rate (scalar operands, clamp, conversions,
-        // shift), now two and a half of ten.  us, before -> after: 4096 x 3072 x 768 16.3 -> 16.1, 8192 x 3072 x 768 29.3 -> 28.9,
-        // 16384 x 4096 x 1024 85.8 -> 85.0, with 100 segments 87.4 -> 85.0 (the card's power limits that one); a base stack
-        // over 16 x 512 tokens 0.4 % less, a large one over 32 x 512 1 %.
-        auto finish = [&](auto form_c) {
-        constexpr int kForm = decltype(form_c)::value;
-        constexpr float kPart = kForm == SLOTS_NONE ? 1.0f : 1.0f / kSlotSegments;
+        // kPow2: the segment's position by one fma (the same bits: DevTable) instead of two steps.  In slots (nm_device.h): of an element's
+        // eleven instructions nine issued at half the rate (scalar operands, clamp, conversions, shift), now two and a half of ten.  us,
+        // before -> after: 4096 x 3072 x 768 16.3 -> 16.1, 8192 x 3072 x 768 29.3 -> 28.9, 16384 x 4096 x 1024 85.8 -> 85.0, with 100 segments
+        // 87.4 -> 85.0 (the card's power limits that one); a base stack over 16 x 512 tokens 0.4 % less, a large one over 32 x 512 1 %.
+        auto finish = [&](auto pow2_c) {
+        constexpr bool kPow2 = decltype(pow2_c)::value;
+        constexpr float kPart = kSlots ? 1.0f / kSlotSegments : 1.0f;
         const float tlo = in_vgpr(p.table.lo), tiw = in_vgpr(p.table.inv_w * kPart), tu0 = in_vgpr(p.table.u0 * kPart);
         const float steps = in_vgpr(8.0f * kSlotSegments), tmax = (float)(p.table.nseg - 1);
         auto stage_a = [&](int G) {
@@ -445,12 +449,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
                 const float v = __builtin_fmaf((float)sum(i, j)[4 * g + e], alpha, bi[j][g][e]);
                 x[G % (DEPTH + 1)][e] = v;
                 if (!kTable) continue;
-                if (kForm == SLOTS_NONE) {  // subtract, multiply, clamp in float, floor
-                    const float u = __builtin_amdgcn_fmed3f((v - tlo) * tiw, 0.0f, tmax);
-                    kb[G % (DEPTH + 1)][e] = s_kb[(int)u];
-                } else {
-                    const float u = kForm == SLOTS_POW2 ? fma_clamp01(v, tiw, tu0) : mul_clamp01(v - tlo, tiw);
+                if (kSlots) {
+                    const float u = kPow2 ? fma_clamp01(v, tiw, tu0) : mul_clamp01(v - tlo, tiw);
                     kb[G % (DEPTH + 1)][e] = slot_line(slot_offset(u, steps));
+                } else {  // clamp in float, floor
+                    const float u = __builtin_amdgcn_fmed3f(kPow2 ? __builtin_fmaf(v, tiw, tu0) : (v - tlo) * tiw, 0.0f, tmax);
+                    kb[G % (DEPTH + 1)][e] = s_kb[(int)u];
                 }
             }
         };
@@ -474,9 +478,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KSPLIT, 2) void gemm_tile_
             __builtin_amdgcn_sched_barrier(0);
         }
         };
-        if (kTable && p.table.slots == SLOTS_POW2) finish(std::integral_constant<int, SLOTS_POW2>{});
-        else if (kTable && p.table.slots == SLOTS_ANY) finish(std::integral_constant<int, SLOTS_ANY>{});
-        else finish(std::integral_constant<int, SLOTS_NONE>{});
+        if (kTable && (kSlots ? p.table.slots == SLOTS_POW2 : p.table.pow2)) finish(std::true_type{}); else finish(std::false_type{});
         // the wavefront reads back the rows it wrote: order its LDS writes before its reads
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -757,7 +759,7 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
     constexpr int kRing = STAGES * ((NBLK + NW - 1) / NW * NW) * 1024;
     constexpr int kFront = tile_front_bytes(BM, BN, NW, BM / WAVES_M / KSPLIT, BN / WAVES_N, kEpi);
     static_assert(kFront % 16 == 0 && kFront + BN * 4 <= 160 * 1024 && kRing <= 160 * 1024, "LDS");
-    const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;   // (table_bytes: 0 for a table in slots)
+    const size_t epilogue = kFront + BN * sizeof(float) + table_bytes, shmem = epilogue > kRing ? epilogue : (size_t)kRing;   // (table_bytes: of EPI_Q_LONG's table)
     static std::once_flag once;  // one attribute call per instantiation
     static int32_t once_rc = NM_OK;
     std::call_once(once, [&] {
@@ -777,33 +779,35 @@ static int32_t launch_tile_epi(Params& p, size_t table_bytes, hipStream_t s)
 
 // The epilogues a configuration is built for (kTileConfigs).
 enum TileOutputs { OUT_ANY, OUT_INT8, OUT_F32 };
-template <bool kEnd, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, TileOutputs kOut = OUT_ANY, int KSPLIT = 1>
+template <bool kEnd, bool kLong, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, TileOutputs kOut = OUT_ANY, int KSPLIT = 1>
 static int32_t launch_tile(GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
 {
-    if constexpr (kOut != OUT_F32) {
+    if constexpr (kOut != OUT_F32 && kLong) {
+        return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_LONG, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
+    } else if constexpr (kOut != OUT_F32) {
         if (epi == EPI_Q) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
         if (epi == EPI_Q_TABLE) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_Q_TABLE, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
     }
-    if constexpr (kOut != OUT_INT8) {
+    if constexpr (kOut != OUT_INT8 && !kLong) {
         if (epi == EPI_F32_RESID) return launch_tile_epi<BM, BN, WAVES_M, WAVES_N, STAGES, EPI_F32_RESID, 128, false, KSPLIT, kEnd>(p, table_bytes, s);
     }
     return fail(NM_ERR_UNSUPPORTED, "gemm: tile configuration not built for this epilogue");
 }
-// Configuration cfg of kTileConfigs.
-template <bool kEnd>
+// Configuration cfg of kTileConfigs.  kLong: with EPI_Q_LONG, which the others are built without.
+template <bool kEnd, bool kLong = false>
 static int32_t launch_tile_config(int cfg, GemmParams& p, int epi, size_t table_bytes, hipStream_t s)
 {
     switch (cfg) {
-    case 0: return launch_tile<kEnd, 256, 256, 2, 4, 2>(p, epi, table_bytes, s);
-    case 1: return launch_tile<kEnd, 256, 192, 4, 2, 2>(p, epi, table_bytes, s);
-    case 2: return launch_tile<kEnd, 256, 128, 4, 2, 3>(p, epi, table_bytes, s);
-    case 3: return launch_tile<kEnd, 128, 192, 2, 2, 3>(p, epi, table_bytes, s);
-    case 4: return launch_tile<kEnd, 128, 192, 2, 2, 2>(p, epi, table_bytes, s);
-    case 5: return launch_tile<kEnd, 128, 128, 2, 2, 3, OUT_INT8>(p, epi, table_bytes, s);
-    case 6: return launch_tile<kEnd, 128, 128, 2, 2, 2>(p, epi, table_bytes, s);
-    case 7: return launch_tile<kEnd, 64, 128, 2, 2, 3>(p, epi, table_bytes, s);
-    case 8: return launch_tile<kEnd, 64, 128, 2, 2, 2>(p, epi, table_bytes, s);
-    default: return launch_tile<kEnd, 128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, table_bytes, s);
+    case 0: return launch_tile<kEnd, kLong, 256, 256, 2, 4, 2>(p, epi, table_bytes, s);
+    case 1: return launch_tile<kEnd, kLong, 256, 192, 4, 2, 2>(p, epi, table_bytes, s);
+    case 2: return launch_tile<kEnd, kLong, 256, 128, 4, 2, 3>(p, epi, table_bytes, s);
+    case 3: return launch_tile<kEnd, kLong, 128, 192, 2, 2, 3>(p, epi, table_bytes, s);
+    case 4: return launch_tile<kEnd, kLong, 128, 192, 2, 2, 2>(p, epi, table_bytes, s);
+    case 5: return launch_tile<kEnd, kLong, 128, 128, 2, 2, 3, OUT_INT8>(p, epi, table_bytes, s);
+    case 6: return launch_tile<kEnd, kLong, 128, 128, 2, 2, 2>(p, epi, table_bytes, s);
+    case 7: return launch_tile<kEnd, kLong, 64, 128, 2, 2, 3>(p, epi, table_bytes, s);
+    case 8: return launch_tile<kEnd, kLong, 64, 128, 2, 2, 2>(p, epi, table_bytes, s);
+    default: return launch_tile<kEnd, kLong, 128, 128, 2, 2, 3, OUT_F32, 2>(p, epi, table_bytes, s);
     }
 }
 

@@ -92,6 +92,8 @@ print("PRODUCT_OK")
     ("relu11", 1200, 912, 192, 0, 1),     # slices of 128 bytes, one and a half of them
     ("direct0", 64, 128, 3072, 4096, 0),  # rings and table together beyond LDS
     ("tile3", 1500, 768, 512, 64, 0),   # one that the configuration does take
+    # tables that slots do not take
+    ("tile0", 700, 1024, 272, 1500, 0), ("tile1", 700, 1008, 384, 300, 0), ("tile4", 500, 1008, 384, 600, 0), ("tile8", 300, 1008, 304, 2100, 0),
     # K in whole chunks but not whole slices, every remainder
     ("tile0", 700, 1024, 272, 128, 0), ("tile1", 700, 1008, 416, 0, 0), ("tile2", 700, 1008, 688, 64, 0), ("tile3", 500, 1008, 576, 0, 0),
     ("tile4", 500, 1008, 336, 100, 0), ("tile5", 500, 1008, 752, 0, 0), ("tile6", 500, 1008, 480, 64, 0), ("tile7", 300, 1008, 400, 300, 0),

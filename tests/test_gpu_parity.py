@@ -349,6 +349,23 @@ def test_table_forms_of_the_tile_kernel(oracle, lo, hi, nseg):
     assert np.all(got[M] == 77)
 
 
+@pytest.mark.parametrize("M,N,K,lo,hi,nseg", [(1100, 1008, 272, -8.0, 8.0, 257), (1100, 1008, 464, -6.0, 7.0, 1025), (700, 3072, 768, -8.0, 8.0, 4096),
+                                              (2100, 1024, 512, -5.0, 8.0, 1000), (4200, 3072, 400, -8.0, 8.0, 2048), (9000, 2304, 768, -8.0, 8.0, 300)])
+def test_long_tables_of_the_tile_kernel(oracle, M, N, K, lo, hi, nseg):
+    """Tables that slots do not take, with an entry per thread, with four and with more, segments whose width is and is not a power of two, K in whole
+    slices and not; sampled rows, both edges of the tiles among them."""
+    ot, dt = both_tables(oracle, [("gelu", lo, hi, nseg)])
+    d = W.gemm_inputs(M, N, K, seed=nseg, full_range=False)
+    rows = np.unique(np.clip(np.concatenate([[0, 63, 64, 127, 128, 255, 256, M - 2, M - 1], np.random.default_rng(K).integers(0, M, 30)]), 0, M - 1))
+    alpha = float(np.float32(0.8 * max(abs(lo), hi) / (20 * 20 * np.sqrt(K))))
+    want = oracle.gemm_pwl(np.ascontiguousarray(d["A"][rows]), d["W"], bias=d["bias"], alpha=alpha, table=ot[0], out_inv_scale=25.0)["q"]
+    q = torch.full((M + 1, N), 77, dtype=torch.int8, device=DEV)
+    nm.nm_gemm_pwl(dev(d["A"]), dev(d["W"]), bias=dev(d["bias"]), alpha=alpha, tables=dt, table_idx=0, out_inv_scale=25.0, out_q=q, M=M)
+    got = host(q)
+    assert_exact(got[rows], want, f"{nseg} segments")
+    assert np.all(got[M] == 77) and len(np.unique(want)) > 30
+
+
 @pytest.mark.parametrize("M,N,K", [(1100, 1008, 272), (1100, 1008, 304), (1100, 1008, 336), (1100, 1008, 464), (2100, 768, 3088), (4096, 704, 704), (4096, 704, 2816 + 32),
                                    (9000, 832, 832), (16390, 960, 400), (300, 704, 704), (300, 576, 2304 + 48), (40, 448, 448), (3000, 448, 272)])
 def test_fp32_results_of_whole_chunks(oracle, M, N, K):
