@@ -450,7 +450,7 @@ int32_t launch_encoder_block(const nm_layer_desc* d, const nm_layer_desc* next, 
     *done = false;
     BlockParams p{};
     size_t shmem = 0;
-    if (!aligned(ctx, 16) || !aligned(x, 16) || !aligned(y_q, 16) || !aligned(y_f32, 16) || !aligned(qkv, 16) || !fill_block(d, next, p)) return NM_OK;
+    if (gemm_switched() || !aligned(ctx, 16) || !aligned(x, 16) || !aligned(y_q, 16) || !aligned(y_f32, 16) || !aligned(qkv, 16) || !fill_block(d, next, p)) return NM_OK;
     int32_t rc = get_dev_table(d->tables, d->gelu_idx, &p.t_gelu, "nm_encoder_layer(gelu)");
     if (rc) return rc;
     if ((rc = get_dev_table(d->tables, d->rsqrt_idx, &p.t_rsqrt, "nm_encoder_layer(rsqrt)"))) return rc;

@@ -276,7 +276,7 @@ static int32_t launch_ln_tile(LnGemmParams& p, bool table, hipStream_t s)
 // registers).
 bool ln_gemm_takes(const LnRows& n, const GemmArgs& g)
 {
-    return g.K % 16 == 0 && g.K >= 192 && g.K <= 1024 && aligned(n.x, 16) && aligned(n.gamma, 16) && aligned(n.beta, 16) && n.table.nseg <= 256 &&
+    return !gemm_switched() && g.K % 16 == 0 && g.K >= 192 && g.K <= 1024 && aligned(n.x, 16) && aligned(n.gamma, 16) && aligned(n.beta, 16) && n.table.nseg <= 256 &&
            (!n.out_q || aligned(n.out_q, 4)) && g.N % 4 == 0 && aligned(g.W, 16) && g.ldw % 16 == 0 && (int64_t)g.N * g.ldw < (1LL << 31) &&
            (!g.bias || aligned(g.bias, 4)) && g.out_q && aligned(g.out_q, 4) && g.ldo % 4 == 0 && g.ldo < (1LL << 31) && !g.out_f32 && !g.out_acc &&
            !g.alpha_vec && !g.resid && !g.out_inv_scale_vec && !g.dbg_seg && !g.conv && !g.w_is_kn && g.outer_count * g.inner_count == 1 &&

@@ -14,7 +14,7 @@ namespace nm {
 
 bool qkv_attention_takes(const AttnArgs& a, const GemmArgs& g)
 {
-    return a.S <= 128 && a.H == 64 * a.heads && g.K % 16 == 0 && aligned(g.A, 16) && aligned(g.W, 16) && (!g.bias || aligned(g.bias, 4)) &&
+    return !gemm_switched() && a.S <= 128 && a.H == 64 * a.heads && g.K % 16 == 0 && aligned(g.A, 16) && aligned(g.W, 16) && (!g.bias || aligned(g.bias, 4)) &&
            aligned(a.ctx, 4) && !a.scores_out && !a.p_out && (int64_t)g.M * g.lda < (1LL << 32) && (int64_t)g.N * g.ldw < (1LL << 32);
 }
 

@@ -102,3 +102,48 @@ def test_forced_configuration_keeps_results(cfg, M, N, K, nseg, per_column):
     run = subprocess.run([sys.executable, "-c", PRODUCT, *map(str, (M, N, K, nseg, per_column))], capture_output=True, text=True, cwd=ROOT,
                          env=dict(os.environ, NM_GEMM_CFG=cfg, PYTHONPATH=ROOT), timeout=100)
     assert run.returncode == 0 and "PRODUCT_OK" in run.stdout, (run.stdout[-1000:], run.stderr[-3000:])
+
+
+# The kernels of one layer, counted as the nodes of its captured graph, and its result.
+LAYER = """
+import ctypes, hashlib, torch
+from paper_2305_14405_amd import binding as nm
+import workloads as W
+DEV = "cuda:0"
+tables = nm.nm_build_tables([("gelu", -8.0, 8.0, 64), ("exp", -16.0, 0.0, 64), ("recip", 1.0, 128.0, 64), ("rsqrt", 1e-3, 64.0, 64)])
+g = torch.Generator(device=DEV).manual_seed(3)
+codes = lambda *s: torch.randint(-100, 101, s, generator=g, device=DEV).to(torch.int8)
+real = lambda n, m=0.0: torch.randn(n, generator=g, device=DEV) * 0.1 + m
+hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+s = torch.cuda.Stream()
+for B, S, H in ((24, 128, 512), (1, 128, 768), (1, 64, 128)):   # the QKV projection with attention, a LayerNorm with FFN1, a narrow layer's block kernel
+    act = dict(q=0.1, k=0.1, v=0.1, p=1.0 / 127, ctx=0.05, ln1=5.0 / 127, ffn1=0.1, out=5.0 / 127)
+    p = W.with_scales(dict(B=B, S=S, H=H, heads=H // 64, F=4 * H, s_x=5.0 / 127, s_wqkv=1e-3, s_wo=1e-3, s_w1=1e-3, s_w2=1e-3, eps1=1e-5, eps2=1e-5), act)
+    F = 4 * H
+    w = dict(Wqkv=codes(3 * H, H), bqkv=real(3 * H), Wo=codes(H, H), bo=real(H), W1=codes(F, H), b1=real(F), W2=codes(H, F), b2=real(H),
+             gamma1=real(H, 1.0), beta1=real(H), gamma2=real(H, 1.0), beta2=real(H))
+    desc = nm.make_layer_desc(p, w, tables)
+    x, y = codes(B * S, H), torch.empty((B * S, H), dtype=torch.int8, device=DEV)
+    ws = torch.empty(nm.nm_encoder_layer_workspace(desc), dtype=torch.uint8, device=DEV)
+    nm.nm_encoder_layer(desc, x, y, None, ws)
+    torch.cuda.synchronize()
+    graph, nodes, stream = ctypes.c_void_p(), ctypes.c_size_t(), ctypes.c_void_p(s.cuda_stream)
+    assert hip.hipStreamBeginCapture(stream, 1) == 0   # (thread local)
+    nm.nm_encoder_layer(desc, x, y, None, ws, stream=s)
+    assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0 and hip.hipGraphDestroy(graph) == 0
+    print(nodes.value, hashlib.md5(y.cpu().numpy().tobytes()).hexdigest())
+"""
+
+
+@pytest.mark.gpu
+def test_switches_reach_the_products_that_layers_fuse():
+    """With either debug switch a layer's products are kernels of their own, seven of them, and its result is the same."""
+    def run(**switch):
+        out = subprocess.run([sys.executable, "-c", LAYER], capture_output=True, text=True, cwd=ROOT, env=dict(os.environ, PYTHONPATH=ROOT, **switch), timeout=100)
+        assert out.returncode == 0, out.stdout + out.stderr
+        return [line.split() for line in out.stdout.splitlines()[-3:]]
+    plain = run()
+    assert [n for n, _ in plain] == ["6", "6", "3"]
+    for switch in (dict(NM_GEMM_GENERIC="1"), dict(NM_GEMM_CFG="direct1")):
+        assert run(**switch) == [["7", result] for _, result in plain]
