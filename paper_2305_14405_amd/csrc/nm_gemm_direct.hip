@@ -77,8 +77,13 @@ static void direct_args(DirectConvParams& q, const GemmParams& p)
 // most of this code once: stamps at 128 x 3072 x 768 put 1300 to 2700 clocks on the 190 instructions in front of the first
 // load and 1400 on the epilogue, of 7000 in all.  The fixed forms are a third of the code on the way, and divisions are by
 // host-made reciprocals: 12 base layers over 1 x 128 tokens 360 -> 340 us, ResNet-50 on one image 245 -> 211.
+// The arguments by value: by reference the compiler loads some of them once more, one by one, where they are chosen among (four images of 28 x 28, 128 to
+// 128 channels 3x3 without a table 4.7 us by reference, 4.5; two convolutions in one launch 5.4 | 5.1, 6.9 | 6.4).  Aligned rows with the
+// generic epilogue alone are better off with fewer held (16 x 2304 x 768 with both results 3.6 us by value, 3.5).
+template <bool kConv, int kEpi, int kAl>
+using DirectArgsIn = std::conditional_t<kEpi == EPI_GENERIC && !kConv && kAl == 16, const DirectArgs<kConv, kEpi>&, const DirectArgs<kConv, kEpi>>;
 template <int BM, int BN, int KW, int D, int kAl, bool kConv, int kEpi, int kForm, bool kEnd>
-__device__ __forceinline__ void direct_tile(const DirectArgs<kConv, kEpi>& p, const unsigned block)
+__device__ __forceinline__ void direct_tile(DirectArgsIn<kConv, kEpi, kAl> p, const unsigned block)
 {
     constexpr int TM = BM / 16, TN = BN / 16, NT = 64 * KW;
     constexpr int NA = BM / 8, NI = (BM + BN) / 8;   // 1 KB pieces (8 rows) of a slice; the first NA are A rows
