@@ -245,7 +245,9 @@ static bool lines_only(const GemmArgs& g) { return g.has_table && g.table.two_se
 int32_t launch_conv_chain(const GemmArgs& a, const GemmArgs& b, hipStream_t stream, bool* done)
 {
     *done = false;
-    if (gemm_switched() || !conv_chain_built(a.K, a.N, b.N) || !conv_chain_faster(a.M, a.K, a.N, b.N) || !lines_only(a) || !lines_only(b)) return NM_OK;
+    if (gemm_switched() || !conv_chain_built(a.K, a.N, b.N) || !lines_only(a) || !lines_only(b)) return NM_OK;
+    const bool relu = relu_codes(a.table, a.out_inv_scale, a.resid_scale) && relu_codes(b.table, b.out_inv_scale, 0.0f);
+    if (!conv_chain_faster(a.M, a.K, a.N, b.N, relu)) return NM_OK;
     const void* const rows[] = {a.A, a.W, a.resid, a.out_q, b.W, b.out_q};
     const void* const cols[] = {a.bias, a.alpha_vec, b.bias, b.alpha_vec};
     for (const void* q : rows)
@@ -257,7 +259,7 @@ int32_t launch_conv_chain(const GemmArgs& a, const GemmArgs& b, hipStream_t stre
     p.x = a.A; p.w1 = a.W; p.w2 = b.W; p.resid = a.resid; p.y1 = a.out_q; p.y2 = b.out_q;
     p.bias1 = a.bias; p.alpha_vec1 = a.alpha_vec; p.bias2 = b.bias; p.alpha_vec2 = b.alpha_vec;
     p.alpha1 = a.alpha; p.alpha2 = b.alpha; p.resid_scale = a.resid_scale; p.inv1 = a.out_inv_scale; p.inv2 = b.out_inv_scale;
-    p.relu = relu_codes(a.table, a.out_inv_scale, a.resid_scale) && relu_codes(b.table, b.out_inv_scale, 0.0f);
+    p.relu = relu;
     p.t1 = {a.table.k0, a.table.b0, a.table.k1, a.table.b1, a.table.tau};
     p.t2 = {b.table.k0, b.table.b0, b.table.k1, b.table.b1, b.table.tau};
     const size_t shmem = conv_chain_lds(a.K, a.N, b.N);

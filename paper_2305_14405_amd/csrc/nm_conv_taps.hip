@@ -151,7 +151,7 @@ int32_t launch_conv_taps(const GemmArgs& g, hipStream_t stream, bool* done)
     *done = false;
     const bool lines = g.has_table && g.table.two_seg && !g.table.clamp_input && !g.table.cellmap;
     if (gemm_switched() || !g.conv || g.cCin != 64 || g.N != 64 || g.cKw != 3 || g.K != 9 * 64 || g.cStride != 1 || g.cPad != 1 || g.cHo != g.cH || g.cWo != g.cW ||
-        !conv_taps_faster(g.M) || (g.has_table && !lines) || g.resid || !g.out_q || g.out_f32 || g.out_acc || g.dbg_seg || !aligned(g.A, 16) || !aligned(g.W, 16) ||
+        !conv_taps_faster(g.M, g.has_table != 0) || (g.has_table && !lines) || g.resid || !g.out_q || g.out_f32 || g.out_acc || g.dbg_seg || !aligned(g.A, 16) || !aligned(g.W, 16) ||
         !aligned(g.out_q, 16) || !aligned(g.bias, 4) || !aligned(g.alpha_vec, 4))
         return NM_OK;
     static std::once_flag once;

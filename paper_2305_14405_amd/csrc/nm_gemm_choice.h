@@ -351,21 +351,36 @@ constexpr int conv_chain_share(int K, int N1, int N2)
 //    64 ->  256 -> 128:  3136 8.1 | 8.6     12544 12.6 |  9.4    36000 13.6 | 14.0   100352 27.6 | 23.8   200704 42.2 | 34.8
 //   128 ->  512 -> 128: 12544 11.6 | 18.9   36000 20.7 | 20.2    50176 25.1 | 21.1    75000 34.8 | 36.4   131072 51.1 | 42.4
 //    64 -> 1024 ->  64: 12544 15.3 | 21.4   32000 26.3 | 23.0    36000 29.7 | 34.0    65536 40.9 | 34.9   200704 135  | 127
-inline bool conv_chain_faster(int M, int K, int N1, int N2)
+// Two-segment tables that are no ReLU (relu: relu_codes holds for both) take a vector instruction or two more per code, and in the one kernel a
+// loop without a ring: constants of their own, fitted to 87 and 204 such pairs (rms 3 to 5 % and 8 %).  Over the 126 that the others' constants
+// chain the choice is 1.3 % slower than the better one and never by more than 2.5 % slower than two kernels (all of them chained: 5 and 34 %);
+// 64 -> 512 -> 64 and wider gain nothing.  us, two kernels | one:
+//    64 ->  256 ->  64:  5000 9.0 | 10.4    12544 12.0 | 10.9    36000 14.2 | 16.5   100352 28.2 | 26.5   200704 45.2 | 42.0
+//    64 ->  256 -> 128:  5000 9.5 | 11.1    16000 11.0 | 11.9    45000 17.2 | 17.8    65536 22.5 | 19.6   131072 36.7 | 32.2
+//   128 ->  512 -> 128: 50176 30.2 | 29.2   58000 33.9 | 30.6    65536 36.6 | 31.7   115000 57.4 | 55.2
+//    64 ->  768 ->  64: 26000 23.5 | 26.5   58000 38.5 | 46.1   200704 130  | 156
+inline bool conv_chain_faster(int M, int K, int N1, int N2, bool relu)
 {
     const double m = M * 1e-6, bytes = m * (K + 2.0 * N1 + N2);
     const long blocks = ((long)M + 31) / 32;
-    const double apart = 6.0 + 0.2 * (bytes + m * N1), least = m * N1 > 1.2 ? 10.0 : 0.0;
     const double turns = (double)(K == 64 ? (blocks + 1023) / 1024 : (blocks + 2047) / 2048) * N1 / 256;
+    if (!relu) {
+        if (N2 == 64 && N1 != 256) return false;
+        const double apart = 7.5 + 0.225 * (bytes + m * N1), least = m * N1 > 3.0 ? 11.5 : 0.0;
+        const double one = K != 64 ? 8.02 + 6.49 * turns + 0.127 * bytes : N2 == 64 ? 6.76 + 3.26 * turns + 0.121 * bytes : 6.79 + 3.8 * turns + 0.12 * bytes;
+        return one < (apart > least ? apart : least);
+    }
+    const double apart = 6.0 + 0.2 * (bytes + m * N1), least = m * N1 > 1.2 ? 10.0 : 0.0;
     const double one = K != 64 ? 6.55 + 5.34 * turns + 0.097 * bytes : N2 == 64 ? 5.04 + 3.03 * turns + 0.05 * bytes : 5.31 + 3.45 * turns + 0.061 * bytes;
     return one < (apart > least ? apart : least);
 }
 
 // 3x3 convolutions of 64 channels (nm_conv_taps.hip), or the small-tile and the tile kernel: up to here the filter, which every workgroup
-// loads whole, costs more than the image read nine times.  us, those | this: 3136 positions 3.7 | 4.4, 6272 4.1 | 4.5, 10000 5.0 | 4.7,
-// 12544 5.2 | 4.8, 25088 8.1 | 5.1, 50176 7.5 | 6.4, 200704 17.2 | 14.0.
+// loads whole, costs more than the image read nine times.  us, those | this, ReLU: 3136 positions 3.7 | 4.4, 6272 4.1 | 4.5, 9000 5.0 | 4.8, 10000
+// 5.1 | 4.8, 12544 5.2 | 4.8, 25088 8.1 | 5.2, 50176 7.4 | 6.3, 200704 17.3 | 13.9; another table 10000 5.1 | 5.1, 16000 5.3 | 5.3, 20000 6.1 | 5.4; without
+// one, which takes the other table's code here, 9000 4.9 | 5.1, 12000 5.0 | 5.2, 16000 5.2 | 5.3, 18000 6.0 | 5.4, 200704 17.7 | 15.2.
 constexpr int kTapsWaves = 8;   // of a workgroup
-constexpr bool conv_taps_faster(int M) { return M >= 8192; }
+constexpr bool conv_taps_faster(int M, bool table) { return M >= (table ? 8192 : 16384); }
 
 // Tile rows per group of the tile order.  Workgroup i runs on XCD i % 8, and the kernels hand XCD x the
 // x-th eighth of the tile sequence, which walks groups of group_m tile rows column by column.  An

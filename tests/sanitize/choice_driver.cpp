@@ -196,6 +196,13 @@ static int layernorm_rows()
     return 0;
 }
 
+// 3x3 convolutions of 64 channels: on both sides of the lines.
+static int taps_lines()
+{
+    EXPECT(!conv_taps_faster(8191, true) && conv_taps_faster(8192, true) && !conv_taps_faster(16383, false) && conv_taps_faster(16384, false));
+    return 0;
+}
+
 // The tile of a product that makes the LayerNorm in front of it, and that its LDS, with the product's table, is what a CU has.
 static int layernorm_products()
 {
@@ -219,9 +226,9 @@ static int configurations(const char* kind, int n, char** v)
 {
     for (int i = 0; i + 3 < n; i += 4) {
         const int M = std::atoi(v[i]), N = std::atoi(v[i + 1]), K = std::atoi(v[i + 2]);
-        if (!std::strcmp(kind, "chain")) {   // M, K, N1, N2
+        if (!std::strncmp(kind, "chain", 5)) {   // M, K, N1, N2; chain_lines: tables that are no ReLU
             const int N2 = std::atoi(v[i + 3]);
-            std::printf("%d\n", conv_chain_built(N, K, N2) && conv_chain_faster(M, N, K, N2));
+            std::printf("%d\n", conv_chain_built(N, K, N2) && conv_chain_faster(M, N, K, N2, !std::strcmp(kind, "chain")));
         } else if (!std::strcmp(kind, "staged")) {
             const int align = std::atoi(v[i + 3]);
             const bool takes = (align < 16 || K % 64 != 0) && staged_faster(align, M, N, K, true, true, true, true);
@@ -235,7 +242,7 @@ static int configurations(const char* kind, int n, char** v)
 int main(int argc, char** argv)
 {
     if (argc > 2) return configurations(argv[1], argc - 2, argv + 2);
-    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows() || layernorm_products()) return 1;
+    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows() || layernorm_products() || taps_lines()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;
 }

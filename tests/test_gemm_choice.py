@@ -9,7 +9,7 @@ import sys
 
 import pytest
 
-from test_gpu_conv import CHAIN_CASES, LARGE_TILE_CASES
+from test_gpu_conv import CHAIN_CASES, CHAIN_LINES_CASES, LARGE_TILE_CASES
 from test_gpu_parity import STAGED_CASES
 from test_sanitizers import SAN, _run
 
@@ -60,6 +60,10 @@ def test_chained_convolutions_are_one_kernel(tmp_path):
     assert {(K, N2) for M, K, N1, N2 in CHAIN_CASES} == {(64, 64), (64, 128), (128, 128)}
     others = [(300, 64, 256, 64), (33000, 64, 256, 64), (70000, 128, 512, 128), (50003, 128, 512, 64), (50003, 64, 320, 64), (50003, 64, 256, 256), (50003, 128, 1024, 128)]
     assert _configurations(tmp_path, "chain", others) == [0] * len(others)
+    # tables that are no ReLU: later, by measured times
+    assert _configurations(tmp_path, "chain_lines", CHAIN_LINES_CASES) == [1] * len(CHAIN_LINES_CASES)
+    slower = [(5000, 64, 256, 64), (8000, 64, 256, 64), (36000, 64, 256, 64), (5000, 64, 256, 128), (20000, 64, 512, 64), (131072, 64, 512, 64), (45000, 64, 768, 64)]
+    assert _configurations(tmp_path, "chain_lines", slower) == [0] * len(slower)
 
 
 # A program of its own: the switch is read once per process.

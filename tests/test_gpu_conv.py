@@ -376,9 +376,9 @@ def test_neighbouring_convolutions(oracle, B, H, Cin, first, second, tie):
 
 @pytest.mark.parametrize("B,H,W,form", [
     (3, 56, 56, "relu"), (9, 31, 33, "relu"), (1, 1, 8193, "relu"), (1, 8200, 1, "relu"), (4100, 1, 2, "relu"), (911, 3, 3, "relu"), (22, 55, 57, "relu"),
-    (3, 53, 59, "lines"), (3, 53, 59, "nonfinite"), (3, 53, 59, "scalar"), (3, 53, 59, "none")])
+    (3, 53, 59, "lines"), (3, 53, 59, "nonfinite"), (3, 53, 59, "scalar"), (3, 53, 59, "none"), (6, 53, 59, "none"), (1, 1, 16385, "none")])
 def test_3x3_convolutions_of_64_channels(oracle, B, H, W, form):
-    """Stride 1, a border of 1, from 8192 positions on: images of one row, one column, fewer pixels than a block; a last block that is not
+    """Stride 1, a border of 1, from 8192 positions on (16384 without a table): images of one row, one column, fewer pixels than a block; a last block that is not
     full; more than one turn of the wavefronts (22 x 55 x 57); any two-segment table, none, columns whose sums are infinite or NaN."""
     g = np.random.default_rng(B + H + W)
     ot, tables = relu_tables(oracle)
@@ -403,10 +403,11 @@ def test_3x3_convolutions_of_64_channels(oracle, B, H, W, form):
 # that are one kernel (tests/test_gemm_choice.py holds them to its rule); forms at the smallest of each kernel
 CHAIN_CASES = [(5037, 64, 256, 64), (5037, 64, 256, 128), (50003, 128, 256, 128), (25089, 64, 512, 64), (100003, 64, 256, 64), (70003, 64, 256, 128),
                (131041, 128, 512, 128)]
+CHAIN_LINES_CASES = [(12551, 64, 256, 64), (58003, 64, 256, 128), (62003, 128, 256, 128)]   # with tables that are no ReLU
 
 
 @pytest.mark.parametrize("M,K,N1,N2,form", [(*c, "relu") for c in CHAIN_CASES] + [
-    (*c, form) for c in CHAIN_CASES[:3] for form in ("lines", "nonfinite", "scalar")] + [
+    (*c, form) for c in CHAIN_CASES[:3] for form in ("lines", "nonfinite", "scalar")] + [(*c, "lines") for c in CHAIN_LINES_CASES] + [
     (5037, 64, 256, 64, form) for form in ("over_x", "over_shortcut", "over_result", "over_bias", "apart")])
 def test_chained_convolutions(oracle, M, K, N1, N2, form):
     """nm_cnn_run on a 1x1 convolution with a shortcut and the 1x1 one behind it gives what the two steps by themselves give, to the
