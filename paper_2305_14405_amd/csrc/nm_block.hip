@@ -12,10 +12,11 @@
 // products (weights do not depend on the activations).  What bounds it is the latency of one slice's round
 // in a wavefront (wait, two LDS reads, two MFMAs, the next request: about 600 clocks), so wavefronts are
 // what hides it: with eight of them and rings twice as deep the stream ran at 43 bytes per ns and CU, with
-// sixteen at 65, of 128 that LDS-direct loads reach.  block_rows has both kinds' times.
+// sixteen at 65, of 128 that LDS-direct loads reach.  block_rows_faster has both kinds' times.
 #include <mutex>
 
 #include "nm_device.h"
+#include "nm_gemm_choice.h"
 
 namespace nm {
 
@@ -395,24 +396,12 @@ static int32_t launch_block(const BlockParams& p, size_t shmem, hipStream_t s)
     }
 }
 
-// Rows per workgroup for this layer, 0 when the separate kernels are the better choice (or the shape,
-// alignment or LDS space rules this kernel out).
-// 0: keep the separate kernels.  One workgroup runs on a CU, so up to 4096 rows 16 per workgroup are one round
-// of the chip and cost what 64 rows cost; beyond, 32 rows halve the rounds.  The cost of a round grows with
-// the weights (65 bytes per ns), that of the separate kernels with the rows: the lines below are where they cross.  us a layer of a
-// stack, heads of 64, F = 4 H, this kernel | separate ones, at 128 tokens a sequence:
-//   H = 128 (0.2 MB)   32 rows 14.1 | 17.8   8192 21.1 | 38.3       H = 320 (1.2 MB)  512 31.0 | 25.1   1024 31.2 | 30.2   1536 31.2 | 31.7
-//   H = 192 (0.4 MB)   32 18.1 | 16.6   512 19.9 | 19.4   768 20.2 | 22.2                 2048 31.6 | 34.6  12288 69.0 | 69.8
-//   H = 256 (0.8 MB)  512 22.9 | 20.8   768 23.0 | 23.6  1024 23.0 | 24.4                      H = 384 (1.8 MB) 1024 33.9 | 30.8   1536 34.1 | 34.3
-//                    8192 32.4 | 47.5  12288 52.3 | 64.0                                       2048 34.6 | 37.1   4096 36.0 | 40.0   6144 64.7 | 51.6
-//   H = 448 (2.4 MB) 1536 43.8 | 37.4  4096 48.3 | 47.1
+// Rows per workgroup for this layer, 0 when the separate kernels are the better choice (block_rows_faster) or the shape,
+// alignment or LDS space rules this kernel out.
 static int block_rows(BlockParams& p, size_t* shmem)
 {
-    if (p.H % 16 || p.F % 16 || p.M > 24576) return 0;
-    const long weights = (long)p.H * (p.H + 2L * p.F + 3 * p.H);
-    const int bm = p.M <= 4096 ? 16 : 32;
-    if (weights > (bm == 16 ? 1900000 : 1250000)) return 0;
-    if (p.M < (weights > 1250000 ? 1536 : weights > 1000000 ? 1300 : weights > 600000 ? 700 : weights > 250000 ? 600 : 0)) return 0;
+    const int bm = block_rows_faster(p.M, p.H, p.F);
+    if (!bm || p.H % 16 || p.F % 16) return 0;
     if (p.H > 16 * kBlockWaves * kBlockHold) return 0;   // the tiles that a wavefront holds in registers
     return block_layout(p, bm, shmem) ? bm : 0;
 }

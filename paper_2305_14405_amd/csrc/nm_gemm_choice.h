@@ -329,6 +329,26 @@ inline int qkv_attention_form(int B, int S, int heads, int K)
     return K > 384 ? QKV_ATTENTION_EIGHT : QKV_ATTENTION_FOUR;
 }
 
+// Rows per workgroup with which steps 5 to 9 of a layer (and step 1 of the next) are one kernel over blocks of rows (nm_block.hip), 0: the separate
+// kernels.  One workgroup runs on a CU, so up to 4096 rows 16 per workgroup are one round of the chip and cost what 64 rows cost;
+// beyond, 32 rows halve the rounds.  The cost of a round grows with the weights (65 bytes per ns), that of the separate kernels with the rows and,
+// little by little, with F: they cross at as many rows as 2.4 H^2 + 2 H F has thousands, earlier never below 0.37 million, later beyond 1.3.  Over 864
+// layers of stacks (H of 128 to 512, F of H to 8 H, 32 to 4096 rows) the choice is 0.05 % slower than the better one and 6 % at worst (by the
+// weights' number alone 0.9 and 23 %).  us a layer, heads of 64, this kernel | separate ones:
+//   H = 128  F 1024   128 rows 16.2 | 18.2   4096 18.1 | 33.1      H = 320  F  640   512 22.2 | 20.5    768 22.5 | 22.8   4096 26.7 | 37.2
+//   H = 192  F  384   128 15.8 | 16.8         768 16.1 | 18.8              F 1280  1024 29.7 | 28.5   1536 30.0 | 31.8   4096 32.9 | 40.1
+//            F  768   384 18.2 | 18.0         768 18.4 | 21.0      H = 384  F  768   768 25.0 | 25.0   1024 25.2 | 27.1   4096 29.5 | 38.8
+//   H = 256  F  512   256 17.4 | 17.1         768 17.9 | 19.9              F 1536  1024 32.8 | 30.2   1536 33.2 | 33.8   4096 36.4 | 39.3
+//            F 1024   512 20.7 | 19.3         768 20.9 | 21.3      H = 512  F 1024  2048 36.7 | 33.5   4096 40.7 | 37.2
+//   beyond 4096 rows (32 to a workgroup), F = 4 H: H = 256 8192 32.4 | 47.5, 12288 52.3 | 64.0; 320 12288 69.0 | 69.8; 384 6144 64.7 | 51.6
+inline int block_rows_faster(int M, int H, int F)
+{
+    const double h = H, weights = 4 * h * h + 2 * h * F, size = 2.4 * h * h + 2 * h * F;
+    if (M > 4096) return M <= 24576 && weights <= 1.25e6 ? 32 : 0;
+    const double rows = size < 0.37e6 ? 0.0 : 1e-3 * size + (size > 1.3e6 ? 1.5e-3 * (size - 1.3e6) : 0.0);
+    return weights <= 2e6 && M >= rows ? 16 : 0;
+}
+
 // Two 1x1 convolutions as one kernel (nm_conv_chain.hip): K to N1 channels with a shortcut, and those to N2, at M positions.
 constexpr int chain_waves(int K) { return K == 64 ? 4 : 8; }   // of a workgroup
 // LDS: both filters, scale and bias of both products' columns, a word per wavefront.

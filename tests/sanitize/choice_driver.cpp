@@ -196,6 +196,19 @@ static int layernorm_rows()
     return 0;
 }
 
+// Layers on both sides of the line between the kernel over blocks of rows and the separate ones, each with the faster kind.
+static int block_line()
+{
+    const struct { int M, H, F, rows; } layers[] = {
+        {32, 128, 512, 16}, {128, 128, 1024, 16}, {64, 192, 384, 16}, {320, 192, 768, 0}, {560, 192, 768, 16}, {256, 256, 512, 0}, {560, 256, 528, 16},
+        {512, 256, 1024, 0}, {768, 256, 1024, 16}, {512, 320, 640, 0}, {768, 320, 640, 16}, {768, 384, 768, 0}, {1024, 384, 768, 16}, {1024, 320, 1280, 0},
+        {1280, 256, 1600, 16}, {1024, 384, 1536, 0}, {4096, 384, 1536, 16}, {4096, 512, 1024, 0}, {4096, 512, 2048, 0}, {8192, 256, 1024, 32},
+        {24576, 128, 512, 32}, {24577, 128, 512, 0}, {6144, 384, 1536, 0}};
+    for (const auto& l : layers) EXPECT(block_rows_faster(l.M, l.H, l.F) == l.rows);
+    EXPECT(block_rows_faster((1 << 30) + 5, 4096, 65536) == 0 && block_rows_faster(1, 1, 1) == 16);
+    return 0;
+}
+
 // 3x3 convolutions of 64 channels: on both sides of the lines.
 static int taps_lines()
 {
@@ -242,7 +255,7 @@ static int configurations(const char* kind, int n, char** v)
 int main(int argc, char** argv)
 {
     if (argc > 2) return configurations(argv[1], argc - 2, argv + 2);
-    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows() || layernorm_products() || taps_lines()) return 1;
+    if (forced_values() || requirements() || staged_line() || group_rows() || layernorm_rows() || layernorm_products() || taps_lines() || block_line()) return 1;
     std::printf("SANITIZE_OK\n");
     return 0;
 }
