@@ -153,9 +153,7 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, Laye
     if (!d->Wqkv || !d->Wo || !d->W1 || !d->W2 || !d->gamma1 || !d->beta1 || !d->gamma2 || !d->beta2)
         return fail(NM_ERR_INVALID_ARG, "nm_encoder_layer: NULL weight or LayerNorm vector");
     DevTable t_gelu, t_exp, t_recip, t_rsqrt;
-    // the GELU table in its two-level form where it has one (FFN1's epilogue looks it up that way);
-    // the row kernels and the attention kernel read the expanded form of theirs
-    if ((rc = get_dev_table(d->tables, d->gelu_idx, &t_gelu, "nm_encoder_layer(gelu)", true))) return rc;
+    if ((rc = get_dev_table(d->tables, d->gelu_idx, &t_gelu, "nm_encoder_layer(gelu)"))) return rc;
     if ((rc = get_dev_table(d->tables, d->exp_idx, &t_exp, "nm_encoder_layer(exp)"))) return rc;
     if ((rc = get_dev_table(d->tables, d->recip_idx, &t_recip, "nm_encoder_layer(recip)"))) return rc;
     if ((rc = get_dev_table(d->tables, d->rsqrt_idx, &t_rsqrt, "nm_encoder_layer(rsqrt)"))) return rc;
@@ -255,7 +253,6 @@ static int32_t run_layer(const nm_layer_desc* d, const nm_layer_desc* next, Laye
         g.has_table = 1; g.table = t_gelu;
         g.out_inv_scale = d->inv_s_ffn1;
         g.ldo = F; g.out_q = ffn1;
-        g.table.cellmap = nullptr;   // (the expanded form, as launch_gemm takes for int8 results)
         const LnRows n{attn, d->gamma1, d->beta1, d->eps1, d->inv_s_ln1, t_rsqrt, ln1};
         const int tile = ln1_done ? -1 : ln_tile(n, g);
         if (tile >= 0) {
