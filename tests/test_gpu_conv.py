@@ -58,7 +58,10 @@ CASES = [  # B, H, W, Cin, Cout, kh, kw, stride, pad   (route)
 @pytest.mark.parametrize("B,H,W,Cin,Cout,kh,kw,stride,pad", [
     (1, 1, 1, 3, 16, 3, 3, 1, 1), (1, 1, 2, 2, 16, 3, 3, 1, 1), (2, 33, 35, 3, 64, 7, 7, 2, 3), (1, 17, 16, 4, 48, 3, 8, 1, 0),
     (3, 50, 61, 1, 16, 4, 5, 4, 2), (1, 40, 19, 2, 32, 9, 2, 3, 5), (2, 5, 5, 3, 64, 1, 3, 2, 0),
-    (2, 70, 150, 3, 64, 4, 8, 4, 2), (3, 19, 68, 4, 16, 2, 8, 4, 0), (1, 68, 65, 1, 32, 4, 6, 4, 1)])   # stride 4: patches of 68 columns
+    (2, 70, 150, 3, 64, 4, 8, 4, 2), (3, 19, 68, 4, 16, 2, 8, 4, 0), (1, 68, 65, 1, 32, 4, 6, 4, 1),   # stride 4: patches of 68 columns
+    # up to 1024 workgroups of 16x16 positions pack the filter themselves, beyond a kernel does
+    (256, 17, 20, 3, 16, 3, 3, 1, 1), (257, 17, 20, 3, 16, 3, 3, 1, 1), (1025, 5, 7, 1, 48, 2, 8, 1, 3), (1030, 9, 6, 4, 16, 5, 4, 2, 2),
+    (513, 40, 9, 2, 32, 9, 1, 1, 0), (600, 9, 33, 3, 64, 7, 7, 2, 3)])
 @pytest.mark.parametrize("table", ["relu", None])
 def test_conv2d_few_channels_int8_output(oracle, B, H, W, Cin, Cout, kh, kw, stride, pad, table):
     """The kernel for at most four input channels: the word that holds the tensor's last pixel, images smaller
@@ -421,6 +424,7 @@ def test_chained_convolutions(oracle, M, K, N1, N2, form):
     if form == "nonfinite":
         bias[0][[3, 77]] = np.nan, np.inf
         alpha[0][200], bias[1][17], alpha[1][60] = 3e38, -np.inf, np.nan
+    if form == "over_result": w2[:] = 0   # (rows of the second product read what others of it have written: its codes are those of its bias)
 
     def run(call):
         dx, dr, d1, d2 = dev(x), dev(r), dev(w1), dev(w2)
@@ -441,9 +445,11 @@ def test_chained_convolutions(oracle, M, K, N1, N2, form):
     ws = torch.empty(256, dtype=torch.uint8, device=DEV)
     got = run(lambda ops: nm.nm_cnn_run(ops, ws))
     want = run(lambda ops: (nm.nm_cnn_run(ops[:1], ws), nm.nm_cnn_run(ops[1:], ws)))
-    if form != "over_result":   # (rows of the second product read what others of it have written: any order is right)
-        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
-        assert 0.1 < np.mean(got[0] != 0) and len(np.unique(got[0])) > 20
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert 0.1 < np.mean(got[0] != 0) and len(np.unique(got[0])) > 20
+    if form == "over_result":   # the second result lies whole over the first
+        own = np.unique(got[1].reshape(M, N2), axis=0)
+        assert len(own) == 1 and len(np.unique(own)) > 10 and np.array_equal(got[0].reshape(-1)[M * N2:2 * M * N2].reshape(got[1].shape), got[1])
     if form == "relu" and M < 10000:
         ot = oracle.relu_table()
         q1 = oracle.conv2d_pwl(x, w1, 1, 0, bias=bias[0], alpha_vec=alpha[0], resid=r, resid_scale=0.01, table=ot, out_inv_scale=30.0)["q"]

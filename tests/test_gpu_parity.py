@@ -223,8 +223,7 @@ def test_elastic_tables_encoder_layer(oracle, label, flags, e_th, dk_th):
 
 
 def test_encoder_layer_two_level_gelu_table_headline_shape(oracle):
-    """The headline layer with merged tables in the two-level form: FFN1 looks its GELU table up in
-    two levels inside the large-tile kernel (the other kernels read the expanded form); every stage
+    """The headline layer with merged tables that are kept in two levels as well: its kernels read their expanded form; every stage
     equals the oracle's layer on the same merged tables."""
     want, got = run_layer(oracle, "bert_base_layer", elastic=(nm.NM_TABLE_MERGE | nm.NM_TABLE_COMPACT, 0.0, 0.01))
     for k in ("qkv", "ctx", "ln1", "ffn1", "y_q"):
@@ -281,8 +280,8 @@ def test_two_level_tables_pwl_apply(oracle, name, lo, hi, nprim, dk, clamp):
 
 @pytest.mark.parametrize("M,N,K", [(256, 384, 256), (70, 50, 96)])
 def test_two_level_table_gemm_epilogue(oracle, M, N, K):
-    """nm_gemm_pwl with a two-level GELU table (streaming and generic kernels): the same outputs as
-    the oracle's GEMM followed by its direct evaluation of the merged table."""
+    """nm_gemm_pwl with a GELU table kept in two levels, looked up in two steps (every output) and expanded (int8 alone): the same
+    outputs as the oracle's GEMM followed by its direct evaluation of the merged table."""
     lo, hi, nprim, dk = -8.0, 8.0, 128, 0.01
     mt = oracle.build_table_merged_direct(OID["gelu"], lo, hi, nprim, dk)
     te, _ = oracle.build_table_merged(OID["gelu"], lo, hi, nprim, dk)
@@ -308,10 +307,9 @@ def test_two_level_table_gemm_epilogue(oracle, M, N, K):
 
 @pytest.mark.parametrize("M,N,K,nprim,dk", [(4096, 3072, 768, 128, 0.01), (3900, 784, 512, 256, 0.001), (8192, 1024, 512, 1024, 0.002)])
 def test_two_level_table_in_the_tile_kernel_sampled(oracle, M, N, K, nprim, dk):
-    """int8 output through a two-level GELU table at shapes the large-tile kernel takes (256 x 192,
-    128 x 128 with ragged edges, 256 x 128; up to 1024 primary cells): its own epilogue looks the cell
-    byte up first and the merged segment's line second.  The oracle computes 64 sampled rows: its GEMM,
-    then its direct evaluation of the merged table."""
+    """int8 output through a GELU table kept in two levels at shapes the large-tile kernel takes (256 x 192,
+    128 x 128 with ragged edges, 256 x 128; up to 1024 primary cells), which reads its expanded form, in slots and not.
+    The oracle computes 64 sampled rows: its GEMM, then its direct evaluation of the merged table."""
     lo, hi = -8.0, 8.0
     mt = oracle.build_table_merged_direct(OID["gelu"], lo, hi, nprim, dk)
     te, _ = oracle.build_table_merged(OID["gelu"], lo, hi, nprim, dk)
@@ -1464,7 +1462,9 @@ def test_encoder_stack(oracle, name, n_layers):
     (1, 1, 16, 1, 16, 2, True), (3, 5, 48, 3, 80, 3, False), (1, 17, 64, 1, 272, 1, True), (2, 16, 160, 10, 144, 2, True),
     (1, 33, 256, 4, 1024, 2, True), (1024, 1, 320, 5, 1280, 1, True), (31, 33, 448, 7, 1792, 2, True),
     (1025, 4, 48, 3, 80, 2, True), (151, 32, 192, 3, 768, 1, False), (8200, 2, 32, 2, 32, 2, True), (129, 32, 320, 5, 1280, 2, True),
-    (100, 13, 320, 5, 1280, 2, True), (97, 16, 384, 6, 1536, 1, True), (47, 15, 256, 4, 1024, 2, True), (19, 32, 192, 3, 768, 2, True)])
+    (100, 13, 320, 5, 1280, 2, True), (97, 16, 384, 6, 1536, 1, True), (47, 15, 256, 4, 1024, 2, True), (19, 32, 192, 3, 768, 2, True),
+    # the widest layers and the largest F that the line leaves to the kernel
+    (119, 16, 384, 6, 1536, 1, True), (65, 32, 448, 7, 1104, 2, True), (73, 16, 512, 8, 512, 2, False), (37, 33, 256, 4, 2048, 2, True)])
 def test_encoder_block_kernel_edges(oracle, B, S, H, heads, F, n_layers, biases):
     """The kernel that runs everything behind attention for a block of rows: row remainders of 16 and
     32 per workgroup, widths that are no multiple of 128, more and fewer tiles than wavefronts, the ring
