@@ -30,7 +30,7 @@ PEAK_HBM_GBS = 8000.0     # MI355X HBM3E, published: 8 TB/s
 # build does not emit).  The fused attention kernel is bound by it: per score its loops execute 10.5
 # vector instructions (row max 0.5; subtract, scale 2; segment index: fma, fma, mask 3; k*t+b 1;
 # row-sum add 1; e*r 1; requantisation: multiply, convert-and-pack 2; the look-up itself not counted).
-# The fraction is that of these: what a wavefront issues once for all its scores comes on top (14.3 in
+# The fraction is that of these: what a wavefront issues once for all its scores comes on top (14.1 in
 # all at 512 keys, by counter).
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 ATTN_OPS_PER_SCORE = 10.5

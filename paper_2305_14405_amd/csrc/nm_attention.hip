@@ -22,7 +22,7 @@
 // of the eight rows addressed by lanes j / 8, j / 8 + 2, ...), with the row addresses chosen so
 // that the keys arrive in the order the probabilities have in the lanes.
 //
-// What bounds it: vector instructions (by counter 14.3 per score at 32 x 512 tokens and 16 heads, 10.5 of them in the loops over
+// What bounds it: vector instructions (by counter 14.1 per score at 32 x 512 tokens and 16 heads, 10.5 of them in the loops over
 // the scores), the matrix instructions, which the SIMD issues in their stead (16 clocks each, an eighth of the time), and
 // what is not hidden of loads and look-ups: without K's and V's loads the kernel takes 91 % of its time, without the
 // look-ups 91 %, without V's reads 92 %.  The instructions beyond the loops' are paid once per 16 queries and up to 256

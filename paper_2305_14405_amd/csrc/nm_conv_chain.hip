@@ -3,14 +3,15 @@
 // activation as a PWL table; arithmetic and order are those of the separate kernels, so results are bit-identical).
 //
 // What bounds it: memory (200704 positions of 64 -> 256 -> 64 channels move 128 MB, 25 us at a copy's rate), then a wavefront's chain of
-// products and vector instructions, which takes 0.5 us per 32 channels alone on a SIMD and hides behind two others.  The wide tensor is
-// written, since the next shortcut needs it, but not read again.  A wavefront takes 32 positions through both products by itself: the
-// widened 32 channels that a matrix instruction leaves in a lane's accumulators become, after two half swaps, the 16 bytes that the
-// second product's operand wants from that lane (and that are its piece of the output row), so neither LDS nor a barrier lies between
-// them.  LDS holds both filters whole, once per workgroup; the shortcut's next 256 channels are requested while the present ones are
-// worked on.  us, two kernels -> this one: 200704 positions of 64 -> 256 -> 64 channels 38.1 -> 29.6, -> 128 42.7 -> 34.5, 50176 of 128 -> 512
-// -> 128 25.3 -> 20.5; conv_chain_faster has the rest.  64 positions a wavefront, which halves the reads of scales and filters, was
-// slower (33.3), as was the next block's first product queued ahead (128 -> 512 -> 128 22.1) and 16 wavefronts a CU, which spill (36.4).
+// products and vector instructions, which takes 0.5 us per 32 channels alone on a SIMD and hides behind two others (by counter vector
+// instructions issue in 46 % of the cycles there, LDS is busy in 21 %, the matrix cores in 9 %).  The wide tensor is written, since the
+// next shortcut needs it, but not read again.  A wavefront takes 32 positions through both products by itself: the widened 32 channels that
+// a matrix instruction leaves in a lane's accumulators become, after two half swaps, the 16 bytes that the second product's operand wants
+// from that lane (and that are its piece of the output row), so neither LDS nor a barrier lies between them.  LDS holds both filters whole,
+// once per workgroup; the shortcut's next 256 channels are requested while the present ones are worked on.  us, two kernels -> this one:
+// 200704 positions of 64 -> 256 -> 64 channels 38.1 -> 29.6, -> 128 42.7 -> 34.5, 50176 of 128 -> 512 -> 128 25.3 -> 20.5;
+// conv_chain_faster has the rest.  64 positions a wavefront, which halves the reads of scales and filters, was slower (33.3), as was the
+// next block's first product queued ahead (128 -> 512 -> 128 22.1) and 16 wavefronts a CU, which spill (36.4).
 #include <mutex>
 
 #include "nm_device.h"

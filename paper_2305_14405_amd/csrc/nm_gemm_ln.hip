@@ -6,7 +6,8 @@
 // front of a product that takes 4.  Here eight wavefronts of a workgroup normalise BM / 8 rows each, a row at a time as in
 // layernorm_row_kernel, and write the codes as the A image of all slices to LDS, while eight others wait for the tile's weights: a
 // slice (128 bytes of K, which is at most 1024) of BN rows each, which they multiply then and whose partial tiles meet in LDS.  What
-// bounds it is latency: the rows' trip from memory, two reductions, and code that arrives as it is first run.  (With the weights
+// bounds it is latency: the rows' trip from memory, two reductions, and code that arrives as it is first run (by counter, 128 rows of 768 columns,
+// vector instructions issue in 29 % of the cycles, LDS is busy in 7 %, the matrix cores in 2 %).  (With the weights
 // requested by the wavefronts that normalise, the counter that tells them of gamma's and beta's arrival made them wait for the weights
 // too: 12 layers of width 768 over 128 tokens 310 us instead of 287, weights not in the caches; the kernels apart 305.)  Every column
 // tile repeats the work, so the kernel is for products of few rows (ln_gemm_tile, with what it measured); of 32 rows a

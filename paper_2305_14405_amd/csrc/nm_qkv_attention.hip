@@ -4,7 +4,8 @@
 // and V, whose codes go to LDS as the images that attention's wavefronts read; no tensor of them exists in memory.
 //
 // What bounds it: the operands' stream into LDS (40 KB a slice for 128 x 192 outputs, of 40 bytes per clock and CU), then
-// attention's vector instructions, which the other workgroup of a CU hides where there are two.  As two kernels the projection's
+// attention's vector instructions, which the other workgroup of a CU hides where there are two (by counter, 32 x 128 tokens and 12 heads,
+// vector instructions issue in 38 % of the cycles, the matrix cores run in 24 %, LDS is busy in 23 %).  As two kernels the projection's
 // prologue and epilogue, a launch, and Q, K and V on their way through memory come on top.  us a layer, two kernels -> this one:
 // 32 x 128 tokens of width 768 71.0 -> 68.4, 128 x 128 202 -> 191, 16 x 128 49.7 -> 47.3, 128 x 64 119 -> 114, 128 x 128 of width 1024
 // 302 -> 284, 64 x 128 of width 384 64.8 -> 59.5.  qkv_attention_form has the rest.
